@@ -33,6 +33,11 @@ class pcsr_params_t(ctypes.Structure):
     _fields_ += [("reserved", ctypes.c_int32 * 1)]
 
 
+class pcsr_epilogue_t(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("bias", "self", "self_eps", "mask")]
+    _fields_ += [("relu", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+
+
 class PcsrError(RuntimeError):
     def __init__(self, code: int, where: str):
         self.code = code
@@ -79,11 +84,18 @@ def _lib():
         lib.pcsr_strerror.argtypes = [ctypes.c_int]
         lib.pcsr_strerror.restype = ctypes.c_char_p
         lib.pcsr_last_hip_error.restype = ctypes.c_int
+        lib.pcsr_spmm_epilogue.argtypes = [vp, vp, vp, i32, ctypes.POINTER(pcsr_epilogue_t), vp]
+        lib.pcsr_gnn_workspace_floats.argtypes = [i32, i32]
+        lib.pcsr_gnn_workspace_floats.restype = i64
+        lib.pcsr_gnn_linear.argtypes = [i64, i32, i32, vp, vp, i32, vp, i32, vp, vp, vp, vp, vp, vp, vp]
+        lib.pcsr_gnn_wgrad.argtypes = [i64, i32, i32, vp, vp, vp, vp, vp, vp]
+        lib.pcsr_gnn_colsum.argtypes = [i64, i32, vp, vp, vp, vp]
         for name in ("pcsr_build", "pcsr_spmm", "pcsr_free", "pcsr_set_kernel_params",
                      "pcsr_query_launch", "pcsr_export", "pcsr_features", "pcsr_select",
                      "pcsr_window_stats", "pcsr_features_device", "pcsr_reorder", "pcsr_permute_csr",
                      "pcsr_transpose_csr", "pcsr_workspace_bytes", "pcsr_reserve_workspace", "pcsr_spmm_static",
-                     "pcsr_export_schedule", "pcsr_reorder_by_degree"):
+                     "pcsr_export_schedule", "pcsr_reorder_by_degree", "pcsr_spmm_epilogue", "pcsr_gnn_linear",
+                     "pcsr_gnn_wgrad", "pcsr_gnn_colsum"):
             getattr(lib, name).restype = ctypes.c_int
         _LIB = lib
     return _LIB

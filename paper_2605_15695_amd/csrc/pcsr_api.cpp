@@ -9,6 +9,7 @@
 
 #include "../../include/pcsr.h"
 #include "pcsr_build_gpu.h"
+#include "pcsr_gnn.h"
 #include "pcsr_host.h"
 #include "pcsr_kernels.h"
 
@@ -126,16 +127,21 @@ static int upload_long_panels(pcsr_handle_s *h, const int32_t *split_slot)
 }
 
 // Launch shape for width K under the handle's kernel parameters ("0 = auto" resolved).
-int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls)
+// epilogue: for pcsr_spmm_epilogue, whose kernels exist for the auto shapes only; a handle with
+// another shape of its own uses those.
+int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilogue = false)
 {
     if (K <= 0) return PCSR_E_UNSUPPORTED;
-    int vec = h->vec ? h->vec : (K % 4 == 0 ? 4 : (K % 2 == 0 ? 2 : 1));
+    const bool plain = h->host.win_cols == 0 && h->ipg <= 1;
+    const bool own = !(epilogue && plain && (h->lpr || h->vec || h->rep));
+    const int h_lpr = own ? h->lpr : 0, h_vec = own ? h->vec : 0, h_rep = own ? h->rep : 0;
+    int vec = h_vec ? h_vec : (K % 4 == 0 ? 4 : (K % 2 == 0 ? 2 : 1));
     // as pcsr_select: K of 9..16 is served by 16 lanes of one dword unless rows are very short
-    if (!h->vec && !h->lpr && K > 8 && K <= 16 && h->host.win_cols == 0 &&
+    if (!h_vec && !h_lpr && K > 8 && K <= 16 && h->host.win_cols == 0 &&
         h->host.nnz_v >= 8 * std::max<int64_t>(h->host.P, 1))
         vec = 1;
     if (K % vec != 0) return PCSR_E_UNSUPPORTED;
-    int lpr = h->lpr;
+    int lpr = h_lpr;
     if (!lpr) {
         int need = (K + vec - 1) / vec;
         if (h->host.win_cols > 0) {
@@ -148,7 +154,7 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls)
         lpr = 4;
         while (lpr < need && lpr < cap) lpr <<= 1;
     }
-    int rep = h->rep;
+    int rep = h_rep;
     if (!rep) {
         int need = (K + lpr * vec - 1) / (lpr * vec);
         rep = 1;
@@ -178,7 +184,9 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls)
         gx = h->n_win_blocks;
     } else {
         if (waves > 8) return PCSR_E_UNSUPPORTED;
-        if (!pcsr::kernel_exists(h->host.V, h->host.S, lpr, vec, rep, ipg)) return PCSR_E_UNSUPPORTED;
+        if (!(epilogue && ipg == 1 ? pcsr::epilogue_kernel_exists(h->host.V, h->host.S, lpr, vec, rep)
+                                   : pcsr::kernel_exists(h->host.V, h->host.S, lpr, vec, rep, ipg)))
+            return PCSR_E_UNSUPPORTED;
         const int64_t items_per_wg = (int64_t)waves * (64 / lpr) * ipg;
         if (h->flags & PCSR_FLAG_NO_XCD_REMAP) {
             gx = (h->host.M + items_per_wg - 1) / items_per_wg;
@@ -456,14 +464,15 @@ static int64_t workspace_need(pcsr_handle_t h, int32_t K)
 }
 
 // Checks shared by the SpMM entry points; resolves the launch shape.
-static int spmm_check(pcsr_handle_t h, const float *B, float *C, int32_t K, pcsr::LaunchShape *ls)
+static int spmm_check(pcsr_handle_t h, const float *B, float *C, int32_t K, pcsr::LaunchShape *ls,
+                      bool epilogue = false)
 {
     if (!valid(h)) return PCSR_E_INVALID_ARG;
     if (h->host_only) return PCSR_E_UNSUPPORTED;
     if (K <= 0) return PCSR_E_UNSUPPORTED;
     if (!C && h->host.n_rows > 0) return PCSR_E_INVALID_ARG;
     if (!B && h->host.n_cols > 0 && h->host.nnz_v > 0) return PCSR_E_INVALID_ARG;
-    int rc = resolve_launch(h, K, ls);
+    int rc = resolve_launch(h, K, ls, epilogue);
     if (rc != PCSR_OK) return rc;
     const uintptr_t align = 4u * (unsigned)ls->vec;
     if ((reinterpret_cast<uintptr_t>(B) % align) || (reinterpret_cast<uintptr_t>(C) % align))
@@ -484,7 +493,7 @@ static int spmm_check(pcsr_handle_t h, const float *B, float *C, int32_t K, pcsr
 // Enqueues the kernels of one SpMM.  ws: workspace of at least workspace_need(h, K) bytes
 // (ignored when that is 0).
 static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, const pcsr::LaunchShape &ls,
-                        float *ws, hipStream_t s)
+                        float *ws, hipStream_t s, const pcsr::Epilogue &epi = pcsr::Epilogue())
 {
     const bool two_pass = workspace_need(h, K) > 0;
     if (h->host.S && h->n_split > 0 && !two_pass) {
@@ -514,10 +523,11 @@ static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, co
     a.win_lo = h->d_win_lo;
     a.win_hi = h->d_win_hi;
     a.n_cols = (int32_t)h->host.n_cols;
+    a.epi = epi;
     if (!hip_ok(pcsr::launch_spmm(h->host.V, h->host.S, ls, a, s))) return PCSR_E_HIP;
     if (two_pass) {
         if (!hip_ok(pcsr::launch_reduce_split(h->d_split, h->d_split_slot, h->n_split, h->d_long, h->n_long, h->host.V, ws, C,
-                                              (int32_t)h->host.n_rows, K, s)))
+                                              (int32_t)h->host.n_rows, K, epi, s)))
             return PCSR_E_HIP;
     }
     return PCSR_OK;
@@ -557,6 +567,30 @@ int pcsr_spmm(pcsr_handle_t h, const float *B, float *C, int32_t K, void *stream
     rc = grow_workspace(h, workspace_need(h, K));
     if (rc != PCSR_OK) return rc;
     return spmm_enqueue(h, B, C, K, ls, h->d_ws, static_cast<hipStream_t>(stream));
+}
+
+int pcsr_spmm_epilogue(pcsr_handle_t h, const float *B, float *C, int32_t K, const pcsr_epilogue_t *epi,
+                       void *stream)
+{
+    if (!epi) return PCSR_E_INVALID_ARG;
+    pcsr::LaunchShape ls;
+    int rc = spmm_check(h, B, C, K, &ls, true);
+    if (rc != PCSR_OK) return rc;
+    const uintptr_t align = 4u * (unsigned)ls.vec;
+    if (reinterpret_cast<uintptr_t>(epi->self) % align || reinterpret_cast<uintptr_t>(epi->mask) % align)
+        return PCSR_E_INVALID_ARG;
+    if (h->n_split > 0 && (h->flags & PCSR_FLAG_ATOMIC_SPLIT)) return PCSR_E_UNSUPPORTED;
+    if (h->host.n_rows == 0) return PCSR_OK;
+    rc = grow_workspace(h, workspace_need(h, K));
+    if (rc != PCSR_OK) return rc;
+    pcsr::Epilogue e;
+    e.on = 1;
+    e.relu = epi->relu;
+    e.bias = epi->bias;
+    e.self = epi->self;
+    e.self_eps = epi->self_eps;
+    e.mask = epi->mask;
+    return spmm_enqueue(h, B, C, K, ls, h->d_ws, static_cast<hipStream_t>(stream), e);
 }
 
 int pcsr_spmm_static(pcsr_handle_t h, const float *B, float *C, int32_t K, void *stream)

@@ -6,6 +6,17 @@
 
 namespace pcsr {
 
+// What the write-back does to an element before it is stored (a GNN layer's elementwise tail,
+// see pcsr_gnn.h); off for a plain SpMM.
+struct Epilogue {
+    int32_t on = 0;
+    int32_t relu = 0;
+    const float *bias = nullptr;     // K
+    const float *self = nullptr;     // n_rows x K
+    const float *self_eps = nullptr; // one value
+    const float *mask = nullptr;     // n_rows x K
+};
+
 struct SpmmArgs {
     const int32_t *rowptr; // M+1, device
     const int32_t *colidx; // nnz_v, device
@@ -36,6 +47,7 @@ struct SpmmArgs {
     const int32_t *win_hi;    // window (an empty range when the block has none)
     int32_t win_cols;         // rows of B staged in LDS
     int32_t n_cols;
+    Epilogue epi;
 };
 
 // Resolved launch shape.
@@ -48,6 +60,8 @@ struct LaunchShape {
 };
 
 bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg);
+// with an epilogue (plain walk; the batched and window kernels take one at any shape)
+bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep);
 bool window_kernel_exists(int V, int lpr, int vec, int rep);
 
 // Enqueues the SpMM kernel <V,S,lpr,vec,rep> with `waves` wavefronts per workgroup.
@@ -68,7 +82,7 @@ constexpr int kLongPanelSlots = 64;
 constexpr int kLongReduceLanes = 16;
 hipError_t launch_reduce_split(const int32_t *split_panels, const int32_t *split_slot, int64_t n_split,
                                const int32_t *long_panels, int64_t n_long, int V, const float *ws, float *C,
-                               int32_t n_rows, int32_t K, hipStream_t stream);
+                               int32_t n_rows, int32_t K, const Epilogue &epi, hipStream_t stream);
 
 // Fixed workspace for callers that cannot allocate: one block of kStaticScratchBytes
 // bytes per GPU, part of the library's device image and held until the process ends.

@@ -77,6 +77,33 @@ template <int VEC> __device__ __forceinline__ void store_vec(float *p, const flo
     }
 }
 
+// Elementwise tail of a row of C, columns k .. k + VEC - 1.  One uniform branch for a plain SpMM.
+template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, long row, int K, int k, float (&v)[VEC])
+{
+    if (!ep.on) return;
+    if (ep.self) {
+        const float scale = 1.0f + (ep.self_eps ? *ep.self_eps : 0.0f);
+        float t[VEC];
+        load_vec<VEC>(ep.self + row * K + k, t);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = fmaf(scale, t[e], v[e]);
+    }
+    if (ep.bias) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] += ep.bias[k + e];
+    }
+    if (ep.relu) { // as written NaN stays NaN
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = v[e] <= 0.0f ? 0.0f : v[e];
+    }
+    if (ep.mask) {
+        float t[VEC];
+        load_vec<VEC>(ep.mask + row * K + k, t);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = t[e] <= 0.0f ? 0.0f : v[e];
+    }
+}
+
 // cacheable store: workspace partials are read back by the next kernel
 template <int VEC> __device__ __forceinline__ void store_vec_cached(float *p, const float (&s)[VEC])
 {
@@ -185,7 +212,9 @@ template <int LPR, bool CONST_LANE> __device__ __forceinline__ float bcast_any(f
     return __int_as_float(bcast_any<LPR, CONST_LANE>(__float_as_int(x), j));
 }
 
-template <int V, bool S, int LPR, int VEC, int REP>
+// EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
+// branch alone cost the instance <2, false, 64, 1, 2> 4 %.
+template <int V, bool S, int LPR, int VEC, int REP, bool EPI = false>
 __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
 {
     constexpr int G = 64 / LPR;
@@ -374,6 +403,7 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
             for (int r = 0; r < REP; ++r) {
                 if (kv[r]) {
                     if (sole) {
+                        if constexpr (EPI) finish<VEC>(a.epi, row, a.K, kc[r], acc[v][r]);
                         store_vec<VEC>(crow + kc[r], acc[v][r]);
                     } else if (wrow) {
                         store_vec_cached<VEC>(crow + kc[r], acc[v][r]);
@@ -520,7 +550,10 @@ __global__ void __launch_bounds__(512) spmm_batched_kernel(SpmmArgs a)
                     float *crow = a.C + row * K;
 #pragma unroll
                     for (int r = 0; r < REP; ++r)
-                        if (kv[r]) store_vec<VEC>(crow + kc[r], acc[i][v][r]);
+                        if (kv[r]) {
+                            finish<VEC>(a.epi, row, a.K, kc[r], acc[i][v][r]);
+                            store_vec<VEC>(crow + kc[r], acc[i][v][r]);
+                        }
                 }
             }
         }
@@ -802,7 +835,10 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                 float *crow = a.C + row * K + kbase;
 #pragma unroll
                 for (int r = 0; r < REP; ++r)
-                    if (kv[r]) store_vec<VEC>(crow + kl[r], acc[v][r]);
+                    if (kv[r]) {
+                        finish<VEC>(a.epi, row, a.K, kbase + kl[r], acc[v][r]);
+                        store_vec<VEC>(crow + kl[r], acc[v][r]);
+                    }
             }
         }
         item = item_next;
@@ -843,7 +879,8 @@ template <int VEC>
 __global__ void __launch_bounds__(256) reduce_split_kernel(const int32_t *__restrict__ split_panels,
                                                            const int32_t *__restrict__ split_slot,
                                                            long n_split, int V, const float *__restrict__ ws,
-                                                           float *C, int n_rows, int K, int skip_above)
+                                                           float *C, int n_rows, int K, int skip_above,
+                                                           Epilogue epi)
 {
     const int kv = K / VEC; // vectors per row
     const long total = n_split * V * (long)kv;
@@ -878,6 +915,7 @@ __global__ void __launch_bounds__(256) reduce_split_kernel(const int32_t *__rest
 #pragma unroll
         for (int e = 0; e < VEC; ++e) sum[e] += t1[e];
     }
+    finish<VEC>(epi, row, K, k, sum);
     store_vec<VEC>(C + row * K + k, sum);
 }
 
@@ -891,7 +929,7 @@ __global__ void __launch_bounds__(256) reduce_long_kernel(const int32_t *__restr
                                                           const int32_t *__restrict__ split_panels,
                                                           const int32_t *__restrict__ split_slot, int V,
                                                           const float *__restrict__ ws, float *C, int n_rows,
-                                                          int K)
+                                                          int K, Epilogue epi)
 {
     __shared__ float part[kLongReduceLanes][16][VEC];
     const int c = threadIdx.x % 16, j = threadIdx.x / 16;
@@ -933,6 +971,7 @@ __global__ void __launch_bounds__(256) reduce_long_kernel(const int32_t *__restr
         for (int jj = 1; jj < kLongReduceLanes; ++jj)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) sum[e] += part[jj][c][e];
+        finish<VEC>(epi, row, K, k, sum);
         store_vec<VEC>(C + row * K + k, sum);
     }
 }
@@ -972,6 +1011,45 @@ KernelFn pick(int V, int S, int lpr, int vec, int rep)
 {
     if (V == 1) return S ? pick_lpr<1, true>(lpr, vec, rep) : pick_lpr<1, false>(lpr, vec, rep);
     if (V == 2) return S ? pick_lpr<2, true>(lpr, vec, rep) : pick_lpr<2, false>(lpr, vec, rep);
+    return nullptr;
+}
+
+// the shapes resolve_launch arrives at when everything is left to it
+template <int V, bool S, int LPR, int VEC> KernelFn picke_rep(int rep)
+{
+    if (rep == 1) return &spmm_kernel<V, S, LPR, VEC, 1, true>;
+    if constexpr (!S && LPR == 64) {
+        if (rep == 2) return &spmm_kernel<V, S, LPR, VEC, 2, true>;
+        if (rep == 4) return &spmm_kernel<V, S, LPR, VEC, 4, true>;
+    }
+    return nullptr;
+}
+template <int V, bool S, int LPR> KernelFn picke_vec(int vec, int rep)
+{
+    switch (vec) {
+    case 1: return picke_rep<V, S, LPR, 1>(rep);
+    case 2: return picke_rep<V, S, LPR, 2>(rep);
+    case 4: return picke_rep<V, S, LPR, 4>(rep);
+    }
+    return nullptr;
+}
+template <int V, bool S> KernelFn picke_lpr(int lpr, int vec, int rep)
+{
+    switch (lpr) {
+    case 4: return picke_vec<V, S, 4>(vec, rep);
+    case 8: return picke_vec<V, S, 8>(vec, rep);
+    case 16: return picke_vec<V, S, 16>(vec, rep);
+    }
+    if constexpr (!S) {
+        if (lpr == 32) return picke_vec<V, S, 32>(vec, rep);
+        if (lpr == 64) return picke_vec<V, S, 64>(vec, rep);
+    }
+    return nullptr;
+}
+KernelFn pick_epilogue(int V, int S, int lpr, int vec, int rep)
+{
+    if (V == 1) return S ? picke_lpr<1, true>(lpr, vec, rep) : picke_lpr<1, false>(lpr, vec, rep);
+    if (V == 2) return S ? picke_lpr<2, true>(lpr, vec, rep) : picke_lpr<2, false>(lpr, vec, rep);
     return nullptr;
 }
 
@@ -1070,6 +1148,11 @@ bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg)
     return pick_any(V, S, lpr, vec, rep, ipg) != nullptr;
 }
 
+bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep)
+{
+    return pick_epilogue(V, S, lpr, vec, rep) != nullptr;
+}
+
 hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args, hipStream_t stream)
 {
     if (ls.grid_x <= 0 || ls.grid_y <= 0) return hipSuccess; // nothing to do
@@ -1097,7 +1180,8 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
         hipLaunchKernelGGL(fn, dim3(ls.grid_x, ls.grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);
         return hipGetLastError();
     }
-    KernelFn fn = pick_any(V, S, ls.lpr, ls.vec, ls.rep, ls.ipg);
+    KernelFn fn = args.epi.on && ls.ipg <= 1 ? pick_epilogue(V, S, ls.lpr, ls.vec, ls.rep)
+                                             : pick_any(V, S, ls.lpr, ls.vec, ls.rep, ls.ipg);
     if (!fn) return hipErrorInvalidValue;
     hipLaunchKernelGGL(fn, dim3(ls.grid_x, ls.grid_y), dim3(64 * ls.waves), 0, stream, args);
     return hipGetLastError();
@@ -1139,12 +1223,14 @@ hipError_t static_scratch(void **ptr)
 
 hipError_t launch_reduce_split(const int32_t *split_panels, const int32_t *split_slot, int64_t n_split,
                                const int32_t *long_panels, int64_t n_long, int V, const float *ws, float *C,
-                               int32_t n_rows, int32_t K, hipStream_t stream)
+                               int32_t n_rows, int32_t K, const Epilogue &epi, hipStream_t stream)
 {
     if (n_split <= 0) return hipSuccess;
     // 16-byte accesses need rows that start on 16-byte boundaries (the workspace always does)
     const bool aligned = K % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(ws) % 16 == 0;
+                         reinterpret_cast<uintptr_t>(ws) % 16 == 0 &&
+                         reinterpret_cast<uintptr_t>(epi.self) % 16 == 0 &&
+                         reinterpret_cast<uintptr_t>(epi.mask) % 16 == 0;
     const int vec = aligned ? 4 : 1;
     const long total = n_split * V * (long)(K / vec);
     const long blocks = (total + 255) / 256;
@@ -1152,10 +1238,10 @@ hipError_t launch_reduce_split(const int32_t *split_panels, const int32_t *split
     const int skip_above = n_long > 0 ? kLongPanelSlots : 0x7fffffff;
     if (vec == 4)
         hipLaunchKernelGGL(reduce_split_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, stream, split_panels,
-                           split_slot, (long)n_split, V, ws, C, n_rows, K, skip_above);
+                           split_slot, (long)n_split, V, ws, C, n_rows, K, skip_above, epi);
     else
         hipLaunchKernelGGL(reduce_split_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, stream, split_panels,
-                           split_slot, (long)n_split, V, ws, C, n_rows, K, skip_above);
+                           split_slot, (long)n_split, V, ws, C, n_rows, K, skip_above, epi);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n_long <= 0) return e;
     const int chunks = (K / vec + 15) / 16; // 16 vectors of C per workgroup
@@ -1163,10 +1249,10 @@ hipError_t launch_reduce_split(const int32_t *split_panels, const int32_t *split
     const dim3 grid((unsigned)(n_long * V), (unsigned)chunks);
     if (vec == 4)
         hipLaunchKernelGGL(reduce_long_kernel<4>, grid, dim3(16 * kLongReduceLanes), 0, stream, long_panels,
-                           split_panels, split_slot, V, ws, C, n_rows, K);
+                           split_panels, split_slot, V, ws, C, n_rows, K, epi);
     else
         hipLaunchKernelGGL(reduce_long_kernel<1>, grid, dim3(16 * kLongReduceLanes), 0, stream, long_panels,
-                           split_panels, split_slot, V, ws, C, n_rows, K);
+                           split_panels, split_slot, V, ws, C, n_rows, K, epi);
     return hipGetLastError();
 }
 

@@ -2,12 +2,14 @@
 Section 6.5): an autograd function whose forward is C = A*B and whose backward is
 dB = A^T * dC, both through pcsr_spmm, plus minimal GCN / GIN layers built on it.
 
-torch supplies tensors, streams, the dense weight GEMMs and the optimiser; every sparse
-product runs in the library's kernels.
+torch supplies tensors, streams, the loss and the optimiser; every sparse product runs in the
+library's kernels, and so do the dense products of layers up to MAX_WIDTH features wide with
+what surrounds them (bias, ReLU, its backward, the gradient sums): see FusedLayers.
 """
 from __future__ import annotations
 
-import numpy as np
+import ctypes
+
 import torch
 
 from . import binding as pc
@@ -72,6 +74,241 @@ class SpMMFunction(torch.autograd.Function):
         return op._run(op.bwd, op.n_cols, dC), None
 
 
+# widest layer side the library's dense kernels take
+MAX_WIDTH = 128
+
+
+class _Dense:
+    """The library's dense kernels on one device and stream, with a workspace for their sums."""
+
+    def __init__(self, X: torch.Tensor, widths):
+        self.lib = pc._lib()
+        self.stream = torch.cuda.current_stream(X.device).cuda_stream
+        self.device = X.device
+        floats = max(self.lib.pcsr_gnn_workspace_floats(a, b) for a, b in widths)
+        self.ws_floats, self._ws = floats, None
+
+    @property
+    def ws(self):
+        if self._ws is None:
+            self._ws = torch.empty(self.ws_floats, dtype=torch.float32, device=self.device)
+        return self._ws.data_ptr()
+
+    def new(self, *shape):
+        return torch.empty(shape, dtype=torch.float32, device=self.device)
+
+    @staticmethod
+    def _check(rc, where):
+        if rc != pc.PCSR_OK:
+            raise pc.PcsrError(rc, where)
+
+    def linear(self, X, W, transposed=False, bias=None, relu=False, mask=None, aux=None, dot=None, colsum=None,
+               store=True):
+        """X * W^T (transposed: X * W) + bias, ReLU, sum(. * aux) into dot, mask, column sums."""
+        n, a = X.shape
+        b = W.shape[1] if transposed else W.shape[0]
+        Y = self.new(n, b) if store else None
+        self._check(self.lib.pcsr_gnn_linear(
+            n, a, b, X.data_ptr(), W.data_ptr(), int(transposed), _p(bias), int(relu), _p(mask), _p(aux), _p(Y),
+            _p(colsum), _p(dot), self.ws if colsum is not None or dot is not None else None, self.stream),
+            "pcsr_gnn_linear")
+        return Y
+
+    def wgrad(self, G, X, bias=False):
+        """(G^T X, column sums of G or None)"""
+        dW = self.new(G.shape[1], X.shape[1])
+        db = self.new(G.shape[1]) if bias else None
+        self._check(self.lib.pcsr_gnn_wgrad(G.shape[0], X.shape[1], G.shape[1], G.data_ptr(), X.data_ptr(),
+                                            dW.data_ptr(), _p(db), self.ws, self.stream), "pcsr_gnn_wgrad")
+        return dW, db
+
+    def colsum(self, G):
+        out = self.new(G.shape[1])
+        self._check(self.lib.pcsr_gnn_colsum(G.shape[0], G.shape[1], G.data_ptr(), out.data_ptr(), self.ws,
+                                             self.stream), "pcsr_gnn_colsum")
+        return out
+
+    def spmm(self, handle, n_out, X, bias=None, relu=False, self_term=None, eps=None, mask=None):
+        out = self.new(n_out, X.shape[1])
+        if bias is None and self_term is None and mask is None and not relu:
+            rc = self.lib.pcsr_spmm(handle.raw, X.data_ptr(), out.data_ptr(), X.shape[1], self.stream)
+        else:
+            epi = pc.pcsr_epilogue_t(_p(bias), _p(self_term), _p(eps), _p(mask), int(relu), 0)
+            rc = self.lib.pcsr_spmm_epilogue(handle.raw, X.data_ptr(), out.data_ptr(), X.shape[1], ctypes.byref(epi),
+                                             self.stream)
+        self._check(rc, "pcsr_spmm")
+        return out
+
+
+def _p(t):
+    return None if t is None else t.data_ptr()
+
+
+class FusedLayers(torch.autograd.Function):
+    """Forward and backward of a chain of GCN / GIN layers with ReLU between them as one autograd
+    node.  Knowing the neighbours of an operation saves the passes that the one-by-one form
+    spends on elementwise work: bias and ReLU are applied where the product is stored, the
+    backward ReLU mask where the gradient is, (1 + eps) H is added in the aggregation, and
+    the bias gradients are summed by the kernel that has the gradient in registers.
+
+    ``chain``: list of (layer, ReLU follows); the last entry has none.  ``params``: the layers'
+    parameters in the order of ``_params``."""
+
+    @staticmethod
+    def forward(ctx, chain, X, *params):
+        d = _Dense(X, [(1, 1)])
+        H, keep, at = X.contiguous(), [], 0
+        for layer, relu in chain:
+            op = layer.op
+            if isinstance(layer, GCNLayer):
+                W = params[at]
+                b = params[at + 1] if layer.bias is not None else None
+                at += 1 + (b is not None)
+                if W.shape[1] >= W.shape[0]:
+                    keep.append(H)
+                    H = d.spmm(op.fwd, op.n_rows, d.linear(H, W), bias=b, relu=relu)
+                else:
+                    A = d.spmm(op.fwd, op.n_rows, H)
+                    keep += [H, A]
+                    H = d.linear(A, W, bias=b, relu=relu)
+            else:
+                eps, W1, b1, W2, b2 = params[at:at + 5]
+                at += 5
+                A = d.spmm(op.fwd, op.n_rows, H, self_term=H, eps=eps)
+                Z = d.linear(A, W1, bias=b1, relu=True)
+                keep += [H, A, Z]
+                H = d.linear(Z, W2, bias=b2, relu=relu)
+        ctx.chain = chain
+        ctx.n_params = len(params)
+        ctx.save_for_backward(*params, *keep)
+        return H
+
+    @staticmethod
+    @torch.autograd.function.once_differentiable
+    def backward(ctx, dOut):
+        saved = ctx.saved_tensors
+        params, keep = saved[:ctx.n_params], list(saved[ctx.n_params:])
+        d = _Dense(dOut, [tuple(p.shape) for p in params if p.dim() == 2])
+        grads = [None] * ctx.n_params
+        need = ctx.needs_input_grad[2:]
+        G, db = dOut.contiguous(), None  # gradient at the layer's output, its column sums if known
+        at = ctx.n_params
+        for i in range(len(ctx.chain) - 1, -1, -1):
+            layer = ctx.chain[i][0]
+            op = layer.op
+            need_dH = i > 0 or ctx.needs_input_grad[1]
+            masked = i > 0 and ctx.chain[i - 1][1]
+            # the layer before wants the column sums of its output gradient for its bias, unless
+            # its weight gradient reads that gradient anyway
+            sums = i > 0 and _linear_first(ctx.chain[i - 1][0]) and ctx.chain[i - 1][0].bias is not None
+            if isinstance(layer, GCNLayer):
+                has_b = layer.bias is not None
+                at -= 1 + has_b
+                W = params[at]
+                if W.shape[1] >= W.shape[0]:
+                    H = keep.pop()
+                    if has_b and need[at + 1]:
+                        grads[at + 1] = db if db is not None else d.colsum(G)
+                    db = None
+                    if need[at] or need_dH:
+                        U = d.spmm(op.bwd, op.n_cols, G)
+                        if need[at]:
+                            grads[at] = d.wgrad(U, H)[0]
+                        if need_dH:
+                            db = d.new(W.shape[1]) if sums else None
+                            G = d.linear(U, W, transposed=True, mask=H if masked else None, colsum=db)
+                else:
+                    A, H = keep.pop(), keep.pop()
+                    if need[at] or (has_b and need[at + 1]):
+                        grads[at], s = d.wgrad(G, A, bias=has_b)
+                        if has_b:
+                            grads[at + 1] = s
+                    db = None
+                    if need_dH:
+                        G = d.spmm(op.bwd, op.n_cols, d.linear(G, W, transposed=True), mask=H if masked else None)
+            else:
+                at -= 5
+                eps, W1, b1, W2, b2 = params[at:at + 5]
+                Z, A, H = keep.pop(), keep.pop(), keep.pop()
+                if need[at + 3] or need[at + 4]:
+                    grads[at + 3], grads[at + 4] = d.wgrad(G, Z, bias=True)
+                G1 = d.linear(G, W2, transposed=True, mask=Z)
+                if need[at + 1] or need[at + 2]:
+                    grads[at + 1], grads[at + 2] = d.wgrad(G1, A, bias=True)
+                db = None
+                if need[at] or need_dH:
+                    if need[at]:
+                        grads[at] = torch.empty_like(eps)
+                    dA = d.linear(G1, W1, transposed=True, aux=H if need[at] else None, dot=grads[at], store=need_dH)
+                    if need_dH:
+                        G = d.spmm(op.bwd, op.n_cols, dA, self_term=dA, eps=eps, mask=H if masked else None)
+        return (None, G if ctx.needs_input_grad[1] else None,
+                *(g if n else None for g, n in zip(grads, need)))
+
+
+def _linear_first(layer):
+    """Whether a GCN layer multiplies by its weights before it aggregates."""
+    return isinstance(layer, GCNLayer) and layer.lin.in_features >= layer.lin.out_features
+
+
+def _params(layer):
+    """Parameters of a layer in the order FusedLayers takes them, None if they are not what it
+    knows (modules exchanged or hooked, other types or devices, too wide)."""
+    if type(layer) is GCNLayer:
+        lins, own = [layer.lin], [layer.lin]
+        ps = [layer.lin.weight] if layer.bias is None else [layer.lin.weight, layer.bias]
+        if layer.lin.bias is not None:
+            return None
+    elif type(layer) is GINLayer:
+        mlp = layer.mlp
+        if len(mlp) != 3 or type(mlp[1]) is not torch.nn.ReLU:
+            return None
+        lins, own = [mlp[0], mlp[2]], [mlp, mlp[0], mlp[1], mlp[2]]
+        if any(type(m) is not torch.nn.Linear or m.bias is None for m in lins):
+            return None
+        ps = [layer.eps, mlp[0].weight, mlp[0].bias, mlp[2].weight, mlp[2].bias]
+    else:
+        return None
+    if not isinstance(layer.op, PcsrOperator) or any(type(m) is not torch.nn.Linear for m in lins):
+        return None
+    if any(_hooked(m) for m in own):
+        return None
+    for m in lins:
+        if m.in_features > MAX_WIDTH or m.out_features > MAX_WIDTH:
+            return None
+    for p in ps:
+        if p.dtype != torch.float32 or not p.is_cuda or not p.is_contiguous():
+            return None
+    return ps
+
+
+def _hooked(m):
+    return bool(m._forward_hooks or m._forward_pre_hooks or m._backward_hooks or m._backward_pre_hooks)
+
+
+def _run_fused(chain, X):
+    """The chain through FusedLayers, or None where that does not apply."""
+    if not isinstance(X, torch.Tensor) or X.dim() != 2 or X.dtype != torch.float32 or not X.is_cuda:
+        return None
+    if torch.is_autocast_enabled():
+        return None
+    params, n, width = [], X.shape[0], X.shape[1]
+    for layer, _ in chain:
+        ps = _params(layer)
+        if ps is None:
+            return None
+        first, last = (layer.lin, layer.lin) if type(layer) is GCNLayer else (layer.mlp[0], layer.mlp[2])
+        if n != layer.op.n_cols or width != first.in_features or any(p.device != X.device for p in ps):
+            return None
+        if type(layer) is GINLayer and layer.op.n_rows != n:
+            return None
+        n, width = layer.op.n_rows, last.out_features
+        params += ps
+    if n == 0 or X.shape[0] == 0:
+        return None
+    return FusedLayers.apply(chain, X, *params)
+
+
 class GCNLayer(torch.nn.Module):
     """H' = A_hat (H W) + b, the graph convolution of Kipf & Welling with a pre-normalised
     adjacency operator; the dense product comes first when it narrows the features."""
@@ -83,6 +320,9 @@ class GCNLayer(torch.nn.Module):
         self.bias = torch.nn.Parameter(torch.zeros(d_out)) if bias else None
 
     def forward(self, H):
+        out = _run_fused([(self, False)], H)
+        if out is not None:
+            return out
         if self.lin.in_features >= self.lin.out_features:
             out = self.op(self.lin(H))
         else:
@@ -101,7 +341,27 @@ class GINLayer(torch.nn.Module):
                                        torch.nn.Linear(d_out, d_out))
 
     def forward(self, H):
-        return self.mlp((1.0 + self.eps) * H + self.op(H))
+        out = _run_fused([(self, False)], H)
+        return out if out is not None else self.mlp((1.0 + self.eps) * H + self.op(H))
+
+
+class LayerChain(torch.nn.Sequential):
+    """Graph layers with ReLU between them, run as one chain where FusedLayers applies and module
+    by module otherwise (other operators, data types or devices, hooks, wide layers)."""
+
+    def forward(self, X):
+        mods = list(self)
+        chain = []
+        for i, m in enumerate(mods):
+            if type(m) is torch.nn.ReLU and chain and not chain[-1][1] and i + 1 < len(mods):
+                chain[-1] = (chain[-1][0], True)
+            else:
+                chain.append((m, False))
+            if _hooked(m):
+                chain = []
+                break
+        out = _run_fused(chain, X) if chain else None
+        return out if out is not None else super().forward(X)
 
 
 def make_model(kind: str, op: PcsrOperator, d_in: int, hidden: int, d_out: int, n_layers: int = 5):
@@ -114,4 +374,4 @@ def make_model(kind: str, op: PcsrOperator, d_in: int, hidden: int, d_out: int, 
         mods.append(layer(op, dims[i], dims[i + 1]))
         if i + 1 < n_layers:
             mods.append(torch.nn.ReLU())
-    return torch.nn.Sequential(*mods)
+    return LayerChain(*mods)

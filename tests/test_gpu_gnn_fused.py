@@ -1,0 +1,136 @@
+"""The fused GNN layers on the GPU: each dense kernel and the SpMM epilogue against fp64 torch at
+the edges of their tiles, and whole models against the same model on a dense adjacency."""
+import numpy as np
+import pytest
+
+import paper_2605_15695_amd as pc
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _close(got, ref, tol=1e-5):
+    err = float((got.double() - ref).norm() / ref.norm().clamp_min(1e-30))
+    assert err < tol, err
+
+
+def _dense(a, b):
+    from paper_2605_15695_amd.gnn import _Dense
+    return _Dense(torch.empty(1, device="cuda"), [(a, b)])
+
+
+# widths: whole tiles, part tiles, odd (no vector loads), one column, the widest
+@pytest.mark.parametrize("a,b", [(16, 64), (64, 64), (64, 16), (24, 48), (96, 32), (128, 128), (33, 7), (1, 1), (47, 65),
+                                 (128, 20), (6, 100)])
+@pytest.mark.parametrize("n", [1, 31, 257, 70001])
+def test_dense_kernels(a, b, n):
+    g = torch.Generator(device="cuda").manual_seed(a * 1000 + b)
+    X, G, aux = (torch.randn(n, w, generator=g, device="cuda") for w in (a, b, b))
+    W, bias = torch.randn(b, a, generator=g, device="cuda"), torch.randn(b, generator=g, device="cuda")
+    mask = torch.where(torch.rand(n, b, generator=g, device="cuda") < 0.5, 0.0, 1.0)
+    d = _dense(a, b)
+    Xd, Wd = X.double(), W.double()
+    lin = Xd @ Wd.t()
+    _close(d.linear(X, W), lin)
+    _close(d.linear(X, W, bias=bias, relu=True), torch.relu(lin + bias.double()))
+    csum, dot = torch.empty(b, device="cuda"), torch.empty((), device="cuda")
+    Wt = W.t().contiguous()
+    Y = d.linear(X, Wt, transposed=True, mask=mask, aux=aux, dot=dot, colsum=csum)
+    _close(Y, lin * mask.double())
+    size = Xd.abs() @ Wd.abs().t()                  # what the rounding errors scale with
+    scale = size.sum(0)
+    assert bool(((csum.double() - (lin * mask.double()).sum(0)).abs() <= 1e-6 * scale + 1e-30).all())
+    total = (size * aux.double().abs()).sum()
+    assert abs(float(dot.double() - (lin * aux.double()).sum())) <= 1e-6 * float(total)
+    dW, db = d.wgrad(G, X, bias=True)
+    ref = G.double().t() @ Xd
+    bound = G.double().abs().t() @ Xd.abs()
+    assert bool(((dW.double() - ref).abs() <= 1e-6 * bound).all())
+    gb = G.double().abs().sum(0)
+    assert bool(((db.double() - G.double().sum(0)).abs() <= 1e-6 * gb).all())
+    assert bool(((d.colsum(G).double() - G.double().sum(0)).abs() <= 1e-6 * gb).all())
+
+
+@pytest.mark.parametrize("name,kw", [("rmat20", dict(V=1, S=1, SG=4)), ("rmat20", dict(V=2, S=0)),
+                                     ("sbm", dict(V=1, col_window=512)), ("road", dict(V=2, items_per_group=2)),
+                                     ("rmat22", dict(V=2, S=1, SG=2))])
+@pytest.mark.parametrize("K", [16, 33])
+def test_spmm_epilogue(name, kw, K):
+    g = synth.workload(name, "small")
+    h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, pc.make_params(**kw))
+    B = torch.from_numpy(synth.dense_operand(g.n_cols, K, "normal", 3)).cuda()
+    own = torch.from_numpy(synth.dense_operand(g.n_rows, K, "normal", 4)).cuda()
+    mask = torch.from_numpy(synth.dense_operand(g.n_rows, K, "normal", 5)).cuda()
+    bias = torch.from_numpy(synth.dense_operand(1, K, "normal", 6)).cuda().reshape(-1)
+    eps = torch.tensor(0.25, device="cuda")
+    d = _dense(1, 1)
+    plain = d.spmm(h, g.n_rows, B)
+    _close(d.spmm(h, g.n_rows, B, bias=bias, relu=True), torch.relu(plain.double() + bias.double()), 1e-6)
+    _close(d.spmm(h, g.n_rows, B, self_term=own, eps=eps, mask=mask),
+           torch.where(mask <= 0, 0.0, plain.double() + 1.25 * own.double()), 1e-6)
+
+
+@pytest.mark.parametrize("kind", ["gcn", "gin"])
+@pytest.mark.parametrize("dims", [(16, 32, 16, 5), (8, 20, 24, 3), (64, 64, 16, 2), (7, 33, 5, 3), (16, 16, 16, 1)])
+@pytest.mark.parametrize("x_grad", [False, True])
+def test_models_match_dense_adjacency(kind, dims, x_grad):
+    import scipy.sparse as sp
+
+    from paper_2605_15695_amd import gnn
+
+    d_in, hidden, d_out, layers = dims
+    g = synth.workload("poisson", "small")
+    op = gnn.PcsrOperator(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, K_hint=hidden)
+    torch.manual_seed(1)
+    model = gnn.make_model(kind, op, d_in, hidden, d_out, layers).cuda()
+    X = torch.from_numpy(synth.dense_operand(g.n_rows, d_in, "normal", 9)).cuda().requires_grad_(x_grad)
+    calls = []
+    out = model(X)
+    assert type(out.grad_fn).__name__ == "FusedLayersBackward"
+    out.square().mean().backward()
+    A = torch.from_numpy(sp.csr_matrix((g.vals, g.colidx, g.rowptr), shape=(g.n_rows, g.n_cols)).toarray()
+                         .astype(np.float64))
+
+    class DenseOp:
+        def __call__(self, H):
+            calls.append(1)
+            return A @ H
+
+    ref = gnn.make_model(kind, DenseOp(), d_in, hidden, d_out, layers).double()
+    ref.load_state_dict({k: v.double().cpu() for k, v in model.state_dict().items()})
+    Xr = X.detach().double().cpu().requires_grad_(x_grad)
+    r = ref(Xr)
+    r.square().mean().backward()
+    assert len(calls) == layers
+    _close(out.cpu(), r.detach(), 1e-4)
+    for p, q in zip(model.parameters(), ref.parameters()):
+        _close(p.grad.cpu(), q.grad, 1e-3)
+    if x_grad:
+        _close(X.grad.cpu(), Xr.grad, 1e-3)
+
+
+def test_hooked_or_wide_models_run_module_by_module():
+    from paper_2605_15695_amd import gnn
+
+    g = synth.workload("poisson", "small")
+    op = gnn.PcsrOperator(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, K_hint=32)
+    X = torch.from_numpy(synth.dense_operand(g.n_rows, 16, "normal", 9)).cuda()
+    model = gnn.make_model("gcn", op, 16, 32, 16, 3).cuda()
+    plain = model(X)
+    seen = []
+    model[1].register_forward_hook(lambda m, i, o: seen.append(o.shape))
+    out = model(X)
+    assert seen == [(g.n_rows, 32)]
+    _close(out.detach(), plain.detach().double(), 1e-5)
+    wide = gnn.make_model("gin", op, 16, 160, 16, 2).cuda()
+    wide(X).sum().backward()
+    assert all(p.grad is not None for p in wide.parameters())
+
+
+def test_epilogue_on_a_handle_with_a_shape_of_its_own():
+    g = synth.workload("sbm", "small")
+    h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, pc.make_params(lanes_per_row=16, vec=1, rep=2))
+    B = torch.from_numpy(synth.dense_operand(g.n_cols, 32, "normal", 3)).cuda()
+    d = _dense(1, 1)
+    _close(d.spmm(h, g.n_rows, B, relu=True), torch.relu(d.spmm(h, g.n_rows, B).double()), 1e-6)
