@@ -12,6 +12,7 @@
 #include "pcsr_gnn.h"
 #include "pcsr_host.h"
 #include "pcsr_kernels.h"
+#include "pcsr_pool.h"
 
 namespace {
 
@@ -75,20 +76,11 @@ inline bool valid(pcsr_handle_t h) { return h && h->magic == kMagic; }
 
 void release_device(pcsr_handle_t h)
 {
-    if (h->d_rowptr) (void)hipFree(h->d_rowptr);
-    if (h->d_colidx) (void)hipFree(h->d_colidx);
-    if (h->d_val) (void)hipFree(h->d_val);
-    if (h->d_trow) (void)hipFree(h->d_trow);
-    if (h->d_split) (void)hipFree(h->d_split);
-    if (h->d_item_slot) (void)hipFree(h->d_item_slot);
-    if (h->d_sched) (void)hipFree(h->d_sched);
-    if (h->d_split_slot) (void)hipFree(h->d_split_slot);
-    if (h->d_long) (void)hipFree(h->d_long);
-    if (h->d_win) (void)hipFree(h->d_win);
-    if (h->d_win_ptr) (void)hipFree(h->d_win_ptr);
-    if (h->d_win_lo) (void)hipFree(h->d_win_lo);
-    if (h->d_win_hi) (void)hipFree(h->d_win_hi);
-    if (h->d_ws) (void)hipFree(h->d_ws);
+    void *const all[] = {h->d_rowptr, h->d_colidx,     h->d_val,  h->d_trow, h->d_split,   h->d_item_slot, h->d_sched,
+                         h->d_split_slot, h->d_long, h->d_win,  h->d_win_ptr, h->d_win_lo, h->d_win_hi, h->d_ws};
+    // the blocks are handed out again at once, so nothing may still be using them
+    const bool idle = h->device >= 0 && pcsr::pool_quiesce(h->device);
+    for (void *p : all) idle ? pcsr::pool_free(p) : pcsr::pool_release(p);
     h->d_rowptr = h->d_colidx = h->d_trow = h->d_split = h->d_win = nullptr;
     h->d_item_slot = h->d_sched = h->d_split_slot = h->d_long = h->d_win_ptr = nullptr;
     h->d_win_lo = h->d_win_hi = nullptr;
@@ -101,7 +93,7 @@ template <class T> int upload(const std::vector<T> &src, T **dst)
     *dst = nullptr;
     // one spare element so empty arrays still have a valid device address
     size_t bytes = (src.size() + 1) * sizeof(T);
-    hipError_t e = hipMalloc((void **)dst, bytes);
+    hipError_t e = pcsr::pool_alloc((void **)dst, bytes);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         return PCSR_E_OOM;
@@ -248,14 +240,15 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
         int32_t *t_rowptr = nullptr, *t_colidx = nullptr;
         float *t_vals = nullptr;
         auto drop_tmp = [&] {
-            if (t_rowptr) (void)hipFree(t_rowptr);
-            if (t_colidx) (void)hipFree(t_colidx);
-            if (t_vals) (void)hipFree(t_vals);
+            (void)hipStreamSynchronize(nullptr);
+            pcsr::pool_free(t_rowptr);
+            pcsr::pool_free(t_colidx);
+            pcsr::pool_free(t_vals);
         };
         if (!device_csr) {
-            bool ok = hip_ok(hipMalloc((void **)&t_rowptr, sizeof(int32_t) * (n_rows + 1))) &&
-                      hip_ok(hipMalloc((void **)&t_colidx, sizeof(int32_t) * (nnz + 1))) &&
-                      hip_ok(hipMalloc((void **)&t_vals, sizeof(float) * (nnz + 1))) &&
+            bool ok = hip_ok(pcsr::pool_alloc((void **)&t_rowptr, sizeof(int32_t) * (n_rows + 1))) &&
+                      hip_ok(pcsr::pool_alloc((void **)&t_colidx, sizeof(int32_t) * (nnz + 1))) &&
+                      hip_ok(pcsr::pool_alloc((void **)&t_vals, sizeof(float) * (nnz + 1))) &&
                       hip_ok(hipMemcpy(t_rowptr, rowptr, sizeof(int32_t) * (n_rows + 1), hipMemcpyHostToDevice)) &&
                       (nnz == 0 ||
                        (hip_ok(hipMemcpy(t_colidx, colidx, sizeof(int32_t) * nnz, hipMemcpyHostToDevice)) &&
@@ -279,14 +272,9 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
         }
         pcsr_handle_s *h = new (std::nothrow) pcsr_handle_s();
         if (!h) {
-            (void)hipFree(db.rowptr);
-            (void)hipFree(db.colidx);
-            (void)hipFree(db.val);
-            if (db.trow) (void)hipFree(db.trow);
-            if (db.split) (void)hipFree(db.split);
-            if (db.item_slot) (void)hipFree(db.item_slot);
-            if (db.sched) (void)hipFree(db.sched);
-            if (db.split_slot) (void)hipFree(db.split_slot);
+            for (void *q : {(void *)db.rowptr, (void *)db.colidx, (void *)db.val, (void *)db.trow, (void *)db.split,
+                            (void *)db.item_slot, (void *)db.sched, (void *)db.split_slot, (void *)db.long_list})
+                pcsr::pool_free(q);
             return PCSR_E_OOM;
         }
         h->host.n_rows = n_rows;
@@ -316,27 +304,12 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
         h->waves = prm.waves_per_wg;
         h->ipg = prm.items_per_group;
         h->flags = prm.flags;
+        h->d_long = db.long_list;
+        h->n_long = db.n_long;
         if (!hip_ok(hipGetDevice(&h->device))) {
             release_device(h);
             delete h;
             return PCSR_E_HIP;
-        }
-        if (h->n_split > 0) {
-            int rc2 = PCSR_E_OOM;
-            try {
-                std::vector<int32_t> slots((size_t)h->n_split + 1);
-                rc2 = hip_ok(hipMemcpy(slots.data(), h->d_split_slot, slots.size() * sizeof(int32_t),
-                                       hipMemcpyDeviceToHost))
-                          ? upload_long_panels(h, slots.data())
-                          : PCSR_E_HIP;
-            } catch (const std::bad_alloc &) {
-                rc2 = PCSR_E_OOM;
-            }
-            if (rc2 != PCSR_OK) {
-                release_device(h);
-                delete h;
-                return rc2;
-            }
         }
         *out = h;
         return PCSR_OK;
@@ -539,12 +512,13 @@ static int grow_workspace(pcsr_handle_t h, int64_t need)
 {
     if (need <= (int64_t)h->ws_bytes) return PCSR_OK;
     if (h->d_ws) {
-        // hipFree waits for the device, so no earlier SpMM still uses the old block
-        if (!hip_ok(hipFree(h->d_ws))) return PCSR_E_HIP;
+        // an earlier SpMM may still use the old block
+        if (!hip_ok(hipDeviceSynchronize())) return PCSR_E_HIP;
+        pcsr::pool_free(h->d_ws);
         h->d_ws = nullptr;
         h->ws_bytes = 0;
     }
-    hipError_t e = hipMalloc((void **)&h->d_ws, (size_t)need);
+    hipError_t e = pcsr::pool_alloc((void **)&h->d_ws, (size_t)need);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         h->d_ws = nullptr;

@@ -3,6 +3,12 @@
 // workload split - but with the CSR arrays already in device memory, so nothing crosses
 // PCIe except a handful of scalars.  The arrays it produces are bit-identical to the
 // host builder's.
+//
+// What bounds it: the arrays are read and written a few times at memory speed (16 M nonzeros:
+// 20-60 us a pass), so passes, launches (about 5 us each with the gaps) and waits of the host
+// (12-15 us each) are what is counted here.  No pass gives one thread a whole row: rows of
+// power-law graphs are up to a thousand times longer than the average, and the one thread
+// that had the longest took 5.3 ms to validate a graph whose average row takes microseconds.
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
@@ -12,6 +18,7 @@
 
 #include "../../include/pcsr.h"
 #include "pcsr_build_gpu.h"
+#include "pcsr_pool.h"
 
 namespace pcsr {
 namespace {
@@ -19,35 +26,84 @@ namespace {
 constexpr int kThreads = 256;
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
-
-// one thread per row: monotone row pointer, columns in range and strictly ascending
-__global__ void validate_kernel(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr,
-                                const int32_t *colidx, int *bad)
+// grid of a kernel that strides over n elements: enough workgroups to fill the chip, few
+// enough that one atomic or partial result from each costs nothing
+inline unsigned strided_blocks(int64_t n, unsigned most = 2048)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_rows) return;
-    const int64_t s = rowptr[i], e = rowptr[i + 1];
-    if (s > e || s < 0 || e > nnz) {
-        *bad = 1;
-        return;
+    const int64_t b = (n + kThreads - 1) / kThreads;
+    return (unsigned)(b < 1 ? 1 : (b > (int64_t)most ? most : b));
+}
+
+// ---- validation and row statistics
+
+// What the host learns from one pass over the row pointer and one over the columns.
+struct Checked {
+    int bad;               // a row pointer or column out of range
+    int first, last;       // rowptr[0], rowptr[n_rows]
+    int longest;           // longest row
+    int descents;          // t > 0 with colidx[t] <= colidx[t - 1]
+    int start_descents;    // ... where t starts a row
+    int nonempty, pad;
+};
+
+// Columns in range; positions where the column does not ascend.  Such a position is fine where
+// a row starts and nowhere else, so the CSR is sound if as many are found here as among the
+// row starts (validate_rows_kernel): no thread has to know which row its element is in.
+__global__ void __launch_bounds__(kThreads) validate_cols_kernel(int64_t n_cols, int64_t nnz, const int32_t *colidx,
+                                                                 Checked *out)
+{
+    int desc = 0, bad = 0;
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < nnz; t += stride) {
+        const int32_t c = colidx[t];
+        bad |= c < 0 || c >= n_cols;
+        desc += t > 0 && c <= colidx[t - 1];
     }
-    int64_t prev = -1;
-    for (int64_t p = s; p < e; ++p) {
-        const int64_t c = colidx[p];
-        if (c <= prev || c >= n_cols) {
-            *bad = 1;
-            return;
-        }
-        prev = c;
+    typedef hipcub::BlockReduce<int, kThreads> Reduce;
+    __shared__ typename Reduce::TempStorage t1, t2;
+    const int d = Reduce(t1).Sum(desc);
+    const int b = Reduce(t2).Sum(bad);
+    if (threadIdx.x == 0) {
+        if (d) atomicAdd(&out->descents, d);
+        if (b) out->bad = 1;
     }
 }
 
-// V = 2, one thread per nonzero, so that a row of 100,000 nonzeros is merged by 100,000
-// threads and not by one.  The vectors of panel p are the sorted union of the columns of
-// rows 2p ("even") and 2p+1 ("odd"); an element's place in the union follows from two
-// counts: the elements of its own row before it, and those of the other row that are
-// smaller and not already counted (columns present in both rows are counted with the even
-// row).
+// Monotone row pointer inside [0, nnz], descents at row starts (with_cols), row statistics.
+__global__ void __launch_bounds__(kThreads) validate_rows_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
+                                                                 const int32_t *colidx, int with_cols, Checked *out)
+{
+    int desc = 0, bad = 0, longest = 0, nonempty = 0;
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_rows; i += stride) {
+        const int64_t s = rowptr[i], e = rowptr[i + 1];
+        if (s < 0 || s > e || e > nnz) {
+            bad = 1;
+        } else if (e > s) {
+            ++nonempty;
+            longest = (int)(e - s) > longest ? (int)(e - s) : longest;
+            if (with_cols && s > 0) desc += colidx[s] <= colidx[s - 1];
+        }
+    }
+    typedef hipcub::BlockReduce<int, kThreads> Reduce;
+    __shared__ typename Reduce::TempStorage t1, t2, t3, t4;
+    const int d = Reduce(t1).Sum(desc);
+    const int b = Reduce(t2).Sum(bad);
+    const int n = Reduce(t3).Sum(nonempty);
+    const int l = Reduce(t4).Reduce(longest, hipcub::Max());
+    if (threadIdx.x == 0) {
+        if (d) atomicAdd(&out->start_descents, d);
+        if (b) out->bad = 1;
+        if (n) atomicAdd(&out->nonempty, n);
+        if (l) atomicMax(&out->longest, l);
+        if (blockIdx.x == 0) {
+            out->first = rowptr[0];
+            out->last = rowptr[n_rows];
+        }
+    }
+}
+
+// ---- which row a nonzero is in
 
 // index of the row that holds nonzero t: the last r with rowptr[r] <= t
 __device__ __forceinline__ int64_t row_of_nonzero(const int32_t *rowptr, int64_t n_rows, int64_t t)
@@ -63,6 +119,68 @@ __device__ __forceinline__ int64_t row_of_nonzero(const int32_t *rowptr, int64_t
     return lo;
 }
 
+// The rows of kSlice consecutive nonzeros, found by a workgroup together: 256-way search for
+// the first row (3 dependent loads instead of 20), then the row starts up to the end of the
+// slice in LDS, where every thread looks its nonzeros up.  A slice that crosses more rows than
+// fit (nearly all of them empty) is searched in memory.
+constexpr int kSlice = 1024;
+constexpr int kSliceRows = 1536;
+struct RowSlice {
+    int32_t start[kSliceRows + 1];
+    int cnt[kThreads / 64];
+    int64_t first; // row of the slice's first nonzero
+    int rows;      // row starts held, 0 = too many
+
+    __device__ void find(const int32_t *rowptr, int64_t n_rows, int64_t t0, int64_t t1)
+    {
+        const int tid = threadIdx.x;
+        int64_t lo = 0, hi = n_rows;
+        while (hi - lo > 1) {
+            const int64_t step = (hi - lo + kThreads) / (kThreads + 1);
+            const int64_t probe = lo + (tid + 1) * step;
+            const bool below = probe < hi && rowptr[probe] <= t0;
+            const unsigned long long m = __ballot(below);
+            __syncthreads(); // cnt of the round before is read
+            if ((tid & 63) == 0) cnt[tid >> 6] = __popcll(m);
+            __syncthreads();
+            int c = 0;
+            for (int w = 0; w < kThreads / 64; ++w) c += cnt[w];
+            lo += c * step;
+            hi = hi < lo + step ? hi : lo + step;
+        }
+        const int64_t r0 = lo;
+        int have = 0;
+        for (int base = 0; base < kSliceRows; base += kThreads) {
+            const int64_t r = r0 + base + tid;
+            start[base + tid] = r <= n_rows ? rowptr[r] : INT32_MAX;
+            __syncthreads();
+            const int32_t lst = start[base + kThreads - 1];
+            if (lst >= t1) {
+                have = base + kThreads;
+                break;
+            }
+        }
+        if (tid == 0) {
+            first = r0;
+            rows = have;
+        }
+        __syncthreads();
+    }
+    __device__ int64_t row(const int32_t *rowptr, int64_t n_rows, int64_t t) const
+    {
+        if (rows == 0) return row_of_nonzero(rowptr, n_rows, t);
+        int lo = 0, hi = rows; // start[lo] <= t
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (start[mid] <= t)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        return first + lo;
+    }
+};
+
 // number of entries of colidx[b, e) smaller than c
 __device__ __forceinline__ int64_t count_below(const int32_t *colidx, int64_t b, int64_t e, int32_t c)
 {
@@ -77,24 +195,31 @@ __device__ __forceinline__ int64_t count_below(const int32_t *colidx, int64_t b,
     return lo - b;
 }
 
-// shared[t] = 1 for a nonzero of an odd row whose column also occurs in the even row of
-// its panel, else 0; shared[nnz] = 0 (scanned together with the rest)
-__global__ void union_shared_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
-                                    int32_t *shared)
+// ---- V = 2.  The vectors of panel p are the sorted union of the columns of rows 2p ("even")
+// and 2p+1 ("odd"); an element's place in the union follows from two counts: the elements of
+// its own row before it, and those of the other row that are smaller and not already counted
+// (columns present in both rows are counted with the even row).
+
+// whether nonzero t of row r is an odd row's column that the even row of its panel has too
+__device__ __forceinline__ bool shared_column(const int32_t *rowptr, const int32_t *colidx, int64_t r, int64_t t)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t > nnz) return;
-    int32_t flag = 0;
-    if (t < nnz) {
-        const int64_t r = row_of_nonzero(rowptr, n_rows, t);
-        if (r & 1) {
-            const int64_t a0 = rowptr[r - 1], a1 = rowptr[r];
-            const int32_t c = colidx[t];
-            const int64_t k = count_below(colidx, a0, a1, c);
-            flag = (a0 + k < a1 && colidx[a0 + k] == c) ? 1 : 0;
-        }
-    }
-    shared[t] = flag;
+    if (!(r & 1)) return false;
+    const int64_t a0 = rowptr[r - 1], a1 = rowptr[r];
+    const int32_t c = colidx[t];
+    const int64_t k = count_below(colidx, a0, a1, c);
+    return a0 + k < a1 && colidx[a0 + k] == c;
+}
+
+// shared[t] = 1 for such a nonzero, else 0; shared[nnz] = 0 (scanned together with the rest)
+__global__ void __launch_bounds__(kThreads) union_shared_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
+                                                                const int32_t *colidx, int32_t *shared)
+{
+    __shared__ RowSlice slice;
+    const int64_t t0 = (int64_t)blockIdx.x * kSlice, t1 = t0 + kSlice < nnz ? t0 + kSlice : nnz;
+    if (t0 < nnz) slice.find(rowptr, n_rows, t0, t1);
+    for (int64_t t = t0 + threadIdx.x; t < t1; t += kThreads)
+        shared[t] = shared_column(rowptr, colidx, slice.row(rowptr, n_rows, t), t) ? 1 : 0;
+    if (nnz >= t0 && nnz < t0 + kSlice && threadIdx.x == 0) shared[nnz] = 0;
 }
 
 // vectors per panel: both rows' nonzeros minus the columns they share; cnt[P] = 0
@@ -115,189 +240,305 @@ __global__ void union_count_kernel(int64_t P, int64_t n_rows, const int32_t *row
 
 // every nonzero writes its vector (ascending column, +0.0f padding); a column that both
 // rows hold is written by the even row's nonzero
-__global__ void union_fill_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
-                                  const float *vals, const int32_t *shared_scan, const int32_t *prow,
-                                  int32_t *out_col, float *out_val)
+__global__ void __launch_bounds__(kThreads) union_fill_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
+                                                              const int32_t *colidx, const float *vals,
+                                                              const int32_t *shared_scan, const int32_t *prow,
+                                                              int32_t *out_col, float *out_val)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nnz) return;
-    const int64_t r = row_of_nonzero(rowptr, n_rows, t);
-    const int64_t p = r >> 1;
-    const int32_t c = colidx[t];
-    const int64_t a0 = rowptr[2 * p], a1 = rowptr[2 * p + 1];
-    const int64_t b1 = (2 * p + 1 < n_rows) ? rowptr[2 * p + 2] : a1;
-    if (!(r & 1)) {
-        const int64_t k = count_below(colidx, a1, b1, c);                // odd-row columns below c
-        const int64_t both = shared_scan[a1 + k] - shared_scan[a1];       // of which also in this row
-        const int64_t o = prow[p] + (t - a0) + (k - both);
-        const bool twin = a1 + k < b1 && colidx[a1 + k] == c;
-        if (o >= prow[p + 1]) return; // only with rows that are not sorted (validation skipped)
-        out_col[o] = c;
-        out_val[2 * o] = vals[t];
-        out_val[2 * o + 1] = twin ? vals[a1 + k] : 0.0f;
-    } else if (shared_scan[t + 1] == shared_scan[t]) {                    // not shared
-        const int64_t k = count_below(colidx, a0, a1, c);                // even-row columns below c
-        const int64_t o = prow[p] + k + ((t - a1) - (shared_scan[t] - shared_scan[a1]));
-        if (o >= prow[p + 1]) return;
-        out_col[o] = c;
-        out_val[2 * o] = 0.0f;
-        out_val[2 * o + 1] = vals[t];
+    __shared__ RowSlice slice;
+    const int64_t t0 = (int64_t)blockIdx.x * kSlice, t1 = t0 + kSlice < nnz ? t0 + kSlice : nnz;
+    slice.find(rowptr, n_rows, t0, t1);
+    for (int64_t t = t0 + threadIdx.x; t < t1; t += kThreads) {
+        const int64_t r = slice.row(rowptr, n_rows, t);
+        const int64_t p = r >> 1;
+        const int32_t c = colidx[t];
+        const int64_t a0 = rowptr[2 * p], a1 = rowptr[2 * p + 1];
+        const int64_t b1 = (2 * p + 1 < n_rows) ? rowptr[2 * p + 2] : a1;
+        if (!(r & 1)) {
+            const int64_t k = count_below(colidx, a1, b1, c);           // odd-row columns below c
+            const int64_t both = shared_scan[a1 + k] - shared_scan[a1]; // of which also in this row
+            const int64_t o = prow[p] + (t - a0) + (k - both);
+            const bool twin = a1 + k < b1 && colidx[a1 + k] == c;
+            if (o >= prow[p + 1]) continue; // only with rows that are not sorted (validation skipped)
+            out_col[o] = c;
+            out_val[2 * o] = vals[t];
+            out_val[2 * o + 1] = twin ? vals[a1 + k] : 0.0f;
+        } else if (shared_scan[t + 1] == shared_scan[t]) { // not shared
+            const int64_t k = count_below(colidx, a0, a1, c); // even-row columns below c
+            const int64_t o = prow[p] + k + ((t - a1) - (shared_scan[t] - shared_scan[a1]));
+            if (o >= prow[p + 1]) continue;
+            out_col[o] = c;
+            out_val[2 * o] = 0.0f;
+            out_val[2 * o + 1] = vals[t];
+        }
     }
 }
 
-// stats[0] = non-empty panels, stats[1] = longest panel
-__global__ void panel_stats_kernel(int64_t P, const int32_t *prow, unsigned long long *nonempty, int *longest)
+// non-empty panels and longest panel (V = 2; validate_rows_kernel has them for V = 1)
+__global__ void __launch_bounds__(kThreads) panel_stats_kernel(int64_t P, const int32_t *prow, Checked *out)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int len = 0;
-    if (p < P) len = prow[p + 1] - prow[p];
+    int n = 0, l = 0;
+    for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p < P; p += (int64_t)gridDim.x * kThreads) {
+        const int len = prow[p + 1] - prow[p];
+        n += len > 0;
+        l = len > l ? len : l;
+    }
     typedef hipcub::BlockReduce<int, kThreads> Reduce;
     __shared__ typename Reduce::TempStorage t1, t2;
-    const int ne = Reduce(t1).Sum(len > 0 ? 1 : 0);
-    const int mx = Reduce(t2).Reduce(len, hipcub::Max());
+    const int ne = Reduce(t1).Sum(n);
+    const int mx = Reduce(t2).Reduce(l, hipcub::Max());
     if (threadIdx.x == 0) {
-        if (ne) atomicAdd(nonempty, (unsigned long long)ne);
-        if (mx) atomicMax(longest, mx);
+        if (ne) atomicAdd(&out->nonempty, ne);
+        if (mx) atomicMax(&out->longest, mx);
     }
 }
 
-// work items per panel: max(1, ceil(len / SG))
-__global__ void items_kernel(int64_t P, const int32_t *prow, int32_t sg, int32_t *items)
-{
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > P) return;
-    if (p == P) {
-        items[P] = 0;
-        return;
+// ---- workload split
+
+// What a panel adds to the four running counts of the split; one scan does for all of them.
+struct SplitCount {
+    int items;  // max(1, ceil(len / SG))
+    int split;  // 1 if that is more than one
+    int slots;  // its items then
+    int longp;  // 1 if it has more than kLongPanelSlots items
+};
+struct SplitSum {
+    __device__ SplitCount operator()(const SplitCount &a, const SplitCount &b) const
+    {
+        return {a.items + b.items, a.split + b.split, a.slots + b.slots, a.longp + b.longp};
     }
+};
+__device__ __forceinline__ SplitCount split_count(const int32_t *prow, int64_t p, int64_t P, int32_t sg)
+{
+    if (p >= P) return {0, 0, 0, 0};
     const int len = prow[p + 1] - prow[p];
-    const int it = (int)(((long)len + sg - 1) / sg);
-    items[p] = it > 1 ? it : 1;
+    int it = (int)(((long)len + sg - 1) / sg);
+    it = it > 1 ? it : 1;
+    return {it, it > 1, it > 1 ? it : 0, it > kLongPanelSlots};
+}
+constexpr int kSplitPanels = 1024; // panels per workgroup
+
+__global__ void __launch_bounds__(kThreads) split_sums_kernel(int64_t P, const int32_t *prow, int32_t sg,
+                                                              SplitCount *sums)
+{
+    typedef hipcub::BlockReduce<SplitCount, kThreads> Reduce;
+    __shared__ typename Reduce::TempStorage tmp;
+    SplitCount c = {0, 0, 0, 0};
+    for (int i = 0; i < kSplitPanels / kThreads; ++i)
+        c = SplitSum()(c, split_count(prow, (int64_t)blockIdx.x * kSplitPanels + i * kThreads + threadIdx.x, P, sg));
+    c = Reduce(tmp).Reduce(c, SplitSum());
+    if (threadIdx.x == 0) sums[blockIdx.x] = c;
 }
 
-// Panels that own more than one item, in ascending order (positions come from scans, so
-// the tables are the same on every run): mark[p] = 1 and cnt[p] = items for such a panel.
-__global__ void split_marks_kernel(int64_t P, const int32_t *items, int32_t *mark, int32_t *cnt)
+// exclusive scan in place by one workgroup; the total goes to sums[n]
+__global__ void __launch_bounds__(1024) split_scan_kernel(int n, SplitCount *sums)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > P) return;
-    const int it = p < P ? items[p] : 0;
-    mark[p] = it > 1 ? 1 : 0;
-    cnt[p] = it > 1 ? it : 0;
-}
-
-// rewritten rowPtr, TRow and the workspace slot of every item (first / slotbase: exclusive
-// scans of items / cnt)
-__global__ void split_fill_kernel(int64_t P, const int32_t *prow, const int32_t *first,
-                                  const int32_t *slotbase, int32_t sg, int32_t *out_rowptr,
-                                  int32_t *out_trow, int32_t *out_slot)
-{
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    int64_t start = prow[p];
-    const int i0 = first[p], i1 = first[p + 1];
-    int slot = i1 - i0 > 1 ? slotbase[p] : -1;
-    for (int it = i0; it < i1; ++it) {
-        out_rowptr[it] = (int32_t)start;
-        out_trow[it] = (int32_t)p;
-        out_slot[it] = slot;
-        if (slot >= 0) ++slot;
-        start += sg;
+    typedef hipcub::BlockScan<SplitCount, 1024> Scan;
+    __shared__ typename Scan::TempStorage tmp;
+    SplitCount before = {0, 0, 0, 0};
+    for (int base = 0; base < n; base += 1024) {
+        const int i = base + threadIdx.x;
+        SplitCount c = {0, 0, 0, 0}, ex, total;
+        if (i < n) c = sums[i];
+        Scan(tmp).ExclusiveScan(c, ex, SplitCount{0, 0, 0, 0}, SplitSum(), total);
+        if (i < n) sums[i] = SplitSum()(before, ex);
+        before = SplitSum()(before, total);
+        __syncthreads();
     }
-    if (p == P - 1) out_rowptr[i1] = prow[P];
+    if (threadIdx.x == 0) sums[n] = before;
 }
 
-// qpos / slotbase: exclusive scans of mark / cnt over P + 1 entries
-__global__ void split_tables_kernel(int64_t P, const int32_t *items, const int32_t *qpos,
-                                    const int32_t *slotbase, int32_t *split_panels, int32_t *split_slot)
+struct SplitOut {
+    int32_t *rowptr, *trow, *item_slot;        // per item (rowptr one more)
+    int32_t *split_panels, *split_slot, *long_list;
+    int32_t *long_key, *long_item, *short_item; // column-ordered schedule (may be null)
+};
+
+// Rewritten rowPtr, TRow, workspace slots, the tables of split panels and, for the schedule, the
+// lists of items of split panels (with their first column) and of the others.  A workgroup
+// numbers its 1024 panels, then its threads take the items one by one: a panel of a
+// thousand items is no longer one thread's.
+__global__ void __launch_bounds__(kThreads) split_fill_kernel(int64_t P, const int32_t *prow, const int32_t *colidx,
+                                                              int32_t sg, const SplitCount *sums, SplitOut o)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > P) return;
-    if (p == P) {
-        split_slot[qpos[P]] = slotbase[P];
-        return;
+    constexpr int N = kSplitPanels / kThreads;
+    typedef hipcub::BlockScan<SplitCount, kThreads> Scan;
+    __shared__ typename Scan::TempStorage tmp;
+    __shared__ int32_t first[kSplitPanels + 1]; // first item of each panel
+    __shared__ int32_t slot[kSplitPanels];      // slots handed out before it
+    const int64_t p0 = (int64_t)blockIdx.x * kSplitPanels;
+    const SplitCount base = sums[blockIdx.x];
+    SplitCount mine[N], ex, own = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        mine[i] = split_count(prow, p0 + threadIdx.x * N + i, P, sg);
+        own = SplitSum()(own, mine[i]);
     }
-    if (items[p] > 1) {
-        const int q = qpos[p];
-        split_panels[q] = (int32_t)p;
-        split_slot[q] = slotbase[p];
+    Scan(tmp).ExclusiveScan(own, ex, SplitCount{0, 0, 0, 0}, SplitSum());
+    ex = SplitSum()(base, ex);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int k = threadIdx.x * N + i;
+        const int64_t p = p0 + k;
+        first[k] = ex.items;
+        slot[k] = ex.slots;
+        if (mine[i].split) {
+            o.split_panels[ex.split] = (int32_t)p;
+            o.split_slot[ex.split] = ex.slots;
+            if (mine[i].longp) o.long_list[ex.longp] = ex.split;
+        }
+        ex = SplitSum()(ex, mine[i]);
+        if (p == P - 1) {
+            o.rowptr[ex.items] = prow[P];
+            o.split_slot[ex.split] = ex.slots;
+        }
+    }
+    if (threadIdx.x == kThreads - 1) first[kSplitPanels] = ex.items;
+    __syncthreads();
+    const int panels = (int)(P - p0 < kSplitPanels ? P - p0 : kSplitPanels);
+    for (int it = first[0] + threadIdx.x; it < first[panels]; it += kThreads) {
+        int lo = 0, hi = panels; // first[lo] <= it
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (first[mid] <= it)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        const int k = it - first[lo];
+        const bool split = first[lo + 1] - first[lo] > 1;
+        const int32_t s = prow[p0 + lo] + k * sg;
+        const int sl = split ? slot[lo] + k : -1;
+        o.rowptr[it] = s;
+        o.trow[it] = (int32_t)(p0 + lo);
+        o.item_slot[it] = sl;
+        if (o.long_key) {
+            if (split) {
+                o.long_key[sl] = colidx[s]; // items of split panels are never empty
+                o.long_item[sl] = it;
+            } else {
+                o.short_item[it - slot[lo]] = it;
+            }
+        }
     }
 }
 
 // ---- column-ordered schedule (same result as the host builder's schedule_by_column)
 
-// flag[it] = 1 for an item of a split panel (one extra trailing 0 so the scan yields the total)
-__global__ void sched_flag_kernel(int64_t M, const int32_t *item_slot, int32_t *flag)
+// work of an item in a list: its vectors + 8
+__device__ __forceinline__ int sched_weight(const int32_t *list, const int32_t *rowptr, int64_t i, int64_t n)
 {
-    const int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (it > M) return;
-    flag[it] = (it < M && item_slot[it] >= 0) ? 1 : 0;
+    return i < n ? rowptr[list[i] + 1] - rowptr[list[i]] + 8 : 0;
+}
+constexpr int kSchedChunk = 1024;
+
+// work of each chunk of 1024 entries: chunks of the long list first, then of the short one
+__global__ void __launch_bounds__(kThreads) sched_sums_kernel(int64_t nl, const int32_t *longs, int64_t ns,
+                                                              const int32_t *shorts, const int32_t *rowptr,
+                                                              long long *sums)
+{
+    const int64_t cl = (nl + kSchedChunk - 1) / kSchedChunk;
+    const bool is_long = blockIdx.x < cl;
+    const int32_t *list = is_long ? longs : shorts;
+    const int64_t n = is_long ? nl : ns, c = is_long ? blockIdx.x : blockIdx.x - cl;
+    long long w = 0;
+    for (int i = threadIdx.x; i < kSchedChunk; i += kThreads) w += sched_weight(list, rowptr, c * kSchedChunk + i, n);
+    typedef hipcub::BlockReduce<long long, kThreads> Reduce;
+    __shared__ typename Reduce::TempStorage tmp;
+    const long long t = Reduce(tmp).Sum(w);
+    if (threadIdx.x == 0) sums[blockIdx.x] = t;
 }
 
-// long items keyed by their first column (in slot order = item order); the others listed in
-// item order.  lrank: exclusive scan of flag.
-__global__ void sched_lists_kernel(int64_t M, const int32_t *rowptr, const int32_t *colidx,
-                                   const int32_t *item_slot, const int32_t *lrank, int32_t *long_key,
-                                   int32_t *long_item, int32_t *short_item)
+// exclusive scan in place of one list's chunk sums, total behind them; workgroup 0 the long
+// list's (n0 sums at sums[0]), workgroup 1 the short one's (n1 at sums[n0], written from
+// scan[n0 + 1])
+__global__ void __launch_bounds__(1024) sched_scan_kernel(int n0, int n1, const long long *sums, long long *scan)
 {
-    const int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (it >= M) return;
-    const int slot = item_slot[it];
-    if (slot >= 0) {
-        long_key[slot] = colidx[rowptr[it]]; // items of split panels are never empty
-        long_item[slot] = (int32_t)it;
-    } else {
-        short_item[it - lrank[it]] = (int32_t)it;
+    typedef hipcub::BlockScan<long long, 1024> Scan;
+    __shared__ typename Scan::TempStorage tmp;
+    const int n = blockIdx.x ? n1 : n0;
+    const long long *in = blockIdx.x ? sums + n0 : sums;
+    long long *out = blockIdx.x ? scan + n0 + 1 : scan;
+    long long before = 0;
+    for (int base = 0; base < n; base += 1024) {
+        const int i = base + threadIdx.x;
+        long long c = i < n ? in[i] : 0, ex, total;
+        Scan(tmp).ExclusiveSum(c, ex, total);
+        if (i < n) out[i] = before + ex;
+        before += total;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[n] = before;
+}
+
+// 8 contiguous equal-work slices of both lists: workgroup x < 9 finds boundary x of the long
+// list, 9 + x that of the short one: the first index whose work before it reaches x eighths.
+__global__ void __launch_bounds__(kThreads) sched_bounds_kernel(int64_t nl, const int32_t *longs, int64_t ns,
+                                                                const int32_t *shorts, const int32_t *rowptr,
+                                                                const long long *scan, int32_t *bounds)
+{
+    const bool is_long = blockIdx.x < 9;
+    const int x = is_long ? blockIdx.x : blockIdx.x - 9;
+    const int64_t n = is_long ? nl : ns, cl = (nl + kSchedChunk - 1) / kSchedChunk;
+    const int64_t chunks = (n + kSchedChunk - 1) / kSchedChunk;
+    const int32_t *list = is_long ? longs : shorts;
+    const long long *cum = is_long ? scan : scan + cl + 1;
+    const long long target = cum[chunks] * x / 8;
+    if (x == 0 || x == 8 || target <= 0) {
+        if (threadIdx.x == 0) bounds[blockIdx.x] = (int32_t)(x == 8 ? n : 0);
+        return;
+    }
+    int64_t lo = 0, hi = chunks; // the last chunk with less work before it than the target
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (cum[mid] < target)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    constexpr int N = kSchedChunk / kThreads;
+    typedef hipcub::BlockScan<long long, kThreads> Scan;
+    __shared__ typename Scan::TempStorage tmp;
+    __shared__ int found;
+    if (threadIdx.x == 0) found = kSchedChunk;
+    long long w[N], own = 0, ex;
+#pragma unroll
+    for (int i = 0; i < N; ++i) own += w[i] = sched_weight(list, rowptr, lo * kSchedChunk + threadIdx.x * N + i, n);
+    Scan(tmp).ExclusiveSum(own, ex);
+    __syncthreads();
+    long long at = cum[lo] + ex;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        at += w[i]; // work before entry threadIdx.x*N + i + 1
+        if (at >= target) {
+            atomicMin(&found, threadIdx.x * N + i + 1);
+            break;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int64_t i = lo * kSchedChunk + found;
+        bounds[blockIdx.x] = (int32_t)(i < n ? i : n);
     }
 }
 
-// w[i] = vectors of list[i] + 8 (the per-item cost), w[n] = 0
-__global__ void sched_weights_kernel(int64_t n, const int32_t *list, const int32_t *rowptr, long long *w)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > n) return;
-    w[i] = i < n ? (long long)(rowptr[list[i] + 1] - rowptr[list[i]]) + 8 : 0;
-}
-
-// 8 contiguous equal-work slices of both lists; cum*: exclusive scans of the weights (n + 1
-// entries, the last one the total).  out: lb[9], sb[9], xb[9].
-__global__ void sched_bounds_kernel(long nl, const long long *cum_l, long ns, const long long *cum_s,
-                                    int32_t *out)
-{
-    const int x = threadIdx.x;
-    if (x > 8) return;
-    auto lower = [](const long long *cum, long n, long long target) {
-        long lo = 0, hi = n + 1; // first index in [0, n] with cum[index] >= target
-        while (lo < hi) {
-            const long mid = (lo + hi) / 2;
-            if (cum[mid] >= target)
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        return lo > n ? n : lo;
-    };
-    const long l = x == 0 ? 0 : (x == 8 ? nl : lower(cum_l, nl, cum_l[nl] * x / 8));
-    const long sh = x == 0 ? 0 : (x == 8 ? ns : lower(cum_s, ns, cum_s[ns] * x / 8));
-    out[x] = (int32_t)l;
-    out[9 + x] = (int32_t)sh;
-    out[18 + x] = (int32_t)(l + sh);
-}
-
 // one record per launch position: XCD x runs its slice of the column-ordered list, then
-// its slice of the others
-__global__ void sched_emit_kernel(int64_t n, const int32_t *list, int is_short, const int32_t *bounds,
-                                  const int32_t *rowptr, const int32_t *trow, const int32_t *item_slot,
-                                  int4 *sched)
+// its slice of the others.  bounds: lb[9], sb[9].
+__global__ void __launch_bounds__(kThreads) sched_emit_kernel(int64_t nl, const int32_t *longs, int64_t ns,
+                                                              const int32_t *shorts, const int32_t *bounds,
+                                                              const int32_t *rowptr, const int32_t *trow,
+                                                              const int32_t *item_slot, int4 *sched)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (t >= nl + ns) return;
+    const bool is_short = t >= nl;
+    const int64_t i = is_short ? t - nl : t;
     const int32_t *lb = bounds, *sb = bounds + 9;
     const int32_t *mine = is_short ? sb : lb;
     int x = 0;
     while (x < 7 && i >= mine[x + 1]) ++x;
     const int64_t pos = is_short ? (int64_t)lb[x + 1] + i : (int64_t)sb[x] + i;
-    const int it = list[i];
+    const int it = is_short ? shorts[i] : longs[i];
     const int start = rowptr[it];
     sched[pos] = make_int4(start, rowptr[it + 1] - start, trow[it], item_slot[it]);
 }
@@ -328,139 +569,183 @@ __global__ void xcd_bounds_kernel(int32_t M, const int32_t *rowptr, int32_t *xb)
     xb[x] = (int32_t)lo;
 }
 
+// ---- Table 3 features on the GPU: one pass over the nonzeros, two over the rows
+constexpr unsigned kFeatBlocks = 512, kNearBlocks = 2048;
 
-// ---- Table 3 features on the GPU (two passes over the row pointer, one over colIdx)
+struct RowPart { // per workgroup of the first row pass
+    long long n_hat, nonempty2, shared;
+    double bw_sum, bw_max;
+    int d_max, pad;
+};
+struct DevPart { // per workgroup of the second
+    double ss, ss_hat;
+    long long M1, M2;
+};
 struct FeatAcc {
-    unsigned long long n_hat, nnz2, nonempty2, M1, M2, near;
-    int d_max;
-    int pad;
+    long long n_hat, nnz2, nonempty2, M1, M2, near;
     double bw_sum, bw_max, ss, ss_hat;
+    int d_max, pad;
+};
+struct RowPartSum {
+    __device__ RowPart operator()(const RowPart &a, const RowPart &b) const
+    {
+        return {a.n_hat + b.n_hat, a.nonempty2 + b.nonempty2, a.shared + b.shared, a.bw_sum + b.bw_sum,
+                a.bw_max > b.bw_max ? a.bw_max : b.bw_max, a.d_max > b.d_max ? a.d_max : b.d_max, 0};
+    }
+};
+struct DevPartSum {
+    __device__ DevPart operator()(const DevPart &a, const DevPart &b) const
+    {
+        return {a.ss + b.ss, a.ss_hat + b.ss_hat, a.M1 + b.M1, a.M2 + b.M2};
+    }
 };
 
-__device__ inline void atomic_max_double(double *addr, double v)
+// Nonzeros within 512 columns of the diagonal, per workgroup; columns that both rows of a
+// V = 2 panel have, per panel (shared: zeros on entry).
+__global__ void __launch_bounds__(kThreads) features_nonzeros_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
+                                                                     const int32_t *colidx, int32_t *shared,
+                                                                     long long *near_out)
 {
-    unsigned long long *a = reinterpret_cast<unsigned long long *>(addr);
-    unsigned long long old = *a;
-    while (__longlong_as_double((long long)old) < v) {
-        const unsigned long long assumed = old;
-        old = atomicCAS(a, assumed, (unsigned long long)__double_as_longlong(v));
-        if (old == assumed) break;
-    }
-}
-
-// pass 1: one thread per row (degree, bandwidth) and, for even rows, the V = 2 panel length
-__global__ void features_pass1_kernel(int64_t n_rows, const int32_t *rowptr, const int32_t *colidx,
-                                      int32_t *len2, FeatAcc *acc)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int nh = 0, dmax = 0, ne2 = 0;
-    long l2 = 0, near = 0;
-    double bw = 0.0;
-    if (i < n_rows) {
-        const int64_t s = rowptr[i], e = rowptr[i + 1];
-        const int l = (int)(e - s);
-        if (l > 0) {
-            nh = 1;
-            dmax = l;
-            bw = (double)colidx[e - 1] - (double)colidx[s];
-            // nonzeros with |column - row| < 512: two binary searches in the ascending row
-            auto lower = [&](int64_t key) {
-                int64_t lo = s, hi = e;
-                while (lo < hi) {
-                    const int64_t mid = (lo + hi) / 2;
-                    if (colidx[mid] < key)
-                        lo = mid + 1;
-                    else
-                        hi = mid;
-                }
-                return lo;
-            };
-            near = lower(i + 512) - lower(i - 511);
-        }
-        if ((i & 1) == 0) {
-            int64_t a = s, ae = e, b = e, be = (i + 1 < n_rows) ? rowptr[i + 2] : e, n = 0;
-            while (a < ae && b < be) {
-                const int32_t ca = colidx[a], cb = colidx[b];
-                a += (ca <= cb);
-                b += (cb <= ca);
-                ++n;
+    __shared__ RowSlice slice;
+    __shared__ int32_t count[kSliceRows / 2 + 1];
+    long long near = 0;
+    for (int64_t t0 = (int64_t)blockIdx.x * kSlice; t0 < nnz; t0 += (int64_t)gridDim.x * kSlice) {
+        const int64_t t1 = t0 + kSlice < nnz ? t0 + kSlice : nnz;
+        __syncthreads(); // the slice before is done with
+        slice.find(rowptr, n_rows, t0, t1);
+        const int panels = slice.rows / 2 + 1;
+        for (int k = threadIdx.x; k < panels; k += kThreads) count[k] = 0;
+        __syncthreads();
+        for (int64_t t = t0 + threadIdx.x; t < t1; t += kThreads) {
+            const int64_t r = slice.row(rowptr, n_rows, t);
+            const int64_t d = (int64_t)colidx[t] - r;
+            near += d > -512 && d < 512;
+            if (shared_column(rowptr, colidx, r, t)) {
+                if (slice.rows)
+                    atomicAdd(&count[(r >> 1) - (slice.first >> 1)], 1);
+                else
+                    atomicAdd(&shared[r >> 1], 1);
             }
-            l2 = n + (ae - a) + (be - b);
-            len2[i >> 1] = (int32_t)l2;
-            ne2 = l2 > 0;
         }
+        __syncthreads();
+        if (slice.rows)
+            for (int k = threadIdx.x; k < panels; k += kThreads)
+                if (count[k]) atomicAdd(&shared[(slice.first >> 1) + k], count[k]);
     }
-    typedef hipcub::BlockReduce<int, kThreads> RI;
-    typedef hipcub::BlockReduce<long, kThreads> RL;
-    typedef hipcub::BlockReduce<double, kThreads> RD;
-    __shared__ typename RI::TempStorage ti;
-    __shared__ typename RL::TempStorage tl;
-    __shared__ typename RD::TempStorage td;
-    const int s_nh = RI(ti).Sum(nh);
-    __syncthreads();
-    const int s_dmax = RI(ti).Reduce(dmax, hipcub::Max());
-    __syncthreads();
-    const int s_ne2 = RI(ti).Sum(ne2);
-    const long s_l2 = RL(tl).Sum(l2);
-    __syncthreads();
-    const long s_near = RL(tl).Sum(near);
-    const double s_bw = RD(td).Sum(bw);
-    __syncthreads();
-    const double m_bw = RD(td).Reduce(bw, hipcub::Max());
-    if (threadIdx.x == 0) {
-        if (s_nh) atomicAdd(&acc->n_hat, (unsigned long long)s_nh);
-        if (s_dmax) atomicMax(&acc->d_max, s_dmax);
-        if (s_ne2) atomicAdd(&acc->nonempty2, (unsigned long long)s_ne2);
-        if (s_l2) atomicAdd(&acc->nnz2, (unsigned long long)s_l2);
-        if (s_near) atomicAdd(&acc->near, (unsigned long long)s_near);
-        if (s_bw != 0.0) atomicAdd(&acc->bw_sum, s_bw);
-        if (m_bw > 0.0) atomic_max_double(&acc->bw_max, m_bw);
-    }
+    typedef hipcub::BlockReduce<long long, kThreads> Reduce;
+    __shared__ typename Reduce::TempStorage tmp;
+    near = Reduce(tmp).Sum(near);
+    if (threadIdx.x == 0) near_out[blockIdx.x] = near;
 }
 
-// pass 2: squared deviations of the degrees and the item counts under Eq. (3)'s SG
-__global__ void features_pass2_kernel(int64_t n_rows, const int32_t *rowptr, const int32_t *len2, double d,
-                                      double d_hat, long sg1, long sg2, FeatAcc *acc)
+__device__ __forceinline__ long panel_len(const int32_t *rowptr, const int32_t *shared, int64_t p, int64_t n_rows)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double ss = 0.0, ssh = 0.0;
-    long m1 = 0, m2 = 0;
-    if (i < n_rows) {
-        const long l = rowptr[i + 1] - rowptr[i];
-        ss = ((double)l - d) * ((double)l - d);
-        if (l > 0) ssh = ((double)l - d_hat) * ((double)l - d_hat);
-        m1 = (l + sg1 - 1) / sg1;
-        if (m1 < 1) m1 = 1;
-        if ((i & 1) == 0) {
-            m2 = (len2[i >> 1] + sg2 - 1) / sg2;
-            if (m2 < 1) m2 = 1;
-        }
-    }
-    typedef hipcub::BlockReduce<long, kThreads> RL;
-    typedef hipcub::BlockReduce<double, kThreads> RD;
-    __shared__ typename RL::TempStorage tl;
-    __shared__ typename RD::TempStorage td;
-    const double s_ss = RD(td).Sum(ss);
-    __syncthreads();
-    const double s_ssh = RD(td).Sum(ssh);
-    const long s_m1 = RL(tl).Sum(m1);
-    __syncthreads();
-    const long s_m2 = RL(tl).Sum(m2);
-    if (threadIdx.x == 0) {
-        atomicAdd(&acc->ss, s_ss);
-        atomicAdd(&acc->ss_hat, s_ssh);
-        atomicAdd(&acc->M1, (unsigned long long)s_m1);
-        atomicAdd(&acc->M2, (unsigned long long)s_m2);
-    }
+    const int64_t end = 2 * p + 2 < n_rows ? 2 * p + 2 : n_rows;
+    return (long)rowptr[end] - rowptr[2 * p] - shared[p];
 }
 
-struct Scratch { // frees everything it still owns on scope exit
-    void *p[32] = {};
+__global__ void __launch_bounds__(kThreads) features_rows_kernel(int64_t n_rows, const int32_t *rowptr,
+                                                                 const int32_t *colidx, const int32_t *shared,
+                                                                 RowPart *parts)
+{
+    RowPart a = {0, 0, 0, 0.0, 0.0, 0, 0};
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * kThreads) {
+        const int64_t s = rowptr[i], e = rowptr[i + 1];
+        if (e > s) {
+            ++a.n_hat;
+            a.d_max = (int)(e - s) > a.d_max ? (int)(e - s) : a.d_max;
+            const double bw = (double)colidx[e - 1] - (double)colidx[s];
+            a.bw_sum += bw;
+            a.bw_max = bw > a.bw_max ? bw : a.bw_max;
+        }
+        if ((i & 1) == 0) {
+            a.shared += shared[i >> 1];
+            a.nonempty2 += panel_len(rowptr, shared, i >> 1, n_rows) > 0;
+        }
+    }
+    typedef hipcub::BlockReduce<RowPart, kThreads> Reduce;
+    __shared__ typename Reduce::TempStorage tmp;
+    a = Reduce(tmp).Reduce(a, RowPartSum());
+    if (threadIdx.x == 0) parts[blockIdx.x] = a;
+}
+
+// sums of the first row pass, the same in every workgroup that asks (result in thread 0)
+__device__ RowPart sum_row_parts(const RowPart *parts, int n)
+{
+    typedef hipcub::BlockReduce<RowPart, kThreads> Reduce;
+    __shared__ typename Reduce::TempStorage tmp;
+    RowPart a = {0, 0, 0, 0.0, 0.0, 0, 0};
+    for (int i = threadIdx.x; i < n; i += kThreads) a = RowPartSum()(a, parts[i]);
+    return Reduce(tmp).Reduce(a, RowPartSum());
+}
+
+// Eq. (3)
+__device__ __forceinline__ long eq3_sg(long v, long nonempty, long omega)
+{
+    return (v == 0 || nonempty == 0) ? omega : ((v + nonempty * omega - 1) / (nonempty * omega)) * omega;
+}
+
+// squared deviations of the degrees and the item counts under Eq. (3)'s SG
+__global__ void __launch_bounds__(kThreads) features_deviation_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
+                                                                      const int32_t *shared, const RowPart *parts,
+                                                                      int n_parts, int32_t omega, DevPart *out)
+{
+    __shared__ double s_d, s_d_hat;
+    __shared__ long s_sg1, s_sg2;
+    const RowPart r = sum_row_parts(parts, n_parts);
+    if (threadIdx.x == 0) {
+        s_d = (double)nnz / (double)n_rows;
+        s_d_hat = r.n_hat ? (double)nnz / (double)r.n_hat : 0.0;
+        s_sg1 = eq3_sg(nnz, r.n_hat, omega);
+        s_sg2 = eq3_sg(nnz - r.shared, r.nonempty2, omega);
+    }
+    __syncthreads();
+    const double d = s_d, d_hat = s_d_hat;
+    const long sg1 = s_sg1, sg2 = s_sg2;
+    DevPart a = {0.0, 0.0, 0, 0};
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * kThreads) {
+        const int l = rowptr[i + 1] - rowptr[i];
+        a.ss += ((double)l - d) * ((double)l - d);
+        if (l > 0) a.ss_hat += ((double)l - d_hat) * ((double)l - d_hat);
+        const long m1 = (l + sg1 - 1) / sg1;
+        a.M1 += m1 < 1 ? 1 : m1;
+        if ((i & 1) == 0) {
+            const long m2 = (panel_len(rowptr, shared, i >> 1, n_rows) + sg2 - 1) / sg2;
+            a.M2 += m2 < 1 ? 1 : m2;
+        }
+    }
+    typedef hipcub::BlockReduce<DevPart, kThreads> Reduce;
+    __shared__ typename Reduce::TempStorage tmp;
+    a = Reduce(tmp).Reduce(a, DevPartSum());
+    if (threadIdx.x == 0) out[blockIdx.x] = a;
+}
+
+__global__ void __launch_bounds__(kThreads) features_final_kernel(int64_t nnz, const RowPart *parts, int n_parts,
+                                                                  const DevPart *devs, int n_devs,
+                                                                  const long long *near_in, int n_near, FeatAcc *out)
+{
+    const RowPart r = sum_row_parts(parts, n_parts);
+    typedef hipcub::BlockReduce<DevPart, kThreads> ReduceD;
+    typedef hipcub::BlockReduce<long long, kThreads> ReduceL;
+    __shared__ typename ReduceD::TempStorage t1;
+    __shared__ typename ReduceL::TempStorage t2;
+    DevPart d = {0.0, 0.0, 0, 0};
+    for (int i = threadIdx.x; i < n_devs; i += kThreads) d = DevPartSum()(d, devs[i]);
+    d = ReduceD(t1).Reduce(d, DevPartSum());
+    long long near = 0;
+    for (int i = threadIdx.x; i < n_near; i += kThreads) near += near_in[i];
+    near = ReduceL(t2).Sum(near);
+    if (threadIdx.x == 0)
+        *out = {r.n_hat, nnz - r.shared, r.nonempty2, d.M1, d.M2, near, r.bw_sum, r.bw_max, d.ss, d.ss_hat, r.d_max, 0};
+}
+
+struct Scratch { // gives back everything it still owns on scope exit
+    void *p[40] = {};
     int n = 0;
     hipError_t alloc(void **out, size_t bytes)
     {
-        if (n >= 32) return hipErrorOutOfMemory;
-        hipError_t e = hipMalloc(out, bytes ? bytes : 16);
+        if (n >= 40) return hipErrorOutOfMemory;
+        hipError_t e = pool_alloc(out, bytes);
         if (e == hipSuccess) p[n++] = *out;
         return e;
     }
@@ -471,8 +756,9 @@ struct Scratch { // frees everything it still owns on scope exit
     }
     ~Scratch()
     {
-        for (int i = 0; i < n; ++i)
-            if (p[i]) (void)hipFree(p[i]);
+        // everything here runs on the null stream; idle by now unless an error cut it short
+        (void)hipStreamSynchronize(nullptr);
+        for (int i = 0; i < n; ++i) pool_free(p[i]);
     }
 };
 
@@ -494,95 +780,47 @@ hipError_t exclusive_scan(const int32_t *in, int32_t *out, int64_t n, Scratch &s
     void *tmp = nullptr;
     e = sc.alloc(&tmp, bytes);
     if (e != hipSuccess) return e;
-    e = hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, (int)n);
-    return e;
-}
-
-hipError_t exclusive_scan64(const long long *in, long long *out, int64_t n, Scratch &sc)
-{
-    size_t bytes = 0;
-    hipError_t e = hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, (int)n);
-    if (e != hipSuccess) return e;
-    void *tmp = nullptr;
-    e = sc.alloc(&tmp, bytes);
-    if (e != hipSuccess) return e;
     return hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, (int)n);
 }
 
-// Column-ordered schedule from the balanced arrays (all device pointers): fills *sched_out
-// (4 int32 per launch position, ownership to the caller) and the position bounds per XCD.
-int schedule_by_column_device(int64_t M, int64_t n_long, const int32_t *rowptr, const int32_t *colidx,
-                              const int32_t *trow, const int32_t *item_slot, int32_t **sched_out,
-                              int32_t xcd_bounds[9], int *hip_err)
+// bits of the largest key below n
+int key_bits(int64_t n)
 {
-    Scratch sc;
-    const int64_t n_short = M - n_long;
-    int32_t *flag = nullptr, *lrank = nullptr, *long_key = nullptr, *long_item = nullptr, *short_item = nullptr;
-    int32_t *key_sorted = nullptr, *long_sorted = nullptr, *d_bounds = nullptr, *sched = nullptr;
-    long long *w_l = nullptr, *w_s = nullptr, *cum_l = nullptr, *cum_s = nullptr;
-    HIP_TRY(sc.alloc((void **)&flag, sizeof(int32_t) * (M + 1)));
-    HIP_TRY(sc.alloc((void **)&lrank, sizeof(int32_t) * (M + 1)));
-    HIP_TRY(sc.alloc((void **)&long_key, sizeof(int32_t) * (n_long + 1)));
-    HIP_TRY(sc.alloc((void **)&long_item, sizeof(int32_t) * (n_long + 1)));
-    HIP_TRY(sc.alloc((void **)&key_sorted, sizeof(int32_t) * (n_long + 1)));
-    HIP_TRY(sc.alloc((void **)&long_sorted, sizeof(int32_t) * (n_long + 1)));
-    HIP_TRY(sc.alloc((void **)&short_item, sizeof(int32_t) * (n_short + 1)));
-    HIP_TRY(sc.alloc((void **)&w_l, sizeof(long long) * (n_long + 1)));
-    HIP_TRY(sc.alloc((void **)&w_s, sizeof(long long) * (n_short + 1)));
-    HIP_TRY(sc.alloc((void **)&cum_l, sizeof(long long) * (n_long + 1)));
-    HIP_TRY(sc.alloc((void **)&cum_s, sizeof(long long) * (n_short + 1)));
-    HIP_TRY(sc.alloc((void **)&d_bounds, sizeof(int32_t) * 27));
-    HIP_TRY(sc.alloc((void **)&sched, sizeof(int32_t) * 4 * (M + 1)));
+    int b = 1;
+    while (b < 32 && (int64_t(1) << b) < n) ++b;
+    return b;
+}
 
-    hipLaunchKernelGGL(sched_flag_kernel, dim3(blocks_for(M + 1)), dim3(kThreads), 0, 0, M, item_slot, flag);
+int check_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
+                 bool validate, Scratch &sc, Checked **d_out, Checked *h, int *hip_err)
+{
+    Checked *d = nullptr;
+    HIP_TRY(sc.alloc((void **)&d, sizeof(Checked)));
+    HIP_TRY(hipMemsetAsync(d, 0, sizeof(Checked), nullptr));
+    hipLaunchKernelGGL(validate_rows_kernel, dim3(strided_blocks(n_rows, 1024)), dim3(kThreads), 0, 0, n_rows, nnz,
+                       d_rowptr, d_colidx, validate && nnz > 0 ? 1 : 0, d);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(exclusive_scan(flag, lrank, M + 1, sc));
-    if (M > 0) {
-        hipLaunchKernelGGL(sched_lists_kernel, dim3(blocks_for(M)), dim3(kThreads), 0, 0, M, rowptr, colidx,
-                           item_slot, lrank, long_key, long_item, short_item);
+    if (validate && nnz > 0) {
+        hipLaunchKernelGGL(validate_cols_kernel, dim3(strided_blocks(nnz)), dim3(kThreads), 0, 0, n_cols, nnz, d_colidx,
+                           d);
         HIP_TRY(hipGetLastError());
     }
-    if (n_long > 0) {
-        // stable: equal first columns stay in item order, as on the host
-        size_t bytes = 0;
-        HIP_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, bytes, long_key, key_sorted, long_item, long_sorted,
-                                                   (int)n_long));
-        void *tmp = nullptr;
-        HIP_TRY(sc.alloc(&tmp, bytes));
-        HIP_TRY(hipcub::DeviceRadixSort::SortPairs(tmp, bytes, long_key, key_sorted, long_item, long_sorted,
-                                                   (int)n_long));
-    }
-    hipLaunchKernelGGL(sched_weights_kernel, dim3(blocks_for(n_long + 1)), dim3(kThreads), 0, 0, n_long,
-                       long_sorted, rowptr, w_l);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(sched_weights_kernel, dim3(blocks_for(n_short + 1)), dim3(kThreads), 0, 0, n_short,
-                       short_item, rowptr, w_s);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(exclusive_scan64(w_l, cum_l, n_long + 1, sc));
-    HIP_TRY(exclusive_scan64(w_s, cum_s, n_short + 1, sc));
-    hipLaunchKernelGGL(sched_bounds_kernel, dim3(1), dim3(64), 0, 0, (long)n_long, cum_l, (long)n_short, cum_s,
-                       d_bounds);
-    HIP_TRY(hipGetLastError());
-    if (n_long > 0) {
-        hipLaunchKernelGGL(sched_emit_kernel, dim3(blocks_for(n_long)), dim3(kThreads), 0, 0, n_long, long_sorted,
-                           0, d_bounds, rowptr, trow, item_slot, reinterpret_cast<int4 *>(sched));
-        HIP_TRY(hipGetLastError());
-    }
-    if (n_short > 0) {
-        hipLaunchKernelGGL(sched_emit_kernel, dim3(blocks_for(n_short)), dim3(kThreads), 0, 0, n_short, short_item,
-                           1, d_bounds, rowptr, trow, item_slot, reinterpret_cast<int4 *>(sched));
-        HIP_TRY(hipGetLastError());
-    }
-    int32_t h_bounds[27];
-    HIP_TRY(hipMemcpy(h_bounds, d_bounds, sizeof(h_bounds), hipMemcpyDeviceToHost));
-    for (int x = 0; x < 9; ++x) xcd_bounds[x] = h_bounds[18 + x];
-    HIP_TRY(hipDeviceSynchronize());
-    *sched_out = sched;
-    sc.release(sched);
+    HIP_TRY(hipMemcpy(h, d, sizeof(Checked), hipMemcpyDeviceToHost));
+    *d_out = d;
+    if (h->first != 0 || h->last != nnz) return PCSR_E_BAD_CSR;
+    if (validate && (h->bad || h->descents != h->start_descents)) return PCSR_E_BAD_CSR;
     return PCSR_OK;
 }
 
 } // namespace
+
+int validate_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
+                    int *hip_err)
+{
+    Scratch sc;
+    Checked *d = nullptr, h;
+    return check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, true, sc, &d, &h, hip_err);
+}
 
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
@@ -593,180 +831,180 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
     Scratch sc;
     const int64_t P = (n_rows + V - 1) / V;
 
-    // the row pointer must start at 0 and end at nnz
-    int32_t ends[2] = {0, 0};
-    HIP_TRY(hipMemcpy(&ends[0], d_rowptr, sizeof(int32_t), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(&ends[1], d_rowptr + n_rows, sizeof(int32_t), hipMemcpyDeviceToHost));
-    if (ends[0] != 0 || ends[1] != nnz) return PCSR_E_BAD_CSR;
-
-    int *d_flags = nullptr; // [0] bad csr, [1] longest panel; [4..5] nonempty (64 bit)
-    HIP_TRY(sc.alloc((void **)&d_flags, 8 * sizeof(int)));
-    HIP_TRY(hipMemset(d_flags, 0, 8 * sizeof(int)));
-    if (validate && n_rows > 0) {
-        hipLaunchKernelGGL(validate_kernel, dim3(blocks_for(n_rows)), dim3(kThreads), 0, 0, n_rows, n_cols,
-                           nnz, d_rowptr, d_colidx, d_flags);
-        HIP_TRY(hipGetLastError());
-        int bad = 0;
-        HIP_TRY(hipMemcpy(&bad, d_flags, sizeof(int), hipMemcpyDeviceToHost));
-        if (bad) return PCSR_E_BAD_CSR;
-    }
+    Checked *d_check = nullptr, check;
+    int rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, validate, sc, &d_check, &check, hip_err);
+    if (rc != PCSR_OK) return rc;
 
     // ---- vectorised blocking
     int32_t *prow = nullptr, *pcol = nullptr;
+    const int32_t *panels = d_rowptr; // row pointer of the panels
     float *pval = nullptr;
     int64_t nnz_v = nnz;
-    HIP_TRY(sc.alloc((void **)&prow, sizeof(int32_t) * (P + 1)));
     if (V == 1) {
-        HIP_TRY(hipMemcpy(prow, d_rowptr, sizeof(int32_t) * (n_rows + 1), hipMemcpyDeviceToDevice));
         HIP_TRY(sc.alloc((void **)&pcol, sizeof(int32_t) * (nnz + 1)));
         HIP_TRY(sc.alloc((void **)&pval, sizeof(float) * (nnz + 1)));
         if (nnz) {
-            HIP_TRY(hipMemcpy(pcol, d_colidx, sizeof(int32_t) * nnz, hipMemcpyDeviceToDevice));
-            HIP_TRY(hipMemcpy(pval, d_vals, sizeof(float) * nnz, hipMemcpyDeviceToDevice));
+            HIP_TRY(hipMemcpyAsync(pcol, d_colidx, sizeof(int32_t) * nnz, hipMemcpyDeviceToDevice, nullptr));
+            HIP_TRY(hipMemcpyAsync(pval, d_vals, sizeof(float) * nnz, hipMemcpyDeviceToDevice, nullptr));
+        }
+        if (!S) {
+            HIP_TRY(sc.alloc((void **)&prow, sizeof(int32_t) * (P + 1)));
+            HIP_TRY(hipMemcpyAsync(prow, d_rowptr, sizeof(int32_t) * (n_rows + 1), hipMemcpyDeviceToDevice, nullptr));
+            panels = prow;
         }
     } else {
         if (nnz + 1 > 0x7fffffffLL) return PCSR_E_TOO_LARGE; // the scan below counts in int32
         int32_t *cnt = nullptr, *shared = nullptr, *shared_scan = nullptr;
+        HIP_TRY(sc.alloc((void **)&prow, sizeof(int32_t) * (P + 1)));
+        panels = prow;
         HIP_TRY(sc.alloc((void **)&cnt, sizeof(int32_t) * (P + 1)));
         HIP_TRY(sc.alloc((void **)&shared, sizeof(int32_t) * (nnz + 1)));
         HIP_TRY(sc.alloc((void **)&shared_scan, sizeof(int32_t) * (nnz + 1)));
-        hipLaunchKernelGGL(union_shared_kernel, dim3(blocks_for(nnz + 1)), dim3(kThreads), 0, 0, n_rows, nnz,
-                           d_rowptr, d_colidx, shared);
+        const unsigned slices = (unsigned)((nnz + 1 + kSlice - 1) / kSlice);
+        hipLaunchKernelGGL(union_shared_kernel, dim3(slices), dim3(kThreads), 0, 0, n_rows, nnz, d_rowptr, d_colidx,
+                           shared);
         HIP_TRY(hipGetLastError());
         HIP_TRY(exclusive_scan(shared, shared_scan, nnz + 1, sc));
         hipLaunchKernelGGL(union_count_kernel, dim3(blocks_for(P + 1)), dim3(kThreads), 0, 0, P, n_rows,
                            d_rowptr, shared_scan, cnt);
         HIP_TRY(hipGetLastError());
         HIP_TRY(exclusive_scan(cnt, prow, P + 1, sc));
+        HIP_TRY(hipMemsetAsync(d_check, 0, sizeof(Checked), nullptr));
+        hipLaunchKernelGGL(panel_stats_kernel, dim3(strided_blocks(P, 1024)), dim3(kThreads), 0, 0, P, prow, d_check);
+        HIP_TRY(hipGetLastError());
         int32_t total = 0;
-        HIP_TRY(hipMemcpy(&total, prow + P, sizeof(int32_t), hipMemcpyDeviceToHost));
+        HIP_TRY(hipMemcpyAsync(&total, prow + P, sizeof(int32_t), hipMemcpyDeviceToHost, nullptr));
+        HIP_TRY(hipMemcpy(&check, d_check, sizeof(Checked), hipMemcpyDeviceToHost));
         nnz_v = total;
         HIP_TRY(sc.alloc((void **)&pcol, sizeof(int32_t) * (nnz_v + 1)));
         HIP_TRY(sc.alloc((void **)&pval, sizeof(float) * (2 * nnz_v + 1)));
         if (nnz > 0) {
-            hipLaunchKernelGGL(union_fill_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, 0, n_rows, nnz,
-                               d_rowptr, d_colidx, d_vals, shared_scan, prow, pcol, pval);
+            hipLaunchKernelGGL(union_fill_kernel, dim3((unsigned)((nnz + kSlice - 1) / kSlice)), dim3(kThreads), 0, 0,
+                               n_rows, nnz, d_rowptr, d_colidx, d_vals, shared_scan, prow, pcol, pval);
             HIP_TRY(hipGetLastError());
         }
     }
 
     // ---- Eq. (3) from the panel lengths
-    if (P > 0) {
-        hipLaunchKernelGGL(panel_stats_kernel, dim3(blocks_for(P)), dim3(kThreads), 0, 0, P, prow,
-                           reinterpret_cast<unsigned long long *>(d_flags + 4), d_flags + 1);
-        HIP_TRY(hipGetLastError());
-    }
-    int h_flags[8];
-    HIP_TRY(hipMemcpy(h_flags, d_flags, sizeof(h_flags), hipMemcpyDeviceToHost));
-    unsigned long long nonempty = 0;
-    memcpy(&nonempty, &h_flags[4], sizeof(nonempty));
-    const int64_t longest = h_flags[1];
     int64_t sg = SG;
     if (sg <= 0) {
-        sg = (nnz_v == 0 || nonempty == 0)
-                 ? omega
-                 : ((nnz_v + (int64_t)nonempty * omega - 1) / ((int64_t)nonempty * omega)) * omega;
+        const int64_t nonempty = check.nonempty;
+        sg = (nnz_v == 0 || nonempty == 0) ? omega : ((nnz_v + nonempty * omega - 1) / (nonempty * omega)) * omega;
     }
     if (sg >= (int64_t(1) << 31)) return PCSR_E_TOO_LARGE;
 
     out->P = P;
     out->nnz_v = nnz_v;
     out->SG = (int32_t)sg;
-    out->n_split = 0;
-    out->n_split_items = 0;
-    out->trow = nullptr;
-    out->split = nullptr;
-    out->item_slot = nullptr;
-    out->split_slot = nullptr;
+    int32_t *d_bounds = nullptr;
+    HIP_TRY(sc.alloc((void **)&d_bounds, 27 * sizeof(int32_t)));
 
-    int32_t *final_rowptr = prow;
-    int64_t M = P;
     if (!S) {
-        out->max_item_len = longest;
+        out->M = P;
+        out->max_item_len = check.longest;
+        hipLaunchKernelGGL(xcd_bounds_kernel, dim3(1), dim3(64), 0, 0, (int32_t)P, prow, d_bounds);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipMemcpy(out->xcd_bounds, d_bounds, 9 * sizeof(int32_t), hipMemcpyDeviceToHost));
     } else {
         if (P + nnz_v / sg >= (int64_t(1) << 31) - 2) return PCSR_E_TOO_LARGE;
-        int32_t *items = nullptr, *first = nullptr;
-        HIP_TRY(sc.alloc((void **)&items, sizeof(int32_t) * (P + 1)));
-        HIP_TRY(sc.alloc((void **)&first, sizeof(int32_t) * (P + 1)));
-        hipLaunchKernelGGL(items_kernel, dim3(blocks_for(P + 1)), dim3(kThreads), 0, 0, P, prow, (int32_t)sg,
-                           items);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(exclusive_scan(items, first, P + 1, sc));
-        int32_t m32 = 0;
-        HIP_TRY(hipMemcpy(&m32, first + P, sizeof(int32_t), hipMemcpyDeviceToHost));
-        M = m32;
-        // panels that were split: ascending list, first workspace slot of each
-        int32_t *mark = nullptr, *cnt = nullptr, *qpos = nullptr, *slotbase = nullptr;
-        HIP_TRY(sc.alloc((void **)&mark, sizeof(int32_t) * (P + 1)));
-        HIP_TRY(sc.alloc((void **)&cnt, sizeof(int32_t) * (P + 1)));
-        HIP_TRY(sc.alloc((void **)&qpos, sizeof(int32_t) * (P + 1)));
-        HIP_TRY(sc.alloc((void **)&slotbase, sizeof(int32_t) * (P + 1)));
-        hipLaunchKernelGGL(split_marks_kernel, dim3(blocks_for(P + 1)), dim3(kThreads), 0, 0, P, items, mark,
-                           cnt);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(exclusive_scan(mark, qpos, P + 1, sc));
-        HIP_TRY(exclusive_scan(cnt, slotbase, P + 1, sc));
-        int32_t n_split = 0, n_split_items = 0;
-        HIP_TRY(hipMemcpy(&n_split, qpos + P, sizeof(int32_t), hipMemcpyDeviceToHost));
-        HIP_TRY(hipMemcpy(&n_split_items, slotbase + P, sizeof(int32_t), hipMemcpyDeviceToHost));
-
-        int32_t *srow = nullptr, *trow = nullptr, *item_slot = nullptr;
-        HIP_TRY(sc.alloc((void **)&srow, sizeof(int32_t) * (M + 1)));
-        HIP_TRY(sc.alloc((void **)&trow, sizeof(int32_t) * (M + 1)));
-        HIP_TRY(sc.alloc((void **)&item_slot, sizeof(int32_t) * (M + 1)));
+        const int64_t chunks = (P + kSplitPanels - 1) / kSplitPanels;
+        SplitCount *sums = nullptr, total = {0, 0, 0, 0};
+        HIP_TRY(sc.alloc((void **)&sums, sizeof(SplitCount) * (chunks + 1)));
         if (P > 0) {
-            hipLaunchKernelGGL(split_fill_kernel, dim3(blocks_for(P)), dim3(kThreads), 0, 0, P, prow, first,
-                               slotbase, (int32_t)sg, srow, trow, item_slot);
+            hipLaunchKernelGGL(split_sums_kernel, dim3((unsigned)chunks), dim3(kThreads), 0, 0, P, panels, (int32_t)sg,
+                               sums);
+            HIP_TRY(hipGetLastError());
+            hipLaunchKernelGGL(split_scan_kernel, dim3(1), dim3(1024), 0, 0, (int)chunks, sums);
+            HIP_TRY(hipGetLastError());
+            HIP_TRY(hipMemcpy(&total, sums + chunks, sizeof(total), hipMemcpyDeviceToHost));
+        }
+        const int64_t M = total.items, n_long = total.slots, n_short = M - n_long;
+        SplitOut o = {};
+        HIP_TRY(sc.alloc((void **)&o.rowptr, sizeof(int32_t) * (M + 1)));
+        HIP_TRY(sc.alloc((void **)&o.trow, sizeof(int32_t) * (M + 1)));
+        HIP_TRY(sc.alloc((void **)&o.item_slot, sizeof(int32_t) * (M + 1)));
+        HIP_TRY(sc.alloc((void **)&o.split_panels, sizeof(int32_t) * (total.split + 1)));
+        HIP_TRY(sc.alloc((void **)&o.split_slot, sizeof(int32_t) * (total.split + 1)));
+        if (total.longp) HIP_TRY(sc.alloc((void **)&o.long_list, sizeof(int32_t) * total.longp));
+        if (column_order) {
+            HIP_TRY(sc.alloc((void **)&o.long_key, sizeof(int32_t) * (n_long + 1)));
+            HIP_TRY(sc.alloc((void **)&o.long_item, sizeof(int32_t) * (n_long + 1)));
+            HIP_TRY(sc.alloc((void **)&o.short_item, sizeof(int32_t) * (n_short + 1)));
+        }
+        if (P > 0) {
+            hipLaunchKernelGGL(split_fill_kernel, dim3((unsigned)chunks), dim3(kThreads), 0, 0, P, panels, pcol,
+                               (int32_t)sg, sums, o);
             HIP_TRY(hipGetLastError());
         } else {
-            HIP_TRY(hipMemset(srow, 0, sizeof(int32_t)));
+            HIP_TRY(hipMemsetAsync(o.rowptr, 0, sizeof(int32_t), nullptr));
+            HIP_TRY(hipMemsetAsync(o.split_slot, 0, sizeof(int32_t), nullptr));
         }
-        int32_t *split = nullptr, *split_slot = nullptr;
-        HIP_TRY(sc.alloc((void **)&split, sizeof(int32_t) * (n_split + 1)));
-        HIP_TRY(sc.alloc((void **)&split_slot, sizeof(int32_t) * (n_split + 1)));
-        hipLaunchKernelGGL(split_tables_kernel, dim3(blocks_for(P + 1)), dim3(kThreads), 0, 0, P, items, qpos,
-                           slotbase, split, split_slot);
-        HIP_TRY(hipGetLastError());
-        out->n_split = n_split;
-        out->n_split_items = n_split_items;
+        int32_t *sched = nullptr;
+        if (column_order) {
+            HIP_TRY(sc.alloc((void **)&sched, sizeof(int32_t) * 4 * (M + 1)));
+            int32_t *sorted = nullptr;
+            if (n_long > 0) {
+                // stable: equal first columns stay in item order, as on the host
+                int32_t *key_sorted = nullptr;
+                void *tmp = nullptr;
+                size_t bytes = 0;
+                const int bits = key_bits(n_cols);
+                HIP_TRY(sc.alloc((void **)&key_sorted, sizeof(int32_t) * n_long));
+                HIP_TRY(sc.alloc((void **)&sorted, sizeof(int32_t) * n_long));
+                HIP_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, bytes, o.long_key, key_sorted, o.long_item, sorted,
+                                                           (int)n_long, 0, bits));
+                HIP_TRY(sc.alloc(&tmp, bytes));
+                HIP_TRY(hipcub::DeviceRadixSort::SortPairs(tmp, bytes, o.long_key, key_sorted, o.long_item, sorted,
+                                                           (int)n_long, 0, bits));
+            }
+            const int64_t cl = (n_long + kSchedChunk - 1) / kSchedChunk, cs = (n_short + kSchedChunk - 1) / kSchedChunk;
+            long long *wsum = nullptr, *wscan = nullptr;
+            HIP_TRY(sc.alloc((void **)&wsum, sizeof(long long) * (cl + cs + 1)));
+            HIP_TRY(sc.alloc((void **)&wscan, sizeof(long long) * (cl + cs + 2)));
+            if (cl + cs > 0) {
+                hipLaunchKernelGGL(sched_sums_kernel, dim3((unsigned)(cl + cs)), dim3(kThreads), 0, 0, n_long, sorted,
+                                   n_short, o.short_item, o.rowptr, wsum);
+                HIP_TRY(hipGetLastError());
+            }
+            hipLaunchKernelGGL(sched_scan_kernel, dim3(2), dim3(1024), 0, 0, (int)cl, (int)cs, wsum, wscan);
+            HIP_TRY(hipGetLastError());
+            hipLaunchKernelGGL(sched_bounds_kernel, dim3(18), dim3(kThreads), 0, 0, n_long, sorted, n_short,
+                               o.short_item, o.rowptr, wscan, d_bounds);
+            HIP_TRY(hipGetLastError());
+            if (M > 0) {
+                hipLaunchKernelGGL(sched_emit_kernel, dim3(blocks_for(M)), dim3(kThreads), 0, 0, n_long, sorted, n_short,
+                                   o.short_item, d_bounds, o.rowptr, o.trow, o.item_slot,
+                                   reinterpret_cast<int4 *>(sched));
+                HIP_TRY(hipGetLastError());
+            }
+            int32_t b[18];
+            HIP_TRY(hipMemcpy(b, d_bounds, sizeof(b), hipMemcpyDeviceToHost));
+            for (int x = 0; x < 9; ++x) out->xcd_bounds[x] = b[x] + b[9 + x];
+        } else {
+            hipLaunchKernelGGL(xcd_bounds_kernel, dim3(1), dim3(64), 0, 0, (int32_t)M, o.rowptr, d_bounds);
+            HIP_TRY(hipGetLastError());
+            HIP_TRY(hipMemcpy(out->xcd_bounds, d_bounds, 9 * sizeof(int32_t), hipMemcpyDeviceToHost));
+        }
+        out->M = M;
+        out->n_split = total.split;
+        out->n_split_items = total.slots;
+        out->n_long = total.longp;
         out->max_item_len = sg < nnz_v ? sg : nnz_v;
-        out->trow = trow;
-        out->split = split;
-        out->item_slot = item_slot;
-        out->split_slot = split_slot;
-        sc.release(trow);
-        sc.release(split);
-        sc.release(item_slot);
-        sc.release(split_slot);
-        final_rowptr = srow;
+        out->trow = o.trow;
+        out->split = o.split_panels;
+        out->item_slot = o.item_slot;
+        out->split_slot = o.split_slot;
+        out->long_list = o.long_list;
+        out->sched = sched;
+        for (void *q : {(void *)o.trow, (void *)o.split_panels, (void *)o.item_slot, (void *)o.split_slot,
+                        (void *)o.long_list, (void *)sched})
+            sc.release(q);
+        prow = o.rowptr;
     }
-    out->M = M;
-
-    int32_t *d_xb = nullptr;
-    HIP_TRY(sc.alloc((void **)&d_xb, 9 * sizeof(int32_t)));
-    hipLaunchKernelGGL(xcd_bounds_kernel, dim3(1), dim3(64), 0, 0, (int32_t)M, final_rowptr, d_xb);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpy(out->xcd_bounds, d_xb, 9 * sizeof(int32_t), hipMemcpyDeviceToHost));
-    HIP_TRY(hipDeviceSynchronize());
-    out->sched = nullptr;
-    if (S && column_order) {
-        const int rc = schedule_by_column_device(M, out->n_split_items, final_rowptr, pcol, out->trow,
-                                                 out->item_slot, &out->sched, out->xcd_bounds, hip_err);
-        if (rc != PCSR_OK) {
-            // the arrays already handed to *out go back to the caller's clean-up
-            (void)hipFree(out->trow);
-            (void)hipFree(out->split);
-            (void)hipFree(out->item_slot);
-            (void)hipFree(out->split_slot);
-            out->trow = out->split = out->item_slot = out->split_slot = nullptr;
-            return rc;
-        }
-    }
-
-    out->rowptr = final_rowptr;
+    out->rowptr = prow;
     out->colidx = pcol;
     out->val = pval;
-    sc.release(final_rowptr);
+    sc.release(prow);
     sc.release(pcol);
     sc.release(pval);
     return PCSR_OK;
@@ -776,33 +1014,43 @@ int features_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *
                     const int32_t *d_colidx, int32_t omega, double *out, int *hip_err)
 {
     if (omega == 0) omega = 64;
-    Scratch sc;
-    FeatAcc *d_acc = nullptr;
-    int32_t *len2 = nullptr;
-    const int64_t P2 = (n_rows + 1) / 2;
-    HIP_TRY(sc.alloc((void **)&d_acc, sizeof(FeatAcc)));
-    HIP_TRY(sc.alloc((void **)&len2, sizeof(int32_t) * (P2 + 1)));
-    HIP_TRY(hipMemset(d_acc, 0, sizeof(FeatAcc)));
     FeatAcc h;
     memset(&h, 0, sizeof(h));
+    const int64_t P2 = (n_rows + 1) / 2;
     if (n_rows > 0) {
-        hipLaunchKernelGGL(features_pass1_kernel, dim3(blocks_for(n_rows)), dim3(kThreads), 0, 0, n_rows,
-                           d_rowptr, d_colidx, len2, d_acc);
+        Scratch sc;
+        const unsigned rb = strided_blocks(n_rows, kFeatBlocks);
+        const int64_t slices = (nnz + kSlice - 1) / kSlice;
+        const unsigned nb = (unsigned)(slices < kNearBlocks ? slices : kNearBlocks);
+        int32_t *shared = nullptr;
+        RowPart *rows = nullptr;
+        DevPart *devs = nullptr;
+        long long *near = nullptr;
+        FeatAcc *acc = nullptr;
+        HIP_TRY(sc.alloc((void **)&shared, sizeof(int32_t) * P2));
+        HIP_TRY(sc.alloc((void **)&rows, sizeof(RowPart) * rb));
+        HIP_TRY(sc.alloc((void **)&devs, sizeof(DevPart) * rb));
+        HIP_TRY(sc.alloc((void **)&near, sizeof(long long) * (nb + 1)));
+        HIP_TRY(sc.alloc((void **)&acc, sizeof(FeatAcc)));
+        HIP_TRY(hipMemsetAsync(shared, 0, sizeof(int32_t) * P2, nullptr));
+        if (nb) {
+            hipLaunchKernelGGL(features_nonzeros_kernel, dim3(nb), dim3(kThreads), 0, 0, n_rows, nnz, d_rowptr, d_colidx,
+                               shared, near);
+            HIP_TRY(hipGetLastError());
+        }
+        hipLaunchKernelGGL(features_rows_kernel, dim3(rb), dim3(kThreads), 0, 0, n_rows, d_rowptr, d_colidx, shared,
+                           rows);
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpy(&h, d_acc, sizeof(h), hipMemcpyDeviceToHost));
+        hipLaunchKernelGGL(features_deviation_kernel, dim3(rb), dim3(kThreads), 0, 0, n_rows, nnz, d_rowptr, shared,
+                           rows, (int)rb, omega, devs);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(features_final_kernel, dim3(1), dim3(kThreads), 0, 0, nnz, rows, (int)rb, devs, (int)rb,
+                           near, (int)nb, acc);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipMemcpy(&h, acc, sizeof(h), hipMemcpyDeviceToHost));
     }
     const double d = n_rows ? double(nnz) / double(n_rows) : 0.0;
     const double d_hat = h.n_hat ? double(nnz) / double(h.n_hat) : 0.0;
-    auto eq3 = [&](int64_t v, int64_t ne) -> int64_t {
-        return (v == 0 || ne == 0) ? omega : ((v + ne * omega - 1) / (ne * omega)) * omega;
-    };
-    const int64_t sg1 = eq3(nnz, (int64_t)h.n_hat), sg2 = eq3((int64_t)h.nnz2, (int64_t)h.nonempty2);
-    if (n_rows > 0) {
-        hipLaunchKernelGGL(features_pass2_kernel, dim3(blocks_for(n_rows)), dim3(kThreads), 0, 0, n_rows,
-                           d_rowptr, len2, d, d_hat, (long)sg1, (long)sg2, d_acc);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpy(&h, d_acc, sizeof(h), hipMemcpyDeviceToHost));
-    }
     out[0] = double(n_rows);
     out[1] = double(h.n_hat);
     out[2] = double(nnz);

@@ -1,0 +1,29 @@
+// Device memory of the library: handles, workspaces and the scratch of the set-up calls come
+// from a cache of freed blocks, one per GPU.  A build needs some twenty arrays; released with
+// hipFree they cost 2-5 ms per build of a 16 M-nonzero graph (each large hipFree unmaps its
+// pages and waits for the device), a third of building, multiplying and releasing it.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+#include <cstdint>
+
+namespace pcsr {
+
+// Blocks kept for reuse per GPU at most; beyond it the longest unused go back to the driver, and
+// so does a block that kPoolIdleAllocs allocations have passed over.  All of them go back
+// before an allocation is reported as out of memory.
+constexpr size_t kPoolBytes = size_t(1) << 30;
+constexpr uint64_t kPoolIdleAllocs = 1024;
+
+// On the current device.  Thread safe.  Contents are undefined.
+hipError_t pool_alloc(void **p, size_t bytes);
+// No work that uses the block may be running or enqueued: the caller has waited for the device
+// (pool_quiesce) or for the stream that used it.  nullptr is a no-op.
+void pool_free(void *p);
+// Waits for a device, as hipFree would.  false: that failed (a stream capture in progress, say)
+// and the blocks have to go back through pool_release instead.
+bool pool_quiesce(int device);
+void pool_release(void *p); // hipFree, past the cache
+
+} // namespace pcsr
