@@ -85,6 +85,7 @@ def _lib():
         lib.pcsr_strerror.restype = ctypes.c_char_p
         lib.pcsr_last_hip_error.restype = ctypes.c_int
         lib.pcsr_spmm_epilogue.argtypes = [vp, vp, vp, i32, ctypes.POINTER(pcsr_epilogue_t), vp]
+        lib.pcsr_operator_build.argtypes = [i64, i64, i64, vp, vp, vp, pp, i32, i32, ctypes.POINTER(vp * 2)]
         lib.pcsr_gnn_workspace_floats.argtypes = [i32, i32]
         lib.pcsr_gnn_workspace_floats.restype = i64
         lib.pcsr_gnn_linear.argtypes = [i64, i32, i32, vp, vp, i32, vp, i32, vp, vp, vp, vp, vp, vp, vp]
@@ -95,7 +96,7 @@ def _lib():
                      "pcsr_window_stats", "pcsr_features_device", "pcsr_reorder", "pcsr_permute_csr",
                      "pcsr_transpose_csr", "pcsr_workspace_bytes", "pcsr_reserve_workspace", "pcsr_spmm_static",
                      "pcsr_export_schedule", "pcsr_reorder_by_degree", "pcsr_spmm_epilogue", "pcsr_gnn_linear",
-                     "pcsr_gnn_wgrad", "pcsr_gnn_colsum"):
+                     "pcsr_gnn_wgrad", "pcsr_gnn_colsum", "pcsr_operator_build"):
             getattr(lib, name).restype = ctypes.c_int
         _LIB = lib
     return _LIB
@@ -167,6 +168,36 @@ def pcsr_build(n_rows, n_cols, rowptr, colidx, vals, params=None) -> Handle:
     if rc != PCSR_OK:
         raise PcsrError(rc, "pcsr_build")
     return Handle(out.value, n_rows, n_cols)
+
+
+PCSR_OPERATOR_SELECT = 1
+
+
+def pcsr_operator_build(n_rows, n_cols, rowptr, colidx, vals, params, K, transpose):
+    """Handles of A and, if asked for, of its transpose (else None); params None = the library's pick for K."""
+    k0, p_r, dev_r = _ptr(rowptr, np.dtype(np.int32))
+    k1, p_c, dev_c = _ptr(colidx, np.dtype(np.int32))
+    k2, p_v, dev_v = _ptr(vals, np.dtype(np.float32))
+    if int(k0.shape[0]) != n_rows + 1:
+        raise ValueError("rowptr must have n_rows + 1 entries")
+    if int(k2.shape[0]) != int(k1.shape[0]):
+        raise ValueError("vals and colidx differ in length")
+    if dev_r != dev_c or dev_r != dev_v:
+        raise ValueError("CSR arrays must be all host or all device")
+    p = pcsr_params_t()
+    if params is not None:
+        ctypes.memmove(ctypes.byref(p), ctypes.byref(params), ctypes.sizeof(p))
+        p.reserved[0] = 0
+    else:
+        p.reserved[0] = PCSR_OPERATOR_SELECT
+    if dev_r:
+        p.flags |= PCSR_FLAG_DEVICE_CSR
+    out = (ctypes.c_void_p * 2)()
+    rc = _lib().pcsr_operator_build(n_rows, n_cols, int(k1.shape[0]), p_r, p_c, p_v, ctypes.byref(p), K,
+                                    int(transpose), ctypes.byref(out))
+    if rc != PCSR_OK:
+        raise PcsrError(rc, "pcsr_operator_build")
+    return Handle(out[0], n_rows, n_cols), Handle(out[1], n_cols, n_rows) if transpose else None
 
 
 def pcsr_spmm(h: Handle, B, C, K: int, stream=None) -> None:

@@ -13,6 +13,7 @@
 #include "pcsr_host.h"
 #include "pcsr_kernels.h"
 #include "pcsr_pool.h"
+#include "pcsr_relabel_gpu.h"
 
 namespace {
 
@@ -102,6 +103,25 @@ template <class T> int upload(const std::vector<T> &src, T **dst)
     if (!src.empty() && !hip_ok(hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice)))
         return PCSR_E_HIP;
     return PCSR_OK;
+}
+
+// PCSR_FLAG_WINDOW_IF_USEFUL: without structure for the window kernel to use, an ordinary handle.
+void drop_poor_windows(pcsr_handle_t h)
+{
+    if (!h->host.win_cols || !(h->flags & PCSR_FLAG_WINDOW_IF_USEFUL)) return;
+    if (h->host.win_hit >= 0.5 && h->host.M >= 128 * h->n_win_blocks) return;
+    h->host.win_cols = 0;
+    h->host.win_hit = 0.0;
+    h->n_win_blocks = 0;
+    std::vector<int32_t>().swap(h->host.win_start);
+    std::vector<int32_t>().swap(h->host.win_ptr);
+    std::vector<int32_t>().swap(h->host.win_lo);
+    std::vector<int32_t>().swap(h->host.win_hi);
+    for (int32_t **p : {&h->d_win, &h->d_win_ptr, &h->d_win_lo, &h->d_win_hi}) {
+        pcsr::pool_free(*p); // built a moment ago, nothing reads them
+        *p = nullptr;
+    }
+    h->lpr = h->vec = h->rep = h->waves = h->ipg = 0;
 }
 
 // Lists the split panels (by position in the split tables) with more than
@@ -202,6 +222,108 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     return PCSR_OK;
 }
 
+// Host CSR arrays in device memory for the length of a call.
+struct UploadedCsr {
+    int32_t *rowptr = nullptr, *colidx = nullptr;
+    float *vals = nullptr;
+    int put(int64_t n_rows, int64_t nnz, const int32_t *h_rowptr, const int32_t *h_colidx, const float *h_vals)
+    {
+        auto one = [](void **d, const void *src, size_t bytes) {
+            hipError_t e = pcsr::pool_alloc(d, bytes + 4);
+            if (e == hipSuccess && bytes) e = pcsr::copy_to_device(*d, src, bytes);
+            return e;
+        };
+        hipError_t e = one((void **)&rowptr, h_rowptr, sizeof(int32_t) * (n_rows + 1));
+        if (e == hipSuccess) e = one((void **)&colidx, h_colidx, sizeof(int32_t) * nnz);
+        if (e == hipSuccess) e = one((void **)&vals, h_vals, sizeof(float) * nnz);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            return PCSR_E_OOM;
+        }
+        return hip_ok(e) ? PCSR_OK : PCSR_E_HIP;
+    }
+    ~UploadedCsr()
+    {
+        if (!rowptr) return;
+        (void)hipStreamSynchronize(nullptr);
+        pcsr::pool_free(rowptr);
+        pcsr::pool_free(colidx);
+        pcsr::pool_free(vals);
+    }
+};
+
+// Returned by handle_from_device where the windows have to be chosen on the host.
+constexpr int kWindowsOnHost = 1;
+
+// A handle from CSR arrays in device memory, everything built there.
+int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
+                       const float *vals, const pcsr_params_t &prm, pcsr_handle_s **out)
+{
+    const bool column_order = (prm.flags & PCSR_FLAG_COLUMN_ORDER) != 0;
+    pcsr_handle_s *h = new (std::nothrow) pcsr_handle_s();
+    if (!h) return PCSR_E_OOM;
+    if (!hip_ok(hipGetDevice(&h->device))) {
+        delete h;
+        return PCSR_E_HIP;
+    }
+    pcsr::DeviceBuild db;
+    int herr = 0;
+    int rc = pcsr::build_device(n_rows, n_cols, nnz, rowptr, colidx, vals, prm.V, prm.S, prm.SG, prm.omega,
+                                !(prm.flags & PCSR_FLAG_NO_VALIDATE), column_order, &db, &herr);
+    h->host.n_rows = n_rows;
+    h->host.n_cols = n_cols;
+    h->host.nnz = nnz;
+    h->host.V = prm.V;
+    h->host.S = prm.S;
+    h->host.P = db.P;
+    h->host.M = db.M;
+    h->host.nnz_v = db.nnz_v;
+    h->host.SG = db.SG;
+    h->host.max_item_len = db.max_item_len;
+    for (int x = 0; x < 9; ++x) h->host.xcd_bounds[x] = db.xcd_bounds[x];
+    h->d_rowptr = db.rowptr;
+    h->d_colidx = db.colidx;
+    h->d_val = db.val;
+    h->d_trow = db.trow;
+    h->d_split = db.split;
+    h->d_item_slot = db.item_slot;
+    h->d_sched = db.sched;
+    h->d_split_slot = db.split_slot;
+    h->d_long = db.long_list;
+    h->n_split = db.n_split;
+    h->n_split_items = db.n_split_items;
+    h->n_long = db.n_long;
+    h->lpr = prm.lanes_per_row;
+    h->vec = prm.vec;
+    h->rep = prm.rep;
+    h->waves = prm.waves_per_wg;
+    h->ipg = prm.items_per_group;
+    h->flags = prm.flags;
+    if (rc == PCSR_OK && prm.col_window) {
+        pcsr::DeviceWindows w;
+        rc = pcsr::windows_device(db.M, n_cols, prm.col_window, db.rowptr, db.colidx, &w, &herr);
+        if (rc == PCSR_E_UNSUPPORTED) rc = kWindowsOnHost;
+        if (rc == PCSR_OK) {
+            h->d_win = w.start;
+            h->d_win_ptr = w.ptr;
+            h->d_win_lo = w.lo;
+            h->d_win_hi = w.hi;
+            h->host.win_cols = prm.col_window;
+            h->host.win_hit = db.nnz_v ? double(w.hits) / double(db.nnz_v) : 0.0;
+            h->n_win_blocks = w.blocks;
+            drop_poor_windows(h);
+        }
+    }
+    if (rc != PCSR_OK) {
+        if (rc == PCSR_E_HIP) g_last_hip = herr;
+        release_device(h);
+        delete h;
+        return rc;
+    }
+    *out = h;
+    return PCSR_OK;
+}
+
 } // namespace
 
 extern "C" {
@@ -234,90 +356,29 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
     const bool device_csr = (prm.flags & PCSR_FLAG_DEVICE_CSR) != 0;
     const bool column_order = (prm.flags & PCSR_FLAG_COLUMN_ORDER) != 0;
     if (column_order && (!prm.S || prm.col_window)) return PCSR_E_UNSUPPORTED;
-    if ((device_csr || (prm.flags & PCSR_FLAG_GPU_BUILD)) && !prm.col_window) {
-        if (host_only) return PCSR_E_INVALID_ARG;
-        // ---- PCSR generation on the GPU
-        int32_t *t_rowptr = nullptr, *t_colidx = nullptr;
-        float *t_vals = nullptr;
-        auto drop_tmp = [&] {
-            (void)hipStreamSynchronize(nullptr);
-            pcsr::pool_free(t_rowptr);
-            pcsr::pool_free(t_colidx);
-            pcsr::pool_free(t_vals);
-        };
+    if (host_only && (prm.flags & PCSR_FLAG_GPU_BUILD) && !prm.col_window) return PCSR_E_INVALID_ARG;
+    // On the GPU wherever the arrays are there already, the caller asks for it, or the upload and
+    // the launches cost less than the host threads take (12 M nonzeros: 6 ms against 25-60).
+    if (!host_only && (device_csr || ((prm.flags & PCSR_FLAG_GPU_BUILD) && !prm.col_window) || pcsr::relabel_on_gpu(nnz))) {
+        UploadedCsr up;
+        const int32_t *d_rowptr = rowptr, *d_colidx = colidx;
+        const float *d_vals = vals;
         if (!device_csr) {
-            bool ok = hip_ok(pcsr::pool_alloc((void **)&t_rowptr, sizeof(int32_t) * (n_rows + 1))) &&
-                      hip_ok(pcsr::pool_alloc((void **)&t_colidx, sizeof(int32_t) * (nnz + 1))) &&
-                      hip_ok(pcsr::pool_alloc((void **)&t_vals, sizeof(float) * (nnz + 1))) &&
-                      hip_ok(hipMemcpy(t_rowptr, rowptr, sizeof(int32_t) * (n_rows + 1), hipMemcpyHostToDevice)) &&
-                      (nnz == 0 ||
-                       (hip_ok(hipMemcpy(t_colidx, colidx, sizeof(int32_t) * nnz, hipMemcpyHostToDevice)) &&
-                        hip_ok(hipMemcpy(t_vals, vals, sizeof(float) * nnz, hipMemcpyHostToDevice))));
-            if (!ok) {
-                drop_tmp();
-                return PCSR_E_HIP;
-            }
-            rowptr = t_rowptr;
-            colidx = t_colidx;
-            vals = t_vals;
+            rc = up.put(n_rows, nnz, rowptr, colidx, vals);
+            if (rc != PCSR_OK) return rc;
+            d_rowptr = up.rowptr;
+            d_colidx = up.colidx;
+            d_vals = up.vals;
         }
-        pcsr::DeviceBuild db;
-        int herr = 0;
-        rc = pcsr::build_device(n_rows, n_cols, nnz, rowptr, colidx, vals, prm.V, prm.S, prm.SG, prm.omega,
-                                !(prm.flags & PCSR_FLAG_NO_VALIDATE), column_order, &db, &herr);
-        drop_tmp();
-        if (rc != PCSR_OK) {
-            if (rc == PCSR_E_HIP) g_last_hip = herr;
-            return rc;
-        }
-        pcsr_handle_s *h = new (std::nothrow) pcsr_handle_s();
-        if (!h) {
-            for (void *q : {(void *)db.rowptr, (void *)db.colidx, (void *)db.val, (void *)db.trow, (void *)db.split,
-                            (void *)db.item_slot, (void *)db.sched, (void *)db.split_slot, (void *)db.long_list})
-                pcsr::pool_free(q);
-            return PCSR_E_OOM;
-        }
-        h->host.n_rows = n_rows;
-        h->host.n_cols = n_cols;
-        h->host.nnz = nnz;
-        h->host.V = prm.V;
-        h->host.S = prm.S;
-        h->host.P = db.P;
-        h->host.M = db.M;
-        h->host.nnz_v = db.nnz_v;
-        h->host.SG = db.SG;
-        h->host.max_item_len = db.max_item_len;
-        for (int x = 0; x < 9; ++x) h->host.xcd_bounds[x] = db.xcd_bounds[x];
-        h->d_rowptr = db.rowptr;
-        h->d_colidx = db.colidx;
-        h->d_val = db.val;
-        h->d_trow = db.trow;
-        h->d_split = db.split;
-        h->d_item_slot = db.item_slot;
-        h->d_sched = db.sched;
-        h->d_split_slot = db.split_slot;
-        h->n_split = db.n_split;
-        h->n_split_items = db.n_split_items;
-        h->lpr = prm.lanes_per_row;
-        h->vec = prm.vec;
-        h->rep = prm.rep;
-        h->waves = prm.waves_per_wg;
-        h->ipg = prm.items_per_group;
-        h->flags = prm.flags;
-        h->d_long = db.long_list;
-        h->n_long = db.n_long;
-        if (!hip_ok(hipGetDevice(&h->device))) {
-            release_device(h);
-            delete h;
-            return PCSR_E_HIP;
-        }
-        *out = h;
-        return PCSR_OK;
+        pcsr_handle_s *h = nullptr;
+        rc = handle_from_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, prm, &h);
+        if (rc == PCSR_OK) *out = h;
+        if (rc != kWindowsOnHost) return rc;
     }
 
     try {
-        // The column-window build runs on the host: CSR arrays handed over in device memory
-        // are copied there first (every other device-CSR build took the GPU branch above).
+        // The host builder: handles without a GPU, small matrices, and column windows over rows
+        // too long for the GPU's (CSR arrays in device memory are copied here for those).
         std::vector<int32_t> s_rowptr, s_colidx;
         std::vector<float> s_vals;
         if (device_csr) {
@@ -370,18 +431,7 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
         h->waves = prm.waves_per_wg;
         h->ipg = prm.items_per_group;
         h->flags = prm.flags;
-        if (prm.col_window && (prm.flags & PCSR_FLAG_WINDOW_IF_USEFUL) &&
-            (h->host.win_hit < 0.5 || h->host.M < 128 * h->n_win_blocks)) {
-            // no structure for the window kernel to use: an ordinary handle
-            h->host.win_cols = 0;
-            h->host.win_hit = 0.0;
-            h->n_win_blocks = 0;
-            std::vector<int32_t>().swap(h->host.win_start);
-            std::vector<int32_t>().swap(h->host.win_ptr);
-            std::vector<int32_t>().swap(h->host.win_lo);
-            std::vector<int32_t>().swap(h->host.win_hi);
-            h->lpr = h->vec = h->rep = h->waves = h->ipg = 0;
-        }
+        drop_poor_windows(h);
         h->n_split = (int64_t)h->host.split_panels.size();
         h->n_split_items = h->host.split_slot.empty() ? 0 : h->host.split_slot.back();
         if (!host_only) {
@@ -426,6 +476,64 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
     } catch (const std::bad_alloc &) {
         return PCSR_E_OOM;
     }
+}
+
+int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
+                        const float *vals, const pcsr_params_t *p, int32_t K, int32_t with_transpose,
+                        pcsr_handle_t out[2])
+{
+    if (!out || !rowptr || n_rows < 0 || n_cols < 0 || nnz < 0 || (nnz > 0 && (!colidx || !vals)))
+        return PCSR_E_INVALID_ARG;
+    if (nnz >= (int64_t(1) << 31) || n_rows >= (int64_t(1) << 31) - 1 || n_cols >= (int64_t(1) << 31) - 1)
+        return PCSR_E_TOO_LARGE;
+    const bool device_csr = p && (p->flags & PCSR_FLAG_DEVICE_CSR);
+    UploadedCsr up;
+    int herr = 0, rc = PCSR_OK;
+    if (!device_csr) {
+        rc = up.put(n_rows, nnz, rowptr, colidx, vals);
+        if (rc != PCSR_OK) return rc;
+        rowptr = up.rowptr;
+        colidx = up.colidx;
+        vals = up.vals;
+    }
+    auto failed = [&](int code) {
+        if (code == PCSR_E_HIP && herr) g_last_hip = herr;
+        return code;
+    };
+    rc = pcsr::validate_device(n_rows, n_cols, nnz, rowptr, colidx, &herr);
+    if (rc != PCSR_OK) return failed(rc);
+    const bool pick = !p || p->reserved[0] == PCSR_OPERATOR_SELECT;
+    auto direction = [&](int64_t nr, int64_t nc, const int32_t *rp, const int32_t *ci, const float *va,
+                         pcsr_handle_t *h) -> int {
+        pcsr_params_t prm;
+        if (pick) {
+            double f[PCSR_N_FEATURES];
+            int r = pcsr::features_device(nr, nc, nnz, rp, ci, 0, f, &herr);
+            if (r == PCSR_OK) r = pcsr_select(f, K, &prm);
+            if (r != PCSR_OK) return failed(r);
+            // launch shape stays on auto so one handle serves every layer width
+            prm.lanes_per_row = prm.vec = prm.rep = 0;
+        } else {
+            prm = *p;
+        }
+        prm.flags |= PCSR_FLAG_DEVICE_CSR | PCSR_FLAG_NO_VALIDATE;
+        return pcsr_build(nr, nc, nnz, rp, ci, va, &prm, h);
+    };
+    pcsr_handle_t made[2] = {nullptr, nullptr};
+    rc = direction(n_rows, n_cols, rowptr, colidx, vals, &made[0]);
+    if (rc == PCSR_OK && with_transpose) {
+        UploadedCsr t;
+        rc = failed(pcsr::transpose_device(n_rows, n_cols, nnz, rowptr, colidx, vals, &t.rowptr, &t.colidx, &t.vals,
+                                           &herr));
+        if (rc == PCSR_OK) rc = direction(n_cols, n_rows, t.rowptr, t.colidx, t.vals, &made[1]);
+    }
+    if (rc != PCSR_OK) {
+        (void)pcsr_free(made[0]);
+        return rc;
+    }
+    out[0] = made[0];
+    out[1] = made[1];
+    return PCSR_OK;
 }
 
 // Bytes of workspace one SpMM of width K needs: V*K floats per item of a split panel

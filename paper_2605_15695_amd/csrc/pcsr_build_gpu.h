@@ -37,4 +37,19 @@ int validate_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *
 int features_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                     const int32_t *d_colidx, int32_t omega, double *out, int *hip_err);
 
+// Window blocks of S = 0 arrays in device memory, the same ones choose_windows picks.
+// UNSUPPORTED where a stretch of items has more vectors than a workgroup can sort (the caller
+// then takes the host builder).  Ownership of the arrays passes to the caller.  Synchronous.
+struct DeviceWindows {
+    int32_t *ptr = nullptr, *start = nullptr, *lo = nullptr, *hi = nullptr;
+    int64_t blocks = 0, hits = 0;
+};
+int windows_device(int64_t M, int64_t n_cols, int32_t win, const int32_t *d_rowptr, const int32_t *d_colidx,
+                   DeviceWindows *out, int *hip_err);
+
+// CSR of the transpose from CSR arrays in device memory, as pcsr_transpose_csr gives it; the
+// outputs (n_cols + 1, nnz, nnz) are allocated here, ownership passes to the caller.  Synchronous.
+int transpose_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
+                     const float *d_vals, int32_t **t_rowptr, int32_t **t_colidx, float **t_vals, int *hip_err);
+
 } // namespace pcsr

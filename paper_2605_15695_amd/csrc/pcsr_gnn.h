@@ -30,6 +30,16 @@ typedef struct {
 int pcsr_spmm_epilogue(pcsr_handle_t h, const float *B, float *C, int32_t K, const pcsr_epilogue_t *epi,
                        void *stream);
 
+// Both directions of a matrix, set up in device memory from one upload (or from arrays there
+// already: PCSR_FLAG_DEVICE_CSR in p->flags): the CSR is checked, each direction gets the
+// parameters pcsr_select picks for width K with the launch shape left on auto, or the caller's
+// (reserved[0] = 0), and is built.  out[0]: A, out[1]: its transpose (with_transpose, else null).
+// p may be null.  Errors as pcsr_build.
+enum { PCSR_OPERATOR_SELECT = 1 }; // in p->reserved[0]: p only carries flags
+int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
+                        const float *vals, const pcsr_params_t *p, int32_t K, int32_t with_transpose,
+                        pcsr_handle_t out[2]);
+
 // Floats of workspace a call below needs for weights of b x a.
 int64_t pcsr_gnn_workspace_floats(int32_t a, int32_t b);
 

@@ -1,9 +1,13 @@
 #include "pcsr_pool.h"
 
 #include <algorithm>
+#include <atomic>
+#include <cstring>
 #include <map>
 #include <mutex>
+#include <thread>
 #include <unordered_map>
+#include <vector>
 
 namespace pcsr {
 namespace {
@@ -134,6 +138,117 @@ void pool_release(void *p)
         P.live.erase(p);
     }
     (void)hipFree(p);
+}
+
+namespace {
+
+constexpr int kCopyThreads = 8;
+constexpr size_t kPiece = size_t(1) << 20;
+
+struct Lane { // one copying thread's buffers and stream
+    char *pin[2] = {nullptr, nullptr};
+    hipStream_t stream[2] = {nullptr, nullptr};
+};
+struct Lanes {
+    std::mutex mu;
+    std::map<int, std::vector<Lane>> per_device;
+};
+Lanes &lanes()
+{
+    static Lanes *l = new Lanes;
+    return *l;
+}
+
+// The lanes of a device, made on first use; empty if that failed.  Lanes::mu held.
+std::vector<Lane> &lanes_of(int dev)
+{
+    std::vector<Lane> &v = lanes().per_device[dev];
+    if (!v.empty()) return v;
+    std::vector<Lane> made(kCopyThreads);
+    bool ok = true;
+    for (Lane &l : made)
+        for (int b = 0; b < 2 && ok; ++b)
+            ok = hipHostMalloc((void **)&l.pin[b], kPiece, hipHostMallocDefault) == hipSuccess &&
+                 hipStreamCreateWithFlags(&l.stream[b], hipStreamNonBlocking) == hipSuccess;
+    if (ok) {
+        v.swap(made);
+    } else {
+        (void)hipGetLastError();
+        for (Lane &l : made)
+            for (int b = 0; b < 2; ++b) {
+                if (l.stream[b]) (void)hipStreamDestroy(l.stream[b]);
+                if (l.pin[b]) (void)hipHostFree(l.pin[b]);
+            }
+    }
+    return v;
+}
+
+hipError_t staged(char *dst, const char *src, size_t bytes, bool to_host)
+{
+    const hipMemcpyKind kind = to_host ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice;
+    int dev = -1;
+    if (bytes < kStagedBytes || hipGetDevice(&dev) != hipSuccess) return hipMemcpy(dst, src, bytes, kind);
+    std::unique_lock<std::mutex> lock(lanes().mu, std::try_to_lock);
+    if (!lock.owns_lock()) return hipMemcpy(dst, src, bytes, kind);
+    std::vector<Lane> &ls = lanes_of(dev);
+    if (ls.empty()) return hipMemcpy(dst, src, bytes, kind);
+    // like hipMemcpy, after everything enqueued on the null stream
+    hipError_t e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) return e;
+    std::atomic<int> failed{hipSuccess};
+    const size_t pieces = (bytes + kPiece - 1) / kPiece;
+    auto work = [&](int t) {
+        Lane &l = ls[t];
+        hipError_t r = hipSetDevice(dev);
+        size_t wait[2] = {pieces, pieces}; // piece in flight in each buffer
+        int b = 0;
+        auto size = [&](size_t p) { return std::min(kPiece, bytes - p * kPiece); };
+        auto settle = [&](int k) { // finishes what buffer k has in flight
+            if (wait[k] == pieces) return;
+            const hipError_t w = hipStreamSynchronize(l.stream[k]);
+            if (w != hipSuccess) r = w;
+            if (to_host && w == hipSuccess) std::memcpy(dst + wait[k] * kPiece, l.pin[k], size(wait[k]));
+            wait[k] = pieces;
+        };
+        for (size_t p = t; p < pieces && r == hipSuccess; p += kCopyThreads, b ^= 1) {
+            settle(b);
+            if (r != hipSuccess) break;
+            const size_t at = p * kPiece;
+            if (to_host) {
+                r = hipMemcpyAsync(l.pin[b], src + at, size(p), kind, l.stream[b]);
+            } else {
+                std::memcpy(l.pin[b], src + at, size(p));
+                r = hipMemcpyAsync(dst + at, l.pin[b], size(p), kind, l.stream[b]);
+            }
+            if (r == hipSuccess) wait[b] = p;
+        }
+        settle(b); // the older piece first
+        settle(b ^ 1);
+        if (r != hipSuccess) failed = r;
+    };
+    std::vector<std::thread> th;
+    const int n = (int)std::min<size_t>(kCopyThreads, pieces);
+    try {
+        for (int t = 1; t < n; ++t) th.emplace_back(work, t);
+    } catch (...) { // no more threads: what they would have moved is moved here
+    }
+    const int started = (int)th.size() + 1;
+    work(0);
+    for (int t = started; t < n; ++t) work(t);
+    for (std::thread &t : th) t.join();
+    return (hipError_t)failed.load();
+}
+
+} // namespace
+
+hipError_t copy_to_host(void *dst, const void *src, size_t bytes)
+{
+    return staged(static_cast<char *>(dst), static_cast<const char *>(src), bytes, true);
+}
+
+hipError_t copy_to_device(void *dst, const void *src, size_t bytes)
+{
+    return staged(static_cast<char *>(dst), static_cast<const char *>(src), bytes, false);
 }
 
 } // namespace pcsr

@@ -19,33 +19,28 @@ class PcsrOperator:
     """A fixed sparse matrix A ready for forward (A*B) and backward (A^T*dC) products.
 
     ``symmetric=True`` states that A equals its transpose (GCN-normalised undirected
-    graphs), so one handle serves both directions.  Otherwise the transpose is built once
-    with pcsr_transpose_csr.  Parameters are picked by pcsr_select for width ``K_hint``
+    graphs), so one handle serves both directions.  Otherwise the transpose is built once.  Parameters are picked by pcsr_select for width ``K_hint``
     unless ``params`` is given.
     """
 
     def __init__(self, n_rows, n_cols, rowptr, colidx, vals, symmetric=False, K_hint=64, params=None):
         self.n_rows, self.n_cols = int(n_rows), int(n_cols)
 
-        def build(nr, nc, rp, ci, va):
-            p = params
-            if p is None:
-                p = pc.pcsr_select(pc.pcsr_features(nr, nc, rp, ci), K_hint)
-                # launch shape stays on auto so one handle serves every layer width
-                p.lanes_per_row = p.vec = p.rep = 0
-            else:
-                p = pc.make_params(**{f: getattr(params, f) for f, _ in pc.pcsr_params_t._fields_
-                                      if f != "reserved"})
-            return pc.pcsr_build(nr, nc, rp, ci, va, p)
-
-        self.fwd = build(self.n_rows, self.n_cols, rowptr, colidx, vals)
+        if symmetric and n_rows != n_cols:
+            raise ValueError("a symmetric operator must be square")
+        if params is not None:
+            params = pc.make_params(**{f: getattr(params, f) for f, _ in pc.pcsr_params_t._fields_ if f != "reserved"})
+        if params is not None and params.flags & pc.PCSR_FLAG_HOST_ONLY:
+            self.fwd = self.bwd = pc.pcsr_build(self.n_rows, self.n_cols, rowptr, colidx, vals, params)
+            if not symmetric:
+                self.bwd = pc.pcsr_build(self.n_cols, self.n_rows,
+                                         *pc.pcsr_transpose_csr(self.n_rows, self.n_cols, rowptr, colidx, vals), params)
+            return
+        # one upload; check, features, selection, transpose and PCSR generation on the GPU
+        self.fwd, self.bwd = pc.pcsr_operator_build(self.n_rows, self.n_cols, rowptr, colidx, vals, params, K_hint,
+                                                    not symmetric)
         if symmetric:
-            if n_rows != n_cols:
-                raise ValueError("a symmetric operator must be square")
             self.bwd = self.fwd
-        else:
-            trp, tci, tva = pc.pcsr_transpose_csr(self.n_rows, self.n_cols, rowptr, colidx, vals)
-            self.bwd = build(self.n_cols, self.n_rows, trp, tci, tva)
 
     def apply(self, B: torch.Tensor) -> torch.Tensor:
         return SpMMFunction.apply(B, self)

@@ -1,0 +1,146 @@
+"""Relabelling, transpose and window blocks on the GPU against numpy restatements and the host
+builder: the integers and bytes have to be the same."""
+import numpy as np
+import pytest
+
+import paper_2605_15695_amd as pc
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _mix(x, r):
+    x = x.astype(np.uint64)
+    m = np.uint64(0xffffffff)
+    x ^= np.uint64((r * 0x9E3779B9) & 0xffffffff)
+    x ^= x >> np.uint64(16)
+    x = (x * np.uint64(0x7feb352d)) & m
+    x ^= x >> np.uint64(15)
+    x = (x * np.uint64(0x846ca68b)) & m
+    x ^= x >> np.uint64(16)
+    return x
+
+
+def _label_propagation(n, rp, ci, rounds=8):
+    """Most frequent neighbour label; ties: the node's own, else the smallest salted hash."""
+    rows = np.repeat(np.arange(n), np.diff(rp))
+    lab = np.arange(n)
+    for r in range(rounds):
+        key, cnt = np.unique(rows * np.int64(n) + lab[ci], return_counts=True)
+        row, label = key // n, key % n
+        order = np.lexsort((_mix(label, r), label != lab[row], -cnt, row))
+        first = np.ones(order.size, bool)
+        first[1:] = row[order][1:] != row[order][:-1]
+        nxt = lab.copy()
+        nxt[row[order][first]] = label[order][first]
+        moved = int((nxt != lab).sum())
+        lab = nxt
+        if moved * 200 < n:
+            break
+    perm = np.empty(n, np.int32)
+    perm[np.argsort(lab, kind="stable")] = np.arange(n)
+    return perm, np.unique(lab).size
+
+
+def _case(name):
+    if name == "sbm":
+        g = synth.sbm(12_000, 24, mean_deg=40.0, shuffled=True)
+        return g.n_rows, g.rowptr, g.colidx, g.vals
+    if name == "power":                     # rows of every class, the longest over several passes
+        g = synth.rmat(14, 24, symmetric=True, permute=True)
+        return g.n_rows, g.rowptr, g.colidx, g.vals
+    rng = np.random.default_rng(3)          # a few rows with nearly every column, many empty ones
+    n = 30_011
+    lengths = np.where(rng.random(n) < 0.6, 0, rng.integers(0, 20, n))
+    lengths[[5, 77, n - 1]] = [n, 25_000, 9_000]
+    lengths[100:140] = [64, 65] * 10 + [1024, 1025] * 10
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths if k]).astype(np.int32)
+    return n, rp, ci, rng.standard_normal(ci.size).astype(np.float32)
+
+
+@pytest.mark.parametrize("name", ["sbm", "power", "uneven"])
+def test_reorder_permute_transpose(name):
+    n, rp, ci, va = _case(name)
+    assert ci.size >= 200_000               # enough for the GPU side to be taken
+    for rounds in (0, 3):
+        perm, clusters = pc.pcsr_reorder(n, rp, ci, rounds)
+        ref, ref_clusters = _label_propagation(n, rp, ci, rounds or 8)
+        assert clusters == ref_clusters and np.array_equal(perm, ref)
+    refs = np.bincount(ci, minlength=n)
+    by_degree = np.empty(n, np.int32)
+    by_degree[np.argsort(-refs, kind="stable")] = np.arange(n)
+    assert np.array_equal(pc.pcsr_reorder_by_degree(n, rp, ci), by_degree)
+
+    rows = np.repeat(np.arange(n), np.diff(rp))
+    order = np.lexsort((perm[ci], perm[rows]))
+    got = pc.pcsr_permute_csr(n, rp, ci, va, perm)
+    assert np.array_equal(got[0], np.concatenate([[0], np.cumsum(np.bincount(perm[rows], minlength=n))]))
+    assert np.array_equal(got[1], perm[ci][order]) and np.array_equal(got[2].view(np.uint32), va[order].view(np.uint32))
+
+    for m in (n, n + 1000):                 # a rectangular one with empty columns at the end
+        order = np.lexsort((rows, ci))
+        t = pc.pcsr_transpose_csr(n, m, rp, ci, va)
+        assert np.array_equal(t[0], np.concatenate([[0], np.cumsum(np.bincount(ci, minlength=m))]))
+        assert np.array_equal(t[1], rows[order]) and np.array_equal(t[2].view(np.uint32), va[order].view(np.uint32))
+
+
+def test_refusals_are_those_of_the_host():
+    n, rp, ci, va = _case("sbm")
+    bad = ci.copy()
+    bad[150_000] = n
+    for call in (lambda: pc.pcsr_reorder(n, rp, bad), lambda: pc.pcsr_reorder_by_degree(n, rp, bad),
+                 lambda: pc.pcsr_permute_csr(n, rp, bad, va, np.arange(n, dtype=np.int32)),
+                 lambda: pc.pcsr_transpose_csr(n, n, rp, bad, va)):
+        with pytest.raises(pc.PcsrError) as e:
+            call()
+        assert e.value.code == pc.binding.PCSR_E_BAD_CSR
+    perm = np.arange(n, dtype=np.int32)
+    perm[7] = 8
+    with pytest.raises(pc.PcsrError) as e:
+        pc.pcsr_permute_csr(n, rp, ci, va, perm)
+    assert e.value.code == pc.binding.PCSR_E_INVALID_ARG
+
+
+@pytest.mark.parametrize("wc", [256, 512, 1024, 2048])
+@pytest.mark.parametrize("V", [1, 2])
+@pytest.mark.parametrize("name", ["sbm", "sbm_shuffled", "cliques", "road", "uneven"])
+def test_windows_are_those_of_the_host_builder(name, V, wc):
+    if name == "uneven":
+        n, rp, ci, va = _case("uneven")
+    else:
+        g = {"sbm": lambda: synth.sbm(20_000, 40, mean_deg=50.0),
+             "sbm_shuffled": lambda: synth.sbm(12_000, 24, shuffled=True),
+             "cliques": lambda: synth.cliques(20_011, 40.0, 0.3, 5),
+             "road": lambda: synth.road_grid(307, 251)}[name]()
+        n, rp, ci, va = g.n_rows, g.rowptr, g.colidx, g.vals
+    host = pc.pcsr_build(n, n, rp, ci, va, pc.make_params(V=V, col_window=wc, flags=pc.PCSR_FLAG_HOST_ONLY))
+    dev = pc.pcsr_build(n, n, *(torch.from_numpy(x).cuda() for x in (rp, ci, va)), pc.make_params(V=V, col_window=wc))
+    assert pc.pcsr_window_stats(host) == pc.pcsr_window_stats(dev)
+    B = torch.from_numpy(synth.dense_operand(n, 16, "normal", 2)).cuda()
+    C = torch.full((n, 16), float("nan"), device="cuda")
+    if wc == 2048:                          # the auto slice of this window exceeds the LDS
+        pc.pcsr_set_kernel_params(dev, 4, 2, 1, 16)
+    pc.pcsr_spmm(dev, B, C, 16)
+    plain = pc.pcsr_build(n, n, rp, ci, va, pc.make_params(V=V))
+    D = torch.empty_like(C)
+    pc.pcsr_spmm(plain, B, D, 16)
+    assert float((C - D).norm() / D.norm()) < 1e-6
+    host.close(), dev.close(), plain.close()
+
+
+def test_operator_takes_device_arrays_and_refuses_bad_ones():
+    from paper_2605_15695_amd.gnn import PcsrOperator
+
+    n, rp, ci, va = _case("power")
+    a = PcsrOperator(n, n, rp, ci, va, K_hint=32)
+    b = PcsrOperator(n, n, *(torch.from_numpy(x).cuda() for x in (rp, ci, va)), K_hint=32)
+    B = torch.from_numpy(synth.dense_operand(n, 32, "normal", 2)).cuda()
+    assert torch.equal(a(B), b(B))
+    assert torch.equal(a._run(a.bwd, n, B), b._run(b.bwd, n, B))
+    bad = ci.copy()
+    bad[3] = bad[2]
+    with pytest.raises(pc.PcsrError) as e:
+        PcsrOperator(n, n, rp, bad, va)
+    assert e.value.code == pc.binding.PCSR_E_BAD_CSR
