@@ -12,6 +12,7 @@ import numpy as np
 
 _PKG = pathlib.Path(__file__).resolve().parent
 LIB_PATH = _PKG / "libpcsr.so"
+PY_PATH = _PKG / "_pcsr_py.so"
 
 PCSR_OK = 0
 PCSR_E_INVALID_ARG, PCSR_E_BAD_CSR, PCSR_E_UNSUPPORTED = -1, -2, -3
@@ -200,16 +201,39 @@ def pcsr_operator_build(n_rows, n_cols, rowptr, colidx, vals, params, K, transpo
     return Handle(out[0], n_rows, n_cols), Handle(out[1], n_cols, n_rows) if transpose else None
 
 
-def pcsr_spmm(h: Handle, B, C, K: int, stream=None) -> None:
-    """B, C: torch device tensors (fp32, contiguous).  stream: torch.cuda.Stream, raw handle or None."""
+def _spmm_checked(h: Handle, B, C, K: int, stream):
     _, p_b, dev_b = _ptr(B, np.dtype(np.float32))
     _, p_c, dev_c = _ptr(C, np.dtype(np.float32))
     if not (dev_b and dev_c):
         raise ValueError("B and C must be device tensors")
     if B.numel() != h.n_cols * K or C.numel() != h.n_rows * K:
         raise ValueError("B must be n_cols x K and C n_rows x K")
-    s = getattr(stream, "cuda_stream", stream)
-    rc = _lib().pcsr_spmm(h.raw, p_b, p_c, K, s)
+    return _lib().pcsr_spmm(h.raw, p_b, p_c, K, getattr(stream, "cuda_stream", stream))
+
+
+def _first_spmm(h, B, C, K, stream):
+    """Loads the module that makes the call without ctypes; from then on it is the one that is asked."""
+    global _spmm
+    import importlib.util
+
+    import torch  # noqa: F401  (its libraries have to be there)
+
+    spec = importlib.util.spec_from_file_location("_pcsr_py", PY_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.init(ctypes.cast(_lib().pcsr_spmm, ctypes.c_void_p).value)
+    _spmm = mod.spmm
+    return _spmm(h, B, C, K, stream)
+
+
+_spmm = _first_spmm
+
+
+def pcsr_spmm(h: Handle, B, C, K: int, stream=None) -> None:
+    """B, C: torch device tensors (fp32, contiguous).  stream: torch.cuda.Stream, raw handle or None."""
+    rc = _spmm(h, B, C, K, stream)
+    if rc is NotImplemented:
+        rc = _spmm_checked(h, B, C, K, stream)
     if rc != PCSR_OK:
         raise PcsrError(rc, "pcsr_spmm")
 

@@ -11,6 +11,7 @@ CSRC = PKG / "csrc"
 OBJ = PKG / "_build"
 LIB = PKG / "libpcsr.so"
 BASELINE_LIB = PKG / "libpcsr_baseline.so"
+PY_LIB = PKG / "_pcsr_py.so"
 
 HIPCC = "/opt/rocm/bin/hipcc"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-command-line-argument"]
@@ -33,10 +34,30 @@ def _compile(src: str) -> pathlib.Path:
     return obj
 
 
+def _build_py() -> pathlib.Path:
+    """The binding's per-call module: host code against torch's headers, found beside this file."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    libdir = pathlib.Path(torch.__file__).parent / "lib"
+    inc = [p for p in cpp_extension.include_paths()] + [sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-D__HIP_PLATFORM_AMD__=1", *[f"-isystem{p}" for p in inc], str(CSRC / "pcsr_py.cpp"), "-o", str(PY_LIB),
+           f"-L{libdir}", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{libdir}"]
+    r = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on pcsr_py.cpp:\n{r.stderr}")
+    return PY_LIB
+
+
 def build(verbose: bool = False) -> pathlib.Path:
     OBJ.mkdir(exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=4) as ex:
+        py = ex.submit(_build_py)
         objs = list(ex.map(_compile, SOURCES))
+        py.result()
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *map(str, objs), "-o", str(LIB),
            "-lpthread"]
     subprocess.run(cmd, check=True)

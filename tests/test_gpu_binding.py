@@ -1,0 +1,38 @@
+"""pcsr_spmm's fast marshalling: every way to pass the arguments, and the errors of those that do not fit."""
+import numpy as np
+import pytest
+
+import paper_2605_15695_amd as pc
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def test_arguments_and_errors():
+    g = synth.workload("poisson", "small")
+    K = 24
+    h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals)
+    B = torch.from_numpy(synth.dense_operand(g.n_cols, K, "normal", 3)).cuda()
+    out = []
+    side = torch.cuda.Stream()
+    for call in (lambda C: pc.pcsr_spmm(h, B, C, K), lambda C: pc.pcsr_spmm(h, B=B, C=C, K=K, stream=None),
+                 lambda C: pc.pcsr_spmm(h, B, C, K, side), lambda C: pc.pcsr_spmm(h, B, C, K, side.cuda_stream),
+                 lambda C: pc.pcsr_spmm(h, B, C, np.int64(K), 0),
+                 lambda C: pc.pcsr_spmm(h, torch.nn.Parameter(B), C, K, torch.cuda.current_stream())):
+        C = torch.full((g.n_rows, K), float("nan"), device="cuda")
+        torch.cuda.synchronize()
+        assert call(C) is None
+        torch.cuda.synchronize()
+        out.append(C)
+    assert all(torch.equal(out[0], o) for o in out) and bool(torch.isfinite(out[0]).all())
+    C = out[0]
+    for bad in ((B.cpu(), C), (B, C.cpu()), (B.double(), C), (B[:, :8], C), (B.t(), C), (B[:-1], C), (B, C[1:]),
+                (B.cpu().numpy(), C)):
+        with pytest.raises(ValueError):
+            pc.pcsr_spmm(h, *bad, K)
+    with pytest.raises(pc.PcsrError):
+        pc.pcsr_spmm(h, B, B.reshape(g.n_rows, K), K)      # B and C overlap
+    h.close()
+    with pytest.raises(pc.PcsrError):
+        pc.pcsr_spmm(h, B, C, K)
