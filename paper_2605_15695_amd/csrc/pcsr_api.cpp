@@ -19,6 +19,13 @@ namespace {
 
 constexpr uint32_t kMagic = 0x50435352u; // "PCSR"
 
+// Bits of pcsr_params_t.flags that pcsr_select sets for widths that are no multiple of 4: the shape
+// to launch instead, with loads of 4 (or, kWidePair, 2) floats per lane at any 4-byte address;
+// lanes per row 4 << (code - 1) for codes 1 to 5.  Cleared by pcsr_set_kernel_params.
+constexpr int kWideShift = 16;
+constexpr int32_t kWideShape = 7 << kWideShift;
+constexpr int32_t kWidePair = 8 << kWideShift;
+
 thread_local int g_last_hip = 0;
 
 inline bool hip_ok(hipError_t e)
@@ -138,6 +145,18 @@ static int upload_long_panels(pcsr_handle_s *h, const int32_t *split_slot)
     return upload(list, &h->d_long);
 }
 
+// Workgroups of `waves` wavefronts of 64/lpr groups, each taking ipg items, for all items.
+int64_t grid_for(pcsr_handle_t h, int waves, int lpr, int ipg)
+{
+    const int64_t items_per_wg = (int64_t)waves * (64 / lpr) * ipg;
+    if (h->flags & PCSR_FLAG_NO_XCD_REMAP) return (h->host.M + items_per_wg - 1) / items_per_wg;
+    // every XCD walks its own item range: 8 x the workgroups of the longest range
+    int64_t longest = 0;
+    for (int x = 0; x < 8; ++x)
+        longest = std::max<int64_t>(longest, h->host.xcd_bounds[x + 1] - h->host.xcd_bounds[x]);
+    return 8 * ((longest + items_per_wg - 1) / items_per_wg);
+}
+
 // Launch shape for width K under the handle's kernel parameters ("0 = auto" resolved).
 // epilogue: for pcsr_spmm_epilogue, whose kernels exist for the auto shapes only; a handle with
 // another shape of its own uses those.
@@ -199,16 +218,7 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
         if (!(epilogue && ipg == 1 ? pcsr::epilogue_kernel_exists(h->host.V, h->host.S, lpr, vec, rep)
                                    : pcsr::kernel_exists(h->host.V, h->host.S, lpr, vec, rep, ipg)))
             return PCSR_E_UNSUPPORTED;
-        const int64_t items_per_wg = (int64_t)waves * (64 / lpr) * ipg;
-        if (h->flags & PCSR_FLAG_NO_XCD_REMAP) {
-            gx = (h->host.M + items_per_wg - 1) / items_per_wg;
-        } else {
-            // every XCD walks its own item range: 8 x the workgroups of the longest range
-            int64_t longest = 0;
-            for (int x = 0; x < 8; ++x)
-                longest = std::max<int64_t>(longest, h->host.xcd_bounds[x + 1] - h->host.xcd_bounds[x]);
-            gx = 8 * ((longest + items_per_wg - 1) / items_per_wg);
-        }
+        gx = grid_for(h, waves, lpr, ipg);
     }
     const int64_t gy = (K + tile - 1) / tile;
     if (gx > 0x7fffffffLL || gy > 65535) return PCSR_E_TOO_LARGE;
@@ -219,6 +229,36 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     ls->ipg = ipg;
     ls->grid_x = (int32_t)gx;
     ls->grid_y = (int32_t)gy;
+    ls->k_lpr = lpr;
+    ls->k_vec = vec;
+    ls->k_rep = rep;
+    ls->k_grid_x = ls->grid_x;
+    ls->k_grid_y = ls->grid_y;
+    // Rows that are no multiple of 16 bytes long, from 17 columns on (below, the dword shapes are
+    // as good or better): the shape the next multiple of 4 gets, with loads of 16 bytes at
+    // 4-byte addresses, one per lane.  Only where the narrow vector is this function's or
+    // pcsr_select's choice, not where the caller asked for it.  300,000 clique rows of 27,
+    // K = 75: 64 lanes x dword x 2 145 us, 32 lanes x dwordx4 see DESIGN table.
+    if (!ls->window && ipg == 1 && K % 4 != 0 && K > 16) {
+        int wide = 0, wide_vec = 4;
+        if (h_lpr || h_vec || h_rep) {
+            if (h->flags & kWideShape) wide = 4 << ((h->flags & kWideShape) >> kWideShift) >> 1;
+            if (h->flags & kWidePair) wide_vec = 2;
+        } else {
+            const int cap = h->host.S ? 16 : 64;
+            for (wide = 4; wide * 4 < K && wide < cap;) wide <<= 1;
+        }
+        if (wide) {
+            const int64_t wx = grid_for(h, waves, wide, 1), wy = (K + wide * wide_vec - 1) / (wide * wide_vec);
+            if (wx <= 0x7fffffffLL && wy <= 65535) {
+                ls->k_lpr = wide;
+                ls->k_vec = wide_vec;
+                ls->k_rep = 1;
+                ls->k_grid_x = (int32_t)wx;
+                ls->k_grid_y = (int32_t)wy;
+            }
+        }
+    }
     return PCSR_OK;
 }
 
@@ -729,7 +769,7 @@ int pcsr_set_kernel_params(pcsr_handle_t h, int32_t lanes_per_row, int32_t vec, 
     h->waves = waves_per_wg;
     h->ipg = items_per_group;
     constexpr int32_t kLaunchFlags = PCSR_FLAG_NO_XCD_REMAP | PCSR_FLAG_ATOMIC_SPLIT;
-    h->flags = (h->flags & ~kLaunchFlags) | (flags & kLaunchFlags);
+    h->flags = (h->flags & ~(kLaunchFlags | kWideShape | kWidePair)) | (flags & kLaunchFlags);
     return PCSR_OK;
 }
 
@@ -933,7 +973,25 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     p.lanes_per_row = lpr;
     p.vec = vec;
     p.rep = rep;
-    if (skewed && lpr * vec > 64) p.SG = 64;
+    // Widths that are no multiple of 4, from 17 on and where no dword shape was chosen: the same
+    // slices as the next multiple of 4, read with wide loads at 4-byte addresses.
+    int slice = lpr * vec;
+    // (paired long scattered rows keep a wavefront of dwords: 4 % faster at K = 47)
+    if (K % 4 != 0 && K > 16 && !wide_scatter && !pair_long && !(lpr == 16 && vec == 1 && rep == 2 && K <= 32)) {
+        // two floats per lane where the rule above takes them and the last 64-column slice is well
+        // filled, and 16 lanes of two for K up to 32 unless rows are short
+        const bool narrow = K <= 32 && !p.S && d_hat >= 8.0;
+        const bool pair = narrow || (!skewed && !long_uniform && scattered && d_hat >= 8.0 && K >= 64 && (-K & 63) < 16);
+        int wide = 4, code = 1;
+        while (wide * 4 < K && wide < lpr_cap) {
+            wide <<= 1;
+            ++code;
+        }
+        if (pair) code = narrow ? 3 : 4; // 16 or 32 lanes
+        p.flags |= (pair ? kWidePair : 0) | code << kWideShift;
+        slice = pair ? 64 : wide * 4;
+    }
+    if (skewed && slice > 64) p.SG = 64;
     // Workgroup size: four wavefronts, two for short rows and for paired long rows (eight
     // were 4-7 % slower than four on every unsplit input of the later validation sets).
     p.waves_per_wg = p.S ? 4 : (d_hat >= 16.0 && !pair_long ? 4 : 2);

@@ -41,25 +41,48 @@ static __device__ __align__(16) float g_zero_row[1024];
 namespace pcsr {
 namespace {
 
+// Vectors of floats in memory.  The hardware takes 8- and 16-byte accesses at any 4-byte
+// address, so widths that are no multiple of the vector need no narrower loads.
 template <int N> struct Vec;
 template <> struct Vec<1> { using type = float; };
-template <> struct Vec<2> { using type = float2; };
-template <> struct Vec<4> { using type = float4; };
+template <> struct Vec<2> { typedef float type __attribute__((ext_vector_type(2), aligned(4))); };
+template <> struct Vec<4> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
 
 template <int VEC> __device__ __forceinline__ void load_vec(const float *p, float (&d)[VEC])
 {
     using T = typename Vec<VEC>::type;
-    T t = *reinterpret_cast<const T *>(p);
+    const T t = *reinterpret_cast<const T *>(p);
     if constexpr (VEC == 1) {
         d[0] = t;
-    } else if constexpr (VEC == 2) {
-        d[0] = t.x;
-        d[1] = t.y;
     } else {
-        d[0] = t.x;
-        d[1] = t.y;
-        d[2] = t.z;
-        d[3] = t.w;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) d[e] = t[e];
+    }
+}
+
+// The same in LDS, where an access that is not known to be aligned is split into dwords.
+template <int N> struct LdsVec {
+    typedef float type __attribute__((ext_vector_type(N)));
+};
+template <int VEC> __device__ __forceinline__ void load_lds(const float *p, float (&d)[VEC])
+{
+    if constexpr (VEC == 1) {
+        d[0] = *p;
+    } else {
+        const auto t = *reinterpret_cast<const typename LdsVec<VEC>::type *>(p);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) d[e] = t[e];
+    }
+}
+template <int VEC> __device__ __forceinline__ void store_lds(float *p, const float (&s)[VEC])
+{
+    if constexpr (VEC == 1) {
+        *p = s[0];
+    } else {
+        typename LdsVec<VEC>::type t;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) t[e] = s[e];
+        *reinterpret_cast<typename LdsVec<VEC>::type *>(p) = t;
     }
 }
 
@@ -69,7 +92,7 @@ template <int VEC> __device__ __forceinline__ void store_vec(float *p, const flo
     if constexpr (VEC == 1) {
         __builtin_nontemporal_store(s[0], p);
     } else {
-        typedef float ext_t __attribute__((ext_vector_type(VEC)));
+        using ext_t = typename Vec<VEC>::type;
         ext_t x;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) x[e] = s[e];
@@ -111,14 +134,9 @@ template <int VEC> __device__ __forceinline__ void store_vec_cached(float *p, co
     T t;
     if constexpr (VEC == 1) {
         t = s[0];
-    } else if constexpr (VEC == 2) {
-        t.x = s[0];
-        t.y = s[1];
     } else {
-        t.x = s[0];
-        t.y = s[1];
-        t.z = s[2];
-        t.w = s[3];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) t[e] = s[e];
     }
     *reinterpret_cast<T *>(p) = t;
 }
@@ -148,7 +166,7 @@ template <int LPR> __device__ __forceinline__ float bcast(float x, int j)
 __device__ __forceinline__ int bcast16_const(int x, int j)
 {
 #define PCSR_DPP_CASE(J) \
-    case J: return __builtin_amdgcn_update_dpp(0, x, 0x150 + J, 0xf, 0xf, false)
+    case J: return __builtin_amdgcn_mov_dpp(x, 0x150 + J, 0xf, 0xf, true)
     switch (j & 15) {
         PCSR_DPP_CASE(0);
         PCSR_DPP_CASE(1);
@@ -165,10 +183,13 @@ __device__ __forceinline__ int bcast16_const(int x, int j)
         PCSR_DPP_CASE(12);
         PCSR_DPP_CASE(13);
         PCSR_DPP_CASE(14);
-    default: return __builtin_amdgcn_update_dpp(0, x, 0x150 + 15, 0xf, 0xf, false);
+    default: return __builtin_amdgcn_mov_dpp(x, 0x150 + 15, 0xf, 0xf, true);
     }
 #undef PCSR_DPP_CASE
 }
+// whether p holds in every active lane of the wavefront (a uniform branch)
+__device__ __forceinline__ bool wave_all(bool p) { return __builtin_amdgcn_ballot_w64(!p) == 0; }
+
 // acc += (lane j of the 16-lane group's a) * b in one instruction: the DPP operand of a
 // VOP2 multiply-add does the broadcast, so no separate move is spent on it.
 __device__ __forceinline__ void fmac_bcast16_const(float &acc, float a, float b, int j)
@@ -211,6 +232,13 @@ template <int LPR, bool CONST_LANE> __device__ __forceinline__ float bcast_any(f
 {
     return __int_as_float(bcast_any<LPR, CONST_LANE>(__float_as_int(x), j));
 }
+// base + the byte offset that lane j of every DPP row holds
+__device__ __forceinline__ const float *row_ptr(const float *base, long off, int j)
+{
+    const int lo = bcast16_const((int)off, j), hi = bcast16_const((int)(off >> 32), j);
+    return reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) +
+                                           (long)(((unsigned long)(unsigned)hi << 32) | (unsigned)lo));
+}
 
 // EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
 // branch alone cost the instance <2, false, 64, 1, 2> 4 %.
@@ -225,7 +253,16 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
     constexpr bool DEEP = S || (V == 1 && LPR <= 8);
     constexpr int U0 = (DEEP ? PCSR_INFLIGHT_SPLIT : PCSR_INFLIGHT) / (REP * VEC);
     constexpr int Uc = U0 < 1 ? 1 : (U0 > PCSR_MAXSTEP ? PCSR_MAXSTEP : U0);
-    constexpr int U = Uc > LPR ? LPR : Uc; // a step never reaches past the group's chunk
+    // Entries per chunk: one per lane, and for groups of more than 16 lanes the same 16 (or twice
+    // 16, two per lane) in each of their DPP rows, so that broadcasts stay inside a row.  32 is
+    // 5 % faster where rows are long (LPR 32, V = 1: scattered inputs), 16 where paired rows
+    // are short (LPR 32, V = 2: road-like and clique inputs, 8-15 %).
+    // A whole wavefront on one row broadcasts through scalar registers (v_readlane) instead: its
+    // row addresses then cost no vector instruction at all.
+    constexpr int CH = LPR == 32 && V == 2 ? 16 : LPR;
+    constexpr bool DPP = LPR == 16 || LPR == 32;
+    constexpr int NH = DPP ? CH / 16 : 1; // entries per lane
+    constexpr int U = Uc > CH ? CH : Uc; // a step never reaches past the chunk
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int waves = blockDim.x >> 6;
@@ -277,6 +314,19 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
         kc[r] = kbase + (r * LPR + lg) * VEC;
         kv[r] = kc[r] < a.K;
     }
+    // K no multiple of VEC (one load per lane only): the last vector of a row is moved back to
+    // end with it.  The columns it shares with its neighbour are computed and stored twice,
+    // the same bits; the atomic write-back skips them.
+    int skip = 0;
+    if constexpr (REP == 1) {
+        if (kv[0] && kc[0] > a.K - VEC) {
+            skip = kc[0] - (a.K - VEC);
+            kc[0] = a.K - VEC;
+        }
+    }
+    // a lane past the last column loads what its neighbour loads and stores nothing
+    const int lane_col = kv[0] ? kc[0] : a.K - VEC;
+    const float *__restrict__ B_lane = a.B + lane_col;
 
     float acc[V][REP][VEC];
 #pragma unroll
@@ -286,40 +336,48 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc[v][r][e] = 0.0f;
 
-    const float *__restrict__ B = a.B;
     const long K = a.K;
 
-    // one lane's entry of the chunk that starts at `base` (zeros past the end of the range)
-    auto load_entry = [&](int base, int &c, float (&av)[V]) {
-        const int idx = base + lg;
-        c = 0;
+    // one lane's entries of the chunk that starts at `base` (zeros past the end of the range)
+    auto load_entry = [&](int base, int (&c)[NH], float (&av)[NH][V]) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) av[v] = 0.0f;
-        if (idx < tail) {
-            c = stream_load(a.colidx + idx);
-            if constexpr (V == 1) {
-                av[0] = stream_load(a.val + idx);
-            } else {
-                typedef float f2 __attribute__((ext_vector_type(2)));
-                const f2 t = stream_load(reinterpret_cast<const f2 *>(a.val) + idx);
-                av[0] = t[0];
-                av[1] = t[1];
+        for (int h = 0; h < NH; ++h) {
+            const int idx = base + 16 * h + (DPP ? lg & 15 : lg);
+            c[h] = 0;
+#pragma unroll
+            for (int v = 0; v < V; ++v) av[h][v] = 0.0f;
+            if (idx < tail) {
+                c[h] = stream_load(a.colidx + idx);
+                if constexpr (V == 1) {
+                    av[h][0] = stream_load(a.val + idx);
+                } else {
+                    typedef float f2 __attribute__((ext_vector_type(2)));
+                    const f2 t = stream_load(reinterpret_cast<const f2 *>(a.val) + idx);
+                    av[h][0] = t[0];
+                    av[h][1] = t[1];
+                }
             }
         }
     };
 
     // The next chunk's colIdx/val are requested before the current chunk's gathers, so
     // that a chunk costs one memory round trip, not two.
-    int c_next;
-    float av_next[V];
+    int c_next[NH];
+    float av_next[NH][V];
     load_entry(head, c_next, av_next);
-    for (int base = head; base < tail; base += LPR) {
-        const int c = c_next;
-        float av[V];
+    for (int base = head; base < tail; base += CH) {
+        long off[NH]; // DPP: in bytes, computed once by the lane that holds the entry
+        int c[NH];
+        float av[NH][V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) av[v] = av_next[v];
-        load_entry(base + LPR, c_next, av_next);
-        const int cnt = min(LPR, tail - base);
+        for (int h = 0; h < NH; ++h) {
+            c[h] = c_next[h];
+            off[h] = (long)c[h] * (K * 4);
+#pragma unroll
+            for (int v = 0; v < V; ++v) av[h][v] = av_next[h][v];
+        }
+        load_entry(base + CH, c_next, av_next);
+        const int cnt = min(CH, tail - base);
 
         float part[V][REP][VEC];
 #pragma unroll
@@ -329,53 +387,73 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) part[v][r][e] = 0.0f;
 
-        // U vectors per step: all broadcasts first, then all gathers, then the FMAs,
-        // so U*REP loads are in flight together.  Slots past the end of the range
-        // carry val = 0 (set above) and load nothing.  (Branching around those loads
-        // measured 1-3 % faster here than reading a row of zeros through an address select,
-        // although it costs more instructions: these kernels wait on memory.)
-        auto step = [&](int j, auto const_lane) {
-            constexpr bool CL = decltype(const_lane)::value;
-            int cj[U];
-            float aj[U][V];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                cj[u] = bcast_any<LPR, CL>(c, j + u);
-#pragma unroll
-                for (int v = 0; v < V; ++v) aj[u][v] = bcast_any<LPR, CL>(av[v], j + u);
-            }
+        // U vectors per step: all gathers first, then the FMAs, so U*REP loads are in flight
+        // together.  Slots past the end of the range carry val = 0 (set above) and load
+        // nothing.  (Branching around those loads measured 1-3 % faster here than reading a
+        // row of zeros through an address select.)  full: no such slots in this step.
+        auto step = [&](int j, auto full_step) {
+            constexpr bool FULL = decltype(full_step)::value;
+            const int h = DPP && NH > 1 ? j >> 4 : 0; // a step stays inside 16 entries
             float b[U][REP][VEC];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const float *brow = B + (long)cj[u] * K;
-                const bool ok = j + u < cnt;
+                const float *at;
+                if constexpr (DPP)
+                    at = row_ptr(B_lane, off[h], j + u);
+                else if constexpr (LPR == 64)
+                    at = a.B + (long)bcast<LPR>(c[h], j + u) * K + lane_col;
+                else
+                    at = B_lane + (long)bcast<LPR>(c[h], j + u) * K;
+                if (FULL || j + u < cnt) {
+                    load_vec<VEC>(at, b[u][0]);
 #pragma unroll
-                for (int r = 0; r < REP; ++r) {
-                    if (ok && kv[r]) {
-                        load_vec<VEC>(brow + kc[r], b[u][r]);
-                    } else {
+                    for (int r = 1; r < REP; ++r) {
+                        if (kv[r]) {
+                            load_vec<VEC>(at + r * LPR * VEC, b[u][r]);
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) b[u][r][e] = 0.0f;
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < REP; ++r)
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) b[u][r][e] = 0.0f;
-                    }
                 }
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int r = 0; r < REP; ++r)
+                for (int v = 0; v < V; ++v) {
+                    float aj;
+                    if constexpr (DPP)
+                        aj = __int_as_float(bcast16_const(__float_as_int(av[h][v]), j + u));
+                    else
+                        aj = bcast<LPR>(av[h][v], j + u);
 #pragma unroll
-                    for (int v = 0; v < V; ++v)
+                    for (int r = 0; r < REP; ++r)
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e)
-                            part[v][r][e] = fmaf(aj[u][v], b[u][r][e], part[v][r][e]);
+                        for (int e = 0; e < VEC; ++e) part[v][r][e] = fmaf(aj, b[u][r][e], part[v][r][e]);
+                }
         };
-        if constexpr (LPR == 16) {
-            // the 16 / U steps written out, so every broadcast lane is a constant
+        if constexpr (DPP) {
+            // the steps written out, so every broadcast lane is a constant
 #pragma unroll
-            for (int j = 0; j < LPR; j += U)
-                if (j < cnt) step(j, std::true_type{});
+            for (int j = 0; j < CH; j += U) {
+                if (j >= cnt) break;
+                if (wave_all(j + U <= cnt))
+                    step(j, std::true_type{});
+                else
+                    step(j, std::false_type{});
+            }
         } else {
-            for (int j = 0; j < cnt; j += U) step(j, std::false_type{});
+            for (int j = 0; j < cnt; j += U) {
+                if (wave_all(j + U <= cnt))
+                    step(j, std::true_type{});
+                else
+                    step(j, std::false_type{});
+            }
         }
 #pragma unroll
         for (int v = 0; v < V; ++v)
@@ -409,7 +487,8 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
                         store_vec_cached<VEC>(crow + kc[r], acc[v][r]);
                     } else {
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) atomicAdd(crow + kc[r] + e, acc[v][r][e]);
+                        for (int e = 0; e < VEC; ++e)
+                            if (e >= skip) atomicAdd(crow + kc[r] + e, acc[v][r][e]);
                     }
                 }
             }
@@ -631,7 +710,7 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) t[i] = 0.0f;
             }
-            store_vec_cached<VEC>(lds + r * LW + e, t);
+            store_lds<VEC>(lds + r * LW + e, t);
         }
     }
 
@@ -746,7 +825,7 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                             if constexpr (LDS) {
                                 // one ds_read of VEC floats, never predicated: slots past the
                                 // end point at the zero row, columns past K were staged as zeros
-                                load_vec<VEC>(lds + cj[u] + kl[r], b[u][r]);
+                                load_lds<VEC>(lds + cj[u] + kl[r], b[u][r]);
                             } else {
                                 const bool ok = j + u < cnt;
                                 const float *src = (ok && kv[r]) ? B + (long)cj[u] * K + kbase + kl[r]
@@ -882,12 +961,12 @@ __global__ void __launch_bounds__(256) reduce_split_kernel(const int32_t *__rest
                                                            float *C, int n_rows, int K, int skip_above,
                                                            Epilogue epi)
 {
-    const int kv = K / VEC; // vectors per row
+    const int kv = (K + VEC - 1) / VEC; // vectors per row, the last one moved back to end with it
     const long total = n_split * V * (long)kv;
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= total) return;
     const long r = t / kv;
-    const int k = (int)(t - r * kv) * VEC;
+    const int k = min((int)(t - r * kv) * VEC, K - VEC);
     const long q = r / V;
     const int v = (int)(r - q * V);
     const long row = (long)split_panels[q] * V + v;
@@ -938,8 +1017,8 @@ __global__ void __launch_bounds__(256) reduce_long_kernel(const int32_t *__restr
     const int v = (int)(r % V);
     const long row = (long)split_panels[q] * V + v;
     if (row >= n_rows) return; // the whole workgroup leaves: no barrier is skipped by a part of it
-    const int k = ((int)blockIdx.y * 16 + c) * VEC;
-    const bool live = k < K;
+    const bool live = ((int)blockIdx.y * 16 + c) * VEC < K;
+    const int k = min(((int)blockIdx.y * 16 + c) * VEC, K - VEC);
     const long s0 = split_slot[q], s1 = split_slot[q + 1];
     const long stride = (long)V * K, step = kLongReduceLanes * stride;
     float sum[VEC];
@@ -1180,10 +1259,10 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
         hipLaunchKernelGGL(fn, dim3(ls.grid_x, ls.grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);
         return hipGetLastError();
     }
-    KernelFn fn = args.epi.on && ls.ipg <= 1 ? pick_epilogue(V, S, ls.lpr, ls.vec, ls.rep)
-                                             : pick_any(V, S, ls.lpr, ls.vec, ls.rep, ls.ipg);
+    KernelFn fn = args.epi.on && ls.ipg <= 1 ? pick_epilogue(V, S, ls.k_lpr, ls.k_vec, ls.k_rep)
+                                             : pick_any(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, ls.ipg);
     if (!fn) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fn, dim3(ls.grid_x, ls.grid_y), dim3(64 * ls.waves), 0, stream, args);
+    hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), 0, stream, args);
     return hipGetLastError();
 }
 
@@ -1226,13 +1305,8 @@ hipError_t launch_reduce_split(const int32_t *split_panels, const int32_t *split
                                int32_t n_rows, int32_t K, const Epilogue &epi, hipStream_t stream)
 {
     if (n_split <= 0) return hipSuccess;
-    // 16-byte accesses need rows that start on 16-byte boundaries (the workspace always does)
-    const bool aligned = K % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(ws) % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(epi.self) % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(epi.mask) % 16 == 0;
-    const int vec = aligned ? 4 : 1;
-    const long total = n_split * V * (long)(K / vec);
+    const int vec = K >= 4 ? 4 : 1;
+    const long total = n_split * V * (long)((K + vec - 1) / vec);
     const long blocks = (total + 255) / 256;
     if (blocks > 0x7fffffffL || n_long * V > 0x7fffffffL) return hipErrorInvalidValue;
     const int skip_above = n_long > 0 ? kLongPanelSlots : 0x7fffffff;
@@ -1244,7 +1318,7 @@ hipError_t launch_reduce_split(const int32_t *split_panels, const int32_t *split
                            split_slot, (long)n_split, V, ws, C, n_rows, K, skip_above, epi);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n_long <= 0) return e;
-    const int chunks = (K / vec + 15) / 16; // 16 vectors of C per workgroup
+    const int chunks = ((K + vec - 1) / vec + 15) / 16; // 16 vectors of C per workgroup
     if (chunks > 65535) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(n_long * V), (unsigned)chunks);
     if (vec == 4)
