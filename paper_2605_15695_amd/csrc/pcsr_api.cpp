@@ -19,12 +19,22 @@ namespace {
 
 constexpr uint32_t kMagic = 0x50435352u; // "PCSR"
 
-// Bits of pcsr_params_t.flags that pcsr_select sets for widths that are no multiple of 4: the shape
-// to launch instead, with loads of 4 (or, kWidePair, 2) floats per lane at any 4-byte address;
-// lanes per row 4 << (code - 1) for codes 1 to 5.  Cleared by pcsr_set_kernel_params.
+// Bits of pcsr_params_t.flags in which pcsr_select passes a shape to launch in place of the one in
+// lanes_per_row, vec and rep (see resolve_launch): 4 (kWidePair: 2) floats per load, one (kWideTwice:
+// two) loads per lane, lanes per row 4 << (code - 1) for codes 1 to 5.  Cleared by
+// pcsr_set_kernel_params.
 constexpr int kWideShift = 16;
 constexpr int32_t kWideShape = 7 << kWideShift;
 constexpr int32_t kWidePair = 8 << kWideShift;
+constexpr int32_t kWideTwice = 16 << kWideShift;
+
+// The narrowest tile of 16-byte loads that covers a row of K columns.
+void wide_shape(int32_t K, int cap, int *lanes, int *rep)
+{
+    *lanes = 4;
+    while (*lanes * 4 < K && *lanes < cap) *lanes <<= 1;
+    *rep = *lanes == 64 && K > 256 ? 2 : 1;
+}
 
 thread_local int g_last_hip = 0;
 
@@ -234,26 +244,27 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     ls->k_rep = rep;
     ls->k_grid_x = ls->grid_x;
     ls->k_grid_y = ls->grid_y;
-    // Rows that are no multiple of 16 bytes long, from 17 columns on (below, the dword shapes are
-    // as good or better): the shape the next multiple of 4 gets, with loads of 16 bytes at
-    // 4-byte addresses, one per lane.  Only where the narrow vector is this function's or
-    // pcsr_select's choice, not where the caller asked for it.  300,000 clique rows of 27,
-    // K = 75: 64 lanes x dword x 2 145 us, 32 lanes x dwordx4 see DESIGN table.
-    if (!ls->window && ipg == 1 && K % 4 != 0 && K > 16) {
-        int wide = 0, wide_vec = 4;
+    // Where the shape above reads rows badly another one is launched in its place, with wide loads
+    // at 4-byte addresses (pcsr_select's, carried in the flags, or this function's own pick for an
+    // auto shape; never where the caller asked for lanes or vectors): widths that are no
+    // multiple of 4, and 64-column slices of rows that are no multiple of 128 bytes long, of which
+    // every slice touches a line more than it needs.
+    if (!ls->window && ipg == 1 && K > 16) {
+        int wide = 0, wide_vec = 4, wide_rep = 1;
         if (h_lpr || h_vec || h_rep) {
             if (h->flags & kWideShape) wide = 4 << ((h->flags & kWideShape) >> kWideShift) >> 1;
             if (h->flags & kWidePair) wide_vec = 2;
-        } else {
-            const int cap = h->host.S ? 16 : 64;
-            for (wide = 4; wide * 4 < K && wide < cap;) wide <<= 1;
+            if (h->flags & kWideTwice) wide_rep = 2;
+        } else if (K % 4 != 0 || (h->host.S && K > 64 && K % 32 != 0)) {
+            wide_shape(K, h->host.S && K <= 64 ? 16 : 64, &wide, &wide_rep);
         }
+        const int64_t wt = (int64_t)wide * wide_vec * wide_rep;
         if (wide) {
-            const int64_t wx = grid_for(h, waves, wide, 1), wy = (K + wide * wide_vec - 1) / (wide * wide_vec);
+            const int64_t wx = grid_for(h, waves, wide, 1), wy = (K + wt - 1) / wt;
             if (wx <= 0x7fffffffLL && wy <= 65535) {
                 ls->k_lpr = wide;
                 ls->k_vec = wide_vec;
-                ls->k_rep = 1;
+                ls->k_rep = wide_rep;
                 ls->k_grid_x = (int32_t)wx;
                 ls->k_grid_y = (int32_t)wy;
             }
@@ -294,6 +305,9 @@ struct UploadedCsr {
 
 // Returned by handle_from_device where the windows have to be chosen on the host.
 constexpr int kWindowsOnHost = 1;
+
+// Nonzeros and rows below which pcsr_operator_build stays on the host.
+constexpr int64_t kHostOperator = 10000; // 0.5 ms there, 0.65 ms on the GPU at any size up to here
 
 // A handle from CSR arrays in device memory, everything built there.
 int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
@@ -529,6 +543,43 @@ int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32
     const bool device_csr = p && (p->flags & PCSR_FLAG_DEVICE_CSR);
     UploadedCsr up;
     int herr = 0, rc = PCSR_OK;
+    const bool pick = !p || p->reserved[0] == PCSR_OPERATOR_SELECT;
+    pcsr_handle_t made[2] = {nullptr, nullptr};
+    if (!device_csr && nnz < kHostOperator && n_rows < kHostOperator && n_cols < kHostOperator) {
+        // small: the host is done before the GPU's launches and waits would be
+        auto direction = [&](int64_t nr, int64_t nc, const int32_t *rp, const int32_t *ci, const float *va,
+                             pcsr_handle_t *h) -> int {
+            pcsr_params_t prm;
+            if (pick) {
+                double f[PCSR_N_FEATURES];
+                int r = pcsr_features(nr, nc, nnz, rp, ci, 0, f, PCSR_N_FEATURES);
+                if (r == PCSR_OK) r = pcsr_select(f, K, &prm);
+                if (r != PCSR_OK) return r;
+                prm.lanes_per_row = prm.vec = prm.rep = 0;
+            } else {
+                prm = *p;
+            }
+            return pcsr_build(nr, nc, nnz, rp, ci, va, &prm, h);
+        };
+        rc = direction(n_rows, n_cols, rowptr, colidx, vals, &made[0]);
+        try {
+            if (rc == PCSR_OK && with_transpose) {
+                std::vector<int32_t> rp(n_cols + 1), ci(nnz);
+                std::vector<float> va(nnz);
+                rc = pcsr_transpose_csr(n_rows, n_cols, rowptr, colidx, vals, rp.data(), ci.data(), va.data());
+                if (rc == PCSR_OK) rc = direction(n_cols, n_rows, rp.data(), ci.data(), va.data(), &made[1]);
+            }
+        } catch (const std::bad_alloc &) {
+            rc = PCSR_E_OOM;
+        }
+        if (rc != PCSR_OK) {
+            (void)pcsr_free(made[0]);
+            return rc;
+        }
+        out[0] = made[0];
+        out[1] = made[1];
+        return PCSR_OK;
+    }
     if (!device_csr) {
         rc = up.put(n_rows, nnz, rowptr, colidx, vals);
         if (rc != PCSR_OK) return rc;
@@ -542,7 +593,6 @@ int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32
     };
     rc = pcsr::validate_device(n_rows, n_cols, nnz, rowptr, colidx, &herr);
     if (rc != PCSR_OK) return failed(rc);
-    const bool pick = !p || p->reserved[0] == PCSR_OPERATOR_SELECT;
     auto direction = [&](int64_t nr, int64_t nc, const int32_t *rp, const int32_t *ci, const float *va,
                          pcsr_handle_t *h) -> int {
         pcsr_params_t prm;
@@ -559,7 +609,6 @@ int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32
         prm.flags |= PCSR_FLAG_DEVICE_CSR | PCSR_FLAG_NO_VALIDATE;
         return pcsr_build(nr, nc, nnz, rp, ci, va, &prm, h);
     };
-    pcsr_handle_t made[2] = {nullptr, nullptr};
     rc = direction(n_rows, n_cols, rowptr, colidx, vals, &made[0]);
     if (rc == PCSR_OK && with_transpose) {
         UploadedCsr t;
@@ -769,7 +818,7 @@ int pcsr_set_kernel_params(pcsr_handle_t h, int32_t lanes_per_row, int32_t vec, 
     h->waves = waves_per_wg;
     h->ipg = items_per_group;
     constexpr int32_t kLaunchFlags = PCSR_FLAG_NO_XCD_REMAP | PCSR_FLAG_ATOMIC_SPLIT;
-    h->flags = (h->flags & ~(kLaunchFlags | kWideShape | kWidePair)) | (flags & kLaunchFlags);
+    h->flags = (h->flags & ~(kLaunchFlags | kWideShape | kWidePair | kWideTwice)) | (flags & kLaunchFlags);
     return PCSR_OK;
 }
 
@@ -923,7 +972,12 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     const bool long_uniform = !skewed && !windowed && !wide_scatter && d_hat >= 40.0 && scattered;
     const bool long_uniform_wide = long_uniform && K >= 64;
     p.S = (skewed || long_uniform_wide) ? 1 : 0;
-    p.SG = p.S ? 32 : 0; // power-law inputs: raised to 64 below for 128-column slices
+    // Items of 32 vectors where uniform rows are split, of 64 for power-law inputs (against 32:
+    // eight R-MAT graphs of 2^18 to 2^22 nodes 0-15 % faster at widths of 16 to 300, and half
+    // the workspace), except where a B of 1 GB or more is gathered in an order that has its hubs
+    // side by side (natural R-MAT ids, scale 22 from K = 64: items of 32 are 5-7 % faster).
+    const bool short_items = !skewed || (!scattered && K >= 64 && n * (double)K * 4.0 >= 1e9);
+    p.SG = p.S ? (short_items ? 32 : 64) : 0;
     p.omega = 64;
     if (p.S) p.flags |= PCSR_FLAG_COLUMN_ORDER;
     // Vector size 2 (Section 3.1) when adjacent rows share columns, and for short rows, where
@@ -973,25 +1027,27 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     p.lanes_per_row = lpr;
     p.vec = vec;
     p.rep = rep;
-    // Widths that are no multiple of 4, from 17 on and where no dword shape was chosen: the same
-    // slices as the next multiple of 4, read with wide loads at 4-byte addresses.
-    int slice = lpr * vec;
-    // (paired long scattered rows keep a wavefront of dwords: 4 % faster at K = 47)
-    if (K % 4 != 0 && K > 16 && !wide_scatter && !pair_long && !(lpr == 16 && vec == 1 && rep == 2 && K <= 32)) {
-        // two floats per lane where the rule above takes them and the last 64-column slice is well
-        // filled, and 16 lanes of two for K up to 32 unless rows are short
-        const bool narrow = K <= 32 && !p.S && d_hat >= 8.0;
-        const bool pair = narrow || (!skewed && !long_uniform && scattered && d_hat >= 8.0 && K >= 64 && (-K & 63) < 16);
-        int wide = 4, code = 1;
-        while (wide * 4 < K && wide < lpr_cap) {
-            wide <<= 1;
-            ++code;
-        }
-        if (pair) code = narrow ? 3 : 4; // 16 or 32 lanes
-        p.flags |= (pair ? kWidePair : 0) | code << kWideShift;
-        slice = pair ? 64 : wide * 4;
+    // Shape to launch in its place (see resolve_launch).  All figures: uniform columns, 12 to 136
+    // per row, R-MAT scale 20, a shuffled community graph.
+    int wide = 0, wide_rep = 1;
+    bool pair = false;
+    const bool dword = wide_scatter || (lpr == 16 && vec == 1 && rep == 2 && K <= 32);
+    if (K > 64 && K % 32 != 0 && (p.S || scattered || K % 4 != 0)) {
+        // one tile for the whole row instead of slices of 64: 1.1-1.3x
+        wide_shape(K, 64, &wide, &wide_rep);
+    } else if (K > 32 && K <= 64 && K % 32 != 0 && !p.S && scattered && d_hat >= 8.0) {
+        wide = 32; // half a wavefront per scattered row: 4-7 %
+    } else if (K % 4 != 0 && K > 16 && !dword) {
+        // 16 lanes of two floats for K up to 32 unless rows are short: 8 % on clique inputs
+        pair = K <= 32 && !p.S && d_hat >= 8.0;
+        wide_shape(K, lpr_cap, &wide, &wide_rep);
+        if (pair) wide = 16;
     }
-    if (skewed && slice > 64) p.SG = 64;
+    if (wide) {
+        int code = 1;
+        while (4 << code >> 1 < wide) ++code;
+        p.flags |= code << kWideShift | (pair ? kWidePair : 0) | (wide_rep == 2 ? kWideTwice : 0);
+    }
     // Workgroup size: four wavefronts, two for short rows and for paired long rows (eight
     // were 4-7 % slower than four on every unsplit input of the later validation sets).
     p.waves_per_wg = p.S ? 4 : (d_hat >= 16.0 && !pair_long ? 4 : 2);

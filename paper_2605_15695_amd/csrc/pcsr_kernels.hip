@@ -314,19 +314,18 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
         kc[r] = kbase + (r * LPR + lg) * VEC;
         kv[r] = kc[r] < a.K;
     }
-    // K no multiple of VEC (one load per lane only): the last vector of a row is moved back to
-    // end with it.  The columns it shares with its neighbour are computed and stored twice,
-    // the same bits; the atomic write-back skips them.
-    int skip = 0;
-    if constexpr (REP == 1) {
-        if (kv[0] && kc[0] > a.K - VEC) {
-            skip = kc[0] - (a.K - VEC);
-            kc[0] = a.K - VEC;
-        }
-    }
+    // K no multiple of VEC: the last vector of a row is moved back to end with it.  The columns it
+    // shares with its neighbour are computed and stored twice, the same bits; the atomic
+    // write-back skips them.
+#pragma unroll
+    for (int r = 0; r < REP; ++r)
+        if (kv[r]) kc[r] = min(kc[r], a.K - VEC);
     // a lane past the last column loads what its neighbour loads and stores nothing
     const int lane_col = kv[0] ? kc[0] : a.K - VEC;
     const float *__restrict__ B_lane = a.B + lane_col;
+    int step_col[REP]; // columns from the first load to the r-th
+#pragma unroll
+    for (int r = 0; r < REP; ++r) step_col[r] = kc[r] - lane_col;
 
     float acc[V][REP][VEC];
 #pragma unroll
@@ -401,15 +400,15 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
                 if constexpr (DPP)
                     at = row_ptr(B_lane, off[h], j + u);
                 else if constexpr (LPR == 64)
-                    at = a.B + (long)bcast<LPR>(c[h], j + u) * K + lane_col;
+                    at = a.B + (long)bcast<LPR>(c[h], j + u) * K;
                 else
                     at = B_lane + (long)bcast<LPR>(c[h], j + u) * K;
                 if (FULL || j + u < cnt) {
-                    load_vec<VEC>(at, b[u][0]);
+                    load_vec<VEC>(LPR == 64 ? at + lane_col : at, b[u][0]);
 #pragma unroll
                     for (int r = 1; r < REP; ++r) {
                         if (kv[r]) {
-                            load_vec<VEC>(at + r * LPR * VEC, b[u][r]);
+                            load_vec<VEC>(at + (LPR == 64 ? kc[r] : step_col[r]), b[u][r]);
                         } else {
 #pragma unroll
                             for (int e = 0; e < VEC; ++e) b[u][r][e] = 0.0f;
@@ -488,7 +487,7 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
                     } else {
 #pragma unroll
                         for (int e = 0; e < VEC; ++e)
-                            if (e >= skip) atomicAdd(crow + kc[r] + e, acc[v][r][e]);
+                            if (kc[r] + e >= kbase + (r * LPR + lg) * VEC) atomicAdd(crow + kc[r] + e, acc[v][r][e]);
                     }
                 }
             }
@@ -1097,9 +1096,10 @@ KernelFn pick(int V, int S, int lpr, int vec, int rep)
 template <int V, bool S, int LPR, int VEC> KernelFn picke_rep(int rep)
 {
     if (rep == 1) return &spmm_kernel<V, S, LPR, VEC, 1, true>;
-    if constexpr (!S && LPR == 64) {
+    if constexpr (LPR == 64) {
         if (rep == 2) return &spmm_kernel<V, S, LPR, VEC, 2, true>;
-        if (rep == 4) return &spmm_kernel<V, S, LPR, VEC, 4, true>;
+        if constexpr (!S)
+            if (rep == 4) return &spmm_kernel<V, S, LPR, VEC, 4, true>;
     }
     return nullptr;
 }
@@ -1119,10 +1119,8 @@ template <int V, bool S> KernelFn picke_lpr(int lpr, int vec, int rep)
     case 8: return picke_vec<V, S, 8>(vec, rep);
     case 16: return picke_vec<V, S, 16>(vec, rep);
     }
-    if constexpr (!S) {
-        if (lpr == 32) return picke_vec<V, S, 32>(vec, rep);
-        if (lpr == 64) return picke_vec<V, S, 64>(vec, rep);
-    }
+    if (lpr == 32) return picke_vec<V, S, 32>(vec, rep);
+    if (lpr == 64) return picke_vec<V, S, 64>(vec, rep);
     return nullptr;
 }
 KernelFn pick_epilogue(int V, int S, int lpr, int vec, int rep)
