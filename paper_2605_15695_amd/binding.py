@@ -90,6 +90,9 @@ def _lib():
         lib.pcsr_gnn_workspace_floats.argtypes = [i32, i32]
         lib.pcsr_gnn_workspace_floats.restype = i64
         lib.pcsr_gnn_linear.argtypes = [i64, i32, i32, vp, vp, i32, vp, i32, vp, vp, vp, vp, vp, vp, vp]
+        lib.pcsr_gnn_mlp.argtypes = [i64, i32, i32, vp, vp, vp, vp, vp, i32, vp, vp, vp]
+        lib.pcsr_gnn_mlp_backward.argtypes = [i64, i32, i32] + [vp] * 14
+        lib.pcsr_gnn_linear_backward.argtypes = [i64, i32, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp]
         lib.pcsr_gnn_wgrad.argtypes = [i64, i32, i32, vp, vp, vp, vp, vp, vp]
         lib.pcsr_gnn_colsum.argtypes = [i64, i32, vp, vp, vp, vp]
         for name in ("pcsr_build", "pcsr_spmm", "pcsr_free", "pcsr_set_kernel_params",
@@ -97,7 +100,8 @@ def _lib():
                      "pcsr_window_stats", "pcsr_features_device", "pcsr_reorder", "pcsr_permute_csr",
                      "pcsr_transpose_csr", "pcsr_workspace_bytes", "pcsr_reserve_workspace", "pcsr_spmm_static",
                      "pcsr_export_schedule", "pcsr_reorder_by_degree", "pcsr_spmm_epilogue", "pcsr_gnn_linear",
-                     "pcsr_gnn_wgrad", "pcsr_gnn_colsum", "pcsr_operator_build"):
+                     "pcsr_gnn_mlp", "pcsr_gnn_mlp_backward", "pcsr_gnn_linear_backward", "pcsr_gnn_wgrad",
+                     "pcsr_gnn_colsum", "pcsr_operator_build"):
             getattr(lib, name).restype = ctypes.c_int
         _LIB = lib
     return _LIB

@@ -50,6 +50,24 @@ int pcsr_gnn_linear(int64_t n, int32_t a, int32_t b, const float *X, const float
                     const float *bias, int32_t relu, const float *mask, const float *dot_aux, float *Y,
                     float *colsum_out, float *dot_out, float *ws, void *stream);
 
+// The two layers of a GIN layer in one pass: Z[n x m] = relu(X[n x a] W1^T + b1), Y[n x m] =
+// Z W2^T + b2, ReLU if asked.  UNSUPPORTED unless both widths are 16, 32, 48 or 64 and the arrays
+// 16-byte aligned; the calls above do the same then.
+int pcsr_gnn_mlp(int64_t n, int32_t a, int32_t m, const float *X, const float *W1, const float *b1, const float *W2,
+                 const float *b2, int32_t relu, float *Z, float *Y, void *stream);
+
+// Its backward from G = dL/dY: dW2 = G^T Z, db2, G1 = (G W2) where Z > 0, dW1 = G1^T A, db1, dA =
+// G1 W1 (may be null), dot = sum(dA * H) (may be null).  Same widths.
+int pcsr_gnn_mlp_backward(int64_t n, int32_t a, int32_t m, const float *G, const float *Z, const float *A,
+                          const float *H, const float *W1, const float *W2, float *dA, float *dW1, float *db1,
+                          float *dW2, float *db2, float *dot, float *ws, void *stream);
+
+// Backward of Y = X W^T, W[b x a], from G = dL/dY: dW = G^T X, dX = G W (where X > 0 if masked; may be
+// null), db and colsum = column sums of G and of dX (may be null).  Same widths.
+int pcsr_gnn_linear_backward(int64_t n, int32_t a, int32_t b, const float *G, const float *X, const float *W,
+                             int32_t masked, float *dX, float *dW, float *db, float *colsum, float *ws,
+                             void *stream);
+
 // dW[b x a] = G^T X, db[b] = column sums of G (db may be null) for G[n x b], X[n x a].
 int pcsr_gnn_wgrad(int64_t n, int32_t a, int32_t b, const float *G, const float *X, float *dW, float *db,
                    float *ws, void *stream);

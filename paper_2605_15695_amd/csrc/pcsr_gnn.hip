@@ -14,7 +14,8 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 constexpr int kWaves = 4;
-constexpr int kLinearBlocks = 2048;
+constexpr int kLinearBlocks = 768; // three per compute unit
+constexpr int kBackBlocks = 512;
 constexpr int kWgradBlocks = 512;
 constexpr int kColsumBlocks = 512;
 
@@ -27,42 +28,172 @@ struct LinearArgs {
     float *ws_dot;    // one value per workgroup
 };
 
-// A wavefront takes 32 rows of X at a time (16 where their registers would leave a SIMD with
-// one wavefront).  D = op(W)-tile (16 outputs) x X^T (16 rows): a
+// A wavefront takes 16 rows of X at a time.  D = op(W)-tile (16 outputs) x X^T (16 rows): a
 // lane reads 16 bytes of one row per 16 inputs (component s of lane l is k = 4*(l/16) + s)
 // and ends up with four consecutive outputs of one row, so loads and stores are 64-byte pieces of
-// rows and X never goes through LDS; the weight fragments do (16 KB for 64 x 64), read as
-// one ds_read_b128 per 4 matrix instructions.  Bound by memory: 2,000,000 x 64 -> 64 is 1.02 GB
-// and 16.4 GFLOP (104 us at the fp32 matrix peak); measured 245 us without a mask, where the
-// vendor GEMM took 290-320 us and left bias, ReLU and mask to passes of 150-230 us each.
-// VEC: widths are multiples of 4 and the arrays 16-byte aligned.  RED: dot and/or column sums.
-template <int KT, int NT, bool VEC, bool RED>
-__global__ void __launch_bounds__(64 * kWaves, KT *NT <= 16 ? (RED ? 3 : 4) : 2) linear_kernel(LinearArgs p)
+// rows, X never goes through LDS, and what comes out has the layout that goes in: two layers
+// can be chained in registers (mlp_kernel).  The weight fragments are in LDS (16 KB for 64 x
+// 64), read as one ds_read_b128 per 4 matrix instructions.
+// Bound by memory: 2,000,000 x 64 -> 64 is 1.02 GB and 16.4 GFLOP (104 us at the fp32 matrix
+// peak).  The next rows are requested before this step's products, and no more workgroups are
+// started than run at once: with 2048 of them, 32 rows a step and no such request the same
+// took 264 us, 367 us with a mask; now 220 and 285 (piece_kernel), where the vendor GEMM takes
+// 290-320 us and leaves bias, ReLU and mask to passes of 150-230 us each.
+// VEC: widths that are multiples of 4, arrays 16-byte aligned.  RED: dot and/or column sums.
+constexpr int blocks_per_cu(int kt, int nt) { return kt + nt <= 8 ? 3 : 2; } // registers and LDS allow no more
+// piece_kernel: eight wavefronts to one copy of the weights where two copies do not fit
+constexpr int piece_waves(int kt, int nt) { return kt + nt > 12 ? 8 : 4; }
+constexpr int piece_blocks_per_cu(int kt, int nt) { return kt + nt > 12 ? 1 : blocks_per_cu(kt, nt); }
+
+// weight fragments of one layer: fragment (kt, nt), lane l, component s is
+// W[out = 16 nt + l%16][in = 16 kt + 4 (l/16) + s] (transposed: W[in][out])
+template <int KT, int NT>
+__device__ __forceinline__ void stage_weights(f4 *wfrag, const float *W, int a, int b, int transposed)
 {
-    constexpr int H = KT + NT >= 10 ? 1 : 2; // 16-row pieces per step
-    __shared__ f4 wfrag[KT * NT * 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane & 15, q = lane >> 4;
-    for (int f = tid; f < KT * NT * 64; f += 64 * kWaves) {
+    for (int f = threadIdx.x; f < KT * NT * 64; f += blockDim.x) {
         const int l = f & 63, t = f >> 6, kt = t / NT, nt = t - kt * NT;
         const int out = nt * 16 + (l & 15), in0 = kt * 16 + 4 * (l >> 4);
         f4 w = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (out < p.b) {
+        if (out < b) {
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-                if (in0 + s < p.a)
-                    w[s] = p.w_transposed ? p.W[(long)(in0 + s) * p.b + out] : p.W[(long)out * p.a + in0 + s];
+                if (in0 + s < a) w[s] = transposed ? W[(long)(in0 + s) * b + out] : W[(long)out * a + in0 + s];
         }
         wfrag[f] = w;
     }
-    f4 bias[NT];
+}
+
+// acc += op(W) x for 16 rows
+template <int KT, int NT> __device__ __forceinline__ void multiply(const f4 *wfrag, int lane, const f4 (&x)[KT], f4 (&acc)[NT])
+{
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int kt = 0; kt < KT; ++kt) {
+        f4 w[NT];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int o = nt * 16 + 4 * q + s;
-            bias[nt][s] = (p.bias && o < p.b) ? p.bias[o] : 0.0f;
+        for (int nt = 0; nt < NT; ++nt) w[nt] = wfrag[(kt * NT + nt) * 64 + lane];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma4(w[nt][s], x[kt][s], acc[nt]);
+    }
+}
+
+// the bias waits in LDS: in registers it would cost what the row pieces need
+template <int NT> __device__ __forceinline__ void stage_bias(f4 *bias, const float *b, int width)
+{
+    for (int o = threadIdx.x; o < 16 * NT; o += blockDim.x)
+        reinterpret_cast<float *>(bias)[o] = b && o < width ? b[o] : 0.0f;
+}
+template <int NT> __device__ __forceinline__ void start_from(const f4 *bias, int lane, f4 (&acc)[NT])
+{
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = bias[nt * 4 + (lane >> 4)];
+}
+
+// Sixteen rows of exactly 16 T floats are one piece of memory.  It is read and written with the lanes
+// side by side, T times 1 KB (lane l, step u: 16-byte word 64 u + l of the piece), and turned
+// to and from the fragments through an LDS patch of the wavefront's own.  Straight from the fragments
+// every access would touch 16 rows, 64 bytes of each: 2,000,000 rows x 64 took 222 us so to write, 3.7 TB/s for
+// 16 -> 64 columns in all; through the patch 5.6.
+constexpr int patch_ld(int t) { return 16 * t + 4; } // floats per row
+constexpr int patch_floats(int t) { return 16 * patch_ld(t); }
+
+// LDS keeps the order of one wavefront's accesses: only the compiler has to keep it as well
+__device__ __forceinline__ void patch_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+template <int T> __device__ __forceinline__ void load_piece(const float *piece, int lane, long rows, f4 (&x)[T])
+{
+    if (rows >= 16) {
+#pragma unroll
+        for (int u = 0; u < T; ++u) x[u] = reinterpret_cast<const f4 *>(piece)[u * 64 + lane];
+    } else { // zeros past the end
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+            x[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            if ((u * 64 + lane) / (4 * T) < rows) x[u] = reinterpret_cast<const f4 *>(piece)[u * 64 + lane];
         }
+    }
+}
+template <int T> __device__ __forceinline__ void store_piece(float *piece, int lane, long rows, const f4 (&x)[T])
+{
+#pragma unroll
+    for (int u = 0; u < T; ++u)
+        if ((u * 64 + lane) / (4 * T) < rows) reinterpret_cast<f4 *>(piece)[u * 64 + lane] = x[u];
+}
+// straight to the fragments
+template <int T> __device__ __forceinline__ void load_frags(const float *piece, int lane, long rows, f4 (&x)[T])
+{
+    const unsigned at = (lane & 15) * (16 * T) + 4 * (lane >> 4);
+    if (rows >= 16 || (lane & 15) < rows) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) x[t] = *reinterpret_cast<const f4 *>(piece + at + t * 16);
+    } else {
+#pragma unroll
+        for (int t = 0; t < T; ++t) x[t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+}
+template <int T> __device__ __forceinline__ void store_frags(float *piece, int lane, long rows, const f4 (&x)[T])
+{
+    const unsigned at = (lane & 15) * (16 * T) + 4 * (lane >> 4);
+    if (rows >= 16 || (lane & 15) < rows) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) *reinterpret_cast<f4 *>(piece + at + t * 16) = x[t];
+    }
+}
+template <int T, int LD> __device__ __forceinline__ void piece_to_patch(float *patch, int lane, const f4 (&x)[T])
+{
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+        const int i = u * 64 + lane;
+        *reinterpret_cast<f4 *>(patch + i / (4 * T) * LD + i % (4 * T) * 4) = x[u];
+    }
+}
+template <int T, int LD> __device__ __forceinline__ void patch_to_piece(const float *patch, int lane, f4 (&x)[T])
+{
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+        const int i = u * 64 + lane;
+        x[u] = *reinterpret_cast<const f4 *>(patch + i / (4 * T) * LD + i % (4 * T) * 4);
+    }
+}
+template <int T, int LD> __device__ __forceinline__ void frags_to_patch(float *patch, int lane, const f4 (&x)[T])
+{
+#pragma unroll
+    for (int t = 0; t < T; ++t) *reinterpret_cast<f4 *>(patch + (lane & 15) * LD + t * 16 + 4 * (lane >> 4)) = x[t];
+}
+template <int T> __device__ __forceinline__ void frags_to_piece(float *patch, int lane, f4 (&x)[T])
+{
+    patch_fence();
+    frags_to_patch<T, patch_ld(T)>(patch, lane, x);
+    patch_fence();
+    patch_to_piece<T, patch_ld(T)>(patch, lane, x);
+}
+template <int T> __device__ __forceinline__ void relu_rows(f4 (&x)[T]) // NaN stays NaN
+{
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x[t][s] = x[t][s] <= 0.0f ? 0.0f : x[t][s];
+}
+template <int T> __device__ __forceinline__ void mask_rows(f4 (&x)[T], const f4 (&m)[T])
+{
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x[t][s] = m[t][s] <= 0.0f ? 0.0f : x[t][s];
+}
+
+template <int KT, int NT, bool VEC, bool RED>
+__global__ void __launch_bounds__(64 * kWaves, blocks_per_cu(KT, NT)) linear_kernel(LinearArgs p)
+{
+    __shared__ f4 wfrag[KT * NT * 64], bias[NT * 4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r = lane & 15, q = lane >> 4;
+    stage_weights<KT, NT>(wfrag, p.W, p.a, p.b, p.w_transposed);
+    stage_bias<NT>(bias, p.bias, p.b);
     __syncthreads();
 
     f4 csum[RED ? NT : 1];
@@ -72,84 +203,74 @@ __global__ void __launch_bounds__(64 * kWaves, KT *NT <= 16 ? (RED ? 3 : 4) : 2)
         for (int nt = 0; nt < NT; ++nt) csum[nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     }
 
-    const long groups = (p.n + 16 * H - 1) / (16 * H);
-    for (long g = (long)blockIdx.x * kWaves + wave; g < groups; g += (long)gridDim.x * kWaves) {
-        // keeps the weight fragments in LDS: hoisted out of the loop they would fill the registers
-        asm volatile("" ::: "memory");
-        f4 x[H][KT];
+    const long groups = (p.n + 15) >> 4, stride = (long)gridDim.x * kWaves;
+    auto fetch = [&](long g, f4 (&x)[KT]) {
+        long row = g * 16 + r;
+        row = row < p.n ? row : p.n - 1; // results of the rows past the end are dropped below
+        const float *xr = p.X + row * p.a;
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
-            long row = (g * H + h) * 16 + r;
-            row = row < p.n ? row : p.n - 1; // results of the rows past the end are dropped below
-            const float *xr = p.X + row * p.a;
+        for (int kt = 0; kt < KT; ++kt) {
+            const int c = kt * 16 + 4 * q;
+            if constexpr (VEC) {
+                x[kt] = c < p.a ? *reinterpret_cast<const f4 *>(xr + c) : f4{0.0f, 0.0f, 0.0f, 0.0f};
+            } else {
 #pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
-                const int c = kt * 16 + 4 * q;
-                if constexpr (VEC) {
-                    x[h][kt] = c < p.a ? *reinterpret_cast<const f4 *>(xr + c) : f4{0.0f, 0.0f, 0.0f, 0.0f};
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) x[h][kt][s] = c + s < p.a ? xr[c + s] : 0.0f;
-                }
+                for (int s = 0; s < 4; ++s) x[kt][s] = c + s < p.a ? xr[c + s] : 0.0f;
             }
         }
-        f4 acc[H][NT];
+    };
+    long g = (long)blockIdx.x * kWaves + wave;
+    f4 xn[KT]; // the next rows are requested before this step's products
+    if (g < groups) fetch(g, xn);
+    for (; g < groups; g += stride) {
+        // keeps the weight fragments in LDS: hoisted out of the loop they would fill the registers
+        asm volatile("" ::: "memory");
+        f4 x[KT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+        for (int kt = 0; kt < KT; ++kt) x[kt] = xn[kt];
+        if (g + stride < groups) fetch(g + stride, xn);
+        f4 acc[NT];
+        start_from<NT>(bias, lane, acc);
+        multiply<KT, NT>(wfrag, lane, x, acc);
+        const long row = g * 16 + r;
+        if (row >= p.n) continue;
+        const long at = row * p.b;
 #pragma unroll
-            for (int h = 0; h < H; ++h) acc[h][nt] = bias[nt];
+        for (int nt = 0; nt < NT; ++nt) {
+            const int c = nt * 16 + 4 * q;
+            f4 v = acc[nt];
+            if (p.relu) {
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
+                for (int s = 0; s < 4; ++s) v[s] = v[s] <= 0.0f ? 0.0f : v[s];
+            }
+            if constexpr (VEC) {
+                if (c < p.b) {
+                    if constexpr (RED) {
+                        if (p.aux) {
+                            const f4 u = *reinterpret_cast<const f4 *>(p.aux + at + c);
+                            dot += (v[0] * u[0] + v[1] * u[1]) + (v[2] * u[2] + v[3] * u[3]);
+                        }
+                    }
+                    if (p.mask) {
+                        const f4 m = *reinterpret_cast<const f4 *>(p.mask + at + c);
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const f4 w = wfrag[(kt * NT + nt) * 64 + lane];
+                        for (int s = 0; s < 4; ++s) v[s] = m[s] <= 0.0f ? 0.0f : v[s];
+                    }
+                    if constexpr (RED) csum[nt] += v;
+                    if (p.Y) *reinterpret_cast<f4 *>(p.Y + at + c) = v;
+                }
+            } else {
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int h = 0; h < H; ++h) acc[h][nt] = mfma4(w[s], x[h][kt][s], acc[h][nt]);
-            }
-#pragma unroll
-        for (int h = 0; h < H; ++h) {
-            const long row = (g * H + h) * 16 + r;
-            if (row >= p.n) continue;
-            const long at = row * p.b;
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int c = nt * 16 + 4 * q;
-                f4 v = acc[h][nt];
-                if (p.relu) {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) v[s] = v[s] <= 0.0f ? 0.0f : v[s];
-                }
-                if constexpr (VEC) {
-                    if (c < p.b) {
+                    if (c + s < p.b) {
+                        float e = v[s];
                         if constexpr (RED) {
-                            if (p.aux) {
-                                const f4 u = *reinterpret_cast<const f4 *>(p.aux + at + c);
-                                dot += (v[0] * u[0] + v[1] * u[1]) + (v[2] * u[2] + v[3] * u[3]);
-                            }
+                            if (p.aux) dot += e * p.aux[at + c + s];
                         }
-                        if (p.mask) {
-                            const f4 m = *reinterpret_cast<const f4 *>(p.mask + at + c);
-#pragma unroll
-                            for (int s = 0; s < 4; ++s) v[s] = m[s] <= 0.0f ? 0.0f : v[s];
-                        }
-                        if constexpr (RED) csum[nt] += v;
-                        if (p.Y) *reinterpret_cast<f4 *>(p.Y + at + c) = v;
+                        if (p.mask && p.mask[at + c + s] <= 0.0f) e = 0.0f;
+                        if constexpr (RED) csum[nt][s] += e;
+                        if (p.Y) p.Y[at + c + s] = e;
                     }
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        if (c + s < p.b) {
-                            float e = v[s];
-                            if constexpr (RED) {
-                                if (p.aux) dot += e * p.aux[at + c + s];
-                            }
-                            if (p.mask && p.mask[at + c + s] <= 0.0f) e = 0.0f;
-                            if constexpr (RED) csum[nt][s] += e;
-                            if (p.Y) p.Y[at + c + s] = e;
-                        }
-                }
             }
         }
     }
@@ -179,6 +300,323 @@ __global__ void __launch_bounds__(64 * kWaves, KT *NT <= 16 ? (RED ? 3 : 4) : 2)
             }
         }
         if (p.ws_dot && tid == 0) p.ws_dot[blockIdx.x] = (dsh[0] + dsh[1]) + (dsh[2] + dsh[3]);
+    }
+}
+
+// Sums over a workgroup in a fixed order.  `lds` may be the patches.
+template <int T, bool FRAGS>
+__device__ __forceinline__ void collect_colsum(float *lds, const f4 (&csum)[T], float *out)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __syncthreads();
+    f4 *s = reinterpret_cast<f4 *>(lds) + wave * T * 64; // word i: columns 4 (i mod 4T) and on
+#pragma unroll
+    for (int u = 0; u < T; ++u) s[FRAGS ? (lane & 15) * (4 * T) + 4 * u + (lane >> 4) : u * 64 + lane] = csum[u];
+    __syncthreads();
+    for (int c = tid; c < 16 * T; c += blockDim.x) {
+        float t = 0.0f;
+        for (int i = 0; i < (int)blockDim.x / 4; ++i) t += lds[i * (16 * T) + c];
+        out[c] = t;
+    }
+}
+__device__ __forceinline__ void collect_dot(float *lds, float dot, float *out)
+{
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) dot += __shfl_xor(dot, m);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = dot;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = (lds[0] + lds[1]) + (lds[2] + lds[3]);
+        if (blockDim.x == 512) t += (lds[4] + lds[5]) + (lds[6] + lds[7]);
+        *out = t;
+    }
+}
+
+// Exact widths, a = 16 KT and b = 16 NT: as linear_kernel, in pieces.
+template <int KT, int NT, bool RED>
+__global__ void __launch_bounds__(64 * piece_waves(KT, NT), piece_waves(KT, NT) == 8 ? 2 : blocks_per_cu(KT, NT)) piece_kernel(LinearArgs p)
+{
+    constexpr int kW = piece_waves(KT, NT), kPatch = patch_floats(NT);
+    __shared__ f4 wfrag[KT * NT * 64], bias[NT * 4];
+    __shared__ __align__(16) float patches[kW * kPatch];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *patch = patches + wave * kPatch;
+    stage_weights<KT, NT>(wfrag, p.W, 16 * KT, 16 * NT, p.w_transposed);
+    stage_bias<NT>(bias, p.bias, 16 * NT);
+    __syncthreads();
+
+    f4 csum[RED ? NT : 1];
+    float dot = 0.0f;
+    if constexpr (RED) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) csum[nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    const long groups = (p.n + 15) >> 4, stride = (long)gridDim.x * kW;
+    long g = (long)blockIdx.x * kW + wave;
+    f4 xn[KT]; // the next rows are requested before this step's products
+    if (g < groups) load_frags<KT>(p.X + g * (256 * KT), lane, p.n - g * 16, xn);
+    for (; g < groups; g += stride) {
+        asm volatile("" ::: "memory"); // as in linear_kernel
+        const long rows = p.n - g * 16;
+        f4 x[KT], y[NT];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) x[kt] = xn[kt];
+        if (g + stride < groups) load_frags<KT>(p.X + (g + stride) * (256 * KT), lane, rows - stride * 16, xn);
+        f4 m[NT]; // aux, or the mask; callers have one of them
+        const float *first = RED && p.aux ? p.aux : p.mask;
+        if (first) load_piece<NT>(first + g * (256 * NT), lane, rows, m);
+        start_from<NT>(bias, lane, y);
+        multiply<KT, NT>(wfrag, lane, x, y);
+        if (p.relu) relu_rows<NT>(y);
+        frags_to_piece<NT>(patch, lane, y);
+        if constexpr (RED) {
+            if (p.aux) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    dot += (y[t][0] * m[t][0] + y[t][1] * m[t][1]) + (y[t][2] * m[t][2] + y[t][3] * m[t][3]);
+                if (p.mask) load_piece<NT>(p.mask + g * (256 * NT), lane, rows, m);
+            }
+        }
+        if (p.mask) mask_rows<NT>(y, m);
+        if constexpr (RED) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) csum[t] += y[t];
+        }
+        if (p.Y) store_piece<NT>(p.Y + g * (256 * NT), lane, rows, y);
+    }
+    if constexpr (RED) {
+        if (p.ws_colsum) collect_colsum<NT, false>(patches, csum, p.ws_colsum + (long)blockIdx.x * (16 * NT));
+        if (p.ws_dot) collect_dot(patches, dot, p.ws_dot + blockIdx.x);
+    }
+}
+
+// Two layers in one pass: Z = relu(X W1^T + b1), Y = Z W2^T + b2 (relu).  Exact widths: a = 16 KT,
+// both layers 16 MT outputs.  Z is stored for the backward pass and not read back: 2,000,000 x 64
+// -> 64 -> 64 takes 367 us where two piece_kernel passes take 464.
+struct MlpArgs {
+    long n;
+    int relu;
+    const float *X, *W1, *b1, *W2, *b2;
+    float *Z, *Y;
+};
+template <int KT, int MT> __global__ void __launch_bounds__(64 * kWaves, 3) mlp_kernel(MlpArgs p)
+{
+    constexpr int kPatch = patch_floats(MT);
+    __shared__ f4 w1[KT * MT * 64], w2[MT * MT * 64], bias1[MT * 4], bias2[MT * 4];
+    __shared__ __align__(16) float patches[kWaves * kPatch];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float *patch = patches + wave * kPatch;
+    stage_weights<KT, MT>(w1, p.W1, 16 * KT, 16 * MT, 0);
+    stage_weights<MT, MT>(w2, p.W2, 16 * MT, 16 * MT, 0);
+    stage_bias<MT>(bias1, p.b1, 16 * MT);
+    stage_bias<MT>(bias2, p.b2, 16 * MT);
+    __syncthreads();
+    const long groups = (p.n + 15) >> 4, stride = (long)gridDim.x * kWaves;
+    long g = (long)blockIdx.x * kWaves + wave;
+    f4 xn[KT];
+    if (g < groups) load_frags<KT>(p.X + g * (256 * KT), lane, p.n - g * 16, xn);
+    for (; g < groups; g += stride) {
+        asm volatile("" ::: "memory"); // as in linear_kernel
+        const long rows = p.n - g * 16;
+        f4 x[KT], z[MT], y[MT];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) x[kt] = xn[kt];
+        if (g + stride < groups) load_frags<KT>(p.X + (g + stride) * (256 * KT), lane, rows - stride * 16, xn);
+        start_from<MT>(bias1, lane, z);
+        multiply<KT, MT>(w1, lane, x, z);
+        relu_rows<MT>(z);
+        start_from<MT>(bias2, lane, y);
+        multiply<MT, MT>(w2, lane, z, y);
+        if (p.relu) relu_rows<MT>(y);
+        frags_to_piece<MT>(patch, lane, z);
+        store_piece<MT>(p.Z + g * (256 * MT), lane, rows, z);
+        frags_to_piece<MT>(patch, lane, y);
+        store_piece<MT>(p.Y + g * (256 * MT), lane, rows, y);
+    }
+}
+
+// Backward of one layer, or of the two of a GIN layer, in one pass over its arrays:
+//   dW2 = G^T Z, db2 = sums of G, G1 = (G W2) masked by Z > 0,
+// and with TWO   dW1 = G1^T A, db1 = sums of G1, dA = G1 W1, dot = sum(dA * H);
+// without it G1 is stored and its column sums are taken.  Exact widths: G 16 BT, Z 16 MT, A and H
+// 16 AT.  The products with the weights run on registers as in mlp_kernel.  For those with
+// G^T and G1^T the rows are the k of the matrix instruction, so 16 rows of both operands are
+// turned in an LDS patch of the wavefront's own: written as they are held, read T consecutive
+// columns of one row per lane, which feeds T tiles (tile t holds the columns T*i + t, as in
+// wgrad_kernel).  G, Z, A and H are read once and G1 never leaves the registers: 2.6 GB for
+// 2,000,000 x 64 (TWO) where the separate kernels move 5.6 GB, 679 us where they take 977; what
+// bounds it is the matrix rate (65.5 GFLOP, 428 us) with two wavefronts to a SIMD, all that the
+// accumulators leave room for.  Without TWO 326 us for 496.
+struct BackArgs {
+    long n;
+    int masked;
+    const float *G, *Z, *W2, *A, *H, *W1;
+    float *out;    // dA, or G1 (may be null)
+    float *ws;     // per workgroup: dW2, db2, then dW1, db1, dot (TWO) or the sums of G1
+    long ws_stride;
+};
+constexpr int back_ld(int t) { return 16 * t + 16; } // floats per row: four rows on different banks
+
+// acc += P^T Q over the 16 rows in the patch; psum: column sums of P
+template <int PT, int QT>
+__device__ __forceinline__ void turned_product(const float *patch, int lane, f4 (&acc)[PT][QT], float (&psum)[PT])
+{
+    constexpr int LP = back_ld(PT), LQ = back_ld(QT);
+    const int c = lane & 15, q = lane >> 4;
+    const float *qpatch = patch + 16 * LP;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        float a[PT], b[QT];
+#pragma unroll
+        for (int t = 0; t < PT; ++t) a[t] = patch[(4 * u + q) * LP + PT * c + t];
+#pragma unroll
+        for (int t = 0; t < QT; ++t) b[t] = qpatch[(4 * u + q) * LQ + QT * c + t];
+#pragma unroll
+        for (int i = 0; i < PT; ++i) {
+            psum[i] += a[i];
+#pragma unroll
+            for (int j = 0; j < QT; ++j) acc[i][j] = mfma4(a[i], b[j], acc[i][j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+// the four wavefronts' accumulators, in order, to out[16 PT x 16 QT] and sums[16 PT]; `red`: LDS
+template <int PT, int QT>
+__device__ __forceinline__ void collect(float *red, const f4 (&acc)[PT][QT], float (&psum)[PT], float *out, float *sums)
+{
+    constexpr int LD = QT * 16 + 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 15, q = lane >> 4;
+    float *sred = red + PT * 16 * LD;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+        psum[i] += __shfl_xor(psum[i], 16);
+        psum[i] += __shfl_xor(psum[i], 32);
+    }
+    __syncthreads();
+    for (int w = 0; w < kWaves; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int i = 0; i < PT; ++i) {
+#pragma unroll
+                for (int j = 0; j < QT; ++j)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        float &d = red[((4 * q + s) * PT + i) * LD + c * QT + j];
+                        d = w ? d + acc[i][j][s] : acc[i][j][s];
+                    }
+                if (q == 0) {
+                    float &d = sred[c * PT + i];
+                    d = w ? d + psum[i] : psum[i];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    for (int e = tid; e < PT * QT * 256; e += 64 * kWaves) out[e] = red[(e / (QT * 16)) * LD + e % (QT * 16)];
+    if (tid < PT * 16) sums[tid] = sred[tid];
+    __syncthreads();
+}
+
+template <int BT, int MT, int AT, bool TWO>
+__global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
+{
+    constexpr int kPatch1 = 16 * (back_ld(BT) + back_ld(MT)), kPatch2 = TWO ? 16 * (back_ld(MT) + back_ld(AT)) : 0;
+    constexpr int kPatch = kPatch1 > kPatch2 ? kPatch1 : kPatch2;
+    constexpr int kRed1 = BT * 16 * (MT * 16 + 1) + BT * 16, kRed2 = TWO ? MT * 16 * (AT * 16 + 1) + MT * 16 : 0;
+    constexpr int kRed = kRed1 > kRed2 ? kRed1 : kRed2;
+    __shared__ f4 w2[BT * MT * 64];
+    __shared__ f4 w1[TWO ? MT * AT * 64 : 1];
+    __shared__ __align__(16) float lds[kWaves * kPatch > kRed ? kWaves * kPatch : kRed];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *patch = lds + wave * kPatch;
+    stage_weights<BT, MT>(w2, p.W2, 16 * BT, 16 * MT, 1);
+    if constexpr (TWO) stage_weights<MT, AT>(w1, p.W1, 16 * MT, 16 * AT, 1);
+    __syncthreads();
+
+    const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f4 acc2[BT][MT], acc1[TWO ? MT : 1][TWO ? AT : 1], csum[MT];
+    float sum2[BT], sum1[TWO ? MT : 1], dot = 0.0f;
+#pragma unroll
+    for (int i = 0; i < BT; ++i) {
+        sum2[i] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < MT; ++j) acc2[i][j] = zero;
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) csum[i] = zero;
+    if constexpr (TWO) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            sum1[i] = 0.0f;
+#pragma unroll
+            for (int j = 0; j < AT; ++j) acc1[i][j] = zero;
+        }
+    }
+
+    constexpr int LG = back_ld(BT), LZ = back_ld(MT), LA = back_ld(AT);
+    const long groups = (p.n + 15) >> 4, stride = (long)gridDim.x * kWaves;
+    long g = (long)blockIdx.x * kWaves + wave;
+    f4 gg[BT], zz[MT];
+    // the next rows of G and Z go into the same registers once these are in the patch and used;
+    // the product that follows covers the wait
+    auto next = [&](long g) {
+        if (g < groups) {
+            load_frags<BT>(p.G + g * (256 * BT), lane, p.n - g * 16, gg);
+            load_frags<MT>(p.Z + g * (256 * MT), lane, p.n - g * 16, zz);
+        }
+    };
+    next(g);
+    for (; g < groups; g += stride) {
+        const long rows = p.n - g * 16;
+        f4 g1[MT], aa[TWO ? AT : 1];
+        if constexpr (TWO) load_piece<AT>(p.A + g * (256 * AT), lane, rows, aa);
+        patch_fence();
+        frags_to_patch<BT, LG>(patch, lane, gg);
+        frags_to_patch<MT, LZ>(patch + 16 * LG, lane, zz);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) g1[t] = zero;
+        multiply<BT, MT>(w2, lane, gg, g1);
+        if (TWO || p.masked) mask_rows<MT>(g1, zz);
+        patch_fence(); // keeps weight fragments and patches in LDS, and what follows below
+        if constexpr (!TWO) {
+            next(g + stride);
+            if (p.out) store_frags<MT>(p.out + g * (256 * MT), lane, rows, g1);
+#pragma unroll
+            for (int t = 0; t < MT; ++t) csum[t] += g1[t];
+            turned_product<BT, MT>(patch, lane, acc2, sum2);
+        } else {
+            turned_product<BT, MT>(patch, lane, acc2, sum2);
+            patch_fence();
+            frags_to_patch<MT, LZ>(patch, lane, g1);
+            piece_to_patch<AT, LA>(patch + 16 * LZ, lane, aa);
+            patch_fence();
+            if (p.H) load_frags<AT>(p.H + g * (256 * AT), lane, rows, aa);
+            f4 da[AT];
+#pragma unroll
+            for (int t = 0; t < AT; ++t) da[t] = zero;
+            multiply<MT, AT>(w1, lane, g1, da);
+            if (p.H) {
+#pragma unroll
+                for (int t = 0; t < AT; ++t)
+                    dot += (da[t][0] * aa[t][0] + da[t][1] * aa[t][1]) + (da[t][2] * aa[t][2] + da[t][3] * aa[t][3]);
+            }
+            if (p.out) store_frags<AT>(p.out + g * (256 * AT), lane, rows, da);
+            patch_fence();
+            next(g + stride);
+            turned_product<MT, AT>(patch, lane, acc1, sum1);
+        }
+    }
+
+    float *ws = p.ws + (long)blockIdx.x * p.ws_stride;
+    collect<BT, MT>(lds, acc2, sum2, ws, ws + BT * MT * 256);
+    ws += BT * MT * 256 + BT * 16;
+    if constexpr (TWO) {
+        collect<MT, AT>(lds, acc1, sum1, ws, ws + MT * AT * 256);
+        collect_dot(lds, dot, ws + MT * AT * 256 + MT * 16);
+    } else {
+        collect_colsum<MT, true>(lds, csum, ws);
     }
 }
 
@@ -379,34 +817,35 @@ int tiles(int w, bool vec)
     if (t <= 6) return vec ? 6 : 8;
     return 8;
 }
-template <int KT, int NT> LinearFn pick_linear(bool vec, bool red)
+template <int KT, int NT> LinearFn pick_linear(int mode, bool red)
 {
-    if (vec) return red ? &linear_kernel<KT, NT, true, true> : &linear_kernel<KT, NT, true, false>;
+    if (mode == 2) return red ? &piece_kernel<KT, NT, true> : &piece_kernel<KT, NT, false>;
+    if (mode == 1) return red ? &linear_kernel<KT, NT, true, true> : &linear_kernel<KT, NT, true, false>;
     if constexpr (KT != 3 && KT != 6 && NT != 3 && NT != 6)
         return red ? &linear_kernel<KT, NT, false, true> : &linear_kernel<KT, NT, false, false>;
     return nullptr;
 }
-template <int KT> LinearFn pick_linear_n(int nt, bool vec, bool red)
+template <int KT> LinearFn pick_linear_n(int nt, int mode, bool red)
 {
     switch (nt) {
-    case 1: return pick_linear<KT, 1>(vec, red);
-    case 2: return pick_linear<KT, 2>(vec, red);
-    case 3: return pick_linear<KT, 3>(vec, red);
-    case 4: return pick_linear<KT, 4>(vec, red);
-    case 6: return pick_linear<KT, 6>(vec, red);
-    case 8: return pick_linear<KT, 8>(vec, red);
+    case 1: return pick_linear<KT, 1>(mode, red);
+    case 2: return pick_linear<KT, 2>(mode, red);
+    case 3: return pick_linear<KT, 3>(mode, red);
+    case 4: return pick_linear<KT, 4>(mode, red);
+    case 6: return pick_linear<KT, 6>(mode, red);
+    case 8: return pick_linear<KT, 8>(mode, red);
     }
     return nullptr;
 }
-LinearFn pick_linear_kn(int kt, int nt, bool vec, bool red)
+LinearFn pick_linear_kn(int kt, int nt, int mode, bool red)
 {
     switch (kt) {
-    case 1: return pick_linear_n<1>(nt, vec, red);
-    case 2: return pick_linear_n<2>(nt, vec, red);
-    case 3: return pick_linear_n<3>(nt, vec, red);
-    case 4: return pick_linear_n<4>(nt, vec, red);
-    case 6: return pick_linear_n<6>(nt, vec, red);
-    case 8: return pick_linear_n<8>(nt, vec, red);
+    case 1: return pick_linear_n<1>(nt, mode, red);
+    case 2: return pick_linear_n<2>(nt, mode, red);
+    case 3: return pick_linear_n<3>(nt, mode, red);
+    case 4: return pick_linear_n<4>(nt, mode, red);
+    case 6: return pick_linear_n<6>(nt, mode, red);
+    case 8: return pick_linear_n<8>(nt, mode, red);
     }
     return nullptr;
 }
@@ -438,6 +877,50 @@ WgradFn pick_wgrad(Side g, Side x)
     return g.v ? pick_wgrad_x<4, true>(x) : pick_wgrad_x<4, false>(x);
 }
 
+// workgroups for groups of 16 rows, one wavefront each
+long row_blocks(long n, long most, int waves = kWaves)
+{
+    const long blocks = ((n + 15) / 16 + waves - 1) / waves;
+    return blocks < 1 ? 1 : (blocks > most ? most : blocks);
+}
+
+// 16, 32, 48 or 64: tiles of the fused kernels, else 0
+int exact_tiles(int w) { return w > 0 && w <= 64 && w % 16 == 0 ? w / 16 : 0; }
+bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
+using MlpFn = void (*)(MlpArgs);
+template <int KT> MlpFn pick_mlp_m(int mt)
+{
+    switch (mt) {
+    case 1: return &mlp_kernel<KT, 1>;
+    case 2: return &mlp_kernel<KT, 2>;
+    case 3: return &mlp_kernel<KT, 3>;
+    case 4: return &mlp_kernel<KT, 4>;
+    }
+    return nullptr;
+}
+using BackFn = void (*)(BackArgs);
+template <int MT> BackFn pick_back_two(int at)
+{
+    switch (at) {
+    case 1: return &back_kernel<MT, MT, 1, true>;
+    case 2: return &back_kernel<MT, MT, 2, true>;
+    case 3: return &back_kernel<MT, MT, 3, true>;
+    case 4: return &back_kernel<MT, MT, 4, true>;
+    }
+    return nullptr;
+}
+template <int BT> BackFn pick_back_one(int mt)
+{
+    switch (mt) {
+    case 1: return &back_kernel<BT, 1, 1, false>;
+    case 2: return &back_kernel<BT, 2, 1, false>;
+    case 3: return &back_kernel<BT, 3, 1, false>;
+    case 4: return &back_kernel<BT, 4, 1, false>;
+    }
+    return nullptr;
+}
+
 bool width_ok(int w) { return w > 0 && w <= PCSR_GNN_MAX_WIDTH; }
 
 } // namespace
@@ -448,8 +931,10 @@ int64_t pcsr_gnn_workspace_floats(int32_t a, int32_t b)
 {
     if (!width_ok(a) || !width_ok(b)) return 0;
     const int64_t wgrad = (int64_t)kWgradBlocks * ((int64_t)a * b + b), linear = (int64_t)kLinearBlocks * (b + 1);
-    const int64_t col = (int64_t)kColsumBlocks * b;
+    const int64_t col = (int64_t)kColsumBlocks * (a > b ? a : b);
+    const int64_t side = a > b ? a : b, back = (int64_t)kBackBlocks * (side * b + side * a + 2 * side + 64);
     int64_t most = wgrad > linear ? wgrad : linear;
+    most = most > back ? most : back;
     return most > col ? most : col;
 }
 
@@ -463,11 +948,12 @@ int pcsr_gnn_linear(int64_t n, int32_t a, int32_t b, const float *X, const float
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto aligned = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
     const bool vec = a % 4 == 0 && b % 4 == 0 && aligned(X) && aligned(mask) && aligned(dot_aux) && aligned(Y);
-    LinearFn fn = pick_linear_kn(tiles(a, vec), tiles(b, vec), vec, red);
+    const int kt = tiles(a, vec), nt = tiles(b, vec);
+    const bool exact = vec && a == 16 * kt && b == 16 * nt;
+    LinearFn fn = pick_linear_kn(kt, nt, exact ? 2 : vec, red);
     if (!fn) return PCSR_E_UNSUPPORTED;
-    const long groups = (n + 31) / 32;
-    long blocks = (groups + kWaves - 1) / kWaves;
-    blocks = blocks < 1 ? 1 : (blocks > kLinearBlocks ? kLinearBlocks : blocks);
+    const int waves = exact ? piece_waves(kt, nt) : kWaves;
+    const long blocks = row_blocks(n, 256 * (exact ? piece_blocks_per_cu(kt, nt) : blocks_per_cu(kt, nt)), waves);
     LinearArgs p;
     p.n = n;
     p.a = a;
@@ -482,10 +968,86 @@ int pcsr_gnn_linear(int64_t n, int32_t a, int32_t b, const float *X, const float
     p.Y = Y;
     p.ws_colsum = colsum_out ? ws : nullptr;
     p.ws_dot = dot_out ? ws + (long)kLinearBlocks * b : nullptr;
-    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, p);
+    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(64 * waves), 0, s, p);
     int rc = to_code(hipGetLastError());
     if (rc == PCSR_OK && colsum_out) rc = sum_partials(p.ws_colsum, (int)blocks, b, b, colsum_out, 0, nullptr, s);
     if (rc == PCSR_OK && dot_out) rc = sum_partials(p.ws_dot, (int)blocks, 1, 1, dot_out, 0, nullptr, s);
+    return rc;
+}
+
+int pcsr_gnn_mlp(int64_t n, int32_t a, int32_t m, const float *X, const float *W1, const float *b1, const float *W2,
+                 const float *b2, int32_t relu, float *Z, float *Y, void *stream)
+{
+    if (n < 0 || !X || !W1 || !W2 || !Z || !Y) return PCSR_E_INVALID_ARG;
+    const int kt = exact_tiles(a), mt = exact_tiles(m);
+    if (!kt || !mt || !aligned16(X) || !aligned16(Z) || !aligned16(Y)) return PCSR_E_UNSUPPORTED;
+    MlpFn fn = kt == 1 ? pick_mlp_m<1>(mt) : kt == 2 ? pick_mlp_m<2>(mt) : kt == 3 ? pick_mlp_m<3>(mt) : pick_mlp_m<4>(mt);
+    const MlpArgs p = {(long)n, relu, X, W1, b1, W2, b2, Z, Y};
+    hipLaunchKernelGGL(fn, dim3((unsigned)row_blocks(n, 768)), dim3(64 * kWaves), 0, static_cast<hipStream_t>(stream), p);
+    return to_code(hipGetLastError());
+}
+
+int pcsr_gnn_mlp_backward(int64_t n, int32_t a, int32_t m, const float *G, const float *Z, const float *A,
+                          const float *H, const float *W1, const float *W2, float *dA, float *dW1, float *db1,
+                          float *dW2, float *db2, float *dot, float *ws, void *stream)
+{
+    if (n < 0 || !G || !Z || !A || !W1 || !W2 || !dW1 || !db1 || !dW2 || !db2 || (dot && !H) || !ws)
+        return PCSR_E_INVALID_ARG;
+    const int at = exact_tiles(a), mt = exact_tiles(m);
+    if (!at || !mt || !aligned16(G) || !aligned16(Z) || !aligned16(A) || !aligned16(H) || !aligned16(dA))
+        return PCSR_E_UNSUPPORTED;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    BackFn fn = mt == 1   ? pick_back_two<1>(at)
+                : mt == 2 ? pick_back_two<2>(at)
+                : mt == 3 ? pick_back_two<3>(at)
+                          : pick_back_two<4>(at);
+    const long n2 = (long)m * m, n1 = (long)m * a, len = n2 + m + n1 + m + 1;
+    BackArgs p = {};
+    p.n = n;
+    p.G = G;
+    p.Z = Z;
+    p.W2 = W2;
+    p.A = A;
+    p.H = dot ? H : nullptr;
+    p.W1 = W1;
+    p.out = dA;
+    p.ws = ws;
+    p.ws_stride = len;
+    const long blocks = row_blocks(n, kBackBlocks);
+    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, p);
+    int rc = to_code(hipGetLastError());
+    if (rc == PCSR_OK) rc = sum_partials(ws, (int)blocks, len, n2, dW2, m, db2, s);
+    if (rc == PCSR_OK) rc = sum_partials(ws + n2 + m, (int)blocks, len, n1, dW1, m, db1, s);
+    if (rc == PCSR_OK && dot) rc = sum_partials(ws + len - 1, (int)blocks, len, 1, dot, 0, nullptr, s);
+    return rc;
+}
+
+int pcsr_gnn_linear_backward(int64_t n, int32_t a, int32_t b, const float *G, const float *X, const float *W,
+                             int32_t masked, float *dX, float *dW, float *db, float *colsum, float *ws, void *stream)
+{
+    if (n < 0 || !G || !X || !W || !dW || !ws) return PCSR_E_INVALID_ARG;
+    const int bt = exact_tiles(b), at = exact_tiles(a);
+    if (!bt || !at || !aligned16(G) || !aligned16(X) || !aligned16(dX)) return PCSR_E_UNSUPPORTED;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    BackFn fn = bt == 1   ? pick_back_one<1>(at)
+                : bt == 2 ? pick_back_one<2>(at)
+                : bt == 3 ? pick_back_one<3>(at)
+                          : pick_back_one<4>(at);
+    const long n2 = (long)a * b, len = n2 + b + a;
+    BackArgs p = {};
+    p.n = n;
+    p.masked = masked;
+    p.G = G;
+    p.Z = X;
+    p.W2 = W;
+    p.out = dX;
+    p.ws = ws;
+    p.ws_stride = len;
+    const long blocks = row_blocks(n, kBackBlocks);
+    hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, p);
+    int rc = to_code(hipGetLastError());
+    if (rc == PCSR_OK) rc = sum_partials(ws, (int)blocks, len, n2, dW, db ? b : 0, db, s);
+    if (rc == PCSR_OK && colsum) rc = sum_partials(ws + n2 + b, (int)blocks, len, a, colsum, 0, nullptr, s);
     return rc;
 }
 

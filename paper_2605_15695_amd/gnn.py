@@ -109,6 +109,53 @@ class _Dense:
             "pcsr_gnn_linear")
         return Y
 
+    def mlp(self, X, W1, b1, W2, b2, relu):
+        """Z = relu(X W1^T + b1), Z W2^T + b2 (ReLU): both, in one pass where the widths allow it"""
+        n, (m, a) = X.shape[0], W1.shape
+        if _pieces(a, m):
+            Z, Y = self.new(n, m), self.new(n, m)
+            rc = self.lib.pcsr_gnn_mlp(n, a, m, X.data_ptr(), W1.data_ptr(), b1.data_ptr(), W2.data_ptr(),
+                                       b2.data_ptr(), int(relu), Z.data_ptr(), Y.data_ptr(), self.stream)
+            if rc != pc.PCSR_E_UNSUPPORTED:
+                self._check(rc, "pcsr_gnn_mlp")
+                return Z, Y
+        Z = self.linear(X, W1, bias=b1, relu=True)
+        return Z, self.linear(Z, W2, bias=b2, relu=relu)
+
+    def mlp_backward(self, G, Z, A, H, W1, W2, store):
+        """(dA or None, sum(dA * H), dW1, db1, dW2, db2) of mlp(A, ...), in one pass where the widths allow it"""
+        n, (m, a) = G.shape[0], W1.shape
+        dot = self.new()
+        if _pieces(a, m):
+            dA = self.new(n, a) if store else None
+            dW1, db1, dW2, db2 = self.new(m, a), self.new(m), self.new(m, m), self.new(m)
+            rc = self.lib.pcsr_gnn_mlp_backward(
+                n, a, m, G.data_ptr(), Z.data_ptr(), A.data_ptr(), H.data_ptr(), W1.data_ptr(), W2.data_ptr(), _p(dA),
+                dW1.data_ptr(), db1.data_ptr(), dW2.data_ptr(), db2.data_ptr(), dot.data_ptr(), self.ws, self.stream)
+            if rc != pc.PCSR_E_UNSUPPORTED:
+                self._check(rc, "pcsr_gnn_mlp_backward")
+                return dA, dot, dW1, db1, dW2, db2
+        dW2, db2 = self.wgrad(G, Z, bias=True)
+        G1 = self.linear(G, W2, transposed=True, mask=Z)
+        dW1, db1 = self.wgrad(G1, A, bias=True)
+        dA = self.linear(G1, W1, transposed=True, aux=H, dot=dot, store=store)
+        return dA, dot, dW1, db1, dW2, db2
+
+    def linear_backward(self, G, X, W, bias=False, mask=False, colsum=None):
+        """(dX, dW, column sums of G or None) of Y = X W^T; dX masked by X > 0 if asked, its column
+        sums into colsum"""
+        n, (b, a) = G.shape[0], W.shape
+        if _pieces(a, b):
+            dX, dW, db = self.new(n, a), self.new(b, a), self.new(b) if bias else None
+            rc = self.lib.pcsr_gnn_linear_backward(n, a, b, G.data_ptr(), X.data_ptr(), W.data_ptr(), int(mask),
+                                                   dX.data_ptr(), dW.data_ptr(), _p(db), _p(colsum), self.ws,
+                                                   self.stream)
+            if rc != pc.PCSR_E_UNSUPPORTED:
+                self._check(rc, "pcsr_gnn_linear_backward")
+                return dX, dW, db
+        dW, db = self.wgrad(G, X, bias=bias)
+        return self.linear(G, W, transposed=True, mask=X if mask else None, colsum=colsum), dW, db
+
     def wgrad(self, G, X, bias=False):
         """(G^T X, column sums of G or None)"""
         dW = self.new(G.shape[1], X.shape[1])
@@ -133,6 +180,11 @@ class _Dense:
                                              self.stream)
         self._check(rc, "pcsr_spmm")
         return out
+
+
+def _pieces(a, b):
+    """Whether the one-pass kernels for two products take these widths."""
+    return a % 16 == 0 and b % 16 == 0 and a <= 64 and b <= 64
 
 
 def _p(t):
@@ -170,9 +222,9 @@ class FusedLayers(torch.autograd.Function):
                 eps, W1, b1, W2, b2 = params[at:at + 5]
                 at += 5
                 A = d.spmm(op.fwd, op.n_rows, H, self_term=H, eps=eps)
-                Z = d.linear(A, W1, bias=b1, relu=True)
+                Z, Y = d.mlp(A, W1, b1, W2, b2, relu)
                 keep += [H, A, Z]
-                H = d.linear(Z, W2, bias=b2, relu=relu)
+                H = Y
         ctx.chain = chain
         ctx.n_params = len(params)
         ctx.save_for_backward(*params, *keep)
@@ -207,36 +259,47 @@ class FusedLayers(torch.autograd.Function):
                     db = None
                     if need[at] or need_dH:
                         U = d.spmm(op.bwd, op.n_cols, G)
-                        if need[at]:
+                        db = d.new(W.shape[1]) if sums and need_dH else None
+                        if need[at] and need_dH:
+                            G, grads[at], _ = d.linear_backward(U, H, W, mask=masked, colsum=db)
+                        elif need[at]:
                             grads[at] = d.wgrad(U, H)[0]
-                        if need_dH:
-                            db = d.new(W.shape[1]) if sums else None
+                        else:
                             G = d.linear(U, W, transposed=True, mask=H if masked else None, colsum=db)
                 else:
                     A, H = keep.pop(), keep.pop()
-                    if need[at] or (has_b and need[at + 1]):
+                    need_W, dA, s, db = need[at] or (has_b and need[at + 1]), None, None, None
+                    if need_W and need_dH:
+                        dA, grads[at], s = d.linear_backward(G, A, W, bias=has_b)
+                    elif need_W:
                         grads[at], s = d.wgrad(G, A, bias=has_b)
-                        if has_b:
-                            grads[at + 1] = s
-                    db = None
+                    elif need_dH:
+                        dA = d.linear(G, W, transposed=True)
+                    if has_b:
+                        grads[at + 1] = s
                     if need_dH:
-                        G = d.spmm(op.bwd, op.n_cols, d.linear(G, W, transposed=True), mask=H if masked else None)
+                        G = d.spmm(op.bwd, op.n_cols, dA, mask=H if masked else None)
             else:
                 at -= 5
                 eps, W1, b1, W2, b2 = params[at:at + 5]
                 Z, A, H = keep.pop(), keep.pop(), keep.pop()
-                if need[at + 3] or need[at + 4]:
-                    grads[at + 3], grads[at + 4] = d.wgrad(G, Z, bias=True)
-                G1 = d.linear(G, W2, transposed=True, mask=Z)
-                if need[at + 1] or need[at + 2]:
-                    grads[at + 1], grads[at + 2] = d.wgrad(G1, A, bias=True)
-                db = None
-                if need[at] or need_dH:
+                db = dA = None
+                if all(need[at:at + 5]):
+                    dA, *grads[at:at + 5] = d.mlp_backward(G, Z, A, H, W1, W2, store=need_dH)
+                    grads[at] = grads[at].view_as(eps)
+                else:
+                    if need[at + 3] or need[at + 4]:
+                        grads[at + 3], grads[at + 4] = d.wgrad(G, Z, bias=True)
+                    G1 = d.linear(G, W2, transposed=True, mask=Z)
+                    if need[at + 1] or need[at + 2]:
+                        grads[at + 1], grads[at + 2] = d.wgrad(G1, A, bias=True)
                     if need[at]:
                         grads[at] = torch.empty_like(eps)
-                    dA = d.linear(G1, W1, transposed=True, aux=H if need[at] else None, dot=grads[at], store=need_dH)
-                    if need_dH:
-                        G = d.spmm(op.bwd, op.n_cols, dA, self_term=dA, eps=eps, mask=H if masked else None)
+                    if need[at] or need_dH:
+                        dA = d.linear(G1, W1, transposed=True, aux=H if need[at] else None, dot=grads[at],
+                                      store=need_dH)
+                if need_dH:
+                    G = d.spmm(op.bwd, op.n_cols, dA, self_term=dA, eps=eps, mask=H if masked else None)
         return (None, G if ctx.needs_input_grad[1] else None,
                 *(g if n else None for g, n in zip(grads, need)))
 

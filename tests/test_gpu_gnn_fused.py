@@ -52,6 +52,40 @@ def test_dense_kernels(a, b, n):
     assert bool(((d.colsum(G).double() - G.double().sum(0)).abs() <= 1e-6 * gb).all())
 
 
+# one pass for two products: each width of the 16-row pieces, rows short of a piece, a misaligned input
+@pytest.mark.parametrize("a,m", [(16, 16), (32, 48), (48, 32), (64, 64), (16, 64)])
+@pytest.mark.parametrize("n,skew", [(1, 0), (15, 0), (17, 1), (70001, 0)])
+def test_two_products_in_one_pass(a, m, n, skew):
+    g = torch.Generator(device="cuda").manual_seed(a * 100 + m)
+    A, H = (torch.randn(n * a + 1, generator=g, device="cuda")[skew:skew + n * a].view(n, a) for _ in range(2))
+    G = torch.randn(n, m, generator=g, device="cuda")
+    W1, W2 = torch.randn(m, a, generator=g, device="cuda"), torch.randn(m, m, generator=g, device="cuda")
+    b1, b2 = torch.randn(m, generator=g, device="cuda"), torch.randn(m, generator=g, device="cuda")
+    d = _dense(a, m)
+    d.ws_floats = max(d.ws_floats, d.lib.pcsr_gnn_workspace_floats(m, m))
+    Ad, Hd, Gd, W1d, W2d = (t.double() for t in (A, H, G, W1, W2))
+    Z, Y = d.mlp(A, W1, b1, W2, b2, True)
+    _close(Z, torch.relu(Ad @ W1d.t() + b1.double()))
+    _close(Y, torch.relu(Z.double() @ W2d.t() + b2.double()))
+    dA, dot, dW1, db1, dW2, db2 = d.mlp_backward(G, Z, A, H, W1, W2, True)
+    G1 = (Gd @ W2d) * (Z > 0)
+    _close(dA, G1 @ W1d)
+    _close(dW2, Gd.t() @ Z.double())
+    _close(dW1, G1.t() @ Ad)
+    _close(db2, Gd.sum(0))
+    _close(db1, G1.sum(0))
+    total = ((Gd.abs() @ W2d.abs()) @ W1d.abs() * Hd.abs()).sum()
+    assert abs(float(dot.double() - ((G1 @ W1d) * Hd).sum())) <= 1e-6 * float(total)
+    cs = torch.empty(a, device="cuda")
+    for mask in (False, True):
+        dX, dW, db = d.linear_backward(G, A, W1, bias=True, mask=mask, colsum=cs)
+        ref = (Gd @ W1d) * ((Ad > 0) if mask else 1.0)
+        _close(dX, ref)
+        _close(dW, Gd.t() @ Ad)
+        _close(db, Gd.sum(0))
+        _close(cs, ref.sum(0))
+
+
 @pytest.mark.parametrize("name,kw", [("rmat20", dict(V=1, S=1, SG=4)), ("rmat20", dict(V=2, S=0)),
                                      ("sbm", dict(V=1, col_window=512)), ("road", dict(V=2, items_per_group=2)),
                                      ("rmat22", dict(V=2, S=1, SG=2))])
