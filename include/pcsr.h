@@ -42,9 +42,9 @@ enum {
                                   handle serves pcsr_export but not pcsr_spmm                 */
     PCSR_FLAG_GPU_BUILD = 16,  /* generate the PCSR arrays with GPU kernels (host CSR arrays
                                   are uploaded first).  CSR arrays given in device memory are
-                                  always built this way.  With col_window the flag is ignored:
-                                  windows are chosen on the host, and CSR arrays given in
-                                  device memory are copied to the host for that build        */
+                                  always built this way, and so are host arrays of 200,000
+                                  nonzeros and more; the arrays come out the same either way.
+                                  The windows of col_window are then chosen there as well      */
     PCSR_FLAG_COLUMN_ORDER = 64,/* S = 1 only: column-ordered schedule.  The work items of
                                   panels that were split run in ascending order of their first
                                   column, dealt to the 8 XCDs as 8 contiguous column ranges,
@@ -92,7 +92,8 @@ enum {
  *                    0 = auto.  Values above 1 need S = 0, items_per_group <
  *                    lanes_per_row, no work item longer than 1024 vectors and
  *                    V*vec*rep*items_per_group <= 32.
- *   flags   PCSR_FLAG_* bits.
+ *   flags   PCSR_FLAG_* bits.  Bits 16-20 are pcsr_select's: launch shapes with loads wider
+ *           than vec (K need not be a multiple of them; C is the same).
  */
 typedef struct {
     int32_t V;
@@ -267,7 +268,8 @@ int pcsr_select(const double *features, int32_t K, pcsr_params_t *out);
 /*
  * Locality reordering pre-step (Section 4.4: a community-based relabelling of the nodes
  * is the default first step of the pipeline and is amortised over many SpMMs).  Own
- * scheme: up to max_rounds (0 = 8) rounds of synchronous label propagation over the
+ * scheme (inputs of 200,000 nonzeros and more on the GPU, where there is one, like the three
+ * calls below): up to max_rounds (0 = 8) rounds of synchronous label propagation over the
  * pattern of a square matrix, then clusters are numbered one after the other, members
  * in their original order.  Deterministic.
  *   rowptr int32[n+1], colidx int32[nnz]: host.  perm (host, int32[n]) receives the new
