@@ -311,31 +311,37 @@ def _linear_first(layer):
 
 def _params(layer):
     """Parameters of a layer in the order FusedLayers takes them, None if they are not what it
-    knows (modules exchanged or hooked, other types or devices, too wide)."""
+    knows (modules exchanged or hooked, other types or shapes, too wide)."""
+    linear = torch.nn.Linear
     if type(layer) is GCNLayer:
         lins, own = [layer.lin], [layer.lin]
-        ps = [layer.lin.weight] if layer.bias is None else [layer.lin.weight, layer.bias]
-        if layer.lin.bias is not None:
+        if type(layer.lin) is not linear or layer.lin.bias is not None:
             return None
+        ps = [layer.lin.weight] if layer.bias is None else [layer.lin.weight, layer.bias]
     elif type(layer) is GINLayer:
         mlp = layer.mlp
-        if len(mlp) != 3 or type(mlp[1]) is not torch.nn.ReLU:
+        if type(mlp) is not torch.nn.Sequential or [type(m) for m in mlp] != [linear, torch.nn.ReLU, linear]:
             return None
-        lins, own = [mlp[0], mlp[2]], [mlp, mlp[0], mlp[1], mlp[2]]
-        if any(type(m) is not torch.nn.Linear or m.bias is None for m in lins):
+        lins, own = [mlp[0], mlp[2]], [mlp, *mlp]
+        if any(m.bias is None for m in lins):
+            return None
+        # the second layer's weights are read as m x m: both kernels and workspaces rely on it
+        if mlp[2].out_features != mlp[0].out_features:
             return None
         ps = [layer.eps, mlp[0].weight, mlp[0].bias, mlp[2].weight, mlp[2].bias]
     else:
         return None
-    if not isinstance(layer.op, PcsrOperator) or any(type(m) is not torch.nn.Linear for m in lins):
+    if not isinstance(layer.op, PcsrOperator):
         return None
     if any(_hooked(m) for m in own):
         return None
-    for m in lins:
-        if m.in_features > MAX_WIDTH or m.out_features > MAX_WIDTH:
+    for i, m in enumerate(lins):
+        if m.in_features > MAX_WIDTH or m.out_features > MAX_WIDTH or m.in_features < 1 or m.out_features < 1:
+            return None
+        if m.weight.shape != (m.out_features, m.in_features) or (i and m.in_features != lins[i - 1].out_features):
             return None
     for p in ps:
-        if p.dtype != torch.float32 or not p.is_cuda or not p.is_contiguous():
+        if p.dtype != torch.float32 or not p.is_contiguous():
             return None
     return ps
 

@@ -1,0 +1,65 @@
+"""Which layers FusedLayers takes: its kernels read raw pointers, so whatever torch's own modules would
+broadcast, refuse or hand to a hook has to run module by module.  No GPU calls."""
+import pytest
+
+import paper_2605_15695_amd as pc
+import synth
+
+torch = pytest.importorskip("torch")
+
+from paper_2605_15695_amd import gnn  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def op():
+    g = synth.workload("poisson", "small")
+    return gnn.PcsrOperator(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals,
+                            params=pc.make_params(flags=pc.PCSR_FLAG_HOST_ONLY))
+
+
+def _param(*shape):
+    return torch.nn.Parameter(torch.zeros(*shape))
+
+
+def test_plain_layers_are_taken(op):
+    assert len(gnn._params(gnn.GCNLayer(op, 16, 64))) == 2
+    assert len(gnn._params(gnn.GCNLayer(op, 7, 5, bias=False))) == 1
+    assert len(gnn._params(gnn.GINLayer(op, 128, 33))) == 5
+
+
+def _gin_second(layer):
+    layer.mlp[2] = torch.nn.Linear(64, 32)
+
+
+def _gin_second_wider(layer):
+    layer.mlp[2] = torch.nn.Linear(64, 100)
+
+
+def _gin_mlp_module(layer):
+    layer.mlp = torch.nn.Linear(16, 64)
+
+
+def _gin_weight(layer):
+    layer.mlp[2].weight = _param(32, 64)
+
+
+@pytest.mark.parametrize("change", [_gin_second, _gin_second_wider, _gin_mlp_module, _gin_weight])
+def test_gin_layers_of_another_form_are_not(op, change):
+    layer = gnn.GINLayer(op, 16, 64)
+    change(layer)
+    assert gnn._params(layer) is None
+
+
+def _gcn_module(layer):
+    layer.lin = torch.nn.Sequential(torch.nn.Linear(16, 64, bias=False))
+
+
+def _gcn_weight(layer):
+    layer.lin.weight = _param(32, 16)
+
+
+@pytest.mark.parametrize("change", [_gcn_module, _gcn_weight])
+def test_gcn_layers_of_another_form_are_not(op, change):
+    layer = gnn.GCNLayer(op, 16, 64)
+    change(layer)
+    assert gnn._params(layer) is None

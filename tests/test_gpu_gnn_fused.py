@@ -168,3 +168,35 @@ def test_epilogue_on_a_handle_with_a_shape_of_its_own():
     B = torch.from_numpy(synth.dense_operand(g.n_cols, 32, "normal", 3)).cuda()
     d = _dense(1, 1)
     _close(d.spmm(h, g.n_rows, B, relu=True), torch.relu(d.spmm(h, g.n_rows, B).double()), 1e-6)
+
+
+def _narrower_second(layer):
+    layer.mlp[2] = torch.nn.Linear(64, 32)
+
+
+# layers that the fused node does not take give what torch's own modules give
+@pytest.mark.parametrize("kind,change", [("gin", _narrower_second)])
+def test_changed_layers_match_torch(kind, change):
+    from paper_2605_15695_amd import gnn
+
+    g = synth.workload("poisson", "small")
+    op = gnn.PcsrOperator(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, K_hint=64)
+    torch.manual_seed(2)
+    layer = {"gcn": gnn.GCNLayer, "gin": gnn.GINLayer}[kind](op, 16, 64)
+    change(layer)
+    layer = layer.cuda()
+    X = torch.from_numpy(synth.dense_operand(g.n_rows, 16, "normal", 9)).cuda()
+    out = layer(X)
+    out.square().mean().backward()
+    assert type(out.grad_fn).__name__ != "FusedLayersBackward"
+    grads = [p.grad.clone() for p in layer.parameters()]
+    layer.zero_grad()
+    if kind == "gcn":
+        ref = op(layer.lin(X)) if layer.lin.in_features >= layer.lin.out_features else layer.lin(op(X))
+        ref = ref + layer.bias
+    else:
+        ref = layer.mlp((1.0 + layer.eps) * X + op(X))
+    ref.square().mean().backward()
+    assert out.shape == ref.shape and torch.equal(out, ref)
+    for a, p in zip(grads, layer.parameters()):
+        _close(a, p.grad.double(), 1e-6)
