@@ -340,6 +340,10 @@ def _params(layer):
             return None
         if m.weight.shape != (m.out_features, m.in_features) or (i and m.in_features != lins[i - 1].out_features):
             return None
+    # a bias that torch would broadcast is one value, not one per output
+    for m, b in zip(lins, [layer.bias] if type(layer) is GCNLayer else [m.bias for m in lins]):
+        if b is not None and b.shape != (m.out_features,):
+            return None
     for p in ps:
         if p.dtype != torch.float32 or not p.is_contiguous():
             return None

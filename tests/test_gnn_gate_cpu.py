@@ -18,7 +18,7 @@ def op():
 
 
 def _param(*shape):
-    return torch.nn.Parameter(torch.zeros(*shape))
+    return torch.nn.Parameter(torch.zeros(shape))
 
 
 def test_plain_layers_are_taken(op):
@@ -62,4 +62,30 @@ def _gcn_weight(layer):
 def test_gcn_layers_of_another_form_are_not(op, change):
     layer = gnn.GCNLayer(op, 16, 64)
     change(layer)
+    assert gnn._params(layer) is None
+
+
+def _gcn_one_bias(layer):
+    layer.bias = _param(1)
+
+
+def _gcn_row_bias(layer):
+    layer.bias = _param(1, 64)
+
+
+def _gcn_scalar_bias(layer):
+    layer.bias = _param()
+
+
+@pytest.mark.parametrize("change", [_gcn_one_bias, _gcn_row_bias, _gcn_scalar_bias])
+def test_biases_that_broadcast_are_not(op, change):
+    layer = gnn.GCNLayer(op, 16, 64)
+    change(layer)
+    assert gnn._params(layer) is None
+
+
+@pytest.mark.parametrize("which", [0, 2])
+def test_gin_biases_that_broadcast_are_not(op, which):
+    layer = gnn.GINLayer(op, 16, 64)
+    layer.mlp[which].bias = _param(1)
     assert gnn._params(layer) is None

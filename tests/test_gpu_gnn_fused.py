@@ -174,8 +174,16 @@ def _narrower_second(layer):
     layer.mlp[2] = torch.nn.Linear(64, 32)
 
 
+def _one_bias(layer):
+    layer.bias = torch.nn.Parameter(torch.full((1,), 0.5))
+
+
+def _one_inner_bias(layer):
+    layer.mlp[0].bias = torch.nn.Parameter(torch.full((1,), 0.5))
+
+
 # layers that the fused node does not take give what torch's own modules give
-@pytest.mark.parametrize("kind,change", [("gin", _narrower_second)])
+@pytest.mark.parametrize("kind,change", [("gin", _narrower_second), ("gcn", _one_bias), ("gin", _one_inner_bias)])
 def test_changed_layers_match_torch(kind, change):
     from paper_2605_15695_amd import gnn
 
