@@ -325,6 +325,9 @@ def _params(layer):
         lins, own = [mlp[0], mlp[2]], [mlp, *mlp]
         if any(m.bias is None for m in lins):
             return None
+        # one value in device memory; of more than two dimensions it would add one to the result
+        if not isinstance(layer.eps, torch.Tensor) or layer.eps.numel() != 1 or layer.eps.dim() > 2:
+            return None
         # the second layer's weights are read as m x m: both kernels and workspaces rely on it
         if mlp[2].out_features != mlp[0].out_features:
             return None

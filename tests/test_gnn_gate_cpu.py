@@ -89,3 +89,18 @@ def test_gin_biases_that_broadcast_are_not(op, which):
     layer = gnn.GINLayer(op, 16, 64)
     layer.mlp[which].bias = _param(1)
     assert gnn._params(layer) is None
+
+
+@pytest.mark.parametrize("eps", [torch.full((64,), 0.5), torch.full((3, 1), 0.5), 0.5, torch.full((1, 1, 1), 0.5)])
+def test_eps_other_than_one_value_is_not(op, eps):
+    layer = gnn.GINLayer(op, 64, 64)
+    del layer.eps
+    layer.eps = eps
+    assert gnn._params(layer) is None
+
+
+def test_one_eps_of_any_rank_the_result_keeps_is(op):
+    layer = gnn.GINLayer(op, 64, 64)
+    for shape in ((), (1,), (1, 1)):
+        layer.eps = _param(*shape)
+        assert gnn._params(layer) is not None

@@ -182,8 +182,18 @@ def _one_inner_bias(layer):
     layer.mlp[0].bias = torch.nn.Parameter(torch.full((1,), 0.5))
 
 
+def _eps_vector(layer):
+    layer.eps = torch.nn.Parameter(torch.linspace(0.0, 1.0, 16))
+
+
+def _eps_number(layer):
+    del layer.eps
+    layer.eps = 0.25
+
+
 # layers that the fused node does not take give what torch's own modules give
-@pytest.mark.parametrize("kind,change", [("gin", _narrower_second), ("gcn", _one_bias), ("gin", _one_inner_bias)])
+@pytest.mark.parametrize("kind,change", [("gin", _narrower_second), ("gcn", _one_bias), ("gin", _one_inner_bias),
+                                         ("gin", _eps_vector), ("gin", _eps_number)])
 def test_changed_layers_match_torch(kind, change):
     from paper_2605_15695_amd import gnn
 
