@@ -334,7 +334,8 @@ def _params(layer):
         ps = [layer.eps, mlp[0].weight, mlp[0].bias, mlp[2].weight, mlp[2].bias]
     else:
         return None
-    if not isinstance(layer.op, PcsrOperator):
+    # a product of the operator's own (edge dropout, scaling, counting) would be passed by
+    if type(layer.op) is not PcsrOperator or "_run" in vars(layer.op):
         return None
     if any(_hooked(m) for m in own):
         return None

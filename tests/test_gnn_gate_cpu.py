@@ -104,3 +104,18 @@ def test_one_eps_of_any_rank_the_result_keeps_is(op):
     for shape in ((), (1,), (1, 1)):
         layer.eps = _param(*shape)
         assert gnn._params(layer) is not None
+
+
+def test_operators_with_a_product_of_their_own_are_not(op):
+    class Dropping(gnn.PcsrOperator):
+        def _run(self, handle, n_out, X):
+            return 0.5 * super()._run(handle, n_out, X)
+
+    sub = Dropping.__new__(Dropping)
+    sub.__dict__.update(op.__dict__)
+    assert gnn._params(gnn.GCNLayer(sub, 16, 64)) is None
+    own = gnn.PcsrOperator.__new__(gnn.PcsrOperator)
+    own.__dict__.update(op.__dict__)
+    assert gnn._params(gnn.GINLayer(own, 16, 64)) is not None
+    own._run = lambda handle, n_out, X: X
+    assert gnn._params(gnn.GINLayer(own, 16, 64)) is None

@@ -218,3 +218,23 @@ def test_changed_layers_match_torch(kind, change):
     assert out.shape == ref.shape and torch.equal(out, ref)
     for a, p in zip(grads, layer.parameters()):
         _close(a, p.grad.double(), 1e-6)
+
+
+def test_an_operator_with_its_own_product_is_asked():
+    from paper_2605_15695_amd import gnn
+
+    class Scaled(gnn.PcsrOperator):
+        def _run(self, handle, n_out, X):
+            return 0.5 * super()._run(handle, n_out, X)
+
+    g = synth.workload("poisson", "small")
+    args = (g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals)
+    X = torch.from_numpy(synth.dense_operand(g.n_rows, 16, "normal", 9)).cuda()
+    for kind in ("gcn", "gin"):
+        torch.manual_seed(3)
+        model = gnn.make_model(kind, gnn.PcsrOperator(*args, K_hint=32), 16, 32, 16, 1).cuda()
+        torch.manual_seed(3)
+        scaled = gnn.make_model(kind, Scaled(*args, K_hint=32), 16, 32, 16, 1).cuda()
+        half = gnn.PcsrOperator(*args[:4], g.vals * np.float32(0.5), K_hint=32)
+        model[0].op = half
+        _close(scaled(X).detach(), model(X).detach().double(), 1e-5)
