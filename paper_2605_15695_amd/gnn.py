@@ -11,6 +11,7 @@ from __future__ import annotations
 import ctypes
 
 import torch
+from torch.nn.modules import module as _all_modules
 
 from . import binding as pc
 
@@ -325,9 +326,6 @@ def _params(layer):
         lins, own = [mlp[0], mlp[2]], [mlp, *mlp]
         if any(m.bias is None for m in lins):
             return None
-        # one value in device memory; of more than two dimensions it would add one to the result
-        if not isinstance(layer.eps, torch.Tensor) or layer.eps.numel() != 1 or layer.eps.dim() > 2:
-            return None
         # the second layer's weights are read as m x m: both kernels and workspaces rely on it
         if mlp[2].out_features != mlp[0].out_features:
             return None
@@ -344,23 +342,34 @@ def _params(layer):
             return None
         if m.weight.shape != (m.out_features, m.in_features) or (i and m.in_features != lins[i - 1].out_features):
             return None
+    if any(type(p) not in _PLAIN for p in ps):
+        return None
     # a bias that torch would broadcast is one value, not one per output
     for m, b in zip(lins, [layer.bias] if type(layer) is GCNLayer else [m.bias for m in lins]):
         if b is not None and b.shape != (m.out_features,):
             return None
+    # one eps, in device memory; of more than two dimensions it would add one to the result
+    if type(layer) is GINLayer and (layer.eps.numel() != 1 or layer.eps.dim() > 2):
+        return None
     for p in ps:
         if p.dtype != torch.float32 or not p.is_contiguous():
             return None
     return ps
 
 
+# tensors without behaviour of their own
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
+
+
 def _hooked(m):
-    return bool(m._forward_hooks or m._forward_pre_hooks or m._backward_hooks or m._backward_pre_hooks)
+    """Whether somebody watches the module's calls, or its forward is not its class's."""
+    return bool(m._forward_hooks or m._forward_pre_hooks or m._backward_hooks or m._backward_pre_hooks
+                or "forward" in vars(m) or _all_modules._has_any_global_hook())
 
 
 def _run_fused(chain, X):
     """The chain through FusedLayers, or None where that does not apply."""
-    if not isinstance(X, torch.Tensor) or X.dim() != 2 or X.dtype != torch.float32 or not X.is_cuda:
+    if type(X) not in _PLAIN or X.dim() != 2 or X.dtype != torch.float32 or not X.is_cuda:
         return None
     if torch.is_autocast_enabled():
         return None

@@ -119,3 +119,32 @@ def test_operators_with_a_product_of_their_own_are_not(op):
     assert gnn._params(gnn.GINLayer(own, 16, 64)) is not None
     own._run = lambda handle, n_out, X: X
     assert gnn._params(gnn.GINLayer(own, 16, 64)) is None
+
+
+def test_modules_that_are_watched_or_changed_are_not(op):
+    layer = gnn.GINLayer(op, 16, 64)
+    from torch.nn.modules.module import (register_module_forward_hook, register_module_forward_pre_hook,
+                                         register_module_full_backward_hook, register_module_full_backward_pre_hook)
+    for register in (register_module_forward_hook, register_module_forward_pre_hook,
+                     register_module_full_backward_hook, register_module_full_backward_pre_hook):
+        handle = register(lambda *a: None)
+        try:
+            assert gnn._params(layer) is None, register
+        finally:
+            handle.remove()
+        assert gnn._params(layer) is not None
+    layer.mlp[0].forward = lambda H: H
+    assert gnn._params(layer) is None
+
+
+def test_tensors_of_another_type_are_not(op):
+    class Watched(torch.Tensor):
+        pass
+
+    layer = gnn.GCNLayer(op, 16, 64, bias=False)
+    layer.bias = 0.5
+    assert gnn._params(layer) is None
+    layer.bias = torch.zeros(64).as_subclass(Watched)
+    assert gnn._params(layer) is None
+    layer.bias = torch.zeros(64)
+    assert gnn._params(layer) is not None
