@@ -371,7 +371,8 @@ def _run_fused(chain, X):
     """The chain through FusedLayers, or None where that does not apply."""
     if type(X) not in _PLAIN or X.dim() != 2 or X.dtype != torch.float32 or not X.is_cuda:
         return None
-    if torch.is_autocast_enabled():
+    # kernels are launched on the current device; torch's own products follow their operands
+    if torch.is_autocast_enabled() or X.device.index != torch.cuda.current_device():
         return None
     params, n, width = [], X.shape[0], X.shape[1]
     for layer, _ in chain:

@@ -238,3 +238,15 @@ def test_an_operator_with_its_own_product_is_asked():
         half = gnn.PcsrOperator(*args[:4], g.vals * np.float32(0.5), K_hint=32)
         model[0].op = half
         _close(scaled(X).detach(), model(X).detach().double(), 1e-5)
+
+
+def test_operands_on_another_device_than_the_current_one_are_left_to_torch(monkeypatch):
+    from paper_2605_15695_amd import gnn
+
+    g = synth.workload("poisson", "small")
+    op = gnn.PcsrOperator(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, K_hint=32)
+    layer = gnn.GCNLayer(op, 16, 16).cuda()
+    X = torch.from_numpy(synth.dense_operand(g.n_rows, 16, "normal", 9)).cuda()
+    assert gnn._run_fused([(layer, False)], X) is not None
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: X.device.index + 1)
+    assert gnn._run_fused([(layer, False)], X) is None
