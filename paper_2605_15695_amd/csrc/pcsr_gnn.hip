@@ -186,6 +186,15 @@ template <int T> __device__ __forceinline__ void mask_rows(f4 (&x)[T], const f4 
         for (int s = 0; s < 4; ++s) x[t][s] = m[t][s] <= 0.0f ? 0.0f : x[t][s];
 }
 
+// fragments of rows past the end: what a sum over rows must not count (a product of zeros plus the bias)
+template <int T> __device__ __forceinline__ void clear_past_end(int lane, long rows, f4 (&x)[T])
+{
+    if ((lane & 15) >= rows) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) x[t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+}
+
 template <int KT, int NT, bool VEC, bool RED>
 __global__ void __launch_bounds__(64 * kWaves, blocks_per_cu(KT, NT)) linear_kernel(LinearArgs p)
 {
@@ -369,6 +378,7 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), piece_waves(KT, NT) 
         start_from<NT>(bias, lane, y);
         multiply<KT, NT>(wfrag, lane, x, y);
         if (p.relu) relu_rows<NT>(y);
+        if constexpr (RED) clear_past_end<NT>(lane, rows, y);
         frags_to_piece<NT>(patch, lane, y);
         if constexpr (RED) {
             if (p.aux) {

@@ -52,6 +52,25 @@ def test_dense_kernels(a, b, n):
     assert bool(((d.colsum(G).double() - G.double().sum(0)).abs() <= 1e-6 * gb).all())
 
 
+# rows short of a piece: the bias of rows that are not there is in no sum
+@pytest.mark.parametrize("a,b", [(16, 16), (64, 64), (128, 128), (96, 32), (24, 48), (33, 7)])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 1000 * 16 + 5])
+@pytest.mark.parametrize("relu", [False, True])
+def test_column_sums_with_a_bias(a, b, n, relu):
+    g = torch.Generator(device="cuda").manual_seed(a * 1000 + b)
+    X = torch.randn(n, a, generator=g, device="cuda")
+    W, bias = torch.randn(b, a, generator=g, device="cuda"), 3.0 + torch.rand(b, generator=g, device="cuda")
+    csum = torch.empty(b, device="cuda")
+    Y = _dense(a, b).linear(X, W, bias=bias, relu=relu, colsum=csum)
+    ref = X.double() @ W.double().t() + bias.double()
+    if relu:
+        ref = torch.relu(ref)
+    _close(Y, ref)
+    # fp32 sums of n terms in short chains: 1e-6 of the sum of the magnitudes, as above
+    scale = (X.double().abs() @ W.double().abs().t() + bias.double()).sum(0)
+    assert bool(((csum.double() - ref.sum(0)).abs() <= 1e-6 * scale).all())
+
+
 # one pass for two products: each width of the 16-row pieces, rows short of a piece, a misaligned input
 @pytest.mark.parametrize("a,m", [(16, 16), (32, 48), (48, 32), (64, 64), (16, 64)])
 @pytest.mark.parametrize("n,skew", [(1, 0), (15, 0), (17, 1), (70001, 0)])
