@@ -593,6 +593,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
         if constexpr (!TWO) {
             next(g + stride);
             if (p.out) store_frags<MT>(p.out + g * (256 * MT), lane, rows, g1);
+            clear_past_end<MT>(lane, rows, g1); // zeros times an infinite weight are no zeros
 #pragma unroll
             for (int t = 0; t < MT; ++t) csum[t] += g1[t];
             turned_product<BT, MT>(patch, lane, acc2, sum2);
@@ -608,6 +609,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
             for (int t = 0; t < AT; ++t) da[t] = zero;
             multiply<MT, AT>(w1, lane, g1, da);
             if (p.H) {
+                clear_past_end<AT>(lane, rows, da);
 #pragma unroll
                 for (int t = 0; t < AT; ++t)
                     dot += (da[t][0] * aa[t][0] + da[t][1] * aa[t][1]) + (da[t][2] * aa[t][2] + da[t][3] * aa[t][3]);

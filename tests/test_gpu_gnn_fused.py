@@ -105,6 +105,21 @@ def test_two_products_in_one_pass(a, m, n, skew):
         _close(cs, ref.sum(0))
 
 
+# rows past the end are zeros, and zeros times an infinite weight are not: sums stay infinite, not NaN
+@pytest.mark.parametrize("n", [1, 17, 32, 4097])
+def test_sums_over_rows_with_an_infinite_weight(n):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    A, H, G = (0.5 + torch.rand(n, 32, generator=g, device="cuda") for _ in range(3))
+    W1, W2 = (0.5 + torch.rand(32, 32, generator=g, device="cuda") for _ in range(2))
+    W1[3, 5] = float("inf")
+    d = _dense(32, 32)
+    cs = torch.empty(32, device="cuda")
+    d.linear_backward(G, A, W1, bias=True, colsum=cs)
+    assert bool(torch.isinf(cs[5])) and bool(torch.isfinite(cs[:5]).all())
+    dA, dot, *_ = d.mlp_backward(G, A, A, H, W1, W2, True)
+    assert bool(torch.isinf(dA[:, 5]).all()) and bool(torch.isinf(dot))
+
+
 @pytest.mark.parametrize("name,kw", [("rmat20", dict(V=1, S=1, SG=4)), ("rmat20", dict(V=2, S=0)),
                                      ("sbm", dict(V=1, col_window=512)), ("road", dict(V=2, items_per_group=2)),
                                      ("rmat22", dict(V=2, S=1, SG=2))])
