@@ -173,14 +173,22 @@ class _Dense:
 
     def spmm(self, handle, n_out, X, bias=None, relu=False, self_term=None, eps=None, mask=None):
         out = self.new(n_out, X.shape[1])
-        if bias is None and self_term is None and mask is None and not relu:
-            rc = self.lib.pcsr_spmm(handle.raw, X.data_ptr(), out.data_ptr(), X.shape[1], self.stream)
-        else:
+        if bias is not None or self_term is not None or mask is not None or relu:
             epi = pc.pcsr_epilogue_t(_p(bias), _p(self_term), _p(eps), _p(mask), int(relu), 0)
             rc = self.lib.pcsr_spmm_epilogue(handle.raw, X.data_ptr(), out.data_ptr(), X.shape[1], ctypes.byref(epi),
                                              self.stream)
-        self._check(rc, "pcsr_spmm")
-        return out
+            if rc != pc.PCSR_E_UNSUPPORTED:
+                self._check(rc, "pcsr_spmm_epilogue")
+                return out
+        self._check(self.lib.pcsr_spmm(handle.raw, X.data_ptr(), out.data_ptr(), X.shape[1], self.stream), "pcsr_spmm")
+        # handles whose product takes no epilogue: PCSR_FLAG_ATOMIC_SPLIT, where partial sums meet in C
+        if self_term is not None:
+            out.add_(self_term if eps is None else (1.0 + eps.reshape(())) * self_term)
+        if bias is not None:
+            out.add_(bias)
+        if relu:
+            out.relu_()
+        return out if mask is None else out.masked_fill_(mask <= 0.0, 0.0)
 
 
 def _pieces(a, b):

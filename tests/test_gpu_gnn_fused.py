@@ -284,3 +284,27 @@ def test_operands_on_another_device_than_the_current_one_are_left_to_torch(monke
     assert gnn._run_fused([(layer, False)], X) is not None
     monkeypatch.setattr(torch.cuda, "current_device", lambda: X.device.index + 1)
     assert gnn._run_fused([(layer, False)], X) is None
+
+
+# split panels whose partial sums meet in C take no epilogue: the elementwise tail follows the product
+@pytest.mark.parametrize("kind", ["gcn", "gin"])
+@pytest.mark.parametrize("features", [16, 48])
+def test_layers_on_an_operator_with_atomic_sums(kind, features):
+    from paper_2605_15695_amd import gnn
+
+    g = synth.workload("rmat20", "small")
+    args = (g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals)
+    X = torch.from_numpy(synth.dense_operand(g.n_rows, features, "normal", 9)).cuda()
+    results = []
+    for flags in (0, pc.PCSR_FLAG_ATOMIC_SPLIT):
+        op = gnn.PcsrOperator(*args, params=pc.make_params(V=1, S=1, SG=8, flags=flags))
+        torch.manual_seed(4)
+        model = gnn.make_model(kind, op, features, 32, 16, 3).cuda()
+        for p in model.parameters():                   # biases and eps that matter
+            if p.dim() < 2:
+                torch.nn.init.constant_(p, 0.25)
+        out = model(X)
+        out.square().mean().backward()
+        results.append([out.detach(), *(p.grad for p in model.parameters())])
+    for a, b in zip(*results):
+        _close(b, a.double(), 1e-4)
