@@ -207,36 +207,25 @@ class FusedLayers(torch.autograd.Function):
     backward ReLU mask where the gradient is, (1 + eps) H is added in the aggregation, and
     the bias gradients are summed by the kernel that has the gradient in registers.
 
-    ``chain``: list of (layer, ReLU follows); the last entry has none.  ``params``: the layers'
+    ``chain``: list of (layer, ReLU follows); the last entry has none.  ``keeps``: whether a
+    backward pass can follow, for which each layer's arrays are kept.  ``params``: the layers'
     parameters in the order of ``_params``."""
 
     @staticmethod
-    def forward(ctx, chain, X, *params):
+    def forward(ctx, chain, keeps, X, *params):
         d = _Dense(X, [(1, 1)])
         H, keep, at = X.contiguous(), [], 0
         for layer, relu in chain:
-            op = layer.op
-            if isinstance(layer, GCNLayer):
-                W = params[at]
-                b = params[at + 1] if layer.bias is not None else None
-                at += 1 + (b is not None)
-                if W.shape[1] >= W.shape[0]:
-                    keep.append(H)
-                    H = d.spmm(op.fwd, op.n_rows, d.linear(H, W), bias=b, relu=relu)
-                else:
-                    A = d.spmm(op.fwd, op.n_rows, H)
-                    keep += [H, A]
-                    H = d.linear(A, W, bias=b, relu=relu)
-            else:
-                eps, W1, b1, W2, b2 = params[at:at + 5]
-                at += 5
-                A = d.spmm(op.fwd, op.n_rows, H, self_term=H, eps=eps)
-                Z, Y = d.mlp(A, W1, b1, W2, b2, relu)
-                keep += [H, A, Z]
-                H = Y
+            n = 1 + (layer.bias is not None) if isinstance(layer, GCNLayer) else 5
+            H, *saved = _layer_forward(d, layer, relu, H, params[at:at + n])
+            at += n
+            if keeps:
+                keep += saved
+            del saved  # without a gradient each layer's arrays go before the next layer's are made
         ctx.chain = chain
         ctx.n_params = len(params)
-        ctx.save_for_backward(*params, *keep)
+        if keeps:
+            ctx.save_for_backward(*params, *keep)
         return H
 
     @staticmethod
@@ -246,13 +235,13 @@ class FusedLayers(torch.autograd.Function):
         params, keep = saved[:ctx.n_params], list(saved[ctx.n_params:])
         d = _Dense(dOut, [tuple(p.shape) for p in params if p.dim() == 2])
         grads = [None] * ctx.n_params
-        need = ctx.needs_input_grad[2:]
+        need = ctx.needs_input_grad[3:]
         G, db = dOut.contiguous(), None  # gradient at the layer's output, its column sums if known
         at = ctx.n_params
         for i in range(len(ctx.chain) - 1, -1, -1):
             layer = ctx.chain[i][0]
             op = layer.op
-            need_dH = i > 0 or ctx.needs_input_grad[1]
+            need_dH = i > 0 or ctx.needs_input_grad[2]
             masked = i > 0 and ctx.chain[i - 1][1]
             # the layer before wants the column sums of its output gradient for its bias, unless
             # its weight gradient reads that gradient anyway
@@ -309,8 +298,23 @@ class FusedLayers(torch.autograd.Function):
                                       store=need_dH)
                 if need_dH:
                     G = d.spmm(op.bwd, op.n_cols, dA, self_term=dA, eps=eps, mask=H if masked else None)
-        return (None, G if ctx.needs_input_grad[1] else None,
+        return (None, None, G if ctx.needs_input_grad[2] else None,
                 *(g if n else None for g, n in zip(grads, need)))
+
+
+def _layer_forward(d, layer, relu, H, params):
+    """(output, then what the layer's backward pass reads) of one layer of a chain"""
+    op = layer.op
+    if isinstance(layer, GCNLayer):
+        W, b = params[0], params[1] if layer.bias is not None else None
+        if W.shape[1] >= W.shape[0]:
+            return d.spmm(op.fwd, op.n_rows, d.linear(H, W), bias=b, relu=relu), H
+        A = d.spmm(op.fwd, op.n_rows, H)
+        return d.linear(A, W, bias=b, relu=relu), H, A
+    eps, W1, b1, W2, b2 = params
+    A = d.spmm(op.fwd, op.n_rows, H, self_term=H, eps=eps)
+    Z, Y = d.mlp(A, W1, b1, W2, b2, relu)
+    return Y, H, A, Z
 
 
 def _linear_first(layer):
@@ -396,7 +400,8 @@ def _run_fused(chain, X):
         params += ps
     if n == 0 or X.shape[0] == 0:
         return None
-    return FusedLayers.apply(chain, X, *params)
+    keeps = torch.is_grad_enabled() and any(t.requires_grad for t in (X, *params))
+    return FusedLayers.apply(chain, keeps, X, *params)
 
 
 class GCNLayer(torch.nn.Module):

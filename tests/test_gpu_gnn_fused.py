@@ -308,3 +308,31 @@ def test_layers_on_an_operator_with_atomic_sums(kind, features):
         results.append([out.detach(), *(p.grad for p in model.parameters())])
     for a, b in zip(*results):
         _close(b, a.double(), 1e-4)
+
+
+@pytest.mark.parametrize("kind", ["gcn", "gin"])
+def test_forward_alone_keeps_no_layer_but_the_current_one(kind):
+    from paper_2605_15695_amd import gnn
+
+    g = synth.workload("road", "small")
+    op = gnn.PcsrOperator(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, symmetric=True, K_hint=128)
+    model = gnn.make_model(kind, op, 128, 128, 128, 8).cuda()
+    X = torch.randn(g.n_rows, 128, device="cuda")
+    array = X.numel() * 4
+
+    def peak():
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        out = model(X)
+        torch.cuda.synchronize()
+        return (torch.cuda.max_memory_allocated() - before) / array, out
+
+    with torch.no_grad():
+        model(X)                                       # the handle's own first call
+        few, out = peak()
+    most, ref = peak()
+    assert torch.equal(out, ref) and ref.requires_grad and not out.requires_grad
+    # input, aggregate, hidden and output rows of one layer; a graph keeps two to three of each of the eight
+    assert few <= 4.5 and most > 8, (few, most)
+    frozen = [p.requires_grad_(False) for p in model.parameters()]
+    assert frozen and peak()[0] <= 4.5
