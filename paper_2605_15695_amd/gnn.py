@@ -9,6 +9,7 @@ what surrounds them (bias, ReLU, its backward, the gradient sums): see FusedLaye
 from __future__ import annotations
 
 import ctypes
+from typing import NamedTuple
 
 import torch
 from torch.nn.modules import module as _all_modules
@@ -207,22 +208,21 @@ class FusedLayers(torch.autograd.Function):
     backward ReLU mask where the gradient is, (1 + eps) H is added in the aggregation, and
     the bias gradients are summed by the kernel that has the gradient in registers.
 
-    ``chain``: list of (layer, ReLU follows); the last entry has none.  ``keeps``: whether a
-    backward pass can follow, for which each layer's arrays are kept.  ``params``: the layers'
-    parameters in the order of ``_params``."""
+    ``steps``: a ``_Step`` per layer; what the modules hold may change before the backward pass.
+    ``keeps``: whether a backward pass can follow, for which each layer's arrays are kept.
+    ``params``: the layers' parameters in the order of ``_params``."""
 
     @staticmethod
-    def forward(ctx, chain, keeps, X, *params):
+    def forward(ctx, steps, keeps, X, *params):
         d = _Dense(X, [(1, 1)])
         H, keep, at = X.contiguous(), [], 0
-        for layer, relu in chain:
-            n = 1 + (layer.bias is not None) if isinstance(layer, GCNLayer) else 5
-            H, *saved = _layer_forward(d, layer, relu, H, params[at:at + n])
-            at += n
+        for step in steps:
+            H, *saved = _layer_forward(d, step, H, params[at:at + step.n_params])
+            at += step.n_params
             if keeps:
                 keep += saved
             del saved  # without a gradient each layer's arrays go before the next layer's are made
-        ctx.chain = chain
+        ctx.steps = steps
         ctx.n_params = len(params)
         if keeps:
             ctx.save_for_backward(*params, *keep)
@@ -238,19 +238,19 @@ class FusedLayers(torch.autograd.Function):
         need = ctx.needs_input_grad[3:]
         G, db = dOut.contiguous(), None  # gradient at the layer's output, its column sums if known
         at = ctx.n_params
-        for i in range(len(ctx.chain) - 1, -1, -1):
-            layer = ctx.chain[i][0]
-            op = layer.op
+        for i in range(len(ctx.steps) - 1, -1, -1):
+            step = ctx.steps[i]
+            op = step.op
             need_dH = i > 0 or ctx.needs_input_grad[2]
-            masked = i > 0 and ctx.chain[i - 1][1]
+            masked = i > 0 and ctx.steps[i - 1].relu
             # the layer before wants the column sums of its output gradient for its bias, unless
             # its weight gradient reads that gradient anyway
-            sums = i > 0 and _linear_first(ctx.chain[i - 1][0]) and ctx.chain[i - 1][0].bias is not None
-            if isinstance(layer, GCNLayer):
-                has_b = layer.bias is not None
-                at -= 1 + has_b
+            sums = i > 0 and ctx.steps[i - 1].linear_first and ctx.steps[i - 1].bias
+            at -= step.n_params
+            if step.gcn:
+                has_b = step.bias
                 W = params[at]
-                if W.shape[1] >= W.shape[0]:
+                if step.linear_first:
                     H = keep.pop()
                     if has_b and need[at + 1]:
                         grads[at + 1] = db if db is not None else d.colsum(G)
@@ -278,7 +278,6 @@ class FusedLayers(torch.autograd.Function):
                     if need_dH:
                         G = d.spmm(op.bwd, op.n_cols, dA, mask=H if masked else None)
             else:
-                at -= 5
                 eps, W1, b1, W2, b2 = params[at:at + 5]
                 Z, A, H = keep.pop(), keep.pop(), keep.pop()
                 db = dA = None
@@ -302,24 +301,29 @@ class FusedLayers(torch.autograd.Function):
                 *(g if n else None for g, n in zip(grads, need)))
 
 
-def _layer_forward(d, layer, relu, H, params):
+class _Step(NamedTuple):
+    """One layer of a chain as the forward pass found it."""
+    gcn: bool
+    op: PcsrOperator
+    n_params: int
+    bias: bool          # GCN: added to the layer's output
+    linear_first: bool  # GCN: multiplied by the weights before the aggregation
+    relu: bool
+
+
+def _layer_forward(d, step, H, params):
     """(output, then what the layer's backward pass reads) of one layer of a chain"""
-    op = layer.op
-    if isinstance(layer, GCNLayer):
-        W, b = params[0], params[1] if layer.bias is not None else None
-        if W.shape[1] >= W.shape[0]:
-            return d.spmm(op.fwd, op.n_rows, d.linear(H, W), bias=b, relu=relu), H
+    op = step.op
+    if step.gcn:
+        W, b = params[0], params[1] if step.bias else None
+        if step.linear_first:
+            return d.spmm(op.fwd, op.n_rows, d.linear(H, W), bias=b, relu=step.relu), H
         A = d.spmm(op.fwd, op.n_rows, H)
-        return d.linear(A, W, bias=b, relu=relu), H, A
+        return d.linear(A, W, bias=b, relu=step.relu), H, A
     eps, W1, b1, W2, b2 = params
     A = d.spmm(op.fwd, op.n_rows, H, self_term=H, eps=eps)
-    Z, Y = d.mlp(A, W1, b1, W2, b2, relu)
+    Z, Y = d.mlp(A, W1, b1, W2, b2, step.relu)
     return Y, H, A, Z
-
-
-def _linear_first(layer):
-    """Whether a GCN layer multiplies by its weights before it aggregates."""
-    return isinstance(layer, GCNLayer) and layer.lin.in_features >= layer.lin.out_features
 
 
 def _params(layer):
@@ -386,22 +390,25 @@ def _run_fused(chain, X):
     # kernels are launched on the current device; torch's own products follow their operands
     if torch.is_autocast_enabled() or X.device.index != torch.cuda.current_device():
         return None
-    params, n, width = [], X.shape[0], X.shape[1]
-    for layer, _ in chain:
+    steps, params, n, width = [], [], X.shape[0], X.shape[1]
+    for layer, relu in chain:
         ps = _params(layer)
         if ps is None:
             return None
-        first, last = (layer.lin, layer.lin) if type(layer) is GCNLayer else (layer.mlp[0], layer.mlp[2])
+        gcn = type(layer) is GCNLayer
+        first, last = (layer.lin, layer.lin) if gcn else (layer.mlp[0], layer.mlp[2])
         if n != layer.op.n_cols or width != first.in_features or any(p.device != X.device for p in ps):
             return None
-        if type(layer) is GINLayer and layer.op.n_rows != n:
+        if not gcn and layer.op.n_rows != n:
             return None
+        steps.append(_Step(gcn, layer.op, len(ps), gcn and layer.bias is not None,
+                           gcn and first.in_features >= first.out_features, relu))
         n, width = layer.op.n_rows, last.out_features
         params += ps
     if n == 0 or X.shape[0] == 0:
         return None
     keeps = torch.is_grad_enabled() and any(t.requires_grad for t in (X, *params))
-    return FusedLayers.apply(chain, keeps, X, *params)
+    return FusedLayers.apply(steps, keeps, X, *params)
 
 
 class GCNLayer(torch.nn.Module):

@@ -336,3 +336,25 @@ def test_forward_alone_keeps_no_layer_but_the_current_one(kind):
     assert few <= 4.5 and most > 8, (few, most)
     frozen = [p.requires_grad_(False) for p in model.parameters()]
     assert frozen and peak()[0] <= 4.5
+
+
+def test_backward_uses_the_operator_of_its_forward():
+    from paper_2605_15695_amd import gnn
+
+    g = synth.workload("poisson", "small")
+    args = (g.n_rows, g.n_cols, g.rowptr, g.colidx)
+    one = gnn.PcsrOperator(*args, g.vals, K_hint=32)
+    other = gnn.PcsrOperator(*args, g.vals * np.float32(3.0), K_hint=32)
+    X = torch.from_numpy(synth.dense_operand(g.n_rows, 16, "normal", 9)).cuda()
+    for kind in ("gcn", "gin"):
+        model = gnn.make_model(kind, one, 16, 32, 16, 2).cuda()
+        want = torch.autograd.grad(model(X).square().mean(), list(model.parameters()))
+        loss = model(X).square().mean()
+        for layer in (model[0], model[2]):             # the next batch's graph
+            layer.op = other
+            if kind == "gcn":
+                layer.bias = None
+        got = torch.autograd.grad(loss, [p for p in model.parameters()])
+        want = want if kind == "gin" else [w for w in want if w.dim() == 2]
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
