@@ -173,6 +173,9 @@ class _Dense:
         return out
 
     def spmm(self, handle, n_out, X, bias=None, relu=False, self_term=None, eps=None, mask=None):
+        # an operator's handles can be exchanged, and the library sees only pointers
+        if X.shape[0] != handle.n_cols or n_out != handle.n_rows:
+            raise ValueError("B must be n_cols x K and C n_rows x K")
         out = self.new(n_out, X.shape[1])
         if bias is not None or self_term is not None or mask is not None or relu:
             epi = pc.pcsr_epilogue_t(_p(bias), _p(self_term), _p(eps), _p(mask), int(relu), 0)

@@ -358,3 +358,22 @@ def test_backward_uses_the_operator_of_its_forward():
         want = want if kind == "gin" else [w for w in want if w.dim() == 2]
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+
+
+def test_a_handle_of_another_size_is_refused():
+    from paper_2605_15695_amd import gnn
+
+    g, small = synth.workload("poisson", "small"), synth.workload("sbm", "small")
+    op = gnn.PcsrOperator(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, K_hint=32)
+    X = torch.from_numpy(synth.dense_operand(g.n_rows, 16, "normal", 9)).cuda()
+    wrong = pc.pcsr_build(small.n_rows, small.n_cols, small.rowptr, small.colidx, small.vals)
+    assert small.n_rows != g.n_rows
+    layer = gnn.GCNLayer(op, 16, 32).cuda()
+    out = layer(X)
+    op.bwd = wrong
+    with pytest.raises(ValueError):
+        layer(X.requires_grad_(True)).sum().backward()
+    op.fwd = wrong
+    with pytest.raises(ValueError):
+        layer(X)
+    assert out.shape == (g.n_rows, 32)
