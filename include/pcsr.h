@@ -43,7 +43,8 @@ enum {
     PCSR_FLAG_GPU_BUILD = 16,  /* generate the PCSR arrays with GPU kernels (host CSR arrays
                                   are uploaded first).  CSR arrays given in device memory are
                                   always built this way, and so are host arrays of 200,000
-                                  nonzeros and more; the arrays come out the same either way.
+                                  nonzeros and more, unless the scratch memory that takes does
+                                  not fit; the arrays come out the same either way.
                                   The windows of col_window are then chosen there as well      */
     PCSR_FLAG_COLUMN_ORDER = 64,/* S = 1 only: column-ordered schedule.  The work items of
                                   panels that were split run in ascending order of their first

@@ -412,22 +412,23 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
     if (column_order && (!prm.S || prm.col_window)) return PCSR_E_UNSUPPORTED;
     if (host_only && (prm.flags & PCSR_FLAG_GPU_BUILD) && !prm.col_window) return PCSR_E_INVALID_ARG;
     // On the GPU wherever the arrays are there already, the caller asks for it, or the upload and
-    // the launches cost less than the host threads take (12 M nonzeros: 6 ms against 25-60).
-    if (!host_only && (device_csr || ((prm.flags & PCSR_FLAG_GPU_BUILD) && !prm.col_window) || pcsr::relabel_on_gpu(nnz))) {
+    // the launches cost less than the host threads take (12 M nonzeros: 6 ms against 25-60).  Nobody
+    // asked in the last case, so if the scratch does not fit the host builder, which needs none, does it.
+    const bool asked = device_csr || ((prm.flags & PCSR_FLAG_GPU_BUILD) && !prm.col_window);
+    if (!host_only && (asked || pcsr::relabel_on_gpu(nnz))) {
         UploadedCsr up;
         const int32_t *d_rowptr = rowptr, *d_colidx = colidx;
         const float *d_vals = vals;
         if (!device_csr) {
             rc = up.put(n_rows, nnz, rowptr, colidx, vals);
-            if (rc != PCSR_OK) return rc;
             d_rowptr = up.rowptr;
             d_colidx = up.colidx;
             d_vals = up.vals;
         }
         pcsr_handle_s *h = nullptr;
-        rc = handle_from_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, prm, &h);
+        if (rc == PCSR_OK) rc = handle_from_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, prm, &h);
         if (rc == PCSR_OK) *out = h;
-        if (rc != kWindowsOnHost) return rc;
+        if (rc != kWindowsOnHost && !(rc == PCSR_E_OOM && !asked)) return rc;
     }
 
     try {
@@ -532,54 +533,53 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
     }
 }
 
-int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
-                        const float *vals, const pcsr_params_t *p, int32_t K, int32_t with_transpose,
-                        pcsr_handle_t out[2])
+// pcsr_operator_build's parameters for one direction: the caller's, or what pcsr_select picks for
+// these features, its launch shape left on auto so that one handle serves every layer width.
+static int operator_params(const pcsr_params_t *p, bool pick, const double *f, int32_t K, pcsr_params_t *prm)
 {
-    if (!out || !rowptr || n_rows < 0 || n_cols < 0 || nnz < 0 || (nnz > 0 && (!colidx || !vals)))
-        return PCSR_E_INVALID_ARG;
-    if (nnz >= (int64_t(1) << 31) || n_rows >= (int64_t(1) << 31) - 1 || n_cols >= (int64_t(1) << 31) - 1)
-        return PCSR_E_TOO_LARGE;
-    const bool device_csr = p && (p->flags & PCSR_FLAG_DEVICE_CSR);
-    UploadedCsr up;
-    int herr = 0, rc = PCSR_OK;
-    const bool pick = !p || p->reserved[0] == PCSR_OPERATOR_SELECT;
-    pcsr_handle_t made[2] = {nullptr, nullptr};
-    if (!device_csr && nnz < kHostOperator && n_rows < kHostOperator && n_cols < kHostOperator) {
-        // small: the host is done before the GPU's launches and waits would be
-        auto direction = [&](int64_t nr, int64_t nc, const int32_t *rp, const int32_t *ci, const float *va,
-                             pcsr_handle_t *h) -> int {
-            pcsr_params_t prm;
-            if (pick) {
-                double f[PCSR_N_FEATURES];
-                int r = pcsr_features(nr, nc, nnz, rp, ci, 0, f, PCSR_N_FEATURES);
-                if (r == PCSR_OK) r = pcsr_select(f, K, &prm);
-                if (r != PCSR_OK) return r;
-                prm.lanes_per_row = prm.vec = prm.rep = 0;
-            } else {
-                prm = *p;
-            }
-            return pcsr_build(nr, nc, nnz, rp, ci, va, &prm, h);
-        };
-        rc = direction(n_rows, n_cols, rowptr, colidx, vals, &made[0]);
-        try {
-            if (rc == PCSR_OK && with_transpose) {
-                std::vector<int32_t> rp(n_cols + 1), ci(nnz);
-                std::vector<float> va(nnz);
-                rc = pcsr_transpose_csr(n_rows, n_cols, rowptr, colidx, vals, rp.data(), ci.data(), va.data());
-                if (rc == PCSR_OK) rc = direction(n_cols, n_rows, rp.data(), ci.data(), va.data(), &made[1]);
-            }
-        } catch (const std::bad_alloc &) {
-            rc = PCSR_E_OOM;
-        }
-        if (rc != PCSR_OK) {
-            (void)pcsr_free(made[0]);
-            return rc;
-        }
-        out[0] = made[0];
-        out[1] = made[1];
+    if (!pick) {
+        *prm = *p;
         return PCSR_OK;
     }
+    const int rc = pcsr_select(f, K, prm);
+    if (rc == PCSR_OK) prm->lanes_per_row = prm->vec = prm->rep = 0;
+    return rc;
+}
+
+// Both directions from arrays in host memory with what needs no scratch on the GPU.
+static int operator_on_host(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
+                            const float *vals, const pcsr_params_t *p, bool pick, int32_t K, bool with_transpose,
+                            pcsr_handle_t made[2])
+{
+    auto direction = [&](int64_t nr, int64_t nc, const int32_t *rp, const int32_t *ci, const float *va,
+                         pcsr_handle_t *h) -> int {
+        pcsr_params_t prm;
+        double f[PCSR_N_FEATURES];
+        int rc = pick ? pcsr_features(nr, nc, nnz, rp, ci, 0, f, PCSR_N_FEATURES) : PCSR_OK;
+        if (rc == PCSR_OK) rc = operator_params(p, pick, f, K, &prm);
+        return rc == PCSR_OK ? pcsr_build(nr, nc, nnz, rp, ci, va, &prm, h) : rc;
+    };
+    int rc = direction(n_rows, n_cols, rowptr, colidx, vals, &made[0]);
+    try {
+        if (rc == PCSR_OK && with_transpose) {
+            std::vector<int32_t> rp(n_cols + 1), ci(nnz);
+            std::vector<float> va(nnz);
+            rc = pcsr_transpose_csr(n_rows, n_cols, rowptr, colidx, vals, rp.data(), ci.data(), va.data());
+            if (rc == PCSR_OK) rc = direction(n_cols, n_rows, rp.data(), ci.data(), va.data(), &made[1]);
+        }
+    } catch (const std::bad_alloc &) {
+        rc = PCSR_E_OOM;
+    }
+    return rc;
+}
+
+// Both directions set up on the GPU, from one upload where the arrays are in host memory.
+static int operator_on_gpu(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
+                           const float *vals, const pcsr_params_t *p, bool pick, int32_t K, bool with_transpose,
+                           bool device_csr, pcsr_handle_t made[2])
+{
+    UploadedCsr up;
+    int herr = 0, rc = PCSR_OK;
     if (!device_csr) {
         rc = up.put(n_rows, nnz, rowptr, colidx, vals);
         if (rc != PCSR_OK) return rc;
@@ -596,16 +596,10 @@ int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32
     auto direction = [&](int64_t nr, int64_t nc, const int32_t *rp, const int32_t *ci, const float *va,
                          pcsr_handle_t *h) -> int {
         pcsr_params_t prm;
-        if (pick) {
-            double f[PCSR_N_FEATURES];
-            int r = pcsr::features_device(nr, nc, nnz, rp, ci, 0, f, &herr);
-            if (r == PCSR_OK) r = pcsr_select(f, K, &prm);
-            if (r != PCSR_OK) return failed(r);
-            // launch shape stays on auto so one handle serves every layer width
-            prm.lanes_per_row = prm.vec = prm.rep = 0;
-        } else {
-            prm = *p;
-        }
+        double f[PCSR_N_FEATURES];
+        int r = pick ? pcsr::features_device(nr, nc, nnz, rp, ci, 0, f, &herr) : PCSR_OK;
+        if (r == PCSR_OK) r = operator_params(p, pick, f, K, &prm);
+        if (r != PCSR_OK) return failed(r);
         prm.flags |= PCSR_FLAG_DEVICE_CSR | PCSR_FLAG_NO_VALIDATE;
         return pcsr_build(nr, nc, nnz, rp, ci, va, &prm, h);
     };
@@ -616,10 +610,38 @@ int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32
                                            &herr));
         if (rc == PCSR_OK) rc = direction(n_cols, n_rows, t.rowptr, t.colidx, t.vals, &made[1]);
     }
-    if (rc != PCSR_OK) {
+    return rc;
+}
+
+int pcsr_operator_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
+                        const float *vals, const pcsr_params_t *p, int32_t K, int32_t with_transpose,
+                        pcsr_handle_t out[2])
+{
+    if (!out || !rowptr || n_rows < 0 || n_cols < 0 || nnz < 0 || (nnz > 0 && (!colidx || !vals)))
+        return PCSR_E_INVALID_ARG;
+    if (nnz >= (int64_t(1) << 31) || n_rows >= (int64_t(1) << 31) - 1 || n_cols >= (int64_t(1) << 31) - 1)
+        return PCSR_E_TOO_LARGE;
+    const bool device_csr = p && (p->flags & PCSR_FLAG_DEVICE_CSR);
+    const bool pick = !p || p->reserved[0] == PCSR_OPERATOR_SELECT;
+    // small: the host is done before the GPU's launches and waits would be
+    const bool small = !device_csr && nnz < kHostOperator && n_rows < kHostOperator && n_cols < kHostOperator;
+    pcsr_handle_t made[2] = {nullptr, nullptr};
+    auto give_back = [&] {
         (void)pcsr_free(made[0]);
-        return rc;
+        (void)pcsr_free(made[1]);
+        made[0] = made[1] = nullptr;
+    };
+    int rc = PCSR_E_OOM;
+    if (!small) {
+        rc = operator_on_gpu(n_rows, n_cols, nnz, rowptr, colidx, vals, p, pick, K, with_transpose, device_csr, made);
+        if (rc != PCSR_OK) give_back();
     }
+    // the scratch did not fit: the host needs none
+    if (rc == PCSR_E_OOM && !device_csr) {
+        rc = operator_on_host(n_rows, n_cols, nnz, rowptr, colidx, vals, p, pick, K, with_transpose, made);
+        if (rc != PCSR_OK) give_back();
+    }
+    if (rc != PCSR_OK) return rc;
     out[0] = made[0];
     out[1] = made[1];
     return PCSR_OK;

@@ -1,0 +1,108 @@
+"""Set-up calls whose GPU scratch does not fit: the host builder needs none, so a host CSR is built there.
+The library runs against a device of host memory (fake_hip) in a process of its own; no GPU calls."""
+import pathlib
+import subprocess
+import sys
+
+import pytest
+
+ROOT = pathlib.Path(__file__).resolve().parent.parent
+
+SCRIPT = r"""
+import ctypes, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)   # before the library looks its symbols up
+import numpy as np
+import paper_2605_15695_amd as pc
+from paper_2605_15695_amd import binding
+
+n, deg = 30000, 8                                          # past the size the GPU is used from
+assert n * deg >= 200000
+rng = np.random.default_rng(5)
+rows = [np.sort(rng.choice(n, deg, replace=False)) for _ in range(n)]
+rows[1:n // 2:2] = rows[0:n // 2:2]                        # half of the row pairs share their columns
+colidx = np.concatenate(rows).astype(np.int32)
+rowptr = np.arange(0, n * deg + 1, deg, dtype=np.int32)
+vals = rng.random(n * deg).astype(np.float32)
+kw = dict(V=2, S=1, SG=4)
+
+
+def same(h, ref):
+    e, r = pc.pcsr_export(h), pc.pcsr_export(ref)
+    return all(np.array_equal(e[k], r[k]) for k in r)
+
+
+host = pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(flags=pc.PCSR_FLAG_HOST_ONLY, **kw))
+row = np.repeat(np.arange(n, dtype=np.int32), deg)
+at = np.lexsort((row, colidx))
+t = np.concatenate([[0], np.cumsum(np.bincount(colidx, minlength=n))]).astype(np.int32), row[at], vals[at]
+host_t = pc.pcsr_build(n, n, *t, pc.make_params(flags=pc.PCSR_FLAG_HOST_ONLY, **kw))
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    lib = tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so"
+    subprocess.run(["gcc", "-O1", "-fPIC", "-shared", "-o", str(lib), str(ROOT / "tests/fake_hip/fake_hip.c")], check=True)
+    return lib
+
+
+def _run(fake, body):
+    r = subprocess.run([sys.executable, "-c", SCRIPT + body, str(fake)], cwd=ROOT, capture_output=True, text=True,
+                       timeout=120)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+
+# the upload's three arrays, then the first of the build's own
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+def test_build_falls_back_to_the_host(fake, k):
+    _run(fake, f"""
+fake.fake_hip_fail({k}, {k})
+h = pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(**kw))
+assert fake.fake_hip_allocations() > {k} and same(h, host)
+h.close()
+""")
+
+
+def test_build_reports_what_fits_nowhere(fake):
+    _run(fake, """
+fake.fake_hip_fail(1, 1 << 30)                             # the product's own arrays neither
+for flags in (0, pc.PCSR_FLAG_GPU_BUILD):
+    try:
+        pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(flags=flags, **kw))
+        assert False
+    except pc.PcsrError as e:
+        assert e.code == binding.PCSR_E_OOM
+assert fake.fake_hip_live() == 0
+""")
+
+
+def test_build_on_the_gpu_is_not_replaced_where_it_was_asked_for(fake):
+    _run(fake, """
+fake.fake_hip_fail(2, 2)
+try:
+    pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(flags=pc.PCSR_FLAG_GPU_BUILD, **kw))
+    assert False
+except pc.PcsrError as e:
+    assert e.code == binding.PCSR_E_OOM
+""")
+
+
+# refused: what the upload of rowptr asks for, not the product's arrays
+@pytest.mark.parametrize("transpose", [True, False])
+def test_operator_falls_back_to_the_host(fake, transpose):
+    _run(fake, f"""
+fake.fake_hip_refuse(n * 4, n * 4 + 4096)
+a, b = binding.pcsr_operator_build(n, n, rowptr, colidx, vals, pc.make_params(**kw), 64, {transpose})
+assert same(a, host) and (same(b, host_t) if {transpose} else b is None)
+""")
+
+
+def test_operator_picks_the_same_parameters_there(fake):
+    _run(fake, """
+p = pc.pcsr_select(pc.pcsr_features(n, n, rowptr, colidx), 64)
+p.flags |= pc.PCSR_FLAG_HOST_ONLY
+ref = pc.pcsr_build(n, n, rowptr, colidx, vals, p)
+fake.fake_hip_refuse(n * 4, n * 4 + 4096)
+picked, _ = binding.pcsr_operator_build(n, n, rowptr, colidx, vals, None, 64, False)
+assert same(picked, ref)
+""")
