@@ -191,6 +191,15 @@ int pcsr_reserve_workspace(pcsr_handle_t h, int32_t K);
 int pcsr_free(pcsr_handle_t h);
 
 /*
+ * Gives device memory that the library keeps for reuse back to the driver: up to 1 GiB of
+ * freed handles, workspaces and set-up scratch per GPU, of the current device.  The library does
+ * so by itself before it reports OOM, and when torch needs more memory on a device of which
+ * less than an eighth is free.  bytes (host, may be NULL) receives how much it was.  Waits for
+ * the device.  Errors: HIP.
+ */
+int pcsr_release_cached(int64_t *bytes);
+
+/*
  * Changes the kernel-only parameters (lanes_per_row, vec, rep, waves_per_wg,
  * items_per_group, and the PCSR_FLAG_NO_XCD_REMAP and PCSR_FLAG_ATOMIC_SPLIT bits of
  * flags) of an existing handle; 0 = auto.  The PCSR

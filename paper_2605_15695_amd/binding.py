@@ -64,6 +64,9 @@ def _lib():
         lib.pcsr_build.argtypes = [i64, i64, i64, vp, vp, vp, pp, ctypes.POINTER(vp)]
         lib.pcsr_spmm.argtypes = [vp, vp, vp, i32, vp]
         lib.pcsr_free.argtypes = [vp]
+        lib.pcsr_release_cached.argtypes = [ctypes.POINTER(i64)]
+        lib.pcsr_release_cached_if_low.argtypes = [vp]
+        lib.pcsr_release_cached_if_low.restype = i64
         lib.pcsr_spmm_static.argtypes = [vp, vp, vp, i32, vp]
         lib.pcsr_static_scratch_bytes.restype = i64
         lib.pcsr_workspace_bytes.argtypes = [vp, i32, ctypes.POINTER(i64)]
@@ -101,7 +104,7 @@ def _lib():
                      "pcsr_transpose_csr", "pcsr_workspace_bytes", "pcsr_reserve_workspace", "pcsr_spmm_static",
                      "pcsr_export_schedule", "pcsr_reorder_by_degree", "pcsr_spmm_epilogue", "pcsr_gnn_linear",
                      "pcsr_gnn_mlp", "pcsr_gnn_mlp_backward", "pcsr_gnn_linear_backward", "pcsr_gnn_wgrad",
-                     "pcsr_gnn_colsum", "pcsr_operator_build"):
+                     "pcsr_gnn_colsum", "pcsr_operator_build", "pcsr_release_cached"):
             getattr(lib, name).restype = ctypes.c_int
         _LIB = lib
     return _LIB
@@ -225,7 +228,8 @@ def _first_spmm(h, B, C, K, stream):
     spec = importlib.util.spec_from_file_location("_pcsr_py", PY_PATH)
     mod = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(mod)
-    mod.init(ctypes.cast(_lib().pcsr_spmm, ctypes.c_void_p).value)
+    lib = _lib()
+    mod.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.pcsr_spmm, lib.pcsr_release_cached_if_low)))
     _spmm = mod.spmm
     return _spmm(h, B, C, K, stream)
 
@@ -279,6 +283,15 @@ def pcsr_free(h: Handle) -> None:
     rc = _lib().pcsr_free(raw)
     if rc != PCSR_OK:
         raise PcsrError(rc, "pcsr_free")
+
+
+def pcsr_release_cached() -> int:
+    """Gives the device memory kept for reuse on the current device back to the driver; returns the bytes."""
+    out = ctypes.c_int64(0)
+    rc = _lib().pcsr_release_cached(ctypes.byref(out))
+    if rc != PCSR_OK:
+        raise PcsrError(rc, "pcsr_release_cached")
+    return int(out.value)
 
 
 def pcsr_set_kernel_params(h: Handle, lanes_per_row=0, vec=0, rep=0, waves_per_wg=0,

@@ -828,6 +828,14 @@ int pcsr_free(pcsr_handle_t h)
     return PCSR_OK;
 }
 
+int pcsr_release_cached(int64_t *bytes)
+{
+    size_t n = 0;
+    if (!hip_ok(pcsr::pool_give_back(&n))) return PCSR_E_HIP;
+    if (bytes) *bytes = (int64_t)n;
+    return PCSR_OK;
+}
+
 int pcsr_set_kernel_params(pcsr_handle_t h, int32_t lanes_per_row, int32_t vec, int32_t rep,
                            int32_t waves_per_wg, int32_t items_per_group, int32_t flags)
 {

@@ -140,6 +140,28 @@ void pool_release(void *p)
     (void)hipFree(p);
 }
 
+hipError_t pool_give_back(size_t *bytes)
+{
+    *bytes = 0;
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    // a capture that another thread has under way must not be ended by these frees: the blocks are no part of it
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    {
+        Pool &P = pool();
+        std::lock_guard<std::mutex> lock(P.mu);
+        auto at = P.caches.find(dev);
+        if (at != P.caches.end()) {
+            *bytes = at->second.bytes;
+            while (!at->second.idle.empty()) drop(at->second, at->second.idle.begin());
+        }
+    }
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return hipSuccess;
+}
+
 namespace {
 
 constexpr int kCopyThreads = 8;
@@ -252,3 +274,14 @@ hipError_t copy_to_device(void *dst, const void *src, size_t bytes)
 }
 
 } // namespace pcsr
+
+extern "C" int64_t pcsr_release_cached_if_low(void *stream)
+{
+    size_t free = 0, total = 0, bytes = 0;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool idle = hipStreamIsCapturing(static_cast<hipStream_t>(stream), &status) == hipSuccess &&
+                      status == hipStreamCaptureStatusNone;
+    const bool low = idle && hipMemGetInfo(&free, &total) == hipSuccess && free < total / pcsr::kPoolLowMemory;
+    if (!idle || (low && pcsr::pool_give_back(&bytes) != hipSuccess)) (void)hipGetLastError();
+    return (int64_t)bytes;
+}

@@ -12,9 +12,11 @@ namespace pcsr {
 
 // Blocks kept for reuse per GPU at most; beyond it the longest unused go back to the driver, and
 // so does a block that kPoolIdleAllocs allocations have passed over.  All of them go back
-// before an allocation is reported as out of memory.
+// before an allocation is reported as out of memory, when the caller asks (pcsr_release_cached), and
+// when torch asks the driver for more with less than one part in kPoolLowMemory of the device free.
 constexpr size_t kPoolBytes = size_t(1) << 30;
 constexpr uint64_t kPoolIdleAllocs = 1024;
+constexpr size_t kPoolLowMemory = 8;
 
 // On the current device.  Thread safe.  Contents are undefined.
 hipError_t pool_alloc(void **p, size_t bytes);
@@ -25,6 +27,8 @@ void pool_free(void *p);
 // and the blocks have to go back through pool_release instead.
 bool pool_quiesce(int device);
 void pool_release(void *p); // hipFree, past the cache
+// Gives the blocks kept for the current device back to the driver; bytes: how many that were.
+hipError_t pool_give_back(size_t *bytes);
 
 // Large synchronous copies between pageable host memory and the current device.  A few threads
 // each move 1 MB pieces through pinned buffers of their own (kept for reuse, 16 MB in all), so
@@ -37,3 +41,8 @@ hipError_t copy_to_host(void *dst, const void *src, size_t bytes);
 hipError_t copy_to_device(void *dst, const void *src, size_t bytes);
 
 } // namespace pcsr
+
+// For torch's allocator, which asks before it takes more memory from the driver (pcsr_py.cpp):
+// pcsr_release_cached if the device is that low and `stream` is not being captured.  Returns the
+// bytes given back.
+extern "C" int64_t pcsr_release_cached_if_low(void *stream);

@@ -3,9 +3,29 @@
 // objects.  A 4 us product is bound by the host, and ctypes with a dozen attribute lookups took
 // 2.5 us of the call's 5.3.  Anything but plain fp32 device tensors is left to the Python code
 // (by returning NotImplemented), which knows the errors.
+#include <c10/hip/HIPCachingAllocator.h>
+#include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+
+namespace {
+
+using ReleaseFn = int64_t (*)(void *);
+ReleaseFn g_release = nullptr;
+
+} // namespace
+
+namespace c10 { // where the registry is declared
+
+// torch's allocator asks before it takes more memory from the driver: what the library keeps for
+// reuse goes first where the device is low
+struct PcsrGiveBack : FreeMemoryCallback {
+    bool Execute() override { return g_release && g_release(hip::getCurrentHIPStream().stream()) > 0; }
+};
+REGISTER_FREE_MEMORY_CALLBACK("pcsr", PcsrGiveBack)
+
+} // namespace c10
 
 namespace {
 
@@ -70,17 +90,23 @@ PyObject *spmm(PyObject *, PyObject *const *args, Py_ssize_t n)
     return PyLong_FromLong(rc);
 }
 
-// init(address of pcsr_spmm)
-PyObject *init(PyObject *, PyObject *arg)
+// init(address of pcsr_spmm, address of pcsr_release_cached_if_low)
+PyObject *init(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
-    g_spmm = reinterpret_cast<SpmmFn>(PyLong_AsVoidPtr(arg));
+    if (n != 2) {
+        PyErr_SetString(PyExc_TypeError, "init(spmm, release)");
+        return nullptr;
+    }
+    void *spmm = PyLong_AsVoidPtr(args[0]), *release = PyErr_Occurred() ? nullptr : PyLong_AsVoidPtr(args[1]);
     if (PyErr_Occurred()) return nullptr;
+    g_spmm = reinterpret_cast<SpmmFn>(spmm);
+    g_release = reinterpret_cast<ReleaseFn>(release);
     Py_RETURN_NONE;
 }
 
 PyMethodDef methods[] = {
     {"spmm", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(spmm)), METH_FASTCALL, nullptr},
-    {"init", init, METH_O, nullptr},
+    {"init", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(init)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_pcsr_py", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -23,6 +23,14 @@ void fake_hip_refuse(size_t from, size_t to)
 int fake_hip_allocations(void) { return calls; }
 long fake_hip_live(void) { return live; }
 
+static size_t free_bytes = 100, total_bytes = 100;
+static int capturing;
+void fake_hip_memory(size_t free_now, size_t total) { free_bytes = free_now; total_bytes = total; }
+void fake_hip_capture(int on) { capturing = on; }
+
+int hipMemGetInfo(size_t *f, size_t *t) { *f = free_bytes; *t = total_bytes; return kOk; }
+int hipStreamIsCapturing(void *s, int *status) { (void)s; *status = capturing; return kOk; }
+int hipThreadExchangeStreamCaptureMode(int *mode) { (void)mode; return kOk; }
 int hipGetDeviceCount(int *n) { *n = 1; return kOk; }
 int hipGetDevice(int *d) { *d = 0; return kOk; }
 int hipSetDevice(int d) { (void)d; return kOk; }

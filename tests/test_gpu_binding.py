@@ -36,3 +36,35 @@ def test_arguments_and_errors():
     h.close()
     with pytest.raises(pc.PcsrError):
         pc.pcsr_spmm(h, B, C, K)
+
+
+def test_memory_kept_for_reuse_goes_back():
+    import ctypes
+    import importlib.util
+
+    from paper_2605_15695_amd import binding
+
+    g = synth.workload("sbm", "small")
+    B = torch.from_numpy(synth.dense_operand(g.n_cols, 16, "normal", 3)).cuda()
+    C = torch.empty(g.n_rows, 16, device="cuda")
+    h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals)
+    pc.pcsr_spmm(h, B, C, 16)
+    h.close()
+    before = torch.cuda.mem_get_info()[0]
+    released = pc.pcsr_release_cached()
+    assert released >= g.nnz * 8 and torch.cuda.mem_get_info()[0] >= before
+    assert pc.pcsr_release_cached() == 0
+    # torch asks before it takes more from the driver
+    spec = importlib.util.spec_from_file_location("_pcsr_py", binding.PY_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    asked = []
+    ask = ctypes.CFUNCTYPE(ctypes.c_int64, ctypes.c_void_p)(lambda stream: asked.append(stream) or 0)
+    lib = binding._lib()
+    mod.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.pcsr_spmm, ask)))
+    try:
+        torch.cuda.empty_cache()
+        torch.empty(100 << 20, device="cuda")
+        assert asked
+    finally:
+        mod.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.pcsr_spmm, lib.pcsr_release_cached_if_low)))

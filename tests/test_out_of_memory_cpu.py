@@ -106,3 +106,28 @@ fake.fake_hip_refuse(n * 4, n * 4 + 4096)
 picked, _ = binding.pcsr_operator_build(n, n, rowptr, colidx, vals, None, 64, False)
 assert same(picked, ref)
 """)
+
+
+def test_kept_memory_goes_back_when_asked_for_and_when_the_device_is_low(fake):
+    _run(fake, """
+lib = binding._lib()
+small = slice(0, 1000 * deg)
+
+
+def build_and_close():
+    pc.pcsr_build(1000, n, rowptr[:1001], colidx[small], vals[small]).close()
+    assert fake.fake_hip_live() > 0
+
+
+build_and_close()
+assert pc.pcsr_release_cached() >= 1000 * deg * 8 and fake.fake_hip_live() == 0
+assert pc.pcsr_release_cached() == 0
+build_and_close()
+fake.fake_hip_memory(13, 100)
+assert lib.pcsr_release_cached_if_low(None) == 0 and fake.fake_hip_live() > 0      # more than an eighth is free
+fake.fake_hip_memory(11, 100)
+fake.fake_hip_capture(1)
+assert lib.pcsr_release_cached_if_low(None) == 0 and fake.fake_hip_live() > 0
+fake.fake_hip_capture(0)
+assert lib.pcsr_release_cached_if_low(None) > 0 and fake.fake_hip_live() == 0
+""")
