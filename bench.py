@@ -158,7 +158,7 @@ def main() -> int:
     t0 = time.time()
     h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, params)
     build_ms = (time.time() - t0) * 1e3
-    launch = pc.pcsr_query_launch(h, K)
+    launch = pc.pcsr_query_kernel(h, K)
     instance = kernel_instance(V, S, launch)
     schedule = "column" if (int(params.flags) & pc.PCSR_FLAG_COLUMN_ORDER) and S else "index"
     workload_name = f"{args.workload}-{args.size}" + (f"+reorder({args.reorder})" if args.reorder else "")

@@ -211,12 +211,19 @@ int pcsr_set_kernel_params(pcsr_handle_t h, int32_t lanes_per_row, int32_t vec, 
                            int32_t waves_per_wg, int32_t items_per_group, int32_t flags);
 
 /*
- * Reports the launch shape pcsr_spmm would use for width K with the handle's current
- * kernel parameters (after "auto" resolution): out[0..7] = lanes_per_row, vec, rep,
- * waves_per_wg, grid.x, grid.y, items_per_group, dynamic LDS bytes (0 unless the
- * column-window kernel runs).  Host memory.  Errors: INVALID_ARG, UNSUPPORTED.
+ * Reports the launch shape that the handle's current kernel parameters mean for width K
+ * (after "auto" resolution): out[0..7] = lanes_per_row, vec, rep, waves_per_wg, grid.x,
+ * grid.y, items_per_group, dynamic LDS bytes (0 unless the column-window kernel runs).
+ * Host memory.  Errors: INVALID_ARG, UNSUPPORTED.
  */
 int pcsr_query_launch(pcsr_handle_t h, int32_t K, int32_t out[8]);
+
+/*
+ * The same for the kernel instance that pcsr_spmm launches.  It differs where another shape
+ * stands in for that one: an auto shape whose K is no multiple of 4 or, for rows in 64-column
+ * slices, of 32, and pcsr_select's shapes with flag bits above 15 (vec need not divide K there).
+ */
+int pcsr_query_kernel(pcsr_handle_t h, int32_t K, int32_t out[8]);
 
 /*
  * Column-window blocking as built into the handle (host, fp64[3]): col_window, average

@@ -73,6 +73,7 @@ def _lib():
         lib.pcsr_reserve_workspace.argtypes = [vp, i32]
         lib.pcsr_set_kernel_params.argtypes = [vp, i32, i32, i32, i32, i32, i32]
         lib.pcsr_query_launch.argtypes = [vp, i32, ctypes.POINTER(i32 * 8)]
+        lib.pcsr_query_kernel.argtypes = [vp, i32, ctypes.POINTER(i32 * 8)]
         lib.pcsr_window_stats.argtypes = [vp, ctypes.POINTER(ctypes.c_double * 3)]
         lib.pcsr_export.argtypes = [vp, ctypes.POINTER(i64 * 6), vp, vp, vp, vp]
         lib.pcsr_export_schedule.argtypes = [vp, ctypes.POINTER(i64), vp, vp]
@@ -99,7 +100,7 @@ def _lib():
         lib.pcsr_gnn_wgrad.argtypes = [i64, i32, i32, vp, vp, vp, vp, vp, vp]
         lib.pcsr_gnn_colsum.argtypes = [i64, i32, vp, vp, vp, vp]
         for name in ("pcsr_build", "pcsr_spmm", "pcsr_free", "pcsr_set_kernel_params",
-                     "pcsr_query_launch", "pcsr_export", "pcsr_features", "pcsr_select",
+                     "pcsr_query_launch", "pcsr_query_kernel", "pcsr_export", "pcsr_features", "pcsr_select",
                      "pcsr_window_stats", "pcsr_features_device", "pcsr_reorder", "pcsr_permute_csr",
                      "pcsr_transpose_csr", "pcsr_workspace_bytes", "pcsr_reserve_workspace", "pcsr_spmm_static",
                      "pcsr_export_schedule", "pcsr_reorder_by_degree", "pcsr_spmm_epilogue", "pcsr_gnn_linear",
@@ -301,13 +302,23 @@ def pcsr_set_kernel_params(h: Handle, lanes_per_row=0, vec=0, rep=0, waves_per_w
         raise PcsrError(rc, "pcsr_set_kernel_params")
 
 
-def pcsr_query_launch(h: Handle, K: int) -> dict:
+def _query(name, h: Handle, K: int) -> dict:
     out = (ctypes.c_int32 * 8)()
-    rc = _lib().pcsr_query_launch(h.raw, K, ctypes.byref(out))
+    rc = getattr(_lib(), name)(h.raw, K, ctypes.byref(out))
     if rc != PCSR_OK:
-        raise PcsrError(rc, "pcsr_query_launch")
+        raise PcsrError(rc, name)
     return dict(zip(("lanes_per_row", "vec", "rep", "waves_per_wg", "grid_x", "grid_y", "items_per_group",
                      "lds_bytes"), list(out)))
+
+
+def pcsr_query_launch(h: Handle, K: int) -> dict:
+    """The launch shape that the handle's parameters mean for width K."""
+    return _query("pcsr_query_launch", h, K)
+
+
+def pcsr_query_kernel(h: Handle, K: int) -> dict:
+    """The shape of the kernel instance that pcsr_spmm launches for width K."""
+    return _query("pcsr_query_kernel", h, K)
 
 
 def pcsr_window_stats(h: Handle) -> dict:

@@ -869,6 +869,23 @@ int pcsr_query_launch(pcsr_handle_t h, int32_t K, int32_t out[8])
     return PCSR_OK;
 }
 
+int pcsr_query_kernel(pcsr_handle_t h, int32_t K, int32_t out[8])
+{
+    if (!valid(h) || !out) return PCSR_E_INVALID_ARG;
+    pcsr::LaunchShape ls;
+    int rc = resolve_launch(h, K, &ls);
+    if (rc != PCSR_OK) return rc;
+    out[0] = ls.k_lpr;
+    out[1] = ls.k_vec;
+    out[2] = ls.k_rep;
+    out[3] = ls.waves;
+    out[4] = ls.k_grid_x;
+    out[5] = ls.k_grid_y;
+    out[6] = ls.ipg;
+    out[7] = ls.lds_bytes;
+    return PCSR_OK;
+}
+
 int pcsr_window_stats(pcsr_handle_t h, double out[3])
 {
     if (!valid(h) || !out) return PCSR_E_INVALID_ARG;

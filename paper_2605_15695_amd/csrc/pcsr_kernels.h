@@ -57,8 +57,8 @@ struct LaunchShape {
     int32_t window; // 1: column-window kernel (one workgroup per item block, B window in LDS)
     int32_t lds_bytes;
     int32_t grid_x, grid_y;
-    // What is launched in place of that shape where K is no multiple of 4 and the vector it asks
-    // for only the widest that divides K: 16-byte loads at 4-byte addresses (see resolve_launch).
+    // What is launched in place of that shape where it reads rows badly: wide loads at 4-byte
+    // addresses (see resolve_launch).  The same shape everywhere else.
     int32_t k_lpr, k_vec, k_rep, k_grid_x, k_grid_y;
 };
 

@@ -204,7 +204,7 @@ def main(argv=None) -> int:
                 pc.pcsr_set_kernel_params(h, lpr, vec, rep, waves, ipg,
                                           0 if remap else pc.PCSR_FLAG_NO_XCD_REMAP)
                 try:
-                    q = pc.pcsr_query_launch(h, K)
+                    q = pc.pcsr_query_kernel(h, K)
                 except pc.PcsrError:
                     continue
                 Cd.fill_(float("nan"))
@@ -255,7 +255,7 @@ def main(argv=None) -> int:
         # the library's own pick (pcsr_select) for this input, timed like the others
         sel = pc.pcsr_select(feats, K)
         hsel = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, sel)
-        qs = pc.pcsr_query_launch(hsel, K)
+        qs = pc.pcsr_query_kernel(hsel, K)
         Cd.fill_(float("nan"))
         med, mn = time_launches(lambda: pc.pcsr_spmm(hsel, Bd, Cd, K, stream), stream, torch,
                                 args.warmup, args.reps)

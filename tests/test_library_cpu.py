@@ -398,3 +398,25 @@ def test_selector_proposes_the_window_only_where_the_build_keeps_it():
     h = pc.pcsr_build(gs.n_rows, gs.n_cols, gs.rowptr, gs.colidx, gs.vals, pc.make_params(col_window=512, flags=HOST))
     assert pc.pcsr_window_stats(h)["col_window"] == 512
     h.close()
+
+
+def test_query_kernel_reports_what_is_launched():
+    """The shape that stands in where the one asked for reads rows badly; elsewhere the two queries agree."""
+    shape = lambda q: (q["lanes_per_row"], q["vec"], q["rep"])  # noqa: E731
+    g = synth.workload("sbm_shuffled", "small")
+    plain = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, pc.make_params(flags=HOST))
+    assert shape(pc.pcsr_query_launch(plain, 75)) == (64, 1, 2)
+    q = pc.pcsr_query_kernel(plain, 75)
+    assert shape(q) == (32, 4, 1) and q["grid_y"] == 1 and q["grid_x"] > 0
+    for K in (8, 16, 32, 64, 128, 512):
+        assert pc.pcsr_query_launch(plain, K) == pc.pcsr_query_kernel(plain, K)
+    pc.pcsr_set_kernel_params(plain, 8, 1, 2)                # a shape asked for is the shape launched
+    assert shape(pc.pcsr_query_kernel(plain, 75)) == (8, 1, 2)
+    plain.close()
+    p = pc.pcsr_select(pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx), 75)
+    p.flags |= HOST
+    h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, p)
+    assert shape(pc.pcsr_query_launch(h, 75)) == (p.lanes_per_row, p.vec, p.rep)
+    q = pc.pcsr_query_kernel(h, 75)
+    assert q["vec"] == 4 and q["lanes_per_row"] * 4 * q["rep"] * q["grid_y"] >= 75
+    h.close()
