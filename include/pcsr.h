@@ -93,8 +93,9 @@ enum {
  *                    0 = auto.  Values above 1 need S = 0, items_per_group <
  *                    lanes_per_row, no work item longer than 1024 vectors and
  *                    V*vec*rep*items_per_group <= 32.
- *   flags   PCSR_FLAG_* bits.  Bits 16-20 are pcsr_select's: launch shapes with loads wider
- *           than vec (K need not be a multiple of them; C is the same).
+ *   flags   PCSR_FLAG_* bits.  Bits 16-27 are pcsr_select's: a launch shape with loads wider
+ *           than vec (K need not be a multiple of them; C is the same) for exactly the
+ *           lanes_per_row, vec and rep it returned with them; ignored with any other.
  */
 typedef struct {
     int32_t V;

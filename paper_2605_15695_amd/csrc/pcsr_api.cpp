@@ -21,12 +21,31 @@ constexpr uint32_t kMagic = 0x50435352u; // "PCSR"
 
 // Bits of pcsr_params_t.flags in which pcsr_select passes a shape to launch in place of the one in
 // lanes_per_row, vec and rep (see resolve_launch): 4 (kWidePair: 2) floats per load, one (kWideTwice:
-// two) loads per lane, lanes per row 4 << (code - 1) for codes 1 to 5.  Cleared by
-// pcsr_set_kernel_params.
+// two) loads per lane, lanes per row 4 << (code - 1) for codes 1 to 5; above them the shape that it
+// stands in for (stands_for), without which the bits say nothing.  Cleared by pcsr_set_kernel_params.
 constexpr int kWideShift = 16;
 constexpr int32_t kWideShape = 7 << kWideShift;
 constexpr int32_t kWidePair = 8 << kWideShift;
 constexpr int32_t kWideTwice = 16 << kWideShift;
+constexpr int kWideForShift = 21;
+constexpr int32_t kWideFor = 127 << kWideForShift;
+constexpr int32_t kWideBits = kWideShape | kWidePair | kWideTwice | kWideFor;
+
+int32_t stands_for(int lanes, int vec, int rep)
+{
+    auto bits = [](int x) { return x > 0 ? 31 - __builtin_clz((unsigned)x) : 0; };
+    return (bits(lanes) | bits(vec) << 3 | bits(rep) << 5) << kWideForShift;
+}
+
+// The flags of a handle: a caller who changed the shape that pcsr_select returned gets that shape,
+// and bits that pcsr_select never sets do nothing.
+int32_t checked_flags(const pcsr_params_t &p)
+{
+    const int code = (p.flags & kWideShape) >> kWideShift;
+    const bool own = p.lanes_per_row && p.vec && p.rep;
+    if (own && code >= 1 && code <= 5 && (p.flags & kWideFor) == stands_for(p.lanes_per_row, p.vec, p.rep)) return p.flags;
+    return p.flags & ~kWideBits;
+}
 
 // The narrowest tile of 16-byte loads that covers a row of K columns.
 void wide_shape(int32_t K, int cap, int *lanes, int *rep)
@@ -352,7 +371,7 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     h->rep = prm.rep;
     h->waves = prm.waves_per_wg;
     h->ipg = prm.items_per_group;
-    h->flags = prm.flags;
+    h->flags = checked_flags(prm);
     if (rc == PCSR_OK && prm.col_window) {
         pcsr::DeviceWindows w;
         rc = pcsr::windows_device(db.M, n_cols, prm.col_window, db.rowptr, db.colidx, &w, &herr);
@@ -485,7 +504,7 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
         h->rep = prm.rep;
         h->waves = prm.waves_per_wg;
         h->ipg = prm.items_per_group;
-        h->flags = prm.flags;
+        h->flags = checked_flags(prm);
         drop_poor_windows(h);
         h->n_split = (int64_t)h->host.split_panels.size();
         h->n_split_items = h->host.split_slot.empty() ? 0 : h->host.split_slot.back();
@@ -848,7 +867,7 @@ int pcsr_set_kernel_params(pcsr_handle_t h, int32_t lanes_per_row, int32_t vec, 
     h->waves = waves_per_wg;
     h->ipg = items_per_group;
     constexpr int32_t kLaunchFlags = PCSR_FLAG_NO_XCD_REMAP | PCSR_FLAG_ATOMIC_SPLIT;
-    h->flags = (h->flags & ~(kLaunchFlags | kWideShape | kWidePair | kWideTwice)) | (flags & kLaunchFlags);
+    h->flags = (h->flags & ~(kLaunchFlags | kWideBits)) | (flags & kLaunchFlags);
     return PCSR_OK;
 }
 
@@ -1093,7 +1112,7 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     if (wide) {
         int code = 1;
         while (4 << code >> 1 < wide) ++code;
-        p.flags |= code << kWideShift | (pair ? kWidePair : 0) | (wide_rep == 2 ? kWideTwice : 0);
+        p.flags |= code << kWideShift | (pair ? kWidePair : 0) | (wide_rep == 2 ? kWideTwice : 0) | stands_for(lpr, vec, rep);
     }
     // Workgroup size: four wavefronts, two for short rows and for paired long rows (eight
     // were 4-7 % slower than four on every unsplit input of the later validation sets).

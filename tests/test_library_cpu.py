@@ -420,3 +420,28 @@ def test_query_kernel_reports_what_is_launched():
     q = pc.pcsr_query_kernel(h, 75)
     assert q["vec"] == 4 and q["lanes_per_row"] * 4 * q["rep"] * q["grid_y"] >= 75
     h.close()
+
+
+def test_shapes_passed_in_flags_hold_only_for_the_shape_they_came_with():
+    g = synth.workload("sbm_shuffled", "small")
+    args = (g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals)
+    f = pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx)
+    launched = lambda p, K: (lambda q: (q["lanes_per_row"], q["vec"], q["rep"]))(  # noqa: E731
+        pc.pcsr_query_kernel(pc.pcsr_build(*args, p), K))
+    carried = 0
+    for K in (18, 27, 33, 40, 75, 100, 130, 300, 515):
+        p = pc.pcsr_select(f, K)
+        p.flags |= HOST
+        own, taken = (p.lanes_per_row, p.vec, p.rep), launched(p, K)
+        carried += taken != own
+        for field, value in (("lanes_per_row", 8), ("vec", 2 if p.vec == 1 and K % 2 == 0 else 1), ("rep", 4)):
+            changed = type(p).from_buffer_copy(p)
+            if getattr(changed, field) == value:
+                continue
+            setattr(changed, field, value)
+            assert launched(changed, K) == (changed.lanes_per_row, changed.vec, changed.rep), (K, field)
+    assert carried >= 5
+    # bits that pcsr_select never sets, among them codes for 128 and 256 lanes per row
+    for bits in [code << 16 for code in range(8)] + [0xfff << 16, 24 << 16, 0xfe0 << 16]:
+        p = pc.make_params(lanes_per_row=8, vec=1, rep=1, flags=HOST | bits)
+        assert launched(p, 33) == (8, 1, 1), hex(bits)
