@@ -220,18 +220,27 @@ def _spmm_checked(h: Handle, B, C, K: int, stream):
 
 
 def _first_spmm(h, B, C, K, stream):
-    """Loads the module that makes the call without ctypes; from then on it is the one that is asked."""
+    """Loads the module that makes the call without ctypes; from then on it is the one that is asked.
+    It is built against one torch: where it is missing or made for another, ctypes makes the call."""
     global _spmm
     import importlib.util
+    import warnings
 
-    import torch  # noqa: F401  (its libraries have to be there)
+    import torch  # its libraries have to be there
 
-    spec = importlib.util.spec_from_file_location("_pcsr_py", PY_PATH)
-    mod = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(mod)
     lib = _lib()
-    mod.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.pcsr_spmm, lib.pcsr_release_cached_if_low)))
-    _spmm = mod.spmm
+    try:
+        spec = importlib.util.spec_from_file_location("_pcsr_py", PY_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        if mod.torch_version != str(torch.__version__):
+            raise ImportError(f"built for torch {mod.torch_version}")
+        mod.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.pcsr_spmm, lib.pcsr_release_cached_if_low)))
+        _spmm = mod.spmm
+    except (ImportError, OSError) as e:
+        warnings.warn(f"{PY_PATH.name} does not load ({e}); pcsr_spmm's calls go through ctypes and cost a few "
+                      "microseconds more: build it with `python -m paper_2605_15695_amd.build`", RuntimeWarning)
+        _spmm = _spmm_checked
     return _spmm(h, B, C, K, stream)
 
 

@@ -44,7 +44,7 @@ def _build_py() -> pathlib.Path:
     libdir = pathlib.Path(torch.__file__).parent / "lib"
     inc = [p for p in cpp_extension.include_paths()] + [sysconfig.get_paths()["include"], "/opt/rocm/include"]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           "-D__HIP_PLATFORM_AMD__=1", *[f"-isystem{p}" for p in inc], str(CSRC / "pcsr_py.cpp"), "-o", str(PY_LIB),
+           "-D__HIP_PLATFORM_AMD__=1", f'-DPCSR_TORCH_VERSION="{torch.__version__}"', *[f"-isystem{p}" for p in inc], str(CSRC / "pcsr_py.cpp"), "-o", str(PY_LIB),
            f"-L{libdir}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-Wl,-rpath,{libdir}"]
     r = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
     if r.returncode != 0:

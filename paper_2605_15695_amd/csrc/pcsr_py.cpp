@@ -119,5 +119,7 @@ PyMODINIT_FUNC PyInit__pcsr_py(void)
     s_rows = PyUnicode_InternFromString("n_rows");
     s_cols = PyUnicode_InternFromString("n_cols");
     s_stream = PyUnicode_InternFromString("cuda_stream");
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", PCSR_TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
 }

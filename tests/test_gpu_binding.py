@@ -68,3 +68,30 @@ def test_memory_kept_for_reuse_goes_back():
         assert asked
     finally:
         mod.init(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.pcsr_spmm, lib.pcsr_release_cached_if_low)))
+
+
+# missing, no library at all, and made for another torch: the call goes through ctypes, with the same checks
+@pytest.mark.parametrize("what", ["missing", "broken", "other torch"])
+def test_products_without_the_call_module(what, tmp_path, monkeypatch):
+    from paper_2605_15695_amd import binding
+
+    g = synth.workload("poisson", "small")
+    K = 24
+    h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals)
+    B = torch.from_numpy(synth.dense_operand(g.n_cols, K, "normal", 3)).cuda()
+    ref, C = torch.empty(g.n_rows, K, device="cuda"), torch.empty(g.n_rows, K, device="cuda")
+    pc.pcsr_spmm(h, B, ref, K)
+    monkeypatch.setattr(binding, "_spmm", binding._first_spmm)
+    if what == "other torch":
+        monkeypatch.setattr(torch, "__version__", "1.0.0+rocm0")
+    else:
+        path = tmp_path / "_pcsr_py.so"
+        if what == "broken":
+            path.write_bytes(b"no library")
+        monkeypatch.setattr(binding, "PY_PATH", path)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        pc.pcsr_spmm(h, B, C, K)
+    pc.pcsr_spmm(h, B, C, K, torch.cuda.current_stream())
+    assert torch.equal(C, ref)
+    with pytest.raises(ValueError):
+        pc.pcsr_spmm(h, B[:-1], C, K)
