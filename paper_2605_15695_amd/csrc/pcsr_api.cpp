@@ -993,9 +993,8 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     const double d_hat = f[5], d_max = f[6], cv = f[7], pr2 = f[15];
 
     // Balancing (Section 3.2) pays when a few rows dwarf the average one.  On MI355X the
-    // recorded sweeps then prefer short items (32 vectors with slices of up to 64 columns, 64
-    // vectors with 128-column slices) run in column order: the items of
-    // the long rows, sorted by first column, make the wavefronts of an XCD gather the same B
+    // recorded sweeps then prefer short items (32 or 64 vectors, see SG below) run in column
+    // order: the items of the long rows, sorted by first column, make the wavefronts of an XCD gather the same B
     // rows at about the same time (R-MAT scale 22: 1.6-2x over the best index-order tuple at
     // every width from 16 to 512; neutral on small or uniform inputs).
     const bool skewed = cv > 1.5 && d_max > 256.0;

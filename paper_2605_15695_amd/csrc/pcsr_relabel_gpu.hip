@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(kThreads) split_pairs_kernel(int64_t nnz, cons
 
 // ---- label propagation
 
-// deterministic tie-break priority of a label in a given round (as on the host)
+// deterministic tie-break priority of a label in a given round (as on the host: lowbias32)
 __device__ __forceinline__ uint32_t mix(uint32_t x, uint32_t round)
 {
     x ^= round * 0x9E3779B9u;

@@ -36,7 +36,8 @@ template <class F> void par_for(int64_t n, F &&fn)
     for (auto &t : th) t.join();
 }
 
-// deterministic tie-break priority of a label in a given round
+// deterministic tie-break priority of a label in a given round: Chris Wellons's 32-bit integer mixer
+// "lowbias32" (hash prospector, public domain) of the label, which the round shifts first
 inline uint32_t mix(uint32_t x, uint32_t round)
 {
     x ^= round * 0x9E3779B9u;

@@ -39,11 +39,25 @@ def records_table(recs, top: int = 6) -> None:
             print()
 
 
+def rules_table(recs) -> None:
+    """Per input and width: the pick's time and, as factors of it, what its rules decided against."""
+    rs = [r for r in recs if r.get("kind") == "rule"]
+    names = [n for n in ("own shape", "row tile", "64-column slices", "half wavefront", "items of 32", "items of 64")
+             if any(r["what"] == n for r in rs)]
+    shape = lambda r: f'{r["lanes_per_row"]}x{r["vec"]}x{r["rep"]}'  # noqa: E731
+    print("| input | K | pick: V, S, SG / launched shape | ms | " + " | ".join(names) + " |")
+    print("|---" * (4 + len(names)) + "|")
+    for w, K in sorted({(r["workload"], r["K"]) for r in rs}):
+        by = {r["what"]: r for r in rs if r["workload"] == w and r["K"] == K}
+        p = by["pick"]
+        cells = [f'{by[n]["ms"] / p["ms"]:.2f} ({shape(by[n])})' if n in by else "" for n in names]
+        print(f'| {w} | {K} | {p["V"]}, {p["S"]}, {p["SG"]} / {shape(p)} | {p["ms"]:.4f} | ' + " | ".join(cells) + " |")
+
+
 def main(argv=None) -> int:
     paths = list(argv or sys.argv[1:])
-    records = "--records" in paths
-    if records:
-        paths.remove("--records")
+    records, rules = "--records" in paths, "--rules" in paths
+    paths = [p for p in paths if p not in ("--records", "--rules")]
     top = 6
     for p in list(paths):
         if p.startswith("--top="):
@@ -53,8 +67,8 @@ def main(argv=None) -> int:
     for p in paths:
         with open(p) as f:
             recs += [json.loads(line) for line in f if line.strip()]
-    if records:
-        records_table(recs, top)
+    if records or rules:
+        records_table(recs, top) if records else rules_table(recs)
         return 0
     keys = sorted({(r["workload"], r["K"]) for r in recs if r.get("kind") == "pcsr"})
     print("| workload | K | n | nnz | best tuple (V,S,SG[c = column-ordered] / lanes,vec,rep,waves,items) | ms | GFLOP/s | roofline frac "

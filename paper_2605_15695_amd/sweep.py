@@ -94,6 +94,37 @@ def _baseline_lib():
     return lib
 
 
+STAND_IN = ~0xffff  # flag bits in which pcsr_select passes a shape that stands in for its own
+
+
+def rule_alternatives(p, K: int):
+    """(name, parameters, launch shape or None) of what pcsr_select's rules on item size and on shapes
+    that stand in for others decide between: its pick first."""
+    def changed(**fields):
+        q = type(p).from_buffer_copy(p)
+        for k, v in fields.items():
+            setattr(q, k, v)
+        return q
+
+    out = [("pick", p, None)]
+    if p.flags & STAND_IN:
+        out.append(("own shape", changed(flags=p.flags & ~STAND_IN), None))
+    if K % 4 == 0 and K > 32 and not p.col_window:
+        lanes = 4
+        while lanes * 4 < K and lanes < 64:
+            lanes *= 2
+        out.append(("row tile", p, (lanes, 4, 2 if lanes == 64 and K > 256 else 1)))
+    if K % 4 == 0 and K > 64 and not p.col_window:
+        out.append(("64-column slices", p, (16, 4, 1)))
+    if K % 2 == 0 and 32 < K <= 64 and not p.col_window:
+        out.append(("half wavefront", p, (32, 2, 1)))
+    if p.S:
+        for SG in (32, 64):
+            if SG != p.SG:
+                out.append((f"items of {SG}", changed(SG=SG), None))
+    return out
+
+
 def main(argv=None) -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--workload", required=True)
@@ -110,6 +141,8 @@ def main(argv=None) -> int:
     ap.add_argument("--reorder", nargs="?", const="cluster", default=None, choices=["cluster", "degree"],
                     help="sweep the matrix after one of the library's relabellings: 'cluster' (pcsr_reorder) "
                          "or 'degree' (pcsr_reorder_by_degree)")
+    ap.add_argument("--rules", action="store_true",
+                    help="time only pcsr_select's pick and what its rules decided against (rule_alternatives)")
     ap.add_argument("--shapes", default=None,
                     help="explicit launch shapes instead of the enumeration: comma list of "
                          "lanes:vec:rep:waves:items_per_group")
@@ -146,6 +179,30 @@ def main(argv=None) -> int:
     feats = pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx)
     emit({"kind": "graph", "workload": args.workload, "size": args.size, "n": g.n_rows, "nnz": g.nnz,
           "features": dict(zip(pc.FEATURE_NAMES, map(float, feats)))})
+
+    if args.rules:
+        for K in Ks:
+            Bd = torch.from_numpy(synth.dense_operand(g.n_cols, K, spec["B"], 2)).cuda()
+            Cd = torch.empty((g.n_rows, K), dtype=torch.float32, device="cuda")
+            sel = pc.pcsr_select(feats, K)
+            built = []
+            for name, p, shape in rule_alternatives(sel, K):
+                h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, p)
+                if shape:
+                    pc.pcsr_set_kernel_params(h, *shape, p.waves_per_wg)
+                built.append(dict(name=name, p=p, h=h))
+            for _ in range(3):                    # in turn, the best of three medians
+                for b in built:
+                    med, _ = time_launches(lambda: pc.pcsr_spmm(b["h"], Bd, Cd, K, stream), stream, torch, args.warmup,
+                                           args.reps)
+                    b["ms"] = min(med, b.get("ms", med))
+            for name, p, h, med in (b.values() for b in built):
+                emit(dict(kind="rule", workload=args.workload, K=K, n=g.n_rows, nnz=g.nnz, what=name, V=p.V, S=p.S,
+                          SG=p.SG, ms=med, **pc.pcsr_query_kernel(h, K)))
+                print(f"[rules] {args.workload} K={K} {name}: {med:.4f} ms", flush=True)
+                h.close()
+        out.close()
+        return 0
 
     if args.formats == "all":
         sg_eq3 = 0

@@ -40,3 +40,32 @@ def test_report_table_and_geomean(tmp_path):
     text = out.getvalue()
     assert "| w | 64 | 100 | 1000 | 1,0,0 / 16,4,1,4,1 | 0.5000 |" in text and text.count("| - |") == 1
     assert "4.00x" in text and "**4.00x**" in text and "80.0 %" in text
+
+
+def test_rule_alternatives_and_their_table():
+    import numpy as np
+
+    import paper_2605_15695_amd as pc
+    import synth
+
+    g = synth.workload("sbm_shuffled", "small")
+    f = np.array(pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx))
+    recs = []
+    for K, names in ((75, {"pick", "own shape", "items of 64"}),
+                     (96, {"pick", "row tile", "64-column slices", "items of 64"}),
+                     (100, {"pick", "own shape", "row tile", "64-column slices", "items of 64"})):
+        alt = sweep.rule_alternatives(pc.pcsr_select(f, K), K)
+        assert alt[0][0] == "pick" and {a[0] for a in alt} == names
+        for i, (name, p, shape) in enumerate(alt):
+            p = type(p).from_buffer_copy(p)
+            p.flags |= pc.PCSR_FLAG_HOST_ONLY
+            h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, p)
+            if shape:
+                pc.pcsr_set_kernel_params(h, *shape, p.waves_per_wg)
+            q = pc.pcsr_query_kernel(h, K)
+            assert not shape or (q["lanes_per_row"], q["vec"], q["rep"]) == shape
+            recs.append(dict(kind="rule", workload="w", K=K, what=name, V=p.V, S=p.S, SG=p.SG, ms=1.0 + i, **q))
+    out = io.StringIO()
+    with redirect_stdout(out):
+        report.rules_table(recs)
+    assert "| w | 100 | 1, 1, 32 / 32x4x1 | 1.0000 | 2.00 (" in out.getvalue()
