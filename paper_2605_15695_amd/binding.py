@@ -149,6 +149,12 @@ class Handle:
         if self.raw:
             pcsr_free(self)
 
+    def __copy__(self):
+        return self  # a copied model shares its matrix: two owners would free it twice
+
+    def __deepcopy__(self, memo):
+        return self
+
     def __del__(self):
         try:
             self.close()

@@ -148,3 +148,13 @@ def test_tensors_of_another_type_are_not(op):
     assert gnn._params(layer) is None
     layer.bias = torch.zeros(64)
     assert gnn._params(layer) is not None
+
+
+def test_a_copied_model_shares_its_matrix(op):
+    import copy
+
+    model = gnn.make_model("gcn", op, 16, 32, 16, 2)
+    other = copy.deepcopy(model)
+    assert other[0].op.fwd is op.fwd and copy.copy(op.fwd) is op.fwd
+    del other
+    assert op.fwd.raw and pc.pcsr_query_launch(op.fwd, 16)["vec"] > 0
