@@ -7,7 +7,7 @@ feature extraction are one-off per graph (the paper amortises them over training
 iterations) and are reported in separate fields, outside the timed region.
 
 Prints ONE JSON line: metric/value (GFLOP/s = 2*nnz*K / t), the HBM roofline of the SpMM
-kernel measured live with device events, and the CPU oracle timed on this box's cores.
+kernel measured live with device events, and the CPU oracle timed on this machine's cores.
 """
 from __future__ import annotations
 
@@ -27,17 +27,17 @@ HBM_PEAK_GBS = 8000.0
 # that was profiled, the item size SG and the item schedule: a run that launches another
 # instance, or the same instance over another PCSR layout, reports null.
 PROFILED_TRAFFIC = {
-    ("poisson-full", 32, "spmm_kernel<1, false, 8, 4, 1>", 0, "index"): 3503085,
-    ("road-full", 128, "spmm_kernel<2, false, 32, 4, 1>", 0, "index"): 2121481179,
-    ("rmat20-full", 64, "spmm_kernel<1, true, 16, 4, 1>", 32, "column"): 2050060690,
-    ("sbm-full", 256, "spmm_window_kernel<1, 16, 4, 1>", 0, "index"): 2230701604,
-    ("sbm_shuffled-full", 256, "spmm_kernel<1, true, 16, 4, 1>", 32, "column"): 10018994230,
-    ("rmat22-full", 16, "spmm_kernel<1, true, 16, 1, 1>", 32, "column"): 6858113234,
-    ("rmat22-full", 32, "spmm_kernel<1, true, 8, 4, 1>", 32, "column"): 9844466834,
-    ("rmat22-full", 64, "spmm_kernel<1, true, 16, 4, 1>", 32, "column"): 17907130971,
-    ("rmat22-full", 128, "spmm_kernel<1, true, 16, 4, 1>", 32, "column"): 36026222500,
-    ("rmat22-full", 256, "spmm_kernel<1, true, 16, 4, 1>", 32, "column"): 75014491538,
-    ("rmat22-full", 512, "spmm_kernel<1, true, 16, 4, 1>", 32, "column"): 155942151679,
+    ("poisson-full", 32, "spmm_kernel<1, false, 8, 4, 1, false>", 0, "index"): 3519439,
+    ("road-full", 128, "spmm_kernel<2, false, 32, 4, 1, false>", 0, "index"): 2121935073,
+    ("rmat20-full", 64, "spmm_kernel<1, true, 16, 4, 1, false>", 64, "column"): 2174585919,
+    ("sbm-full", 256, "spmm_window_kernel<1, 16, 4, 1>", 0, "index"): 2242603406,
+    ("sbm_shuffled-full", 256, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 10006511034,
+    ("rmat22-full", 16, "spmm_kernel<1, true, 16, 1, 1, false>", 64, "column"): 7068248499,
+    ("rmat22-full", 32, "spmm_kernel<1, true, 8, 4, 1, false>", 64, "column"): 9984136412,
+    ("rmat22-full", 64, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 17939440492,
+    ("rmat22-full", 128, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 36093605165,
+    ("rmat22-full", 256, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 75169090801,
+    ("rmat22-full", 512, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 156284305416,
 }
 
 
@@ -48,7 +48,7 @@ def kernel_instance(V: int, S: int, launch: dict) -> str:
         return f"spmm_window_kernel<{V}, {shape}>"
     if launch["items_per_group"] > 1:
         return f"spmm_batched_kernel<{V}, {shape}, {launch['items_per_group']}>"
-    return f"spmm_kernel<{V}, {'true' if S else 'false'}, {shape}>"
+    return f"spmm_kernel<{V}, {'true' if S else 'false'}, {shape}, false>"  # false: no elementwise tail
 
 
 def algorithmic_bytes(g, K: int) -> int:
@@ -199,7 +199,7 @@ def main() -> int:
     bytes_min = algorithmic_bytes(g, K)
     achieved = bytes_min / (kern_ms * 1e-3) / 1e9
 
-    # What a plain copy reaches on this box (1 GiB read + 1 GiB written per launch): the
+    # What a plain copy reaches on this machine (1 GiB read + 1 GiB written per launch): the
     # practical ceiling beside the 8 TB/s of the data sheet.
     stream_gbs = None
     if not args.no_stream:
@@ -278,7 +278,7 @@ def main() -> int:
                                "us_per_spmm_eager_events": kern_ms * 1e3,
                                "us_per_step_eager_wall": ms_per_step * 1e3}
 
-    # ---- the CPU oracle as it stands, on this machine's host cores, on a bounded sample of rows
+    # ---- the CPU oracle as it stands, on this machine's cores, on a bounded sample of rows
     rows = ref = bound = None
     if not args.no_check or not args.no_cpu_baseline:
         import oracle
