@@ -189,6 +189,7 @@ template <int T> __device__ __forceinline__ void mask_rows(f4 (&x)[T], const f4 
 // fragments of rows past the end: what a sum over rows must not count (a product of zeros plus the bias)
 template <int T> __device__ __forceinline__ void clear_past_end(int lane, long rows, f4 (&x)[T])
 {
+    if (rows >= 16) return; // all but the last of a wavefront's groups
     if ((lane & 15) >= rows) {
 #pragma unroll
         for (int t = 0; t < T; ++t) x[t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -608,8 +609,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
 #pragma unroll
             for (int t = 0; t < AT; ++t) da[t] = zero;
             multiply<MT, AT>(w1, lane, g1, da);
-            if (p.H) {
-                clear_past_end<AT>(lane, rows, da);
+            if (p.H && (lane & 15) < rows) {
 #pragma unroll
                 for (int t = 0; t < AT; ++t)
                     dot += (da[t][0] * aa[t][0] + da[t][1] * aa[t][1]) + (da[t][2] * aa[t][2] + da[t][3] * aa[t][3]);
