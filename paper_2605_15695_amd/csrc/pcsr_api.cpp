@@ -1037,11 +1037,15 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     const bool long_uniform = !skewed && !windowed && !wide_scatter && d_hat >= 40.0 && scattered;
     const bool long_uniform_wide = long_uniform && K >= 64;
     p.S = (skewed || long_uniform_wide) ? 1 : 0;
-    // Items of 32 vectors where uniform rows are split, of 64 for power-law inputs (against 32:
-    // eight R-MAT graphs of 2^18 to 2^22 nodes 0-15 % faster at widths of 16 to 300, and half
-    // the workspace), except where a B of 1 GB or more is gathered in an order that has its hubs
-    // side by side (natural R-MAT ids, scale 22 from K = 64: items of 32 are 5-7 % faster).
-    const bool short_items = !skewed || (!scattered && K >= 64 && n * (double)K * 4.0 >= 1e9);
+    // Items of 32 vectors where uniform rows are split (of 64: 2-31 % slower on rows of 70 and more,
+    // 9-12 % faster on uniform rows of 48).  Of 64 for power-law
+    // inputs, at half the workspace, with two exceptions.  Small products end with few items in
+    // flight: R-MAT graphs of under 15 M nonzeros (2^16 to 2^20 nodes, 8 to 60 per row) are 0-13 % faster
+    // with items of 32 up to K = 48, on a par or slower from K = 64; from 15 M on items of 64 are 1-15 % faster from
+    // K = 32 (below, between 7 % slower and 7 % faster).  And where a B of 1 GB or more is gathered in
+    // an order that has its hubs side by side (natural R-MAT ids, scale 22 from K = 64) items of 32
+    // are 1-5 % faster.
+    const bool short_items = !skewed || (f[2] < 15e6 && K <= 48) || (!scattered && K >= 64 && n * (double)K * 4.0 >= 1e9);
     p.SG = p.S ? (short_items ? 32 : 64) : 0;
     p.omega = 64;
     if (p.S) p.flags |= PCSR_FLAG_COLUMN_ORDER;
@@ -1098,7 +1102,7 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     bool pair = false;
     const bool dword = wide_scatter || (lpr == 16 && vec == 1 && rep == 2 && K <= 32);
     if (K > 64 && K % 32 != 0 && (p.S || scattered || K % 4 != 0)) {
-        // one tile for the whole row instead of slices of 64: 1.1-1.3x
+        // one tile for the whole row instead of slices of 64: 1.06-1.36x (0.96x on rows of 96, K = 300)
         wide_shape(K, 64, &wide, &wide_rep);
     } else if (K > 32 && K <= 64 && K % 32 != 0 && !p.S && scattered && d_hat >= 8.0) {
         wide = 32; // half a wavefront per scattered row: 4-7 %

@@ -85,7 +85,7 @@ __device__ int32_t densest_sorted(CutShared &sh, unsigned long long &best, const
 // decides where the next begins); everything inside a step is spread over its threads.  The
 // window of a whole block comes from a histogram of the 3 * win columns around the probe
 // window where that one already holds more than half of the block's vectors: a better window
-// then has to overlap it.  250,000 rows of 48: 0.6 ms, where the host builder sorted every
+// then has to overlap it.  250,000 rows of 48: 0.86 ms, where the host builder sorted every
 // block's columns, 50 ms on 16 threads.
 __global__ void __launch_bounds__(kCutThreads) window_cut_kernel(CutArgs a)
 {

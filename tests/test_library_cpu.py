@@ -445,3 +445,23 @@ def test_shapes_passed_in_flags_hold_only_for_the_shape_they_came_with():
     for bits in [code << 16 for code in range(8)] + [0xfff << 16, 24 << 16, 0xfe0 << 16]:
         p = pc.make_params(lanes_per_row=8, vec=1, rep=1, flags=HOST | bits)
         assert launched(p, 33) == (8, 1, 1), hex(bits)
+
+
+def _features(name, **fields):
+    g = synth.workload(name, "small")
+    f = np.array(pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx), dtype=np.float64)
+    for k, v in fields.items():
+        f[pc.FEATURE_NAMES.index(k)] = v
+    return f
+
+
+def test_item_size_of_power_law_inputs():
+    near = 16 / (1 << 19)                                    # permuted ids
+    small = _features("rmat20", n=1 << 19, nnz=14e6, d_max=30_000, CV=8.0, near_512=near)
+    large = _features("rmat20", n=1 << 20, nnz=16e6, d_max=30_000, CV=8.0, near_512=near)
+    for K in (8, 16, 32, 48):
+        assert pc.pcsr_select(small, K).SG == 32 and pc.pcsr_select(large, K).SG == 64
+    for K in (64, 75, 100, 300):
+        assert pc.pcsr_select(small, K).SG == 64 and pc.pcsr_select(large, K).SG == 64
+    natural = _features("rmat22", n=1 << 22, nnz=128e6, d_max=100_000, CV=10.0, near_512=0.1)
+    assert pc.pcsr_select(natural, 32).SG == 64 and pc.pcsr_select(natural, 64).SG == 32
