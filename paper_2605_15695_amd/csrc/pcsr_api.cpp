@@ -1104,8 +1104,10 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     if (K > 64 && K % 32 != 0 && (p.S || scattered || K % 4 != 0)) {
         // one tile for the whole row instead of slices of 64: 1.06-1.36x (0.96x on rows of 96, K = 300)
         wide_shape(K, 64, &wide, &wide_rep);
-    } else if (K > 32 && K <= 64 && K % 32 != 0 && !p.S && scattered && d_hat >= 8.0) {
-        wide = 32; // half a wavefront per scattered row: 4-7 %
+    } else if (K > 32 && K <= 64 && K % 32 != 0 && !p.S && scattered && d_hat >= 8.0 && b_bytes > 24.0 * 1048576.0) {
+        // half a wavefront per scattered row: 0-6 % where B is gathered from the memory side, 20-30 %
+        // slower where L2 holds it (uniform columns, 9 to 200 per row; on a par at 20-25 MB)
+        wide = 32;
     } else if (K % 4 != 0 && K > 16 && !dword) {
         // 16 lanes of two floats for K up to 32 unless rows are short: 8 % on clique inputs
         pair = K <= 32 && !p.S && d_hat >= 8.0;

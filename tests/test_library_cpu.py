@@ -465,3 +465,12 @@ def test_item_size_of_power_law_inputs():
         assert pc.pcsr_select(small, K).SG == 64 and pc.pcsr_select(large, K).SG == 64
     natural = _features("rmat22", n=1 << 22, nnz=128e6, d_max=100_000, CV=10.0, near_512=0.1)
     assert pc.pcsr_select(natural, 32).SG == 64 and pc.pcsr_select(natural, 64).SG == 32
+
+
+def test_half_a_wavefront_per_row_only_where_b_is_gathered_from_memory():
+    launched = lambda n, d, K: (lambda p: p.flags >> 16 & 7)(pc.pcsr_select(  # noqa: E731
+        _features("poisson", n=n, nnz=n * d, d=d, d_hat=d, d_max=2 * d, CV=0.2, PR_2=0.49, near_512=1000 / n), K))
+    for K in (40, 52, 60):
+        assert launched(30_000, 20.0, K) == launched(90_000, 72.0, K) == 0     # the shape asked for: 16 lanes of 4
+        assert launched(250_000, 20.0, K) == launched(500_000, 9.0, K) == 4    # 32 lanes
+    assert launched(30_000, 20.0, 33) == 3 and launched(250_000, 20.0, 33) == 4
