@@ -36,9 +36,8 @@ struct LinearArgs {
 // 64), read as one ds_read_b128 per 4 matrix instructions.
 // Bound by memory: 2,000,000 x 64 -> 64 is 1.02 GB and 16.4 GFLOP (104 us at the fp32 matrix
 // peak).  The next rows are requested before this step's products, and no more workgroups are
-// started than run at once: with 2048 of them, 32 rows a step and no such request the same
-// took 264 us, 367 us with a mask; now 220 and 285 (piece_kernel), where the vendor GEMM takes
-// 290-320 us and leaves bias, ReLU and mask to passes of 150-230 us each.
+// started than run at once.  With bias and ReLU 238 us (piece_kernel, 4.3 TB/s), with a mask to read as
+// well 291 (5.3 TB/s), where torch's product, bias and ReLU take 488.
 // VEC: widths that are multiples of 4, arrays 16-byte aligned.  RED: dot and/or column sums.
 constexpr int blocks_per_cu(int kt, int nt) { return kt + nt <= 8 ? 3 : 2; } // registers and LDS allow no more
 // piece_kernel: eight wavefronts to one copy of the weights where two copies do not fit
@@ -93,8 +92,8 @@ template <int NT> __device__ __forceinline__ void start_from(const f4 *bias, int
 // Sixteen rows of exactly 16 T floats are one piece of memory.  It is read and written with the lanes
 // side by side, T times 1 KB (lane l, step u: 16-byte word 64 u + l of the piece), and turned
 // to and from the fragments through an LDS patch of the wavefront's own.  Straight from the fragments
-// every access would touch 16 rows, 64 bytes of each: 2,000,000 rows x 64 took 222 us so to write, 3.7 TB/s for
-// 16 -> 64 columns in all; through the patch 5.6.
+// every access would touch 16 rows, 64 bytes of each: 16 -> 64 columns ran at 3.7 TB/s so, and run at
+// 5.3 through the patch (2,000,000 rows, 121 us).
 constexpr int patch_ld(int t) { return 16 * t + 4; } // floats per row
 constexpr int patch_floats(int t) { return 16 * patch_ld(t); }
 
@@ -404,7 +403,7 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), piece_waves(KT, NT) 
 
 // Two layers in one pass: Z = relu(X W1^T + b1), Y = Z W2^T + b2 (relu).  Exact widths: a = 16 KT,
 // both layers 16 MT outputs.  Z is stored for the backward pass and not read back: 2,000,000 x 64
-// -> 64 -> 64 takes 367 us where two piece_kernel passes take 464.
+// -> 64 -> 64 takes 350 us where two piece_kernel passes take 403.
 struct MlpArgs {
     long n;
     int relu;
@@ -456,9 +455,10 @@ template <int KT, int MT> __global__ void __launch_bounds__(64 * kWaves, 3) mlp_
 // turned in an LDS patch of the wavefront's own: written as they are held, read T consecutive
 // columns of one row per lane, which feeds T tiles (tile t holds the columns T*i + t, as in
 // wgrad_kernel).  G, Z, A and H are read once and G1 never leaves the registers: 2.6 GB for
-// 2,000,000 x 64 (TWO) where the separate kernels move 5.6 GB, 679 us where they take 977; what
-// bounds it is the matrix rate (65.5 GFLOP, 428 us) with two wavefronts to a SIMD, all that the
-// accumulators leave room for.  Without TWO 326 us for 496.
+// 2,000,000 x 64 (TWO) where the separate kernels move 5.6 GB, 680-700 us where they take 977 (counted in
+// a training step: 2.8 GB, matrix cores busy for 66 %); what bounds it is the matrix rate (65.5 GFLOP,
+// 428 us) with two wavefronts to a SIMD, all that the accumulators leave room for.  Without TWO,
+// masked and with column sums, 365-415 us for 511; without these 325.
 struct BackArgs {
     long n;
     int masked;
@@ -646,8 +646,8 @@ struct WgradArgs {
 // 16 rows per wavefront and step, the next step's rows being loaded meanwhile; wider weights
 // are cut into such squares by grid.y / grid.z.  Rows are dealt to about 2000 wavefronts,
 // each leaves one partial dW, summed by sum_partials_kernel in a fixed order.
-// 2,000,000 rows, 64 x 64: 197 us (5.2 TB/s of G and X) + 16 us for the sums; the vendor GEMM,
-// which splits this shape over too few workgroups, took 2900 us.
+// 2,000,000 rows, 64 x 64: 207 us with the sums (5.0 TB/s of G and X); torch's product of the
+// transposed G takes 2900.
 template <int TG, bool VG, int TX, bool VX>
 __global__ void __launch_bounds__(64 * kWaves) wgrad_kernel(WgradArgs p)
 {
