@@ -322,6 +322,23 @@ struct UploadedCsr {
     }
 };
 
+// A handle in the making, given up if the scope is left without keep().
+struct Draft {
+    pcsr_handle_t h;
+    pcsr_handle_t keep()
+    {
+        pcsr_handle_t made = h;
+        h = nullptr;
+        return made;
+    }
+    ~Draft()
+    {
+        if (!h) return;
+        release_device(h);
+        delete h;
+    }
+};
+
 // Returned by handle_from_device where the windows have to be chosen on the host.
 constexpr int kWindowsOnHost = 1;
 
@@ -476,26 +493,18 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
             return PCSR_E_BAD_CSR;
         }
 
-        pcsr_handle_s *h = new pcsr_handle_s();
+        Draft draft{new pcsr_handle_s()};
+        pcsr_handle_s *const h = draft.h;
         rc = pcsr::build_host(n_rows, n_cols, nnz, rowptr, colidx, vals, prm.V, prm.S, prm.SG,
                               prm.omega, &h->host);
-        if (rc != PCSR_OK) {
-            delete h;
-            return rc;
-        }
+        if (rc != PCSR_OK) return rc;
         if (column_order) {
             rc = pcsr::schedule_by_column(&h->host);
-            if (rc != PCSR_OK) {
-                delete h;
-                return rc;
-            }
+            if (rc != PCSR_OK) return rc;
         }
         if (prm.col_window) {
             rc = pcsr::choose_windows(&h->host, prm.col_window);
-            if (rc != PCSR_OK) {
-                delete h;
-                return rc;
-            }
+            if (rc != PCSR_OK) return rc;
         }
         h->n_win_blocks = (int64_t)h->host.win_start.size();
         h->host_only = host_only;
@@ -509,10 +518,7 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
         h->n_split = (int64_t)h->host.split_panels.size();
         h->n_split_items = h->host.split_slot.empty() ? 0 : h->host.split_slot.back();
         if (!host_only) {
-            if (!hip_ok(hipGetDevice(&h->device))) {
-                delete h;
-                return PCSR_E_HIP;
-            }
+            if (!hip_ok(hipGetDevice(&h->device))) return PCSR_E_HIP;
             rc = upload(h->host.rowptr, &h->d_rowptr);
             if (rc == PCSR_OK) rc = upload(h->host.colidx, &h->d_colidx);
             if (rc == PCSR_OK) rc = upload(h->host.val, &h->d_val);
@@ -526,11 +532,7 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
             if (rc == PCSR_OK && h->host.win_cols) rc = upload(h->host.win_ptr, &h->d_win_ptr);
             if (rc == PCSR_OK && h->host.win_cols) rc = upload(h->host.win_lo, &h->d_win_lo);
             if (rc == PCSR_OK && h->host.win_cols) rc = upload(h->host.win_hi, &h->d_win_hi);
-            if (rc != PCSR_OK) {
-                release_device(h);
-                delete h;
-                return rc;
-            }
+            if (rc != PCSR_OK) return rc;
             // the device copies are the product; drop the host staging arrays
             std::vector<int32_t>().swap(h->host.rowptr);
             std::vector<int32_t>().swap(h->host.colidx);
@@ -545,7 +547,7 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
             std::vector<int32_t>().swap(h->host.win_lo);
             std::vector<int32_t>().swap(h->host.win_hi);
         }
-        *out = h;
+        *out = draft.keep();
         return PCSR_OK;
     } catch (const std::bad_alloc &) {
         return PCSR_E_OOM;

@@ -7,33 +7,12 @@
 #include <cmath>
 #include <cstring>
 #include <new>
-#include <thread>
 
 #include "../../include/pcsr.h"
+#include "pcsr_parallel.h"
 
 namespace pcsr {
 namespace {
-
-template <class F> void parallel_for(int64_t n, int64_t grain, F &&fn)
-{
-    if (n <= 0) return;
-    unsigned hw = std::thread::hardware_concurrency();
-    int64_t nt = std::max<int64_t>(1, std::min<int64_t>(hw ? hw : 4, 16));
-    nt = std::min<int64_t>(nt, (n + grain - 1) / grain);
-    if (nt <= 1) {
-        fn(int64_t(0), n);
-        return;
-    }
-    std::vector<std::thread> th;
-    th.reserve(nt);
-    int64_t per = (n + nt - 1) / nt;
-    for (int64_t t = 0; t < nt; ++t) {
-        int64_t lo = t * per, hi = std::min(n, lo + per);
-        if (lo >= hi) break;
-        th.emplace_back([=, &fn] { fn(lo, hi); });
-    }
-    for (auto &t : th) t.join();
-}
 
 inline int64_t ceildiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

@@ -1251,7 +1251,10 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
                 e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
                 if (e != hipSuccess) return e;
-                raised.insert(key);
+                try {
+                    raised.insert(key);
+                } catch (...) { // no memory to note it: raised again next time
+                }
             }
         }
         hipLaunchKernelGGL(fn, dim3(ls.grid_x, ls.grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);

@@ -53,8 +53,8 @@ void drop(Cache &c, std::multimap<size_t, Idle>::iterator it)
 
 } // namespace
 
-hipError_t pool_alloc(void **out, size_t bytes)
-{
+hipError_t pool_alloc(void **out, size_t bytes) noexcept
+try {
     *out = nullptr;
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -67,8 +67,8 @@ hipError_t pool_alloc(void **out, size_t bytes)
     // a block up to a quarter (or 1 MB) larger than asked for
     auto it = c.idle.lower_bound(need);
     if (it != c.idle.end() && it->first <= need + std::max(need / 4, size_t(1) << 20)) {
+        P.live[it->second.p] = {it->first, dev};
         *out = it->second.p;
-        P.live[*out] = {it->first, dev};
         c.bytes -= it->first;
         c.idle.erase(it);
         return hipSuccess;
@@ -85,9 +85,13 @@ hipError_t pool_alloc(void **out, size_t bytes)
     }
     P.live[*out] = {need, dev};
     return hipSuccess;
+} catch (...) { // no host memory for the books
+    if (*out) (void)hipFree(*out);
+    *out = nullptr;
+    return hipErrorOutOfMemory;
 }
 
-void pool_free(void *p)
+void pool_free(void *p) noexcept
 {
     if (!p) return;
     Pool &P = pool();
@@ -104,7 +108,12 @@ void pool_free(void *p)
         (void)hipFree(p);
         return;
     }
-    c.idle.insert({bytes, {p, P.clock}});
+    try {
+        c.idle.insert({bytes, {p, P.clock}});
+    } catch (...) {
+        (void)hipFree(p);
+        return;
+    }
     c.bytes += bytes;
     for (auto i = c.idle.begin(); i != c.idle.end();) {
         auto at = i++;
@@ -129,7 +138,7 @@ bool pool_quiesce(int device)
     return e == hipSuccess;
 }
 
-void pool_release(void *p)
+void pool_release(void *p) noexcept
 {
     if (!p) return;
     Pool &P = pool();
@@ -212,8 +221,13 @@ hipError_t staged(char *dst, const char *src, size_t bytes, bool to_host)
     if (bytes < kStagedBytes || hipGetDevice(&dev) != hipSuccess) return hipMemcpy(dst, src, bytes, kind);
     std::unique_lock<std::mutex> lock(lanes().mu, std::try_to_lock);
     if (!lock.owns_lock()) return hipMemcpy(dst, src, bytes, kind);
-    std::vector<Lane> &ls = lanes_of(dev);
-    if (ls.empty()) return hipMemcpy(dst, src, bytes, kind);
+    Lane *ls = nullptr;
+    try {
+        std::vector<Lane> &v = lanes_of(dev);
+        if (!v.empty()) ls = v.data();
+    } catch (...) {
+    }
+    if (!ls) return hipMemcpy(dst, src, bytes, kind);
     // like hipMemcpy, after everything enqueued on the null stream
     hipError_t e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return e;

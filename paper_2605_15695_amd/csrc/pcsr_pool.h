@@ -19,14 +19,14 @@ constexpr uint64_t kPoolIdleAllocs = 1024;
 constexpr size_t kPoolLowMemory = 8;
 
 // On the current device.  Thread safe.  Contents are undefined.
-hipError_t pool_alloc(void **p, size_t bytes);
+hipError_t pool_alloc(void **p, size_t bytes) noexcept;
 // No work that uses the block may be running or enqueued: the caller has waited for the device
 // (pool_quiesce) or for the stream that used it.  nullptr is a no-op.
-void pool_free(void *p);
+void pool_free(void *p) noexcept;
 // Waits for a device, as hipFree would.  false: that failed (a stream capture in progress, say)
 // and the blocks have to go back through pool_release instead.
 bool pool_quiesce(int device);
-void pool_release(void *p); // hipFree, past the cache
+void pool_release(void *p) noexcept; // hipFree, past the cache
 // Gives the blocks kept for the current device back to the driver; bytes: how many that were.
 hipError_t pool_give_back(size_t *bytes);
 

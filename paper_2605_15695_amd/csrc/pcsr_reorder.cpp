@@ -9,32 +9,15 @@
 #include <cstring>
 #include <new>
 #include <numeric>
-#include <thread>
 #include <vector>
 
 #include "../../include/pcsr.h"
+#include "pcsr_parallel.h"
 #include "pcsr_relabel_gpu.h"
 
 namespace {
 
-template <class F> void par_for(int64_t n, F &&fn)
-{
-    unsigned hw = std::thread::hardware_concurrency();
-    int64_t nt = std::max<int64_t>(1, std::min<int64_t>(hw ? hw : 4, 16));
-    if (n < 4096) nt = 1;
-    if (nt == 1) {
-        fn(int64_t(0), n);
-        return;
-    }
-    std::vector<std::thread> th;
-    int64_t per = (n + nt - 1) / nt;
-    for (int64_t t = 0; t < nt; ++t) {
-        int64_t lo = t * per, hi = std::min(n, lo + per);
-        if (lo >= hi) break;
-        th.emplace_back([=, &fn] { fn(lo, hi); });
-    }
-    for (auto &t : th) t.join();
-}
+template <class F> void par_for(int64_t n, F &&fn) { pcsr::parallel_for(n, n < 4096 ? 4096 : 1, fn); }
 
 // deterministic tie-break priority of a label in a given round: Chris Wellons's 32-bit integer mixer
 // "lowbias32" (hash prospector, public domain) of the label, which the round shifts first

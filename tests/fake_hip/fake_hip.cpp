@@ -1,0 +1,91 @@
+// A device of host memory for the CPU tests of the library's host code: the HIP calls it makes, with
+// allocations that can be made to fail, on the device and (operator new) on the host.  Kernels do not run
+// (hipLaunchKernel does nothing), so only what happens before the first result of one is read can be
+// tested.
+#include <cstdlib>
+#include <cstring>
+#include <new>
+
+static int new_calls, bad_new; // the bad_new-th from now on throws, counted from 1; 0: none
+void *operator new(std::size_t bytes)
+{
+    if (bad_new && ++new_calls == bad_new) throw std::bad_alloc();
+    if (void *p = std::malloc(bytes ? bytes : 1)) return p;
+    throw std::bad_alloc();
+}
+void *operator new(std::size_t bytes, const std::nothrow_t &) noexcept
+{
+    if (bad_new && ++new_calls == bad_new) return nullptr;
+    return std::malloc(bytes ? bytes : 1);
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, std::size_t) noexcept { std::free(p); }
+
+extern "C" {
+enum { kOk = 0, kOutOfMemory = 2 };
+static int calls, first_bad, last_bad; // allocations [first_bad, last_bad] fail, counted from 1
+static std::size_t refuse_from, refuse_to; // and those of refuse_from to refuse_to bytes
+static long live;
+
+void fake_hip_fail(int first, int last)
+{
+    calls = 0;
+    first_bad = first;
+    last_bad = last;
+}
+void fake_hip_refuse(std::size_t from, std::size_t to)
+{
+    refuse_from = from;
+    refuse_to = to;
+}
+void fake_new_fail(int at)
+{
+    new_calls = 0;
+    bad_new = at;
+}
+int fake_new_calls(void) { return new_calls; }
+int fake_hip_allocations(void) { return calls; }
+long fake_hip_live(void) { return live; }
+
+static std::size_t free_bytes = 100, total_bytes = 100;
+static int capturing;
+void fake_hip_memory(std::size_t free_now, std::size_t total) { free_bytes = free_now; total_bytes = total; }
+void fake_hip_capture(int on) { capturing = on; }
+
+int hipMemGetInfo(std::size_t *f, std::size_t *t) { *f = free_bytes; *t = total_bytes; return kOk; }
+int hipStreamIsCapturing(void *s, int *status) { (void)s; *status = capturing; return kOk; }
+int hipThreadExchangeStreamCaptureMode(int *mode) { (void)mode; return kOk; }
+int hipGetDeviceCount(int *n) { *n = 1; return kOk; }
+int hipGetDevice(int *d) { *d = 0; return kOk; }
+int hipSetDevice(int d) { (void)d; return kOk; }
+int hipGetLastError(void) { return kOk; }
+int hipDeviceSynchronize(void) { return kOk; }
+int hipStreamSynchronize(void *s) { (void)s; return kOk; }
+int hipMalloc(void **p, std::size_t bytes)
+{
+    ++calls;
+    if (calls >= first_bad && calls <= last_bad) return kOutOfMemory;
+    if (refuse_to && bytes >= refuse_from && bytes <= refuse_to) return kOutOfMemory;
+    *p = std::calloc(1, bytes ? bytes : 1);
+    if (!*p) return kOutOfMemory;
+    ++live;
+    return kOk;
+}
+int hipFree(void *p)
+{
+    if (p) --live;
+    std::free(p);
+    return kOk;
+}
+int hipHostMalloc(void **p, std::size_t bytes, unsigned flags) { (void)p; (void)bytes; (void)flags; return kOutOfMemory; }
+int hipMemcpy(void *dst, const void *src, std::size_t bytes, int kind) { (void)kind; std::memcpy(dst, src, bytes); return kOk; }
+int hipMemcpyAsync(void *dst, const void *src, std::size_t bytes, int kind, void *s)
+{
+    (void)kind;
+    (void)s;
+    std::memcpy(dst, src, bytes);
+    return kOk;
+}
+int hipMemsetAsync(void *dst, int v, std::size_t bytes, void *s) { (void)s; std::memset(dst, v, bytes); return kOk; }
+int hipLaunchKernel(const void *fn, ...) { (void)fn; return kOk; }
+}

@@ -42,7 +42,7 @@ host_t = pc.pcsr_build(n, n, *t, pc.make_params(flags=pc.PCSR_FLAG_HOST_ONLY, **
 @pytest.fixture(scope="module")
 def fake(tmp_path_factory):
     lib = tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so"
-    subprocess.run(["gcc", "-O1", "-fPIC", "-shared", "-o", str(lib), str(ROOT / "tests/fake_hip/fake_hip.c")], check=True)
+    subprocess.run(["g++", "-O1", "-fPIC", "-shared", "-o", str(lib), str(ROOT / "tests/fake_hip/fake_hip.cpp")], check=True)
     return lib
 
 
@@ -130,4 +130,41 @@ fake.fake_hip_capture(1)
 assert lib.pcsr_release_cached_if_low(None) == 0 and fake.fake_hip_live() > 0
 fake.fake_hip_capture(0)
 assert lib.pcsr_release_cached_if_low(None) > 0 and fake.fake_hip_live() == 0
+""")
+
+
+def test_no_exception_leaves_the_library(fake):
+    """Each of the library's own allocations on the host fails once: a call returns a code, and nothing leaks."""
+    _run(fake, """
+lib = binding._lib()
+small = slice(0, 1000 * deg)
+arrays = rowptr[:1001], colidx[small], vals[small]
+ptrs = [a.ctypes.data for a in arrays]
+
+
+def call(params):                                          # without Python's own allocations in between
+    p, h = pc.make_params(**params), ctypes.c_void_p()
+    def run(bad):
+        fake.fake_new_fail(bad)
+        rc = lib.pcsr_build(1000, n, 1000 * deg, *ptrs, ctypes.byref(p), ctypes.byref(h))
+        if rc == 0:
+            rc = lib.pcsr_reserve_workspace(h, 64)
+            free = lib.pcsr_free(h)
+            assert free == 0
+        lib.pcsr_release_cached(None)
+        used = fake.fake_new_calls()
+        fake.fake_new_fail(0)
+        return rc, used
+    return run
+
+
+for params in (dict(V=1), dict(V=2, S=1, SG=4), dict(V=1, S=1, SG=4, flags=pc.PCSR_FLAG_COLUMN_ORDER)):
+    run = call(params)
+    assert run(0)[0] == 0
+    rc, used = run(1 << 30)
+    assert rc == 0 and used >= 8 and fake.fake_hip_live() == 0
+    for bad in range(1, used + 1):
+        rc, _ = run(bad)
+        assert rc in (0, binding.PCSR_E_OOM), (params, bad, rc)
+        assert fake.fake_hip_live() == 0, (params, bad)
 """)
