@@ -225,10 +225,13 @@ def _spmm_checked(h: Handle, B, C, K: int, stream):
     return _lib().pcsr_spmm(h.raw, p_b, p_c, K, getattr(stream, "cuda_stream", stream))
 
 
-def _first_spmm(h, B, C, K, stream):
-    """Loads the module that makes the call without ctypes; from then on it is the one that is asked.
-    It is built against one torch: where it is missing or made for another, ctypes makes the call."""
+def load_call_module() -> None:
+    """Loads the module that makes pcsr_spmm's calls without ctypes and tells torch's allocator about the
+    memory the library keeps; from then on it is the one that is asked.  It is built against one torch:
+    where it is missing or made for another, ctypes makes the calls."""
     global _spmm
+    if _spmm is not _first_spmm:
+        return
     import importlib.util
     import warnings
 
@@ -247,6 +250,10 @@ def _first_spmm(h, B, C, K, stream):
         warnings.warn(f"{PY_PATH.name} does not load ({e}); pcsr_spmm's calls go through ctypes and cost a few "
                       "microseconds more: build it with `python -m paper_2605_15695_amd.build`", RuntimeWarning)
         _spmm = _spmm_checked
+
+
+def _first_spmm(h, B, C, K, stream):
+    load_call_module()
     return _spmm(h, B, C, K, stream)
 
 

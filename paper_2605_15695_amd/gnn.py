@@ -38,6 +38,7 @@ class PcsrOperator:
                 self.bwd = pc.pcsr_build(self.n_cols, self.n_rows,
                                          *pc.pcsr_transpose_csr(self.n_rows, self.n_cols, rowptr, colidx, vals), params)
             return
+        pc.load_call_module()
         # one upload; check, features, selection, transpose and PCSR generation on the GPU
         self.fwd, self.bwd = pc.pcsr_operator_build(self.n_rows, self.n_cols, rowptr, colidx, vals, params, K_hint,
                                                     not symmetric)

@@ -81,7 +81,7 @@ def test_products_without_the_call_module(what, tmp_path, monkeypatch):
     B = torch.from_numpy(synth.dense_operand(g.n_cols, K, "normal", 3)).cuda()
     ref, C = torch.empty(g.n_rows, K, device="cuda"), torch.empty(g.n_rows, K, device="cuda")
     pc.pcsr_spmm(h, B, ref, K)
-    monkeypatch.setattr(binding, "_spmm", binding._first_spmm)
+    monkeypatch.setattr(binding, "_spmm", binding._first_spmm)  # as before the first call
     if what == "other torch":
         monkeypatch.setattr(torch, "__version__", "1.0.0+rocm0")
     else:
@@ -95,3 +95,12 @@ def test_products_without_the_call_module(what, tmp_path, monkeypatch):
     assert torch.equal(C, ref)
     with pytest.raises(ValueError):
         pc.pcsr_spmm(h, B[:-1], C, K)
+
+
+def test_an_operator_loads_the_call_module(monkeypatch):
+    from paper_2605_15695_amd import binding, gnn
+
+    g = synth.workload("poisson", "small")
+    monkeypatch.setattr(binding, "_spmm", binding._first_spmm)
+    gnn.PcsrOperator(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, K_hint=32)
+    assert binding._spmm not in (binding._first_spmm, binding._spmm_checked)
