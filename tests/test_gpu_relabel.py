@@ -130,6 +130,48 @@ def test_windows_are_those_of_the_host_builder(name, V, wc):
     host.close(), dev.close(), plain.close()
 
 
+def _window_case(name, wc, rng):
+    """Rows whose densest window is where the search for it can go wrong."""
+    n, m = 600, 40 * wc
+    if name == "wide":                      # more stretches of wc columns than the search counts in LDS
+        m = 6200 * wc + 7
+    rows = []
+    for i in range(n):
+        g = i // 150                        # blocks of 150 rows
+        if name == "ties":                  # the same columns in four places, two of them side by side
+            base = rng.choice(wc // 2, 10, replace=False)
+            c = np.concatenate([base + k * wc for k in (3 * g, 3 * g + 1, 20, 33)])
+        elif name == "edges":               # runs of wc - 1, wc and wc + 1 columns across a multiple of wc, both ends
+            first = (0, 5 * wc - 1, 9 * wc + 1 - wc // 2, m - wc - 1)[g]
+            c = np.concatenate([first + rng.choice(wc - 1, 30, replace=False), [first, first + wc + (g % 3) - 2]])
+        elif name == "scattered":           # no window stands out
+            c = rng.choice(m, 20, replace=False)
+        else:
+            c = np.concatenate([(m // 5) * (g + 1) + rng.choice(wc, 40, replace=False), rng.choice(m, 5)])
+        rows.append(np.unique(c))
+    rp = np.concatenate([[0], np.cumsum([len(c) for c in rows])]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    return n, m, rp, ci, rng.standard_normal(ci.shape[0]).astype(np.float32)
+
+
+@pytest.mark.parametrize("wc", [256, 2048])
+@pytest.mark.parametrize("name", ["ties", "edges", "scattered", "wide"])
+def test_window_search_at_its_edges(name, wc):
+    n, m, rp, ci, va = _window_case(name, wc, np.random.default_rng(wc))
+    host = pc.pcsr_build(n, m, rp, ci, va, pc.make_params(col_window=wc, flags=pc.PCSR_FLAG_HOST_ONLY))
+    dev = pc.pcsr_build(n, m, *(torch.from_numpy(x).cuda() for x in (rp, ci, va)), pc.make_params(col_window=wc))
+    assert pc.pcsr_window_stats(host) == pc.pcsr_window_stats(dev)
+    B = torch.from_numpy(synth.dense_operand(m, 8, "normal", 2)).cuda()
+    C = torch.full((n, 8), float("nan"), device="cuda")
+    pc.pcsr_set_kernel_params(dev, 4, 2, 1, 16)
+    pc.pcsr_spmm(dev, B, C, 8)
+    plain = pc.pcsr_build(n, m, rp, ci, va, pc.make_params())
+    D = torch.empty_like(C)
+    pc.pcsr_spmm(plain, B, D, 8)
+    assert float((C - D).norm() / D.norm()) < 1e-6
+    host.close(), dev.close(), plain.close()
+
+
 def test_operator_takes_device_arrays_and_refuses_bad_ones():
     from paper_2605_15695_amd.gnn import PcsrOperator
 
