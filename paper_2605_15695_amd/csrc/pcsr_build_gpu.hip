@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -19,6 +20,7 @@
 #include "../../include/pcsr.h"
 #include "pcsr_build_gpu.h"
 #include "pcsr_gpu_util.h"
+#include "pcsr_sort_gpu.h"
 
 namespace pcsr {
 namespace {
@@ -27,61 +29,46 @@ namespace {
 
 // What the host learns from one pass over the row pointer and one over the columns.
 struct Checked {
-    int bad;               // a row pointer or column out of range
-    int first, last;       // rowptr[0], rowptr[n_rows]
-    int longest;           // longest row
-    int descents;          // t > 0 with colidx[t] <= colidx[t - 1]
-    int start_descents;    // ... where t starts a row
-    int nonempty, pad;
+    int bad;         // a row pointer or column out of range, a column that does not ascend
+    int first, last; // rowptr[0], rowptr[n_rows]
+    int longest;     // longest row
+    int nonempty, pad[3];
 };
 
-// Columns in range; positions where the column does not ascend.  Such a position is fine where
-// a row starts and nowhere else, so the CSR is sound if as many are found here as among the
-// row starts (validate_rows_kernel): no thread has to know which row its element is in.
-__global__ void __launch_bounds__(kThreads) validate_cols_kernel(int64_t n_cols, int64_t nnz, const int32_t *colidx,
-                                                                 Checked *out)
+// Monotone row pointer inside [0, nnz], row statistics, the row at the start of each slice.  Few, large
+// workgroups: each ends in atomics to one line of memory (1,048,576 rows: 9 us, 27 with 1024 workgroups of 256).
+constexpr int kRowThreads = 1024, kRowBlocks = 128;
+__global__ void __launch_bounds__(kRowThreads) check_rows_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
+                                                                 int32_t *slices, Checked *out)
 {
-    int desc = 0, bad = 0;
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < nnz; t += stride) {
-        const int32_t c = colidx[t];
-        bad |= c < 0 || c >= n_cols;
-        desc += t > 0 && c <= colidx[t - 1];
-    }
-    typedef hipcub::BlockReduce<int, kThreads> Reduce;
-    __shared__ typename Reduce::TempStorage t1, t2;
-    const int d = Reduce(t1).Sum(desc);
-    const int b = Reduce(t2).Sum(bad);
-    if (threadIdx.x == 0) {
-        if (d) atomicAdd(&out->descents, d);
-        if (b) out->bad = 1;
-    }
-}
-
-// Monotone row pointer inside [0, nnz], descents at row starts (with_cols), row statistics.
-__global__ void __launch_bounds__(kThreads) validate_rows_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
-                                                                 const int32_t *colidx, int with_cols, Checked *out)
-{
-    int desc = 0, bad = 0, longest = 0, nonempty = 0;
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_rows; i += stride) {
-        const int64_t s = rowptr[i], e = rowptr[i + 1];
-        if (s < 0 || s > e || e > nnz) {
-            bad = 1;
-        } else if (e > s) {
-            ++nonempty;
-            longest = (int)(e - s) > longest ? (int)(e - s) : longest;
-            if (with_cols && s > 0) desc += colidx[s] <= colidx[s - 1];
+    int bad = 0, longest = 0, nonempty = 0;
+    constexpr int N = 4; // rows in flight
+    const int64_t stride = (int64_t)gridDim.x * kRowThreads;
+    for (int64_t i0 = (int64_t)blockIdx.x * kRowThreads + threadIdx.x; i0 < n_rows; i0 += N * stride) {
+        int32_t s[N], e[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int64_t i = i0 + k * stride;
+            s[k] = i < n_rows ? rowptr[i] : 0;
+            e[k] = i < n_rows ? rowptr[i + 1] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if (s[k] < 0 || s[k] > e[k] || e[k] > nnz) {
+                bad = 1;
+            } else if (e[k] > s[k]) {
+                ++nonempty;
+                longest = e[k] - s[k] > longest ? e[k] - s[k] : longest;
+                note_slices(slices, i0 + k * stride, s[k], e[k]);
+            }
         }
     }
-    typedef hipcub::BlockReduce<int, kThreads> Reduce;
-    __shared__ typename Reduce::TempStorage t1, t2, t3, t4;
-    const int d = Reduce(t1).Sum(desc);
+    typedef hipcub::BlockReduce<int, kRowThreads> Reduce;
+    __shared__ typename Reduce::TempStorage t2, t3, t4;
     const int b = Reduce(t2).Sum(bad);
     const int n = Reduce(t3).Sum(nonempty);
     const int l = Reduce(t4).Reduce(longest, hipcub::Max());
     if (threadIdx.x == 0) {
-        if (d) atomicAdd(&out->start_descents, d);
         if (b) out->bad = 1;
         if (n) atomicAdd(&out->nonempty, n);
         if (l) atomicMax(&out->longest, l);
@@ -90,6 +77,55 @@ __global__ void __launch_bounds__(kThreads) validate_rows_kernel(int64_t n_rows,
             out->last = rowptr[n_rows];
         }
     }
+}
+
+// Columns in range and ascending inside every row (check); the arrays copied (pcol, with V = 1).  One pass
+// for both: 16 M nonzeros 49 us (5.2 TB/s), where a check that met every row start on its own took 77 and the copies 45.
+__global__ void __launch_bounds__(kThreads) check_copy_kernel(int64_t n_rows, int64_t n_cols, int64_t nnz,
+                                                              const int32_t *rowptr, const int32_t *colidx,
+                                                              const float *vals, const int32_t *slices, int check,
+                                                              int32_t *pcol, float *pval, Checked *out)
+{
+    __shared__ int32_t starts_lds[kSlice];
+    __shared__ int32_t last_col[kThreads + 1];
+    const int tid = threadIdx.x;
+    const int64_t t0 = (int64_t)blockIdx.x * kSlice, t1 = t0 + kSlice < nnz ? t0 + kSlice : nnz;
+    const int64_t t = t0 + tid * kPerThread;
+    int4u c = {0, 0, 0, 0};
+    if (t + kPerThread <= t1) {
+        c = *reinterpret_cast<const int4u *>(colidx + t);
+        if (pcol) {
+            const float4u v = *reinterpret_cast<const float4u *>(vals + t);
+            *reinterpret_cast<int4u *>(pcol + t) = c;
+            *reinterpret_cast<float4u *>(pval + t) = v;
+        }
+    } else {
+        for (int k = 0; k < kPerThread && t + k < t1; ++k) {
+            c[k] = colidx[t + k];
+            if (pcol) {
+                pcol[t + k] = c[k];
+                pval[t + k] = vals[t + k];
+            }
+        }
+    }
+    if (!check) return; // the whole grid
+    last_col[tid + 1] = c[kPerThread - 1];
+    if (tid == 0) last_col[0] = t0 > 0 ? colidx[t0 - 1] : -1;
+    RowStarts rows{starts_lds};
+    rows.find(rowptr, n_rows, slices[blockIdx.x], t0, t1);
+    bool bad = false;
+    int32_t before = last_col[tid];
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) {
+        if (t + k < t1) {
+            bad |= c[k] < 0 || c[k] >= n_cols;
+            if (c[k] <= before && t + k > 0) { // fine where a row starts
+                bad |= !rows.starts_row(rowptr, n_rows, t0, t + k);
+            }
+        }
+        before = c[k];
+    }
+    if (__syncthreads_or(bad) && tid == 0) out->bad = 1;
 }
 
 // number of entries of colidx[b, e) smaller than c
@@ -104,6 +140,23 @@ __device__ __forceinline__ int64_t count_below(const int32_t *colidx, int64_t b,
             hi = mid;
     }
     return lo - b;
+}
+
+// One step of a search for the first of colidx[lo, hi) that is >= key (lo == hi at the end): three probes at a
+// time, since such a chain is bound by its round trips to memory (features of R-MAT scale 20: 77 us for 102 with one).
+__device__ __forceinline__ void narrow(const int32_t *colidx, int64_t key, int32_t &lo, int32_t &hi)
+{
+    const int32_t n = hi - lo;
+    if (n <= 0) return;
+    const int32_t at[3] = {lo + (n >> 2), lo + (n >> 1), hi - 1 - (n >> 2)};
+    const int32_t c[3] = {colidx[at[0]], colidx[at[1]], colidx[at[2]]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        if (c[k] < key)
+            lo = at[k] + 1 > lo ? at[k] + 1 : lo;
+        else
+            hi = at[k] < hi ? at[k] : hi;
+    }
 }
 
 // ---- V = 2.  The vectors of panel p are the sorted union of the columns of rows 2p ("even")
@@ -480,11 +533,12 @@ __global__ void xcd_bounds_kernel(int32_t M, const int32_t *rowptr, int32_t *xb)
     xb[x] = (int32_t)lo;
 }
 
-// ---- Table 3 features on the GPU: one pass over the nonzeros, two over the rows
-constexpr unsigned kFeatBlocks = 512, kNearBlocks = 2048;
+// ---- Table 3 features on the GPU: one pass over the panels of two rows, one over the rows
+constexpr unsigned kPanelBlocks = 512, kDevBlocks = 512;
+constexpr int kPanelThreads = 1024;
 
-struct RowPart { // per workgroup of the first row pass
-    long long n_hat, nonempty2, shared;
+struct RowPart { // per workgroup of the pass over the panels
+    long long n_hat, nonempty2, shared, near;
     double bw_sum, bw_max;
     int d_max, pad;
 };
@@ -500,7 +554,7 @@ struct FeatAcc {
 struct RowPartSum {
     __device__ RowPart operator()(const RowPart &a, const RowPart &b) const
     {
-        return {a.n_hat + b.n_hat, a.nonempty2 + b.nonempty2, a.shared + b.shared, a.bw_sum + b.bw_sum,
+        return {a.n_hat + b.n_hat, a.nonempty2 + b.nonempty2, a.shared + b.shared, a.near + b.near, a.bw_sum + b.bw_sum,
                 a.bw_max > b.bw_max ? a.bw_max : b.bw_max, a.d_max > b.d_max ? a.d_max : b.d_max, 0};
     }
 };
@@ -511,42 +565,128 @@ struct DevPartSum {
     }
 };
 
-// Nonzeros within 512 columns of the diagonal, per workgroup; columns that both rows of a
-// V = 2 panel have, per panel (shared: zeros on entry).
-__global__ void __launch_bounds__(kThreads) features_nonzeros_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
-                                                                     const int32_t *colidx, int32_t *shared,
-                                                                     long long *near_out)
+// Panels that eight lanes would take too long for, in units of 64 nonzeros of the shorter row, and the columns found in
+// both rows of them.
+constexpr int kFarBlocks = 1024;
+constexpr int kMostPanels = 1024; // of a workgroup
+__device__ __forceinline__ bool far_panel(int32_t shorter, int32_t longer) { return shorter > 64 || (shorter > 8 && longer > 256); }
+struct FarList {
+    int32_t n, pad;
+    unsigned long long shared;
+};
+
+// Statistics of the rows and, per panel, how many columns both of its rows have (shared).  Eight lanes take a panel:
+// the nonzeros of its shorter row are looked up in the longer one (whose few lines of memory are in the vector cache
+// by the second step), and four of the lanes find the ends of the two rows' stretches within 512 columns of the
+// diagonal.  What bounds it is the chain of loads per panel, so as many panels as fit are in flight.  With
+// features_far_kernel 56 us for 250,000 rows of 48 and 105 for R-MAT scale 20 (16 M nonzeros), where passes over
+// the nonzeros and over the rows took 100 and 125.
+__global__ void __launch_bounds__(kPanelThreads) features_panels_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
+                                                                        const int32_t *colidx, int32_t *shared, int64_t room,
+                                                                        int2 *units, FarList *far, RowPart *parts)
 {
-    __shared__ RowSlice slice;
-    __shared__ int32_t count[kSliceRows / 2 + 1];
-    long long near = 0;
-    for (int64_t t0 = (int64_t)blockIdx.x * kSlice; t0 < nnz; t0 += (int64_t)gridDim.x * kSlice) {
-        const int64_t t1 = t0 + kSlice < nnz ? t0 + kSlice : nnz;
-        __syncthreads(); // the slice before is done with
-        slice.find(rowptr, n_rows, t0, t1);
-        const int panels = slice.rows / 2 + 1;
-        for (int k = threadIdx.x; k < panels; k += kThreads) count[k] = 0;
-        __syncthreads();
-        for (int64_t t = t0 + threadIdx.x; t < t1; t += kThreads) {
-            const int64_t r = slice.row(rowptr, n_rows, t);
-            const int64_t d = (int64_t)colidx[t] - r;
-            near += d > -512 && d < 512;
-            if (shared_column(rowptr, colidx, r, t)) {
-                if (slice.rows)
-                    atomicAdd(&count[(r >> 1) - (slice.first >> 1)], 1);
-                else
-                    atomicAdd(&shared[r >> 1], 1);
+    constexpr int G = 8;
+    __shared__ int32_t held[kMostPanels];
+    __shared__ int n_held;
+    if (threadIdx.x == 0) n_held = 0;
+    __syncthreads();
+    const int l = threadIdx.x % G;
+    const int64_t P = (n_rows + 1) / 2, step = (int64_t)gridDim.x * (kPanelThreads / G);
+    RowPart a = {0, 0, 0, 0, 0.0, 0.0, 0, 0};
+    for (int64_t p = (int64_t)blockIdx.x * (kPanelThreads / G) + threadIdx.x / G; p < P; p += step) {
+        const int64_t r = 2 * p;
+        const int32_t s = rowptr[r], m = rowptr[r + 1], e = r + 1 < n_rows ? rowptr[r + 2] : m;
+        if (s < 0 || s > m || m > e || e > nnz) continue; // (no CSR)
+        // lanes 0 and 1: first and last column of the even row, 2 and 3: of the odd one
+        const int32_t row0 = l & 2 ? m : s, row1 = l & 2 ? e : m;
+        const int32_t own_col = l < 4 && row1 > row0 ? colidx[l & 1 ? row1 - 1 : row0] : 0;
+        // the shorter row
+        const bool odd = e - m <= m - s;
+        const int32_t own0 = odd ? m : s, own1 = odd ? e : m, in0 = odd ? s : m, in1 = odd ? m : e;
+        const bool near_by = !far_panel(own1 - own0, in1 - in0);
+        int both = 0;
+        int32_t near_lo = row0, near_hi = l < 4 ? row1 : row0; // (lanes 0 to 3, beside the first of the look-ups)
+        const int64_t bound = r + (l >> 1) + (l & 1 ? 512 : -511);
+        for (int32_t t = own0 + l;; t += G) {
+            const bool more = near_by && t < own1;
+            const int32_t c = more ? colidx[t] : 0;
+            int32_t lo = in0, hi = more ? in1 : in0;
+            while (lo < hi || near_lo < near_hi) {
+                narrow(colidx, c, lo, hi);
+                narrow(colidx, bound, near_lo, near_hi);
             }
+            if (!more) break;
+            both += lo < in1 && colidx[lo] == c;
         }
-        __syncthreads();
-        if (slice.rows)
-            for (int k = threadIdx.x; k < panels; k += kThreads)
-                if (count[k]) atomicAdd(&shared[(slice.first >> 1) + k], count[k]);
+        if (!near_by && l == 0) held[atomicAdd(&n_held, 1)] = (int32_t)p; // (the grid leaves it kMostPanels at most)
+#pragma unroll
+        for (int k = 1; k < G; k <<= 1) both += __shfl_xor(both, k);
+        const int32_t other_col = __shfl_xor(own_col, 1), other_lo = __shfl_xor(near_lo, 1);
+        if (l == 0) {
+            shared[p] = both;
+            a.shared += both;
+            a.nonempty2 += e > s;
+        }
+        if ((l == 0 || l == 2) && row1 > row0) {
+            ++a.n_hat;
+            a.d_max = row1 - row0 > a.d_max ? row1 - row0 : a.d_max;
+            const double bw = (double)other_col - (double)own_col;
+            a.bw_sum += bw;
+            a.bw_max = bw > a.bw_max ? bw : a.bw_max;
+            a.near += other_lo - near_lo;
+        }
     }
-    typedef hipcub::BlockReduce<long long, kThreads> Reduce;
+    typedef hipcub::BlockReduce<RowPart, kPanelThreads> Reduce;
     __shared__ typename Reduce::TempStorage tmp;
-    near = Reduce(tmp).Sum(near);
-    if (threadIdx.x == 0) near_out[blockIdx.x] = near;
+    a = Reduce(tmp).Reduce(a, RowPartSum());
+    if (threadIdx.x == 0) parts[blockIdx.x] = a;
+    __syncthreads();
+    // the panels set aside: one atomic for all of them
+    const int n_mine = n_held;
+    if (n_mine == 0) return; // uniform
+    typedef hipcub::BlockScan<int, kPanelThreads> Scan;
+    __shared__ typename Scan::TempStorage scan;
+    __shared__ int base;
+    int n = 0, at, total;
+    if ((int)threadIdx.x < n_mine) {
+        const int64_t r = 2 * (int64_t)held[threadIdx.x];
+        const int32_t s = rowptr[r], m = rowptr[r + 1], e = rowptr[r + 2];
+        n = ((e - m <= m - s ? e - m : m - s) + 63) / 64;
+    }
+    Scan(scan).ExclusiveSum(n, at, total);
+    if (threadIdx.x == 0) base = atomicAdd(&far->n, total);
+    __syncthreads();
+    for (int k = 0; k < n; ++k)
+        if (base + at + k < room) units[base + at + k] = make_int2(held[threadIdx.x], k);
+}
+
+// The listed units, a wavefront each.
+__global__ void __launch_bounds__(kThreads) features_far_kernel(int64_t n_rows, const int32_t *rowptr, const int32_t *colidx,
+                                                                int64_t room, const int2 *units, FarList *far,
+                                                                int32_t *shared)
+{
+    const int64_t n = far->n < room ? far->n : room;
+    const int lane = threadIdx.x & 63;
+    int found = 0;
+    for (int64_t u = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); u < n; u += kFarBlocks * (kThreads / 64)) {
+        const int2 unit = units[u];
+        const int64_t r = 2 * (int64_t)unit.x;
+        const int32_t s = rowptr[r], m = rowptr[r + 1], e = rowptr[r + 2]; // both rows have nonzeros
+        const bool odd = e - m <= m - s;
+        const int32_t own0 = odd ? m : s, own1 = odd ? e : m, in0 = odd ? s : m, in1 = odd ? m : e;
+        const int64_t t = own0 + 64 * (int64_t)unit.y + lane;
+        bool both = false;
+        if (t < own1) {
+            const int32_t c = colidx[t];
+            int32_t lo = in0, hi = in1;
+            while (lo < hi) narrow(colidx, c, lo, hi);
+            both = lo < in1 && colidx[lo] == c;
+        }
+        const int c = __popcll(__ballot(both));
+        if (lane == 0 && c) atomicAdd(&shared[unit.x], c);
+        found += c;
+    }
+    if (lane == 0 && found) atomicAdd(&far->shared, (unsigned long long)found);
 }
 
 __device__ __forceinline__ long panel_len(const int32_t *rowptr, const int32_t *shared, int64_t p, int64_t n_rows)
@@ -555,39 +695,16 @@ __device__ __forceinline__ long panel_len(const int32_t *rowptr, const int32_t *
     return (long)rowptr[end] - rowptr[2 * p] - shared[p];
 }
 
-__global__ void __launch_bounds__(kThreads) features_rows_kernel(int64_t n_rows, const int32_t *rowptr,
-                                                                 const int32_t *colidx, const int32_t *shared,
-                                                                 RowPart *parts)
-{
-    RowPart a = {0, 0, 0, 0.0, 0.0, 0, 0};
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * kThreads) {
-        const int64_t s = rowptr[i], e = rowptr[i + 1];
-        if (e > s) {
-            ++a.n_hat;
-            a.d_max = (int)(e - s) > a.d_max ? (int)(e - s) : a.d_max;
-            const double bw = (double)colidx[e - 1] - (double)colidx[s];
-            a.bw_sum += bw;
-            a.bw_max = bw > a.bw_max ? bw : a.bw_max;
-        }
-        if ((i & 1) == 0) {
-            a.shared += shared[i >> 1];
-            a.nonempty2 += panel_len(rowptr, shared, i >> 1, n_rows) > 0;
-        }
-    }
-    typedef hipcub::BlockReduce<RowPart, kThreads> Reduce;
-    __shared__ typename Reduce::TempStorage tmp;
-    a = Reduce(tmp).Reduce(a, RowPartSum());
-    if (threadIdx.x == 0) parts[blockIdx.x] = a;
-}
-
-// sums of the first row pass, the same in every workgroup that asks (result in thread 0)
-__device__ RowPart sum_row_parts(const RowPart *parts, int n)
+// sums over the panels, the same in every workgroup that asks (result in thread 0)
+__device__ RowPart sum_row_parts(const RowPart *parts, int n, const FarList *far)
 {
     typedef hipcub::BlockReduce<RowPart, kThreads> Reduce;
     __shared__ typename Reduce::TempStorage tmp;
-    RowPart a = {0, 0, 0, 0.0, 0.0, 0, 0};
+    RowPart a = {0, 0, 0, 0, 0.0, 0.0, 0, 0};
     for (int i = threadIdx.x; i < n; i += kThreads) a = RowPartSum()(a, parts[i]);
-    return Reduce(tmp).Reduce(a, RowPartSum());
+    a = Reduce(tmp).Reduce(a, RowPartSum());
+    a.shared += (long long)far->shared;
+    return a;
 }
 
 // Eq. (3)
@@ -599,11 +716,12 @@ __device__ __forceinline__ long eq3_sg(long v, long nonempty, long omega)
 // squared deviations of the degrees and the item counts under Eq. (3)'s SG
 __global__ void __launch_bounds__(kThreads) features_deviation_kernel(int64_t n_rows, int64_t nnz, const int32_t *rowptr,
                                                                       const int32_t *shared, const RowPart *parts,
-                                                                      int n_parts, int32_t omega, DevPart *out)
+                                                                      int n_parts, const FarList *far, int32_t omega,
+                                                                      DevPart *out)
 {
     __shared__ double s_d, s_d_hat;
     __shared__ long s_sg1, s_sg2;
-    const RowPart r = sum_row_parts(parts, n_parts);
+    const RowPart r = sum_row_parts(parts, n_parts, far);
     if (threadIdx.x == 0) {
         s_d = (double)nnz / (double)n_rows;
         s_d_hat = r.n_hat ? (double)nnz / (double)r.n_hat : 0.0;
@@ -632,22 +750,17 @@ __global__ void __launch_bounds__(kThreads) features_deviation_kernel(int64_t n_
 }
 
 __global__ void __launch_bounds__(kThreads) features_final_kernel(int64_t nnz, const RowPart *parts, int n_parts,
-                                                                  const DevPart *devs, int n_devs,
-                                                                  const long long *near_in, int n_near, FeatAcc *out)
+                                                                  const FarList *far, const DevPart *devs, int n_devs,
+                                                                  FeatAcc *out)
 {
-    const RowPart r = sum_row_parts(parts, n_parts);
+    const RowPart r = sum_row_parts(parts, n_parts, far);
     typedef hipcub::BlockReduce<DevPart, kThreads> ReduceD;
-    typedef hipcub::BlockReduce<long long, kThreads> ReduceL;
     __shared__ typename ReduceD::TempStorage t1;
-    __shared__ typename ReduceL::TempStorage t2;
     DevPart d = {0.0, 0.0, 0, 0};
     for (int i = threadIdx.x; i < n_devs; i += kThreads) d = DevPartSum()(d, devs[i]);
     d = ReduceD(t1).Reduce(d, DevPartSum());
-    long long near = 0;
-    for (int i = threadIdx.x; i < n_near; i += kThreads) near += near_in[i];
-    near = ReduceL(t2).Sum(near);
     if (threadIdx.x == 0)
-        *out = {r.n_hat, nnz - r.shared, r.nonempty2, d.M1, d.M2, near, r.bw_sum, r.bw_max, d.ss, d.ss_hat, r.d_max, 0};
+        *out = {r.n_hat, nnz - r.shared, r.nonempty2, d.M1, d.M2, r.near, r.bw_sum, r.bw_max, d.ss, d.ss_hat, r.d_max, 0};
 }
 
 hipError_t exclusive_scan(const int32_t *in, int32_t *out, int64_t n, Scratch &sc)
@@ -661,24 +774,30 @@ hipError_t exclusive_scan(const int32_t *in, int32_t *out, int64_t n, Scratch &s
     return hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, (int)n);
 }
 
+// The check of the CSR, and its columns and values copied to pcol / pval where these are given.
 int check_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
-                 bool validate, Scratch &sc, Checked **d_out, Checked *h, int *hip_err)
+                 const float *d_vals, bool validate, int32_t *pcol, float *pval, Scratch &sc, Checked **d_out, Checked *h,
+                 int *hip_err)
 {
     Checked *d = nullptr;
+    int32_t *slices = nullptr;
+    const int64_t n_slices = (nnz + kSlice - 1) / kSlice;
     HIP_TRY(sc.alloc((void **)&d, sizeof(Checked)));
+    HIP_TRY(sc.alloc((void **)&slices, sizeof(int32_t) * (n_slices + 1)));
     HIP_TRY(hipMemsetAsync(d, 0, sizeof(Checked), nullptr));
-    hipLaunchKernelGGL(validate_rows_kernel, dim3(strided_blocks(n_rows, 1024)), dim3(kThreads), 0, 0, n_rows, nnz,
-                       d_rowptr, d_colidx, validate && nnz > 0 ? 1 : 0, d);
+    const int64_t row_blocks = (n_rows + kRowThreads - 1) / kRowThreads;
+    hipLaunchKernelGGL(check_rows_kernel, dim3((unsigned)(row_blocks < 1 ? 1 : (row_blocks > kRowBlocks ? kRowBlocks : row_blocks))),
+                       dim3(kRowThreads), 0, 0, n_rows, nnz, d_rowptr, slices, d);
     HIP_TRY(hipGetLastError());
-    if (validate && nnz > 0) {
-        hipLaunchKernelGGL(validate_cols_kernel, dim3(strided_blocks(nnz)), dim3(kThreads), 0, 0, n_cols, nnz, d_colidx,
-                           d);
+    if (nnz > 0 && n_rows > 0 && (validate || pcol)) {
+        hipLaunchKernelGGL(check_copy_kernel, dim3((unsigned)n_slices), dim3(kThreads), 0, 0, n_rows, n_cols, nnz, d_rowptr,
+                           d_colidx, d_vals, slices, validate ? 1 : 0, pcol, pval, d);
         HIP_TRY(hipGetLastError());
     }
     HIP_TRY(hipMemcpy(h, d, sizeof(Checked), hipMemcpyDeviceToHost));
     *d_out = d;
     if (h->first != 0 || h->last != nnz) return PCSR_E_BAD_CSR;
-    if (validate && (h->bad || h->descents != h->start_descents)) return PCSR_E_BAD_CSR;
+    if (validate && h->bad) return PCSR_E_BAD_CSR;
     return PCSR_OK;
 }
 
@@ -689,7 +808,7 @@ int validate_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *
 {
     Scratch sc;
     Checked *d = nullptr, h;
-    return check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, true, sc, &d, &h, hip_err);
+    return check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, nullptr, true, nullptr, nullptr, sc, &d, &h, hip_err);
 }
 
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
@@ -701,22 +820,19 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
     Scratch sc;
     const int64_t P = (n_rows + V - 1) / V;
 
-    Checked *d_check = nullptr, check;
-    int rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, validate, sc, &d_check, &check, hip_err);
-    if (rc != PCSR_OK) return rc;
-
     // ---- vectorised blocking
     int32_t *prow = nullptr, *pcol = nullptr;
     const int32_t *panels = d_rowptr; // row pointer of the panels
     float *pval = nullptr;
     int64_t nnz_v = nnz;
-    if (V == 1) {
+    if (V == 1) { // the arrays as they are
         HIP_TRY(sc.alloc((void **)&pcol, sizeof(int32_t) * (nnz + 1)));
         HIP_TRY(sc.alloc((void **)&pval, sizeof(float) * (nnz + 1)));
-        if (nnz) {
-            HIP_TRY(hipMemcpyAsync(pcol, d_colidx, sizeof(int32_t) * nnz, hipMemcpyDeviceToDevice, nullptr));
-            HIP_TRY(hipMemcpyAsync(pval, d_vals, sizeof(float) * nnz, hipMemcpyDeviceToDevice, nullptr));
-        }
+    }
+    Checked *d_check = nullptr, check;
+    int rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, validate, pcol, pval, sc, &d_check, &check, hip_err);
+    if (rc != PCSR_OK) return rc;
+    if (V == 1) {
         if (!S) {
             HIP_TRY(sc.alloc((void **)&prow, sizeof(int32_t) * (P + 1)));
             HIP_TRY(hipMemcpyAsync(prow, d_rowptr, sizeof(int32_t) * (n_rows + 1), hipMemcpyDeviceToDevice, nullptr));
@@ -816,16 +932,12 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
             if (n_long > 0) {
                 // stable: equal first columns stay in item order, as on the host
                 int32_t *key_sorted = nullptr;
-                void *tmp = nullptr;
-                size_t bytes = 0;
-                const int bits = key_bits(n_cols);
                 HIP_TRY(sc.alloc((void **)&key_sorted, sizeof(int32_t) * n_long));
                 HIP_TRY(sc.alloc((void **)&sorted, sizeof(int32_t) * n_long));
-                HIP_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, bytes, o.long_key, key_sorted, o.long_item, sorted,
-                                                           (int)n_long, 0, bits));
-                HIP_TRY(sc.alloc(&tmp, bytes));
-                HIP_TRY(hipcub::DeviceRadixSort::SortPairs(tmp, bytes, o.long_key, key_sorted, o.long_item, sorted,
-                                                           (int)n_long, 0, bits));
+                HIP_TRY(sort_pairs_u32(reinterpret_cast<const uint32_t *>(o.long_key),
+                                       reinterpret_cast<uint32_t *>(key_sorted),
+                                       reinterpret_cast<const uint32_t *>(o.long_item),
+                                       reinterpret_cast<uint32_t *>(sorted), n_long, key_bits(n_cols), sc));
             }
             const int64_t cl = (n_long + kSchedChunk - 1) / kSchedChunk, cs = (n_short + kSchedChunk - 1) / kSchedChunk;
             long long *wsum = nullptr, *wscan = nullptr;
@@ -889,33 +1001,34 @@ int features_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *
     const int64_t P2 = (n_rows + 1) / 2;
     if (n_rows > 0) {
         Scratch sc;
-        const unsigned rb = strided_blocks(n_rows, kFeatBlocks);
-        const int64_t slices = (nnz + kSlice - 1) / kSlice;
-        const unsigned nb = (unsigned)(slices < kNearBlocks ? slices : kNearBlocks);
+        const int64_t room = nnz / 9 + 64; // units there can be at most: of 9 nonzeros or more
+        const int64_t groups = kPanelThreads / 8;
+        const unsigned pb = (unsigned)std::max(std::min<int64_t>((P2 + groups - 1) / groups, kPanelBlocks),
+                                               (P2 + kMostPanels - 1) / kMostPanels);
+        const unsigned db = strided_blocks(n_rows, kDevBlocks);
         int32_t *shared = nullptr;
+        int2 *units = nullptr;
+        FarList *far = nullptr;
         RowPart *rows = nullptr;
         DevPart *devs = nullptr;
-        long long *near = nullptr;
         FeatAcc *acc = nullptr;
         HIP_TRY(sc.alloc((void **)&shared, sizeof(int32_t) * P2));
-        HIP_TRY(sc.alloc((void **)&rows, sizeof(RowPart) * rb));
-        HIP_TRY(sc.alloc((void **)&devs, sizeof(DevPart) * rb));
-        HIP_TRY(sc.alloc((void **)&near, sizeof(long long) * (nb + 1)));
+        HIP_TRY(sc.alloc((void **)&units, sizeof(int2) * room));
+        HIP_TRY(sc.alloc((void **)&far, sizeof(FarList)));
+        HIP_TRY(sc.alloc((void **)&rows, sizeof(RowPart) * pb));
+        HIP_TRY(sc.alloc((void **)&devs, sizeof(DevPart) * db));
         HIP_TRY(sc.alloc((void **)&acc, sizeof(FeatAcc)));
-        HIP_TRY(hipMemsetAsync(shared, 0, sizeof(int32_t) * P2, nullptr));
-        if (nb) {
-            hipLaunchKernelGGL(features_nonzeros_kernel, dim3(nb), dim3(kThreads), 0, 0, n_rows, nnz, d_rowptr, d_colidx,
-                               shared, near);
-            HIP_TRY(hipGetLastError());
-        }
-        hipLaunchKernelGGL(features_rows_kernel, dim3(rb), dim3(kThreads), 0, 0, n_rows, d_rowptr, d_colidx, shared,
-                           rows);
+        HIP_TRY(hipMemsetAsync(far, 0, sizeof(FarList), nullptr));
+        hipLaunchKernelGGL(features_panels_kernel, dim3(pb), dim3(kPanelThreads), 0, 0, n_rows, nnz, d_rowptr, d_colidx, shared,
+                           room, units, far, rows);
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(features_deviation_kernel, dim3(rb), dim3(kThreads), 0, 0, n_rows, nnz, d_rowptr, shared,
-                           rows, (int)rb, omega, devs);
+        hipLaunchKernelGGL(features_far_kernel, dim3(kFarBlocks), dim3(kThreads), 0, 0, n_rows, d_rowptr, d_colidx, room,
+                           units, far, shared);
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(features_final_kernel, dim3(1), dim3(kThreads), 0, 0, nnz, rows, (int)rb, devs, (int)rb,
-                           near, (int)nb, acc);
+        hipLaunchKernelGGL(features_deviation_kernel, dim3(db), dim3(kThreads), 0, 0, n_rows, nnz, d_rowptr, shared, rows,
+                           (int)pb, far, omega, devs);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(features_final_kernel, dim3(1), dim3(kThreads), 0, 0, nnz, rows, (int)pb, far, devs, (int)db, acc);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipMemcpy(&h, acc, sizeof(h), hipMemcpyDeviceToHost));
     }

@@ -105,6 +105,45 @@ struct RowSlice {
     }
 };
 
+// Whether nonzeros start a row, for kSlice consecutive ones, from a table of the row that holds each slice's first one
+// (note_slices): the row starts inside the slice are marked in LDS.  A slice that more rows start in than fit is looked
+// up in memory.  (Row pointers that do not ascend give wrong answers, never an access out of bounds.)
+constexpr int kPerThread = kSlice / kThreads;
+typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+static_assert(kPerThread == 4, "a thread's nonzeros are one 16-byte access");
+
+struct RowStarts {
+    int32_t *starts; // kSlice of LDS: 1 where a row starts
+    bool marked;
+
+    __device__ void find(const int32_t *rowptr, int64_t n_rows, int64_t first_row, int64_t t0, int64_t t1)
+    {
+        const int tid = threadIdx.x;
+        const int64_t first = first_row < 0 ? 0 : (first_row < n_rows ? first_row : n_rows - 1);
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) starts[k * kThreads + tid] = 0;
+        __syncthreads();
+        marked = false;
+        for (int base = 0; base < kSliceRows && !marked; base += kThreads) {
+            const int64_t r = first + base + tid;
+            const int32_t v = r <= n_rows ? rowptr[r] : INT32_MAX;
+            if (v >= t0 && v < t1) starts[v - t0] = 1;
+            marked = !__syncthreads_or(tid == kThreads - 1 && v < t1);
+        }
+    }
+    __device__ bool starts_row(const int32_t *rowptr, int64_t n_rows, int64_t t0, int64_t t) const
+    {
+        return marked ? starts[t - t0] != 0 : rowptr[row_of_nonzero(rowptr, n_rows, t)] == t;
+    }
+};
+
+// For one row of a pass over the row pointer: the slices whose first nonzero it holds.
+__device__ __forceinline__ void note_slices(int32_t *table, int64_t row, int64_t s, int64_t e)
+{
+    for (int64_t k = (s + kSlice - 1) / kSlice; k * kSlice < e; ++k) table[k] = (int32_t)row;
+}
+
 struct Scratch { // gives back everything it still owns on scope exit
     void *p[40] = {};
     int n = 0;

@@ -21,6 +21,8 @@ def _csr(n, lengths, seed):
 
 def _case(name):
     n = 6001
+    if name == "around_the_limits":               # panels of 0, 1, 8, 9, 64 and 300 beside 256 and 257 nonzeros
+        n = 1301
     lengths = np.zeros(n, np.int64)
     if name == "long_rows":                       # several slices of 1024 inside one row
         lengths[[0, 1, 2, 3000, n - 1]] = [5000, 4096, 1, 6001, 2500]
@@ -28,13 +30,19 @@ def _case(name):
         lengths[::1999] = 700
     elif name == "one_per_row":
         lengths[:] = 1
+    elif name == "around_the_limits":
+        pairs = [(a, b) for a in (0, 1, 8, 9, 64, 300) for b in (255, 256, 257, 1024, 1300)]
+        lengths = np.zeros(n, np.int64)
+        flat = np.array(pairs + [p[::-1] for p in pairs]).ravel()
+        lengths[:flat.shape[0]] = flat
+        lengths[n - 1] = 700
     elif name == "mixed":
         lengths = np.random.default_rng(1).integers(0, 60, n)
         lengths[17] = 3000
     return (n,) + _csr(n, lengths, len(name))
 
 
-@pytest.mark.parametrize("name", ["long_rows", "empty_runs", "one_per_row", "mixed"])
+@pytest.mark.parametrize("name", ["long_rows", "empty_runs", "one_per_row", "mixed", "around_the_limits"])
 def test_features_and_arrays(name):
     n, rp, ci, va = _case(name)
     d = [torch.from_numpy(x).cuda() for x in (rp, ci, va)]
@@ -96,3 +104,50 @@ def test_freed_memory_is_kept_within_a_bound_and_reused():
     for h in hs:
         h.close()
     assert before - torch.cuda.mem_get_info()[0] <= (1 << 30) + (64 << 20)
+
+
+@pytest.mark.parametrize("n_items", [1, 16_383, 16_384, 70_001, 1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("bits", [1, 11, 21])
+def test_items_come_in_column_order_whatever_their_number(n_items, bits):
+    """The sort behind the column-ordered schedule: rows of two nonzeros cut into items of one."""
+    rng = np.random.default_rng(n_items + bits)
+    n_cols = (1 << bits) + 1
+    first = np.minimum(rng.integers(0, n_cols - 1, n_items), rng.integers(0, n_cols - 1, n_items))
+    rp = torch.arange(0, 2 * n_items + 1, 2, dtype=torch.int32, device="cuda")
+    ci = torch.from_numpy(np.stack([first, np.full(n_items, n_cols - 1)], 1).ravel().astype(np.int32)).cuda()
+    h = pc.pcsr_build(n_items, n_cols, rp, ci, torch.ones(2 * n_items, device="cuda"),
+                      pc.make_params(S=1, SG=1, flags=pc.PCSR_FLAG_COLUMN_ORDER))
+    e, got = pc.pcsr_export(h), pc.pcsr_export_schedule(h)
+    sched, xb = column_ordered_schedule(e["rowptr"], e["colidx"], e["trow"], e["P"])
+    assert np.array_equal(got["xcd_bounds"], xb) and np.array_equal(got["sched"], sched)
+    h.close()
+
+
+def _device_build_fails(n, m, rp, ci, flags=0):
+    with pytest.raises(pc.PcsrError) as err:
+        pc.pcsr_build(n, m, *(torch.from_numpy(x).cuda() for x in (rp, ci, np.ones(ci.shape[0], np.float32))),
+                      pc.make_params(flags=flags))
+    return err.value.code == pc.binding.PCSR_E_BAD_CSR
+
+
+@pytest.mark.parametrize("where", [0, 1, 3, 1023, 1024, 1025, 2047, 2499])
+def test_one_wrong_column_is_found_wherever_it_is(where):
+    """Rows of 1, 2, 3, ... nonzeros with runs of empty ones, so that row starts fall everywhere in a slice."""
+    lengths = np.concatenate([np.tile(np.arange(8), 90), np.zeros(2000, np.int64)])
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    n, m = lengths.shape[0], 50
+    ci = np.concatenate([5 + 3 * np.arange(k) for k in lengths]).astype(np.int32)
+    h = pc.pcsr_build(n, m, *(torch.from_numpy(x).cuda() for x in (rp, ci, np.ones(ci.shape[0], np.float32))))
+    assert np.array_equal(pc.pcsr_export(h)["colidx"], ci)
+    h.close()
+    starts = set(rp.tolist())
+    for value in (m, -1) + (() if where in starts else (int(ci[where - 1]), int(ci[where - 1]) - 1)):
+        bad = ci.copy()
+        bad[where] = value
+        assert _device_build_fails(n, m, rp, bad), value
+    pointer = rp.copy()
+    row = int(np.searchsorted(rp, where, side="right"))
+    pointer[row] = rp[-1] + 1
+    assert _device_build_fails(n, m, pointer, ci)
+    pointer[row] = -3
+    assert _device_build_fails(n, m, pointer, ci)
