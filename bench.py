@@ -159,8 +159,11 @@ def main() -> int:
     h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, params)
     build_ms = (time.time() - t0) * 1e3
     launch = pc.pcsr_query_kernel(h, K)
+    built = pc.pcsr_format(h)
+    by_cluster = int(params.flags) & pc.PCSR_FLAG_CLUSTER_IF_USEFUL and built["SG"] == 1024
+    schedule = "cluster" if by_cluster else "column" if (int(params.flags) & pc.PCSR_FLAG_COLUMN_ORDER) and S else "index"
+    S, SG = built["S"], built["SG"] if by_cluster else int(params.SG)
     instance = kernel_instance(V, S, launch)
-    schedule = "column" if (int(params.flags) & pc.PCSR_FLAG_COLUMN_ORDER) and S else "index"
     workload_name = f"{args.workload}-{args.size}" + (f"+reorder({args.reorder})" if args.reorder else "")
     pc.pcsr_reserve_workspace(h, K)
 
@@ -230,14 +233,14 @@ def main() -> int:
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": workload_name, "graph": g.name, "n": g.n_rows,
-                   "nnz": g.nnz, "K": K, "V": V, "S": S, "SG": int(params.SG), "schedule": schedule,
+                   "nnz": g.nnz, "K": K, "V": V, "S": S, "SG": SG, "schedule": schedule,
                    **launch, "kernel": instance,
                    "workspace_bytes": pc.pcsr_workspace_bytes(h, K)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "copy_kernel_gbs": stream_gbs,
                      "frac_of_copy_kernel": achieved / stream_gbs if stream_gbs else None,
-                     "traffic": PROFILED_TRAFFIC.get((workload_name, K, instance, int(params.SG), schedule)),
+                     "traffic": PROFILED_TRAFFIC.get((workload_name, K, instance, SG, schedule)),
                      "kernel_ms_mean": kern_ms, "kernel_ms_median": statistics.median(per_launch_ms),
                      "kernel_ms_min": min(per_launch_ms), "algorithmic_bytes": bytes_min},
         "setup": {"generate_s": gen_s, "features_select_ms": feat_ms, "pcsr_build_ms": build_ms,

@@ -57,6 +57,13 @@ enum {
                                   vectors inside their block's window and blocks of 128 items or
                                   more on average); otherwise the handle is built as if
                                   col_window were 0 and its kernel parameters are set to auto */
+    PCSR_FLAG_CLUSTER_IF_USEFUL = 256, /* V = 1, square matrices, built on the GPU, no col_window: if the rows
+                                  turn out to form communities (most of a row's columns are rows of
+                                  its own one) the handle is built with S = 1, items of up to 1024
+                                  vectors and a schedule that runs the rows of a community one after
+                                  another, dealt to the 8 XCDs as contiguous ranges of equal work
+                                  (items of longer rows first, in column order), and its kernel
+                                  parameters are set to auto.  Otherwise the flag does nothing   */
     PCSR_FLAG_ATOMIC_SPLIT = 32 /* S = 1 only: panels that were split accumulate into C with
                                   fp32 atomics, as Algorithm 2 prints it, instead of the
                                   default two-pass write-back (see pcsr_spmm)                 */

@@ -22,6 +22,7 @@ PCSR_FLAG_GPU_BUILD = 16
 PCSR_FLAG_ATOMIC_SPLIT = 32
 PCSR_FLAG_COLUMN_ORDER = 64
 PCSR_FLAG_WINDOW_IF_USEFUL = 128
+PCSR_FLAG_CLUSTER_IF_USEFUL = 256
 PCSR_N_FEATURES = 17
 FEATURE_NAMES = ("n", "n_hat", "nnz", "delta", "d", "d_hat", "d_max", "CV", "CV_hat",
                  "SR_1", "SR_2", "rho", "b", "b_max", "PR_1", "PR_2", "near_512")
@@ -351,12 +352,18 @@ def pcsr_window_stats(h: Handle) -> dict:
     return dict(col_window=int(out[0]), items_per_block=float(out[1]), hit_fraction=float(out[2]))
 
 
-def pcsr_export(h: Handle) -> dict:
+def pcsr_format(h: Handle) -> dict:
+    """Sizes and format parameters of the handle as it was built."""
     sizes = (ctypes.c_int64 * 6)()
     rc = _lib().pcsr_export(h.raw, ctypes.byref(sizes), None, None, None, None)
     if rc != PCSR_OK:
         raise PcsrError(rc, "pcsr_export")
-    P, M, nnz_v, V, SG, has_trow = list(sizes)
+    return dict(zip(("P", "M", "nnz_v", "V", "SG", "S"), list(sizes)))
+
+
+def pcsr_export(h: Handle) -> dict:
+    sizes = (ctypes.c_int64 * 6)()
+    P, M, nnz_v, V, SG, has_trow = pcsr_format(h).values()
     rowptr = np.empty(M + 1, np.int32)
     colidx = np.empty(nnz_v, np.int32)
     val = np.empty(nnz_v * V, np.float32)

@@ -100,6 +100,7 @@ struct pcsr_handle_s {
     int32_t *d_win_lo = nullptr;  // per item: run of vectors inside the block's window
     int32_t *d_win_hi = nullptr;
     int64_t n_win_blocks = 0;
+    bool clustered = false; // scheduled community by community (PCSR_FLAG_CLUSTER_IF_USEFUL)
     int64_t n_split = 0;
     int64_t n_split_items = 0; // workspace slots: items that belong to split panels
     float *d_ws = nullptr;     // partial rows of those items, grown on demand
@@ -209,8 +210,10 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
             const int fit = (128 * 1024 / 4 / h->host.win_cols - 4) / vec;
             if (need > fit) need = fit;
         }
-        // balanced (power-law) handles: four items per wavefront, as pcsr_select picks
-        const int cap = h->host.S ? 16 : 64;
+        // balanced (power-law) handles: four items per wavefront, as pcsr_select picks.  Rows run community by
+        // community gather from L2, and whole rows of B then beat slices of 64 columns (250,000 rows of 48:
+        // K = 128 262 us for 296, K = 256 578 for 680, K = 300 879 for 1032).
+        const int cap = h->host.S && !h->clustered ? 16 : 64;
         lpr = 4;
         while (lpr < need && lpr < cap) lpr <<= 1;
     }
@@ -218,8 +221,9 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     if (!rep) {
         int need = (K + lpr * vec - 1) / (lpr * vec);
         rep = 1;
-        if (h->host.win_cols == 0 && !h->host.S)
-            while (rep < need && rep < 4) rep <<= 1;
+        const int most = !h->host.S ? 4 : (h->clustered ? 2 : 1);
+        if (h->host.win_cols == 0)
+            while (rep < need && rep < most) rep <<= 1;
     }
     int waves = h->waves ? h->waves : 4;
     int ipg = h->ipg ? h->ipg : 1;
@@ -359,12 +363,13 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     pcsr::DeviceBuild db;
     int herr = 0;
     int rc = pcsr::build_device(n_rows, n_cols, nnz, rowptr, colidx, vals, prm.V, prm.S, prm.SG, prm.omega,
-                                !(prm.flags & PCSR_FLAG_NO_VALIDATE), column_order, &db, &herr);
+                                !(prm.flags & PCSR_FLAG_NO_VALIDATE), column_order,
+                                (prm.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && !prm.col_window, &db, &herr);
     h->host.n_rows = n_rows;
     h->host.n_cols = n_cols;
     h->host.nnz = nnz;
     h->host.V = prm.V;
-    h->host.S = prm.S;
+    h->host.S = rc == PCSR_OK ? db.S : prm.S;
     h->host.P = db.P;
     h->host.M = db.M;
     h->host.nnz_v = db.nnz_v;
@@ -389,6 +394,11 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     h->waves = prm.waves_per_wg;
     h->ipg = prm.items_per_group;
     h->flags = checked_flags(prm);
+    if (rc == PCSR_OK && db.clustered) { // the caller's shape was for the order it would have had otherwise
+        h->clustered = true;
+        h->lpr = h->vec = h->rep = h->waves = h->ipg = 0;
+        h->flags &= ~kWideBits;
+    }
     if (rc == PCSR_OK && prm.col_window) {
         pcsr::DeviceWindows w;
         rc = pcsr::windows_device(db.M, n_cols, prm.col_window, db.rowptr, db.colidx, &w, &herr);
@@ -1061,6 +1071,13 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // 160, K = 32: V = 2 runs at 0.55 of V = 1).
     const bool pair_long = long_uniform && n * (double)(K < 32 ? 4 : 8) / 128.0 >= 3500.0;
     p.V = (!p.S && (d_hat < 6.0 || (d_hat < 12.0 && pr2 < 0.45) || pr2 < 0.20 || pair_long)) ? 2 : 1;
+
+    // Scattered rows may belong to communities whose ids were shuffled.  Looking for them and ordering the schedule by
+    // them costs the build some 0.15 ms and 0.6 ns a row; run side by side the rows of a community gather from L2 and the
+    // product takes 0.3 ps per nonzero and column less (250,000 rows of 48: K = 64 377 -> 145 us, K = 128
+    // 747 -> 262, K = 256 1485 -> 578; rows of 12, K = 256: 919 -> 508).  Asked for where one product pays for it.
+    if (!skewed && !windowed && scattered && p.V == 1 && d_hat >= 12.0 && 3e-7 * f[2] * (double)K >= 150.0 + 6e-4 * n)
+        p.flags |= PCSR_FLAG_CLUSTER_IF_USEFUL;
 
     // Launch shape: the widest vector load that divides K, one lane group spanning the
     // whole row of C when it fits a wavefront, repeats beyond that.

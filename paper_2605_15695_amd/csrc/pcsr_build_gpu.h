@@ -18,15 +18,30 @@ struct DeviceBuild {
     int32_t *long_list = nullptr;   // positions in split of the panels with more than kLongPanelSlots items
     int32_t *sched = nullptr;       // column-ordered schedule, 4 int32 per launch position (or null)
     int64_t P = 0, M = 0, nnz_v = 0, n_split = 0, n_split_items = 0, n_long = 0, max_item_len = 0;
-    int32_t SG = 0;
+    int32_t S = 0, SG = 0;
+    bool clustered = false; // the schedule runs the rows community by community
     int32_t xcd_bounds[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
 };
 
 // d_rowptr / d_colidx / d_vals are device pointers.  Returns PCSR_OK or a PCSR_E_* code;
 // on PCSR_E_HIP *hip_err holds the hipError_t.  Synchronous.
+// clusters: where the rows turn out to form communities, S = 1 with items of kClusterItem and the schedule by community.
+constexpr int32_t kClusterItem = 1024;
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
-                 int32_t omega, bool validate, bool column_order, DeviceBuild *out, int *hip_err);
+                 int32_t omega, bool validate, bool column_order, bool clusters, DeviceBuild *out, int *hip_err);
+
+// Whether rows share more columns than chance has them: enqueues the count of a sample on the null stream (d_out: two
+// sums, zeros on entry), and what the sums say.  The arrays need not have been checked.
+hipError_t cluster_probe(int64_t n, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx, unsigned long long *d_out);
+bool cluster_probe_says(const unsigned long long found[2], int64_t n);
+// A label in [0, n) for every row of a checked square CSR, rows of a community having the same one; null where too few do for
+// an order by label to pay.  Ownership passes to the caller.  The same labels on every run.  Synchronous.
+int cluster_rows(int64_t n, const int32_t *d_rowptr, const int32_t *d_colidx, int32_t **labels, int *hip_err);
+// Keys of cluster_key_bits(n) bits by which items sort into the order of their rows' labels (enqueued on the null stream).
+int cluster_key_bits(int64_t n);
+hipError_t cluster_keys(int64_t n, const int32_t *d_labels, int64_t n_items, const int32_t *d_items, const int32_t *d_rows,
+                        uint32_t *d_key);
 
 // The check build_device makes, alone: PCSR_OK or PCSR_E_BAD_CSR (or HIP, OOM).  Synchronous.
 int validate_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,

@@ -32,7 +32,8 @@ struct Checked {
     int bad;         // a row pointer or column out of range, a column that does not ascend
     int first, last; // rowptr[0], rowptr[n_rows]
     int longest;     // longest row
-    int nonempty, pad[3];
+    int nonempty;
+    unsigned long long common[2]; // cluster_probe's sums
 };
 
 // Monotone row pointer inside [0, nnz], row statistics, the row at the start of each slice.  Few, large
@@ -140,23 +141,6 @@ __device__ __forceinline__ int64_t count_below(const int32_t *colidx, int64_t b,
             hi = mid;
     }
     return lo - b;
-}
-
-// One step of a search for the first of colidx[lo, hi) that is >= key (lo == hi at the end): three probes at a
-// time, since such a chain is bound by its round trips to memory (features of R-MAT scale 20: 77 us for 102 with one).
-__device__ __forceinline__ void narrow(const int32_t *colidx, int64_t key, int32_t &lo, int32_t &hi)
-{
-    const int32_t n = hi - lo;
-    if (n <= 0) return;
-    const int32_t at[3] = {lo + (n >> 2), lo + (n >> 1), hi - 1 - (n >> 2)};
-    const int32_t c[3] = {colidx[at[0]], colidx[at[1]], colidx[at[2]]};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        if (c[k] < key)
-            lo = at[k] + 1 > lo ? at[k] + 1 : lo;
-        else
-            hi = at[k] < hi ? at[k] : hi;
-    }
 }
 
 // ---- V = 2.  The vectors of panel p are the sorted union of the columns of rows 2p ("even")
@@ -776,8 +760,8 @@ hipError_t exclusive_scan(const int32_t *in, int32_t *out, int64_t n, Scratch &s
 
 // The check of the CSR, and its columns and values copied to pcol / pval where these are given.
 int check_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
-                 const float *d_vals, bool validate, int32_t *pcol, float *pval, Scratch &sc, Checked **d_out, Checked *h,
-                 int *hip_err)
+                 const float *d_vals, bool validate, bool probe, int32_t *pcol, float *pval, Scratch &sc, Checked **d_out,
+                 Checked *h, int *hip_err)
 {
     Checked *d = nullptr;
     int32_t *slices = nullptr;
@@ -794,6 +778,7 @@ int check_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
                            d_colidx, d_vals, slices, validate ? 1 : 0, pcol, pval, d);
         HIP_TRY(hipGetLastError());
     }
+    if (probe) HIP_TRY(cluster_probe(n_rows, nnz, d_rowptr, d_colidx, d->common));
     HIP_TRY(hipMemcpy(h, d, sizeof(Checked), hipMemcpyDeviceToHost));
     *d_out = d;
     if (h->first != 0 || h->last != nnz) return PCSR_E_BAD_CSR;
@@ -808,12 +793,25 @@ int validate_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *
 {
     Scratch sc;
     Checked *d = nullptr, h;
-    return check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, nullptr, true, nullptr, nullptr, sc, &d, &h, hip_err);
+    return check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, nullptr, true, false, nullptr, nullptr, sc, &d, &h,
+                        hip_err);
 }
+
+namespace {
+struct LabelsGuard { // what cluster_rows made, given back on scope exit
+    int32_t *p = nullptr;
+    ~LabelsGuard()
+    {
+        if (!p) return;
+        (void)hipStreamSynchronize(nullptr);
+        pool_free(p);
+    }
+};
+} // namespace
 
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
-                 int32_t omega, bool validate, bool column_order, DeviceBuild *out, int *hip_err)
+                 int32_t omega, bool validate, bool column_order, bool clusters, DeviceBuild *out, int *hip_err)
 {
     if (V != 1 && V != 2) return PCSR_E_UNSUPPORTED;
     if (omega == 0) omega = 64;
@@ -830,8 +828,21 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
         HIP_TRY(sc.alloc((void **)&pval, sizeof(float) * (nnz + 1)));
     }
     Checked *d_check = nullptr, check;
-    int rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, validate, pcol, pval, sc, &d_check, &check, hip_err);
+    clusters = clusters && V == 1 && n_rows == n_cols && nnz > 0;
+    int rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, validate, clusters, pcol, pval, sc, &d_check, &check,
+                          hip_err);
     if (rc != PCSR_OK) return rc;
+    LabelsGuard labels;
+    if (clusters && cluster_probe_says(check.common, n_rows)) {
+        rc = cluster_rows(n_rows, d_rowptr, d_colidx, &labels.p, hip_err);
+        if (rc != PCSR_OK && rc != PCSR_E_OOM) return rc; // without the memory for it: the order asked for otherwise
+        if (labels.p) {
+            S = 1;
+            SG = kClusterItem;
+            column_order = true;
+            out->clustered = true;
+        }
+    }
     if (V == 1) {
         if (!S) {
             HIP_TRY(sc.alloc((void **)&prow, sizeof(int32_t) * (P + 1)));
@@ -881,6 +892,7 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
 
     out->P = P;
     out->nnz_v = nnz_v;
+    out->S = S;
     out->SG = (int32_t)sg;
     int32_t *d_bounds = nullptr;
     HIP_TRY(sc.alloc((void **)&d_bounds, 27 * sizeof(int32_t)));
@@ -939,23 +951,34 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
                                        reinterpret_cast<const uint32_t *>(o.long_item),
                                        reinterpret_cast<uint32_t *>(sorted), n_long, key_bits(n_cols), sc));
             }
+            const int32_t *shorts = o.short_item;
+            if (labels.p && n_short > 0) { // the rows of a community side by side
+                uint32_t *key = nullptr, *key_sorted = nullptr, *ordered = nullptr;
+                HIP_TRY(sc.alloc((void **)&key, sizeof(uint32_t) * n_short));
+                HIP_TRY(sc.alloc((void **)&key_sorted, sizeof(uint32_t) * n_short));
+                HIP_TRY(sc.alloc((void **)&ordered, sizeof(uint32_t) * n_short));
+                HIP_TRY(cluster_keys(n_rows, labels.p, n_short, o.short_item, o.trow, key));
+                HIP_TRY(sort_pairs_u32(key, key_sorted, reinterpret_cast<const uint32_t *>(o.short_item), ordered, n_short,
+                                       cluster_key_bits(n_rows), sc));
+                shorts = reinterpret_cast<const int32_t *>(ordered);
+            }
             const int64_t cl = (n_long + kSchedChunk - 1) / kSchedChunk, cs = (n_short + kSchedChunk - 1) / kSchedChunk;
             long long *wsum = nullptr, *wscan = nullptr;
             HIP_TRY(sc.alloc((void **)&wsum, sizeof(long long) * (cl + cs + 1)));
             HIP_TRY(sc.alloc((void **)&wscan, sizeof(long long) * (cl + cs + 2)));
             if (cl + cs > 0) {
                 hipLaunchKernelGGL(sched_sums_kernel, dim3((unsigned)(cl + cs)), dim3(kThreads), 0, 0, n_long, sorted,
-                                   n_short, o.short_item, o.rowptr, wsum);
+                                   n_short, shorts, o.rowptr, wsum);
                 HIP_TRY(hipGetLastError());
             }
             hipLaunchKernelGGL(sched_scan_kernel, dim3(2), dim3(1024), 0, 0, (int)cl, (int)cs, wsum, wscan);
             HIP_TRY(hipGetLastError());
             hipLaunchKernelGGL(sched_bounds_kernel, dim3(18), dim3(kThreads), 0, 0, n_long, sorted, n_short,
-                               o.short_item, o.rowptr, wscan, d_bounds);
+                               shorts, o.rowptr, wscan, d_bounds);
             HIP_TRY(hipGetLastError());
             if (M > 0) {
                 hipLaunchKernelGGL(sched_emit_kernel, dim3(blocks_for(M)), dim3(kThreads), 0, 0, n_long, sorted, n_short,
-                                   o.short_item, d_bounds, o.rowptr, o.trow, o.item_slot,
+                                   shorts, d_bounds, o.rowptr, o.trow, o.item_slot,
                                    reinterpret_cast<int4 *>(sched));
                 HIP_TRY(hipGetLastError());
             }

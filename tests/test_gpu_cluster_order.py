@@ -1,0 +1,158 @@
+"""PCSR_FLAG_CLUSTER_IF_USEFUL: rows of communities with shuffled ids run side by side, and everything else stays as it
+is without the flag."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2605_15695_amd as pc
+from tests.helpers import column_ordered_schedule
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+FLAG = pc.PCSR_FLAG_CLUSTER_IF_USEFUL
+
+
+def _planted(n, block, inner, outer, seed, extra=()):
+    """Rows with `inner` columns in their own block of `block` nodes and `outer` anywhere, ids shuffled; extra: (row,
+    length) of rows with that many uniform columns in place of their own."""
+    rng = np.random.default_rng(seed)
+    of = rng.permutation(n) // block
+    members = [np.nonzero(of == b)[0] for b in range(int(of.max()) + 1)]
+    rows = []
+    for i in range(n):
+        own = members[of[i]]
+        rows.append(np.unique(np.concatenate([rng.choice(own, min(inner, own.shape[0]), replace=False),
+                                              rng.integers(0, n, outer)])))
+    for r, length in extra:
+        rows[r] = np.sort(rng.choice(n, length, replace=False))
+    rp = np.concatenate([[0], np.cumsum([len(c) for c in rows])]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    return n, rp, ci, rng.standard_normal(ci.shape[0]).astype(np.float32), of
+
+
+def _device(*arrays):
+    return [torch.from_numpy(a).cuda() for a in arrays]
+
+
+def _check_product(h, n, rp, ci, va, K):
+    B = np.random.default_rng(K).uniform(-1, 1, (n, K)).astype(np.float32)
+    C = torch.full((n, K), float("nan"), device="cuda")
+    pc.pcsr_spmm(h, torch.from_numpy(B).cuda(), C, K)
+    ref, bound = oracle.spmm(rp, ci, va, B)
+    ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, bound)
+    assert ok, (K, worst)
+
+
+@pytest.mark.parametrize("S", [0, 1])
+@pytest.mark.parametrize("n,block,inner,outer,extra", [
+    (6001, 100, 20, 2, ()),                                   # blocks of 100, rows of about 22
+    (5003, 50, 40, 6, ((7, 0), (8, 1), (5002, 0), (4000, 3))),  # empty and short rows among them
+    (8192, 512, 30, 5, ((0, 1025), (5, 1024), (8191, 4000))),   # rows longer than an item
+])
+def test_rows_of_a_community_run_side_by_side(n, block, inner, outer, extra, S):
+    n, rp, ci, va, of = _planted(n, block, inner, outer, n, extra)
+    prm = pc.make_params(S=S, SG=32 if S else 0, flags=FLAG | (pc.PCSR_FLAG_COLUMN_ORDER if S else 0),
+                         lanes_per_row=16, vec=2)
+    h = pc.pcsr_build(n, n, *_device(rp, ci, va), prm)
+    e, got = pc.pcsr_export(h), pc.pcsr_export_schedule(h)
+    sched, xb = got["sched"], got["xcd_bounds"]
+    assert e["SG"] == 1024 and np.array_equal(e["colidx"], ci) and np.array_equal(e["val"], va)
+    lengths = np.diff(rp)
+    assert e["M"] == int(np.maximum(1, -(-lengths // 1024)).sum()) == sched.shape[0]
+    # every item once, and where it was
+    order = np.lexsort((sched[:, 0], sched[:, 2]))
+    items = np.lexsort((e["rowptr"][:-1], e["trow"]))
+    assert np.array_equal(sched[order, 0][lengths[sched[order, 2]] > 0], e["rowptr"][:-1][items][lengths[e["trow"][items]] > 0])
+    assert np.array_equal(np.bincount(sched[:, 2], weights=sched[:, 1], minlength=n).astype(int), lengths)
+    # positions one after another within an XCD's range mostly belong to one community: its own rows and at most a few others
+    # that its key is shared with
+    runs = 0
+    for x in range(8):
+        rows = sched[xb[x]:xb[x + 1], 2]
+        c = of[rows[sched[xb[x]:xb[x + 1], 3] < 0]]
+        for k in range(0, c.shape[0] - block, block):
+            runs += np.unique(c[k:k + block], return_counts=True)[1].max() >= 0.3 * block
+    assert runs >= 0.8 * (n // block - 16)
+    work = np.add.reduceat(sched[:, 1] + 8, xb[:-1])
+    assert work.max() - work.min() <= 2 * (1024 + 8)
+    again = pc.pcsr_build(n, n, *_device(rp, ci, va), prm)
+    assert np.array_equal(pc.pcsr_export_schedule(again)["sched"], sched)
+    for K in (1, 7, 16, 33, 64, 100, 256, 300, 516):
+        _check_product(h, n, rp, ci, va, K)
+    h.close(), again.close()
+
+
+def test_shape_is_chosen_for_the_order_the_build_found():
+    n, rp, ci, va, _ = _planted(6001, 100, 20, 2, 1)
+    h = pc.pcsr_build(n, n, *_device(rp, ci, va), pc.make_params(flags=FLAG, lanes_per_row=32, vec=2, rep=1, waves_per_wg=2))
+    for K, shape in ((64, (16, 4, 1)), (128, (32, 4, 1)), (256, (64, 4, 1)), (512, (64, 4, 2)), (2048, (64, 4, 2))):
+        q = pc.pcsr_query_kernel(h, K)
+        assert (q["lanes_per_row"], q["vec"], q["rep"], q["waves_per_wg"]) == shape + (4,)
+    h.close()
+
+
+def _uniform(n, m, k, seed):
+    rng = np.random.default_rng(seed)
+    ci = np.sort(np.argsort(rng.random((n, m)), axis=1)[:, :k].astype(np.int32), axis=1).ravel()
+    return np.arange(0, n * k + 1, k, dtype=np.int32), ci, rng.standard_normal(ci.shape[0]).astype(np.float32)
+
+
+@pytest.mark.parametrize("name", ["uniform", "one_clique", "rectangular", "paired", "empty"])
+def test_nothing_changes_without_communities(name):
+    n = m = 3000
+    V = 2 if name == "paired" else 1
+    if name == "uniform":
+        rp, ci, va = _uniform(n, n, 20, 1)
+    elif name == "one_clique":                       # every row the same columns: one label for all
+        rp, ci, va = _uniform(1, n, 24, 2)
+        rp, ci, va = np.arange(0, 24 * n + 1, 24, dtype=np.int32), np.tile(ci, n), np.tile(va, n)
+    elif name == "rectangular":
+        _, rp, ci, va, _ = _planted(n, 100, 20, 2, 3)
+        m = n + 1
+    elif name == "paired":
+        _, rp, ci, va, _ = _planted(n, 100, 20, 2, 4)
+    else:
+        rp, ci, va = np.zeros(n + 1, np.int32), np.zeros(0, np.int32), np.zeros(0, np.float32)
+    for S in (0, 1):
+        flags = pc.PCSR_FLAG_COLUMN_ORDER if S else 0
+        a, b = (pc.pcsr_build(n, m, *_device(rp, ci, va), pc.make_params(V=V, S=S, SG=8 if S else 0, flags=flags | f))
+                for f in (0, FLAG))
+        x, y = pc.pcsr_export(a), pc.pcsr_export(b)
+        assert all(np.array_equal(x[k], y[k]) for k in x)
+        x, y = pc.pcsr_export_schedule(a), pc.pcsr_export_schedule(b)
+        assert np.array_equal(x["xcd_bounds"], y["xcd_bounds"])
+        assert (x["sched"] is None) == (y["sched"] is None) and (not S or np.array_equal(x["sched"], y["sched"]))
+        if S and n == m and ci.size:
+            sched, _ = column_ordered_schedule(pc.pcsr_export(b)["rowptr"], pc.pcsr_export(b)["colidx"],
+                                               pc.pcsr_export(b)["trow"], pc.pcsr_export(b)["P"])
+            assert np.array_equal(y["sched"], sched)
+        a.close(), b.close()
+
+
+def test_a_training_layer_on_such_an_operator():
+    """Forward and backward at several widths."""
+    from paper_2605_15695_amd.gnn import PcsrOperator
+
+    n, rp, ci, va, _ = _planted(6001, 100, 20, 2, 9)
+    prm = pc.make_params(flags=FLAG)
+    a = PcsrOperator(n, n, *_device(rp, ci, va), params=prm)
+    b = PcsrOperator(n, n, *_device(rp, ci, va), params=pc.make_params())
+    assert pc.pcsr_export(a.fwd)["SG"] == 1024
+    for K in (16, 30, 128, 600):
+        X = torch.randn(n, K, device="cuda")
+        x, y = X.clone().requires_grad_(True), X.clone().requires_grad_(True)
+        u, v = a(x), b(y)
+        u.backward(X), v.backward(X)
+        for got, want in ((u.detach(), v.detach()), (x.grad, y.grad)):
+            assert float((got - want).norm() / want.norm()) < 1e-6
+
+
+def test_selector_asks_where_one_product_pays_for_the_search():
+    f = np.zeros(len(pc.FEATURE_NAMES))
+    f[0] = f[1] = 250_000
+    f[2], f[4], f[5], f[6], f[7], f[15], f[16] = 12e6, 48.0, 48.0, 80.0, 0.15, 0.5, 0.004
+    assert not pc.pcsr_select(f, 64).flags & FLAG and pc.pcsr_select(f, 128).flags & FLAG
+    f[2], f[4], f[5] = 3e6, 12.0, 12.0                          # rows of 12: from K = 334 on
+    assert not pc.pcsr_select(f, 256).flags & FLAG and pc.pcsr_select(f, 512).flags & FLAG
+    f[16] = 0.5                                                # local columns
+    assert not pc.pcsr_select(f, 512).flags & FLAG
