@@ -467,7 +467,9 @@ struct BackArgs {
     float *ws;     // per workgroup: dW2, db2, then dW1, db1, dot (TWO) or the sums of G1
     long ws_stride;
 };
-constexpr int back_ld(int t) { return 16 * t + 16; } // floats per row: four rows on different banks
+// floats per row: 16 lanes that write 16 bytes of a row each meet all 64 banks (16 t + 16 had four of them on
+// the same ones: conflicts 19 % of the LDS cycles for 52, 2,000,000 x 64 656-662 us for 672); rows of 16 are dense as they are
+constexpr int back_ld(int t) { return t == 1 ? 16 : 16 * t + 4; }
 
 // acc += P^T Q over the 16 rows in the patch; psum: column sums of P
 template <int PT, int QT>
@@ -762,7 +764,8 @@ __global__ void __launch_bounds__(64 * kWaves) wgrad_kernel(WgradArgs p)
 }
 
 // out[e] = sum over the parts of ws[part*len + e] for e < n0 (dst0), then dst1: 16 threads per
-// element, each every 16th part in order, the 16 sums in order.
+// element, each every 16th part in order, the 16 sums in order.  Eight loads in flight: 512 parts of 64 x 64 in 5 us
+// where one after the other took 10.
 __global__ void __launch_bounds__(256) sum_partials_kernel(const float *ws, int parts, long stride, long n0, float *dst0,
                                                            long n1, float *dst1)
 {
@@ -770,8 +773,17 @@ __global__ void __launch_bounds__(256) sum_partials_kernel(const float *ws, int 
     const int c = threadIdx.x & 15, j = threadIdx.x >> 4;
     const long e = (long)blockIdx.x * 16 + c;
     float t = 0.0f;
-    if (e < n0 + n1)
-        for (int s = j; s < parts; s += 16) t += ws[s * stride + e];
+    if (e < n0 + n1) {
+        int s = j;
+        for (; s + 7 * 16 < parts; s += 8 * 16) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = ws[(s + k * 16) * stride + e];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) t += v[k];
+        }
+        for (; s < parts; s += 16) t += ws[s * stride + e];
+    }
     sh[j][c] = t;
     __syncthreads();
     if (j == 0 && e < n0 + n1) {
