@@ -86,6 +86,33 @@ def test_reorder_permute_transpose(name):
         assert np.array_equal(t[1], rows[order]) and np.array_equal(t[2].view(np.uint32), va[order].view(np.uint32))
 
 
+@pytest.mark.parametrize("longest", [63, 64, 65, 1024, 1025, 8192, 8193])
+@pytest.mark.parametrize("twice", [False, True])
+def test_permuted_rows_of_every_class(longest, twice):
+    """Rows up to and beyond what a wavefront, a workgroup and LDS sort, and a column that comes twice in one of them."""
+    rng = np.random.default_rng(longest)
+    n = 10_001
+    lengths = rng.integers(0, 45, n)
+    lengths[[0, 4000, n - 1]] = [longest, 0, longest]
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths]).astype(np.int32)
+    assert ci.size >= 200_000               # enough for the GPU side to be taken
+    va = rng.standard_normal(ci.size).astype(np.float32)
+    if twice:
+        ci[longest - 1] = ci[longest // 2]
+    perm = rng.permutation(n).astype(np.int32)
+    rows = np.repeat(np.arange(n), lengths)
+    order = np.lexsort((va, perm[ci], perm[rows]))
+    got = pc.pcsr_permute_csr(n, rp, ci, va, perm)
+    assert np.array_equal(got[0], np.concatenate([[0], np.cumsum(np.bincount(perm[rows], minlength=n))]))
+    assert np.array_equal(got[1], perm[ci][order])
+    at = np.repeat(np.arange(n), np.diff(got[0]))
+    if twice:                               # which of the two comes first is not said
+        assert np.array_equal(got[2][np.lexsort((got[2], got[1], at))], va[order])
+    else:
+        assert np.array_equal(got[2].view(np.uint32), va[order].view(np.uint32))
+
+
 def test_refusals_are_those_of_the_host():
     n, rp, ci, va = _case("sbm")
     bad = ci.copy()
