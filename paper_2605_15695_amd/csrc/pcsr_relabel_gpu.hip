@@ -134,7 +134,7 @@ __device__ __forceinline__ unsigned wave_max(unsigned x) // of all 64 lanes, uni
 // One round for rows of up to 64 nonzeros, a wavefront per row, a lane per neighbour.  Labels are taken one at a time and
 // counted by a ballot until none that is left can lead: once communities have formed that is after a step or two.  Where
 // kTries labels have not decided it, every lane's label is counted by having every lane's broadcast.  Bound by vector
-// instructions: 10 M nonzeros FIG us a round on average over eight, 126 with all rows counted the second way.
+// instructions: 10 M nonzeros 97 us a round on average over eight, 126 with all rows counted the second way.
 constexpr int kTries = 6;
 __global__ void __launch_bounds__(kThreads) propagate_short_kernel(int64_t n, Rows r, const int32_t *lab, int32_t *nxt,
                                                                    int slot, uint32_t round, int32_t *changed)
@@ -306,7 +306,7 @@ struct PermutedRows {
 
 // New rows of up to 64 nonzeros, a wavefront each: a nonzero's place is how many of the row's new columns are smaller,
 // counted against every lane's broadcast.  (All places are taken, and add up to that, unless a column comes twice.)  The next
-// row's bounds are requested while this one is counted.  10 M nonzeros FIG us; a sort of all nonzeros by row and column took
+// row's bounds are requested while this one is counted.  10 M nonzeros 125 us; a sort of all nonzeros by row and column took
 // 590 with the passes around it.
 __global__ void __launch_bounds__(kThreads) permute_short_kernel(int64_t n, PermutedRows a)
 {
