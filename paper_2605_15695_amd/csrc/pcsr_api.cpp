@@ -296,28 +296,33 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     return PCSR_OK;
 }
 
-// Host CSR arrays in device memory for the length of a call.
+// Host CSR arrays in device memory for the length of a call.  The values follow beside the work on the pattern:
+// their half of the upload (48 MB: 1 ms) is under way when put() returns.
 struct UploadedCsr {
     int32_t *rowptr = nullptr, *colidx = nullptr;
     float *vals = nullptr;
+    pcsr::Upload values;
     int put(int64_t n_rows, int64_t nnz, const int32_t *h_rowptr, const int32_t *h_colidx, const float *h_vals)
     {
         auto one = [](void **d, const void *src, size_t bytes) {
             hipError_t e = pcsr::pool_alloc(d, bytes + 4);
-            if (e == hipSuccess && bytes) e = pcsr::copy_to_device(*d, src, bytes);
+            if (e == hipSuccess && bytes && src) e = pcsr::copy_to_device(*d, src, bytes);
             return e;
         };
         hipError_t e = one((void **)&rowptr, h_rowptr, sizeof(int32_t) * (n_rows + 1));
+        if (e == hipSuccess) e = one((void **)&vals, nullptr, sizeof(float) * nnz);
         if (e == hipSuccess) e = one((void **)&colidx, h_colidx, sizeof(int32_t) * nnz);
-        if (e == hipSuccess) e = one((void **)&vals, h_vals, sizeof(float) * nnz);
         if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
             return PCSR_E_OOM;
         }
-        return hip_ok(e) ? PCSR_OK : PCSR_E_HIP;
+        if (!hip_ok(e)) return PCSR_E_HIP;
+        values.start(vals, h_vals, sizeof(float) * nnz);
+        return PCSR_OK;
     }
     ~UploadedCsr()
     {
+        (void)values.wait();
         if (!rowptr) return;
         (void)hipStreamSynchronize(nullptr);
         pcsr::pool_free(rowptr);
@@ -349,9 +354,10 @@ constexpr int kWindowsOnHost = 1;
 // Nonzeros and rows below which pcsr_operator_build stays on the host.
 constexpr int64_t kHostOperator = 10000; // 0.5 ms there, 0.65 ms on the GPU at any size up to here
 
-// A handle from CSR arrays in device memory, everything built there.
+// A handle from CSR arrays in device memory, everything built there.  late: the copy that fills vals, if it is still
+// under way.
 int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
-                       const float *vals, const pcsr_params_t &prm, pcsr_handle_s **out)
+                       const float *vals, const pcsr_params_t &prm, pcsr::Upload *late, pcsr_handle_s **out)
 {
     const bool column_order = (prm.flags & PCSR_FLAG_COLUMN_ORDER) != 0;
     pcsr_handle_s *h = new (std::nothrow) pcsr_handle_s();
@@ -364,7 +370,7 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     int herr = 0;
     int rc = pcsr::build_device(n_rows, n_cols, nnz, rowptr, colidx, vals, prm.V, prm.S, prm.SG, prm.omega,
                                 !(prm.flags & PCSR_FLAG_NO_VALIDATE), column_order,
-                                (prm.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && !prm.col_window, &db, &herr);
+                                (prm.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && !prm.col_window, late, &db, &herr);
     h->host.n_rows = n_rows;
     h->host.n_cols = n_cols;
     h->host.nnz = nnz;
@@ -414,6 +420,17 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
             drop_poor_windows(h);
         }
     }
+    if (rc == PCSR_OK && db.vals_due) {
+        hipError_t e = late->wait();
+        if (e == hipSuccess && nnz > 0)
+            e = hipMemcpyAsync(h->d_val, vals, sizeof(float) * nnz, hipMemcpyDeviceToDevice, nullptr);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        if (e != hipSuccess) {
+            herr = (int)e;
+            (void)hipGetLastError();
+            rc = PCSR_E_HIP;
+        }
+    }
     if (rc != PCSR_OK) {
         if (rc == PCSR_E_HIP) g_last_hip = herr;
         release_device(h);
@@ -428,9 +445,9 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
 
 extern "C" {
 
-int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr,
-               const int32_t *colidx, const float *vals, const pcsr_params_t *p,
-               pcsr_handle_t *out)
+// pcsr_build; late: the copy that fills vals (device memory), if it is still under way.
+static int build_from(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
+                      const float *vals, const pcsr_params_t *p, pcsr::Upload *late, pcsr_handle_t *out)
 {
     if (!out || !rowptr || n_rows < 0 || n_cols < 0 || nnz < 0) return PCSR_E_INVALID_ARG;
     if (nnz > 0 && (!colidx || !vals)) return PCSR_E_INVALID_ARG;
@@ -472,7 +489,8 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
             d_vals = up.vals;
         }
         pcsr_handle_s *h = nullptr;
-        if (rc == PCSR_OK) rc = handle_from_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, prm, &h);
+        if (rc == PCSR_OK)
+            rc = handle_from_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, prm, device_csr ? late : &up.values, &h);
         if (rc == PCSR_OK) *out = h;
         if (rc != kWindowsOnHost && !(rc == PCSR_E_OOM && !asked)) return rc;
     }
@@ -483,6 +501,7 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
         std::vector<int32_t> s_rowptr, s_colidx;
         std::vector<float> s_vals;
         if (device_csr) {
+            if (late && !hip_ok(late->wait())) return PCSR_E_HIP;
             s_rowptr.resize(n_rows + 1);
             s_colidx.resize(nnz);
             s_vals.resize(nnz);
@@ -564,6 +583,12 @@ int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowpt
     }
 }
 
+int pcsr_build(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *rowptr, const int32_t *colidx,
+               const float *vals, const pcsr_params_t *p, pcsr_handle_t *out)
+{
+    return build_from(n_rows, n_cols, nnz, rowptr, colidx, vals, p, nullptr, out);
+}
+
 // pcsr_operator_build's parameters for one direction: the caller's, or what pcsr_select picks for
 // these features, its launch shape left on auto so that one handle serves every layer width.
 static int operator_params(const pcsr_params_t *p, bool pick, const double *f, int32_t K, pcsr_params_t *prm)
@@ -625,21 +650,22 @@ static int operator_on_gpu(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
     rc = pcsr::validate_device(n_rows, n_cols, nnz, rowptr, colidx, &herr);
     if (rc != PCSR_OK) return failed(rc);
     auto direction = [&](int64_t nr, int64_t nc, const int32_t *rp, const int32_t *ci, const float *va,
-                         pcsr_handle_t *h) -> int {
+                         pcsr::Upload *late, pcsr_handle_t *h) -> int {
         pcsr_params_t prm;
         double f[PCSR_N_FEATURES];
         int r = pick ? pcsr::features_device(nr, nc, nnz, rp, ci, 0, f, &herr) : PCSR_OK;
         if (r == PCSR_OK) r = operator_params(p, pick, f, K, &prm);
         if (r != PCSR_OK) return failed(r);
         prm.flags |= PCSR_FLAG_DEVICE_CSR | PCSR_FLAG_NO_VALIDATE;
-        return pcsr_build(nr, nc, nnz, rp, ci, va, &prm, h);
+        return build_from(nr, nc, nnz, rp, ci, va, &prm, late, h);
     };
-    rc = direction(n_rows, n_cols, rowptr, colidx, vals, &made[0]);
+    rc = direction(n_rows, n_cols, rowptr, colidx, vals, device_csr ? nullptr : &up.values, &made[0]);
     if (rc == PCSR_OK && with_transpose) {
         UploadedCsr t;
+        if (!hip_ok(up.values.wait())) return PCSR_E_HIP;
         rc = failed(pcsr::transpose_device(n_rows, n_cols, nnz, rowptr, colidx, vals, &t.rowptr, &t.colidx, &t.vals,
                                            &herr));
-        if (rc == PCSR_OK) rc = direction(n_cols, n_rows, t.rowptr, t.colidx, t.vals, &made[1]);
+        if (rc == PCSR_OK) rc = direction(n_cols, n_rows, t.rowptr, t.colidx, t.vals, nullptr, &made[1]);
     }
     return rc;
 }

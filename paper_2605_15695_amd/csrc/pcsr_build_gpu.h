@@ -3,6 +3,7 @@
 #include <cstdint>
 
 #include "pcsr_kernels.h"
+#include "pcsr_pool.h"
 
 namespace pcsr {
 
@@ -19,17 +20,21 @@ struct DeviceBuild {
     int32_t *sched = nullptr;       // column-ordered schedule, 4 int32 per launch position (or null)
     int64_t P = 0, M = 0, nnz_v = 0, n_split = 0, n_split_items = 0, n_long = 0, max_item_len = 0;
     int32_t S = 0, SG = 0;
+    bool vals_due = false;  // val is still to be filled, once `late` is there
     bool clustered = false; // the schedule runs the rows community by community
     int32_t xcd_bounds[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
 };
 
+// late: the copy that fills d_vals, if it is still under way (null: it is not).  With V = 1 nothing but val needs the
+// values: the call then leaves that to the caller (vals_due); else it waits.
 // d_rowptr / d_colidx / d_vals are device pointers.  Returns PCSR_OK or a PCSR_E_* code;
 // on PCSR_E_HIP *hip_err holds the hipError_t.  Synchronous.
 // clusters: where the rows turn out to form communities, S = 1 with items of kClusterItem and the schedule by community.
 constexpr int32_t kClusterItem = 1024;
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
-                 int32_t omega, bool validate, bool column_order, bool clusters, DeviceBuild *out, int *hip_err);
+                 int32_t omega, bool validate, bool column_order, bool clusters, Upload *late, DeviceBuild *out,
+                 int *hip_err);
 
 // Whether rows share more columns than chance has them: enqueues the count of a sample on the null stream (d_out: two
 // sums, zeros on entry), and what the sums say.  The arrays need not have been checked.

@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(kRowThreads) check_rows_kernel(int64_t n_rows,
     }
 }
 
-// Columns in range and ascending inside every row (check); the arrays copied (pcol, with V = 1).  One pass
+// Columns in range and ascending inside every row (check); the arrays copied (pcol, with V = 1; vals null: the columns alone).  One pass
 // for both: 16 M nonzeros 49 us (5.2 TB/s), where a check that met every row start on its own took 77 and the copies 45.
 __global__ void __launch_bounds__(kThreads) check_copy_kernel(int64_t n_rows, int64_t n_cols, int64_t nnz,
                                                               const int32_t *rowptr, const int32_t *colidx,
@@ -95,18 +95,13 @@ __global__ void __launch_bounds__(kThreads) check_copy_kernel(int64_t n_rows, in
     int4u c = {0, 0, 0, 0};
     if (t + kPerThread <= t1) {
         c = *reinterpret_cast<const int4u *>(colidx + t);
-        if (pcol) {
-            const float4u v = *reinterpret_cast<const float4u *>(vals + t);
-            *reinterpret_cast<int4u *>(pcol + t) = c;
-            *reinterpret_cast<float4u *>(pval + t) = v;
-        }
+        if (pcol) *reinterpret_cast<int4u *>(pcol + t) = c;
+        if (pcol && vals) *reinterpret_cast<float4u *>(pval + t) = *reinterpret_cast<const float4u *>(vals + t);
     } else {
         for (int k = 0; k < kPerThread && t + k < t1; ++k) {
             c[k] = colidx[t + k];
-            if (pcol) {
-                pcol[t + k] = c[k];
-                pval[t + k] = vals[t + k];
-            }
+            if (pcol) pcol[t + k] = c[k];
+            if (pcol && vals) pval[t + k] = vals[t + k];
         }
     }
     if (!check) return; // the whole grid
@@ -811,7 +806,8 @@ struct LabelsGuard { // what cluster_rows made, given back on scope exit
 
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
-                 int32_t omega, bool validate, bool column_order, bool clusters, DeviceBuild *out, int *hip_err)
+                 int32_t omega, bool validate, bool column_order, bool clusters, Upload *late, DeviceBuild *out,
+                 int *hip_err)
 {
     if (V != 1 && V != 2) return PCSR_E_UNSUPPORTED;
     if (omega == 0) omega = 64;
@@ -829,8 +825,8 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
     }
     Checked *d_check = nullptr, check;
     clusters = clusters && V == 1 && n_rows == n_cols && nnz > 0;
-    int rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, validate, clusters, pcol, pval, sc, &d_check, &check,
-                          hip_err);
+    int rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, late ? nullptr : d_vals, validate, clusters, pcol, pval, sc,
+                          &d_check, &check, hip_err);
     if (rc != PCSR_OK) return rc;
     LabelsGuard labels;
     if (clusters && cluster_probe_says(check.common, n_rows)) {
@@ -875,6 +871,7 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
         nnz_v = total;
         HIP_TRY(sc.alloc((void **)&pcol, sizeof(int32_t) * (nnz_v + 1)));
         HIP_TRY(sc.alloc((void **)&pval, sizeof(float) * (2 * nnz_v + 1)));
+        if (late) HIP_TRY(late->wait());
         if (nnz > 0) {
             hipLaunchKernelGGL(union_fill_kernel, dim3((unsigned)((nnz + kSlice - 1) / kSlice)), dim3(kThreads), 0, 0,
                                n_rows, nnz, d_rowptr, d_colidx, d_vals, shared_scan, prow, pcol, pval);
@@ -1006,6 +1003,7 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
             sc.release(q);
         prow = o.rowptr;
     }
+    out->vals_due = late && V == 1;
     out->rowptr = prow;
     out->colidx = pcol;
     out->val = pval;

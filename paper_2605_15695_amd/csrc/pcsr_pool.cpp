@@ -173,7 +173,7 @@ hipError_t pool_give_back(size_t *bytes)
 
 namespace {
 
-constexpr int kCopyThreads = 8;
+constexpr int kCopyThreads = 8, kBesideThreads = 4;
 constexpr size_t kPiece = size_t(1) << 20;
 
 struct Lane { // one copying thread's buffers and stream
@@ -184,18 +184,18 @@ struct Lanes {
     std::mutex mu;
     std::map<int, std::vector<Lane>> per_device;
 };
-Lanes &lanes()
+Lanes &lanes(bool beside) // of copies the caller waits for, of those beside its work
 {
-    static Lanes *l = new Lanes;
-    return *l;
+    static Lanes *l = new Lanes[2];
+    return l[beside];
 }
 
 // The lanes of a device, made on first use; empty if that failed.  Lanes::mu held.
-std::vector<Lane> &lanes_of(int dev)
+std::vector<Lane> &lanes_of(Lanes &all, int dev, int threads)
 {
-    std::vector<Lane> &v = lanes().per_device[dev];
+    std::vector<Lane> &v = all.per_device[dev];
     if (!v.empty()) return v;
-    std::vector<Lane> made(kCopyThreads);
+    std::vector<Lane> made(threads);
     bool ok = true;
     for (Lane &l : made)
         for (int b = 0; b < 2 && ok; ++b)
@@ -214,22 +214,24 @@ std::vector<Lane> &lanes_of(int dev)
     return v;
 }
 
-hipError_t staged(char *dst, const char *src, size_t bytes, bool to_host)
+hipError_t staged(char *dst, const char *src, size_t bytes, bool to_host, bool beside = false)
 {
     const hipMemcpyKind kind = to_host ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice;
     int dev = -1;
     if (bytes < kStagedBytes || hipGetDevice(&dev) != hipSuccess) return hipMemcpy(dst, src, bytes, kind);
-    std::unique_lock<std::mutex> lock(lanes().mu, std::try_to_lock);
+    Lanes &all = lanes(beside);
+    std::unique_lock<std::mutex> lock(all.mu, std::try_to_lock);
     if (!lock.owns_lock()) return hipMemcpy(dst, src, bytes, kind);
+    const int threads = beside ? kBesideThreads : kCopyThreads;
     Lane *ls = nullptr;
     try {
-        std::vector<Lane> &v = lanes_of(dev);
+        std::vector<Lane> &v = lanes_of(all, dev, threads);
         if (!v.empty()) ls = v.data();
     } catch (...) {
     }
     if (!ls) return hipMemcpy(dst, src, bytes, kind);
     // like hipMemcpy, after everything enqueued on the null stream
-    hipError_t e = hipStreamSynchronize(nullptr);
+    hipError_t e = beside ? hipSuccess : hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return e;
     std::atomic<int> failed{hipSuccess};
     const size_t pieces = (bytes + kPiece - 1) / kPiece;
@@ -246,7 +248,7 @@ hipError_t staged(char *dst, const char *src, size_t bytes, bool to_host)
             if (to_host && w == hipSuccess) std::memcpy(dst + wait[k] * kPiece, l.pin[k], size(wait[k]));
             wait[k] = pieces;
         };
-        for (size_t p = t; p < pieces && r == hipSuccess; p += kCopyThreads, b ^= 1) {
+        for (size_t p = t; p < pieces && r == hipSuccess; p += threads, b ^= 1) {
             settle(b);
             if (r != hipSuccess) break;
             const size_t at = p * kPiece;
@@ -263,7 +265,7 @@ hipError_t staged(char *dst, const char *src, size_t bytes, bool to_host)
         if (r != hipSuccess) failed = r;
     };
     std::vector<std::thread> th;
-    const int n = (int)std::min<size_t>(kCopyThreads, pieces);
+    const int n = (int)std::min<size_t>(threads, pieces);
     try {
         for (int t = 1; t < n; ++t) th.emplace_back(work, t);
     } catch (...) { // no more threads: what they would have moved is moved here
@@ -285,6 +287,52 @@ hipError_t copy_to_host(void *dst, const void *src, size_t bytes)
 hipError_t copy_to_device(void *dst, const void *src, size_t bytes)
 {
     return staged(static_cast<char *>(dst), static_cast<const char *>(src), bytes, false);
+}
+
+void Upload::start(void *dst, const void *src, size_t bytes) noexcept
+{
+    result = wait();
+    if (result != hipSuccess || bytes == 0) return;
+    int dev = -1;
+    if (bytes >= kStagedBytes && hipGetDevice(&dev) == hipSuccess) {
+        try {
+            thread = std::thread([=] {
+                result = hipSetDevice(dev);
+                if (result == hipSuccess)
+                    result = staged(static_cast<char *>(dst), static_cast<const char *>(src), bytes, false, true);
+            });
+            return;
+        } catch (...) { // no thread
+        }
+    }
+    result = copy_to_device(dst, src, bytes);
+}
+
+hipError_t Upload::wait() noexcept
+{
+    if (thread.joinable()) thread.join();
+    return result;
+}
+
+void PageToucher::start(void *p, size_t bytes) noexcept
+{
+    constexpr size_t kPage = 4096, kThreads = 4;
+    if (bytes < kStagedBytes) return;
+    char *const at = static_cast<char *>(p);
+    try {
+        for (size_t t = 0; t < kThreads; ++t)
+            threads.emplace_back([=] {
+                const size_t end = bytes / kThreads * (t + 1);
+                for (size_t i = bytes / kThreads * t; i < end; i += kPage) __atomic_fetch_or(at + i, 0, __ATOMIC_RELAXED);
+            });
+    } catch (...) { // no more threads: the faults are taken later
+    }
+}
+
+void PageToucher::wait() noexcept
+{
+    for (std::thread &t : threads) t.join();
+    threads.clear();
 }
 
 } // namespace pcsr

@@ -7,6 +7,8 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <thread>
+#include <vector>
 
 namespace pcsr {
 
@@ -39,6 +41,38 @@ hipError_t pool_give_back(size_t *bytes);
 constexpr size_t kStagedBytes = size_t(4) << 20;
 hipError_t copy_to_host(void *dst, const void *src, size_t bytes);
 hipError_t copy_to_device(void *dst, const void *src, size_t bytes);
+
+// copy_to_device beside what the caller does meanwhile, on threads (half as many) and pinned buffers of its own.
+// Nothing enqueued may still use dst; src has to stay until wait() (or the destructor) returns.  Where no thread is to be had the
+// copy is made by start().
+class Upload {
+public:
+    Upload() = default;
+    Upload(const Upload &) = delete;
+    Upload &operator=(const Upload &) = delete;
+    ~Upload() { (void)wait(); }
+    void start(void *dst, const void *src, size_t bytes) noexcept;
+    hipError_t wait() noexcept;
+
+private:
+    std::thread thread;
+    hipError_t result = hipSuccess;
+};
+
+// Takes the page faults of host memory that is about to be written, on four threads beside what the caller does
+// meanwhile: fresh pages of two 41 MB arrays cost a download 0.7 of 2.6 ms.  Contents do not change.
+class PageToucher {
+public:
+    PageToucher() = default;
+    PageToucher(const PageToucher &) = delete;
+    PageToucher &operator=(const PageToucher &) = delete;
+    ~PageToucher() { wait(); }
+    void start(void *p, size_t bytes) noexcept;
+    void wait() noexcept;
+
+private:
+    std::vector<std::thread> threads;
+};
 
 } // namespace pcsr
 

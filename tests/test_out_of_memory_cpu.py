@@ -168,3 +168,29 @@ for params in (dict(V=1), dict(V=2, S=1, SG=4), dict(V=1, S=1, SG=4, flags=pc.PC
         assert rc in (0, binding.PCSR_E_OOM), (params, bad, rc)
         assert fake.fake_hip_live() == 0, (params, bad)
 """)
+
+
+# large enough for the values to follow on threads of their own: the build gives up, or ends, while they do
+@pytest.mark.parametrize("k", [0, 2, 3, 4, 5])
+def test_values_still_under_way_when_the_build_ends(fake, k):
+    _run(fake, f"""
+n = 150_000
+colidx = np.tile(colidx, n // 30000)
+rowptr = np.arange(0, n * deg + 1, deg, dtype=np.int32)
+vals = rng.random(n * deg).astype(np.float32)              # 4.8 MB
+assert vals.nbytes >= 4 << 20
+host = pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(flags=pc.PCSR_FLAG_HOST_ONLY, **kw))
+if {k}:
+    fake.fake_hip_fail({k}, {k})
+    h = pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(**kw))
+    assert same(h, host)
+    h.close()
+else:
+    bad = rowptr.copy()
+    bad[7] = bad[8] + 1
+    try:
+        pc.pcsr_build(n, n, bad, colidx, vals, pc.make_params(**kw))
+        assert False
+    except pc.PcsrError as e:
+        assert e.code == binding.PCSR_E_BAD_CSR
+""")
