@@ -100,16 +100,22 @@ template <int VEC> __device__ __forceinline__ void store_vec(float *p, const flo
     }
 }
 
-// Elementwise tail of a row of C, columns k .. k + VEC - 1.  One uniform branch for a plain SpMM.
-template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, long row, int K, int k, float (&v)[VEC])
+// Elementwise tail of a row of C, columns k .. k + VEC - 1, in two parts: what it reads of that row, which can be
+// requested long before the row is there, and what it does.  One uniform branch for a plain SpMM.
+template <int VEC> struct TailRow {
+    float self[VEC], mask[VEC];
+};
+template <int VEC> __device__ __forceinline__ void fetch_tail(const Epilogue &ep, long row, int K, int k, TailRow<VEC> &t)
 {
-    if (!ep.on) return;
+    if (ep.self) load_vec<VEC>(ep.self + row * K + k, t.self);
+    if (ep.mask) load_vec<VEC>(ep.mask + row * K + k, t.mask);
+}
+template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, int k, const TailRow<VEC> &t, float (&v)[VEC])
+{
     if (ep.self) {
         const float scale = 1.0f + (ep.self_eps ? *ep.self_eps : 0.0f);
-        float t[VEC];
-        load_vec<VEC>(ep.self + row * K + k, t);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = fmaf(scale, t[e], v[e]);
+        for (int e = 0; e < VEC; ++e) v[e] = fmaf(scale, t.self[e], v[e]);
     }
     if (ep.bias) {
 #pragma unroll
@@ -120,11 +126,16 @@ template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, lo
         for (int e = 0; e < VEC; ++e) v[e] = v[e] <= 0.0f ? 0.0f : v[e];
     }
     if (ep.mask) {
-        float t[VEC];
-        load_vec<VEC>(ep.mask + row * K + k, t);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = t[e] <= 0.0f ? 0.0f : v[e];
+        for (int e = 0; e < VEC; ++e) v[e] = t.mask[e] <= 0.0f ? 0.0f : v[e];
     }
+}
+template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, long row, int K, int k, float (&v)[VEC])
+{
+    if (!ep.on) return;
+    TailRow<VEC> t;
+    fetch_tail<VEC>(ep, row, K, k, t);
+    finish<VEC>(ep, k, t, v);
 }
 
 // cacheable store: workspace partials are read back by the next kernel
@@ -337,6 +348,24 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
 
     const long K = a.K;
 
+    // What the tail reads is requested before the traversal, where it fits the registers: behind it, it is one more round trip
+    // to memory for an item that is three of them in all (road graph of 2,000,000 rows with a self term: K = 64 304 -> 292
+    // us, K = 16 106 -> 98).  Items of balanced handles have too many registers in flight for it (R-MAT 2^20, K = 64: 420 ->
+    // 447).
+    constexpr bool EARLY = EPI && !S && V * REP * VEC <= 8;
+    TailRow<VEC> tail_row[EARLY ? V : 1][EARLY ? REP : 1];
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const long row = (long)panel * V + v;
+            if (row < a.n_rows) {
+#pragma unroll
+                for (int r = 0; r < REP; ++r)
+                    if (kv[r]) fetch_tail<VEC>(a.epi, row, a.K, kc[r], tail_row[v][r]);
+            }
+        }
+    }
+
     // one lane's entries of the chunk that starts at `base` (zeros past the end of the range)
     auto load_entry = [&](int base, int (&c)[NH], float (&av)[NH][V]) {
 #pragma unroll
@@ -480,7 +509,10 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
             for (int r = 0; r < REP; ++r) {
                 if (kv[r]) {
                     if (sole) {
-                        if constexpr (EPI) finish<VEC>(a.epi, row, a.K, kc[r], acc[v][r]);
+                        if constexpr (EARLY)
+                            finish<VEC>(a.epi, kc[r], tail_row[v][r], acc[v][r]);
+                        else if constexpr (EPI)
+                            finish<VEC>(a.epi, row, a.K, kc[r], acc[v][r]);
                         store_vec<VEC>(crow + kc[r], acc[v][r]);
                     } else if (wrow) {
                         store_vec_cached<VEC>(crow + kc[r], acc[v][r]);
