@@ -981,34 +981,86 @@ __global__ void __launch_bounds__(256) zero_panels_kernel(const int32_t *__restr
     }
 }
 
-// One thread per VEC consecutive elements (q, v, k..k+VEC) of the rows of split panels.  The
-// partial rows of panel q sit in consecutive workspace slots in item order and are added in
-// that order, whatever the grid looks like, so the balanced result is the same bits on
-// every run.  Panels with more than `skip_above` slots are left to reduce_long_kernel.
-template <int VEC>
-__global__ void __launch_bounds__(256) reduce_split_kernel(const int32_t *__restrict__ split_panels,
-                                                           const int32_t *__restrict__ split_slot,
-                                                           long n_split, int V, const float *__restrict__ ws,
-                                                           float *C, int n_rows, int K, int skip_above,
-                                                           Epilogue epi)
+struct ReduceArgs {
+    const int32_t *split_panels, *split_slot, *long_panels;
+    int64_t n_split;
+    int32_t long_blocks, long_chunks; // workgroups of the long panels; per row of one
+    int32_t lanes_log2, chunks;       // of the others: lanes to a row (in vectors), workgroups that share its width
+    int32_t V, n_rows, K;
+    const float *ws;
+    float *C;
+    Epilogue epi;
+};
+
+// Second pass of the balanced write-back.  Long panels (a hub row of a power-law graph is cut into thousands of items)
+// take the first workgroups: one per (row, 16 vectors of C), 16 threads per vector.  Thread j of a vector adds slots j, j+16,
+// j+32, ... in ascending order, then the 16 partial sums are added in ascending j.  Of the other split panels a thread takes
+// VEC consecutive elements of a row and adds its slots in item order.  Both orders depend on the slot numbers alone, so the
+// balanced result is the same bits on every run and for every schedule.
+// One launch for both, so that the long panels' serial sums run beside the others' traffic: R-MAT 2^22, K = 16 34 + 25 us as
+// two, 39 as one; 2^20, K = 64 18 + 9, 18.  At K = 512 (8.8 GB, 5.1 TB/s) it is 1.72 ms either way.
+template <int VEC> __global__ void __launch_bounds__(256) reduce_kernel(ReduceArgs a)
 {
-    const int kv = (K + VEC - 1) / VEC; // vectors per row, the last one moved back to end with it
-    const long total = n_split * V * (long)kv;
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= total) return;
-    const long r = t / kv;
-    const int k = min((int)(t - r * kv) * VEC, K - VEC);
-    const long q = r / V;
-    const int v = (int)(r - q * V);
-    const long row = (long)split_panels[q] * V + v;
-    if (row >= n_rows) return;
-    const long s0 = split_slot[q], s1 = split_slot[q + 1];
-    if (s1 - s0 > skip_above) return;
-    const long stride = (long)V * K;
-    const float *w = ws + (s0 * V + v) * (long)K + k;
+    __shared__ float part[kLongReduceLanes][16][VEC];
+    const int vectors = (a.K + VEC - 1) / VEC; // per row, the last one moved back to end with it
+    const long stride = (long)a.V * a.K;
     float sum[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) sum[e] = 0.0f;
+
+    if ((int)blockIdx.x < a.long_blocks) { // uniform
+        const int c = threadIdx.x % 16, j = threadIdx.x / 16;
+        const int r = blockIdx.x / a.long_chunks, at = (blockIdx.x - r * a.long_chunks) * 16 + c;
+        const int q = a.long_panels[r / a.V], v = r % a.V;
+        const long row = (long)a.split_panels[q] * a.V + v;
+        if (row >= a.n_rows) return; // the whole workgroup leaves: no barrier is skipped by a part of it
+        const bool live = at < vectors;
+        const int k = min(at * VEC, a.K - VEC);
+        const long s0 = a.split_slot[q], s1 = a.split_slot[q + 1];
+        const long step = kLongReduceLanes * stride;
+        if (live) {
+            long jj = s0 + j;
+            const float *w = a.ws + (jj * a.V + v) * (long)a.K + k;
+            for (; jj + 3 * kLongReduceLanes < s1; jj += 4 * kLongReduceLanes, w += 4 * step) {
+                float t4[4][VEC];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) load_vec<VEC>(w + u * step, t4[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) sum[e] += t4[u][e];
+            }
+            for (; jj < s1; jj += kLongReduceLanes, w += step) {
+                float t1[VEC];
+                load_vec<VEC>(w, t1);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) sum[e] += t1[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) part[j][c][e] = sum[e];
+        __syncthreads();
+        if (j == 0 && live) {
+            for (int jj = 1; jj < kLongReduceLanes; ++jj)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) sum[e] += part[jj][c][e];
+            finish<VEC>(a.epi, row, a.K, k, sum);
+            store_vec<VEC>(a.C + row * a.K + k, sum);
+        }
+        return;
+    }
+
+    const int b = blockIdx.x - a.long_blocks, group = b / a.chunks; // uniform
+    const int at = ((b - group * a.chunks) << a.lanes_log2) + (threadIdx.x & ((1 << a.lanes_log2) - 1));
+    const long r = ((long)group << (8 - a.lanes_log2)) + (threadIdx.x >> a.lanes_log2);
+    const long q = a.V == 1 ? r : r >> 1;
+    const int v = a.V == 1 ? 0 : (int)(r & 1);
+    if (q >= a.n_split || at >= vectors) return;
+    const int k = min(at * VEC, a.K - VEC);
+    const long row = (long)a.split_panels[q] * a.V + v;
+    const long s0 = a.split_slot[q], s1 = a.split_slot[q + 1];
+    if (row >= a.n_rows || (a.long_blocks && s1 - s0 > kLongPanelSlots)) return;
+    const float *w = a.ws + (s0 * a.V + v) * (long)a.K + k;
     long j = s0;
     for (; j + 4 <= s1; j += 4, w += 4 * stride) { // four loads in flight, adds in item order
         float t4[4][VEC];
@@ -1025,65 +1077,8 @@ __global__ void __launch_bounds__(256) reduce_split_kernel(const int32_t *__rest
 #pragma unroll
         for (int e = 0; e < VEC; ++e) sum[e] += t1[e];
     }
-    finish<VEC>(epi, row, K, k, sum);
-    store_vec<VEC>(C + row * K + k, sum);
-}
-
-// Split panels with many partial rows (a hub row of a power-law graph is cut into thousands
-// of items): one workgroup per (panel row, 16 vectors of C), 16 threads per vector.  Thread
-// j of a vector adds slots j, j+16, j+32, ... in ascending order, then the 16 partial sums
-// are added in ascending j.  The order depends on the slot numbers alone, so the result is
-// again the same bits on every run and for every schedule.
-template <int VEC>
-__global__ void __launch_bounds__(256) reduce_long_kernel(const int32_t *__restrict__ long_panels,
-                                                          const int32_t *__restrict__ split_panels,
-                                                          const int32_t *__restrict__ split_slot, int V,
-                                                          const float *__restrict__ ws, float *C, int n_rows,
-                                                          int K, Epilogue epi)
-{
-    __shared__ float part[kLongReduceLanes][16][VEC];
-    const int c = threadIdx.x % 16, j = threadIdx.x / 16;
-    const long r = blockIdx.x;
-    const long q = long_panels[r / V];
-    const int v = (int)(r % V);
-    const long row = (long)split_panels[q] * V + v;
-    if (row >= n_rows) return; // the whole workgroup leaves: no barrier is skipped by a part of it
-    const bool live = ((int)blockIdx.y * 16 + c) * VEC < K;
-    const int k = min(((int)blockIdx.y * 16 + c) * VEC, K - VEC);
-    const long s0 = split_slot[q], s1 = split_slot[q + 1];
-    const long stride = (long)V * K, step = kLongReduceLanes * stride;
-    float sum[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) sum[e] = 0.0f;
-    if (live) {
-        long jj = s0 + j;
-        const float *w = ws + (jj * V + v) * (long)K + k;
-        for (; jj + 3 * kLongReduceLanes < s1; jj += 4 * kLongReduceLanes, w += 4 * step) {
-            float t4[4][VEC];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) load_vec<VEC>(w + u * step, t4[u]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) sum[e] += t4[u][e];
-        }
-        for (; jj < s1; jj += kLongReduceLanes, w += step) {
-            float t1[VEC];
-            load_vec<VEC>(w, t1);
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) sum[e] += t1[e];
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) part[j][c][e] = sum[e];
-    __syncthreads();
-    if (j == 0 && live) {
-        for (int jj = 1; jj < kLongReduceLanes; ++jj)
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) sum[e] += part[jj][c][e];
-        finish<VEC>(epi, row, K, k, sum);
-        store_vec<VEC>(C + row * K + k, sum);
-    }
+    finish<VEC>(a.epi, row, a.K, k, sum);
+    store_vec<VEC>(a.C + row * a.K + k, sum);
 }
 
 using KernelFn = void (*)(SpmmArgs);
@@ -1338,28 +1333,31 @@ hipError_t launch_reduce_split(const int32_t *split_panels, const int32_t *split
                                int32_t n_rows, int32_t K, const Epilogue &epi, hipStream_t stream)
 {
     if (n_split <= 0) return hipSuccess;
-    const int vec = K >= 4 ? 4 : 1;
-    const long total = n_split * V * (long)((K + vec - 1) / vec);
-    const long blocks = (total + 255) / 256;
-    if (blocks > 0x7fffffffL || n_long * V > 0x7fffffffL) return hipErrorInvalidValue;
-    const int skip_above = n_long > 0 ? kLongPanelSlots : 0x7fffffff;
+    const int vec = K >= 4 ? 4 : 1, vectors = (K + vec - 1) / vec;
+    ReduceArgs a;
+    a.split_panels = split_panels;
+    a.split_slot = split_slot;
+    a.long_panels = long_panels;
+    a.n_split = n_split;
+    a.long_chunks = (vectors + 15) / 16;
+    a.lanes_log2 = 0;
+    while (a.lanes_log2 < 6 && (1 << a.lanes_log2) < vectors) ++a.lanes_log2;
+    a.chunks = (vectors + (1 << a.lanes_log2) - 1) >> a.lanes_log2;
+    a.V = V;
+    a.n_rows = n_rows;
+    a.K = K;
+    a.ws = ws;
+    a.C = C;
+    a.epi = epi;
+    const int rows = 256 >> a.lanes_log2; // of a workgroup
+    const int64_t long_blocks = n_long > 0 ? n_long * V * a.long_chunks : 0;
+    const int64_t blocks = long_blocks + (n_split * V + rows - 1) / rows * a.chunks;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    a.long_blocks = (int32_t)long_blocks;
     if (vec == 4)
-        hipLaunchKernelGGL(reduce_split_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, stream, split_panels,
-                           split_slot, (long)n_split, V, ws, C, n_rows, K, skip_above, epi);
+        hipLaunchKernelGGL(reduce_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
     else
-        hipLaunchKernelGGL(reduce_split_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, stream, split_panels,
-                           split_slot, (long)n_split, V, ws, C, n_rows, K, skip_above, epi);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || n_long <= 0) return e;
-    const int chunks = ((K + vec - 1) / vec + 15) / 16; // 16 vectors of C per workgroup
-    if (chunks > 65535) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(n_long * V), (unsigned)chunks);
-    if (vec == 4)
-        hipLaunchKernelGGL(reduce_long_kernel<4>, grid, dim3(16 * kLongReduceLanes), 0, stream, long_panels,
-                           split_panels, split_slot, V, ws, C, n_rows, K, epi);
-    else
-        hipLaunchKernelGGL(reduce_long_kernel<1>, grid, dim3(16 * kLongReduceLanes), 0, stream, long_panels,
-                           split_panels, split_slot, V, ws, C, n_rows, K, epi);
+        hipLaunchKernelGGL(reduce_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
