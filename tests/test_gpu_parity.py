@@ -185,6 +185,36 @@ def test_column_window_kernel(name, V, wc):
     h.close()
 
 
+@pytest.mark.parametrize("n,K,kern", [(150, 64, None), (500, 200, None), (1337, 24, (4, 1, 1, 2)),
+                                      (2000, 65, (16, 1, 1, 4)), (2600, 1030, (8, 2, 1, 16)),
+                                      (5003, 320, None), (5003, 36, (16, 4, 2, 1)), (19950, 64, None)])
+def test_window_blocks_and_slices(n, K, kern):
+    """Blocks x slices below, at and past multiples of the 8 XCDs and of their compute units, a last window that ends
+    outside the matrix, workgroups of few and many wavefronts; the same bits in the hardware's order of workgroups."""
+    rng = np.random.default_rng(n + K)
+    base = np.arange(n) // 150 * 150                       # communities of 150, 20 entries inside, 2 anywhere
+    cols = np.concatenate([base[:, None] + rng.integers(0, 150, (n, 20)), rng.integers(0, n, (n, 2))], axis=1) % n
+    cols = [np.unique(c) for c in cols]
+    rp = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+    ci = np.concatenate(cols).astype(np.int32)
+    va = rng.standard_normal(len(ci)).astype(np.float32)
+    B = rng.standard_normal((n, K)).astype(np.float32)
+    ref, bound = oracle.spmm(rp, ci, va, B)
+    Bd = torch.from_numpy(B).cuda()
+    got = []
+    for flags in (0, pc.PCSR_FLAG_NO_XCD_REMAP):
+        h = pc.pcsr_build(n, n, rp, ci, va, pc.make_params(col_window=256, flags=flags))
+        if kern:
+            pc.pcsr_set_kernel_params(h, *kern)
+        print(f"case window blocks n={n} K={K} {pc.pcsr_query_launch(h, K)} {pc.pcsr_window_stats(h)}", flush=True)
+        C = torch.full((n, K), float("nan"), dtype=torch.float32, device="cuda")
+        pc.pcsr_spmm(h, Bd, C, K)
+        got.append(C.cpu().numpy())
+        h.close()
+    _check(got[0], ref, bound, f"window blocks n={n} K={K}")
+    assert np.array_equal(got[0], got[1])
+
+
 def test_column_window_edges():
     """Window wider than the matrix, last block partly filled, odd row count with V = 2."""
     rng = np.random.default_rng(11)
