@@ -187,6 +187,38 @@ int64_t grid_for(pcsr_handle_t h, int waves, int lpr, int ipg)
     return 8 * ((longest + items_per_wg - 1) / items_per_wg);
 }
 
+// Column-window launches: a compute unit holds one or two workgroups, each of a whole (block, slice) pair, so the
+// last round of them leaves most of the chip idle (1056 pairs on 256 compute units: 4 rounds and an eighth).  Its
+// pairs are cut into `parts` workgroups of as many items less, each staging the window again: a part costs 1/parts
+// of a whole one and 0.15 for the staging, and the cheapest number of rounds is taken, if it beats one whole round.
+// Communities of 500 rows of 48, us whole / cut: 250,000 rows K = 64 120 / 96, 128 181 / 173, 256 352 / 341, 512
+// 730 / 720; 60,000 rows K = 64 44 / 28, 192 85 / 69.  Where the last round is nearly full no cut pays (60,000 rows,
+// K = 512: 171 whole, 172 in 2, 190 in 8) and the rule takes none.  Not for blocks of fewer items than a
+// workgroup's 64 lane groups, which a part would leave idle.
+void window_tail(pcsr_handle_t h, pcsr::LaunchShape *ls)
+{
+    ls->win_whole = 0x7fffffff;
+    ls->win_parts = 1;
+    const int64_t pairs = (int64_t)ls->grid_x * ls->grid_y;
+    if ((h->flags & PCSR_FLAG_NO_XCD_REMAP) || pairs == 0 || pairs > (1 << 20)) return;
+    const int64_t at_once = 32 * std::max(1, std::min(160 * 1024 / ls->lds_bytes, 16 / ls->waves)); // of an XCD
+    const int64_t most = (pairs + 7) / 8, rest = most % at_once;
+    int parts = 1;
+    double best = 1.15;
+    for (int p = 2; rest && p <= 8; ++p) {
+        const double cost = (double)((rest * p + at_once - 1) / at_once) * (1.0 / p + 0.15);
+        if (cost < best - 0.05) {
+            best = cost;
+            parts = p;
+        }
+    }
+    if (parts == 1 || h->host.M < pairs / ls->grid_y * 64) return;
+    ls->win_whole = (int32_t)(most - rest);
+    ls->win_parts = parts;
+    ls->k_grid_x = (int32_t)(8 * (most - rest + rest * parts));
+    ls->k_grid_y = 1;
+}
+
 // Launch shape for width K under the handle's kernel parameters ("0 = auto" resolved).
 // epilogue: for pcsr_spmm_epilogue, whose kernels exist for the auto shapes only; a handle with
 // another shape of its own uses those.
@@ -267,6 +299,7 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     ls->k_rep = rep;
     ls->k_grid_x = ls->grid_x;
     ls->k_grid_y = ls->grid_y;
+    if (ls->window) window_tail(h, ls);
     // Where the shape above reads rows badly another one is launched in its place, with wide loads
     // at 4-byte addresses (pcsr_select's, carried in the flags, or this function's own pick for an
     // auto shape; never where the caller asked for lanes or vectors): widths that are no
@@ -772,6 +805,9 @@ static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, co
     a.win_lo = h->d_win_lo;
     a.win_hi = h->d_win_hi;
     a.n_cols = (int32_t)h->host.n_cols;
+    a.n_slices = ls.grid_y;
+    a.win_whole = ls.win_whole;
+    a.win_parts = ls.win_parts;
     a.epi = epi;
     if (!hip_ok(pcsr::launch_spmm(h->host.V, h->host.S, ls, a, s))) return PCSR_E_HIP;
     if (two_pass) {

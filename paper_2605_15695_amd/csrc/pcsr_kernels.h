@@ -47,6 +47,9 @@ struct SpmmArgs {
     const int32_t *win_hi;    // window (an empty range when the block has none)
     int32_t win_cols;         // rows of B staged in LDS
     int32_t n_cols;
+    int32_t n_slices;  // column slices of a block (window kernel only)
+    int32_t win_whole; // (block, slice) pairs an XCD takes whole; the rest run as win_parts workgroups each
+    int32_t win_parts;
     Epilogue epi;
 };
 
@@ -60,6 +63,7 @@ struct LaunchShape {
     // What is launched in place of that shape where it reads rows badly: wide loads at 4-byte
     // addresses (see resolve_launch).  The same shape everywhere else.
     int32_t k_lpr, k_vec, k_rep, k_grid_x, k_grid_y;
+    int32_t win_whole, win_parts; // as SpmmArgs (window only)
 };
 
 bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg);

@@ -706,21 +706,37 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
     // side on one XCD and its colIdx/val stream comes from that L2 for all but the first (one block after another per
     // slice read it from memory each time: sbm, 250,000 rows of 48, K = 256: 17.5 M lines from memory for 14.7 M now,
     // 395 us for 380).  Workgroups go round-robin over the XCDs in the order of their linear index.
-    int bid = blockIdx.x, slice = blockIdx.y;
+    // The pairs past a.win_whole, fewer than the XCD's compute units hold at once, are cut into a.win_parts each
+    // (window_tail says when).
+    int bid = blockIdx.x, slice = blockIdx.y, part = 0, parts = 1;
     if (a.xcd_remap) {
-        const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, total = gridDim.x * gridDim.y;
+        const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, total = (unsigned)a.nblk * a.n_slices;
         const unsigned x = id & 7, q = total >> 3, r = total & 7;
-        const unsigned pair = x * q + (x < r ? x : r) + (id >> 3);
-        bid = pair / gridDim.y;
-        slice = pair - bid * gridDim.y;
+        unsigned pair = id >> 3;
+        if (pair >= (unsigned)a.win_whole) {
+            const unsigned t = pair - a.win_whole;
+            parts = a.win_parts;
+            pair = a.win_whole + t / parts;
+            part = t % parts;
+            if (pair >= q + (x < r)) return; // an XCD of one pair less than the others
+        }
+        pair += x * q + (x < r ? x : r);
+        bid = pair / a.n_slices;
+        slice = pair - bid * a.n_slices;
     }
     const int lg = lane & (LPR - 1);
     const int kbase = slice * TW;
     const float *__restrict__ B = a.B;
     const long K = a.K;
 
-    const int item_begin = a.win_ptr[bid];
-    const int item_end = a.win_ptr[bid + 1];
+    int item_begin = a.win_ptr[bid];
+    int item_end = a.win_ptr[bid + 1];
+    if (parts > 1) {
+        const int n = item_end - item_begin;
+        item_end = item_begin + (int)((long)n * (part + 1) / parts);
+        item_begin += (int)((long)n * part / parts);
+        if (item_begin == item_end) return;
+    }
     const int stride = waves * G;
     int item = item_begin + wave * G + lane / LPR;
     // the first item's ranges are requested before the window is staged
@@ -1297,7 +1313,7 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
                 }
             }
         }
-        hipLaunchKernelGGL(fn, dim3(ls.grid_x, ls.grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);
+        hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);
         return hipGetLastError();
     }
     KernelFn fn = args.epi.on && ls.ipg <= 1 ? pick_epilogue(V, S, ls.k_lpr, ls.k_vec, ls.k_rep)

@@ -190,7 +190,8 @@ def test_column_window_kernel(name, V, wc):
                                       (5003, 320, None), (5003, 36, (16, 4, 2, 1)), (19950, 64, None)])
 def test_window_blocks_and_slices(n, K, kern):
     """Blocks x slices below, at and past multiples of the 8 XCDs and of their compute units, a last window that ends
-    outside the matrix, workgroups of few and many wavefronts; the same bits in the hardware's order of workgroups."""
+    outside the matrix, workgroups of few and many wavefronts; the same bits in the hardware's order of workgroups,
+    where no block is cut into parts."""
     rng = np.random.default_rng(n + K)
     base = np.arange(n) // 150 * 150                       # communities of 150, 20 entries inside, 2 anywhere
     cols = np.concatenate([base[:, None] + rng.integers(0, 150, (n, 20)), rng.integers(0, n, (n, 2))], axis=1) % n
