@@ -45,7 +45,7 @@ def kernel_instance(V: int, S: int, launch: dict) -> str:
     """Name of the SpMM kernel instance as rocprofv3 prints it."""
     shape = f"{launch['lanes_per_row']}, {launch['vec']}, {launch['rep']}"
     if launch["lds_bytes"]:
-        return f"spmm_window_kernel<{V}, {shape}>"
+        return f"spmm_window_kernel<{V}, {shape}, {'true' if S else 'false'}>"  # true: windows of communities
     if launch["items_per_group"] > 1:
         return f"spmm_batched_kernel<{V}, {shape}, {launch['items_per_group']}>"
     return f"spmm_kernel<{V}, {'true' if S else 'false'}, {shape}, false>"  # false: no elementwise tail

@@ -63,7 +63,10 @@ enum {
                                   vectors and a schedule that runs the rows of a community one after
                                   another, dealt to the 8 XCDs as contiguous ranges of equal work
                                   (items of longer rows first, in column order), and its kernel
-                                  parameters are set to auto.  Otherwise the flag does nothing   */
+                                  parameters are set to auto.  Otherwise the flag does nothing.
+                                  Where pcsr_select finds it worth a second copy of the nonzeros,
+                                  products of 64 columns or more (a multiple of 4, parameters on
+                                  auto) stage the community's rows of B in LDS                   */
     PCSR_FLAG_ATOMIC_SPLIT = 32 /* S = 1 only: panels that were split accumulate into C with
                                   fp32 atomics, as Algorithm 2 prints it, instead of the
                                   default two-pass write-back (see pcsr_spmm)                 */

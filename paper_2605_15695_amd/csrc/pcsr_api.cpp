@@ -17,6 +17,8 @@
 
 namespace {
 
+// Columns from which a handle with windows of communities uses them (250,000 rows of 48: K = 64 146 -> 110 us, 128 262 -> 183).
+constexpr int kRowsLeast = 64;
 constexpr uint32_t kMagic = 0x50435352u; // "PCSR"
 
 // Bits of pcsr_params_t.flags in which pcsr_select passes a shape to launch in place of the one in
@@ -29,6 +31,7 @@ constexpr int32_t kWidePair = 8 << kWideShift;
 constexpr int32_t kWideTwice = 16 << kWideShift;
 constexpr int kWideForShift = 21;
 constexpr int32_t kWideFor = 127 << kWideForShift;
+constexpr int32_t kClusterWindows = 1 << 28; // with PCSR_FLAG_CLUSTER_IF_USEFUL: windows of communities too (pcsr_select)
 constexpr int32_t kWideBits = kWideShape | kWidePair | kWideTwice | kWideFor;
 
 int32_t stands_for(int lanes, int vec, int rep)
@@ -101,6 +104,7 @@ struct pcsr_handle_s {
     int32_t *d_win_hi = nullptr;
     int64_t n_win_blocks = 0;
     bool clustered = false; // scheduled community by community (PCSR_FLAG_CLUSTER_IF_USEFUL)
+    decltype(pcsr::DeviceBuild::win) win; // of such a handle: windows of communities (blocks 0: none)
     int64_t n_split = 0;
     int64_t n_split_items = 0; // workspace slots: items that belong to split panels
     float *d_ws = nullptr;     // partial rows of those items, grown on demand
@@ -115,7 +119,8 @@ inline bool valid(pcsr_handle_t h) { return h && h->magic == kMagic; }
 void release_device(pcsr_handle_t h)
 {
     void *const all[] = {h->d_rowptr, h->d_colidx,     h->d_val,  h->d_trow, h->d_split,   h->d_item_slot, h->d_sched,
-                         h->d_split_slot, h->d_long, h->d_win,  h->d_win_ptr, h->d_win_lo, h->d_win_hi, h->d_ws};
+                         h->d_split_slot, h->d_long, h->d_win,  h->d_win_ptr, h->d_win_lo, h->d_win_hi, h->d_ws,
+                         h->win.rowptr, h->win.colidx, h->win.val, h->win.rows, h->win.ptr, h->win.hi};
     // the blocks are handed out again at once, so nothing may still be using them
     const bool idle = h->device >= 0 && pcsr::pool_quiesce(h->device);
     for (void *p : all) idle ? pcsr::pool_free(p) : pcsr::pool_release(p);
@@ -124,6 +129,7 @@ void release_device(pcsr_handle_t h)
     h->d_win_lo = h->d_win_hi = nullptr;
     h->d_val = h->d_ws = nullptr;
     h->ws_bytes = 0;
+    h->win = {};
 }
 
 template <class T> int upload(const std::vector<T> &src, T **dst)
@@ -225,6 +231,20 @@ void window_tail(pcsr_handle_t h, pcsr::LaunchShape *ls)
 int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilogue = false)
 {
     if (K <= 0) return PCSR_E_UNSUPPORTED;
+    if (h->win.blocks && K >= kRowsLeast && K % 4 == 0 && !(h->lpr || h->vec || h->rep || h->waves || h->ipg)) {
+        const int tile = pcsr::kRowsLanes * pcsr::kRowsVec, gy = (K + tile - 1) / tile;
+        if (gy > 65535) return PCSR_E_TOO_LARGE;
+        ls->lpr = ls->k_lpr = pcsr::kRowsLanes;
+        ls->vec = ls->k_vec = pcsr::kRowsVec;
+        ls->rep = ls->k_rep = ls->ipg = 1;
+        ls->waves = 16;
+        ls->window = 1;
+        ls->lds_bytes = (pcsr::kRowsMost + 1) * (tile + 4) * 4;
+        ls->grid_x = ls->k_grid_x = (int32_t)h->win.blocks;
+        ls->grid_y = ls->k_grid_y = gy;
+        window_tail(h, ls);
+        return PCSR_OK;
+    }
     const bool plain = h->host.win_cols == 0 && h->ipg <= 1;
     const bool own = !(epilogue && plain && (h->lpr || h->vec || h->rep));
     const int h_lpr = own ? h->lpr : 0, h_vec = own ? h->vec : 0, h_rep = own ? h->rep : 0;
@@ -403,7 +423,8 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     int herr = 0;
     int rc = pcsr::build_device(n_rows, n_cols, nnz, rowptr, colidx, vals, prm.V, prm.S, prm.SG, prm.omega,
                                 !(prm.flags & PCSR_FLAG_NO_VALIDATE), column_order,
-                                (prm.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && !prm.col_window, late, &db, &herr);
+                                (prm.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && !prm.col_window,
+                                (prm.flags & kClusterWindows) != 0, late, &db, &herr);
     h->host.n_rows = n_rows;
     h->host.n_cols = n_cols;
     h->host.nnz = nnz;
@@ -427,6 +448,7 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     h->n_split = db.n_split;
     h->n_split_items = db.n_split_items;
     h->n_long = db.n_long;
+    h->win = db.win;
     h->lpr = prm.lanes_per_row;
     h->vec = prm.vec;
     h->rep = prm.rep;
@@ -808,6 +830,16 @@ static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, co
     a.n_slices = ls.grid_y;
     a.win_whole = ls.win_whole;
     a.win_parts = ls.win_parts;
+    a.rows = nullptr;
+    if (ls.window && h->win.blocks) {
+        a.rowptr = a.win_lo = h->win.rowptr;
+        a.colidx = h->win.colidx;
+        a.val = h->win.val;
+        a.win_ptr = h->win.ptr;
+        a.win_hi = h->win.hi;
+        a.win_cols = pcsr::kRowsMost;
+        a.rows = h->win.rows;
+    }
     a.epi = epi;
     if (!hip_ok(pcsr::launch_spmm(h->host.V, h->host.S, ls, a, s))) return PCSR_E_HIP;
     if (two_pass) {
@@ -1140,6 +1172,13 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // 747 -> 262, K = 256 1485 -> 578; rows of 12, K = 256: 919 -> 508).  Asked for where one product pays for it.
     if (!skewed && !windowed && scattered && p.V == 1 && d_hat >= 12.0 && 3e-7 * f[2] * (double)K >= 150.0 + 6e-4 * n)
         p.flags |= PCSR_FLAG_CLUSTER_IF_USEFUL;
+    // And, for wide rows, windows of those communities in LDS (cluster_windows): 0.1 ms and 0.25 ns a row of build for
+    // 0.06 ps per nonzero and column (250,000 rows of 48 in communities of 500: K = 256 577 -> 378 us, build 414 -> 586;
+    // of 30: 379 -> 279, 382 -> 525; 500,000 of 24: K = 512 1550 -> 1150, 529 -> 726).  Fewer vectors a row do not
+    // pay for the staging (250,000 rows of 14: 205 -> 225).  Where one product pays for it, too.
+    if ((p.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && d_hat >= 22.0 && K >= 192 && K % 4 == 0 &&
+        6e-8 * f[2] * (double)K >= 100.0 + 2.5e-4 * n)
+        p.flags |= kClusterWindows;
 
     // Launch shape: the widest vector load that divides K, one lane group spanning the
     // whole row of C when it fits a wavefront, repeats beyond that.

@@ -22,6 +22,11 @@ struct DeviceBuild {
     int32_t S = 0, SG = 0;
     bool vals_due = false;  // val is still to be filled, once `late` is there
     bool clustered = false; // the schedule runs the rows community by community
+    struct {                // the arrays of a product with windows of communities (blocks 0: none)
+        int32_t *rowptr = nullptr, *colidx = nullptr, *rows = nullptr, *ptr = nullptr, *hi = nullptr;
+        float *val = nullptr;
+        int64_t blocks = 0;
+    } win;
     int32_t xcd_bounds[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
 };
 
@@ -29,11 +34,12 @@ struct DeviceBuild {
 // values: the call then leaves that to the caller (vals_due); else it waits.
 // d_rowptr / d_colidx / d_vals are device pointers.  Returns PCSR_OK or a PCSR_E_* code;
 // on PCSR_E_HIP *hip_err holds the hipError_t.  Synchronous.
-// clusters: where the rows turn out to form communities, S = 1 with items of kClusterItem and the schedule by community.
+// clusters: where the rows turn out to form communities, S = 1 with items of kClusterItem and the schedule by community;
+// windows: and, where they fit in LDS, out->win beside it.
 constexpr int32_t kClusterItem = 1024;
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
-                 int32_t omega, bool validate, bool column_order, bool clusters, Upload *late, DeviceBuild *out,
+                 int32_t omega, bool validate, bool column_order, bool clusters, bool windows, Upload *late, DeviceBuild *out,
                  int *hip_err);
 
 // Whether rows share more columns than chance has them: enqueues the count of a sample on the null stream (d_out: two
@@ -41,12 +47,18 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
 hipError_t cluster_probe(int64_t n, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx, unsigned long long *d_out);
 bool cluster_probe_says(const unsigned long long found[2], int64_t n);
 // A label in [0, n) for every row of a checked square CSR, rows of a community having the same one; null where too few do for
-// an order by label to pay.  Ownership passes to the caller.  The same labels on every run.  Synchronous.
-int cluster_rows(int64_t n, const int32_t *d_rowptr, const int32_t *d_colidx, int32_t **labels, int *hip_err);
+// an order by label to pay.  Ownership passes to the caller.  The same labels on every run.  *mean_size: of the label that
+// a row has.  Synchronous.
+int cluster_rows(int64_t n, const int32_t *d_rowptr, const int32_t *d_colidx, int32_t **labels, double *mean_size, int *hip_err);
 // Keys of cluster_key_bits(n) bits by which items sort into the order of their rows' labels (enqueued on the null stream).
 int cluster_key_bits(int64_t n);
 hipError_t cluster_keys(int64_t n, const int32_t *d_labels, int64_t n_items, const int32_t *d_items, const int32_t *d_rows,
                         uint32_t *d_key);
+
+// out->win of a square CSR whose rows have these labels: rows sorted by label, cut into blocks of communities, each row's
+// vectors partitioned.  Nothing where too few vectors lie inside the blocks.  Synchronous.
+int cluster_windows(int64_t n, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx, const float *d_vals,
+                    const int32_t *d_labels, DeviceBuild *out, int *hip_err);
 
 // The check build_device makes, alone: PCSR_OK or PCSR_E_BAD_CSR (or HIP, OOM).  Synchronous.
 int validate_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,

@@ -50,6 +50,9 @@ struct SpmmArgs {
     int32_t n_slices;  // column slices of a block (window kernel only)
     int32_t win_whole; // (block, slice) pairs an XCD takes whole; the rest run as win_parts workgroups each
     int32_t win_parts;
+    // Windows of communities (cluster_windows; null: column windows): item i is row rows[i] of C, the window of a block
+    // its own rows of B, and colIdx holds an item's vectors inside the window first, as items, the others as columns.
+    const int32_t *rows;
     Epilogue epi;
 };
 
@@ -70,6 +73,9 @@ bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg);
 // with an epilogue (plain walk; the batched and window kernels take one at any shape)
 bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep);
 bool window_kernel_exists(int V, int lpr, int vec, int rep);
+// The one shape of the kernel for windows of communities; what its first launch on a device needs done outside a capture.
+constexpr int kRowsLanes = 16, kRowsVec = 4, kRowsMost = 512;
+hipError_t prepare_row_windows();
 
 // Enqueues the SpMM kernel <V,S,lpr,vec,rep> with `waves` wavefronts per workgroup.
 hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args,

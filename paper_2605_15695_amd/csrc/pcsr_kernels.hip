@@ -681,7 +681,9 @@ __global__ void __launch_bounds__(512) spmm_batched_kernel(SpmmArgs a)
 // Everything that would put a memory round trip into the walk is requested one step ahead:
 // the next item's vector range while the current item is processed, the next chunk of
 // colIdx/val while the current chunk's rows are read.
-template <int V, int LPR, int VEC, int REP>
+// ROWS: windows of communities (SpmmArgs::rows): the window of a block is the rows of B with the numbers of its own
+// items, found through a list, and the vectors inside come first in each item.
+template <int V, int LPR, int VEC, int REP, bool ROWS>
 __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
 {
     extern __shared__ __align__(16) float lds[];
@@ -731,6 +733,8 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
 
     int item_begin = a.win_ptr[bid];
     int item_end = a.win_ptr[bid + 1];
+    const int c0 = ROWS ? item_begin : a.win_start[bid];
+    const int staged = ROWS ? item_end - item_begin : a.win_cols; // rows of B in LDS
     if (parts > 1) {
         const int n = item_end - item_begin;
         item_end = item_begin + (int)((long)n * (part + 1) / parts);
@@ -740,28 +744,35 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
     const int stride = waves * G;
     int item = item_begin + wave * G + lane / LPR;
     // the first item's ranges are requested before the window is staged
-    int head = 0, tail = 0, lo = 0, hi = 0;
+    int head = 0, tail = 0, lo = 0, hi = 0, row = 0;
     if (item < item_end) {
         head = a.rowptr[item];
         tail = a.rowptr[item + 1];
         lo = a.win_lo[item];
         hi = a.win_hi[item];
+        if constexpr (ROWS) row = a.rows[item];
     }
 
-    const int c0 = a.win_start[bid];
     if (c0 >= 0) { // uniform over the workgroup
         // A compute unit holds one workgroup (139 of 160 KB), so nothing runs beside the staging: all of a thread's
         // loads (8 of 16 bytes) are requested before the first is written.  One after the other they were nine
         // round trips per workgroup: sbm, K = 256: 380 us for 365 now.
         constexpr int VPR = TW / VEC;  // vector loads per staged row
         constexpr int PASS = 32 / VEC; // loads in flight per thread
-        const int total = a.win_cols * VPR;
+        const int total = staged * VPR;
         for (int q0 = tid; q0 < total; q0 += PASS * blockDim.x) {
             float t[PASS][VEC];
+            int cols[PASS];
 #pragma unroll
             for (int i = 0; i < PASS; ++i) {
                 const int q = q0 + i * blockDim.x;
-                const int col = c0 + q / VPR, e = q % VPR * VEC;
+                cols[i] = c0 + q / VPR;
+                if constexpr (ROWS) cols[i] = a.rows[q < total ? cols[i] : c0];
+            }
+#pragma unroll
+            for (int i = 0; i < PASS; ++i) {
+                const int q = q0 + i * blockDim.x;
+                const int col = cols[i], e = q % VPR * VEC;
                 const bool ok = q < total && col < a.n_cols && kbase + e < a.K;
                 load_vec<VEC>(ok ? B + (long)col * K + kbase + e : g_zero_row, t[i]);
             }
@@ -813,12 +824,13 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
     while (item < item_end) {
         // ranges of the item this group takes next
         const int item_next = item + stride;
-        int head_next = 0, tail_next = 0, lo_next = 0, hi_next = 0;
+        int head_next = 0, tail_next = 0, lo_next = 0, hi_next = 0, row_next = 0;
         if (item_next < item_end) {
             head_next = a.rowptr[item_next];
             tail_next = a.rowptr[item_next + 1];
             lo_next = a.win_lo[item_next];
             hi_next = a.win_hi[item_next];
+            if constexpr (ROWS) row_next = a.rows[item_next];
         }
 
         float acc[V][REP][VEC];
@@ -969,18 +981,19 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
 
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            const long row = (long)item * V + v;
-            if (row < a.n_rows) {
-                float *crow = a.C + row * K + kbase;
+            const long at = ROWS ? (long)row : (long)item * V + v;
+            if (at < a.n_rows) {
+                float *crow = a.C + at * K + kbase;
 #pragma unroll
                 for (int r = 0; r < REP; ++r)
                     if (kv[r]) {
-                        finish<VEC>(a.epi, row, a.K, kbase + kl[r], acc[v][r]);
+                        finish<VEC>(a.epi, at, a.K, kbase + kl[r], acc[v][r]);
                         store_vec<VEC>(crow + kl[r], acc[v][r]);
                     }
             }
         }
         item = item_next;
+        row = row_next;
         head = head_next;
         tail = tail_next;
         lo = lo_next;
@@ -1236,9 +1249,9 @@ KernelFn pick_any(int V, int S, int lpr, int vec, int rep, int ipg)
 template <int V, int LPR, int VEC> KernelFn pickw_rep(int rep)
 {
     switch (rep) {
-    case 1: return &spmm_window_kernel<V, LPR, VEC, 1>;
-    case 2: return &spmm_window_kernel<V, LPR, VEC, 2>;
-    case 4: return &spmm_window_kernel<V, LPR, VEC, 4>;
+    case 1: return &spmm_window_kernel<V, LPR, VEC, 1, false>;
+    case 2: return &spmm_window_kernel<V, LPR, VEC, 2, false>;
+    case 4: return &spmm_window_kernel<V, LPR, VEC, 4, false>;
     }
     return nullptr;
 }
@@ -1271,6 +1284,32 @@ KernelFn pick_window(int V, int lpr, int vec, int rep)
 
 } // namespace
 
+// More than 64 KiB of dynamic LDS has to be allowed per kernel function: raised to
+// the 160 KiB of the CU once per function and device, not on every launch (the
+// call is host work and is not capturable in a HIP graph).
+static hipError_t allow_window_lds(KernelFn fn)
+{
+    static std::mutex mu;
+    static std::set<std::pair<int, const void *>> raised;
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
+    const auto key = std::make_pair(dev, reinterpret_cast<const void *>(fn));
+    if (!raised.count(key)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        try {
+            raised.insert(key);
+        } catch (...) { // no memory to note it: raised again next time
+        }
+    }
+    return hipSuccess;
+}
+
+hipError_t prepare_row_windows() { return allow_window_lds(&spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true>); }
+
 bool window_kernel_exists(int V, int lpr, int vec, int rep)
 {
     return pick_window(V, lpr, vec, rep) != nullptr;
@@ -1290,29 +1329,11 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
 {
     if (ls.grid_x <= 0 || ls.grid_y <= 0) return hipSuccess; // nothing to do
     if (ls.window) {
-        KernelFn fn = S ? nullptr : pick_window(V, ls.lpr, ls.vec, ls.rep);
+        KernelFn fn = args.rows ? &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true>
+                                : (S ? nullptr : pick_window(V, ls.lpr, ls.vec, ls.rep));
         if (!fn) return hipErrorInvalidValue;
-        // More than 64 KiB of dynamic LDS has to be allowed per kernel function: raised to
-        // the 160 KiB of the CU once per function and device, not on every launch (the
-        // call is host work and is not capturable in a HIP graph).
-        {
-            static std::mutex mu;
-            static std::set<std::pair<int, const void *>> raised;
-            int dev = -1;
-            hipError_t e = hipGetDevice(&dev);
-            if (e != hipSuccess) return e;
-            std::lock_guard<std::mutex> lock(mu);
-            const auto key = std::make_pair(dev, reinterpret_cast<const void *>(fn));
-            if (!raised.count(key)) {
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-                if (e != hipSuccess) return e;
-                try {
-                    raised.insert(key);
-                } catch (...) { // no memory to note it: raised again next time
-                }
-            }
-        }
+        const hipError_t e = allow_window_lds(fn);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);
         return hipGetLastError();
     }

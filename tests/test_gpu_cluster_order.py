@@ -156,3 +156,98 @@ def test_selector_asks_where_one_product_pays_for_the_search():
     assert not pc.pcsr_select(f, 256).flags & FLAG and pc.pcsr_select(f, 512).flags & FLAG
     f[16] = 0.5                                                # local columns
     assert not pc.pcsr_select(f, 512).flags & FLAG
+
+
+WINDOWS = 1 << 28  # what pcsr_select adds to FLAG where windows of the communities pay as well
+
+
+@pytest.mark.parametrize("n,block,inner,outer,extra,windows", [
+    (6001, 100, 20, 2, (), True),                                    # several communities to a block of the product
+    (5003, 50, 40, 6, ((7, 0), (8, 1), (5002, 0), (4000, 3)), True),  # empty and short rows among them
+    (5003, 256, 50, 3, (), True), (5003, 257, 50, 3, (), True),      # the largest that shares a block, the smallest alone
+    (8192, 512, 60, 0, (), True), (8210, 513, 60, 1, (), True),      # a block's most rows, a community of two pieces
+    (6000, 700, 60, 1, (), None), (20000, 1000, 40, 2, (), False),   # ever fewer vectors inside
+    (8192, 512, 30, 5, ((5, 1024), (8191, 1000)), True),             # the longest rows that are one item
+    (8192, 512, 30, 5, ((5, 1025),), False),                         # one of two items
+])
+def test_windows_of_communities(n, block, inner, outer, extra, windows):
+    n, rp, ci, va, _ = _planted(n, block, inner, outer, n + block, extra)
+    arrays = _device(rp, ci, va)
+    plain, h = (pc.pcsr_build(n, n, *arrays, pc.make_params(flags=FLAG | f)) for f in (0, WINDOWS))
+    x, y = pc.pcsr_export(plain), pc.pcsr_export(h)
+    assert y["SG"] == 1024 and all(np.array_equal(x[k], y[k]) for k in x)
+    has = pc.pcsr_query_launch(h, 64)["lds_bytes"] > 0
+    assert windows is None or has == windows
+    for K in (60, 64, 66, 68, 100, 256, 300, 516):
+        q = pc.pcsr_query_launch(h, K)
+        assert (q["lds_bytes"] > 0) == (has and K % 4 == 0 and K >= 64)
+        _check_product(h, n, rp, ci, va, K)
+    # a row of B reaches the rows that refer to it and no others, NaN included
+    K, j = 64, int(ci[rp[n // 2]])
+    B = torch.randn(n, K, device="cuda")
+    B[j] = float("nan")
+    C = torch.empty(n, K, device="cuda")
+    pc.pcsr_spmm(h, B, C, K)
+    refer = np.zeros(n, bool)
+    refer[np.repeat(np.arange(n), np.diff(rp))[ci == j]] = True
+    assert np.array_equal(torch.isnan(C).any(1).cpu().numpy(), refer) and np.array_equal(torch.isnan(C).all(1).cpu().numpy(), refer)
+    # the same bits on another build, in the hardware's order of workgroups and with the caller's own shape once it is taken back
+    again = pc.pcsr_build(n, n, *arrays, pc.make_params(flags=FLAG | WINDOWS))
+    D = torch.empty(n, K, device="cuda")
+    pc.pcsr_set_kernel_params(again, lanes_per_row=16, vec=4, rep=1)
+    assert pc.pcsr_query_launch(again, K)["lds_bytes"] == 0
+    pc.pcsr_spmm(again, B.nan_to_num(), D, K)
+    pc.pcsr_set_kernel_params(again, flags=pc.PCSR_FLAG_NO_XCD_REMAP)
+    pc.pcsr_spmm(again, B, D, K)
+    assert torch.equal(torch.nan_to_num(C), torch.nan_to_num(D))
+    # from host arrays, whose values are still under way when the rest of the build is done
+    late = pc.pcsr_build(n, n, rp, ci, va, pc.make_params(flags=FLAG | WINDOWS | pc.PCSR_FLAG_GPU_BUILD))
+    pc.pcsr_spmm(late, B, D, K)
+    assert torch.equal(torch.nan_to_num(C), torch.nan_to_num(D))
+    for handle in (plain, h, again, late):
+        handle.close()
+
+
+def test_windows_of_communities_in_a_graph_and_a_layer():
+    """The first product of all is captured and replayed beside eager ones; a layer with its elementwise tail agrees with
+    one on an ordinary handle."""
+    n, rp, ci, va, _ = _planted(6001, 300, 40, 3, 11)
+    arrays, K = _device(rp, ci, va), 192
+    h = pc.pcsr_build(n, n, *arrays, pc.make_params(flags=FLAG | WINDOWS))
+    assert pc.pcsr_query_launch(h, K)["lds_bytes"] > 0
+    B, C = torch.randn(n, K, device="cuda"), torch.zeros(n, K, device="cuda")
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        pc.pcsr_spmm(h, B, C, K, torch.cuda.current_stream())
+    for k in range(4):
+        B.normal_()
+        want = torch.empty_like(C)
+        pc.pcsr_spmm(h, B, want, K)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, want), k
+    h.close()
+
+    from paper_2605_15695_amd.gnn import PcsrOperator, make_model
+
+    models = []
+    for prm in (pc.make_params(flags=FLAG | WINDOWS), pc.make_params()):
+        torch.manual_seed(1)
+        op = PcsrOperator(n, n, *arrays, params=prm)
+        models.append(make_model("gcn", op, 64, 128, 64, 3).cuda())
+    X = torch.randn(n, 64, device="cuda")
+    outs = [m(X) for m in models]
+    for o in outs:
+        o.square().mean().backward()
+    for got, want in [(outs[0].detach(), outs[1].detach())] + [(a.grad, b.grad) for a, b in zip(*(m.parameters() for m in models))]:
+        assert float((got - want).norm() / want.norm()) < 1e-5
+
+
+def test_selector_asks_for_windows_where_one_product_pays_for_them():
+    f = np.zeros(len(pc.FEATURE_NAMES))
+    f[0] = f[1] = 250_000
+    f[2], f[4], f[5], f[6], f[7], f[15], f[16] = 12e6, 48.0, 48.0, 80.0, 0.15, 0.5, 0.004
+    assert [bool(pc.pcsr_select(f, K).flags & WINDOWS) for K in (128, 192, 256, 258, 512)] == [False, False, True, False, True]
+    f[2], f[4], f[5] = 4.5e6, 18.0, 18.0                       # short rows
+    assert not pc.pcsr_select(f, 1024).flags & WINDOWS
