@@ -19,7 +19,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-command-line-argum
 DEVICE = ["--offload-arch=gfx950", "-munsafe-fp-atomics",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 SOURCES = ["pcsr_kernels.hip", "pcsr_build_gpu.hip", "pcsr_gnn.hip", "pcsr_api.cpp", "pcsr_host.cpp", "pcsr_reorder.cpp",
-           "pcsr_pool.cpp", "pcsr_window_gpu.hip", "pcsr_relabel_gpu.hip", "pcsr_cluster_gpu.hip"]
+           "pcsr_pool.cpp", "pcsr_window_gpu.hip", "pcsr_relabel_gpu.hip", "pcsr_cluster_gpu.hip",
+           "pcsr_transpose_gpu.hip"]
 
 
 def _compile(src: str) -> pathlib.Path:

@@ -22,4 +22,9 @@ int transpose_gpu(int64_t n_rows, int64_t n_cols, const int32_t *rowptr, const i
                   int32_t *out_rowptr, int32_t *out_colidx, float *out_vals);
 int degree_order_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, int32_t *perm);
 
+// transpose_device for matrices that it takes (bits of a column, of a row, enough nonzeros): outputs in device memory.
+bool transpose_in_two_passes(int64_t n_rows, int64_t n_cols, int64_t nnz);
+int transpose_two_passes(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
+                         const float *d_vals, int32_t *t_rowptr, int32_t *t_colidx, float *t_vals, int *hip_err);
+
 } // namespace pcsr

@@ -502,6 +502,15 @@ int transpose_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t 
     HIP_TRY(sc.alloc((void **)&rp, sizeof(int32_t) * (n_cols + 1)));
     HIP_TRY(sc.alloc((void **)&ci, sizeof(int32_t) * (nnz + 1)));
     HIP_TRY(sc.alloc((void **)&va, sizeof(float) * (nnz + 1)));
+    if (transpose_in_two_passes(n_rows, n_cols, nnz)) {
+        const int rc = transpose_two_passes(n_rows, n_cols, nnz, d_rowptr, d_colidx, d_vals, rp, ci, va, hip_err);
+        if (rc != PCSR_OK) return rc;
+        *t_rowptr = rp;
+        *t_colidx = ci;
+        *t_vals = va;
+        for (void *q : {(void *)rp, (void *)ci, (void *)va}) sc.release(q);
+        return PCSR_OK;
+    }
     HIP_TRY(sc.alloc((void **)&keys, sizeof(int32_t) * (nnz + 1)));
     HIP_TRY(sc.alloc((void **)&in, sizeof(uint2) * (nnz + 1)));
     HIP_TRY(sc.alloc((void **)&sorted, sizeof(uint2) * (nnz + 1)));

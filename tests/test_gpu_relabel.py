@@ -113,6 +113,36 @@ def test_permuted_rows_of_every_class(longest, twice):
         assert np.array_equal(got[2].view(np.uint32), va[order].view(np.uint32))
 
 
+@pytest.mark.parametrize("n,m,nnz,kind", [
+    (250_001, 250_007, 1_500_001, ""), (3, 2, 1 << 20, ""), (5000, 3, 1_100_000, ""), (70_000, 1 << 20, (1 << 20) + 1, ""),
+    (70_000, 1000, (1 << 18) - 1, ""), (70_000, 1000, 1 << 18, ""),  # around the least it is used for
+    (70_000, (1 << 20) + 1, (1 << 20) + 1, ""),     # one bit more than two passes take
+    ((1 << 22) - 5, 1_000_000, 1_200_000, "gap"),   # more rows than a tile looks at between two nonzeros
+    ((1 << 22) + 5, 1_000_000, 1_200_000, ""),      # rows too many for the word beside the digit
+    (100_000, 100_000, 1_300_000, "hub"), (8192, 1025, 1 << 20, "last"), (4096, 512, (1 << 20) - 1, ""),
+])
+def test_transpose_of_every_size(n, m, nnz, kind):
+    """Columns of 1 to 21 bits, tiles that are full to the last nonzero and one over, rows of any length, a column with half
+    of the nonzeros, a column that comes more than once in a row (in its order there)."""
+    rng = np.random.default_rng(nnz + m)
+    rows = np.sort(rng.integers(0, n, nnz))
+    if kind == "gap":
+        rows[:nnz // 2] //= 1000
+        rows = np.sort(rows)
+    ci = rng.integers(0, m, nnz).astype(np.int32)
+    if kind == "hub":
+        ci[rng.random(nnz) < 0.5] = m // 3
+    if kind == "last":
+        ci[:] = m - 1
+    ci = ci[np.lexsort((ci, rows))]
+    rp = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int32)
+    va = rng.standard_normal(nnz).astype(np.float32)
+    order = np.argsort(ci, kind="stable")
+    got = pc.pcsr_transpose_csr(n, m, rp, ci, va)
+    assert np.array_equal(got[0], np.concatenate([[0], np.cumsum(np.bincount(ci, minlength=m))]))
+    assert np.array_equal(got[1], rows[order]) and np.array_equal(got[2].view(np.uint32), va[order].view(np.uint32))
+
+
 def test_refusals_are_those_of_the_host():
     n, rp, ci, va = _case("sbm")
     bad = ci.copy()
