@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(kThreads) union_fill_kernel(int64_t n_rows, in
     }
 }
 
-// non-empty panels and longest panel (V = 2; validate_rows_kernel has them for V = 1)
+// non-empty panels and longest panel (V = 2; check_rows_kernel has them for V = 1)
 __global__ void __launch_bounds__(kThreads) panel_stats_kernel(int64_t P, const int32_t *prow, Checked *out)
 {
     int n = 0, l = 0;

@@ -32,7 +32,7 @@ struct SpmmArgs {
     int32_t xb[9];     // item range [xb[x], xb[x+1]) of XCD x (xcd_remap only)
     // Balanced handles, deterministic write-back: an item of a panel that was split over
     // several items stores its partial rows in `ws` (slot-major: (slot*V + v)*K + k) and
-    // reduce_split adds them in item order.  ws == nullptr selects the atomic write-back.
+    // reduce_kernel adds them in item order.  ws == nullptr selects the atomic write-back.
     float *ws;
     const int32_t *item_slot; // M (S only): workspace slot of an item of a split panel, -1 for
                               // an item that is the only one of its panel
