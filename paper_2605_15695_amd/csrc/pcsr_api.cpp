@@ -821,6 +821,10 @@ static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, co
     a.ws = two_pass ? ws : nullptr;
     a.item_slot = h->d_item_slot;
     a.sched = reinterpret_cast<const int4 *>(h->d_sched);
+    // Where an item's sum would be less exact than that of items of 32 vectors: in the order by community, whose items
+    // are whole rows, past 32; elsewhere, where 32 lanes and more keep sums of 8 apart in place of a chunk's, past 64.
+    const int64_t exact = h->clustered ? 32 : (ls.k_lpr >= 32 ? 64 : INT32_MAX);
+    a.outer = h->host.S && !ls.window && h->host.max_item_len > exact;
     a.win_start = h->d_win;
     a.win_cols = h->host.win_cols;
     a.win_ptr = h->d_win_ptr;

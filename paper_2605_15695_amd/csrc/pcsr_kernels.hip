@@ -251,11 +251,21 @@ __device__ __forceinline__ const float *row_ptr(const float *base, long off, int
                                            (long)(((unsigned long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
+// What an instance of spmm_kernel is for beside the plain product.  Instances of their own: products with short items lost
+// 0.5 % to kLongItems' three branches (R-MAT 2^22, K = 16: 1404 -> 1411 us).
+constexpr int kAsIs = 0;
+constexpr int kLongItems = 1; // balanced handles with long items (SpmmArgs::outer): sums of 32 vectors are added up apart
+
 // EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
 // branch alone cost the instance <2, false, 64, 1, 2> 4 %.
-template <int V, bool S, int LPR, int VEC, int REP, bool EPI = false>
-__global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
+// (Seven waves per SIMD are asked for where the compiler would take six for want of a few registers; two is what 512
+// threads imply.)
+template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM>
+__global__ void __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(FORM == kLongItems && V == 2 && LPR == 32 && VEC == 4 && REP == 1 && !EPI ? 7 : 2)))
+spmm_kernel(SpmmArgs a)
 {
+    constexpr bool OUTER = FORM == kLongItems;
     constexpr int G = 64 / LPR;
     // vectors gathered per inner step: 16 registers of B data in flight, 32 for balanced
     // handles and for V = 1 with groups of up to 8 lanes (K <= 32: 4-8 % faster on rows of 40
@@ -388,11 +398,44 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
         }
     };
 
+    // OUTER, as the second pass adds the sums of items of 32 (64 where a whole wavefront takes an item, whose own sums are of 8).
+    // One running sum over a whole row loses more the longer the row.  Rms of the difference from 64 bits, relative to the sum
+    // of magnitudes, at K = 8, 32, 64, 256: rows of 300 6.1, 5.9, 6.7 and 6.0e-9 (11.0, 8.1, 7.5 and 8.5e-9 with one running sum,
+    // 6.1, 5.9, 6.7 and 6.7e-9 by items of 32), of 1000 4.4, 4.4, 4.7 and 3.9e-9 (9.8, 7.2, 5.8 and 7.4e-9; 4.5, 4.5, 4.8 and 4.8e-9).
+    // The time is the same within 1 % (250,000 rows of 48, K = 16 80 -> 82 us, 128 263, 512 1285).  In LDS, four floats or so per thread, which only that
+    // thread uses: four more registers would cost an instance a wavefront per SIMD, and so the slot's address is made anew
+    // each time, and the slot holds zeros at first.
+    extern __shared__ __align__(16) float lds[];
+    const int wave_at = __builtin_amdgcn_readfirstlane(wave) * 64;
+    auto outer = [&](auto use) {
+        int t; // lane; volatile: not kept in a register across the walk
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(t));
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int r = 0; r < REP; ++r) use(acc[v][r], lds + ((v * REP + r) * 64 * waves + wave_at + t) * VEC);
+    };
+    auto add_outer = [](float (&x)[VEC], const float *at) {
+        float t[VEC];
+        load_lds<VEC>(at, t);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) x[e] += t[e];
+    };
+    auto keep_apart = [&](float (&x)[VEC], float *at) {
+        add_outer(x, at);
+        store_lds<VEC>(at, x);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) x[e] = 0.0f;
+    };
+    if constexpr (OUTER) outer([](float (&x)[VEC], float *at) { store_lds<VEC>(at, x); });
+
     // The next chunk's colIdx/val are requested before the current chunk's gathers, so
     // that a chunk costs one memory round trip, not two.
     int c_next[NH];
     float av_next[NH][V];
     load_entry(head, c_next, av_next);
+    constexpr int PERIOD = CH < 32 ? 32 / CH : 1;
+    int until = PERIOD; // chunks until the next sum is put apart (the same in every lane group)
     for (int base = head; base < tail; base += CH) {
         long off[NH]; // DPP: in bytes, computed once by the lane that holds the entry
         int c[NH];
@@ -508,7 +551,15 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
             for (int r = 0; r < REP; ++r)
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) acc[v][r][e] += part[v][r][e];
+        if constexpr (OUTER) {
+            if (--until == 0) {
+                until = PERIOD;
+                const bool more = LPR == 64 ? wave_all(base + CH < tail) : base + CH < tail; // (as one keeps a register free)
+                if (more) outer(keep_apart);
+            }
+        }
     }
+    if constexpr (OUTER) outer(add_outer);
 
     // write-back (Algorithm 2, last block): plain store for an item that is the only one
     // of its panel.  An item of a panel that was split (TRow names the panel) either
@@ -545,7 +596,6 @@ __global__ void __launch_bounds__(512) spmm_kernel(SpmmArgs a)
         }
     }
 }
-
 
 // Batched walk for matrices of short rows (no balancing): one lane group owns IPG
 // consecutive work items and walks their joint colIdx/val range as one stream, so the
@@ -1158,77 +1208,55 @@ template <int VEC> __global__ void __launch_bounds__(256) reduce_kernel(ReduceAr
 
 using KernelFn = void (*)(SpmmArgs);
 
-template <int V, bool S, int LPR, int VEC> KernelFn pick_rep(int rep)
+template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn instance()
 {
-    switch (rep) {
-    case 1: return &spmm_kernel<V, S, LPR, VEC, 1>;
-    case 2: return &spmm_kernel<V, S, LPR, VEC, 2>;
-    case 4: return &spmm_kernel<V, S, LPR, VEC, 4>;
+    if constexpr (FORM == kLongItems && !(S && (V == 1 || LPR >= 32))) // (spmm_enqueue says which)
+        return nullptr;
+    else
+        return &spmm_kernel<V, S, LPR, VEC, REP, EPI, FORM>;
+}
+template <int V, bool S, int LPR, int VEC, bool EPI, int FORM> KernelFn pick_rep(int rep)
+{
+    if constexpr (!EPI) {
+        switch (rep) {
+        case 1: return instance<V, S, LPR, VEC, 1, EPI, FORM>();
+        case 2: return instance<V, S, LPR, VEC, 2, EPI, FORM>();
+        case 4: return instance<V, S, LPR, VEC, 4, EPI, FORM>();
+        }
+    } else { // the shapes resolve_launch arrives at when everything is left to it
+        if (rep == 1) return instance<V, S, LPR, VEC, 1, EPI, FORM>();
+        if constexpr (LPR == 64) {
+            if (rep == 2) return instance<V, S, LPR, VEC, 2, EPI, FORM>();
+            if constexpr (!S)
+                if (rep == 4) return instance<V, S, LPR, VEC, 4, EPI, FORM>();
+        }
     }
     return nullptr;
 }
-template <int V, bool S, int LPR> KernelFn pick_vec(int vec, int rep)
+template <int V, bool S, int LPR, bool EPI, int FORM> KernelFn pick_vec(int vec, int rep)
 {
     switch (vec) {
-    case 1: return pick_rep<V, S, LPR, 1>(rep);
-    case 2: return pick_rep<V, S, LPR, 2>(rep);
-    case 4: return pick_rep<V, S, LPR, 4>(rep);
+    case 1: return pick_rep<V, S, LPR, 1, EPI, FORM>(rep);
+    case 2: return pick_rep<V, S, LPR, 2, EPI, FORM>(rep);
+    case 4: return pick_rep<V, S, LPR, 4, EPI, FORM>(rep);
     }
     return nullptr;
 }
-template <int V, bool S> KernelFn pick_lpr(int lpr, int vec, int rep)
+template <int V, bool S, bool EPI, int FORM> KernelFn pick_lpr(int lpr, int vec, int rep)
 {
     switch (lpr) {
-    case 4: return pick_vec<V, S, 4>(vec, rep);
-    case 8: return pick_vec<V, S, 8>(vec, rep);
-    case 16: return pick_vec<V, S, 16>(vec, rep);
-    case 32: return pick_vec<V, S, 32>(vec, rep);
-    case 64: return pick_vec<V, S, 64>(vec, rep);
+    case 4: return pick_vec<V, S, 4, EPI, FORM>(vec, rep);
+    case 8: return pick_vec<V, S, 8, EPI, FORM>(vec, rep);
+    case 16: return pick_vec<V, S, 16, EPI, FORM>(vec, rep);
+    case 32: return pick_vec<V, S, 32, EPI, FORM>(vec, rep);
+    case 64: return pick_vec<V, S, 64, EPI, FORM>(vec, rep);
     }
     return nullptr;
 }
-KernelFn pick(int V, int S, int lpr, int vec, int rep)
+template <bool EPI, int FORM = kAsIs> KernelFn pick(int V, int S, int lpr, int vec, int rep)
 {
-    if (V == 1) return S ? pick_lpr<1, true>(lpr, vec, rep) : pick_lpr<1, false>(lpr, vec, rep);
-    if (V == 2) return S ? pick_lpr<2, true>(lpr, vec, rep) : pick_lpr<2, false>(lpr, vec, rep);
-    return nullptr;
-}
-
-// the shapes resolve_launch arrives at when everything is left to it
-template <int V, bool S, int LPR, int VEC> KernelFn picke_rep(int rep)
-{
-    if (rep == 1) return &spmm_kernel<V, S, LPR, VEC, 1, true>;
-    if constexpr (LPR == 64) {
-        if (rep == 2) return &spmm_kernel<V, S, LPR, VEC, 2, true>;
-        if constexpr (!S)
-            if (rep == 4) return &spmm_kernel<V, S, LPR, VEC, 4, true>;
-    }
-    return nullptr;
-}
-template <int V, bool S, int LPR> KernelFn picke_vec(int vec, int rep)
-{
-    switch (vec) {
-    case 1: return picke_rep<V, S, LPR, 1>(rep);
-    case 2: return picke_rep<V, S, LPR, 2>(rep);
-    case 4: return picke_rep<V, S, LPR, 4>(rep);
-    }
-    return nullptr;
-}
-template <int V, bool S> KernelFn picke_lpr(int lpr, int vec, int rep)
-{
-    switch (lpr) {
-    case 4: return picke_vec<V, S, 4>(vec, rep);
-    case 8: return picke_vec<V, S, 8>(vec, rep);
-    case 16: return picke_vec<V, S, 16>(vec, rep);
-    }
-    if (lpr == 32) return picke_vec<V, S, 32>(vec, rep);
-    if (lpr == 64) return picke_vec<V, S, 64>(vec, rep);
-    return nullptr;
-}
-KernelFn pick_epilogue(int V, int S, int lpr, int vec, int rep)
-{
-    if (V == 1) return S ? picke_lpr<1, true>(lpr, vec, rep) : picke_lpr<1, false>(lpr, vec, rep);
-    if (V == 2) return S ? picke_lpr<2, true>(lpr, vec, rep) : picke_lpr<2, false>(lpr, vec, rep);
+    if (V == 1) return S ? pick_lpr<1, true, EPI, FORM>(lpr, vec, rep) : pick_lpr<1, false, EPI, FORM>(lpr, vec, rep);
+    if (V == 2) return S ? pick_lpr<2, true, EPI, FORM>(lpr, vec, rep) : pick_lpr<2, false, EPI, FORM>(lpr, vec, rep);
     return nullptr;
 }
 
@@ -1272,7 +1300,7 @@ template <int V> KernelFn pickb_lpr(int lpr, int vec, int rep, int ipg)
 }
 KernelFn pick_any(int V, int S, int lpr, int vec, int rep, int ipg)
 {
-    if (ipg <= 1) return pick(V, S, lpr, vec, rep);
+    if (ipg <= 1) return pick<false>(V, S, lpr, vec, rep);
     if (S) return nullptr;
     if (V == 1) return pickb_lpr<1>(lpr, vec, rep, ipg);
     if (V == 2) return pickb_lpr<2>(lpr, vec, rep, ipg);
@@ -1355,7 +1383,7 @@ bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg)
 
 bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep)
 {
-    return pick_epilogue(V, S, lpr, vec, rep) != nullptr;
+    return pick<true>(V, S, lpr, vec, rep) != nullptr;
 }
 
 hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args, hipStream_t stream)
@@ -1370,10 +1398,18 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
         hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);
         return hipGetLastError();
     }
-    KernelFn fn = args.epi.on && ls.ipg <= 1 ? pick_epilogue(V, S, ls.k_lpr, ls.k_vec, ls.k_rep)
-                                             : pick_any(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, ls.ipg);
+    const bool epi = args.epi.on && ls.ipg <= 1;
+    KernelFn fn;
+    size_t lds = 0;
+    if (args.outer) {
+        fn = epi ? pick<true, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep)
+                 : pick<false, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep);
+        lds = sizeof(float) * 64 * ls.waves * V * ls.k_rep * ls.k_vec; // 64 KB at most
+    } else {
+        fn = epi ? pick<true>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep) : pick_any(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, ls.ipg);
+    }
     if (!fn) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), 0, stream, args);
+    hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), lds, stream, args);
     return hipGetLastError();
 }
 

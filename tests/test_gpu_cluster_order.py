@@ -251,3 +251,58 @@ def test_selector_asks_for_windows_where_one_product_pays_for_them():
     assert [bool(pc.pcsr_select(f, K).flags & WINDOWS) for K in (128, 192, 256, 258, 512)] == [False, False, True, False, True]
     f[2], f[4], f[5] = 4.5e6, 18.0, 18.0                       # short rows
     assert not pc.pcsr_select(f, 1024).flags & WINDOWS
+
+
+@pytest.fixture(scope="module")
+def long_rows():
+    """Rows of a length in communities that hold them, with equal values and with random ones."""
+    made = {}
+
+    def get(length):
+        if length not in made:
+            block = max(100, length + length // 4)
+            n, rp, ci, va, _ = _planted(10 * block + 1, block, length, length // 12, length)
+            made[length] = n, rp, ci, (np.full_like(va, 1.0 / length), va)
+        return made[length]
+
+    return get
+
+
+def _rms(params, n, rp, ci, va, B, ref, bound):
+    """Of the differences from 64 bits, relative to each element's sum of magnitudes."""
+    h = pc.pcsr_build(n, n, *_device(rp, ci, va), params)
+    C = torch.full(B.shape, float("nan"), device="cuda")
+    pc.pcsr_spmm(h, torch.from_numpy(B).cuda(), C, B.shape[1])
+    e = (C.cpu().numpy().astype(np.float64) - ref) / np.maximum(bound, 1e-30)
+    made = pc.pcsr_format(h)["SG"], pc.pcsr_query_kernel(h, B.shape[1])
+    h.close()
+    return float(np.sqrt(np.mean(e * e))), made
+
+
+# The fewest independent squares (rows of 48, K = 8: 8000) have a mean within 5 % of its expectation at three standard
+# deviations (their kurtosis is about 3); the root halves that, and the two sides share inputs: 1.04.
+@pytest.mark.parametrize("length", [48, 100, 300, 1000])
+@pytest.mark.parametrize("K", [8, 32, 64, 256])
+def test_long_rows_are_as_exact_as_split_ones(long_rows, length, K):
+    """Against 64 bits: no further off than items of 32 vectors whose sums are added by the second pass."""
+    n, rp, ci, values = long_rows(length)
+    for va in values:
+        B = np.random.default_rng(K).uniform(-1, 1, (n, K)).astype(np.float32)
+        ref, bound = oracle.spmm(rp, ci, va, B)
+        split, _ = _rms(pc.make_params(S=1, SG=32, flags=pc.PCSR_FLAG_COLUMN_ORDER), n, rp, ci, va, B, ref, bound)
+        whole, (SG, shape) = _rms(pc.make_params(flags=FLAG), n, rp, ci, va, B, ref, bound)
+        print(f"rms of rows of {length}, K={K}: {whole:.3e}, split {split:.3e} {shape}", flush=True)
+        assert SG == 1024 and whole <= 1.04 * split, (length, K, whole, split, shape)
+
+
+@pytest.mark.parametrize("V", [1, 2])
+@pytest.mark.parametrize("lanes", [4, 32, 64])
+def test_long_items_are_as_exact_as_short_ones(long_rows, V, lanes):
+    n, rp, ci, values = long_rows(300)
+    B = np.random.default_rng(lanes).uniform(-1, 1, (n, 128)).astype(np.float32)
+    for va in values:
+        ref, bound = oracle.spmm(rp, ci, va, B)
+        short, long = (_rms(pc.make_params(V=V, S=1, SG=SG, lanes_per_row=lanes, vec=2, rep=1, waves_per_wg=8), n, rp, ci, va, B,
+                            ref, bound)[0] for SG in (32, 1024))
+        print(f"rms V={V}, {lanes} lanes: {long:.3e}, items of 32 {short:.3e}", flush=True)
+        assert lanes < 32 or long <= 1.04 * short, (V, lanes, long, short)
