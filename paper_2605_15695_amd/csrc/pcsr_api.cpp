@@ -822,9 +822,12 @@ static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, co
     a.item_slot = h->d_item_slot;
     a.sched = reinterpret_cast<const int4 *>(h->d_sched);
     // Where an item's sum would be less exact than that of items of 32 vectors: in the order by community, whose items
-    // are whole rows, past 32; elsewhere, where 32 lanes and more keep sums of 8 apart in place of a chunk's, past 64.
-    const int64_t exact = h->clustered ? 32 : (ls.k_lpr >= 32 ? 64 : INT32_MAX);
-    a.outer = h->host.S && !ls.window && h->host.max_item_len > exact;
+    // are whole rows, past 32, or 88 from their windows (sums of 8 there: rows of 80 1.36e-8 against 1.39e-8, of 100 1.30 against
+    // 1.28); elsewhere, where 32 lanes and more keep sums of 8 apart in place of a chunk's, past 64.  Column windows: sums
+    // of 16 in place of 8 where the longest row (or pair) has over 256.  They are better for rows of 130 and more (200: 0.83 against
+    // 0.90e-8), worse for shorter ones (90: by 4 %), which such a handle may hold as well.
+    const int64_t exact = h->host.win_cols ? 256 : ls.window ? 88 : h->clustered ? 32 : h->host.S && ls.k_lpr >= 32 ? 64 : INT32_MAX;
+    a.outer = h->host.max_item_len > exact;
     a.win_start = h->d_win;
     a.win_cols = h->host.win_cols;
     a.win_ptr = h->d_win_ptr;

@@ -1001,7 +1001,7 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
         out->n_split = total.split;
         out->n_split_items = total.slots;
         out->n_long = total.longp;
-        out->max_item_len = sg < nnz_v ? sg : nnz_v;
+        out->max_item_len = std::min<int64_t>(sg, check.longest);
         out->trow = o.trow;
         out->split = o.split_panels;
         out->item_slot = o.item_slot;

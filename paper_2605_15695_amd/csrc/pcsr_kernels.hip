@@ -752,7 +752,8 @@ __global__ void __launch_bounds__(512) spmm_batched_kernel(SpmmArgs a)
 // colIdx/val while the current chunk's rows are read.
 // ROWS: windows of communities (SpmmArgs::rows): the window of a block is the rows of B with the numbers of its own
 // items, found through a list, and the vectors inside come first in each item.
-template <int V, int LPR, int VEC, int REP, bool ROWS>
+// LONG: for long items (SpmmArgs::outer), see the sums below.
+template <int V, int LPR, int VEC, int REP, bool ROWS, bool LONG>
 __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
 {
     extern __shared__ __align__(16) float lds[];
@@ -902,13 +903,36 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
             if constexpr (ROWS) row_next = a.rows[item_next];
         }
 
-        float acc[V][REP][VEC];
+        // Sums of 8 vectors (16 where a step has as many), which one running sum adds up: it loses more the longer the row.  LONG
+        // therefore adds up sums of 32 apart with ROWS, whose rows were items of 32 vectors and a second pass without the windows,
+        // and makes the sums 16 vectors elsewhere, which costs no registers.  Rms of the difference from 64 bits, relative to
+        // the sum of magnitudes, equal values: ROWS at rows of 48, 100 and 300 1.25, 1.03 and 0.85e-8, with LONG 1.16, 0.88 and
+        // 0.60e-8, items of 32 1.30, 0.99 and 0.67e-8; column windows at rows of 100, 200 and 400 1.01, 0.90 and 0.81e-8, with
+        // LONG 0.99, 0.83 and 0.70e-8, gathered from memory 1.01, 0.82 and 0.68e-8.  (A third level for all of them: 250,000 rows of 48,
+        // K = 256 366 -> 371 us; paired rows, whose instances spill, 532 -> 660.)
+        constexpr bool OUTER = LONG && ROWS;
+        constexpr int PART = LONG && !ROWS ? 16 : 8; // vectors of a sum, in whole steps and within a chunk
+        float acc[V][REP][VEC], outer[OUTER ? V : 1][OUTER ? REP : 1][VEC];
+        auto add_to = [](auto &sum, float (&x)[V][REP][VEC]) { // sum += x, x = 0
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+#pragma unroll
+                for (int r = 0; r < REP; ++r)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) {
+                        sum[v][r][e] += x[v][r][e];
+                        x[v][r][e] = 0.0f;
+                    }
+        };
 #pragma unroll
         for (int v = 0; v < V; ++v)
 #pragma unroll
             for (int r = 0; r < REP; ++r)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[v][r][e] = 0.0f;
+                for (int e = 0; e < VEC; ++e) {
+                    acc[v][r][e] = 0.0f;
+                    if constexpr (OUTER) outer[v][r][e] = 0.0f;
+                }
 
         // Walks the n vectors whose i-th member is vector first + i (i < n1) or
         // second + (i - n1): one contiguous run, or two runs taken as one.  The columns of an
@@ -934,6 +958,13 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                 // where this lane's entry sits in the staged window (floats from lds); a slot
                 // past the end of the run reads the row of zeros staged after the window
                 const int loff = LDS ? (base + lg < n ? c - c0 : a.win_cols) * LW : 0;
+                float part[V][REP][VEC];
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+#pragma unroll
+                    for (int r = 0; r < REP; ++r)
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) part[v][r][e] = 0.0f;
                 auto step = [&](int j, auto const_lane) {
                     constexpr bool CL = decltype(const_lane)::value;
                     // LDS reads of a 16-lane group with constant source lanes: the broadcast of
@@ -967,13 +998,6 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                             }
                         }
                     }
-                    float part[V][REP][VEC];
-#pragma unroll
-                    for (int v = 0; v < V; ++v)
-#pragma unroll
-                        for (int r = 0; r < REP; ++r)
-#pragma unroll
-                            for (int e = 0; e < VEC; ++e) part[v][r][e] = 0.0f;
 #pragma unroll
                     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -987,12 +1011,7 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                                     else
                                         part[v][r][e] = fmaf(aj[u][v], b[u][r][e], part[v][r][e]);
                                 }
-#pragma unroll
-                    for (int v = 0; v < V; ++v)
-#pragma unroll
-                        for (int r = 0; r < REP; ++r)
-#pragma unroll
-                            for (int e = 0; e < VEC; ++e) acc[v][r][e] += part[v][r][e];
+                    if (U >= PART || ((j + U) & (PART - 1)) == 0) add_to(acc, part);
                 };
                 if constexpr (LPR == 16) {
 #pragma unroll
@@ -1001,6 +1020,9 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                 } else {
                     for (int j = 0; j < cnt; j += U) step(j, std::false_type{});
                 }
+                if constexpr (U < PART) add_to(acc, part);
+                if constexpr (OUTER)
+                    if (((base - i_start + LPR) & 31) == 0 && base + LPR < n) add_to(outer, acc);
             }
         };
         // Outside the window: memory gathers.  Those of the first UP such vectors are only
@@ -1048,12 +1070,7 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                         else
                             part[v][r][e] = fmaf(bcast<LPR>(avg0[v], u), gb[u][r][e], part[v][r][e]);
                     }
-#pragma unroll
-        for (int v = 0; v < V; ++v)
-#pragma unroll
-            for (int r = 0; r < REP; ++r)
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[v][r][e] += part[v][r][e];
+        add_to(acc, part);
         // the rare item with more out-of-window vectors than that: the rest, one step at a time
         if (n_out > UP) {
             int cg;
@@ -1061,6 +1078,7 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
             load_entry(head, lo - head, hi, n_out, UP, cg, avg);
             walk(head, lo - head, hi, n_out, UP, cg, avg, std::false_type{});
         }
+        if constexpr (OUTER) add_to(acc, outer);
 
 #pragma unroll
         for (int v = 0; v < V; ++v) {
@@ -1307,40 +1325,47 @@ KernelFn pick_any(int V, int S, int lpr, int vec, int rep, int ipg)
     return nullptr;
 }
 
-template <int V, int LPR, int VEC> KernelFn pickw_rep(int rep)
+template <int V, int LPR, int VEC> KernelFn pickw_rep(int rep, bool long_items)
 {
+    if constexpr (LPR >= 16 && VEC == 4) // steps of 8 in chunks of more, of the shapes that are taken unasked
+        if (rep == 1 && long_items) return &spmm_window_kernel<V, LPR, VEC, 1, false, true>;
     switch (rep) {
-    case 1: return &spmm_window_kernel<V, LPR, VEC, 1, false>;
-    case 2: return &spmm_window_kernel<V, LPR, VEC, 2, false>;
-    case 4: return &spmm_window_kernel<V, LPR, VEC, 4, false>;
+    case 1: return &spmm_window_kernel<V, LPR, VEC, 1, false, false>;
+    case 2: return &spmm_window_kernel<V, LPR, VEC, 2, false, false>;
+    case 4: return &spmm_window_kernel<V, LPR, VEC, 4, false, false>;
     }
     return nullptr;
 }
-template <int V, int LPR> KernelFn pickw_vec(int vec, int rep)
+template <int V, int LPR> KernelFn pickw_vec(int vec, int rep, bool long_items)
 {
     switch (vec) {
-    case 1: return pickw_rep<V, LPR, 1>(rep);
-    case 2: return pickw_rep<V, LPR, 2>(rep);
-    case 4: return pickw_rep<V, LPR, 4>(rep);
+    case 1: return pickw_rep<V, LPR, 1>(rep, long_items);
+    case 2: return pickw_rep<V, LPR, 2>(rep, long_items);
+    case 4: return pickw_rep<V, LPR, 4>(rep, long_items);
     }
     return nullptr;
 }
-template <int V> KernelFn pickw_lpr(int lpr, int vec, int rep)
+template <int V> KernelFn pickw_lpr(int lpr, int vec, int rep, bool long_items)
 {
     switch (lpr) {
-    case 4: return pickw_vec<V, 4>(vec, rep);
-    case 8: return pickw_vec<V, 8>(vec, rep);
-    case 16: return pickw_vec<V, 16>(vec, rep);
-    case 32: return pickw_vec<V, 32>(vec, rep);
-    case 64: return pickw_vec<V, 64>(vec, rep);
+    case 4: return pickw_vec<V, 4>(vec, rep, long_items);
+    case 8: return pickw_vec<V, 8>(vec, rep, long_items);
+    case 16: return pickw_vec<V, 16>(vec, rep, long_items);
+    case 32: return pickw_vec<V, 32>(vec, rep, long_items);
+    case 64: return pickw_vec<V, 64>(vec, rep, long_items);
     }
     return nullptr;
 }
-KernelFn pick_window(int V, int lpr, int vec, int rep)
+KernelFn pick_window(int V, int lpr, int vec, int rep, bool long_items)
 {
-    if (V == 1) return pickw_lpr<1>(lpr, vec, rep);
-    if (V == 2) return pickw_lpr<2>(lpr, vec, rep);
+    if (V == 1) return pickw_lpr<1>(lpr, vec, rep, long_items);
+    if (V == 2) return pickw_lpr<2>(lpr, vec, rep, long_items);
     return nullptr;
+}
+KernelFn pick_row_window(bool long_items)
+{
+    return long_items ? &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true, true>
+                      : &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true, false>;
 }
 
 } // namespace
@@ -1369,11 +1394,15 @@ static hipError_t allow_window_lds(KernelFn fn)
     return hipSuccess;
 }
 
-hipError_t prepare_row_windows() { return allow_window_lds(&spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true>); }
+hipError_t prepare_row_windows()
+{
+    const hipError_t e = allow_window_lds(pick_row_window(false));
+    return e == hipSuccess ? allow_window_lds(pick_row_window(true)) : e;
+}
 
 bool window_kernel_exists(int V, int lpr, int vec, int rep)
 {
-    return pick_window(V, lpr, vec, rep) != nullptr;
+    return pick_window(V, lpr, vec, rep, false) != nullptr;
 }
 
 bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg)
@@ -1390,8 +1419,8 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
 {
     if (ls.grid_x <= 0 || ls.grid_y <= 0) return hipSuccess; // nothing to do
     if (ls.window) {
-        KernelFn fn = args.rows ? &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true>
-                                : (S ? nullptr : pick_window(V, ls.lpr, ls.vec, ls.rep));
+        KernelFn fn = args.rows ? pick_row_window(args.outer != 0)
+                                : (S ? nullptr : pick_window(V, ls.lpr, ls.vec, ls.rep, args.outer != 0));
         if (!fn) return hipErrorInvalidValue;
         const hipError_t e = allow_window_lds(fn);
         if (e != hipSuccess) return e;

@@ -306,3 +306,40 @@ def test_long_items_are_as_exact_as_short_ones(long_rows, V, lanes):
                             ref, bound)[0] for SG in (32, 1024))
         print(f"rms V={V}, {lanes} lanes: {long:.3e}, items of 32 {short:.3e}", flush=True)
         assert lanes < 32 or long <= 1.04 * short, (V, lanes, long, short)
+
+
+@pytest.mark.parametrize("length", [48, 100, 300, 400])
+@pytest.mark.parametrize("K", [64, 256])
+def test_long_rows_from_windows_of_communities_are_as_exact(long_rows, length, K):
+    n, rp, ci, values = long_rows(length)
+    for va in values:
+        B = np.random.default_rng(K).uniform(-1, 1, (n, K)).astype(np.float32)
+        ref, bound = oracle.spmm(rp, ci, va, B)
+        split, _ = _rms(pc.make_params(S=1, SG=32, flags=pc.PCSR_FLAG_COLUMN_ORDER), n, rp, ci, va, B, ref, bound)
+        staged, (SG, shape) = _rms(pc.make_params(flags=FLAG | WINDOWS), n, rp, ci, va, B, ref, bound)
+        print(f"rms of rows of {length}, K={K}: staged {staged:.3e}, split {split:.3e} {shape}", flush=True)
+        assert SG == 1024 and shape["lds_bytes"] > 0 and staged <= 1.04 * split, (length, K, staged, split, shape)
+
+
+@pytest.mark.parametrize("V", [1, 2])
+@pytest.mark.parametrize("length", [48, 100, 400])
+@pytest.mark.parametrize("wc,kern", [(512, dict(lanes_per_row=16, vec=4, rep=1)), (256, dict(lanes_per_row=32, vec=2, rep=1)),
+                                     (256, dict(lanes_per_row=64, vec=1, rep=1)), (256, dict(lanes_per_row=4, vec=4, rep=4)),
+                                     (256, dict(lanes_per_row=8, vec=2, rep=4))])
+def test_rows_from_column_windows_are_as_exact_as_from_memory(long_rows, V, length, wc, kern):
+    """Rows of a community brought together; steps of 16 vectors down to 2, chunks of 4 to 64, on both sides of the rule for long rows."""
+    n, rp, ci, values = long_rows(length)
+    perm, _ = pc.pcsr_reorder(n, rp, ci)
+    K = 128
+    for va in values:
+        prp, pci, pva = pc.pcsr_permute_csr(n, rp, ci, va, perm)
+        B = np.random.default_rng(V).uniform(-1, 1, (n, K)).astype(np.float32)
+        ref, bound = oracle.spmm(prp, pci, pva, B)
+        plain, _ = _rms(pc.make_params(V=V, **kern), n, prp, pci, pva, B, ref, bound)
+        staged, (_, shape) = _rms(pc.make_params(V=V, col_window=wc, **kern), n, prp, pci, pva, B, ref, bound)
+        # the vectors outside the window are a sum of their own: one more rounding of the whole, of rms 2^-23 / sqrt(24)
+        # (uniform within half a unit, mantissas from 1 to 2)
+        whole = 2.0 ** -23 / 24 ** 0.5 * float(np.sqrt(np.mean((ref / np.maximum(bound, 1e-30)) ** 2)))
+        limit = 1.04 * (plain ** 2 + whole ** 2) ** 0.5
+        print(f"case rows of {length}, V={V}, window of {wc} {kern}: staged {staged:.3e}, plain {plain:.3e}, {limit:.3e}", flush=True)
+        assert shape["lds_bytes"] > 0 and staged <= limit, (V, wc, kern, staged, plain, limit)
