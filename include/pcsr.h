@@ -66,7 +66,8 @@ enum {
                                   parameters are set to auto.  Otherwise the flag does nothing.
                                   Where pcsr_select finds it worth a second copy of the nonzeros,
                                   products of 64 columns or more (a multiple of 4, parameters on
-                                  auto) stage the community's rows of B in LDS                   */
+                                  auto) stage the community's rows of B in LDS.  The alignment
+                                  asked of B and C stays that of the vec passed, if any          */
     PCSR_FLAG_ATOMIC_SPLIT = 32 /* S = 1 only: panels that were split accumulate into C with
                                   fp32 atomics, as Algorithm 2 prints it, instead of the
                                   default two-pass write-back (see pcsr_spmm)                 */

@@ -104,6 +104,7 @@ struct pcsr_handle_s {
     int32_t *d_win_hi = nullptr;
     int64_t n_win_blocks = 0;
     bool clustered = false; // scheduled community by community (PCSR_FLAG_CLUSTER_IF_USEFUL)
+    int32_t asked_vec = 0;  // of such a handle: the load width of the shape that the order replaced (0: none given)
     decltype(pcsr::DeviceBuild::win) win; // of such a handle: windows of communities (blocks 0: none)
     int64_t n_split = 0;
     int64_t n_split_items = 0; // workspace slots: items that belong to split panels
@@ -457,6 +458,7 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     h->flags = checked_flags(prm);
     if (rc == PCSR_OK && db.clustered) { // the caller's shape was for the order it would have had otherwise
         h->clustered = true;
+        h->asked_vec = h->vec;
         h->lpr = h->vec = h->rep = h->waves = h->ipg = 0;
         h->flags &= ~kWideBits;
     }
@@ -767,6 +769,13 @@ static int64_t workspace_need(pcsr_handle_t h, int32_t K)
     return h->n_split_items * (int64_t)h->host.V * (int64_t)K * (int64_t)sizeof(float);
 }
 
+// Bytes that the operands have to be aligned to: those of the load width that the parameters mean, not of what is launched
+// (whose loads are at 4-byte addresses anyway).  An order that the build found does not ask for more.
+static uintptr_t operand_align(pcsr_handle_t h, const pcsr::LaunchShape &ls)
+{
+    return 4u * (unsigned)(h->asked_vec ? std::min(h->asked_vec, ls.vec) : ls.vec);
+}
+
 // Checks shared by the SpMM entry points; resolves the launch shape.
 static int spmm_check(pcsr_handle_t h, const float *B, float *C, int32_t K, pcsr::LaunchShape *ls,
                       bool epilogue = false)
@@ -778,7 +787,7 @@ static int spmm_check(pcsr_handle_t h, const float *B, float *C, int32_t K, pcsr
     if (!B && h->host.n_cols > 0 && h->host.nnz_v > 0) return PCSR_E_INVALID_ARG;
     int rc = resolve_launch(h, K, ls, epilogue);
     if (rc != PCSR_OK) return rc;
-    const uintptr_t align = 4u * (unsigned)ls->vec;
+    const uintptr_t align = operand_align(h, *ls);
     if ((reinterpret_cast<uintptr_t>(B) % align) || (reinterpret_cast<uintptr_t>(C) % align))
         return PCSR_E_INVALID_ARG;
     if (h->host.n_rows == 0) return PCSR_OK;
@@ -901,7 +910,7 @@ int pcsr_spmm_epilogue(pcsr_handle_t h, const float *B, float *C, int32_t K, con
     pcsr::LaunchShape ls;
     int rc = spmm_check(h, B, C, K, &ls, true);
     if (rc != PCSR_OK) return rc;
-    const uintptr_t align = 4u * (unsigned)ls.vec;
+    const uintptr_t align = operand_align(h, ls);
     if (reinterpret_cast<uintptr_t>(epi->self) % align || reinterpret_cast<uintptr_t>(epi->mask) % align)
         return PCSR_E_INVALID_ARG;
     if (h->n_split > 0 && (h->flags & PCSR_FLAG_ATOMIC_SPLIT)) return PCSR_E_UNSUPPORTED;
@@ -976,6 +985,7 @@ int pcsr_set_kernel_params(pcsr_handle_t h, int32_t lanes_per_row, int32_t vec, 
     if (rc != PCSR_OK) return rc;
     h->lpr = lanes_per_row;
     h->vec = vec;
+    h->asked_vec = 0;
     h->rep = rep;
     h->waves = waves_per_wg;
     h->ipg = items_per_group;

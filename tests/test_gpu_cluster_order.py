@@ -343,3 +343,44 @@ def test_rows_from_column_windows_are_as_exact_as_from_memory(long_rows, V, leng
         limit = 1.04 * (plain ** 2 + whole ** 2) ** 0.5
         print(f"case rows of {length}, V={V}, window of {wc} {kern}: staged {staged:.3e}, plain {plain:.3e}, {limit:.3e}", flush=True)
         assert shape["lds_bytes"] > 0 and staged <= limit, (V, wc, kern, staged, plain, limit)
+
+
+@pytest.mark.parametrize("vec", [1, 2])
+@pytest.mark.parametrize("flags", [FLAG, FLAG | WINDOWS])
+def test_alignment_asked_for_is_that_of_the_parameters(vec, flags):
+    """What pcsr_select returns for scattered rows of 8 to 40 has vec = 2 (1 at K up to 32): operands at such addresses are taken
+    whatever order the build finds, others refused."""
+    n, rp, ci, va, _ = _planted(6001, 300, 30, 2, 21)
+    h = pc.pcsr_build(n, n, *_device(rp, ci, va), pc.make_params(lanes_per_row=32, vec=vec, rep=1, flags=flags))
+    assert pc.pcsr_format(h)["SG"] == 1024
+    for K in (32, 64, 128):
+        B, S = torch.randn(n, K, device="cuda"), torch.randn(n, K, device="cuda")
+        want, tailed = torch.empty_like(B), torch.empty_like(B)
+        pc.pcsr_spmm(h, B, want, K)
+
+        def at(offset, source=None):
+            t = torch.full((n * K + 4,), float("nan"), device="cuda")[offset:offset + n * K].view(n, K)
+            return t if source is None else t.copy_(source)
+
+        def epilogue(B, C, S):
+            e = pc.binding.pcsr_epilogue_t(None, S.data_ptr(), None, None, 0, 0)
+            return pc.binding._lib().pcsr_spmm_epilogue(h.raw, B.data_ptr(), C.data_ptr(), K, pc.binding.ctypes.byref(e), None)
+
+        assert epilogue(B, tailed, S) == 0
+        C = at(vec)
+        pc.pcsr_spmm(h, at(vec, B), C, K)
+        assert torch.equal(C, want)
+        C = at(vec)
+        assert epilogue(at(vec, B), C, at(vec, S)) == 0 and torch.equal(C, tailed)
+        if vec == 2:
+            assert epilogue(at(2, B), at(2), at(1, S)) == pc.binding.PCSR_E_INVALID_ARG
+            for b, c in ((1, 2), (2, 1)):
+                with pytest.raises(pc.PcsrError) as err:
+                    pc.pcsr_spmm(h, at(b, B), at(c), K)
+                assert err.value.code == pc.binding.PCSR_E_INVALID_ARG
+        pc.pcsr_set_kernel_params(h)
+        with pytest.raises(pc.PcsrError):
+            pc.pcsr_spmm(h, at(vec, B), want, K)
+        h.close()
+        h = pc.pcsr_build(n, n, *_device(rp, ci, va), pc.make_params(lanes_per_row=32, vec=vec, rep=1, flags=flags))
+    h.close()
