@@ -1186,8 +1186,11 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // Scattered rows may belong to communities whose ids were shuffled.  Looking for them and ordering the schedule by
     // them costs the build some 0.15 ms and 0.6 ns a row; run side by side the rows of a community gather from L2 and the
     // product takes 0.3 ps per nonzero and column less (250,000 rows of 48: K = 64 377 -> 145 us, K = 128
-    // 747 -> 262, K = 256 1485 -> 578; rows of 12, K = 256: 919 -> 508).  Asked for where one product pays for it.
-    if (!skewed && !windowed && scattered && p.V == 1 && d_hat >= 12.0 && 3e-7 * f[2] * (double)K >= 150.0 + 6e-4 * n)
+    // 747 -> 262, K = 256 1485 -> 578; rows of 12, K = 256: 919 -> 508).  Asked for where one product pays for it, and not
+    // where it would split a row of a handle that is not split otherwise: products on that one need no workspace, so
+    // the first of all may be captured in a graph.
+    if (!skewed && !windowed && scattered && p.V == 1 && (p.S || d_max <= pcsr::kClusterItem) && d_hat >= 12.0 &&
+        3e-7 * f[2] * (double)K >= 150.0 + 6e-4 * n)
         p.flags |= PCSR_FLAG_CLUSTER_IF_USEFUL;
     // And, for wide rows, windows of those communities in LDS (cluster_windows): 0.1 ms and 0.25 ns a row of build for
     // 0.06 ps per nonzero and column (250,000 rows of 48 in communities of 500: K = 256 577 -> 378 us, build 414 -> 586;

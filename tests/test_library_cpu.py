@@ -474,3 +474,16 @@ def test_half_a_wavefront_per_row_only_where_b_is_gathered_from_memory():
         assert launched(30_000, 20.0, K) == launched(90_000, 72.0, K) == 0     # the shape asked for: 16 lanes of 4
         assert launched(250_000, 20.0, K) == launched(500_000, 9.0, K) == 4    # 32 lanes
     assert launched(30_000, 20.0, 33) == 3 and launched(250_000, 20.0, 33) == 4
+
+
+def test_no_search_for_communities_where_it_would_split_a_row_that_is_whole():
+    """A product on a handle with S = 0 needs no workspace; in the order by community rows of over 1024 are split."""
+    def picked(d, d_max):
+        return pc.pcsr_select(_features("poisson", n=250_000, nnz=250_000 * d, d=d, d_hat=d, d_max=d_max, CV=0.4, PR_2=0.5,
+                                        near_512=1000 / 250_000), 512)
+
+    flag = pc.PCSR_FLAG_CLUSTER_IF_USEFUL
+    for d_max in (40, 1024):
+        assert picked(20.0, d_max).S == 0 and picked(20.0, d_max).flags & flag
+    assert picked(20.0, 1025).S == 0 and not picked(20.0, 1025).flags & flag
+    assert picked(48.0, 1025).S == 1 and picked(48.0, 1025).flags & flag   # split as it is
