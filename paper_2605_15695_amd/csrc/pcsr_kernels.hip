@@ -100,22 +100,18 @@ template <int VEC> __device__ __forceinline__ void store_vec(float *p, const flo
     }
 }
 
-// Elementwise tail of a row of C, columns k .. k + VEC - 1, in two parts: what it reads of that row, which can be
-// requested long before the row is there, and what it does.  One uniform branch for a plain SpMM.
-template <int VEC> struct TailRow {
-    float self[VEC], mask[VEC];
-};
-template <int VEC> __device__ __forceinline__ void fetch_tail(const Epilogue &ep, long row, int K, int k, TailRow<VEC> &t)
-{
-    if (ep.self) load_vec<VEC>(ep.self + row * K + k, t.self);
-    if (ep.mask) load_vec<VEC>(ep.mask + row * K + k, t.mask);
-}
-template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, int k, const TailRow<VEC> &t, float (&v)[VEC])
+// Elementwise tail of a row of C, columns k .. k + VEC - 1.  self_row and mask_row fetch what it reads of that row; where they
+// load it, that is at the point of use (loaded ahead of the bias the mask costs registers also where there is none: road graph of
+// 2,000,000 rows with a ReLU, K = 128 402 -> 418 us).
+template <int VEC, class Self, class Mask>
+__device__ __forceinline__ void finish(const Epilogue &ep, int k, Self self_row, Mask mask_row, float (&v)[VEC])
 {
     if (ep.self) {
         const float scale = 1.0f + (ep.self_eps ? *ep.self_eps : 0.0f);
+        float t[VEC];
+        self_row(t);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = fmaf(scale, t.self[e], v[e]);
+        for (int e = 0; e < VEC; ++e) v[e] = fmaf(scale, t[e], v[e]);
     }
     if (ep.bias) {
 #pragma unroll
@@ -126,16 +122,35 @@ template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, in
         for (int e = 0; e < VEC; ++e) v[e] = v[e] <= 0.0f ? 0.0f : v[e];
     }
     if (ep.mask) {
+        float t[VEC];
+        mask_row(t);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) v[e] = t.mask[e] <= 0.0f ? 0.0f : v[e];
+        for (int e = 0; e < VEC; ++e) v[e] = t[e] <= 0.0f ? 0.0f : v[e];
     }
 }
+// One uniform branch for a plain SpMM.
 template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, long row, int K, int k, float (&v)[VEC])
 {
     if (!ep.on) return;
-    TailRow<VEC> t;
-    fetch_tail<VEC>(ep, row, K, k, t);
-    finish<VEC>(ep, k, t, v);
+    finish<VEC>(ep, k, [&](float (&t)[VEC]) { load_vec<VEC>(ep.self + row * K + k, t); },
+                [&](float (&t)[VEC]) { load_vec<VEC>(ep.mask + row * K + k, t); }, v);
+}
+// What the tail reads of a row, requested long before the row is there.
+template <int VEC> struct TailRow {
+    float self[VEC], mask[VEC];
+};
+template <int VEC> __device__ __forceinline__ void fetch_tail(const Epilogue &ep, long row, int K, int k, TailRow<VEC> &t)
+{
+    if (ep.self) load_vec<VEC>(ep.self + row * K + k, t.self);
+    if (ep.mask) load_vec<VEC>(ep.mask + row * K + k, t.mask);
+}
+template <int VEC> __device__ __forceinline__ void finish(const Epilogue &ep, int k, const TailRow<VEC> &row, float (&v)[VEC])
+{
+    auto copy = [](const float (&from)[VEC], float (&t)[VEC]) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) t[e] = from[e];
+    };
+    finish<VEC>(ep, k, [&](float (&t)[VEC]) { copy(row.self, t); }, [&](float (&t)[VEC]) { copy(row.mask, t); }, v);
 }
 
 // cacheable store: workspace partials are read back by the next kernel
@@ -255,6 +270,7 @@ __device__ __forceinline__ const float *row_ptr(const float *base, long off, int
 // 0.5 % to kLongItems' three branches (R-MAT 2^22, K = 16: 1404 -> 1411 us).
 constexpr int kAsIs = 0;
 constexpr int kLongItems = 1; // balanced handles with long items (SpmmArgs::outer): sums of 32 vectors are added up apart
+constexpr int kEarlyTail = 2; // unsplit products whose tail reads the row: the self and mask rows are requested before the traversal
 
 // EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
 // branch alone cost the instance <2, false, 64, 1, 2> 4 %.
@@ -359,10 +375,11 @@ spmm_kernel(SpmmArgs a)
     const long K = a.K;
 
     // What the tail reads is requested before the traversal, where it fits the registers: behind it, it is one more round trip
-    // to memory for an item that is three of them in all (road graph of 2,000,000 rows with a self term: K = 64 304 -> 292
-    // us, K = 16 106 -> 98).  Items of balanced handles have too many registers in flight for it (R-MAT 2^20, K = 64: 420 ->
-    // 447).
-    constexpr bool EARLY = EPI && !S && V * REP * VEC <= 8;
+    // to memory for an item that is three of them in all (road graph of 2,000,000 rows with a self term: K = 64 285 -> 275
+    // us, K = 128 557 -> 534, with a mask 288 -> 281).  Not where it reads nothing: the registers cost a wavefront per SIMD (with a
+    // bias K = 64 235 -> 255, K = 128 449 -> 492).  Items of balanced handles have too many registers in flight for it (R-MAT 2^20,
+    // K = 64: 420 -> 447).
+    constexpr bool EARLY = FORM == kEarlyTail;
     TailRow<VEC> tail_row[EARLY ? V : 1][EARLY ? REP : 1];
     if constexpr (EARLY) {
 #pragma unroll
@@ -1230,6 +1247,8 @@ template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn
 {
     if constexpr (FORM == kLongItems && !(S && (V == 1 || LPR >= 32))) // (spmm_enqueue says which)
         return nullptr;
+    else if constexpr (FORM == kEarlyTail && (S || V * REP * VEC > 8))
+        return nullptr;
     else
         return &spmm_kernel<V, S, LPR, VEC, REP, EPI, FORM>;
 }
@@ -1435,7 +1454,8 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
                  : pick<false, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep);
         lds = sizeof(float) * 64 * ls.waves * V * ls.k_rep * ls.k_vec; // 64 KB at most
     } else {
-        fn = epi ? pick<true>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep) : pick_any(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, ls.ipg);
+        fn = epi && (args.epi.self || args.epi.mask) ? pick<true, kEarlyTail>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep) : nullptr;
+        if (!fn) fn = epi ? pick<true>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep) : pick_any(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, ls.ipg);
     }
     if (!fn) return hipErrorInvalidValue;
     hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), lds, stream, args);

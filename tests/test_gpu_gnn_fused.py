@@ -377,3 +377,23 @@ def test_a_handle_of_another_size_is_refused():
     with pytest.raises(ValueError):
         layer(X)
     assert out.shape == (g.n_rows, 32)
+
+
+@pytest.mark.parametrize("V", [1, 2])
+@pytest.mark.parametrize("K", [16, 33, 128, 512])
+def test_every_part_of_the_tail_alone_and_with_the_others(V, K):
+    """Tails with a self term or a mask run other instances than those without."""
+    g = synth.workload("poisson", "small")
+    h = pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, pc.make_params(V=V))
+    B, own, mask, bias = (torch.from_numpy(synth.dense_operand(n, K, "normal", 3 + i)).cuda()
+                          for i, n in enumerate((g.n_cols, g.n_rows, g.n_rows, 1)))
+    d = _dense(1, 1)
+    plain = d.spmm(h, g.n_rows, B).double()
+    for parts in range(1, 16):
+        kw = dict(self_term=own if parts & 1 else None, bias=bias.reshape(-1) if parts & 2 else None, relu=bool(parts & 4),
+                  mask=mask if parts & 8 else None)
+        want = plain + (own.double() if parts & 1 else 0.0) + (bias.double() if parts & 2 else 0.0)
+        want = torch.relu(want) if parts & 4 else want
+        want = torch.where(mask <= 0, 0.0, want) if parts & 8 else want
+        _close(d.spmm(h, g.n_rows, B, **kw), want, 1e-6)
+    h.close()
