@@ -314,27 +314,6 @@ hipError_t Upload::wait() noexcept
     return result;
 }
 
-void PageToucher::start(void *p, size_t bytes) noexcept
-{
-    constexpr size_t kPage = 4096, kThreads = 4;
-    if (bytes < kStagedBytes) return;
-    char *const at = static_cast<char *>(p);
-    try {
-        for (size_t t = 0; t < kThreads; ++t)
-            threads.emplace_back([=] {
-                const size_t end = bytes / kThreads * (t + 1);
-                for (size_t i = bytes / kThreads * t; i < end; i += kPage) __atomic_fetch_or(at + i, 0, __ATOMIC_RELAXED);
-            });
-    } catch (...) { // no more threads: the faults are taken later
-    }
-}
-
-void PageToucher::wait() noexcept
-{
-    for (std::thread &t : threads) t.join();
-    threads.clear();
-}
-
 } // namespace pcsr
 
 extern "C" int64_t pcsr_release_cached_if_low(void *stream)

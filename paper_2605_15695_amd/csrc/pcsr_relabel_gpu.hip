@@ -658,11 +658,9 @@ int permute_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, const f
                 int32_t *out_rowptr, int32_t *out_colidx, float *out_vals)
 {
     const int64_t nnz = rowptr[n];
-    // Beside the work: the faults of fresh output pages during the uploads, the values' upload during the columns' download
-    // (the link carries both ways at once).  10 M nonzeros: 4.3 ms, 4.8 one after the other (the link takes 1.5 ms for 41 MB up and 41 MB down at once, 0.9 for either).
-    PageToucher pages;
-    pages.start(out_colidx, sizeof(int32_t) * nnz);
-    pages.start(out_vals, sizeof(float) * nnz);
+    // Beside the work: the values' upload during the columns' download (the link carries both ways at once).  10 M
+    // nonzeros: 4.0 ms, 4.8 one after the other (the link takes 1.5 ms for 41 MB up and 41 MB down at once, 0.9 for
+    // either).  Taking the faults of fresh output pages ahead, on threads of their own, costs more than it saves: 4.2 ms.
     Scratch sc;
     Upload values; // waits before the memory it writes is given back
     int32_t *d_perm = nullptr, *inv = nullptr, *flag = nullptr, *len = nullptr, *from = nullptr, *rp = nullptr, *ci = nullptr,
@@ -729,7 +727,6 @@ int permute_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, const f
     }
     TRY_GPU(hipMemcpy(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost));
     if (bad) return kUseHost; // a column twice in a row: their order is the host sort's business
-    pages.wait();
     // (an output in the place of the values is not written before they are read)
     if (reinterpret_cast<uintptr_t>(out_colidx) < reinterpret_cast<uintptr_t>(vals + nnz) &&
         reinterpret_cast<uintptr_t>(vals) < reinterpret_cast<uintptr_t>(out_colidx + nnz))
