@@ -728,9 +728,11 @@ int permute_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, const f
     TRY_GPU(hipMemcpy(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost));
     if (bad) return kUseHost; // a column twice in a row: their order is the host sort's business
     // (an output in the place of the values is not written before they are read)
-    if (reinterpret_cast<uintptr_t>(out_colidx) < reinterpret_cast<uintptr_t>(vals + nnz) &&
-        reinterpret_cast<uintptr_t>(vals) < reinterpret_cast<uintptr_t>(out_colidx + nnz))
-        TRY_GPU(values.wait());
+    auto in_values = [&](const int32_t *out, int64_t count) {
+        return reinterpret_cast<uintptr_t>(out) < reinterpret_cast<uintptr_t>(vals + nnz) &&
+               reinterpret_cast<uintptr_t>(vals) < reinterpret_cast<uintptr_t>(out + count);
+    };
+    if (in_values(out_rowptr, n + 1) || in_values(out_colidx, nnz)) TRY_GPU(values.wait());
     TRY_GPU(copy_to_host(out_rowptr, rp, sizeof(int32_t) * (n + 1)));
     TRY_GPU(copy_to_host(out_colidx, ci, sizeof(int32_t) * nnz));
     TRY_GPU(values.wait());

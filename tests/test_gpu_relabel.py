@@ -243,3 +243,32 @@ def test_operator_takes_device_arrays_and_refuses_bad_ones():
     with pytest.raises(pc.PcsrError) as e:
         PcsrOperator(n, n, rp, bad, va)
     assert e.value.code == pc.binding.PCSR_E_BAD_CSR
+
+
+@pytest.mark.parametrize("shared", ["rowptr", "colidx", "vals", "all inputs"])
+def test_permuted_matrix_may_take_the_place_of_its_inputs(shared):
+    """Outputs in memory that an input is read from, the values among them, which are uploaded beside the work."""
+    rng = np.random.default_rng(5)
+    n = 1_300_000
+    lengths = rng.integers(1, 3, n)                       # more row pointers than a copying thread is done with at once
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = rng.integers(0, n // 2, n)
+    ci = np.stack([ci, ci + 1 + rng.integers(0, n // 2 - 1, n)], 1)[np.arange(2)[None, :] < lengths[:, None]].astype(np.int32)
+    va = rng.standard_normal(ci.size).astype(np.float32)
+    perm = rng.permutation(n).astype(np.int32)
+    want = pc.pcsr_permute_csr(n, rp, ci, va, perm)
+    at = va.copy()                                        # the values' own memory, for an output or two
+    ins = [rp.copy(), ci.copy(), at]
+    outs = [np.empty_like(x) for x in want]
+    if shared == "rowptr":
+        outs[0] = at.view(np.int32)[-(n + 1):]
+    elif shared == "colidx":
+        outs[1] = at.view(np.int32)
+    elif shared == "vals":
+        outs[2] = at
+    else:
+        outs = ins
+    rc = pc.binding._lib().pcsr_permute_csr(n, *(x.ctypes.data for x in ins), perm.ctypes.data, *(x.ctypes.data for x in outs))
+    assert rc == 0
+    for k in range(3):
+        assert np.array_equal(outs[k].view(np.uint32), want[k].view(np.uint32)), k
