@@ -44,7 +44,8 @@ enum {
                                   are uploaded first).  CSR arrays given in device memory are
                                   always built this way, and so are host arrays of 200,000
                                   nonzeros and more, unless the scratch memory that takes does
-                                  not fit; the arrays come out the same either way.
+                                  not fit; the arrays come out the same either way (except with
+                                  PCSR_FLAG_CLUSTER_IF_USEFUL, which the host builder ignores).
                                   The windows of col_window are then chosen there as well      */
     PCSR_FLAG_COLUMN_ORDER = 64,/* S = 1 only: column-ordered schedule.  The work items of
                                   panels that were split run in ascending order of their first
@@ -67,7 +68,10 @@ enum {
                                   Where pcsr_select finds it worth a second copy of the nonzeros,
                                   products of 64 columns or more (a multiple of 4, parameters on
                                   auto) stage the community's rows of B in LDS.  The alignment
-                                  asked of B and C stays that of the vec passed, if any          */
+                                  asked of B and C stays that of the vec passed, if any.
+                                  So the format depends on the scratch memory at hand: where that
+                                  of the search does not fit the flag does nothing, where that of
+                                  the second copy does not the order is had without it           */
     PCSR_FLAG_ATOMIC_SPLIT = 32 /* S = 1 only: panels that were split accumulate into C with
                                   fp32 atomics, as Algorithm 2 prints it, instead of the
                                   default two-pass write-back (see pcsr_spmm)                 */

@@ -1,7 +1,7 @@
 // A device of host memory for the CPU tests of the library's host code: the HIP calls it makes, with
 // allocations that can be made to fail, on the device and (operator new) on the host.  Kernels do not run
 // (hipLaunchKernel does nothing), so only what happens before the first result of one is read can be
-// tested.
+// tested, and what follows a result that a test supplies (fake_hip_answer).
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -78,7 +78,21 @@ int hipFree(void *p)
     return kOk;
 }
 int hipHostMalloc(void **p, std::size_t bytes, unsigned flags) { (void)p; (void)bytes; (void)flags; return kOutOfMemory; }
-int hipMemcpy(void *dst, const void *src, std::size_t bytes, int kind) { (void)kind; std::memcpy(dst, src, bytes); return kOk; }
+// A copy of `bytes` bytes to the host brings these in place of what is there (bytes 0: none does).
+static std::size_t answer_bytes[4];
+static unsigned char answers[4][64];
+void fake_hip_answer(int slot, std::size_t bytes, const void *what)
+{
+    answer_bytes[slot] = bytes;
+    std::memcpy(answers[slot], what, bytes);
+}
+int hipMemcpy(void *dst, const void *src, std::size_t bytes, int kind)
+{
+    std::memcpy(dst, src, bytes);
+    for (int i = 0; i < 4; ++i)
+        if (kind == 2 && bytes && bytes == answer_bytes[i]) std::memcpy(dst, answers[i], bytes);
+    return kOk;
+}
 int hipMemcpyAsync(void *dst, const void *src, std::size_t bytes, int kind, void *s)
 {
     (void)kind;

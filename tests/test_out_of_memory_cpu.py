@@ -194,3 +194,31 @@ else:
     except pc.PcsrError as e:
         assert e.code == binding.PCSR_E_BAD_CSR
 """)
+
+
+# the upload's three arrays, the columns and values, the check's two; then what the search for communities asks for
+@pytest.mark.parametrize("k", range(8, 13))
+@pytest.mark.parametrize("S", [0, 1])
+def test_without_scratch_for_communities_the_build_goes_on(fake, k, S):
+    """Rows that look like communities, by what the library is told that the probe and the rounds found: out of memory in the
+    search leaves the format asked for, out of memory for the windows the order without them."""
+    _run(fake, f"""
+checked = np.zeros(10, np.int32)                           # bad, first, last, longest, nonempty, -, two sums of 64 bits
+checked[[2, 3, 4, 6]] = n * deg, deg, n, 1 << 20
+found = np.array([n * 16, n * 16, (1 << 17) // 100], np.uint64)  # same, sampled, pairs with one label
+for slot, a in enumerate((checked, found)):
+    fake.fake_hip_answer(slot, ctypes.c_size_t(a.nbytes), a.ctypes.data_as(ctypes.c_void_p))
+flags = pc.PCSR_FLAG_CLUSTER_IF_USEFUL | 1 << 28 | pc.PCSR_FLAG_GPU_BUILD | ({S} and pc.PCSR_FLAG_COLUMN_ORDER)
+fake.fake_hip_fail({k}, {k} + ({k} == 12))                 # (there once more after the blocks kept for reuse have gone back)
+h = pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(V=1, S={S}, SG=32 * {S}, flags=flags, vec=2, lanes_per_row=16))
+assert fake.fake_hip_allocations() >= {k}
+f, launch = pc.pcsr_format(h), pc.pcsr_query_launch(h, 64)
+assert launch["lds_bytes"] == 0                            # no windows
+if {k} < 12:
+    assert f["S"] == {S} and (not {S} or f["SG"] == 32) and (launch["lanes_per_row"], launch["vec"]) == (16, 2)
+else:
+    assert f["S"] == 1 and f["SG"] == 1024 and (launch["lanes_per_row"], launch["vec"]) == (16, 4)
+h.close()
+pc.pcsr_release_cached()
+assert fake.fake_hip_live() == 0
+""")
