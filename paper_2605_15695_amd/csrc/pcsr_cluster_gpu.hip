@@ -19,7 +19,7 @@ constexpr int kRoundThreads = 1024, kRoundBlocks = 512;
 constexpr int kRounds = 6;
 constexpr int kSamples = 4096; // rows the probe looks at
 
-// the integer mixer of pcsr_reorder
+// the integer mixer of pcsr_reorder: lowbias32, a published 32-bit hash (found by C. Wellons' hash-prospector search)
 __device__ __forceinline__ uint32_t mix(uint32_t x)
 {
     x ^= x >> 16;

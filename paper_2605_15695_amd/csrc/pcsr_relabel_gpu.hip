@@ -54,7 +54,7 @@ __global__ void __launch_bounds__(kThreads) split_pairs_kernel(int64_t nnz, cons
 // deterministic tie-break priority of a label in a given round (as on the host: lowbias32)
 __device__ __forceinline__ uint32_t mix(uint32_t x, uint32_t round)
 {
-    x ^= round * 0x9E3779B9u;
+    x ^= round * 0x9E3779B9u; // the rest: lowbias32, a published 32-bit hash (C. Wellons' hash-prospector)
     x ^= x >> 16;
     x *= 0x7feb352du;
     x ^= x >> 15;

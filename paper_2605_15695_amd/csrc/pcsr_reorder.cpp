@@ -23,7 +23,7 @@ template <class F> void par_for(int64_t n, F &&fn) { pcsr::parallel_for(n, n < 4
 // "lowbias32" (hash prospector, public domain) of the label, which the round shifts first
 inline uint32_t mix(uint32_t x, uint32_t round)
 {
-    x ^= round * 0x9E3779B9u;
+    x ^= round * 0x9E3779B9u; // the rest: lowbias32, a published 32-bit hash (C. Wellons' hash-prospector)
     x ^= x >> 16;
     x *= 0x7feb352du;
     x ^= x >> 15;

@@ -124,7 +124,6 @@ __global__ void __launch_bounds__(kTurnThreads) __attribute__((amdgpu_waves_per_
     __shared__ int32_t from[1 << kTurnDigit], to[1 << kTurnDigit];
     typedef hipcub::BlockScan<int, kTurnThreads> Scan;
     __shared__ typename Scan::TempStorage tmp;
-    __shared__ int64_t s_row;
     __shared__ int s_cnt[kTurnWaves];
     const Tile<SECOND> tile(a);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = (int)(tile.end - tile.begin);

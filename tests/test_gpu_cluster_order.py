@@ -197,6 +197,9 @@ def test_windows_of_communities(n, block, inner, outer, extra, windows):
     pc.pcsr_set_kernel_params(again, lanes_per_row=16, vec=4, rep=1)
     assert pc.pcsr_query_launch(again, K)["lds_bytes"] == 0
     pc.pcsr_spmm(again, B.nan_to_num(), D, K)
+    E = torch.empty_like(D)
+    pc.pcsr_spmm(plain, B.nan_to_num(), E, K)
+    assert torch.equal(D, E)
     pc.pcsr_set_kernel_params(again, flags=pc.PCSR_FLAG_NO_XCD_REMAP)
     pc.pcsr_spmm(again, B, D, K)
     assert torch.equal(torch.nan_to_num(C), torch.nan_to_num(D))
