@@ -42,7 +42,8 @@ PROFILED_TRAFFIC = {
 
 
 def kernel_instance(V: int, S: int, launch: dict) -> str:
-    """Name of the SpMM kernel instance as rocprofv3 prints it."""
+    """Name of the SpMM kernel instance as rocprofv3 prints it, less the last argument (which only handles with long
+    rows change: a form of the instance that adds up their sums in more steps, over the same traffic)."""
     shape = f"{launch['lanes_per_row']}, {launch['vec']}, {launch['rep']}"
     if launch["lds_bytes"]:
         return f"spmm_window_kernel<{V}, {shape}, {'true' if S else 'false'}>"  # true: windows of communities

@@ -65,13 +65,16 @@ enum {
                                   another, dealt to the 8 XCDs as contiguous ranges of equal work
                                   (items of longer rows first, in column order), and its kernel
                                   parameters are set to auto.  Otherwise the flag does nothing.
-                                  Where pcsr_select finds it worth a second copy of the nonzeros,
-                                  products of 64 columns or more (a multiple of 4, parameters on
-                                  auto) stage the community's rows of B in LDS.  The alignment
-                                  asked of B and C stays that of the vec passed, if any.
-                                  So the format depends on the scratch memory at hand: where that
-                                  of the search does not fit the flag does nothing, where that of
-                                  the second copy does not the order is had without it           */
+                                  The alignment asked of B and C stays that of the vec passed, if
+                                  any.  The format depends on the scratch memory at hand: where that
+                                  of the search does not fit the flag does nothing               */
+    PCSR_FLAG_CLUSTER_WINDOWS = 1 << 28, /* with CLUSTER_IF_USEFUL, and set by pcsr_select where one
+                                  product pays for it: a second copy of the nonzeros (8 bytes each,
+                                  for as long as the handle lives) by which products of 64 columns
+                                  or more (a multiple of 4, parameters on auto) stage the
+                                  community's rows of B in LDS.  Only if at least half of the
+                                  vectors then lie inside, no row is longer than 1024 and the memory
+                                  for it fits; cleared, the order by community is had alone      */
     PCSR_FLAG_ATOMIC_SPLIT = 32 /* S = 1 only: panels that were split accumulate into C with
                                   fp32 atomics, as Algorithm 2 prints it, instead of the
                                   default two-pass write-back (see pcsr_spmm)                 */
@@ -237,7 +240,7 @@ int pcsr_query_launch(pcsr_handle_t h, int32_t K, int32_t out[8]);
 /*
  * The same for the kernel instance that pcsr_spmm launches.  It differs where another shape
  * stands in for that one: an auto shape whose K is no multiple of 4 or, for rows in 64-column
- * slices, of 32, and pcsr_select's shapes with flag bits above 15 (vec need not divide K there).
+ * slices, of 32, and pcsr_select's shapes with flag bits 16-27 (vec need not divide K there).
  */
 int pcsr_query_kernel(pcsr_handle_t h, int32_t K, int32_t out[8]);
 

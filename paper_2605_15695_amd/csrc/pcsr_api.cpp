@@ -31,7 +31,6 @@ constexpr int32_t kWidePair = 8 << kWideShift;
 constexpr int32_t kWideTwice = 16 << kWideShift;
 constexpr int kWideForShift = 21;
 constexpr int32_t kWideFor = 127 << kWideForShift;
-constexpr int32_t kClusterWindows = 1 << 28; // with PCSR_FLAG_CLUSTER_IF_USEFUL: windows of communities too (pcsr_select)
 constexpr int32_t kWideBits = kWideShape | kWidePair | kWideTwice | kWideFor;
 
 int32_t stands_for(int lanes, int vec, int rep)
@@ -425,7 +424,7 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     int rc = pcsr::build_device(n_rows, n_cols, nnz, rowptr, colidx, vals, prm.V, prm.S, prm.SG, prm.omega,
                                 !(prm.flags & PCSR_FLAG_NO_VALIDATE), column_order,
                                 (prm.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && !prm.col_window,
-                                (prm.flags & kClusterWindows) != 0, late, &db, &herr);
+                                (prm.flags & PCSR_FLAG_CLUSTER_WINDOWS) != 0, late, &db, &herr);
     h->host.n_rows = n_rows;
     h->host.n_cols = n_cols;
     h->host.nnz = nnz;
@@ -1198,7 +1197,7 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // pay for the staging (250,000 rows of 14: 205 -> 225).  Where one product pays for it, too.
     if ((p.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && d_hat >= 22.0 && K >= 192 && K % 4 == 0 &&
         6e-8 * f[2] * (double)K >= 100.0 + 2.5e-4 * n)
-        p.flags |= kClusterWindows;
+        p.flags |= PCSR_FLAG_CLUSTER_WINDOWS;
 
     // Launch shape: the widest vector load that divides K, one lane group spanning the
     // whole row of C when it fits a wavefront, repeats beyond that.

@@ -158,7 +158,7 @@ def test_selector_asks_where_one_product_pays_for_the_search():
     assert not pc.pcsr_select(f, 512).flags & FLAG
 
 
-WINDOWS = 1 << 28  # what pcsr_select adds to FLAG where windows of the communities pay as well
+WINDOWS = pc.PCSR_FLAG_CLUSTER_WINDOWS
 
 
 @pytest.mark.parametrize("n,block,inner,outer,extra,windows", [

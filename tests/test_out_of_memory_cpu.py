@@ -208,7 +208,7 @@ checked[[2, 3, 4, 6]] = n * deg, deg, n, 1 << 20
 found = np.array([n * 16, n * 16, (1 << 17) // 100], np.uint64)  # same, sampled, pairs with one label
 for slot, a in enumerate((checked, found)):
     fake.fake_hip_answer(slot, ctypes.c_size_t(a.nbytes), a.ctypes.data_as(ctypes.c_void_p))
-flags = pc.PCSR_FLAG_CLUSTER_IF_USEFUL | 1 << 28 | pc.PCSR_FLAG_GPU_BUILD | ({S} and pc.PCSR_FLAG_COLUMN_ORDER)
+flags = pc.PCSR_FLAG_CLUSTER_IF_USEFUL | pc.PCSR_FLAG_CLUSTER_WINDOWS | pc.PCSR_FLAG_GPU_BUILD | ({S} and pc.PCSR_FLAG_COLUMN_ORDER)
 fake.fake_hip_fail({k}, {k} + ({k} == 12))                 # (there once more after the blocks kept for reuse have gone back)
 h = pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(V=1, S={S}, SG=32 * {S}, flags=flags, vec=2, lanes_per_row=16))
 assert fake.fake_hip_allocations() >= {k}
