@@ -1392,7 +1392,8 @@ KernelFn pick_row_window(bool long_items)
 // More than 64 KiB of dynamic LDS has to be allowed per kernel function: raised to
 // the 160 KiB of the CU once per function and device, not on every launch (the
 // call is host work and is not capturable in a HIP graph).
-static hipError_t allow_window_lds(KernelFn fn)
+// also: another function to be raised with it, so that a handle whose products run that one finds it done.
+static hipError_t allow_window_lds(KernelFn fn, KernelFn also)
 {
     static std::mutex mu;
     static std::set<std::pair<int, const void *>> raised;
@@ -1402,22 +1403,21 @@ static hipError_t allow_window_lds(KernelFn fn)
     std::lock_guard<std::mutex> lock(mu);
     const auto key = std::make_pair(dev, reinterpret_cast<const void *>(fn));
     if (!raised.count(key)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
+        for (KernelFn f : {fn, also}) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(f),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return e;
+        }
         try {
             raised.insert(key);
+            raised.insert(std::make_pair(dev, reinterpret_cast<const void *>(also)));
         } catch (...) { // no memory to note it: raised again next time
         }
     }
     return hipSuccess;
 }
 
-hipError_t prepare_row_windows()
-{
-    const hipError_t e = allow_window_lds(pick_row_window(false));
-    return e == hipSuccess ? allow_window_lds(pick_row_window(true)) : e;
-}
+hipError_t prepare_row_windows() { return allow_window_lds(pick_row_window(false), pick_row_window(true)); }
 
 bool window_kernel_exists(int V, int lpr, int vec, int rep)
 {
@@ -1438,10 +1438,13 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
 {
     if (ls.grid_x <= 0 || ls.grid_y <= 0) return hipSuccess; // nothing to do
     if (ls.window) {
-        KernelFn fn = args.rows ? pick_row_window(args.outer != 0)
-                                : (S ? nullptr : pick_window(V, ls.lpr, ls.vec, ls.rep, args.outer != 0));
+        auto pick_for = [&](bool long_items) -> KernelFn {
+            if (args.rows) return pick_row_window(long_items);
+            return S ? nullptr : pick_window(V, ls.lpr, ls.vec, ls.rep, long_items);
+        };
+        KernelFn fn = pick_for(args.outer != 0);
         if (!fn) return hipErrorInvalidValue;
-        const hipError_t e = allow_window_lds(fn);
+        const hipError_t e = allow_window_lds(fn, pick_for(args.outer == 0));
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);
         return hipGetLastError();

@@ -387,3 +387,30 @@ def test_alignment_asked_for_is_that_of_the_parameters(vec, flags):
         h.close()
         h = pc.pcsr_build(n, n, *_device(rp, ci, va), pc.make_params(lanes_per_row=32, vec=vec, rep=1, flags=flags))
     h.close()
+
+
+def test_first_product_from_column_windows_over_long_rows_may_be_captured(long_rows):
+    """Beside products of a handle with short rows, whose kernel is another one."""
+    n, rp, ci, values = long_rows(300)
+    perm, _ = pc.pcsr_reorder(n, rp, ci)
+    rp, ci, va = pc.pcsr_permute_csr(n, rp, ci, values[1], perm)
+    m, srp, sci, svalues = long_rows(48)
+    sperm, _ = pc.pcsr_reorder(m, srp, sci)
+    short = pc.pcsr_build(m, m, *pc.pcsr_permute_csr(m, srp, sci, svalues[1], sperm), pc.make_params(col_window=256))
+    h = pc.pcsr_build(n, n, rp, ci, va, pc.make_params(col_window=256))
+    K = 128
+    assert all(pc.pcsr_query_launch(x, K)["lanes_per_row"] == 32 and pc.pcsr_query_launch(x, K)["lds_bytes"] for x in (short, h))
+    pc.pcsr_spmm(short, torch.randn(m, K, device="cuda"), torch.empty(m, K, device="cuda"), K)
+    B, C = torch.randn(n, K, device="cuda"), torch.zeros(n, K, device="cuda")
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        pc.pcsr_spmm(h, B, C, K, torch.cuda.current_stream())
+    for _ in range(3):
+        B.normal_()
+        want = torch.empty_like(C)
+        pc.pcsr_spmm(h, B, want, K)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, want)
+    short.close(), h.close()
