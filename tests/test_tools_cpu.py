@@ -69,3 +69,15 @@ def test_rule_alternatives_and_their_table():
     with redirect_stdout(out):
         report.rules_table(recs)
     assert "| w | 100 | 1, 1, 32 / 32x4x1 | 1.0000 | 2.00 (" in out.getvalue()
+
+
+def test_windows_of_communities_are_no_stand_in_shape():
+    import numpy as np
+
+    import paper_2605_15695_amd as pc
+
+    f = np.zeros(len(pc.FEATURE_NAMES))
+    f[0] = f[1] = 250_000
+    f[2], f[4], f[5], f[6], f[7], f[15], f[16] = 12e6, 48.0, 48.0, 80.0, 0.15, 0.5, 0.004
+    alt = sweep.rule_alternatives(pc.pcsr_select(f, 256), 256)
+    assert "own shape" not in {a[0] for a in alt} and all(a[1].flags & pc.PCSR_FLAG_CLUSTER_WINDOWS for a in alt)
