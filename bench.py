@@ -32,7 +32,7 @@ PROFILED_TRAFFIC = {
     ("rmat20-full", 64, "spmm_kernel<1, true, 16, 4, 1, false>", 64, "column"): 2174585919,
     ("sbm-full", 256, "spmm_window_kernel<1, 16, 4, 1, false>", 0, "index"): 1879832989,
     ("sbm_shuffled-full", 256, "spmm_window_kernel<1, 16, 4, 1, true>", 1024, "cluster"): 1957128174,
-    ("rmat22-full", 16, "spmm_kernel<1, true, 16, 1, 1, false>", 64, "column"): 7068248499,
+    ("rmat22-full", 16, "spmm_kernel<1, true, 16, 1, 1, false>", 64, "column"): 7060422290,
     ("rmat22-full", 32, "spmm_kernel<1, true, 8, 4, 1, false>", 64, "column"): 9984136412,
     ("rmat22-full", 64, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 17939440492,
     ("rmat22-full", 128, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 36093605165,

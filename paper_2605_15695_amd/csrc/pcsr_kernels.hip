@@ -924,8 +924,8 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
         // therefore adds up sums of 32 apart with ROWS, whose rows were items of 32 vectors and a second pass without the windows,
         // and makes the sums 16 vectors elsewhere, which costs no registers.  Rms of the difference from 64 bits, relative to
         // the sum of magnitudes, equal values: ROWS at rows of 48, 100 and 300 1.25, 1.03 and 0.85e-8, with LONG 1.16, 0.88 and
-        // 0.60e-8, items of 32 1.30, 0.99 and 0.67e-8; column windows at rows of 100, 200 and 400 1.01, 0.90 and 0.81e-8, with
-        // LONG 0.99, 0.83 and 0.70e-8, gathered from memory 1.01, 0.82 and 0.68e-8.  (A third level for all of them: 250,000 rows of 48,
+        // 0.60e-8, items of 32 1.30, 0.99 and 0.67e-8; column windows at rows of 200 and 400 0.90 and 0.81e-8, with
+        // LONG 0.83 and 0.70e-8, gathered from memory 0.82 and 0.68e-8.  (A third level for all of them: 250,000 rows of 48,
         // K = 256 366 -> 371 us; paired rows, whose instances spill, 532 -> 660.)
         constexpr bool OUTER = LONG && ROWS;
         constexpr int PART = LONG && !ROWS ? 16 : 8; // vectors of a sum, in whole steps and within a chunk
