@@ -261,9 +261,30 @@ template <int LPR, bool CONST_LANE> __device__ __forceinline__ float bcast_any(f
 // base + the byte offset that lane j of every DPP row holds
 __device__ __forceinline__ const float *row_ptr(const float *base, long off, int j)
 {
-    const int lo = bcast16_const((int)off, j), hi = bcast16_const((int)(off >> 32), j);
-    return reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) +
-                                           (long)(((unsigned long)(unsigned)hi << 32) | (unsigned)lo));
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    const i2 o = {bcast16_const((int)off, j), bcast16_const((int)(off >> 32), j)};
+    return reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + __builtin_bit_cast(long, o));
+}
+
+// Operands of at most kNearBytes: a gather's address is a scalar base and a 32-bit offset, one addition that takes the
+// broadcast with it, where 64-bit addresses took five vector instructions.  Where a lane loads one dword, B is a buffer: a
+// slot with nothing to load reads past the end, at kPast, which the hardware answers with zeros and no access, and the
+// branches around such slots go as well.  (8- and 16-byte loads were 4-6 % slower as buffer loads, at any alignment.)  A
+// lane past the last column reads the last one, as its neighbour does: reading anything else, past the end too, it doubled
+// the time of a load (16 lanes x dword x 2, K = 22: 131 us for 66).  Cliques of 40, 300,000 rows: K = 16 61 -> 50 us, K = 22
+// 77 -> 67, paired rows 45 -> 38 and 61 -> 48; where B comes from memory, R-MAT 2^22, K = 16 1417 -> 1392.  16-byte loads:
+// cliques of 24, K = 75 126.6 -> 123.7, paired rows of 40, K = 64 78 -> 76, others as before.
+constexpr uint64_t kNearBytes = 0xe0000000u;
+constexpr unsigned kPast = 0xf0000000u; // plus a column's bytes (launch_spmm: K is below 2^20) still past the end, and no wrap
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t near_operand(const SpmmArgs &a)
+{
+    // stride 0: num_records in bytes; word 3: 32-bit data
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.B), 0, (int)((unsigned)a.n_cols * ((unsigned)a.K * 4u)),
+                                             0x00020000);
+}
+__device__ __forceinline__ float load_near(__amdgpu_buffer_rsrc_t b, unsigned at)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)at, 0, 0));
 }
 
 // What an instance of spmm_kernel is for beside the plain product.  Instances of their own: products with short items lost
@@ -276,12 +297,14 @@ constexpr int kEarlyTail = 2; // unsplit products whose tail reads the row: the 
 // branch alone cost the instance <2, false, 64, 1, 2> 4 %.
 // (Seven waves per SIMD are asked for where the compiler would take six for want of a few registers; two is what 512
 // threads imply.)
-template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM>
+// NEAR: offsets of 32 bits (kNearBytes).
+template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM, bool NEAR>
 __global__ void __launch_bounds__(512)
 __attribute__((amdgpu_waves_per_eu(FORM == kLongItems && V == 2 && LPR == 32 && VEC == 4 && REP == 1 && !EPI ? 7 : 2)))
 spmm_kernel(SpmmArgs a)
 {
     constexpr bool OUTER = FORM == kLongItems;
+    constexpr bool BUFFER = NEAR && VEC == 1;
     constexpr int G = 64 / LPR;
     // vectors gathered per inner step: 16 registers of B data in flight, 32 for balanced
     // handles and for V = 1 with groups of up to 8 lanes (K <= 32: 4-8 % faster on rows of 40
@@ -373,6 +396,13 @@ spmm_kernel(SpmmArgs a)
             for (int e = 0; e < VEC; ++e) acc[v][r][e] = 0.0f;
 
     const long K = a.K;
+    __amdgpu_buffer_rsrc_t Bn;
+    unsigned near_col[REP]; // bytes
+    if constexpr (BUFFER) Bn = near_operand(a);
+    if constexpr (NEAR) {
+#pragma unroll
+        for (int r = 0; r < REP; ++r) near_col[r] = (unsigned)(kv[r] ? kc[r] : a.K - VEC) * 4u;
+    }
 
     // What the tail reads is requested before the traversal, where it fits the registers: behind it, it is one more round trip
     // to memory for an item that is three of them in all (road graph of 2,000,000 rows with a self term: K = 64 285 -> 275
@@ -455,12 +485,18 @@ spmm_kernel(SpmmArgs a)
     int until = PERIOD; // chunks until the next sum is put apart (the same in every lane group)
     for (int base = head; base < tail; base += CH) {
         long off[NH]; // DPP: in bytes, computed once by the lane that holds the entry
+        unsigned near_off[NH]; // NEAR: the same
         int c[NH];
         float av[NH][V];
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
             c[h] = c_next[h];
-            off[h] = (long)c[h] * (K * 4);
+            if constexpr (NEAR) {
+                const int idx = base + 16 * h + (DPP ? lg & 15 : lg);
+                near_off[h] = idx < tail ? (unsigned)c[h] * ((unsigned)a.K * 4u) : kPast;
+            } else {
+                off[h] = (long)c[h] * (K * 4);
+            }
 #pragma unroll
             for (int v = 0; v < V; ++v) av[h][v] = av_next[h][v];
         }
@@ -502,8 +538,18 @@ spmm_kernel(SpmmArgs a)
             float b[U][REP][VEC];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                unsigned near_row = 0;
+                if constexpr (NEAR) near_row = (unsigned)bcast_any<DPP ? 16 : LPR, DPP>((int)near_off[h], j + u);
+                if constexpr (BUFFER) {
+#pragma unroll
+                    for (int r = 0; r < REP; ++r)
+                        b[u][r][0] = load_near(Bn, near_row + near_col[r]);
+                    continue;
+                }
                 const float *at;
-                if constexpr (DPP)
+                if constexpr (NEAR)
+                    at = reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.B) + (near_row + near_col[0]));
+                else if constexpr (DPP)
                     at = row_ptr(B_lane, off[h], j + u);
                 else if constexpr (LPR == 64)
                     at = a.B + (long)bcast<LPR>(c[h], j + u) * K;
@@ -514,7 +560,10 @@ spmm_kernel(SpmmArgs a)
 #pragma unroll
                     for (int r = 1; r < REP; ++r) {
                         if (kv[r]) {
-                            load_vec<VEC>(at + (LPR == 64 ? kc[r] : step_col[r]), b[u][r]);
+                            load_vec<VEC>(NEAR ? reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.B) +
+                                                                                 (near_row + near_col[r]))
+                                               : at + (LPR == 64 ? kc[r] : step_col[r]),
+                                          b[u][r]);
                         } else {
 #pragma unroll
                             for (int e = 0; e < VEC; ++e) b[u][r][e] = 0.0f;
@@ -549,14 +598,14 @@ spmm_kernel(SpmmArgs a)
 #pragma unroll
             for (int j = 0; j < CH; j += U) {
                 if (j >= cnt) break;
-                if (wave_all(j + U <= cnt))
+                if (BUFFER || wave_all(j + U <= cnt))
                     step(j, std::true_type{});
                 else
                     step(j, std::false_type{});
             }
         } else {
             for (int j = 0; j < cnt; j += U) {
-                if (wave_all(j + U <= cnt))
+                if (BUFFER || wave_all(j + U <= cnt))
                     step(j, std::true_type{});
                 else
                     step(j, std::false_type{});
@@ -1243,57 +1292,61 @@ template <int VEC> __global__ void __launch_bounds__(256) reduce_kernel(ReduceAr
 
 using KernelFn = void (*)(SpmmArgs);
 
-template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn instance()
+template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn instance(bool near)
 {
     if constexpr (FORM == kLongItems && !(S && (V == 1 || LPR >= 32))) // (spmm_enqueue says which)
         return nullptr;
     else if constexpr (FORM == kEarlyTail && (S || V * REP * VEC > 8))
         return nullptr;
-    else
-        return &spmm_kernel<V, S, LPR, VEC, REP, EPI, FORM>;
+    else {
+        // A whole wavefront to a row has its addresses in scalar registers; more repeats than these are taken only where asked for.
+        if constexpr (LPR < 64 && REP <= 2)
+            if (near) return &spmm_kernel<V, S, LPR, VEC, REP, EPI, FORM, true>;
+        return &spmm_kernel<V, S, LPR, VEC, REP, EPI, FORM, false>;
+    }
 }
-template <int V, bool S, int LPR, int VEC, bool EPI, int FORM> KernelFn pick_rep(int rep)
+template <int V, bool S, int LPR, int VEC, bool EPI, int FORM> KernelFn pick_rep(int rep, bool near)
 {
     if constexpr (!EPI) {
         switch (rep) {
-        case 1: return instance<V, S, LPR, VEC, 1, EPI, FORM>();
-        case 2: return instance<V, S, LPR, VEC, 2, EPI, FORM>();
-        case 4: return instance<V, S, LPR, VEC, 4, EPI, FORM>();
+        case 1: return instance<V, S, LPR, VEC, 1, EPI, FORM>(near);
+        case 2: return instance<V, S, LPR, VEC, 2, EPI, FORM>(near);
+        case 4: return instance<V, S, LPR, VEC, 4, EPI, FORM>(near);
         }
     } else { // the shapes resolve_launch arrives at when everything is left to it
-        if (rep == 1) return instance<V, S, LPR, VEC, 1, EPI, FORM>();
+        if (rep == 1) return instance<V, S, LPR, VEC, 1, EPI, FORM>(near);
         if constexpr (LPR == 64) {
-            if (rep == 2) return instance<V, S, LPR, VEC, 2, EPI, FORM>();
+            if (rep == 2) return instance<V, S, LPR, VEC, 2, EPI, FORM>(near);
             if constexpr (!S)
-                if (rep == 4) return instance<V, S, LPR, VEC, 4, EPI, FORM>();
+                if (rep == 4) return instance<V, S, LPR, VEC, 4, EPI, FORM>(near);
         }
     }
     return nullptr;
 }
-template <int V, bool S, int LPR, bool EPI, int FORM> KernelFn pick_vec(int vec, int rep)
+template <int V, bool S, int LPR, bool EPI, int FORM> KernelFn pick_vec(int vec, int rep, bool near)
 {
     switch (vec) {
-    case 1: return pick_rep<V, S, LPR, 1, EPI, FORM>(rep);
-    case 2: return pick_rep<V, S, LPR, 2, EPI, FORM>(rep);
-    case 4: return pick_rep<V, S, LPR, 4, EPI, FORM>(rep);
+    case 1: return pick_rep<V, S, LPR, 1, EPI, FORM>(rep, near);
+    case 2: return pick_rep<V, S, LPR, 2, EPI, FORM>(rep, near);
+    case 4: return pick_rep<V, S, LPR, 4, EPI, FORM>(rep, near);
     }
     return nullptr;
 }
-template <int V, bool S, bool EPI, int FORM> KernelFn pick_lpr(int lpr, int vec, int rep)
+template <int V, bool S, bool EPI, int FORM> KernelFn pick_lpr(int lpr, int vec, int rep, bool near)
 {
     switch (lpr) {
-    case 4: return pick_vec<V, S, 4, EPI, FORM>(vec, rep);
-    case 8: return pick_vec<V, S, 8, EPI, FORM>(vec, rep);
-    case 16: return pick_vec<V, S, 16, EPI, FORM>(vec, rep);
-    case 32: return pick_vec<V, S, 32, EPI, FORM>(vec, rep);
-    case 64: return pick_vec<V, S, 64, EPI, FORM>(vec, rep);
+    case 4: return pick_vec<V, S, 4, EPI, FORM>(vec, rep, near);
+    case 8: return pick_vec<V, S, 8, EPI, FORM>(vec, rep, near);
+    case 16: return pick_vec<V, S, 16, EPI, FORM>(vec, rep, near);
+    case 32: return pick_vec<V, S, 32, EPI, FORM>(vec, rep, near);
+    case 64: return pick_vec<V, S, 64, EPI, FORM>(vec, rep, near);
     }
     return nullptr;
 }
-template <bool EPI, int FORM = kAsIs> KernelFn pick(int V, int S, int lpr, int vec, int rep)
+template <bool EPI, int FORM = kAsIs> KernelFn pick(int V, int S, int lpr, int vec, int rep, bool near = false)
 {
-    if (V == 1) return S ? pick_lpr<1, true, EPI, FORM>(lpr, vec, rep) : pick_lpr<1, false, EPI, FORM>(lpr, vec, rep);
-    if (V == 2) return S ? pick_lpr<2, true, EPI, FORM>(lpr, vec, rep) : pick_lpr<2, false, EPI, FORM>(lpr, vec, rep);
+    if (V == 1) return S ? pick_lpr<1, true, EPI, FORM>(lpr, vec, rep, near) : pick_lpr<1, false, EPI, FORM>(lpr, vec, rep, near);
+    if (V == 2) return S ? pick_lpr<2, true, EPI, FORM>(lpr, vec, rep, near) : pick_lpr<2, false, EPI, FORM>(lpr, vec, rep, near);
     return nullptr;
 }
 
@@ -1335,9 +1388,9 @@ template <int V> KernelFn pickb_lpr(int lpr, int vec, int rep, int ipg)
     }
     return nullptr;
 }
-KernelFn pick_any(int V, int S, int lpr, int vec, int rep, int ipg)
+KernelFn pick_any(int V, int S, int lpr, int vec, int rep, int ipg, bool near = false)
 {
-    if (ipg <= 1) return pick<false>(V, S, lpr, vec, rep);
+    if (ipg <= 1) return pick<false>(V, S, lpr, vec, rep, near);
     if (S) return nullptr;
     if (V == 1) return pickb_lpr<1>(lpr, vec, rep, ipg);
     if (V == 2) return pickb_lpr<2>(lpr, vec, rep, ipg);
@@ -1434,6 +1487,11 @@ bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep)
     return pick<true>(V, S, lpr, vec, rep) != nullptr;
 }
 
+static bool near_enough(const SpmmArgs &a)
+{
+    return (uint64_t)a.n_cols * (uint64_t)a.K * 4u <= kNearBytes && a.K < (1 << 20);
+}
+
 hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args, hipStream_t stream)
 {
     if (ls.grid_x <= 0 || ls.grid_y <= 0) return hipSuccess; // nothing to do
@@ -1450,15 +1508,16 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
         return hipGetLastError();
     }
     const bool epi = args.epi.on && ls.ipg <= 1;
+    const bool near = near_enough(args);
     KernelFn fn;
     size_t lds = 0;
     if (args.outer) {
-        fn = epi ? pick<true, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep)
-                 : pick<false, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep);
+        fn = epi ? pick<true, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near)
+                 : pick<false, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near);
         lds = sizeof(float) * 64 * ls.waves * V * ls.k_rep * ls.k_vec; // 64 KB at most
     } else {
-        fn = epi && (args.epi.self || args.epi.mask) ? pick<true, kEarlyTail>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep) : nullptr;
-        if (!fn) fn = epi ? pick<true>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep) : pick_any(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, ls.ipg);
+        fn = epi && (args.epi.self || args.epi.mask) ? pick<true, kEarlyTail>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near) : nullptr;
+        if (!fn) fn = epi ? pick<true>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near) : pick_any(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, ls.ipg, near);
     }
     if (!fn) return hipErrorInvalidValue;
     hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), lds, stream, args);
