@@ -16,6 +16,7 @@
 // logarithmic-ish on rows with 1e5 nonzeros.
 #include "pcsr_kernels.h"
 
+#include <array>
 #include <mutex>
 #include <type_traits>
 #include <set>
@@ -285,6 +286,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t near_operand(const SpmmArgs &a
 __device__ __forceinline__ float load_near(__amdgpu_buffer_rsrc_t b, unsigned at)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)at, 0, 0));
+}
+template <int VEC> __device__ __forceinline__ void load_near4(__amdgpu_buffer_rsrc_t b, unsigned at, float (&d)[VEC])
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4 t = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)at, 0, 0));
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) d[e] = t[e & 3];
 }
 
 // What an instance of spmm_kernel is for beside the plain product.  Instances of their own: products with short items lost
@@ -819,7 +827,8 @@ __global__ void __launch_bounds__(512) spmm_batched_kernel(SpmmArgs a)
 // ROWS: windows of communities (SpmmArgs::rows): the window of a block is the rows of B with the numbers of its own
 // items, found through a list, and the vectors inside come first in each item.
 // LONG: for long items (SpmmArgs::outer), see the sums below.
-template <int V, int LPR, int VEC, int REP, bool ROWS, bool LONG>
+// NEAR: gathers read B as a buffer (near_operand), with slots past the end of a run past its end.
+template <int V, int LPR, int VEC, int REP, bool ROWS, bool LONG, bool NEAR>
 __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
 {
     extern __shared__ __align__(16) float lds[];
@@ -928,6 +937,14 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
         kl[r] = (r * LPR + lg) * VEC;
         kv[r] = kbase + kl[r] < a.K;
     }
+    [[maybe_unused]] __amdgpu_buffer_rsrc_t Bn;
+    unsigned near_col = 0; // bytes
+    if constexpr (NEAR) {
+        static_assert(VEC == 4 && REP == 1);
+        Bn = near_operand(a);
+        near_col = (unsigned)min(kbase + kl[0], a.K - VEC) * 4u;
+    }
+    const unsigned row_bytes = (unsigned)K * 4u;
 
     // This lane's entry of the chunk that starts at member i0 of a walk: the walk's i-th
     // member is vector first + i (i < n1) or second + (i - n1); zeros past its n members.
@@ -1021,9 +1038,10 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                 for (int v = 0; v < V; ++v) av[v] = av_next[v];
                 load_entry(first, n1, second, n, base + LPR, c_next, av_next);
                 const int cnt = min(LPR, n - base);
-                // where this lane's entry sits in the staged window (floats from lds); a slot
-                // past the end of the run reads the row of zeros staged after the window
-                const int loff = LDS ? (base + lg < n ? c - c0 : a.win_cols) * LW : 0;
+                // where this lane's entry sits in the staged window (bytes from lds); a slot
+                // past the end of the run reads the row of zeros staged after the window.  NEAR: in B
+                const int loff = LDS ? (base + lg < n ? c - c0 : a.win_cols) * (LW * 4)
+                                     : (NEAR && base + lg < n ? (int)((unsigned)c * row_bytes) : (int)kPast);
                 float part[V][REP][VEC];
 #pragma unroll
                 for (int v = 0; v < V; ++v)
@@ -1041,7 +1059,7 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                     float aj[U][V];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        cj[u] = bcast_any<LPR, CL>(LDS ? loff : c, j + u);
+                        cj[u] = bcast_any<LPR, CL>(LDS || NEAR ? loff : c, j + u);
                         if constexpr (!FUSED) {
 #pragma unroll
                             for (int v = 0; v < V; ++v) aj[u][v] = bcast_any<LPR, CL>(av[v], j + u);
@@ -1055,7 +1073,11 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                             if constexpr (LDS) {
                                 // one ds_read of VEC floats, never predicated: slots past the
                                 // end point at the zero row, columns past K were staged as zeros
-                                load_lds<VEC>(lds + cj[u] + kl[r], b[u][r]);
+                                load_lds<VEC>(reinterpret_cast<const float *>(reinterpret_cast<const char *>(lds) +
+                                                                              (unsigned)(cj[u] + kl[r] * 4)),
+                                              b[u][r]);
+                            } else if constexpr (NEAR) {
+                                load_near4(Bn, (unsigned)cj[u] + near_col, b[u][r]);
                             } else {
                                 const bool ok = j + u < cnt;
                                 const float *src = (ok && kv[r]) ? B + (long)cj[u] * K + kbase + kl[r]
@@ -1095,8 +1117,13 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
         // issued here; the LDS walk below runs while they are in flight, then they are added.
         const int n_out = (lo - head) + (tail - hi);
         float gb[UP][REP][VEC];
+        [[maybe_unused]] const int goff = NEAR && lg < n_out ? (int)((unsigned)cg0 * row_bytes) : (int)kPast;
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
+            if constexpr (NEAR) {
+                load_near4(Bn, (unsigned)bcast_any<LPR, true>(goff, u) + near_col, gb[u][0]);
+                continue;
+            }
             const int cu = bcast_any<LPR, true>(cg0, u);
 #pragma unroll
             for (int r = 0; r < REP; ++r) {
@@ -1397,47 +1424,54 @@ KernelFn pick_any(int V, int S, int lpr, int vec, int rep, int ipg, bool near = 
     return nullptr;
 }
 
-template <int V, int LPR, int VEC> KernelFn pickw_rep(int rep, bool long_items)
+template <int V, int LPR, int VEC> KernelFn pickw_rep(int rep, bool long_items, bool near)
 {
+    if constexpr (LPR == 16 && VEC == 4) // the shape that is taken unasked
+        if (rep == 1 && near)
+            return long_items ? &spmm_window_kernel<V, LPR, VEC, 1, false, true, true>
+                              : &spmm_window_kernel<V, LPR, VEC, 1, false, false, true>;
     if constexpr (LPR >= 16 && VEC == 4) // steps of 8 in chunks of more, of the shapes that are taken unasked
-        if (rep == 1 && long_items) return &spmm_window_kernel<V, LPR, VEC, 1, false, true>;
+        if (rep == 1 && long_items) return &spmm_window_kernel<V, LPR, VEC, 1, false, true, false>;
     switch (rep) {
-    case 1: return &spmm_window_kernel<V, LPR, VEC, 1, false, false>;
-    case 2: return &spmm_window_kernel<V, LPR, VEC, 2, false, false>;
-    case 4: return &spmm_window_kernel<V, LPR, VEC, 4, false, false>;
+    case 1: return &spmm_window_kernel<V, LPR, VEC, 1, false, false, false>;
+    case 2: return &spmm_window_kernel<V, LPR, VEC, 2, false, false, false>;
+    case 4: return &spmm_window_kernel<V, LPR, VEC, 4, false, false, false>;
     }
     return nullptr;
 }
-template <int V, int LPR> KernelFn pickw_vec(int vec, int rep, bool long_items)
+template <int V, int LPR> KernelFn pickw_vec(int vec, int rep, bool long_items, bool near)
 {
     switch (vec) {
-    case 1: return pickw_rep<V, LPR, 1>(rep, long_items);
-    case 2: return pickw_rep<V, LPR, 2>(rep, long_items);
-    case 4: return pickw_rep<V, LPR, 4>(rep, long_items);
+    case 1: return pickw_rep<V, LPR, 1>(rep, long_items, near);
+    case 2: return pickw_rep<V, LPR, 2>(rep, long_items, near);
+    case 4: return pickw_rep<V, LPR, 4>(rep, long_items, near);
     }
     return nullptr;
 }
-template <int V> KernelFn pickw_lpr(int lpr, int vec, int rep, bool long_items)
+template <int V> KernelFn pickw_lpr(int lpr, int vec, int rep, bool long_items, bool near)
 {
     switch (lpr) {
-    case 4: return pickw_vec<V, 4>(vec, rep, long_items);
-    case 8: return pickw_vec<V, 8>(vec, rep, long_items);
-    case 16: return pickw_vec<V, 16>(vec, rep, long_items);
-    case 32: return pickw_vec<V, 32>(vec, rep, long_items);
-    case 64: return pickw_vec<V, 64>(vec, rep, long_items);
+    case 4: return pickw_vec<V, 4>(vec, rep, long_items, near);
+    case 8: return pickw_vec<V, 8>(vec, rep, long_items, near);
+    case 16: return pickw_vec<V, 16>(vec, rep, long_items, near);
+    case 32: return pickw_vec<V, 32>(vec, rep, long_items, near);
+    case 64: return pickw_vec<V, 64>(vec, rep, long_items, near);
     }
     return nullptr;
 }
-KernelFn pick_window(int V, int lpr, int vec, int rep, bool long_items)
+KernelFn pick_window(int V, int lpr, int vec, int rep, bool long_items, bool near)
 {
-    if (V == 1) return pickw_lpr<1>(lpr, vec, rep, long_items);
-    if (V == 2) return pickw_lpr<2>(lpr, vec, rep, long_items);
+    if (V == 1) return pickw_lpr<1>(lpr, vec, rep, long_items, near);
+    if (V == 2) return pickw_lpr<2>(lpr, vec, rep, long_items, near);
     return nullptr;
 }
-KernelFn pick_row_window(bool long_items)
+KernelFn pick_row_window(bool long_items, bool near)
 {
-    return long_items ? &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true, true>
-                      : &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true, false>;
+    if (near)
+        return long_items ? &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true, true, true>
+                          : &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true, false, true>;
+    return long_items ? &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true, true, false>
+                      : &spmm_window_kernel<1, kRowsLanes, kRowsVec, 1, true, false, false>;
 }
 
 } // namespace
@@ -1445,8 +1479,9 @@ KernelFn pick_row_window(bool long_items)
 // More than 64 KiB of dynamic LDS has to be allowed per kernel function: raised to
 // the 160 KiB of the CU once per function and device, not on every launch (the
 // call is host work and is not capturable in a HIP graph).
-// also: another function to be raised with it, so that a handle whose products run that one finds it done.
-static hipError_t allow_window_lds(KernelFn fn, KernelFn also)
+// all: the forms of an instance, raised together, so that a handle whose products run another one finds it done.
+using WindowForms = std::array<KernelFn, 4>;
+static hipError_t allow_window_lds(const WindowForms &all)
 {
     static std::mutex mu;
     static std::set<std::pair<int, const void *>> raised;
@@ -1454,27 +1489,31 @@ static hipError_t allow_window_lds(KernelFn fn, KernelFn also)
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     std::lock_guard<std::mutex> lock(mu);
-    const auto key = std::make_pair(dev, reinterpret_cast<const void *>(fn));
-    if (!raised.count(key)) {
-        for (KernelFn f : {fn, also}) {
+    if (!raised.count(std::make_pair(dev, reinterpret_cast<const void *>(all[0])))) {
+        for (KernelFn f : all) {
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(f),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return e;
         }
         try {
-            raised.insert(key);
-            raised.insert(std::make_pair(dev, reinterpret_cast<const void *>(also)));
+            raised.insert(std::make_pair(dev, reinterpret_cast<const void *>(all[0])));
         } catch (...) { // no memory to note it: raised again next time
         }
     }
     return hipSuccess;
 }
 
-hipError_t prepare_row_windows() { return allow_window_lds(pick_row_window(false), pick_row_window(true)); }
+// form 2 * near + long_items
+template <class Pick> static WindowForms window_forms(Pick pick)
+{
+    return {pick(false, false), pick(true, false), pick(false, true), pick(true, true)};
+}
+
+hipError_t prepare_row_windows() { return allow_window_lds(window_forms(pick_row_window)); }
 
 bool window_kernel_exists(int V, int lpr, int vec, int rep)
 {
-    return pick_window(V, lpr, vec, rep, false) != nullptr;
+    return pick_window(V, lpr, vec, rep, false, false) != nullptr;
 }
 
 bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg)
@@ -1496,13 +1535,13 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
 {
     if (ls.grid_x <= 0 || ls.grid_y <= 0) return hipSuccess; // nothing to do
     if (ls.window) {
-        auto pick_for = [&](bool long_items) -> KernelFn {
-            if (args.rows) return pick_row_window(long_items);
-            return S ? nullptr : pick_window(V, ls.lpr, ls.vec, ls.rep, long_items);
-        };
-        KernelFn fn = pick_for(args.outer != 0);
+        const WindowForms all = window_forms([&](bool long_items, bool near) -> KernelFn {
+            if (args.rows) return pick_row_window(long_items, near);
+            return S ? nullptr : pick_window(V, ls.lpr, ls.vec, ls.rep, long_items, near);
+        });
+        KernelFn fn = all[2 * near_enough(args) + (args.outer != 0)];
         if (!fn) return hipErrorInvalidValue;
-        const hipError_t e = allow_window_lds(fn, pick_for(args.outer == 0));
+        const hipError_t e = allow_window_lds(all);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(fn, dim3(ls.k_grid_x, ls.k_grid_y), dim3(64 * ls.waves), ls.lds_bytes, stream, args);
         return hipGetLastError();
