@@ -75,6 +75,22 @@ template <int VEC> __device__ __forceinline__ void load_lds(const float *p, floa
         for (int e = 0; e < VEC; ++e) d[e] = t[e];
     }
 }
+// The same by LDS address: an address that is made of a broadcast and a sum takes both in one instruction then.
+__device__ __forceinline__ unsigned lds_address(const float *p)
+{
+    return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) float *)p;
+}
+template <int VEC> __device__ __forceinline__ void load_lds_at(unsigned at, float (&d)[VEC])
+{
+    using T = typename std::conditional<VEC == 1, float, typename LdsVec<VEC>::type>::type;
+    const T t = *(const __attribute__((address_space(3))) T *)(uintptr_t)at;
+    if constexpr (VEC == 1) {
+        d[0] = t;
+    } else {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) d[e] = t[e];
+    }
+}
 template <int VEC> __device__ __forceinline__ void store_lds(float *p, const float (&s)[VEC])
 {
     if constexpr (VEC == 1) {
@@ -931,10 +947,12 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
     }
 
     int kl[REP]; // column offset inside the slice
+    unsigned lds_col[REP]; // its LDS address in a row at 0
     bool kv[REP];
 #pragma unroll
     for (int r = 0; r < REP; ++r) {
         kl[r] = (r * LPR + lg) * VEC;
+        lds_col[r] = lds_address(lds) + (unsigned)kl[r] * 4u;
         kv[r] = kbase + kl[r] < a.K;
     }
     [[maybe_unused]] __amdgpu_buffer_rsrc_t Bn;
@@ -1059,7 +1077,10 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                     float aj[U][V];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        cj[u] = bcast_any<LPR, CL>(LDS || NEAR ? loff : c, j + u);
+                        if constexpr (LDS && REP == 1)
+                            cj[u] = (int)((unsigned)bcast_any<LPR, CL>(loff, j + u) + lds_col[0]);
+                        else
+                            cj[u] = bcast_any<LPR, CL>(LDS || NEAR ? loff : c, j + u);
                         if constexpr (!FUSED) {
 #pragma unroll
                             for (int v = 0; v < V; ++v) aj[u][v] = bcast_any<LPR, CL>(av[v], j + u);
@@ -1073,9 +1094,7 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                             if constexpr (LDS) {
                                 // one ds_read of VEC floats, never predicated: slots past the
                                 // end point at the zero row, columns past K were staged as zeros
-                                load_lds<VEC>(reinterpret_cast<const float *>(reinterpret_cast<const char *>(lds) +
-                                                                              (unsigned)(cj[u] + kl[r] * 4)),
-                                              b[u][r]);
+                                load_lds_at<VEC>((unsigned)cj[u] + (REP == 1 ? 0u : lds_col[r]), b[u][r]);
                             } else if constexpr (NEAR) {
                                 load_near4(Bn, (unsigned)cj[u] + near_col, b[u][r]);
                             } else {
@@ -1086,6 +1105,7 @@ __global__ void __launch_bounds__(1024) spmm_window_kernel(SpmmArgs a)
                             }
                         }
                     }
+                    if constexpr (FUSED && V == 1) __builtin_amdgcn_sched_barrier(0); // a step's reads in flight together
 #pragma unroll
                     for (int u = 0; u < U; ++u)
 #pragma unroll
