@@ -6,6 +6,7 @@
 #include "pcsr_gnn.h"
 
 #include <hip/hip_runtime.h>
+#include <type_traits>
 
 namespace {
 
@@ -94,6 +95,10 @@ template <int NT> __device__ __forceinline__ void start_from(const f4 *bias, int
 // to and from the fragments through an LDS patch of the wavefront's own.  Straight from the fragments
 // every access would touch 16 rows, 64 bytes of each: 16 -> 64 columns ran at 3.7 TB/s so, and run at
 // 5.3 through the patch (2,000,000 rows, 121 us).
+//
+// Groups of 16 rows that are whole have a loop of their own: with no load or store in it that may be left out, the compiler
+// counts what is in flight, and a wait for the next rows is not one for the stores before it.
+constexpr std::integral_constant<long, 16> kWhole{};
 constexpr int patch_ld(int t) { return 16 * t + 4; } // floats per row
 constexpr int patch_floats(int t) { return 16 * patch_ld(t); }
 
@@ -103,11 +108,20 @@ __device__ __forceinline__ void patch_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
+// a scalar base and 32 bits of offset
+__device__ __forceinline__ const f4 *at_byte(const float *base, unsigned off)
+{
+    return reinterpret_cast<const f4 *>(reinterpret_cast<const char *>(base) + off);
+}
+__device__ __forceinline__ f4 *at_byte(float *base, unsigned off)
+{
+    return reinterpret_cast<f4 *>(reinterpret_cast<char *>(base) + off);
+}
 template <int T> __device__ __forceinline__ void load_piece(const float *piece, int lane, long rows, f4 (&x)[T])
 {
     if (rows >= 16) {
 #pragma unroll
-        for (int u = 0; u < T; ++u) x[u] = reinterpret_cast<const f4 *>(piece)[u * 64 + lane];
+        for (int u = 0; u < T; ++u) x[u] = *at_byte(piece + u * 256, 16u * (unsigned)lane);
     } else { // zeros past the end
 #pragma unroll
         for (int u = 0; u < T; ++u) {
@@ -120,15 +134,15 @@ template <int T> __device__ __forceinline__ void store_piece(float *piece, int l
 {
 #pragma unroll
     for (int u = 0; u < T; ++u)
-        if ((u * 64 + lane) / (4 * T) < rows) reinterpret_cast<f4 *>(piece)[u * 64 + lane] = x[u];
+        if (rows >= 16 || (u * 64 + lane) / (4 * T) < rows) *at_byte(piece + u * 256, 16u * (unsigned)lane) = x[u];
 }
 // straight to the fragments
 template <int T> __device__ __forceinline__ void load_frags(const float *piece, int lane, long rows, f4 (&x)[T])
 {
-    const unsigned at = (lane & 15) * (16 * T) + 4 * (lane >> 4);
+    const unsigned at = 4u * ((lane & 15) * (16 * T) + 4 * (lane >> 4));
     if (rows >= 16 || (lane & 15) < rows) {
 #pragma unroll
-        for (int t = 0; t < T; ++t) x[t] = *reinterpret_cast<const f4 *>(piece + at + t * 16);
+        for (int t = 0; t < T; ++t) x[t] = *at_byte(piece + t * 16, at);
     } else {
 #pragma unroll
         for (int t = 0; t < T; ++t) x[t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -136,10 +150,10 @@ template <int T> __device__ __forceinline__ void load_frags(const float *piece, 
 }
 template <int T> __device__ __forceinline__ void store_frags(float *piece, int lane, long rows, const f4 (&x)[T])
 {
-    const unsigned at = (lane & 15) * (16 * T) + 4 * (lane >> 4);
+    const unsigned at = 4u * ((lane & 15) * (16 * T) + 4 * (lane >> 4));
     if (rows >= 16 || (lane & 15) < rows) {
 #pragma unroll
-        for (int t = 0; t < T; ++t) *reinterpret_cast<f4 *>(piece + at + t * 16) = x[t];
+        for (int t = 0; t < T; ++t) *at_byte(piece + t * 16, at) = x[t];
     }
 }
 template <int T, int LD> __device__ __forceinline__ void piece_to_patch(float *patch, int lane, const f4 (&x)[T])
@@ -361,17 +375,16 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), piece_waves(KT, NT) 
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) csum[nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    const long groups = (p.n + 15) >> 4, stride = (long)gridDim.x * kW;
+    const long full = p.n >> 4, stride = (long)gridDim.x * kW;
     long g = (long)blockIdx.x * kW + wave;
     f4 xn[KT]; // the next rows are requested before this step's products
-    if (g < groups) load_frags<KT>(p.X + g * (256 * KT), lane, p.n - g * 16, xn);
-    for (; g < groups; g += stride) {
+    auto load = [&](long g, auto rows) { load_frags<KT>(p.X + g * (256 * KT), lane, rows, xn); };
+    auto step = [&](long g, auto rows, auto next) {
         asm volatile("" ::: "memory"); // as in linear_kernel
-        const long rows = p.n - g * 16;
         f4 x[KT], y[NT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) x[kt] = xn[kt];
-        if (g + stride < groups) load_frags<KT>(p.X + (g + stride) * (256 * KT), lane, rows - stride * 16, xn);
+        next();
         f4 m[NT]; // aux, or the mask; callers have one of them
         const float *first = RED && p.aux ? p.aux : p.mask;
         if (first) load_piece<NT>(first + g * (256 * NT), lane, rows, m);
@@ -394,6 +407,14 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), piece_waves(KT, NT) 
             for (int t = 0; t < NT; ++t) csum[t] += y[t];
         }
         if (p.Y) store_piece<NT>(p.Y + g * (256 * NT), lane, rows, y);
+    };
+    if (g < full) load(g, kWhole);
+    for (; g < full; g += stride) step(g, kWhole, [&] {
+            if (g + stride < full) load(g + stride, kWhole);
+        });
+    if (const long rows = p.n - g * 16; rows > 0) { // the rows that are left over
+        load(g, rows);
+        step(g, rows, [] {});
     }
     if constexpr (RED) {
         if (p.ws_colsum) collect_colsum<NT, false>(patches, csum, p.ws_colsum + (long)blockIdx.x * (16 * NT));
@@ -422,17 +443,16 @@ template <int KT, int MT> __global__ void __launch_bounds__(64 * kWaves, 3) mlp_
     stage_bias<MT>(bias1, p.b1, 16 * MT);
     stage_bias<MT>(bias2, p.b2, 16 * MT);
     __syncthreads();
-    const long groups = (p.n + 15) >> 4, stride = (long)gridDim.x * kWaves;
+    const long full = p.n >> 4, stride = (long)gridDim.x * kWaves;
     long g = (long)blockIdx.x * kWaves + wave;
     f4 xn[KT];
-    if (g < groups) load_frags<KT>(p.X + g * (256 * KT), lane, p.n - g * 16, xn);
-    for (; g < groups; g += stride) {
+    auto load = [&](long g, auto rows) { load_frags<KT>(p.X + g * (256 * KT), lane, rows, xn); };
+    auto step = [&](long g, auto rows, auto next) {
         asm volatile("" ::: "memory"); // as in linear_kernel
-        const long rows = p.n - g * 16;
         f4 x[KT], z[MT], y[MT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) x[kt] = xn[kt];
-        if (g + stride < groups) load_frags<KT>(p.X + (g + stride) * (256 * KT), lane, rows - stride * 16, xn);
+        next();
         start_from<MT>(bias1, lane, z);
         multiply<KT, MT>(w1, lane, x, z);
         relu_rows<MT>(z);
@@ -443,6 +463,15 @@ template <int KT, int MT> __global__ void __launch_bounds__(64 * kWaves, 3) mlp_
         store_piece<MT>(p.Z + g * (256 * MT), lane, rows, z);
         frags_to_piece<MT>(patch, lane, y);
         store_piece<MT>(p.Y + g * (256 * MT), lane, rows, y);
+    };
+    if (g < full) load(g, kWhole);
+    for (; g < full; g += stride)
+        step(g, kWhole, [&] {
+            if (g + stride < full) load(g + stride, kWhole);
+        });
+    if (const long rows = p.n - g * 16; rows > 0) { // the rows that are left over
+        load(g, rows);
+        step(g, rows, [] {});
     }
 }
 
@@ -569,22 +598,19 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
     }
 
     constexpr int LG = back_ld(BT), LZ = back_ld(MT), LA = back_ld(AT);
-    const long groups = (p.n + 15) >> 4, stride = (long)gridDim.x * kWaves;
+    const long full = p.n >> 4, stride = (long)gridDim.x * kWaves;
     long g = (long)blockIdx.x * kWaves + wave;
-    f4 gg[BT], zz[MT];
-    // the next rows of G and Z go into the same registers once these are in the patch and used;
-    // the product that follows covers the wait
-    auto next = [&](long g) {
-        if (g < groups) {
-            load_frags<BT>(p.G + g * (256 * BT), lane, p.n - g * 16, gg);
-            load_frags<MT>(p.Z + g * (256 * MT), lane, p.n - g * 16, zz);
-        }
-    };
-    next(g);
-    for (; g < groups; g += stride) {
-        const long rows = p.n - g * 16;
-        f4 g1[MT], aa[TWO ? AT : 1];
+    f4 gg[BT], zz[MT], aa[TWO ? AT : 1];
+    constexpr bool kLateZ = TWO && MT + AT > 7; // no registers to hold the next rows of Z as well from early on
+    auto load_g = [&](long g, auto rows) { load_frags<BT>(p.G + g * (256 * BT), lane, rows, gg); };
+    auto load_z = [&](long g, auto rows) { load_frags<MT>(p.Z + g * (256 * MT), lane, rows, zz); };
+    auto load_a = [&](long g, auto rows) {
         if constexpr (TWO) load_piece<AT>(p.A + g * (256 * AT), lane, rows, aa);
+    };
+    // the next rows of G, Z and A go into the same registers once these are in the patch and used;
+    // the products that follow cover the wait
+    auto step = [&](long g, auto rows, auto next_g, auto next_z, auto next_a) {
+        f4 g1[MT];
         patch_fence();
         frags_to_patch<BT, LG>(patch, lane, gg);
         frags_to_patch<MT, LZ>(patch + 16 * LG, lane, zz);
@@ -594,13 +620,16 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
         if (TWO || p.masked) mask_rows<MT>(g1, zz);
         patch_fence(); // keeps weight fragments and patches in LDS, and what follows below
         if constexpr (!TWO) {
-            next(g + stride);
+            next_g();
+            next_z();
             if (p.out) store_frags<MT>(p.out + g * (256 * MT), lane, rows, g1);
             clear_past_end<MT>(lane, rows, g1); // zeros times an infinite weight are no zeros
 #pragma unroll
             for (int t = 0; t < MT; ++t) csum[t] += g1[t];
             turned_product<BT, MT>(patch, lane, acc2, sum2);
         } else {
+            next_g();
+            if constexpr (!kLateZ) next_z();
             turned_product<BT, MT>(patch, lane, acc2, sum2);
             patch_fence();
             frags_to_patch<MT, LZ>(patch, lane, g1);
@@ -611,16 +640,32 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
 #pragma unroll
             for (int t = 0; t < AT; ++t) da[t] = zero;
             multiply<MT, AT>(w1, lane, g1, da);
-            if (p.H && (lane & 15) < rows) {
+            if (p.H && (rows >= 16 || (lane & 15) < rows)) {
 #pragma unroll
                 for (int t = 0; t < AT; ++t)
                     dot += (da[t][0] * aa[t][0] + da[t][1] * aa[t][1]) + (da[t][2] * aa[t][2] + da[t][3] * aa[t][3]);
             }
+            if constexpr (kLateZ) next_z();
+            next_a();
             if (p.out) store_frags<AT>(p.out + g * (256 * AT), lane, rows, da);
             patch_fence();
-            next(g + stride);
             turned_product<MT, AT>(patch, lane, acc1, sum1);
         }
+    };
+    if (g < full) {
+        load_g(g, kWhole);
+        load_z(g, kWhole);
+        load_a(g, kWhole);
+    }
+    for (; g < full; g += stride) {
+        const long after = g + stride < full ? g + stride : g;
+        step(g, kWhole, [&] { load_g(after, kWhole); }, [&] { load_z(after, kWhole); }, [&] { load_a(after, kWhole); });
+    }
+    if (const long rows = p.n - g * 16; rows > 0) { // the rows that are left over
+        load_g(g, rows);
+        load_z(g, rows);
+        load_a(g, rows);
+        step(g, rows, [] {}, [] {}, [] {});
     }
 
     float *ws = p.ws + (long)blockIdx.x * p.ws_stride;
