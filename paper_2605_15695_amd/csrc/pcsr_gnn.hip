@@ -17,7 +17,8 @@ __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_a
 constexpr int kWaves = 4;
 constexpr int kLinearBlocks = 768; // three per compute unit
 constexpr int kBackBlocks = 512;
-constexpr int kWgradBlocks = 512;
+constexpr int kWgradBlocks = 512; // 768 and 1024: 0.5 to 5 % slower at 2,000,000 rows, more below
+constexpr int kWgradAhead = 2;
 constexpr int kColsumBlocks = 512;
 
 struct LinearArgs {
@@ -683,24 +684,32 @@ struct WgradArgs {
     long n;
     int a, b;
     const float *G, *X;
-    float *ws; // per workgroup of grid.x: b*a of dW, then b column sums
+    float *ws; // per workgroup: b*a of dW, then b column sums
     int sums;
+    int squares_g, squares_x; // of dW, 1 or 2 each way
+    long unchecked;           // rows before which a lane may read past the end of its row
 };
 
-// dW = G^T X: the rows are the k of the matrix instruction, four per instruction.  With VG / VX
-// a lane's 16-byte load of a row (columns T*(l%16) ...) feeds T tiles at once: tile t holds
-// the columns T*i + t.  A workgroup keeps up to 64 x 64 of dW in its accumulators and walks
-// 16 rows per wavefront and step, the next step's rows being loaded meanwhile; wider weights
-// are cut into such squares by grid.y / grid.z.  Rows are dealt to about 2000 wavefronts,
-// each leaves one partial dW, summed by sum_partials_kernel in a fixed order.
-// 2,000,000 rows, 64 x 64: 207 us with the sums (5.0 TB/s of G and X); torch's product of the
-// transposed G takes 2900.
-template <int TG, bool VG, int TX, bool VX>
-__global__ void __launch_bounds__(64 * kWaves) wgrad_kernel(WgradArgs p)
+// dW = G^T X: the rows are the k of the matrix instruction, four per instruction.  A lane reads T consecutive
+// columns of a row (T*(l%16) and on), which feed T tiles: tile t holds the columns T*i + t.  A wavefront
+// keeps up to 64 x 64 of dW in its accumulators and walks 16 rows a step; the rows of the next two steps are on their way
+// (requested right after the products that free their registers: no copies between two sets).
+// Weights wider than 64 are cut into two or four squares, taken by wavefronts of one workgroup over the same rows.
+// Rows are dealt to 512 to 2048 wavefronts; each workgroup leaves one partial dW, summed by sum_partials_kernel in a fixed order.
+// Whole steps read without conditions.  Where a width is rounded up, lanes past the end of a row read the next
+// one's columns, whose sums nobody stores; the last rows, where that would pass the end of the array, and
+// steps of fewer rows take loads that check both.  Four-byte addresses do for loads of any width.
+// 2,000,000 rows, with the sums (before: conditions on every load, squares of 64 as workgroups of their own): 128 x 128 750 -> 701 us
+// (matrix cores 78 % busy at 2.0 GHz), 96 x 96 717 -> 473, 64 x 64 220 -> 203, 48 x 48 219 -> 143, 24 x 24 99 -> 73,
+// 47 x 65 394 -> 240; 16 x 64 111 -> 116 (5.5 TB/s either way, nothing to gain there).  torch's product of the transposed G takes 2900 at 64 x 64.
+template <int TG, int TX>
+__global__ void __launch_bounds__(64 * kWaves, 2) wgrad_kernel(WgradArgs p)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, q = lane >> 4;
-    const int g0 = blockIdx.y * TG * 16, x0 = blockIdx.z * TX * 16;
+    const int squares = p.squares_g * p.squares_x, row_waves = kWaves / squares;
+    const int square = wave & (squares - 1), row_wave = wave / squares;
+    const int g0 = square / p.squares_x * TG * 16, x0 = square % p.squares_x * TX * 16;
 
     f4 acc[TG][TX];
     float gsum[TG];
@@ -711,101 +720,139 @@ __global__ void __launch_bounds__(64 * kWaves) wgrad_kernel(WgradArgs p)
         for (int j = 0; j < TX; ++j) acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     }
 
-    auto load = [&](const float *base, int width, int off, long row, auto t_const, auto vec_const, float *d) {
-        constexpr int T = decltype(t_const)::value;
-        constexpr bool V = decltype(vec_const)::value;
-        const bool ok = row < p.n;
-        const float *src = base + row * width;
-        if constexpr (V && T == 4) {
-            const int col = off + 4 * c;
-            f4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (ok && col < width) t = *reinterpret_cast<const f4 *>(src + col);
+    constexpr int U = 4; // 4 x 4 rows per step
+    const unsigned gat = 4u * (unsigned)(q * p.b + g0 + TG * c), xat = 4u * (unsigned)(q * p.a + x0 + TX * c);
+    struct Rows {
+        float g[U][TG], x[U][TX];
+    };
+    auto fetch = [&](long row0, Rows &r) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) d[s] = t[s];
-        } else if constexpr (V && T == 2) {
-            const int col = off + 2 * c;
-            float2 t = make_float2(0.0f, 0.0f);
-            if (ok && col < width) t = *reinterpret_cast<const float2 *>(src + col);
-            d[0] = t.x;
-            d[1] = t.y;
-        } else {
+        for (int u = 0; u < U; ++u) {
+            const float *g = reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.G + (row0 + 4 * u) * p.b) + gat);
+            const float *x = reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.X + (row0 + 4 * u) * p.a) + xat);
 #pragma unroll
-            for (int s = 0; s < T; ++s) {
-                const int col = off + 16 * s + c;
-                d[s] = (ok && col < width) ? src[col] : 0.0f;
+            for (int i = 0; i < TG; ++i) r.g[u][i] = g[i];
+#pragma unroll
+            for (int j = 0; j < TX; ++j) r.x[u][j] = x[j];
+        }
+    };
+    auto fetch_checked = [&](long row0, Rows &r) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const long row = row0 + 4 * u + q;
+#pragma unroll
+            for (int i = 0; i < TG; ++i) {
+                const int col = g0 + TG * c + i;
+                const bool in = row < p.n && col < p.b;
+                const float v = p.G[in ? row * p.b + col : 0];
+                r.g[u][i] = in ? v : 0.0f;
+            }
+#pragma unroll
+            for (int j = 0; j < TX; ++j) {
+                const int col = x0 + TX * c + j;
+                const bool in = row < p.n && col < p.a;
+                const float v = p.X[in ? row * p.a + col : 0];
+                r.x[u][j] = in ? v : 0.0f;
             }
         }
     };
-    constexpr int U = 4; // 4 x 4 rows per step
-    float gn[U][TG], xn[U][TX];
-    auto fetch = [&](long row0) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            load(p.G, p.b, g0, row0 + 4 * u + q, std::integral_constant<int, TG>{}, std::integral_constant<bool, VG>{},
-                 gn[u]);
-            load(p.X, p.a, x0, row0 + 4 * u + q, std::integral_constant<int, TX>{}, std::integral_constant<bool, VX>{},
-                 xn[u]);
-        }
-    };
-    const long step = (long)gridDim.x * kWaves * 4 * U;
-    long row0 = ((long)blockIdx.x * kWaves + wave) * 4 * U;
-    fetch(row0);
-    for (; row0 < p.n; row0 += step) {
-        float g[U][TG], x[U][TX];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int i = 0; i < TG; ++i) g[u][i] = gn[u][i];
-#pragma unroll
-            for (int j = 0; j < TX; ++j) x[u][j] = xn[u][j];
-        }
-        fetch(row0 + step);
+    auto products = [&](const Rows &r) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int i = 0; i < TG; ++i) {
-                gsum[i] += g[u][i];
+                gsum[i] += r.g[u][i];
 #pragma unroll
-                for (int j = 0; j < TX; ++j) acc[i][j] = mfma4(g[u][i], x[u][j], acc[i][j]);
+                for (int j = 0; j < TX; ++j) acc[i][j] = mfma4(r.g[u][i], r.x[u][j], acc[i][j]);
             }
         }
+    };
+    const long step = (long)gridDim.x * row_waves * 4 * U;
+    const long whole = p.unchecked - 4 * U; // the last row a step may begin at
+    long row0 = ((long)blockIdx.x * row_waves + row_wave) * 4 * U;
+    Rows r[kWgradAhead];
+#pragma unroll
+    for (int d = 0; d < kWgradAhead; ++d)
+        if (row0 + d * step <= whole) fetch(row0 + d * step, r[d]);
+    for (; row0 + (kWgradAhead - 1) * step <= whole; row0 += kWgradAhead * step) {
+#pragma unroll
+        for (int d = 0; d < kWgradAhead; ++d) {
+            products(r[d]);
+            const long next = row0 + (d + kWgradAhead) * step;
+            asm volatile("" ::: "memory"); // requested here, not where they are used
+            fetch(next <= whole ? next : row0, r[d]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < kWgradAhead; ++d)
+        if (row0 <= whole) {
+            products(r[d]);
+            row0 += step;
+        }
+    for (; row0 < p.n; row0 += step) {
+        fetch_checked(row0, r[0]);
+        products(r[0]);
     }
 
-    // the four wavefronts of the workgroup, in order
-    __shared__ float red[TG * 16][TX * 16 + 1];
-    __shared__ float gred[TG * 16];
-    auto gcol = [](int i, int t) { return VG ? i * TG + t : t * 16 + i; };
-    auto xcol = [](int j, int t) { return VX ? j * TX + t : t * 16 + j; };
 #pragma unroll
     for (int i = 0; i < TG; ++i) {
         gsum[i] += __shfl_xor(gsum[i], 16);
         gsum[i] += __shfl_xor(gsum[i], 32);
     }
-    for (int w = 0; w < kWaves; ++w) {
-        if (wave == w) {
+    float *out = p.ws + (long)blockIdx.x * ((long)p.b * p.a + p.b);
+    float *sums = p.sums && x0 == 0 ? out + (long)p.b * p.a : nullptr;
+    if (row_waves == 1) { // a square each: no sum over wavefronts
+#pragma unroll
+        for (int i = 0; i < TG; ++i) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int row = g0 + (4 * q + s) * TG + i, col = x0 + TX * c;
+                if (row < p.b) {
+#pragma unroll
+                    for (int j = 0; j < TX; ++j)
+                        if (col + j < p.a) out[(long)row * p.a + col + j] = acc[i][j][s];
+                }
+            }
+            const int row = g0 + TG * c + i;
+            if (sums && q == 0 && row < p.b) sums[row] = gsum[i];
+        }
+        return;
+    }
+    // the wavefronts of a square, in order
+    __shared__ float red[2][TG * 16][TX * 16 + 1];
+    for (int w = 0; w < row_waves; ++w) {
+        if (row_wave == w) {
 #pragma unroll
             for (int i = 0; i < TG; ++i) {
 #pragma unroll
                 for (int j = 0; j < TX; ++j)
 #pragma unroll
                     for (int s = 0; s < 4; ++s) {
-                        float &d = red[gcol(4 * q + s, i)][xcol(c, j)];
+                        float &d = red[square][TG * (4 * q + s) + i][TX * c + j];
                         d = w ? d + acc[i][j][s] : acc[i][j][s];
                     }
-                if (q == 0) {
-                    float &d = gred[gcol(c, i)];
-                    d = w ? d + gsum[i] : gsum[i];
-                }
             }
         }
         __syncthreads();
     }
-    float *out = p.ws + (long)blockIdx.x * ((long)p.b * p.a + p.b);
-    for (int e = tid; e < TG * TX * 256; e += 64 * kWaves) {
-        const int i = e / (TX * 16), j = e - i * (TX * 16);
-        if (g0 + i < p.b && x0 + j < p.a) out[(long)(g0 + i) * p.a + x0 + j] = red[i][j];
+    for (int e = tid; e < squares * (TG * TX * 256); e += 64 * kWaves) {
+        const int sq = e / (TG * TX * 256), f = e - sq * (TG * TX * 256), i = f / (TX * 16), j = f - i * (TX * 16);
+        const int row = sq / p.squares_x * TG * 16 + i, col = sq % p.squares_x * TX * 16 + j;
+        if (row < p.b && col < p.a) out[(long)row * p.a + col] = red[sq][i][j];
     }
-    if (p.sums && blockIdx.z == 0 && tid < TG * 16 && g0 + tid < p.b) out[(long)p.b * p.a + g0 + tid] = gred[tid];
+    __syncthreads();
+    float(*gred)[TG * 16] = reinterpret_cast<float(*)[TG * 16]>(&red[0][0][0]); // [kWaves]
+    if (q == 0) {
+#pragma unroll
+        for (int i = 0; i < TG; ++i) gred[wave][TG * c + i] = gsum[i];
+    }
+    __syncthreads();
+    if (sums && row_wave == 0 && lane < TG * 16 && g0 + lane < p.b) {
+        float t = gred[wave][lane];
+        for (int w = 1; w < row_waves; ++w) t += gred[wave + w * squares][lane];
+        sums[g0 + lane] = t;
+    }
 }
 
 // out[e] = sum over the parts of ws[part*len + e] for e < n0 (dst0), then dst1: 16 threads per
@@ -825,7 +872,8 @@ __global__ void __launch_bounds__(256) sum_partials_kernel(const float *ws, int 
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = ws[(s + k * 16) * stride + e];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) t += v[k];
+            for (int k = 0; k < 4; ++k) v[k] += v[k + 4];
+            t += (v[0] + v[2]) + (v[1] + v[3]);
         }
         for (; s < parts; s += 16) t += ws[s * stride + e];
     }
@@ -920,30 +968,31 @@ LinearFn pick_linear_kn(int kt, int nt, int mode, bool red)
 }
 
 using WgradFn = void (*)(WgradArgs);
-// how one operand of the weight gradient is read: tiles per workgroup and whether a lane's
-// columns are consecutive (the row then has to be a multiple of that many floats)
-struct Side {
-    int t;
-    bool v;
-};
-Side side(int w, const float *p)
+// Squares of one side of the weight gradient, and their tiles: as few columns of padding as two squares allow.
+// 2,000,000 rows, 96 x 96: 48 + 48 columns a side 473 us, 64 + 64 (the work of 128 x 128) 700.
+int wgrad_squares(int w) { return w > 64 ? 2 : 1; }
+int wgrad_tiles(int w)
 {
-    const uintptr_t at = reinterpret_cast<uintptr_t>(p);
-    if (w <= 16) return {1, false};
-    if (w <= 32) return {2, w % 2 == 0 && at % 8 == 0};
-    return {4, w % 4 == 0 && at % 16 == 0};
+    const int squares = wgrad_squares(w);
+    return (w + 16 * squares - 1) / (16 * squares);
 }
-template <int TG, bool VG> WgradFn pick_wgrad_x(Side x)
+template <int TG> WgradFn pick_wgrad_x(int tx)
 {
-    if (x.t == 1) return &wgrad_kernel<TG, VG, 1, false>;
-    if (x.t == 2) return x.v ? &wgrad_kernel<TG, VG, 2, true> : &wgrad_kernel<TG, VG, 2, false>;
-    return x.v ? &wgrad_kernel<TG, VG, 4, true> : &wgrad_kernel<TG, VG, 4, false>;
+    switch (tx) {
+    case 1: return &wgrad_kernel<TG, 1>;
+    case 2: return &wgrad_kernel<TG, 2>;
+    case 3: return &wgrad_kernel<TG, 3>;
+    }
+    return &wgrad_kernel<TG, 4>;
 }
-WgradFn pick_wgrad(Side g, Side x)
+WgradFn pick_wgrad(int tg, int tx)
 {
-    if (g.t == 1) return pick_wgrad_x<1, false>(x);
-    if (g.t == 2) return g.v ? pick_wgrad_x<2, true>(x) : pick_wgrad_x<2, false>(x);
-    return g.v ? pick_wgrad_x<4, true>(x) : pick_wgrad_x<4, false>(x);
+    switch (tg) {
+    case 1: return pick_wgrad_x<1>(tx);
+    case 2: return pick_wgrad_x<2>(tx);
+    case 3: return pick_wgrad_x<3>(tx);
+    }
+    return pick_wgrad_x<4>(tx);
 }
 
 // workgroups for groups of 16 rows, one wavefront each
@@ -1126,12 +1175,16 @@ int pcsr_gnn_wgrad(int64_t n, int32_t a, int32_t b, const float *G, const float 
     if (n < 0 || !G || !X || !dW || !ws) return PCSR_E_INVALID_ARG;
     if (!width_ok(a) || !width_ok(b)) return PCSR_E_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const Side sg = side(b, G), sx = side(a, X);
-    const unsigned gy = (unsigned)((b + sg.t * 16 - 1) / (sg.t * 16)), gz = (unsigned)((a + sx.t * 16 - 1) / (sx.t * 16));
-    long blocks = (n + 64 * kWaves - 1) / (64 * kWaves); // at least four steps of 16 rows per wavefront
-    const long most = kWgradBlocks / (gy * gz);
-    blocks = blocks < 1 ? 1 : (blocks > most ? most : blocks);
+    const int tg = wgrad_tiles(b), tx = wgrad_tiles(a);
     WgradArgs p;
+    p.squares_g = wgrad_squares(b);
+    p.squares_x = wgrad_squares(a);
+    const long rows = 64 * (kWaves / (p.squares_g * p.squares_x)); // at least four steps of 16 rows per wavefront
+    long blocks = (n + rows - 1) / rows;
+    blocks = blocks < 1 ? 1 : (blocks > kWgradBlocks ? kWgradBlocks : blocks);
+    // rows that the columns past a row's end reach into
+    const long past_g = (16 * tg * p.squares_g - 1) / b, past_x = (16 * tx * p.squares_x - 1) / a;
+    p.unchecked = n - (past_g > past_x ? past_g : past_x);
     p.n = n;
     p.a = a;
     p.b = b;
@@ -1139,7 +1192,7 @@ int pcsr_gnn_wgrad(int64_t n, int32_t a, int32_t b, const float *G, const float 
     p.X = X;
     p.ws = ws;
     p.sums = db != nullptr;
-    hipLaunchKernelGGL(pick_wgrad(sg, sx), dim3((unsigned)blocks, gy, gz), dim3(64 * kWaves), 0, s, p);
+    hipLaunchKernelGGL(pick_wgrad(tg, tx), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, p);
     int rc = to_code(hipGetLastError());
     const long len = (long)a * b;
     if (rc == PCSR_OK) rc = sum_partials(ws, (int)blocks, len + b, len, dW, db ? b : 0, db, s);

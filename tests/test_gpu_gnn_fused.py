@@ -52,6 +52,30 @@ def test_dense_kernels(a, b, n):
     assert bool(((d.colsum(G).double() - G.double().sum(0)).abs() <= 1e-6 * gb).all())
 
 
+# weight gradients: one, two and four squares, widths short of a tile, rows short of a step, rows at no multiple of 16 bytes.
+# Lanes past the end of a row read the next one: an infinite column there reaches no other column's sum.
+# A sum of n terms is off by at most n * 2^-24 of the sum of their magnitudes, 1e-6 up to n = 16; beyond that rounding errors
+# of the chains add up like sqrt(n), and a wavefront's chain is n / 512 terms at the least.
+@pytest.mark.parametrize("a,b", [(1, 128), (2, 40), (17, 33), (48, 48), (49, 96), (65, 64), (80, 97), (96, 96), (127, 5),
+                                 (128, 65)])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 64 * 16 + 3, 40009])
+@pytest.mark.parametrize("skew", [0, 1])
+def test_weight_gradient(a, b, n, skew):
+    g = torch.Generator(device="cuda").manual_seed(a * 1000 + b + n)
+    X, G = (torch.randn(n * w + skew, generator=g, device="cuda")[skew:].view(n, w) for w in (a, b))
+    d = _dense(a, b)
+    dW, db = d.wgrad(G, X, bias=True)
+    bound = G.double().abs().t() @ X.double().abs()
+    assert bool(((dW.double() - G.double().t() @ X.double()).abs() <= 1e-6 * bound).all())
+    assert bool(((db.double() - G.double().sum(0)).abs() <= 1e-6 * G.double().abs().sum(0)).all())
+    first, sums = dW.clone(), db.clone()
+    X[:, 0] = float("inf")
+    G[:, 0] = float("inf")
+    dW, db = d.wgrad(G, X, bias=True)
+    assert torch.equal(dW[1:, 1:], first[1:, 1:]) and torch.equal(db[1:], sums[1:])
+    assert bool(torch.isinf(db[0])) and not bool(torch.isfinite(dW[0]).any() or torch.isfinite(dW[:, 0]).any())
+
+
 # rows short of a piece: the bias of rows that are not there is in no sum
 @pytest.mark.parametrize("a,b", [(16, 16), (64, 64), (128, 128), (96, 32), (24, 48), (33, 7)])
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 1000 * 16 + 5])
