@@ -1180,7 +1180,11 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // that halving the number of work items leaves wavefront slots empty (30,000 rows of
     // 160, K = 32: V = 2 runs at 0.55 of V = 1).
     const bool pair_long = long_uniform && n * (double)(K < 32 ? 4 : 8) / 128.0 >= 3500.0;
-    p.V = (!p.S && (d_hat < 6.0 || (d_hat < 12.0 && pr2 < 0.45) || pr2 < 0.20 || pair_long)) ? 2 : 1;
+    // Rows of C of 48 or 64 bytes are written one by one by a pair's lanes, part lines each, where single rows' lane groups
+    // fill lines together: V = 1 takes 0.77-0.92 of V = 2 (with a self term 0.61-1.0, and a mask 0.59-0.98) on road-like and uniform
+    // graphs of 300,000 and 2,000,000 rows of 2 to 6.  Wider rows and K = 8 do better paired, products of under 10 us are on a par.
+    const bool part_lines = K > 8 && K <= 16 && K % 4 == 0 && d_hat < 8.0 && pr2 >= 0.20 && n * (double)K * 4.0 >= 8e6;
+    p.V = (!p.S && !part_lines && (d_hat < 6.0 || (d_hat < 12.0 && pr2 < 0.45) || pr2 < 0.20 || pair_long)) ? 2 : 1;
 
     // Scattered rows may belong to communities whose ids were shuffled.  Looking for them and ordering the schedule by
     // them costs the build some 0.15 ms and 0.6 ns a row; run side by side the rows of a community gather from L2 and the

@@ -345,6 +345,18 @@ def test_reorder_by_degree():
     assert pc.pcsr_reorder_by_degree(0, np.zeros(1, np.int32), np.zeros(0, np.int32)).size == 0
 
 
+def test_selector_pairs_short_rows_unless_their_rows_of_c_are_part_lines():
+    g = synth.workload("road", "small")
+    f = np.array(pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx))
+    assert f[5] < 6.0 and 0.2 <= f[15]
+    for n, single in ((2_000_000, (12, 16)), (167_000, (12, 16)), (166_000, (16,)), (125_000, (16,)), (124_000, ())):
+        f[0] = n
+        for K in (8, 9, 10, 12, 13, 16, 17, 20, 24, 32, 64):
+            assert pc.pcsr_select(f, K).V == (1 if K in single else 2), (n, K)
+    f[0], f[15] = 2_000_000, 0.1  # neighbouring rows that share their columns stay paired
+    assert pc.pcsr_select(f, 16).V == 2
+
+
 def test_selector_proposes_the_window_only_where_the_build_keeps_it():
     g = synth.workload("sbm", "small")                       # 24 communities of 500 consecutive ids
     f = np.array(pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx), dtype=np.float64)
