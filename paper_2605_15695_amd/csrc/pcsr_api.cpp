@@ -821,6 +821,7 @@ static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, co
     a.B = B;
     a.C = C;
     a.M = (int32_t)h->host.M;
+    a.mean_item = (int32_t)(h->host.nnz_v / std::max<int64_t>(h->host.M, 1));
     a.n_rows = (int32_t)h->host.n_rows;
     a.K = K;
     a.nblk = ls.grid_x;

@@ -1567,7 +1567,12 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
         return hipGetLastError();
     }
     const bool epi = args.epi.on && ls.ipg <= 1;
-    const bool near = near_enough(args);
+    // Unsplit items of less than a chunk: what 32-bit offsets save is little beside the slots and lanes that have nothing to load
+    // and now read all the same.  Paired cliques of 8 (16 lanes x dword), 2,000,000 rows: K = 12 127 us without, 143 with, K = 16
+    // 151 and 157; with 4 and 8 lanes on a par (road-like graph, K = 8 42.5 and 43).  Wide loads of 16 lanes and more gain 0-5 %
+    // there, and one-dword shapes with a tail 3-9 %.
+    const bool short_items = !S && args.mean_item < 16 && (ls.k_lpr < 16 || (ls.k_vec == 1 && !epi));
+    const bool near = near_enough(args) && !short_items;
     KernelFn fn;
     size_t lds = 0;
     if (args.outer) {
