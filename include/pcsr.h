@@ -68,6 +68,8 @@ enum {
                                   The alignment asked of B and C stays that of the vec passed, if
                                   any.  The format depends on the scratch memory at hand: where that
                                   of the search does not fit the flag does nothing               */
+    PCSR_FLAG_FAR_OFFSETS = 512, /* rows of B are addressed in 64 bits whatever its size, as those of a B of more than
+                                  0xe0000000 bytes always are.  C is the same bits either way: for tests and timing    */
     PCSR_FLAG_CLUSTER_WINDOWS = 1 << 28, /* with CLUSTER_IF_USEFUL, and set by pcsr_select where one
                                   product pays for it: a second copy of the nonzeros (8 bytes each,
                                   for as long as the handle lives) by which products of 64 columns
@@ -220,8 +222,8 @@ int pcsr_release_cached(int64_t *bytes);
 
 /*
  * Changes the kernel-only parameters (lanes_per_row, vec, rep, waves_per_wg,
- * items_per_group, and the PCSR_FLAG_NO_XCD_REMAP and PCSR_FLAG_ATOMIC_SPLIT bits of
- * flags) of an existing handle; 0 = auto.  The PCSR
+ * items_per_group, and the PCSR_FLAG_NO_XCD_REMAP, PCSR_FLAG_ATOMIC_SPLIT and
+ * PCSR_FLAG_FAR_OFFSETS bits of flags) of an existing handle; 0 = auto.  The PCSR
  * arrays are untouched, so one build can be timed under many launch shapes (the
  * exhaustive sweep that stands in for the training data of Section 5.2).
  * Errors: INVALID_ARG, UNSUPPORTED.

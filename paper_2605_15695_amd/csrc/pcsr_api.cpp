@@ -822,6 +822,7 @@ static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, co
     a.C = C;
     a.M = (int32_t)h->host.M;
     a.mean_item = (int32_t)(h->host.nnz_v / std::max<int64_t>(h->host.M, 1));
+    a.far = (h->flags & PCSR_FLAG_FAR_OFFSETS) != 0;
     a.n_rows = (int32_t)h->host.n_rows;
     a.K = K;
     a.nblk = ls.grid_x;
@@ -989,7 +990,7 @@ int pcsr_set_kernel_params(pcsr_handle_t h, int32_t lanes_per_row, int32_t vec, 
     h->rep = rep;
     h->waves = waves_per_wg;
     h->ipg = items_per_group;
-    constexpr int32_t kLaunchFlags = PCSR_FLAG_NO_XCD_REMAP | PCSR_FLAG_ATOMIC_SPLIT;
+    constexpr int32_t kLaunchFlags = PCSR_FLAG_NO_XCD_REMAP | PCSR_FLAG_ATOMIC_SPLIT | PCSR_FLAG_FAR_OFFSETS;
     h->flags = (h->flags & ~(kLaunchFlags | kWideBits)) | (flags & kLaunchFlags);
     return PCSR_OK;
 }

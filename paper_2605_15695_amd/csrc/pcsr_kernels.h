@@ -42,6 +42,7 @@ struct SpmmArgs {
     const int4 *sched;
     int32_t outer; // long items: sums of 32 vectors are added up apart (plain walk with S), or as the window kernel says
     int32_t mean_item; // vectors of a work item on average
+    int32_t far; // 1: no 32-bit offsets into B
     // column-window blocking (window kernel only)
     const int32_t *win_ptr;   // item range [win_ptr[b], win_ptr[b+1]) of block b (= workgroup b)
     const int32_t *win_start; // per item block: first column of the staged window or -1

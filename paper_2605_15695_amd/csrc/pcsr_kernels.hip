@@ -1548,7 +1548,7 @@ bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep)
 
 static bool near_enough(const SpmmArgs &a)
 {
-    return (uint64_t)a.n_cols * (uint64_t)a.K * 4u <= kNearBytes && a.K < (1 << 20);
+    return !a.far && (uint64_t)a.n_cols * (uint64_t)a.K * 4u <= kNearBytes && a.K < (1 << 20);
 }
 
 hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args, hipStream_t stream)
