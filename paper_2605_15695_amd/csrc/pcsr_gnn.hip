@@ -17,7 +17,7 @@ __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_a
 constexpr int kWaves = 4;
 constexpr int kLinearBlocks = 768; // three per compute unit
 constexpr int kBackBlocks = 512;
-constexpr int kWgradBlocks = 512; // 768 and 1024: 0.5 to 5 % slower at 2,000,000 rows, more below
+constexpr int kWgradBlocks = 512; // of four wavefronts; 768 and 1024: 0.5 to 5 % slower at 2,000,000 rows, more below
 constexpr int kWgradAhead = 2;
 constexpr int kColsumBlocks = 512;
 
@@ -680,36 +680,48 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
     }
 }
 
+// Bound by memory whatever the layout.  Arrays larger than the memory-side cache leave it as they are read (2,000,000 rows, 16 x 64
+// 114 -> 104 us, 128 x 16 194 -> 170, 32 x 32 91 -> 82; 300,000 rows, which fit, are 3-4 % slower so at 128 x 16, and left there for the next
+// kernel).  Only a side that one square reads: the others' reads come from L2 (128 x 32 215 -> 190 us, with both sides 222).
+// Wider shapes lose (96 x 96 398 -> 483).
+constexpr bool wgrad_light(int tg, int tx) { return tg * tx <= 8; }
+constexpr long kMemorySideCache = 256l << 20;
+
 struct WgradArgs {
     long n;
     int a, b;
     const float *G, *X;
     float *ws; // per workgroup: b*a of dW, then b column sums
     int sums;
-    int squares_g, squares_x; // of dW, 1 or 2 each way
-    long unchecked;           // rows before which a lane may read past the end of its row
+    int squares_x;      // of dW, side by side along X: 1 or 2
+    int squares;        // of a workgroup: 1, 2 or 4; grid.y has the others
+    int once_g, once_x; // nothing will be read again that is read of G / of X
+    long unchecked;     // rows before which a lane may read past the end of its row
 };
 
 // dW = G^T X: the rows are the k of the matrix instruction, four per instruction.  A lane reads T consecutive
 // columns of a row (T*(l%16) and on), which feed T tiles: tile t holds the columns T*i + t.  A wavefront
 // keeps up to 64 x 64 of dW in its accumulators and walks 16 rows a step; the rows of the next two steps are on their way
 // (requested right after the products that free their registers: no copies between two sets).
-// Weights wider than 64 are cut into two or four squares, taken by wavefronts of one workgroup over the same rows.
-// Rows are dealt to 512 to 2048 wavefronts; each workgroup leaves one partial dW, summed by sum_partials_kernel in a fixed order.
+// Weights wider than 64 are cut into two or four squares.  Long inputs: workgroups of eight wavefronts take all squares over the
+// same rows.  Short ones are in the caches, and what a workgroup leaves costs more than the second read of them: four
+// wavefronts to a square, fewer partial dW of fewer rows each.
+// Rows are dealt to 512 to 2048 wavefronts.  Those of a workgroup and square are added through LDS, and each workgroup leaves one
+// partial of its squares, summed by sum_partials_kernel in a fixed order.
 // Whole steps read without conditions.  Where a width is rounded up, lanes past the end of a row read the next
 // one's columns, whose sums nobody stores; the last rows, where that would pass the end of the array, and
 // steps of fewer rows take loads that check both.  Four-byte addresses do for loads of any width.
-// 2,000,000 rows, with the sums (before: conditions on every load, squares of 64 as workgroups of their own): 128 x 128 750 -> 701 us
-// (matrix cores 78 % busy at 2.0 GHz), 96 x 96 717 -> 473, 64 x 64 220 -> 203, 48 x 48 219 -> 143, 24 x 24 99 -> 73,
-// 47 x 65 394 -> 240; 16 x 64 111 -> 116 (5.5 TB/s either way, nothing to gain there).  torch's product of the transposed G takes 2900 at 64 x 64.
+// 2,000,000 rows, with the sums, beside conditions on every load and squares of 64 as workgroups of their own: 128 x 128 676 -> 581 us
+// (matrix cores 78 % busy at 2.0 GHz), 96 x 96 692 -> 389, 64 x 64 203 -> 182, 48 x 48 187 -> 139, 128 x 16 187 -> 170, 16 x 64 108 -> 104;
+// 32,768 rows: 128 x 128 23.9 -> 23.1, 64 x 128 18.0 -> 15.9, 96 x 96 22.7 -> 16.4.  torch's product of the transposed G takes 2900 at 64 x 64.
 template <int TG, int TX>
-__global__ void __launch_bounds__(64 * kWaves, 2) wgrad_kernel(WgradArgs p)
+__global__ void __launch_bounds__(2 * 64 * kWaves, 2) wgrad_kernel(WgradArgs p)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, q = lane >> 4;
-    const int squares = p.squares_g * p.squares_x, row_waves = kWaves / squares;
-    const int square = wave & (squares - 1), row_wave = wave / squares;
-    const int g0 = square / p.squares_x * TG * 16, x0 = square % p.squares_x * TX * 16;
+    const int squares = p.squares, row_waves = (int)(blockDim.x >> 6) / squares;
+    const int square = wave & (squares - 1), row_wave = wave / squares, of_dw = (int)blockIdx.y * squares + square;
+    const int g0 = of_dw / p.squares_x * TG * 16, x0 = of_dw % p.squares_x * TX * 16;
 
     f4 acc[TG][TX];
     float gsum[TG];
@@ -725,15 +737,15 @@ __global__ void __launch_bounds__(64 * kWaves, 2) wgrad_kernel(WgradArgs p)
     struct Rows {
         float g[U][TG], x[U][TX];
     };
-    auto fetch = [&](long row0, Rows &r) {
+    auto fetch = [&](long row0, Rows &r, auto once_g, auto once_x) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const float *g = reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.G + (row0 + 4 * u) * p.b) + gat);
             const float *x = reinterpret_cast<const float *>(reinterpret_cast<const char *>(p.X + (row0 + 4 * u) * p.a) + xat);
 #pragma unroll
-            for (int i = 0; i < TG; ++i) r.g[u][i] = g[i];
+            for (int i = 0; i < TG; ++i) r.g[u][i] = once_g ? __builtin_nontemporal_load(g + i) : g[i];
 #pragma unroll
-            for (int j = 0; j < TX; ++j) r.x[u][j] = x[j];
+            for (int j = 0; j < TX; ++j) r.x[u][j] = once_x ? __builtin_nontemporal_load(x + j) : x[j];
         }
     };
     auto fetch_checked = [&](long row0, Rows &r) {
@@ -771,25 +783,41 @@ __global__ void __launch_bounds__(64 * kWaves, 2) wgrad_kernel(WgradArgs p)
     const long whole = p.unchecked - 4 * U; // the last row a step may begin at
     long row0 = ((long)blockIdx.x * row_waves + row_wave) * 4 * U;
     Rows r[kWgradAhead];
+    auto walk = [&](auto once_g, auto once_x) {
 #pragma unroll
-    for (int d = 0; d < kWgradAhead; ++d)
-        if (row0 + d * step <= whole) fetch(row0 + d * step, r[d]);
-    for (; row0 + (kWgradAhead - 1) * step <= whole; row0 += kWgradAhead * step) {
+        for (int d = 0; d < kWgradAhead; ++d)
+            if (row0 + d * step <= whole) fetch(row0 + d * step, r[d], once_g, once_x);
+        for (; row0 + (kWgradAhead - 1) * step <= whole; row0 += kWgradAhead * step) {
 #pragma unroll
-        for (int d = 0; d < kWgradAhead; ++d) {
-            products(r[d]);
-            const long next = row0 + (d + kWgradAhead) * step;
-            asm volatile("" ::: "memory"); // requested here, not where they are used
-            fetch(next <= whole ? next : row0, r[d]);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int d = 0; d < kWgradAhead; ++d) {
+                products(r[d]);
+                const long next = row0 + (d + kWgradAhead) * step;
+                asm volatile("" ::: "memory"); // requested here, not where they are used
+                fetch(next <= whole ? next : row0, r[d], once_g, once_x);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
+#pragma unroll
+        for (int d = 0; d < kWgradAhead; ++d)
+            if (row0 <= whole) {
+                products(r[d]);
+                row0 += step;
+            }
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if constexpr (wgrad_light(TG, TX)) {
+        if (p.once_g && p.once_x)
+            walk(yes, yes);
+        else if (p.once_g)
+            walk(yes, no);
+        else if (p.once_x)
+            walk(no, yes);
+        else
+            walk(no, no);
+    } else {
+        walk(no, no);
     }
-#pragma unroll
-    for (int d = 0; d < kWgradAhead; ++d)
-        if (row0 <= whole) {
-            products(r[d]);
-            row0 += step;
-        }
     for (; row0 < p.n; row0 += step) {
         fetch_checked(row0, r[0]);
         products(r[0]);
@@ -802,7 +830,37 @@ __global__ void __launch_bounds__(64 * kWaves, 2) wgrad_kernel(WgradArgs p)
     }
     float *out = p.ws + (long)blockIdx.x * ((long)p.b * p.a + p.b);
     float *sums = p.sums && x0 == 0 ? out + (long)p.b * p.a : nullptr;
-    if (row_waves == 1) { // a square each: no sum over wavefronts
+    // The wavefronts of a square, in order, lane by lane as they hold it; the last one ends with the sum.
+    __shared__ f4 red[4][TG * TX * 64];
+    __shared__ float gred[2 * kWaves][TG * 16];
+    if (q == 0) {
+#pragma unroll
+        for (int i = 0; i < TG; ++i) gred[wave][TG * c + i] = gsum[i];
+    }
+    f4 *held = red[square] + lane;
+    for (int w = 0; w < row_waves; ++w) {
+        if (row_wave == w) {
+            if (w) {
+                f4 t[TG][TX]; // requested together
+#pragma unroll
+                for (int i = 0; i < TG; ++i)
+#pragma unroll
+                    for (int j = 0; j < TX; ++j) t[i][j] = held[(i * TX + j) * 64];
+#pragma unroll
+                for (int i = 0; i < TG; ++i)
+#pragma unroll
+                    for (int j = 0; j < TX; ++j) acc[i][j] = t[i][j] + acc[i][j];
+            }
+            if (w + 1 < row_waves) {
+#pragma unroll
+                for (int i = 0; i < TG; ++i)
+#pragma unroll
+                    for (int j = 0; j < TX; ++j) held[(i * TX + j) * 64] = acc[i][j];
+            }
+        }
+        __syncthreads();
+    }
+    if (row_wave == row_waves - 1) {
 #pragma unroll
         for (int i = 0; i < TG; ++i) {
 #pragma unroll
@@ -814,40 +872,8 @@ __global__ void __launch_bounds__(64 * kWaves, 2) wgrad_kernel(WgradArgs p)
                         if (col + j < p.a) out[(long)row * p.a + col + j] = acc[i][j][s];
                 }
             }
-            const int row = g0 + TG * c + i;
-            if (sums && q == 0 && row < p.b) sums[row] = gsum[i];
         }
-        return;
     }
-    // the wavefronts of a square, in order
-    __shared__ float red[2][TG * 16][TX * 16 + 1];
-    for (int w = 0; w < row_waves; ++w) {
-        if (row_wave == w) {
-#pragma unroll
-            for (int i = 0; i < TG; ++i) {
-#pragma unroll
-                for (int j = 0; j < TX; ++j)
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        float &d = red[square][TG * (4 * q + s) + i][TX * c + j];
-                        d = w ? d + acc[i][j][s] : acc[i][j][s];
-                    }
-            }
-        }
-        __syncthreads();
-    }
-    for (int e = tid; e < squares * (TG * TX * 256); e += 64 * kWaves) {
-        const int sq = e / (TG * TX * 256), f = e - sq * (TG * TX * 256), i = f / (TX * 16), j = f - i * (TX * 16);
-        const int row = sq / p.squares_x * TG * 16 + i, col = sq % p.squares_x * TX * 16 + j;
-        if (row < p.b && col < p.a) out[(long)row * p.a + col] = red[sq][i][j];
-    }
-    __syncthreads();
-    float(*gred)[TG * 16] = reinterpret_cast<float(*)[TG * 16]>(&red[0][0][0]); // [kWaves]
-    if (q == 0) {
-#pragma unroll
-        for (int i = 0; i < TG; ++i) gred[wave][TG * c + i] = gsum[i];
-    }
-    __syncthreads();
     if (sums && row_wave == 0 && lane < TG * 16 && g0 + lane < p.b) {
         float t = gred[wave][lane];
         for (int w = 1; w < row_waves; ++w) t += gred[wave + w * squares][lane];
@@ -1177,13 +1203,21 @@ int pcsr_gnn_wgrad(int64_t n, int32_t a, int32_t b, const float *G, const float 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int tg = wgrad_tiles(b), tx = wgrad_tiles(a);
     WgradArgs p;
-    p.squares_g = wgrad_squares(b);
-    p.squares_x = wgrad_squares(a);
-    const long rows = 64 * (kWaves / (p.squares_g * p.squares_x)); // at least four steps of 16 rows per wavefront
-    long blocks = (n + rows - 1) / rows;
-    blocks = blocks < 1 ? 1 : (blocks > kWgradBlocks ? kWgradBlocks : blocks);
+    const int squares_g = wgrad_squares(b), squares_x = wgrad_squares(a), all = squares_g * squares_x;
+    // Squares as workgroups of their own, where dW is cut, up to 131,072 rows (us beside all squares in one: 128 x 128 32,768 rows 23.1 / 27.3,
+    // 65,536 31.8 / 35.4, 131,072 49.1 / 52.3; 64 x 128 15.9 / 20.1, 23.8 / 23.5 and 32.5 / 32.2; 300,000 rows, the old form, 112 / 101 and 62 / 55).
+    const bool apart = all == 1 || n <= (1 << 17);
+    const int waves = apart ? kWaves : 2 * kWaves;
+    const long most = kWgradBlocks / (apart ? all : 2);
+    long blocks = (n + 64 * kWaves - 1) / (64 * kWaves); // at least four steps of 16 rows per wavefront of a square of its own
+    blocks = blocks < 1 ? 1 : (blocks > most ? most : blocks);
+    const bool large = (double)n * 4.0 * (a + b) > (double)kMemorySideCache;
+    p.squares_x = squares_x;
+    p.squares = apart ? 1 : all;
+    p.once_g = large && squares_x == 1;
+    p.once_x = large && squares_g == 1;
     // rows that the columns past a row's end reach into
-    const long past_g = (16 * tg * p.squares_g - 1) / b, past_x = (16 * tx * p.squares_x - 1) / a;
+    const long past_g = (16 * tg * squares_g - 1) / b, past_x = (16 * tx * squares_x - 1) / a;
     p.unchecked = n - (past_g > past_x ? past_g : past_x);
     p.n = n;
     p.a = a;
@@ -1192,7 +1226,7 @@ int pcsr_gnn_wgrad(int64_t n, int32_t a, int32_t b, const float *G, const float 
     p.X = X;
     p.ws = ws;
     p.sums = db != nullptr;
-    hipLaunchKernelGGL(pick_wgrad(tg, tx), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, p);
+    hipLaunchKernelGGL(pick_wgrad(tg, tx), dim3((unsigned)blocks, (unsigned)(all / p.squares)), dim3(64 * waves), 0, s, p);
     int rc = to_code(hipGetLastError());
     const long len = (long)a * b;
     if (rc == PCSR_OK) rc = sum_partials(ws, (int)blocks, len + b, len, dW, db ? b : 0, db, s);

@@ -55,7 +55,8 @@ def test_dense_kernels(a, b, n):
 # weight gradients: one, two and four squares, widths short of a tile, rows short of a step, rows at no multiple of 16 bytes.
 # Lanes past the end of a row read the next one: an infinite column there reaches no other column's sum.
 # A sum of n terms is off by at most n * 2^-24 of the sum of their magnitudes, 1e-6 up to n = 16; beyond that rounding errors
-# of the chains add up like sqrt(n), and a wavefront's chain is n / 512 terms at the least.
+# of the chains add up like sqrt(n), and a wavefront's chain is 64 terms up to n = 131,072 (one square) or 32,768 (four), and n / 2048
+# or n / 512 above.
 @pytest.mark.parametrize("a,b", [(1, 128), (2, 40), (17, 33), (48, 48), (49, 96), (65, 64), (80, 97), (96, 96), (127, 5),
                                  (128, 65)])
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 64 * 16 + 3, 40009])
@@ -74,6 +75,29 @@ def test_weight_gradient(a, b, n, skew):
     dW, db = d.wgrad(G, X, bias=True)
     assert torch.equal(dW[1:, 1:], first[1:, 1:]) and torch.equal(db[1:], sums[1:])
     assert bool(torch.isinf(db[0])) and not bool(torch.isfinite(dW[0]).any() or torch.isfinite(dW[:, 0]).any())
+
+
+# both sides of the lines between its forms: squares in workgroups of their own and together, arrays that the memory-side cache holds
+# and larger ones (256 MB), whose rows are read past it on the sides that are read once; tolerances as above
+@pytest.mark.parametrize("a,b,n", [(96, 96, 131072), (96, 96, 131073), (128, 100, 131089), (47, 65, 131073), (128, 64, 131100),
+                                   (16, 16, (1 << 21) + 5), (128, 16, 500003), (16, 128, 500003), (40, 64, 700001)])
+def test_weight_gradient_of_many_rows(a, b, n):
+    g = torch.Generator(device="cuda").manual_seed(n + a)
+    X, G = (torch.randn(n, w, generator=g, device="cuda") for w in (a, b))
+    dW, db = _dense(a, b).wgrad(G, X, bias=True)
+    Xd, Gd = X.double(), G.double()
+    assert bool(((dW.double() - Gd.t() @ Xd).abs() <= 1e-6 * (Gd.abs().t() @ Xd.abs())).all())
+    assert bool(((db.double() - Gd.sum(0)).abs() <= 1e-6 * Gd.abs().sum(0)).all())
+
+
+# what is left for the second pass: one partial dW for 256 rows at most where dW is cut, or short inputs spend their time on it
+@pytest.mark.parametrize("a,b", [(64, 128), (128, 64), (128, 128), (96, 96)])
+@pytest.mark.parametrize("n", [5000, 32768])
+def test_weight_gradient_leaves_few_partial_sums(a, b, n):
+    d = _dense(a, b)
+    ws = d._ws = torch.full((d.ws_floats,), float("nan"), device="cuda")
+    d.wgrad(torch.randn(n, b, device="cuda"), torch.randn(n, a, device="cuda"), bias=True)
+    assert int((~torch.isnan(ws)).sum()) == -(-n // 256) * (a * b + b)
 
 
 # rows short of a piece: the bias of rows that are not there is in no sum
