@@ -38,13 +38,20 @@ struct LinearArgs {
 // 64), read as one ds_read_b128 per 4 matrix instructions.
 // Bound by memory: 2,000,000 x 64 -> 64 is 1.02 GB and 16.4 GFLOP (104 us at the fp32 matrix
 // peak).  The next rows are requested before this step's products, and no more workgroups are
-// started than run at once.  With bias and ReLU 238 us (piece_kernel, 4.3 TB/s), with a mask to read as
-// well 291 (5.3 TB/s), where torch's product, bias and ReLU take 488.
+// started than run at once.  With bias and ReLU 186 us (piece_kernel, 5.5 TB/s), with a mask to read as
+// well and column sums 268 (5.7 TB/s), where torch's product, bias and ReLU take 488.
 // VEC: widths that are multiples of 4, arrays 16-byte aligned.  RED: dot and/or column sums.
 constexpr int blocks_per_cu(int kt, int nt) { return kt + nt <= 8 ? 3 : 2; } // registers and LDS allow no more
 // piece_kernel: eight wavefronts to one copy of the weights where two copies do not fit
 constexpr int piece_waves(int kt, int nt) { return kt + nt > 12 ? 8 : 4; }
-constexpr int piece_blocks_per_cu(int kt, int nt) { return kt + nt > 12 ? 1 : blocks_per_cu(kt, nt); }
+// Without conditions in its loop a wavefront keeps more loads and stores on their way, and fewer of them do: at 2,000,000 / 300,000 /
+// 65,536 rows one workgroup to a compute unit in place of two or three takes 0.88 / 0.80 / 0.73 of the time of 64 -> 64 before (two: 0.95, 0.86,
+// 0.89), 48 -> 48 0.92 / 0.91 / 0.82, 128 -> 16 0.96 / 0.94 / 0.88, with a mask and column sums 0.99 / 0.97 / 0.95.  Narrower ones want two (16 -> 64
+// 1.17 with one, 0.97 with two, 1.05 with three), and so do sums over 48 and 64 columns of 128 (1.03-1.05 at 300,000 rows, 0.9-0.96).
+constexpr int piece_blocks_per_cu(int kt, int nt, bool red)
+{
+    return kt + nt <= 5 || (red && kt == 8 && (nt == 3 || nt == 4)) ? 2 : 1;
+}
 
 // weight fragments of one layer: fragment (kt, nt), lane l, component s is
 // W[out = 16 nt + l%16][in = 16 kt + 4 (l/16) + s] (transposed: W[in][out])
@@ -95,11 +102,12 @@ template <int NT> __device__ __forceinline__ void start_from(const f4 *bias, int
 // side by side, T times 1 KB (lane l, step u: 16-byte word 64 u + l of the piece), and turned
 // to and from the fragments through an LDS patch of the wavefront's own.  Straight from the fragments
 // every access would touch 16 rows, 64 bytes of each: 16 -> 64 columns ran at 3.7 TB/s so, and run at
-// 5.3 through the patch (2,000,000 rows, 121 us).
+// 5.6 through the patch (2,000,000 rows, 115 us).
 //
-// Groups of 16 rows that are whole have a loop of their own: with no load or store in it that may be left out, the compiler
-// counts what is in flight, and a wait for the next rows is not one for the stores before it.
+// Groups of 16 rows that are whole have a loop of their own: with no load or store in it that may be left out, but for the
+// request of the next rows, the compiler counts what is in flight, and a wait for the next rows is not one for the stores before it.
 constexpr std::integral_constant<long, 16> kWhole{};
+constexpr int kSumRun = 8;
 constexpr int patch_ld(int t) { return 16 * t + 4; } // floats per row
 constexpr int patch_floats(int t) { return 16 * patch_ld(t); }
 
@@ -338,9 +346,11 @@ __device__ __forceinline__ void collect_colsum(float *lds, const f4 (&csum)[T], 
     for (int u = 0; u < T; ++u) s[FRAGS ? (lane & 15) * (4 * T) + 4 * u + (lane >> 4) : u * 64 + lane] = csum[u];
     __syncthreads();
     for (int c = tid; c < 16 * T; c += blockDim.x) {
-        float t = 0.0f;
-        for (int i = 0; i < (int)blockDim.x / 4; ++i) t += lds[i * (16 * T) + c];
-        out[c] = t;
+        float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int i = 0; i < (int)blockDim.x / 4; i += 4) // 64 or 128 of them
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] += lds[(i + u) * (16 * T) + c];
+        out[c] = (t[0] + t[1]) + (t[2] + t[3]);
     }
 }
 __device__ __forceinline__ void collect_dot(float *lds, float dot, float *out)
@@ -370,56 +380,86 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), piece_waves(KT, NT) 
     stage_bias<NT>(bias, p.bias, 16 * NT);
     __syncthreads();
 
-    f4 csum[RED ? NT : 1];
-    float dot = 0.0f;
+    f4 csum[RED ? NT : 1], csums[RED ? NT : 1]; // sums of kSumRun groups are put apart
+    float dot = 0.0f, dots = 0.0f;
+    [[maybe_unused]] int run = 0;
+    auto put_apart = [&] {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            csums[nt] += csum[nt];
+            csum[nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        dots += dot;
+        dot = 0.0f;
+        run = 0;
+    };
     if constexpr (RED) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) csum[nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int nt = 0; nt < NT; ++nt) csum[nt] = csums[nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
     }
     const long full = p.n >> 4, stride = (long)gridDim.x * kW;
     long g = (long)blockIdx.x * kW + wave;
     f4 xn[KT]; // the next rows are requested before this step's products
     auto load = [&](long g, auto rows) { load_frags<KT>(p.X + g * (256 * KT), lane, rows, xn); };
-    auto step = [&](long g, auto rows, auto next) {
+    // aux, mask, store: which of these arrays there are, as constants in the loops of the layers' own calls
+    auto step = [&](long g, auto rows, auto aux, auto mask, auto store, auto next) {
         asm volatile("" ::: "memory"); // as in linear_kernel
         f4 x[KT], y[NT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) x[kt] = xn[kt];
         next();
         f4 m[NT]; // aux, or the mask; callers have one of them
-        const float *first = RED && p.aux ? p.aux : p.mask;
-        if (first) load_piece<NT>(first + g * (256 * NT), lane, rows, m);
+        if (aux || mask) load_piece<NT>((aux ? p.aux : p.mask) + g * (256 * NT), lane, rows, m);
         start_from<NT>(bias, lane, y);
         multiply<KT, NT>(wfrag, lane, x, y);
         if (p.relu) relu_rows<NT>(y);
         if constexpr (RED) clear_past_end<NT>(lane, rows, y);
         frags_to_piece<NT>(patch, lane, y);
-        if constexpr (RED) {
-            if (p.aux) {
+        if (aux) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    dot += (y[t][0] * m[t][0] + y[t][1] * m[t][1]) + (y[t][2] * m[t][2] + y[t][3] * m[t][3]);
-                if (p.mask) load_piece<NT>(p.mask + g * (256 * NT), lane, rows, m);
-            }
+            for (int t = 0; t < NT; ++t)
+                dot += (y[t][0] * m[t][0] + y[t][1] * m[t][1]) + (y[t][2] * m[t][2] + y[t][3] * m[t][3]);
+            if (mask) load_piece<NT>(p.mask + g * (256 * NT), lane, rows, m);
         }
-        if (p.mask) mask_rows<NT>(y, m);
+        if (mask) mask_rows<NT>(y, m);
         if constexpr (RED) {
 #pragma unroll
             for (int t = 0; t < NT; ++t) csum[t] += y[t];
         }
-        if (p.Y) store_piece<NT>(p.Y + g * (256 * NT), lane, rows, y);
+        if (store) store_piece<NT>(p.Y + g * (256 * NT), lane, rows, y);
+        if constexpr (RED)
+            if (++run == kSumRun) put_apart();
     };
-    if (g < full) load(g, kWhole);
-    for (; g < full; g += stride) step(g, kWhole, [&] {
-            if (g + stride < full) load(g + stride, kWhole);
-        });
+    auto walk = [&](auto aux, auto mask, auto store) {
+        if (g < full) load(g, kWhole);
+        for (; g < full; g += stride)
+            step(g, kWhole, aux, mask, store, [&] {
+                if (g + stride < full) load(g + stride, kWhole);
+            });
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    const bool aux = RED && p.aux, mask = p.mask, store = p.Y;
+    if constexpr (RED) {
+        if (aux && !mask && store)
+            walk(yes, no, yes);
+        else if (!aux && mask && store)
+            walk(no, yes, yes);
+        else
+            walk(aux, mask, store);
+    } else if (mask) {
+        walk(no, yes, yes);
+    } else {
+        walk(no, no, yes);
+    }
     if (const long rows = p.n - g * 16; rows > 0) { // the rows that are left over
         load(g, rows);
-        step(g, rows, [] {});
+        step(g, rows, aux, mask, store, [] {});
     }
     if constexpr (RED) {
-        if (p.ws_colsum) collect_colsum<NT, false>(patches, csum, p.ws_colsum + (long)blockIdx.x * (16 * NT));
-        if (p.ws_dot) collect_dot(patches, dot, p.ws_dot + blockIdx.x);
+        put_apart();
+        if (p.ws_colsum) collect_colsum<NT, false>(patches, csums, p.ws_colsum + (long)blockIdx.x * (16 * NT));
+        if (p.ws_dot) collect_dot(patches, dots, p.ws_dot + blockIdx.x);
     }
 }
 
@@ -1097,7 +1137,7 @@ int pcsr_gnn_linear(int64_t n, int32_t a, int32_t b, const float *X, const float
     LinearFn fn = pick_linear_kn(kt, nt, exact ? 2 : vec, red);
     if (!fn) return PCSR_E_UNSUPPORTED;
     const int waves = exact ? piece_waves(kt, nt) : kWaves;
-    const long blocks = row_blocks(n, 256 * (exact ? piece_blocks_per_cu(kt, nt) : blocks_per_cu(kt, nt)), waves);
+    const long blocks = row_blocks(n, 256 * (exact ? piece_blocks_per_cu(kt, nt, red) : blocks_per_cu(kt, nt)), waves);
     LinearArgs p;
     p.n = n;
     p.a = a;

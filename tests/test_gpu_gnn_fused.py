@@ -100,6 +100,31 @@ def test_weight_gradient_leaves_few_partial_sums(a, b, n):
     assert int((~torch.isnan(ws)).sum()) == -(-n // 256) * (a * b + b)
 
 
+# exact widths: each set of arrays beside X has a loop of its own, and sums of eight groups of rows are put apart (of 16 rows: from
+# 131,072 or 262,144 rows on, with one and two workgroups to a compute unit)
+@pytest.mark.parametrize("a,b", [(16, 16), (64, 64), (16, 128), (128, 48), (128, 128)])
+@pytest.mark.parametrize("n", [15, 300007])
+@pytest.mark.parametrize("aux,mask,store,sums", [(0, 0, 1, 0), (0, 1, 1, 0), (1, 0, 1, 1), (0, 1, 1, 1), (1, 0, 0, 1), (0, 0, 1, 1), (1, 1, 1, 1)])
+def test_arrays_beside_the_rows(a, b, n, aux, mask, store, sums):
+    g = torch.Generator(device="cuda").manual_seed(a + b + n)
+    X, A, M = (torch.randn(n, w, generator=g, device="cuda") for w in (a, b, b))
+    W = torch.randn(a, b, generator=g, device="cuda")
+    dot, csum = torch.empty((), device="cuda"), torch.empty(b, device="cuda")
+    Y = _dense(a, b).linear(X, W, transposed=True, mask=M if mask else None, aux=A if aux else None, dot=dot if aux else None,
+                            colsum=csum if sums else None, store=bool(store))
+    lin, size = X.double() @ W.double(), X.double().abs() @ W.double().abs()
+    if aux:
+        assert abs(float(dot.double() - (lin * A.double()).sum())) <= 1e-6 * float((size * A.double().abs()).sum())
+    if mask:
+        lin = lin * (M > 0)
+    if store:
+        _close(Y, lin)
+    else:
+        assert Y is None
+    if sums:
+        assert bool(((csum.double() - lin.sum(0)).abs() <= 1e-6 * size.sum(0)).all())
+
+
 # rows short of a piece: the bias of rows that are not there is in no sum
 @pytest.mark.parametrize("a,b", [(16, 16), (64, 64), (128, 128), (96, 32), (24, 48), (33, 7)])
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 1000 * 16 + 5])
