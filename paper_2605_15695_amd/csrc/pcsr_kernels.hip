@@ -1567,11 +1567,14 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
         return hipGetLastError();
     }
     const bool epi = args.epi.on && ls.ipg <= 1;
-    // Unsplit items of less than a chunk: what 32-bit offsets save is little beside the slots and lanes that have nothing to load
-    // and now read all the same.  Paired cliques of 8 (16 lanes x dword), 2,000,000 rows: K = 12 127 us without, 143 with, K = 16
-    // 151 and 157; with 4 and 8 lanes on a par (road-like graph, K = 8 42.5 and 43).  Wide loads of 16 lanes and more gain 0-5 %
-    // there, and one-dword shapes with a tail 3-9 %.
-    const bool short_items = !S && args.mean_item < 16 && (ls.k_lpr < 16 || (ls.k_vec == 1 && !epi));
+    // Unsplit items of less than a chunk.  4 and 8 lanes: 32-bit offsets save little beside the slots and lanes that have nothing to
+    // load and now read all the same (time with them over without, rows of 3 to 14, the shapes that are taken unasked: 300,000 rows
+    // 0.97-1.05, 1,500,000 0.96-1.10 but for one 0.82; items of 16 to 24 0.96-1.05).  Paired items of one dword a lane, plain: B of 72 and 96 MB
+    // 1.00-1.11 with 10 and 14 vectors, 0.96-1.05 with 17 and 20; of 14 and 19 MB, which L2 holds, 0.93-0.96 at any length.  Single ones gain
+    // (8 to 18 vectors 0.84-1.00, uniform columns 0.98-1.00), and so do tails (pairs 0.87-1.03, mostly below 0.95) and wide loads of 16
+    // lanes and more (0.93-1.02).
+    const bool past_l2 = (double)args.n_cols * args.K * 4.0 > 32.0 * 1048576.0;
+    const bool short_items = !S && args.mean_item < 16 && (ls.k_lpr < 16 || (V == 2 && ls.k_vec == 1 && !epi && past_l2));
     const bool near = near_enough(args) && !short_items;
     KernelFn fn;
     size_t lds = 0;
