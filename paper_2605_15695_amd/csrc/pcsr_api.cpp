@@ -1183,8 +1183,12 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // 160, K = 32: V = 2 runs at 0.55 of V = 1).
     const bool pair_long = long_uniform && n * (double)(K < 32 ? 4 : 8) / 128.0 >= 3500.0;
     // Rows of C of 48 or 64 bytes are written one by one by a pair's lanes, part lines each, where single rows' lane groups
-    // fill lines together: V = 1 takes 0.77-0.92 of V = 2 (with a self term 0.61-1.0, and a mask 0.59-0.98) on road-like and uniform
-    // graphs of 300,000 and 2,000,000 rows of 2 to 6.  Wider rows and K = 8 do better paired, products of under 10 us are on a par.
+    // fill lines together: V = 1 takes 0.59-0.99 of V = 2 (with a self term 0.50-1.03, and a mask 0.58-0.99) on road-like graphs of 2 to 7
+    // a row and uniform ones of 3 to 6, 300,000 and 2,000,000 rows.  C below 8 MB (120,000 rows) 0.85-1.01, products of under 10 us.
+    // A handle has one V, so an operator made for these widths runs its others so too: training with hidden 12 and 16 and 8, 16 or 32
+    // features takes 0.80-1.02 of V = 2 on graphs of 3 to 7 a row (but 1.05 in a GCN of two layers from 8 features on 2,000,000 rows of 3).
+    // Its plain products of 8 columns 0.81-1.15, of 20 to 32 0.87-1.30, the slowest where rows are local: which is why those
+    // widths stay paired where they are what the handle is made for.
     const bool part_lines = K > 8 && K <= 16 && K % 4 == 0 && d_hat < 8.0 && pr2 >= 0.20 && n * (double)K * 4.0 >= 8e6;
     p.V = (!p.S && !part_lines && (d_hat < 6.0 || (d_hat < 12.0 && pr2 < 0.45) || pr2 < 0.20 || pair_long)) ? 2 : 1;
 
