@@ -47,10 +47,11 @@ constexpr int piece_waves(int kt, int nt) { return kt + nt > 12 ? 8 : 4; }
 // Without conditions in its loop a wavefront keeps more loads and stores on their way, and fewer of them do: at 2,000,000 / 300,000 /
 // 65,536 rows one workgroup to a compute unit in place of two or three takes 0.88 / 0.80 / 0.73 of the time of 64 -> 64 before (two: 0.95, 0.86,
 // 0.89), 48 -> 48 0.92 / 0.91 / 0.82, 128 -> 16 0.96 / 0.94 / 0.88, with a mask and column sums 0.99 / 0.97 / 0.95.  Narrower ones want two (16 -> 64
-// 1.17 with one, 0.97 with two, 1.05 with three), and so do sums over 48 and 64 columns of 128 (1.03-1.05 at 300,000 rows, 0.9-0.96).
+// 1.17 with one, 0.97 with two, 1.05 with three), and so do sums over 48 and 64 columns of 128 (1.03-1.05 at 300,000 rows, 0.9-0.96)
+// and 16 -> 96, written by more than it is read (158 and 154 us in a training step of 2,000,000 rows).
 constexpr int piece_blocks_per_cu(int kt, int nt, bool red)
 {
-    return kt + nt <= 5 || (red && kt == 8 && (nt == 3 || nt == 4)) ? 2 : 1;
+    return kt + nt <= 5 || (red && kt == 8 && (nt == 3 || nt == 4)) || (!red && kt == 1 && nt == 6) ? 2 : 1;
 }
 
 // weight fragments of one layer: fragment (kt, nt), lane l, component s is
@@ -722,8 +723,9 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
 
 // Bound by memory whatever the layout.  Arrays larger than the memory-side cache leave it as they are read (2,000,000 rows, 16 x 64
 // 114 -> 104 us, 128 x 16 194 -> 170, 32 x 32 91 -> 82; 300,000 rows, which fit, are 3-4 % slower so at 128 x 16, and left there for the next
-// kernel).  Only a side that one square reads: the others' reads come from L2 (128 x 32 215 -> 190 us, with both sides 222).
-// Wider shapes lose (96 x 96 398 -> 483).
+// kernel).  Only a side that one square reads: the others' reads come from L2 (128 x 32 215 -> 190 us, with both sides 222), and so
+// does the rest of a line of 128 bytes that two squares of 48 columns share (in a training step of 2,000,000 rows 96 x 16 192 us so, 172
+// kept).  Wider shapes lose (96 x 96 398 -> 483).
 constexpr bool wgrad_light(int tg, int tx) { return tg * tx <= 8; }
 constexpr long kMemorySideCache = 256l << 20;
 
@@ -1254,8 +1256,8 @@ int pcsr_gnn_wgrad(int64_t n, int32_t a, int32_t b, const float *G, const float 
     const bool large = (double)n * 4.0 * (a + b) > (double)kMemorySideCache;
     p.squares_x = squares_x;
     p.squares = apart ? 1 : all;
-    p.once_g = large && squares_x == 1;
-    p.once_x = large && squares_g == 1;
+    p.once_g = large && squares_x == 1 && (squares_g == 1 || tg % 2 == 0);
+    p.once_x = large && squares_g == 1 && (squares_x == 1 || tx % 2 == 0);
     // rows that the columns past a row's end reach into
     const long past_g = (16 * tg * squares_g - 1) / b, past_x = (16 * tx * squares_x - 1) / a;
     p.unchecked = n - (past_g > past_x ? past_g : past_x);
