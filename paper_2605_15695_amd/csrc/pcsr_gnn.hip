@@ -370,7 +370,7 @@ __device__ __forceinline__ void collect_dot(float *lds, float dot, float *out)
 
 // Exact widths, a = 16 KT and b = 16 NT: as linear_kernel, in pieces.
 template <int KT, int NT, bool RED>
-__global__ void __launch_bounds__(64 * piece_waves(KT, NT), piece_waves(KT, NT) == 8 ? 2 : blocks_per_cu(KT, NT)) piece_kernel(LinearArgs p)
+__global__ void __launch_bounds__(64 * piece_waves(KT, NT), RED || piece_waves(KT, NT) == 8 ? 2 : blocks_per_cu(KT, NT)) piece_kernel(LinearArgs p)
 {
     constexpr int kW = piece_waves(KT, NT), kPatch = patch_floats(NT);
     __shared__ f4 wfrag[KT * NT * 64], bias[NT * 4];
