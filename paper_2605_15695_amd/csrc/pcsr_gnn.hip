@@ -47,11 +47,12 @@ constexpr int piece_waves(int kt, int nt) { return kt + nt > 12 ? 8 : 4; }
 // Without conditions in its loop a wavefront keeps more loads and stores on their way, and fewer of them do: at 2,000,000 / 300,000 /
 // 65,536 rows one workgroup to a compute unit in place of two or three takes 0.88 / 0.80 / 0.73 of the time of 64 -> 64 before (two: 0.95, 0.86,
 // 0.89), 48 -> 48 0.92 / 0.91 / 0.82, 128 -> 16 0.96 / 0.94 / 0.88, with a mask and column sums 0.99 / 0.97 / 0.95.  Narrower ones want two (16 -> 64
-// 1.17 with one, 0.97 with two, 1.05 with three), and so do sums over 48 and 64 columns of 128 (1.03-1.05 at 300,000 rows, 0.9-0.96)
-// and 16 -> 96, written by more than it is read (158 and 154 us in a training step of 2,000,000 rows).
-constexpr int piece_blocks_per_cu(int kt, int nt, bool red)
+// 1.17 with one, 0.97 with two, 1.05 with three).  So do 64 columns of 96 and of 128 (one takes 1.04-1.20 of two at 300,000 rows, 0.96-1.07 at
+// 2,000,000; with a mask and no sums 128 -> 64 had lost: 63 us for 56, now 53), 48 of 128 with a mask or sums (1.07-1.08; 0.91-0.96), and 16 -> 96
+// without, written by more than it is read (158 and 154 us in a training step of 2,000,000 rows; with a mask 305 and 323).
+constexpr int piece_blocks_per_cu(int kt, int nt, bool red, bool mask)
 {
-    return kt + nt <= 5 || (red && kt == 8 && (nt == 3 || nt == 4)) || (!red && kt == 1 && nt == 6) ? 2 : 1;
+    return kt + nt <= 5 || (kt >= 6 && nt == 4) || (kt == 8 && nt == 3 && (red || mask)) || (kt == 1 && nt == 6 && !red && !mask) ? 2 : 1;
 }
 
 // weight fragments of one layer: fragment (kt, nt), lane l, component s is
@@ -1139,7 +1140,7 @@ int pcsr_gnn_linear(int64_t n, int32_t a, int32_t b, const float *X, const float
     LinearFn fn = pick_linear_kn(kt, nt, exact ? 2 : vec, red);
     if (!fn) return PCSR_E_UNSUPPORTED;
     const int waves = exact ? piece_waves(kt, nt) : kWaves;
-    const long blocks = row_blocks(n, 256 * (exact ? piece_blocks_per_cu(kt, nt, red) : blocks_per_cu(kt, nt)), waves);
+    const long blocks = row_blocks(n, 256 * (exact ? piece_blocks_per_cu(kt, nt, red, mask != nullptr) : blocks_per_cu(kt, nt)), waves);
     LinearArgs p;
     p.n = n;
     p.a = a;
