@@ -28,22 +28,22 @@ HBM_PEAK_GBS = 8000.0
 # instance, or the same instance over another PCSR layout, reports null.
 PROFILED_TRAFFIC = {
     ("poisson-full", 32, "spmm_kernel<1, false, 8, 4, 1, false>", 0, "index"): 3519439,
-    ("road-full", 128, "spmm_kernel<2, false, 32, 4, 1, false>", 0, "index"): 2121935073,
-    ("rmat20-full", 64, "spmm_kernel<1, true, 16, 4, 1, false>", 64, "column"): 2174585919,
-    ("sbm-full", 256, "spmm_window_kernel<1, 16, 4, 1, false>", 0, "index"): 1879832989,
-    ("sbm_shuffled-full", 256, "spmm_window_kernel<1, 16, 4, 1, true>", 1024, "cluster"): 1957128174,
-    ("rmat22-full", 16, "spmm_kernel<1, true, 16, 1, 1, false>", 64, "column"): 7060422290,
-    ("rmat22-full", 32, "spmm_kernel<1, true, 8, 4, 1, false>", 64, "column"): 9984136412,
-    ("rmat22-full", 64, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 17939440492,
-    ("rmat22-full", 128, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 36093605165,
+    ("road-full", 128, "spmm_kernel<2, false, 32, 4, 1, false>", 0, "index"): 2121985865,
+    ("rmat20-full", 64, "spmm_kernel<1, true, 16, 4, 1, false>", 64, "column"): 2174954221,
+    ("sbm-full", 256, "spmm_window_kernel<1, 16, 4, 1, false>", 0, "index"): 1878325597,
+    ("sbm_shuffled-full", 256, "spmm_window_kernel<1, 16, 4, 1, true>", 1024, "cluster"): 1964254111,
+    ("rmat22-full", 16, "spmm_kernel<1, true, 16, 1, 1, false>", 64, "column"): 7028255102,
+    ("rmat22-full", 32, "spmm_kernel<1, true, 8, 4, 1, false>", 64, "column"): 9964128241,
+    ("rmat22-full", 64, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 17946603545,
+    ("rmat22-full", 128, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 36110849745,
     ("rmat22-full", 256, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 75169090801,
     ("rmat22-full", 512, "spmm_kernel<1, true, 16, 4, 1, false>", 32, "column"): 156284305416,
 }
 
 
 def kernel_instance(V: int, S: int, launch: dict) -> str:
-    """Name of the SpMM kernel instance as rocprofv3 prints it, less the last argument (which only handles with long
-    rows change: a form of the instance that adds up their sums in more steps, over the same traffic)."""
+    """Name of the SpMM kernel instance as rocprofv3 prints it, less the last two arguments (forms of the instance over the
+    same traffic: how the sums of long rows are added up, and whether the size of B allows offsets of 32 bits)."""
     shape = f"{launch['lanes_per_row']}, {launch['vec']}, {launch['rep']}"
     if launch["lds_bytes"]:
         return f"spmm_window_kernel<{V}, {shape}, {'true' if S else 'false'}>"  # true: windows of communities

@@ -467,7 +467,7 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), RED || piece_waves(K
 
 // Two layers in one pass: Z = relu(X W1^T + b1), Y = Z W2^T + b2 (relu).  Exact widths: a = 16 KT,
 // both layers 16 MT outputs.  Z is stored for the backward pass and not read back: 2,000,000 x 64
-// -> 64 -> 64 takes 310-330 us where two piece_kernel passes take 381.
+// -> 64 -> 64 takes 310-335 us where two piece_kernel passes take 370.
 struct MlpArgs {
     long n;
     int relu;
@@ -527,10 +527,10 @@ template <int KT, int MT> __global__ void __launch_bounds__(64 * kWaves, 3) mlp_
 // turned in an LDS patch of the wavefront's own: written as they are held, read T consecutive
 // columns of one row per lane, which feeds T tiles (tile t holds the columns T*i + t, as in
 // wgrad_kernel).  G, Z, A and H are read once and G1 never leaves the registers: 2.6 GB for
-// 2,000,000 x 64 (TWO) where the separate kernels move 5.6 GB, 545-590 us where they take 970 (660-700 with conditions
+// 2,000,000 x 64 (TWO) where the separate kernels move 5.6 GB, 550-595 us where they take 920 (650-700 with conditions
 // on loads and stores in the loop); what bounds it is the matrix rate (65.5 GFLOP,
-// 428 us) with two wavefronts to a SIMD, all that the accumulators leave room for.  Without TWO,
-// masked and with column sums, 390 us for 493.
+// 428 us; matrix cores 84 % busy) with two wavefronts to a SIMD, all that the accumulators leave room for.  Without TWO,
+// masked and with column sums, 317 us for 468.
 struct BackArgs {
     long n;
     int masked;
