@@ -7,12 +7,83 @@
 
 #include <hip/hip_runtime.h>
 #include <type_traits>
+#include <utility>
 
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// fp32 products on the bf16 matrix instructions, which do 16 times the work.  A float is the sum of three bf16 numbers, to the last
+// bit (8 of its 24 bits each), and a product of two floats that of the six products of their pieces that reach 2^-24 of it.
+// v_mfma_f32_16x16x32_bf16: lane l holds A[i = l%16][k = 8*(l/16) and on] and B likewise, eight numbers each; results as above.
+// The five smaller products are added up apart from the largest.  Against 64 bits, 2-norm of normal numbers: 0.50 / 0.65e-7 over 64 /
+// 128 of them, where the fp32 instructions are off by 1.44 / 2.03e-7.  One accumulator for all six is off by 0.93 / 1.53, but to one side: these
+// instructions cut off what does not reach the last bit of a sum, and sums of 200,000 such results were off 5 to 10 times as much as before.
+// They do 2420 TFLOP/s here for 150: 2.7 times the rate with six of them.
+// Rows with numbers of 2^60 and more, infinities among them, and all rows where a weight or a bias reaches 2^20 and 2^60, are left to the
+// fp32 instructions, in a loop of their own: an infinity has no pieces, and below that neither the products of two layers nor their pieces'
+// overflow.  Below 2^-110 the last piece runs out of exponent: off by 2^-134 at most.
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+struct Pieces {
+    u4 p[3]; // of eight floats
+};
+constexpr float kRowsBelow = 0x1p60f, kWeightsBelow = 0x1p20f;
+
+__device__ __forceinline__ unsigned bf16_pair(float a, float b)
+{
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    const f2 t = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(t, b2)); // to nearest
+}
+__device__ __forceinline__ float bf16_low(unsigned p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float bf16_high(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+__device__ __forceinline__ Pieces split(float (&x)[8])
+{
+    Pieces s;
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const unsigned t = bf16_pair(x[2 * i], x[2 * i + 1]);
+            s.p[p][i] = t;
+            if (p < 2) {
+                x[2 * i] -= bf16_low(t);
+                x[2 * i + 1] -= bf16_high(t);
+            }
+        }
+    return s;
+}
+// two fragments of fp32 products, side by side: k = 32 to 32 as long as both operands are put together so
+__device__ __forceinline__ Pieces split(const f4 &lo, const f4 &hi)
+{
+    float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return split(x);
+}
+__device__ __forceinline__ f4 mfma32(const u4 &a, const u4 &b, f4 c)
+{
+    typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
+}
+// acc[i] + low[i] += A[i] B; side by side, since an instruction that adds to the sum of the last one waits for it.
+template <int N> __device__ __forceinline__ void mfma_pieces(const Pieces (&a)[N], const Pieces &b, f4 *acc, f4 *low)
+{
+    constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+    for (int o = 0; o < 6; ++o)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            f4 &sum = o < 5 ? low[i] : acc[i];
+            sum = mfma32(a[i].p[order[o][0]], b.p[order[o][1]], sum);
+        }
+}
+// the largest magnitude so far; a NaN may be passed over: its pieces are NaN
+__device__ __forceinline__ void largest(float a, float b, float &most)
+{
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(a), "v"(b));
+}
 
 constexpr int kWaves = 4;
 constexpr int kLinearBlocks = 768; // three per compute unit
@@ -73,19 +144,154 @@ __device__ __forceinline__ void stage_weights(f4 *wfrag, const float *W, int a, 
     }
 }
 
-// acc += op(W) x for 16 rows
-template <int KT, int NT> __device__ __forceinline__ void multiply(const f4 *wfrag, int lane, const f4 (&x)[KT], f4 (&acc)[NT])
+// acc += op(W) x for 16 rows, outputs 16 N0 to 16 (N0 + NS)
+template <int KT, int NT, int N0 = 0, int NS = NT>
+__device__ __forceinline__ void multiply(const f4 *wfrag, int lane, const f4 (&x)[KT], f4 (&acc)[NS])
 {
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
-        f4 w[NT];
+        f4 w[NS];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) w[nt] = wfrag[(kt * NT + nt) * 64 + lane];
+        for (int nt = 0; nt < NS; ++nt) w[nt] = wfrag[(kt * NT + N0 + nt) * 64 + lane];
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma4(w[nt][s], x[kt][s], acc[nt]);
+            for (int nt = 0; nt < NS; ++nt) acc[nt] = mfma4(w[nt][s], x[kt][s], acc[nt]);
     }
+}
+
+// Where pieces are taken: where the matrix rate bounds a pass as much as memory does.  Elsewhere the work of splitting shows (us at 2,000,000
+// rows, fp32 products / pieces): 32 -> 32 92 / 113, 48 -> 64 157 / 174, 96 -> 16 162 / 178, 64 -> 64 alone 186 / 193; but 64 -> 128 333 / 315, 128 -> 64
+// 315 / 302, 96 -> 96 359 / 336, 96 -> 128 451 / 361, 128 -> 128 558 / 434 (200,000 rows 77 / 53); two layers 16 -> 64 -> 64 237 / 225, 64 -> 64 -> 64
+// 323 / 284 (200,000 rows 41 / 31) but 48 -> 48 -> 48 230 / 230; one layer backward 64 -> 64 327 / 300, 48 -> 48 226 / 226, 32 -> 32 151 / 156; two
+// layers backward 64 from 32 450 / 410, 48 from 48 387 / 389.  64 from 48 and 64 backward have no registers for it (spilled, 587 -> 616).
+constexpr bool split_piece(int kt, int nt) { return kt >= 4 && nt >= 4 && kt * nt > 16; }
+constexpr bool split_mlp(int mt) { return mt == 4; }
+constexpr bool split_back(int bt, int mt, int at, bool two) { return two ? mt == 4 && at <= 2 : bt * mt >= 12; }
+
+// acc += op(W) x for 16 rows, with W in LDS as `words` of 16 bytes.  SPLIT: in pieces, but for sixteen inputs, where six products take as long.
+constexpr std::true_type kInPieces{};
+constexpr std::false_type kAsTheyAre{};
+template <int KT, int NT, bool SPLIT> struct Product {
+    static constexpr bool kSplit = SPLIT && KT > 1;
+    static constexpr int kSteps = (KT + 1) / 2;
+    static constexpr int words = kSplit ? kSteps * NT * 3 * 64 : KT * NT * 64;
+    using Split = Pieces[kSteps];
+    const f4 *frag;
+    const float *W;
+    int transposed;
+
+    // Piece p of fragment (step, nt), lane l: W[out = 16 nt + l%16][in = 32 step + 16 (s/4) + 4 (l/16) + s%4], s < 8.  `most`: the
+    // largest magnitude that this thread has seen.
+    static __device__ __forceinline__ Product stage(f4 *frag, const float *W, int transposed, float &most)
+    {
+        constexpr int a = 16 * KT, b = 16 * NT;
+        if constexpr (!kSplit) {
+            stage_weights<KT, NT>(frag, W, a, b, transposed);
+            if (SPLIT) // for what follows
+                for (int i = threadIdx.x; i < a * b; i += blockDim.x) most = fmaxf(most, fabsf(W[i]));
+        } else {
+            for (int f = threadIdx.x; f < kSteps * NT * 64; f += blockDim.x) {
+                const int l = f & 63, t = f >> 6, k = t / NT, out = (t - k * NT) * 16 + (l & 15);
+                float w[8];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    const int in = 32 * k + 16 * (s >> 2) + 4 * (l >> 4) + (s & 3);
+                    w[s] = in < a ? (transposed ? W[(long)in * b + out] : W[(long)out * a + in]) : 0.0f;
+                }
+#pragma unroll
+                for (int s = 0; s < 8; s += 2) largest(w[s], w[s + 1], most);
+                const Pieces x = split(w);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) frag[(t * 3 + p) * 64 + l] = __builtin_bit_cast(f4, x.p[p]);
+            }
+        }
+        return {frag, W, transposed};
+    }
+
+    static __device__ __forceinline__ void split_rows(const f4 (&x)[KT], Split &s)
+    {
+        if constexpr (kSplit) {
+#pragma unroll
+            for (int k = 0; k < kSteps; ++k) s[k] = split(x[2 * k], 2 * k + 1 < KT ? x[2 * k + 1] : f4{0.0f, 0.0f, 0.0f, 0.0f});
+        }
+    }
+    // x[kt] without an index into registers
+    template <int... I> static __device__ __forceinline__ f4 pick(const f4 (&x)[KT], int kt, std::integer_sequence<int, I...>)
+    {
+        f4 t = x[0];
+        ((kt == I ? (void)(t = x[I]) : (void)0), ...);
+        return t;
+    }
+    // Outputs 16 N0 to 16 (N0 + NS).  kAsTheyAre: seldom, so with no registers of its own and no room in LDS.
+    template <int N0, int NS, class Form> __device__ __forceinline__ void add(Form, int lane, const f4 (&x)[KT], const Split &xs, f4 (&acc)[NS]) const
+    {
+        if constexpr (!kSplit) {
+            multiply<KT, NT, N0, NS>(frag, lane, x, acc);
+        } else if constexpr (Form::value) {
+            constexpr int S = NS % 2 == 0 ? 2 : 1;
+#pragma unroll
+            for (int nt = 0; nt < NS; nt += S) {
+                f4 low[S];
+#pragma unroll
+                for (int i = 0; i < S; ++i) low[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int k = 0; k < kSteps; ++k) {
+                    Pieces w[S];
+#pragma unroll
+                    for (int i = 0; i < S; ++i)
+#pragma unroll
+                        for (int p = 0; p < 3; ++p)
+                            w[i].p[p] = __builtin_bit_cast(u4, frag[((k * NT + N0 + nt + i) * 3 + p) * 64 + lane]);
+                    mfma_pieces<S>(w, xs[k], acc + nt, low);
+                }
+#pragma unroll
+                for (int i = 0; i < S; ++i) acc[nt + i] += low[i];
+            }
+        } else {
+#pragma unroll 1
+            for (int kt = 0; kt < KT; ++kt) {
+                const f4 xk = pick(x, kt, std::make_integer_sequence<int, KT>{});
+#pragma unroll
+                for (int nt = 0; nt < NS; ++nt) {
+                    const int out = (N0 + nt) * 16 + (lane & 15), in = kt * 16 + 4 * (lane >> 4);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        acc[nt] = mfma4(transposed ? W[(in + s) * (16 * NT) + out] : W[out * (16 * KT) + in + s], xk[s], acc[nt]);
+                    asm volatile("" ::: "memory");
+                }
+            }
+        }
+    }
+    template <class Form> __device__ __forceinline__ void add(Form form, int lane, const f4 (&x)[KT], f4 (&acc)[NT]) const
+    {
+        Split xs;
+        if constexpr (Form::value) split_rows(x, xs);
+        add<0, NT>(form, lane, x, xs, acc);
+    }
+};
+
+// whether all of this is small enough for pieces, in the whole wavefront
+template <int T> __device__ __forceinline__ bool small_rows(const f4 (&x)[T])
+{
+    float most = 0.0f;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        largest(x[t][0], x[t][1], most);
+        largest(x[t][2], x[t][3], most);
+    }
+    return __builtin_amdgcn_ballot_w64(!(most < kRowsBelow)) == 0;
+}
+// the same of the weights and a bias (null: none) for the workgroup; a barrier
+template <int N, bool SPLIT> __device__ __forceinline__ bool small_weights(float most, const f4 *bias)
+{
+    if (!SPLIT) {
+        __syncthreads();
+        return true;
+    }
+    float b = 0.0f;
+    for (int o = threadIdx.x; bias && o < N; o += blockDim.x) b = fmaxf(b, fabsf(reinterpret_cast<const float *>(bias)[o]));
+    return !__syncthreads_or(!(most < kWeightsBelow) || !(b < kRowsBelow));
 }
 
 // the bias waits in LDS: in registers it would cost what the row pieces need
@@ -128,24 +334,30 @@ __device__ __forceinline__ f4 *at_byte(float *base, unsigned off)
 {
     return reinterpret_cast<f4 *>(reinterpret_cast<char *>(base) + off);
 }
-template <int T> __device__ __forceinline__ void load_piece(const float *piece, int lane, long rows, f4 (&x)[T])
+// T: tiles of a row; S: of the part of it that is meant (from `piece` on), all of them or four
+template <int T, int S> __device__ __forceinline__ unsigned piece_byte(int lane) // plus 1 KB times T/S times u
 {
+    return T == S ? 16u * (unsigned)lane : 64u * T * ((unsigned)lane / (4 * S)) + 16u * ((unsigned)lane % (4 * S));
+}
+template <int T, int S> __device__ __forceinline__ void load_piece(const float *piece, int lane, long rows, f4 (&x)[S])
+{
+    static_assert(T == S || S == 4);
     if (rows >= 16) {
 #pragma unroll
-        for (int u = 0; u < T; ++u) x[u] = *at_byte(piece + u * 256, 16u * (unsigned)lane);
+        for (int u = 0; u < S; ++u) x[u] = *at_byte(piece + u * 256 * (T / S), piece_byte<T, S>(lane));
     } else { // zeros past the end
 #pragma unroll
-        for (int u = 0; u < T; ++u) {
+        for (int u = 0; u < S; ++u) {
             x[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            if ((u * 64 + lane) / (4 * T) < rows) x[u] = reinterpret_cast<const f4 *>(piece)[u * 64 + lane];
+            if ((u * 64 + lane) / (4 * S) < rows) x[u] = *at_byte(piece + u * 256 * (T / S), piece_byte<T, S>(lane));
         }
     }
 }
-template <int T> __device__ __forceinline__ void store_piece(float *piece, int lane, long rows, const f4 (&x)[T])
+template <int T, int S> __device__ __forceinline__ void store_piece(float *piece, int lane, long rows, const f4 (&x)[S])
 {
 #pragma unroll
-    for (int u = 0; u < T; ++u)
-        if (rows >= 16 || (u * 64 + lane) / (4 * T) < rows) *at_byte(piece + u * 256, 16u * (unsigned)lane) = x[u];
+    for (int u = 0; u < S; ++u)
+        if (rows >= 16 || (u * 64 + lane) / (4 * S) < rows) *at_byte(piece + u * 256 * (T / S), piece_byte<T, S>(lane)) = x[u];
 }
 // straight to the fragments
 template <int T> __device__ __forceinline__ void load_frags(const float *piece, int lane, long rows, f4 (&x)[T])
@@ -373,14 +585,17 @@ __device__ __forceinline__ void collect_dot(float *lds, float dot, float *out)
 template <int KT, int NT, bool RED>
 __global__ void __launch_bounds__(64 * piece_waves(KT, NT), RED || piece_waves(KT, NT) == 8 ? 2 : blocks_per_cu(KT, NT)) piece_kernel(LinearArgs p)
 {
-    constexpr int kW = piece_waves(KT, NT), kPatch = patch_floats(NT);
-    __shared__ f4 wfrag[KT * NT * 64], bias[NT * 4];
+    // Eight tiles of outputs in two halves: the patch of one leaves room for the weights' pieces.
+    constexpr int kW = piece_waves(KT, NT), kHalves = NT == 8 ? 2 : 1, NS = NT / kHalves, kPatch = patch_floats(NS);
+    using Weights = Product<KT, NT, split_piece(KT, NT)>;
+    __shared__ f4 wfrag[Weights::words], bias[NT * 4];
     __shared__ __align__(16) float patches[kW * kPatch];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float *patch = patches + wave * kPatch;
-    stage_weights<KT, NT>(wfrag, p.W, 16 * KT, 16 * NT, p.w_transposed);
     stage_bias<NT>(bias, p.bias, 16 * NT);
-    __syncthreads();
+    float most = 0.0f;
+    const auto W = Weights::stage(wfrag, p.W, p.w_transposed, most);
+    bool in_pieces = small_weights<0, Weights::kSplit>(most, nullptr);
 
     f4 csum[RED ? NT : 1], csums[RED ? NT : 1]; // sums of kSumRun groups are put apart
     float dot = 0.0f, dots = 0.0f;
@@ -404,45 +619,59 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), RED || piece_waves(K
     f4 xn[KT]; // the next rows are requested before this step's products
     auto load = [&](long g, auto rows) { load_frags<KT>(p.X + g * (256 * KT), lane, rows, xn); };
     // aux, mask, store: which of these arrays there are, as constants in the loops of the layers' own calls
-    auto step = [&](long g, auto rows, auto aux, auto mask, auto store, auto next) {
+    auto step = [&](auto form, long g, auto rows, auto aux, auto mask, auto store, auto next) {
         asm volatile("" ::: "memory"); // as in linear_kernel
-        f4 x[KT], y[NT];
+        f4 x[KT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) x[kt] = xn[kt];
         next();
-        f4 m[NT]; // aux, or the mask; callers have one of them
-        if (aux || mask) load_piece<NT>((aux ? p.aux : p.mask) + g * (256 * NT), lane, rows, m);
-        start_from<NT>(bias, lane, y);
-        multiply<KT, NT>(wfrag, lane, x, y);
-        if (p.relu) relu_rows<NT>(y);
-        if constexpr (RED) clear_past_end<NT>(lane, rows, y);
-        frags_to_piece<NT>(patch, lane, y);
-        if (aux) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                dot += (y[t][0] * m[t][0] + y[t][1] * m[t][1]) + (y[t][2] * m[t][2] + y[t][3] * m[t][3]);
-            if (mask) load_piece<NT>(p.mask + g * (256 * NT), lane, rows, m);
+        if (decltype(form)::value && Weights::kSplit && !small_rows(x)) { // asked for once the next rows have been
+            in_pieces = false;
+            return;
         }
-        if (mask) mask_rows<NT>(y, m);
-        if constexpr (RED) {
+        typename Weights::Split xs;
+        if constexpr (decltype(form)::value) Weights::split_rows(x, xs);
+        auto half = [&](auto h) {
+            constexpr int N0 = decltype(h)::value * NS;
+            f4 y[NS], m[NS]; // aux, or the mask; callers have one of them
+            if (aux || mask) load_piece<NT, NS>((aux ? p.aux : p.mask) + g * (256 * NT) + 16 * N0, lane, rows, m);
+            start_from<NS>(bias + 4 * N0, lane, y);
+            W.template add<N0, NS>(form, lane, x, xs, y);
+            if (p.relu) relu_rows<NS>(y);
+            if constexpr (RED) clear_past_end<NS>(lane, rows, y);
+            frags_to_piece<NS>(patch, lane, y);
+            if (aux) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) csum[t] += y[t];
-        }
-        if (store) store_piece<NT>(p.Y + g * (256 * NT), lane, rows, y);
+                for (int t = 0; t < NS; ++t)
+                    dot += (y[t][0] * m[t][0] + y[t][1] * m[t][1]) + (y[t][2] * m[t][2] + y[t][3] * m[t][3]);
+                if (mask) load_piece<NT, NS>(p.mask + g * (256 * NT) + 16 * N0, lane, rows, m);
+            }
+            if (mask) mask_rows<NS>(y, m);
+            if constexpr (RED) {
+#pragma unroll
+                for (int t = 0; t < NS; ++t) csum[N0 + t] += y[t];
+            }
+            if (store) store_piece<NT, NS>(p.Y + g * (256 * NT) + 16 * N0, lane, rows, y);
+        };
+        half(std::integral_constant<int, 0>{});
+        if constexpr (kHalves == 2) half(std::integral_constant<int, 1>{});
         if constexpr (RED)
             if (++run == kSumRun) put_apart();
     };
     auto walk = [&](auto aux, auto mask, auto store) {
         if (g < full) load(g, kWhole);
-        for (; g < full; g += stride)
-            step(g, kWhole, aux, mask, store, [&] {
+        for (; g < full; g += stride) {
+            step(kInPieces, g, kWhole, aux, mask, store, [&] {
                 if (g + stride < full) load(g + stride, kWhole);
             });
+            if (Weights::kSplit && !in_pieces) break;
+        }
     };
     const std::true_type yes;
     const std::false_type no;
     const bool aux = RED && p.aux, mask = p.mask, store = p.Y;
-    if constexpr (RED) {
+    if (!in_pieces) {
+    } else if constexpr (RED) {
         if (aux && !mask && store)
             walk(yes, no, yes);
         else if (!aux && mask && store)
@@ -454,13 +683,29 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), RED || piece_waves(K
     } else {
         walk(no, no, yes);
     }
-    if (const long rows = p.n - g * 16; rows > 0) { // the rows that are left over
+    if (const long rows = p.n - g * 16; rows > 0 && in_pieces) { // the rows that are left over
         load(g, rows);
-        step(g, rows, aux, mask, store, [] {});
+        step(kInPieces, g, rows, aux, mask, store, [] {});
+    }
+    if constexpr (Weights::kSplit) {
+        for (; !in_pieces && g * 16 < p.n; g += stride) {
+            load(g, p.n - g * 16);
+            step(kAsTheyAre, g, p.n - g * 16, aux, mask, store, [] {});
+        }
     }
     if constexpr (RED) {
         put_apart();
-        if (p.ws_colsum) collect_colsum<NT, false>(patches, csums, p.ws_colsum + (long)blockIdx.x * (16 * NT));
+        if (p.ws_colsum) {
+            float *out = p.ws_colsum + (long)blockIdx.x * (16 * NT);
+            static_assert(kPatch >= NS * 256, "collect_colsum's words in the patches");
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h) {
+                f4 sums[NS];
+#pragma unroll
+                for (int t = 0; t < NS; ++t) sums[t] = csums[h * NS + t];
+                collect_colsum<NS, false>(patches, sums, out + h * (16 * NS));
+            }
+        }
         if (p.ws_dot) collect_dot(patches, dots, p.ws_dot + blockIdx.x);
     }
 }
@@ -474,47 +719,62 @@ struct MlpArgs {
     const float *X, *W1, *b1, *W2, *b2;
     float *Z, *Y;
 };
-template <int KT, int MT> __global__ void __launch_bounds__(64 * kWaves, 3) mlp_kernel(MlpArgs p)
+constexpr int mlp_blocks_per_cu(int kt, int mt) { return kt + mt > 5 && split_mlp(mt) ? 2 : 3; }
+template <int KT, int MT> __global__ void __launch_bounds__(64 * kWaves, mlp_blocks_per_cu(KT, MT)) mlp_kernel(MlpArgs p)
 {
     constexpr int kPatch = patch_floats(MT);
-    __shared__ f4 w1[KT * MT * 64], w2[MT * MT * 64], bias1[MT * 4], bias2[MT * 4];
+    __shared__ f4 w1[Product<KT, MT, split_mlp(MT)>::words], w2[Product<MT, MT, split_mlp(MT)>::words], bias1[MT * 4], bias2[MT * 4];
     __shared__ __align__(16) float patches[kWaves * kPatch];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *patch = patches + wave * kPatch;
-    stage_weights<KT, MT>(w1, p.W1, 16 * KT, 16 * MT, 0);
-    stage_weights<MT, MT>(w2, p.W2, 16 * MT, 16 * MT, 0);
     stage_bias<MT>(bias1, p.b1, 16 * MT);
     stage_bias<MT>(bias2, p.b2, 16 * MT);
-    __syncthreads();
+    float most = 0.0f;
+    const auto W1 = Product<KT, MT, split_mlp(MT)>::stage(w1, p.W1, 0, most);
+    const auto W2 = Product<MT, MT, split_mlp(MT)>::stage(w2, p.W2, 0, most);
+    constexpr bool kSplit = split_mlp(MT);
+    bool in_pieces = small_weights<16 * MT, kSplit>(most, bias1);
     const long full = p.n >> 4, stride = (long)gridDim.x * kWaves;
     long g = (long)blockIdx.x * kWaves + wave;
     f4 xn[KT];
     auto load = [&](long g, auto rows) { load_frags<KT>(p.X + g * (256 * KT), lane, rows, xn); };
-    auto step = [&](long g, auto rows, auto next) {
+    auto step = [&](auto form, long g, auto rows, auto next) {
         asm volatile("" ::: "memory"); // as in linear_kernel
         f4 x[KT], z[MT], y[MT];
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt) x[kt] = xn[kt];
         next();
+        if (decltype(form)::value && kSplit && !small_rows(x)) { // as in piece_kernel
+            in_pieces = false;
+            return;
+        }
         start_from<MT>(bias1, lane, z);
-        multiply<KT, MT>(w1, lane, x, z);
+        W1.add(form, lane, x, z);
         relu_rows<MT>(z);
         start_from<MT>(bias2, lane, y);
-        multiply<MT, MT>(w2, lane, z, y);
+        W2.add(form, lane, z, y);
         if (p.relu) relu_rows<MT>(y);
         frags_to_piece<MT>(patch, lane, z);
-        store_piece<MT>(p.Z + g * (256 * MT), lane, rows, z);
+        store_piece<MT, MT>(p.Z + g * (256 * MT), lane, rows, z);
         frags_to_piece<MT>(patch, lane, y);
-        store_piece<MT>(p.Y + g * (256 * MT), lane, rows, y);
+        store_piece<MT, MT>(p.Y + g * (256 * MT), lane, rows, y);
     };
-    if (g < full) load(g, kWhole);
-    for (; g < full; g += stride)
-        step(g, kWhole, [&] {
+    if (g < full && in_pieces) load(g, kWhole);
+    for (; g < full && in_pieces; g += stride) {
+        step(kInPieces, g, kWhole, [&] {
             if (g + stride < full) load(g + stride, kWhole);
         });
-    if (const long rows = p.n - g * 16; rows > 0) { // the rows that are left over
+        if (kSplit && !in_pieces) break;
+    }
+    if (const long rows = p.n - g * 16; rows > 0 && in_pieces) { // the rows that are left over
         load(g, rows);
-        step(g, rows, [] {});
+        step(kInPieces, g, rows, [] {});
+    }
+    if constexpr (kSplit) {
+        for (; !in_pieces && g * 16 < p.n; g += stride) {
+            load(g, p.n - g * 16);
+            step(kAsTheyAre, g, p.n - g * 16, [] {});
+        }
     }
 }
 
@@ -611,14 +871,19 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
     constexpr int kPatch = kPatch1 > kPatch2 ? kPatch1 : kPatch2;
     constexpr int kRed1 = BT * 16 * (MT * 16 + 1) + BT * 16, kRed2 = TWO ? MT * 16 * (AT * 16 + 1) + MT * 16 : 0;
     constexpr int kRed = kRed1 > kRed2 ? kRed1 : kRed2;
-    __shared__ f4 w2[BT * MT * 64];
-    __shared__ f4 w1[TWO ? MT * AT * 64 : 1];
+    constexpr bool kSplit = split_back(BT, MT, AT, TWO);
+    __shared__ f4 w2[Product<BT, MT, kSplit>::words];
+    __shared__ f4 w1[TWO ? Product<MT, AT, kSplit>::words : 1];
     __shared__ __align__(16) float lds[kWaves * kPatch > kRed ? kWaves * kPatch : kRed];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float *patch = lds + wave * kPatch;
-    stage_weights<BT, MT>(w2, p.W2, 16 * BT, 16 * MT, 1);
-    if constexpr (TWO) stage_weights<MT, AT>(w1, p.W1, 16 * MT, 16 * AT, 1);
-    __syncthreads();
+    float most = 0.0f;
+    const auto W2 = Product<BT, MT, kSplit>::stage(w2, p.W2, 1, most);
+    const auto W1 = [&] {
+        if constexpr (TWO) return Product<MT, AT, kSplit>::stage(w1, p.W1, 1, most);
+        else return 0;
+    }();
+    bool in_pieces = small_weights<0, kSplit>(most, nullptr);
 
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     f4 acc2[BT][MT], acc1[TWO ? MT : 1][TWO ? AT : 1], csum[MT];
@@ -648,18 +913,18 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
     auto load_g = [&](long g, auto rows) { load_frags<BT>(p.G + g * (256 * BT), lane, rows, gg); };
     auto load_z = [&](long g, auto rows) { load_frags<MT>(p.Z + g * (256 * MT), lane, rows, zz); };
     auto load_a = [&](long g, auto rows) {
-        if constexpr (TWO) load_piece<AT>(p.A + g * (256 * AT), lane, rows, aa);
+        if constexpr (TWO) load_piece<AT, AT>(p.A + g * (256 * AT), lane, rows, aa);
     };
     // the next rows of G, Z and A go into the same registers once these are in the patch and used;
     // the products that follow cover the wait
-    auto step = [&](long g, auto rows, auto next_g, auto next_z, auto next_a) {
+    auto step = [&](auto form, long g, auto rows, auto next_g, auto next_z, auto next_a) {
         f4 g1[MT];
         patch_fence();
         frags_to_patch<BT, LG>(patch, lane, gg);
         frags_to_patch<MT, LZ>(patch + 16 * LG, lane, zz);
 #pragma unroll
         for (int t = 0; t < MT; ++t) g1[t] = zero;
-        multiply<BT, MT>(w2, lane, gg, g1);
+        W2.add(form, lane, gg, g1);
         if (TWO || p.masked) mask_rows<MT>(g1, zz);
         patch_fence(); // keeps weight fragments and patches in LDS, and what follows below
         if constexpr (!TWO) {
@@ -682,7 +947,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
             f4 da[AT];
 #pragma unroll
             for (int t = 0; t < AT; ++t) da[t] = zero;
-            multiply<MT, AT>(w1, lane, g1, da);
+            W1.add(form, lane, g1, da);
             if (p.H && (rows >= 16 || (lane & 15) < rows)) {
 #pragma unroll
                 for (int t = 0; t < AT; ++t)
@@ -695,20 +960,34 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
             turned_product<MT, AT>(patch, lane, acc1, sum1);
         }
     };
-    if (g < full) {
+    if (g < full && in_pieces) {
         load_g(g, kWhole);
         load_z(g, kWhole);
         load_a(g, kWhole);
     }
-    for (; g < full; g += stride) {
+    for (; g < full && in_pieces; g += stride) {
+        if (kSplit && !small_rows(gg)) {
+            in_pieces = false;
+            break;
+        }
         const long after = g + stride < full ? g + stride : g;
-        step(g, kWhole, [&] { load_g(after, kWhole); }, [&] { load_z(after, kWhole); }, [&] { load_a(after, kWhole); });
+        step(kInPieces, g, kWhole, [&] { load_g(after, kWhole); }, [&] { load_z(after, kWhole); }, [&] { load_a(after, kWhole); });
     }
-    if (const long rows = p.n - g * 16; rows > 0) { // the rows that are left over
+    auto load_all = [&](long g, auto rows) {
         load_g(g, rows);
         load_z(g, rows);
         load_a(g, rows);
-        step(g, rows, [] {}, [] {}, [] {});
+    };
+    if (const long rows = p.n - g * 16; rows > 0 && in_pieces) { // the rows that are left over
+        load_all(g, rows);
+        in_pieces = !kSplit || small_rows(gg);
+        if (in_pieces) step(kInPieces, g, rows, [] {}, [] {}, [] {});
+    }
+    if constexpr (kSplit) {
+        for (; !in_pieces && g * 16 < p.n; g += stride) {
+            load_all(g, p.n - g * 16);
+            step(kAsTheyAre, g, p.n - g * 16, [] {}, [] {}, [] {});
+        }
     }
 
     float *ws = p.ws + (long)blockIdx.x * p.ws_stride;
@@ -1170,7 +1449,7 @@ int pcsr_gnn_mlp(int64_t n, int32_t a, int32_t m, const float *X, const float *W
     if (!kt || !mt || !aligned16(X) || !aligned16(Z) || !aligned16(Y)) return PCSR_E_UNSUPPORTED;
     MlpFn fn = kt == 1 ? pick_mlp_m<1>(mt) : kt == 2 ? pick_mlp_m<2>(mt) : kt == 3 ? pick_mlp_m<3>(mt) : pick_mlp_m<4>(mt);
     const MlpArgs p = {(long)n, relu, X, W1, b1, W2, b2, Z, Y};
-    hipLaunchKernelGGL(fn, dim3((unsigned)row_blocks(n, 768)), dim3(64 * kWaves), 0, static_cast<hipStream_t>(stream), p);
+    hipLaunchKernelGGL(fn, dim3((unsigned)row_blocks(n, 256 * mlp_blocks_per_cu(kt, mt))), dim3(64 * kWaves), 0, static_cast<hipStream_t>(stream), p);
     return to_code(hipGetLastError());
 }
 

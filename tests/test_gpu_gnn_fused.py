@@ -193,6 +193,61 @@ def test_sums_over_rows_with_an_infinite_weight(n):
     assert bool(torch.isinf(dA[:, 5]).all()) and bool(torch.isinf(dot))
 
 
+def _matches(got, ref, size, terms):
+    """Infinite and no number where ref is; elsewhere within the bound of a chain of so many fp32 sums, one rounding each."""
+    got, ref = got.double(), torch.where(ref.abs() > 3.4028235e38, ref * float("inf"), ref)
+    finite = torch.isfinite(ref)
+    assert bool((torch.isnan(got) == torch.isnan(ref)).all()) and bool((torch.isinf(got) == torch.isinf(ref)).all())
+    assert bool((got == ref)[torch.isinf(ref)].all())
+    assert bool(((got - ref).abs() <= terms * 2.0 ** -24 * size + 1e-30)[finite].all())
+
+
+# products in pieces: rows, weights and biases that have no pieces (from 2^60 and 2^20 on, and infinities), in the first rows, among those of
+# a loop that has begun, in a group that is not whole.  One number of a product may be all of its size, so that every sum after it is
+# rounded at that size: the bound is that of the whole chain, of as many terms as the product has and, for sums over rows, as a wavefront has
+# rows (40009 / 2048 groups of 16, or steps of 16 rows in four parts) and a column has partial sums (512, 16 of them in a chain).
+@pytest.mark.parametrize("a,b", [(16, 64), (32, 64), (64, 64), (48, 64), (64, 96), (96, 96), (64, 128), (128, 128)])
+@pytest.mark.parametrize("n,row", [(5, 0), (40009, 39000), (40009, 40008)])
+@pytest.mark.parametrize("value,where", [(float("inf"), "row"), (-3e30, "row"), (2.0 ** 60, "row"), (float("inf"), "weight"),
+                                         (2.0 ** 20, "weight"), (1e30, "weight"), (float("inf"), "bias"), (1e30, "bias")])
+def test_numbers_without_pieces(a, b, n, row, value, where):
+    g = torch.Generator(device="cuda").manual_seed(a * 100 + b)
+    X, H = (torch.randn(n, a, generator=g, device="cuda") for _ in range(2))
+    G = torch.randn(n, b, generator=g, device="cuda")
+    W1, W2 = torch.randn(b, a, generator=g, device="cuda"), torch.randn(b, b, generator=g, device="cuda")
+    b1, b2 = torch.randn(b, generator=g, device="cuda"), torch.randn(b, generator=g, device="cuda")
+    if where == "row":
+        X[row, 7] = value
+        G[row, 9] = value
+    elif where == "weight":
+        W1[5, 3] = value
+    else:
+        b1[5] = value
+    d = _dense(a, b)
+    d.ws_floats = max(d.ws_floats, d.lib.pcsr_gnn_workspace_floats(b, b))
+    Xd, Gd, Hd, W1d, W2d, b1d, b2d = (t.double() for t in (X, G, H, W1, W2, b1, b2))
+    size1 = Xd.abs() @ W1d.abs().t() + b1d.abs()
+    _matches(d.linear(X, W1, bias=b1, relu=True), torch.relu(Xd @ W1d.t() + b1d), size1, a + 2)
+    cs = torch.empty(a, device="cuda")
+    back, size = Gd @ W1d, Gd.abs() @ W1d.abs()
+    _matches(d.linear(G, W1, transposed=True, colsum=cs), back, size, b + 2)
+    _matches(cs, back.sum(0), size.sum(0), b + 400)
+    Z, Y = d.mlp(X, W1, b1, W2, b2, True)
+    _matches(Z, torch.relu(Xd @ W1d.t() + b1d), size1, a + 2)
+    _matches(Y, torch.relu(Z.double() @ W2d.t() + b2d), Z.double().abs() @ W2d.abs().t() + b2d.abs(), b + 2)
+    dX, dW, db = d.linear_backward(G, X, W1, bias=True, colsum=cs)
+    _matches(dX, back, size, b + 2)
+    _matches(dW, Gd.t() @ Xd, Gd.abs().t() @ Xd.abs(), 400)
+    Z = torch.relu(torch.randn(n, b, generator=g, device="cuda"))
+    dA, dot, dW1, db1, dW2, db2 = d.mlp_backward(G, Z, X, H, W1, W2, True)
+    G1 = torch.where(Z > 0, Gd @ W2d, 0.0)
+    size2 = torch.where(Z > 0, Gd.abs() @ W2d.abs(), 0.0)
+    _matches(dA, G1 @ W1d, size2 @ W1d.abs(), 2 * b + 4)
+    _matches(dW1, G1.t() @ Xd, size2.t() @ Xd.abs(), b + 400)
+    _matches(dW2, Gd.t() @ Z.double(), Gd.abs().t() @ Z.double(), 400)
+    _matches(db1, G1.sum(0), size2.sum(0), b + 400)
+
+
 @pytest.mark.parametrize("name,kw", [("rmat20", dict(V=1, S=1, SG=4)), ("rmat20", dict(V=2, S=0)),
                                      ("sbm", dict(V=1, col_window=512)), ("road", dict(V=2, items_per_group=2)),
                                      ("rmat22", dict(V=2, S=1, SG=2))])
