@@ -34,13 +34,17 @@ struct DeviceBuild {
 // values: the call then leaves that to the caller (vals_due); else it waits.
 // d_rowptr / d_colidx / d_vals are device pointers.  Returns PCSR_OK or a PCSR_E_* code;
 // on PCSR_E_HIP *hip_err holds the hipError_t.  Synchronous.
+// known: what the check counts, of arrays that have been checked (null: they are checked if `validate`, and counted).
 // clusters: where the rows turn out to form communities, S = 1 with items of kClusterItem and the schedule by community;
 // windows: and, where they fit in LDS, out->win beside it.
 constexpr int32_t kClusterItem = 1024;
+struct RowStats {
+    int64_t longest, nonempty;
+};
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
-                 int32_t omega, bool validate, bool column_order, bool clusters, bool windows, Upload *late, DeviceBuild *out,
-                 int *hip_err);
+                 int32_t omega, bool validate, bool column_order, bool clusters, bool windows, const RowStats *known, Late *late,
+                 DeviceBuild *out, int *hip_err);
 
 // Whether rows share more columns than chance has them: enqueues the count of a sample on the null stream (d_out: two
 // sums, zeros on entry), and what the sums say.  The arrays need not have been checked.
@@ -59,6 +63,9 @@ hipError_t cluster_keys(int64_t n, const int32_t *d_labels, int64_t n_items, con
 // vectors partitioned.  Nothing where too few vectors lie inside the blocks.  Synchronous.
 int cluster_windows(int64_t n, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx, const float *d_vals,
                     const int32_t *d_labels, DeviceBuild *out, int *hip_err);
+
+// Enqueues: `words` words from device memory to pinned host memory, then seq to *flag there.
+hipError_t deliver(void *to, const void *from, int words, unsigned *flag, unsigned seq, hipStream_t stream);
 
 // The check build_device makes, alone: PCSR_OK or PCSR_E_BAD_CSR (or HIP, OOM).  Synchronous.
 int validate_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
@@ -81,6 +88,9 @@ int windows_device(int64_t M, int64_t n_cols, int32_t win, const int32_t *d_rowp
 
 // CSR of the transpose from CSR arrays in device memory, as pcsr_transpose_csr gives it; the
 // outputs (n_cols + 1, nnz, nnz) are allocated here, ownership passes to the caller.  Synchronous.
+// d_vals null (only where transpose_in_two_passes says so): *t_vals gets the bits of the place that each value has in the
+// array to come, and turned_values puts the values there, in the same place.
+hipError_t turned_values(int64_t nnz, const float *d_vals, float *t_vals); // enqueued on setup_stream()
 int transpose_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
                      const float *d_vals, int32_t **t_rowptr, int32_t **t_colidx, float **t_vals, int *hip_err);
 

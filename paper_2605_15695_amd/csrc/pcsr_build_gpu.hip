@@ -742,15 +742,23 @@ __global__ void __launch_bounds__(kThreads) features_final_kernel(int64_t nnz, c
         *out = {r.n_hat, nnz - r.shared, r.nonempty2, d.M1, d.M2, r.near, r.bw_sum, r.bw_max, d.ss, d.ss_hat, r.d_max, 0};
 }
 
+__global__ void __launch_bounds__(64) deliver_kernel(unsigned *to, const unsigned *from, int words, unsigned *flag, unsigned seq)
+{
+    for (int i = threadIdx.x; i < words; i += 64) to[i] = from[i];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 hipError_t exclusive_scan(const int32_t *in, int32_t *out, int64_t n, Scratch &sc)
 {
     size_t bytes = 0;
-    hipError_t e = hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, (int)n);
+    hipError_t e = hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, (int)n, setup_stream());
     if (e != hipSuccess) return e;
     void *tmp = nullptr;
     e = sc.alloc(&tmp, bytes);
     if (e != hipSuccess) return e;
-    return hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, (int)n);
+    return hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, (int)n, setup_stream());
 }
 
 // The check of the CSR, and its columns and values copied to pcol / pval where these are given.
@@ -763,18 +771,18 @@ int check_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
     const int64_t n_slices = (nnz + kSlice - 1) / kSlice;
     HIP_TRY(sc.alloc((void **)&d, sizeof(Checked)));
     HIP_TRY(sc.alloc((void **)&slices, sizeof(int32_t) * (n_slices + 1)));
-    HIP_TRY(hipMemsetAsync(d, 0, sizeof(Checked), nullptr));
+    HIP_TRY(hipMemsetAsync(d, 0, sizeof(Checked), setup_stream()));
     const int64_t row_blocks = (n_rows + kRowThreads - 1) / kRowThreads;
     hipLaunchKernelGGL(check_rows_kernel, dim3((unsigned)(row_blocks < 1 ? 1 : (row_blocks > kRowBlocks ? kRowBlocks : row_blocks))),
-                       dim3(kRowThreads), 0, 0, n_rows, nnz, d_rowptr, slices, d);
+                       dim3(kRowThreads), 0, setup_stream(), n_rows, nnz, d_rowptr, slices, d);
     HIP_TRY(hipGetLastError());
     if (nnz > 0 && n_rows > 0 && (validate || pcol)) {
-        hipLaunchKernelGGL(check_copy_kernel, dim3((unsigned)n_slices), dim3(kThreads), 0, 0, n_rows, n_cols, nnz, d_rowptr,
+        hipLaunchKernelGGL(check_copy_kernel, dim3((unsigned)n_slices), dim3(kThreads), 0, setup_stream(), n_rows, n_cols, nnz, d_rowptr,
                            d_colidx, d_vals, slices, validate ? 1 : 0, pcol, pval, d);
         HIP_TRY(hipGetLastError());
     }
     if (probe) HIP_TRY(cluster_probe(n_rows, nnz, d_rowptr, d_colidx, d->common));
-    HIP_TRY(hipMemcpy(h, d, sizeof(Checked), hipMemcpyDeviceToHost));
+    HIP_TRY(setup_copy(h, d, sizeof(Checked), hipMemcpyDeviceToHost));
     *d_out = d;
     if (h->first != 0 || h->last != nnz) return PCSR_E_BAD_CSR;
     if (validate && h->bad) return PCSR_E_BAD_CSR;
@@ -782,6 +790,13 @@ int check_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
 }
 
 } // namespace
+
+hipError_t deliver(void *to, const void *from, int words, unsigned *flag, unsigned seq, hipStream_t stream)
+{
+    hipLaunchKernelGGL(deliver_kernel, dim3(1), dim3(64), 0, stream, static_cast<unsigned *>(to),
+                       static_cast<const unsigned *>(from), words, flag, seq);
+    return hipGetLastError();
+}
 
 int validate_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx,
                     int *hip_err)
@@ -798,7 +813,7 @@ struct LabelsGuard { // what cluster_rows made, given back on scope exit
     ~LabelsGuard()
     {
         if (!p) return;
-        (void)hipStreamSynchronize(nullptr);
+        (void)setup_wait();
         pool_free(p);
     }
 };
@@ -806,8 +821,8 @@ struct LabelsGuard { // what cluster_rows made, given back on scope exit
 
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
-                 int32_t omega, bool validate, bool column_order, bool clusters, bool windows, Upload *late, DeviceBuild *out,
-                 int *hip_err)
+                 int32_t omega, bool validate, bool column_order, bool clusters, bool windows, const RowStats *known, Late *late,
+                 DeviceBuild *out,                 int *hip_err)
 {
     if (V != 1 && V != 2) return PCSR_E_UNSUPPORTED;
     if (omega == 0) omega = 64;
@@ -823,11 +838,22 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
         HIP_TRY(sc.alloc((void **)&pcol, sizeof(int32_t) * (nnz + 1)));
         HIP_TRY(sc.alloc((void **)&pval, sizeof(float) * (nnz + 1)));
     }
-    Checked *d_check = nullptr, check;
+    Checked *d_check = nullptr, check = {};
     clusters = clusters && V == 1 && n_rows == n_cols && nnz > 0;
-    int rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, late ? nullptr : d_vals, validate, clusters, pcol, pval, sc,
+    int rc = PCSR_OK;
+    if (known && !clusters) {
+        check.longest = (int)known->longest;
+        check.nonempty = (int)known->nonempty;
+        HIP_TRY(sc.alloc((void **)&d_check, sizeof(Checked)));
+        if (pcol && nnz > 0)
+            HIP_TRY(hipMemcpyAsync(pcol, d_colidx, sizeof(int32_t) * nnz, hipMemcpyDeviceToDevice, setup_stream()));
+        if (pval && !late && nnz > 0)
+            HIP_TRY(hipMemcpyAsync(pval, d_vals, sizeof(float) * nnz, hipMemcpyDeviceToDevice, setup_stream()));
+    } else {
+        rc = check_device(n_rows, n_cols, nnz, d_rowptr, d_colidx, late ? nullptr : d_vals, validate, clusters, pcol, pval, sc,
                           &d_check, &check, hip_err);
-    if (rc != PCSR_OK) return rc;
+        if (rc != PCSR_OK) return rc;
+    }
     LabelsGuard labels;
     double label_size = 0.0;
     if (clusters && cluster_probe_says(check.common, n_rows)) {
@@ -850,7 +876,7 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
     if (V == 1) {
         if (!S) {
             HIP_TRY(sc.alloc((void **)&prow, sizeof(int32_t) * (P + 1)));
-            HIP_TRY(hipMemcpyAsync(prow, d_rowptr, sizeof(int32_t) * (n_rows + 1), hipMemcpyDeviceToDevice, nullptr));
+            HIP_TRY(hipMemcpyAsync(prow, d_rowptr, sizeof(int32_t) * (n_rows + 1), hipMemcpyDeviceToDevice, setup_stream()));
             panels = prow;
         }
     } else {
@@ -862,26 +888,26 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
         HIP_TRY(sc.alloc((void **)&shared, sizeof(int32_t) * (nnz + 1)));
         HIP_TRY(sc.alloc((void **)&shared_scan, sizeof(int32_t) * (nnz + 1)));
         const unsigned slices = (unsigned)((nnz + 1 + kSlice - 1) / kSlice);
-        hipLaunchKernelGGL(union_shared_kernel, dim3(slices), dim3(kThreads), 0, 0, n_rows, nnz, d_rowptr, d_colidx,
+        hipLaunchKernelGGL(union_shared_kernel, dim3(slices), dim3(kThreads), 0, setup_stream(), n_rows, nnz, d_rowptr, d_colidx,
                            shared);
         HIP_TRY(hipGetLastError());
         HIP_TRY(exclusive_scan(shared, shared_scan, nnz + 1, sc));
-        hipLaunchKernelGGL(union_count_kernel, dim3(blocks_for(P + 1)), dim3(kThreads), 0, 0, P, n_rows,
+        hipLaunchKernelGGL(union_count_kernel, dim3(blocks_for(P + 1)), dim3(kThreads), 0, setup_stream(), P, n_rows,
                            d_rowptr, shared_scan, cnt);
         HIP_TRY(hipGetLastError());
         HIP_TRY(exclusive_scan(cnt, prow, P + 1, sc));
-        HIP_TRY(hipMemsetAsync(d_check, 0, sizeof(Checked), nullptr));
-        hipLaunchKernelGGL(panel_stats_kernel, dim3(strided_blocks(P, 1024)), dim3(kThreads), 0, 0, P, prow, d_check);
+        HIP_TRY(hipMemsetAsync(d_check, 0, sizeof(Checked), setup_stream()));
+        hipLaunchKernelGGL(panel_stats_kernel, dim3(strided_blocks(P, 1024)), dim3(kThreads), 0, setup_stream(), P, prow, d_check);
         HIP_TRY(hipGetLastError());
         int32_t total = 0;
-        HIP_TRY(hipMemcpyAsync(&total, prow + P, sizeof(int32_t), hipMemcpyDeviceToHost, nullptr));
-        HIP_TRY(hipMemcpy(&check, d_check, sizeof(Checked), hipMemcpyDeviceToHost));
+        HIP_TRY(setup_copy(&total, prow + P, sizeof(int32_t), hipMemcpyDeviceToHost));
+        HIP_TRY(setup_copy(&check, d_check, sizeof(Checked), hipMemcpyDeviceToHost));
         nnz_v = total;
         HIP_TRY(sc.alloc((void **)&pcol, sizeof(int32_t) * (nnz_v + 1)));
         HIP_TRY(sc.alloc((void **)&pval, sizeof(float) * (2 * nnz_v + 1)));
         if (late) HIP_TRY(late->wait());
         if (nnz > 0) {
-            hipLaunchKernelGGL(union_fill_kernel, dim3((unsigned)((nnz + kSlice - 1) / kSlice)), dim3(kThreads), 0, 0,
+            hipLaunchKernelGGL(union_fill_kernel, dim3((unsigned)((nnz + kSlice - 1) / kSlice)), dim3(kThreads), 0, setup_stream(),
                                n_rows, nnz, d_rowptr, d_colidx, d_vals, shared_scan, prow, pcol, pval);
             HIP_TRY(hipGetLastError());
         }
@@ -905,21 +931,21 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
     if (!S) {
         out->M = P;
         out->max_item_len = check.longest;
-        hipLaunchKernelGGL(xcd_bounds_kernel, dim3(1), dim3(64), 0, 0, (int32_t)P, prow, d_bounds);
+        hipLaunchKernelGGL(xcd_bounds_kernel, dim3(1), dim3(64), 0, setup_stream(), (int32_t)P, prow, d_bounds);
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpy(out->xcd_bounds, d_bounds, 9 * sizeof(int32_t), hipMemcpyDeviceToHost));
+        HIP_TRY(setup_copy(out->xcd_bounds, d_bounds, 9 * sizeof(int32_t), hipMemcpyDeviceToHost));
     } else {
         if (P + nnz_v / sg >= (int64_t(1) << 31) - 2) return PCSR_E_TOO_LARGE;
         const int64_t chunks = (P + kSplitPanels - 1) / kSplitPanels;
         SplitCount *sums = nullptr, total = {0, 0, 0, 0};
         HIP_TRY(sc.alloc((void **)&sums, sizeof(SplitCount) * (chunks + 1)));
         if (P > 0) {
-            hipLaunchKernelGGL(split_sums_kernel, dim3((unsigned)chunks), dim3(kThreads), 0, 0, P, panels, (int32_t)sg,
+            hipLaunchKernelGGL(split_sums_kernel, dim3((unsigned)chunks), dim3(kThreads), 0, setup_stream(), P, panels, (int32_t)sg,
                                sums);
             HIP_TRY(hipGetLastError());
-            hipLaunchKernelGGL(split_scan_kernel, dim3(1), dim3(1024), 0, 0, (int)chunks, sums);
+            hipLaunchKernelGGL(split_scan_kernel, dim3(1), dim3(1024), 0, setup_stream(), (int)chunks, sums);
             HIP_TRY(hipGetLastError());
-            HIP_TRY(hipMemcpy(&total, sums + chunks, sizeof(total), hipMemcpyDeviceToHost));
+            HIP_TRY(setup_copy(&total, sums + chunks, sizeof(total), hipMemcpyDeviceToHost));
         }
         const int64_t M = total.items, n_long = total.slots, n_short = M - n_long;
         SplitOut o = {};
@@ -935,12 +961,12 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
             HIP_TRY(sc.alloc((void **)&o.short_item, sizeof(int32_t) * (n_short + 1)));
         }
         if (P > 0) {
-            hipLaunchKernelGGL(split_fill_kernel, dim3((unsigned)chunks), dim3(kThreads), 0, 0, P, panels, pcol,
+            hipLaunchKernelGGL(split_fill_kernel, dim3((unsigned)chunks), dim3(kThreads), 0, setup_stream(), P, panels, pcol,
                                (int32_t)sg, sums, o);
             HIP_TRY(hipGetLastError());
         } else {
-            HIP_TRY(hipMemsetAsync(o.rowptr, 0, sizeof(int32_t), nullptr));
-            HIP_TRY(hipMemsetAsync(o.split_slot, 0, sizeof(int32_t), nullptr));
+            HIP_TRY(hipMemsetAsync(o.rowptr, 0, sizeof(int32_t), setup_stream()));
+            HIP_TRY(hipMemsetAsync(o.split_slot, 0, sizeof(int32_t), setup_stream()));
         }
         int32_t *sched = nullptr;
         if (column_order) {
@@ -974,28 +1000,28 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
             HIP_TRY(sc.alloc((void **)&wsum, sizeof(long long) * (cl + cs + 1)));
             HIP_TRY(sc.alloc((void **)&wscan, sizeof(long long) * (cl + cs + 2)));
             if (cl + cs > 0) {
-                hipLaunchKernelGGL(sched_sums_kernel, dim3((unsigned)(cl + cs)), dim3(kThreads), 0, 0, n_long, sorted,
+                hipLaunchKernelGGL(sched_sums_kernel, dim3((unsigned)(cl + cs)), dim3(kThreads), 0, setup_stream(), n_long, sorted,
                                    n_short, shorts, o.rowptr, wsum);
                 HIP_TRY(hipGetLastError());
             }
-            hipLaunchKernelGGL(sched_scan_kernel, dim3(2), dim3(1024), 0, 0, (int)cl, (int)cs, wsum, wscan);
+            hipLaunchKernelGGL(sched_scan_kernel, dim3(2), dim3(1024), 0, setup_stream(), (int)cl, (int)cs, wsum, wscan);
             HIP_TRY(hipGetLastError());
-            hipLaunchKernelGGL(sched_bounds_kernel, dim3(18), dim3(kThreads), 0, 0, n_long, sorted, n_short,
+            hipLaunchKernelGGL(sched_bounds_kernel, dim3(18), dim3(kThreads), 0, setup_stream(), n_long, sorted, n_short,
                                shorts, o.rowptr, wscan, d_bounds);
             HIP_TRY(hipGetLastError());
             if (M > 0) {
-                hipLaunchKernelGGL(sched_emit_kernel, dim3(blocks_for(M)), dim3(kThreads), 0, 0, n_long, sorted, n_short,
+                hipLaunchKernelGGL(sched_emit_kernel, dim3(blocks_for(M)), dim3(kThreads), 0, setup_stream(), n_long, sorted, n_short,
                                    shorts, d_bounds, o.rowptr, o.trow, o.item_slot,
                                    reinterpret_cast<int4 *>(sched));
                 HIP_TRY(hipGetLastError());
             }
             int32_t b[18];
-            HIP_TRY(hipMemcpy(b, d_bounds, sizeof(b), hipMemcpyDeviceToHost));
+            HIP_TRY(setup_copy(b, d_bounds, sizeof(b), hipMemcpyDeviceToHost));
             for (int x = 0; x < 9; ++x) out->xcd_bounds[x] = b[x] + b[9 + x];
         } else {
-            hipLaunchKernelGGL(xcd_bounds_kernel, dim3(1), dim3(64), 0, 0, (int32_t)M, o.rowptr, d_bounds);
+            hipLaunchKernelGGL(xcd_bounds_kernel, dim3(1), dim3(64), 0, setup_stream(), (int32_t)M, o.rowptr, d_bounds);
             HIP_TRY(hipGetLastError());
-            HIP_TRY(hipMemcpy(out->xcd_bounds, d_bounds, 9 * sizeof(int32_t), hipMemcpyDeviceToHost));
+            HIP_TRY(setup_copy(out->xcd_bounds, d_bounds, 9 * sizeof(int32_t), hipMemcpyDeviceToHost));
         }
         out->M = M;
         out->n_split = total.split;
@@ -1049,19 +1075,19 @@ int features_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *
         HIP_TRY(sc.alloc((void **)&rows, sizeof(RowPart) * pb));
         HIP_TRY(sc.alloc((void **)&devs, sizeof(DevPart) * db));
         HIP_TRY(sc.alloc((void **)&acc, sizeof(FeatAcc)));
-        HIP_TRY(hipMemsetAsync(far, 0, sizeof(FarList), nullptr));
-        hipLaunchKernelGGL(features_panels_kernel, dim3(pb), dim3(kPanelThreads), 0, 0, n_rows, nnz, d_rowptr, d_colidx, shared,
+        HIP_TRY(hipMemsetAsync(far, 0, sizeof(FarList), setup_stream()));
+        hipLaunchKernelGGL(features_panels_kernel, dim3(pb), dim3(kPanelThreads), 0, setup_stream(), n_rows, nnz, d_rowptr, d_colidx, shared,
                            room, units, far, rows);
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(features_far_kernel, dim3(kFarBlocks), dim3(kThreads), 0, 0, n_rows, d_rowptr, d_colidx, room,
+        hipLaunchKernelGGL(features_far_kernel, dim3(kFarBlocks), dim3(kThreads), 0, setup_stream(), n_rows, d_rowptr, d_colidx, room,
                            units, far, shared);
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(features_deviation_kernel, dim3(db), dim3(kThreads), 0, 0, n_rows, nnz, d_rowptr, shared, rows,
+        hipLaunchKernelGGL(features_deviation_kernel, dim3(db), dim3(kThreads), 0, setup_stream(), n_rows, nnz, d_rowptr, shared, rows,
                            (int)pb, far, omega, devs);
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(features_final_kernel, dim3(1), dim3(kThreads), 0, 0, nnz, rows, (int)pb, far, devs, (int)db, acc);
+        hipLaunchKernelGGL(features_final_kernel, dim3(1), dim3(kThreads), 0, setup_stream(), nnz, rows, (int)pb, far, devs, (int)db, acc);
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpy(&h, acc, sizeof(h), hipMemcpyDeviceToHost));
+        HIP_TRY(setup_copy(&h, acc, sizeof(h), hipMemcpyDeviceToHost));
     }
     const double d = n_rows ? double(nnz) / double(n_rows) : 0.0;
     const double d_hat = h.n_hat ? double(nnz) / double(h.n_hat) : 0.0;

@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(kRoundThreads) cluster_fill_kernel(int64_t n, 
 
 hipError_t cluster_probe(int64_t n, int64_t nnz, const int32_t *d_rowptr, const int32_t *d_colidx, unsigned long long *d_out)
 {
-    hipLaunchKernelGGL(cluster_probe_kernel, dim3(kSamples / (kThreads / 64)), dim3(kThreads), 0, 0, n, nnz, d_rowptr,
+    hipLaunchKernelGGL(cluster_probe_kernel, dim3(kSamples / (kThreads / 64)), dim3(kThreads), 0, setup_stream(), n, nnz, d_rowptr,
                        d_colidx, d_out);
     return hipGetLastError();
 }
@@ -370,20 +370,20 @@ int cluster_rows(int64_t n, const int32_t *d_rowptr, const int32_t *d_colidx, in
     for (int b = 0; b < 2; ++b) HIP_TRY(sc.alloc((void **)&lab[b], sizeof(int32_t) * n));
     HIP_TRY(sc.alloc((void **)&parts, sizeof(RoundPart) * kRoundBlocks));
     HIP_TRY(sc.alloc((void **)&d_stats, sizeof(Stats)));
-    HIP_TRY(hipMemsetAsync(d_stats, 0, sizeof(Stats), nullptr));
+    HIP_TRY(hipMemsetAsync(d_stats, 0, sizeof(Stats), setup_stream()));
     const int64_t need = (n + kRoundThreads / 16 - 1) / (kRoundThreads / 16);
     const int blocks = (int)(need < kRoundBlocks ? need : kRoundBlocks);
     for (int k = 0; k < kRounds; ++k) {
-        hipLaunchKernelGGL(cluster_round_kernel, dim3(blocks), dim3(kRoundThreads), 0, 0, n, d_rowptr, d_colidx, k,
+        hipLaunchKernelGGL(cluster_round_kernel, dim3(blocks), dim3(kRoundThreads), 0, setup_stream(), n, d_rowptr, d_colidx, k,
                            k ? lab[(k - 1) & 1] : (const int32_t *)nullptr, lab[k & 1],
                            k == kRounds - 1 ? parts : (RoundPart *)nullptr);
         HIP_TRY(hipGetLastError());
     }
     int32_t *const made = lab[(kRounds - 1) & 1];
-    hipLaunchKernelGGL(cluster_stats_kernel, dim3(kPairs / kRoundThreads), dim3(kRoundThreads), 0, 0, n, made, blocks, parts,
+    hipLaunchKernelGGL(cluster_stats_kernel, dim3(kPairs / kRoundThreads), dim3(kRoundThreads), 0, setup_stream(), n, made, blocks, parts,
                        d_stats);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpy(&h, d_stats, sizeof(h), hipMemcpyDeviceToHost));
+    HIP_TRY(setup_copy(&h, d_stats, sizeof(h), hipMemcpyDeviceToHost));
     // Worth it where most neighbours share the row's label and the label's rows of B (64 columns of them at a time)
     // take up no more than half of an XCD's L2.
     const double mean = (double)h.pairs / kPairs * (double)n; // size of the label a row has
@@ -425,27 +425,27 @@ int cluster_windows(int64_t n, int64_t nnz, const int32_t *d_rowptr, const int32
     HIP_TRY(sc.alloc((void **)&new_colidx, sizeof(int32_t) * (nnz + 1)));
     HIP_TRY(sc.alloc((void **)&new_vals, sizeof(float) * (nnz + 1)));
     HIP_TRY(sc.alloc((void **)&inner_end, sizeof(int32_t) * n));
-    HIP_TRY(hipcub::DeviceSelect::Flagged(nullptr, select_bytes, places, cut, ptr_in, &count->blocks, (int)n));
-    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, len, new_rowptr, (int)(n + 1)));
+    HIP_TRY(hipcub::DeviceSelect::Flagged(nullptr, select_bytes, places, cut, ptr_in, &count->blocks, (int)n, setup_stream()));
+    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, len, new_rowptr, (int)(n + 1), setup_stream()));
     HIP_TRY(sc.alloc(&tmp, select_bytes > scan_bytes ? select_bytes : scan_bytes));
-    HIP_TRY(hipMemsetAsync(sizes, 0, sizeof(int32_t) * kSizeParts * n, nullptr));
-    HIP_TRY(hipMemsetAsync(count, 0, sizeof(WindowCount), nullptr));
-    hipLaunchKernelGGL(cluster_sizes_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, 0, n, d_labels, sizes);
+    HIP_TRY(hipMemsetAsync(sizes, 0, sizeof(int32_t) * kSizeParts * n, setup_stream()));
+    HIP_TRY(hipMemsetAsync(count, 0, sizeof(WindowCount), setup_stream()));
+    hipLaunchKernelGGL(cluster_sizes_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, setup_stream(), n, d_labels, sizes);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(cluster_order_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, 0, n, d_labels, sizes, large, key,
+    hipLaunchKernelGGL(cluster_order_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, setup_stream(), n, d_labels, sizes, large, key,
                        row);
     HIP_TRY(hipGetLastError());
     HIP_TRY(sort_pairs_u32(key, key_sorted, row, rows, n, bits + 1, sc));
-    hipLaunchKernelGGL(cluster_cut_kernel, dim3(blocks_for(n + 1)), dim3(kThreads), 0, 0, n, key_sorted,
+    hipLaunchKernelGGL(cluster_cut_kernel, dim3(blocks_for(n + 1)), dim3(kThreads), 0, setup_stream(), n, key_sorted,
                        reinterpret_cast<const int32_t *>(rows), sizes, large, d_rowptr, len, cut);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipcub::DeviceSelect::Flagged(tmp, select_bytes, places, cut, ptr_in, &count->blocks, (int)n));
-    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tmp, scan_bytes, len, new_rowptr, (int)(n + 1)));
-    hipLaunchKernelGGL(cluster_fill_kernel, dim3((unsigned)most), dim3(kRoundThreads), 0, 0, n, ptr_in, count,
+    HIP_TRY(hipcub::DeviceSelect::Flagged(tmp, select_bytes, places, cut, ptr_in, &count->blocks, (int)n, setup_stream()));
+    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tmp, scan_bytes, len, new_rowptr, (int)(n + 1), setup_stream()));
+    hipLaunchKernelGGL(cluster_fill_kernel, dim3((unsigned)most), dim3(kRoundThreads), 0, setup_stream(), n, ptr_in, count,
                        reinterpret_cast<const int32_t *>(rows), d_rowptr, d_colidx, d_vals, new_rowptr, ptr, new_colidx, new_vals,
                        inner_end);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpy(&h, count, sizeof(h), hipMemcpyDeviceToHost));
+    HIP_TRY(setup_copy(&h, count, sizeof(h), hipMemcpyDeviceToHost));
     // as the column windows: half of the vectors inside, and blocks that are worth a workgroup
     if (2 * h.hits < (unsigned long long)nnz || n < 128 * (int64_t)h.blocks || h.blocks > most) return PCSR_OK;
     HIP_TRY(prepare_row_windows());
@@ -471,7 +471,7 @@ int cluster_key_bits(int64_t n)
 hipError_t cluster_keys(int64_t n, const int32_t *d_labels, int64_t n_items, const int32_t *d_items, const int32_t *d_rows,
                         uint32_t *d_key)
 {
-    hipLaunchKernelGGL(cluster_keys_kernel, dim3(blocks_for(n_items)), dim3(kThreads), 0, 0, n_items, d_items, d_rows, d_labels,
+    hipLaunchKernelGGL(cluster_keys_kernel, dim3(blocks_for(n_items)), dim3(kThreads), 0, setup_stream(), n_items, d_items, d_rows, d_labels,
                        (1u << cluster_key_bits(n)) - 1, d_key);
     return hipGetLastError();
 }

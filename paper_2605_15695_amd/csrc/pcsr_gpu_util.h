@@ -178,8 +178,8 @@ struct Scratch { // gives back everything it still owns on scope exit
     }
     ~Scratch()
     {
-        // everything here runs on the null stream; idle by now unless an error cut it short
-        (void)hipStreamSynchronize(nullptr);
+        // everything here runs on the set-up stream; idle by now unless an error cut it short
+        (void)setup_wait();
         for (int i = 0; i < n; ++i) pool_free(p[i]);
     }
 };

@@ -1,4 +1,5 @@
 #include "pcsr_pool.h"
+#include "pcsr_build_gpu.h"
 
 #include <algorithm>
 #include <atomic>
@@ -292,6 +293,7 @@ hipError_t copy_to_device(void *dst, const void *src, size_t bytes)
 void Upload::start(void *dst, const void *src, size_t bytes) noexcept
 {
     result = wait();
+    on_thread = false;
     if (result != hipSuccess || bytes == 0) return;
     int dev = -1;
     if (bytes >= kStagedBytes && hipGetDevice(&dev) == hipSuccess) {
@@ -301,6 +303,7 @@ void Upload::start(void *dst, const void *src, size_t bytes) noexcept
                 if (result == hipSuccess)
                     result = staged(static_cast<char *>(dst), static_cast<const char *>(src), bytes, false, true);
             });
+            on_thread = true;
             return;
         } catch (...) { // no thread
         }
@@ -310,8 +313,166 @@ void Upload::start(void *dst, const void *src, size_t bytes) noexcept
 
 hipError_t Upload::wait() noexcept
 {
+    std::lock_guard<std::mutex> lock(joining);
     if (thread.joinable()) thread.join();
     return result;
+}
+
+namespace {
+thread_local hipStream_t t_setup_stream = nullptr;
+
+struct Side {
+    hipStream_t stream = nullptr;
+    bool taken = false;
+};
+struct Sides {
+    std::mutex mu;
+    std::map<int, Side> per_device;
+};
+Sides &sides()
+{
+    static Sides *s = new Sides;
+    return *s;
+}
+} // namespace
+
+namespace {
+// Pinned memory that a kernel leaves results in for the host: of one thread at a time, kept for the next one when that ends.
+constexpr size_t kMailBytes = 256;
+struct Mail {
+    unsigned char data[kMailBytes];
+    unsigned seq; // of the last results in it
+};
+struct MailList {
+    std::mutex mu;
+    std::vector<Mail *> idle;
+};
+MailList &mail_list()
+{
+    static MailList *l = new MailList;
+    return *l;
+}
+struct OwnMail {
+    Mail *mail = nullptr;
+    bool tried = false;
+    Mail *get() noexcept
+    try {
+        if (mail || tried) return mail;
+        tried = true;
+        MailList &l = mail_list();
+        {
+            std::lock_guard<std::mutex> lock(l.mu);
+            l.idle.reserve(l.idle.size() + 1);
+            if (!l.idle.empty()) {
+                mail = l.idle.back();
+                l.idle.pop_back();
+                return mail;
+            }
+        }
+        void *p = nullptr;
+        if (hipHostMalloc(&p, sizeof(Mail), hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        mail = static_cast<Mail *>(p);
+        mail->seq = 0;
+        return mail;
+    } catch (...) {
+        return nullptr;
+    }
+    ~OwnMail()
+    {
+        if (!mail) return;
+        try {
+            MailList &l = mail_list();
+            std::lock_guard<std::mutex> lock(l.mu);
+            l.idle.push_back(mail);
+        } catch (...) {
+        }
+    }
+};
+thread_local OwnMail t_mail;
+thread_local bool t_enqueued = true; // on t_setup_stream, since it was last known to be idle
+constexpr int kSpins = 200000;       // some milliseconds; then the runtime's own wait, which also reports errors
+} // namespace
+
+hipStream_t setup_stream() noexcept
+{
+    t_enqueued = true;
+    return t_setup_stream;
+}
+
+hipError_t setup_wait() noexcept
+{
+    if (!t_enqueued) return hipSuccess;
+    const hipError_t e = hipStreamSynchronize(t_setup_stream);
+    if (e == hipSuccess) t_enqueued = false;
+    return e;
+}
+
+hipError_t setup_copy(void *dst, const void *src, size_t bytes, hipMemcpyKind kind) noexcept
+{
+    const hipStream_t s = t_setup_stream;
+    Mail *const mail = kind == hipMemcpyDeviceToHost && bytes <= kMailBytes && bytes % 4 == 0 ? t_mail.get() : nullptr;
+    if (mail) {
+        const unsigned seq = mail->seq + 1;
+        hipError_t e = deliver(mail->data, src, (int)(bytes / 4), &mail->seq, seq, s);
+        if (e != hipSuccess) return e;
+        const volatile unsigned *const arrived = &mail->seq;
+        for (int i = 0; i < kSpins && *arrived != seq; ++i) __builtin_ia32_pause();
+        if (*arrived != seq) {
+            e = hipStreamSynchronize(s);
+            if (e != hipSuccess) return e;
+            if (*arrived != seq) return hipErrorUnknown;
+        }
+        std::atomic_thread_fence(std::memory_order_acquire);
+        std::memcpy(dst, mail->data, bytes);
+        t_enqueued = false;
+        return hipSuccess;
+    }
+    if (!s) {
+        const hipError_t e = hipMemcpy(dst, src, bytes, kind);
+        if (e == hipSuccess && kind == hipMemcpyDeviceToHost) t_enqueued = false;
+        return e;
+    }
+    const hipError_t e = hipMemcpyAsync(dst, src, bytes, kind, s), w = hipStreamSynchronize(s);
+    return e != hipSuccess ? e : w;
+}
+
+SetupOn::SetupOn(hipStream_t s) noexcept : before(t_setup_stream)
+{
+    t_setup_stream = s;
+    t_enqueued = true;
+}
+SetupOn::~SetupOn()
+{
+    t_setup_stream = before;
+    t_enqueued = true;
+}
+
+SideStream::SideStream() noexcept
+try {
+    if (hipGetDevice(&device) != hipSuccess) return;
+    Sides &all = sides();
+    std::lock_guard<std::mutex> lock(all.mu);
+    Side &s = all.per_device[device];
+    if (s.taken) return;
+    if (!s.stream && hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking) != hipSuccess) {
+        (void)hipGetLastError();
+        s.stream = nullptr;
+        return;
+    }
+    s.taken = true;
+    stream = s.stream;
+} catch (...) { // no host memory for the books
+}
+
+SideStream::~SideStream()
+{
+    if (!stream) return;
+    Sides &all = sides();
+    std::lock_guard<std::mutex> lock(all.mu);
+    all.per_device[device].taken = false;
 }
 
 } // namespace pcsr

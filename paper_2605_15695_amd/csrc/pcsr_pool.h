@@ -7,6 +7,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <mutex>
 #include <thread>
 
 namespace pcsr {
@@ -41,20 +42,66 @@ constexpr size_t kStagedBytes = size_t(4) << 20;
 hipError_t copy_to_host(void *dst, const void *src, size_t bytes);
 hipError_t copy_to_device(void *dst, const void *src, size_t bytes);
 
+// Where the set-up code enqueues its work: the null stream, or, on a thread that has put a SetupOn in scope, the stream of that.
+hipStream_t setup_stream() noexcept;
+// hipMemcpy there.  What a few kernels have counted is brought to pinned memory by one more, with a flag after it that the host looks
+// for: 9.3 us from the launch of the last of them where hipMemcpy takes 14.5, and 23 on another stream than the null stream.
+hipError_t setup_copy(void *dst, const void *src, size_t bytes, hipMemcpyKind kind) noexcept;
+// Waits for what this thread has enqueued there, unless setup_copy has and nothing was since (setup_stream was not asked for).
+hipError_t setup_wait() noexcept;
+class SetupOn {
+public:
+    explicit SetupOn(hipStream_t s) noexcept;
+    SetupOn(const SetupOn &) = delete;
+    SetupOn &operator=(const SetupOn &) = delete;
+    ~SetupOn();
+
+private:
+    hipStream_t before;
+};
+// The current device's stream for set-up work beside that on the null stream, which it does not wait for, nor that for it: what it is
+// to read has to be there.  One caller at a time has it; others, and one for whom none could be made, get null.
+class SideStream {
+public:
+    SideStream() noexcept;
+    SideStream(const SideStream &) = delete;
+    SideStream &operator=(const SideStream &) = delete;
+    ~SideStream();
+    hipStream_t get() const noexcept { return stream; }
+
+private:
+    hipStream_t stream = nullptr;
+    int device = -1;
+};
+
+// Values that come later than the pattern they belong to.  wait(): until they are there, for what is enqueued on
+// setup_stream() afterwards.
+class Late {
+public:
+    virtual hipError_t wait() noexcept = 0;
+
+protected:
+    ~Late() = default;
+};
+
 // copy_to_device beside what the caller does meanwhile, on threads (half as many) and pinned buffers of its own.
 // Nothing enqueued may still use dst; src has to stay until wait() (or the destructor) returns.  Where no thread is to be had the
 // copy is made by start().
-class Upload {
+// wait() may be called by several threads.
+class Upload final : public Late {
 public:
     Upload() = default;
     Upload(const Upload &) = delete;
     Upload &operator=(const Upload &) = delete;
     ~Upload() { (void)wait(); }
     void start(void *dst, const void *src, size_t bytes) noexcept;
-    hipError_t wait() noexcept;
+    hipError_t wait() noexcept override;
+    bool beside() const noexcept { return on_thread; } // whether start() left the copy to a thread
 
 private:
+    std::mutex joining;
     std::thread thread;
+    bool on_thread = false;
     hipError_t result = hipSuccess;
 };
 

@@ -417,8 +417,8 @@ hipError_t sort_pairs(const K *kin, K *kout, const T *vin, T *vout, int64_t n, i
     size_t bytes = 0;
     void *tmp = nullptr;
     auto go = [&]() {
-        return descending ? hipcub::DeviceRadixSort::SortPairsDescending(tmp, bytes, kin, kout, vin, vout, (int)n, 0, bits)
-                          : hipcub::DeviceRadixSort::SortPairs(tmp, bytes, kin, kout, vin, vout, (int)n, 0, bits);
+        return descending ? hipcub::DeviceRadixSort::SortPairsDescending(tmp, bytes, kin, kout, vin, vout, (int)n, 0, bits, setup_stream())
+                          : hipcub::DeviceRadixSort::SortPairs(tmp, bytes, kin, kout, vin, vout, (int)n, 0, bits, setup_stream());
     };
     hipError_t e = go();
     if (e != hipSuccess) return e;
@@ -458,16 +458,16 @@ struct DevicePattern {
         r.colidx = colidx;
         r.counts = counts;
         // rows first: with a broken row pointer the lists could overflow
-        TRY_GPU(hipMemsetAsync(counts, 0, sizeof(int32_t) * 5, nullptr));
-        hipLaunchKernelGGL(classify_kernel, dim3(strided_blocks(n > nnz ? n : nnz)), dim3(kThreads), 0, 0, n, n_cols,
+        TRY_GPU(hipMemsetAsync(counts, 0, sizeof(int32_t) * 5, setup_stream()));
+        hipLaunchKernelGGL(classify_kernel, dim3(strided_blocks(n > nnz ? n : nnz)), dim3(kThreads), 0, setup_stream(), n, n_cols,
                            nnz, r, (int32_t *)nullptr, (int32_t *)nullptr);
         TRY_GPU(hipGetLastError());
         int32_t h[5];
-        TRY_GPU(hipMemcpy(h, counts, sizeof(h), hipMemcpyDeviceToHost));
+        TRY_GPU(setup_copy(h, counts, sizeof(h), hipMemcpyDeviceToHost));
         if (h[2]) return kUseHost;
         longest = h[4];
         if (lists) {
-            hipLaunchKernelGGL(classify_kernel, dim3(strided_blocks(n)), dim3(kThreads), 0, 0, n, n_cols, nnz, r, medium,
+            hipLaunchKernelGGL(classify_kernel, dim3(strided_blocks(n)), dim3(kThreads), 0, setup_stream(), n, n_cols, nnz, r, medium,
                                large);
             TRY_GPU(hipGetLastError());
             r.medium = medium;
@@ -515,18 +515,18 @@ int transpose_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t 
     HIP_TRY(sc.alloc((void **)&in, sizeof(uint2) * (nnz + 1)));
     HIP_TRY(sc.alloc((void **)&sorted, sizeof(uint2) * (nnz + 1)));
     if (nnz > 0) {
-        hipLaunchKernelGGL(row_value_kernel, dim3((unsigned)((nnz + kSlice - 1) / kSlice)), dim3(kThreads), 0, 0, n_rows,
+        hipLaunchKernelGGL(row_value_kernel, dim3((unsigned)((nnz + kSlice - 1) / kSlice)), dim3(kThreads), 0, setup_stream(), n_rows,
                            nnz, d_rowptr, d_vals, in);
         HIP_TRY(hipGetLastError());
         // stable, and the nonzeros come in row order: every output row ends up ascending
         HIP_TRY(sort_pairs(d_colidx, keys, reinterpret_cast<const unsigned long long *>(in),
                            reinterpret_cast<unsigned long long *>(sorted), nnz, key_bits(n_cols), false, sc));
-        hipLaunchKernelGGL(split_pairs_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, 0, nnz, sorted, ci, va);
+        hipLaunchKernelGGL(split_pairs_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, setup_stream(), nnz, sorted, ci, va);
         HIP_TRY(hipGetLastError());
     }
-    hipLaunchKernelGGL(lower_bounds_kernel, dim3(blocks_for(n_cols + 1)), dim3(kThreads), 0, 0, n_cols, nnz, keys, rp);
+    hipLaunchKernelGGL(lower_bounds_kernel, dim3(blocks_for(n_cols + 1)), dim3(kThreads), 0, setup_stream(), n_cols, nnz, keys, rp);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(nullptr));
+    HIP_TRY(setup_wait());
     *t_rowptr = rp;
     *t_colidx = ci;
     *t_vals = va;
@@ -553,7 +553,7 @@ int transpose_gpu(int64_t n_rows, int64_t n_cols, const int32_t *rowptr, const i
     hipError_t e = copy_to_host(out_rowptr, rp, sizeof(int32_t) * (n_cols + 1));
     if (e == hipSuccess) e = copy_to_host(out_colidx, ci, sizeof(int32_t) * nnz);
     if (e == hipSuccess) e = copy_to_host(out_vals, va, sizeof(float) * nnz);
-    (void)hipStreamSynchronize(nullptr);
+    (void)setup_wait();
     pool_free(rp);
     pool_free(ci);
     pool_free(va);
@@ -574,31 +574,31 @@ int reorder_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, int32_t
     for (int b = 0; b < 2; ++b) TRY_GPU(sc.alloc((void **)&lab[b], sizeof(int32_t) * n));
     TRY_GPU(sc.alloc((void **)&ids, sizeof(int32_t) * n));
     TRY_GPU(sc.alloc((void **)&changed, sizeof(int32_t) * (kBatch + 1)));
-    hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, 0, n, lab[0], ids);
+    hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, setup_stream(), n, lab[0], ids);
     TRY_GPU(hipGetLastError());
     int at = 0;
     const unsigned waves = (unsigned)((n + kThreads / 64 - 1) / (kThreads / 64));
     const unsigned blocks = waves < 2048 ? waves : 2048;
     for (int32_t done = 0; done < max_rounds;) {
         const int batch = max_rounds - done < kBatch ? max_rounds - done : kBatch;
-        TRY_GPU(hipMemsetAsync(changed, 0, sizeof(int32_t) * (kBatch + 1), nullptr));
+        TRY_GPU(hipMemsetAsync(changed, 0, sizeof(int32_t) * (kBatch + 1), setup_stream()));
         for (int b = 0; b < batch; ++b) {
             const int32_t *from = lab[(at + b) & 1];
             int32_t *to = lab[(at + b + 1) & 1];
             const uint32_t round = (uint32_t)(done + b);
-            hipLaunchKernelGGL(propagate_short_kernel, dim3(blocks), dim3(kThreads), 0, 0, n, m.r, from, to, b, round,
+            hipLaunchKernelGGL(propagate_short_kernel, dim3(blocks), dim3(kThreads), 0, setup_stream(), n, m.r, from, to, b, round,
                                changed);
             TRY_GPU(hipGetLastError());
-            hipLaunchKernelGGL((propagate_long_kernel<256, 2048>), dim3(2048), dim3(256), 0, 0, n, m.r, m.r.medium,
+            hipLaunchKernelGGL((propagate_long_kernel<256, 2048>), dim3(2048), dim3(256), 0, setup_stream(), n, m.r, m.r.medium,
                                m.r.counts, from, to, b, round, changed);
             TRY_GPU(hipGetLastError());
-            hipLaunchKernelGGL((propagate_long_kernel<1024, 8192>), dim3(512), dim3(1024), 0, 0, n, m.r, m.r.large,
+            hipLaunchKernelGGL((propagate_long_kernel<1024, 8192>), dim3(512), dim3(1024), 0, setup_stream(), n, m.r, m.r.large,
                                m.r.counts + 1, from, to, b, round, changed);
             TRY_GPU(hipGetLastError());
         }
         int32_t h[kBatch], counts[4];
-        TRY_GPU(hipMemcpyAsync(counts, m.r.counts, sizeof(counts), hipMemcpyDeviceToHost, nullptr));
-        TRY_GPU(hipMemcpy(h, changed, sizeof(int32_t) * kBatch, hipMemcpyDeviceToHost));
+        TRY_GPU(setup_copy(counts, m.r.counts, sizeof(counts), hipMemcpyDeviceToHost));
+        TRY_GPU(setup_copy(h, changed, sizeof(int32_t) * kBatch, hipMemcpyDeviceToHost));
         if (counts[3]) return kUseHost;
         int ran = batch;
         bool over = false;
@@ -616,12 +616,12 @@ int reorder_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, int32_t
     TRY_GPU(sc.alloc((void **)&order, sizeof(int32_t) * n));
     TRY_GPU(sc.alloc((void **)&d_perm, sizeof(int32_t) * n));
     TRY_GPU(sc.alloc((void **)&distinct, sizeof(int32_t)));
-    TRY_GPU(hipMemsetAsync(distinct, 0, sizeof(int32_t), nullptr));
+    TRY_GPU(hipMemsetAsync(distinct, 0, sizeof(int32_t), setup_stream()));
     TRY_GPU(sort_pairs_u32(reinterpret_cast<const uint32_t *>(lab[at]), reinterpret_cast<uint32_t *>(sorted),
                            reinterpret_cast<const uint32_t *>(ids), reinterpret_cast<uint32_t *>(order), n, key_bits(n), sc));
-    hipLaunchKernelGGL(number_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, 0, n, order, sorted, d_perm, distinct);
+    hipLaunchKernelGGL(number_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, setup_stream(), n, order, sorted, d_perm, distinct);
     TRY_GPU(hipGetLastError());
-    TRY_GPU(hipMemcpy(&clusters, distinct, sizeof(clusters), hipMemcpyDeviceToHost));
+    TRY_GPU(setup_copy(&clusters, distinct, sizeof(clusters), hipMemcpyDeviceToHost));
     TRY_GPU(copy_to_host(perm, d_perm, sizeof(int32_t) * n));
     if (n_clusters) *n_clusters = clusters;
     return PCSR_OK;
@@ -641,13 +641,13 @@ int degree_order_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, in
     TRY_GPU(sc.alloc((void **)&ids, sizeof(int32_t) * n));
     TRY_GPU(sc.alloc((void **)&order, sizeof(int32_t) * n));
     TRY_GPU(sc.alloc((void **)&d_perm, sizeof(int32_t) * n));
-    TRY_GPU(hipMemsetAsync(refs, 0, sizeof(uint32_t) * n, nullptr));
-    hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, 0, n, ids, (int32_t *)nullptr);
+    TRY_GPU(hipMemsetAsync(refs, 0, sizeof(uint32_t) * n, setup_stream()));
+    hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, setup_stream(), n, ids, (int32_t *)nullptr);
     TRY_GPU(hipGetLastError());
-    hipLaunchKernelGGL(count_columns_kernel, dim3(strided_blocks(nnz)), dim3(kThreads), 0, 0, nnz, m.colidx, refs);
+    hipLaunchKernelGGL(count_columns_kernel, dim3(strided_blocks(nnz)), dim3(kThreads), 0, setup_stream(), nnz, m.colidx, refs);
     TRY_GPU(hipGetLastError());
     TRY_GPU(sort_pairs(refs, sorted, ids, order, n, key_bits(nnz + 1), true, sc)); // descending, stable
-    hipLaunchKernelGGL(number_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, 0, n, order, (const int32_t *)nullptr,
+    hipLaunchKernelGGL(number_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, setup_stream(), n, order, (const int32_t *)nullptr,
                        d_perm, (int32_t *)nullptr);
     TRY_GPU(hipGetLastError());
     TRY_GPU(copy_to_host(perm, d_perm, sizeof(int32_t) * n));
@@ -673,38 +673,38 @@ int permute_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, const f
     TRY_GPU(sc.alloc((void **)&from, sizeof(int32_t) * (n + 1)));
     TRY_GPU(sc.alloc((void **)&rp, sizeof(int32_t) * (n + 1)));
     TRY_GPU(copy_to_device(d_perm, perm, sizeof(int32_t) * n));
-    TRY_GPU(hipMemsetAsync(inv, 0xff, sizeof(int32_t) * n, nullptr));
-    TRY_GPU(hipMemsetAsync(flag, 0, sizeof(int32_t), nullptr));
-    hipLaunchKernelGGL(invert_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, 0, n, d_perm, inv, flag);
+    TRY_GPU(hipMemsetAsync(inv, 0xff, sizeof(int32_t) * n, setup_stream()));
+    TRY_GPU(hipMemsetAsync(flag, 0, sizeof(int32_t), setup_stream()));
+    hipLaunchKernelGGL(invert_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, setup_stream(), n, d_perm, inv, flag);
     TRY_GPU(hipGetLastError());
     DevicePattern m;
     const int rc = m.upload(n, n, nnz, rowptr, colidx, true, sc);
     if (rc != PCSR_OK) return rc;
-    TRY_GPU(hipMemcpy(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost));
+    TRY_GPU(setup_copy(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost));
     if (bad) return kUseHost;
     TRY_GPU(sc.alloc((void **)&va, sizeof(float) * nnz));
     values.start(va, vals, sizeof(float) * nnz);
-    hipLaunchKernelGGL(permuted_len_kernel, dim3(blocks_for(n + 1)), dim3(kThreads), 0, 0, n, m.rowptr, inv, len, from);
+    hipLaunchKernelGGL(permuted_len_kernel, dim3(blocks_for(n + 1)), dim3(kThreads), 0, setup_stream(), n, m.rowptr, inv, len, from);
     TRY_GPU(hipGetLastError());
     size_t bytes = 0;
     void *tmp = nullptr;
-    TRY_GPU(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, len, rp, (int)(n + 1)));
+    TRY_GPU(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, len, rp, (int)(n + 1), setup_stream()));
     TRY_GPU(sc.alloc(&tmp, bytes));
-    TRY_GPU(hipcub::DeviceScan::ExclusiveSum(tmp, bytes, len, rp, (int)(n + 1)));
+    TRY_GPU(hipcub::DeviceScan::ExclusiveSum(tmp, bytes, len, rp, (int)(n + 1), setup_stream()));
     TRY_GPU(sc.alloc((void **)&va_out, sizeof(float) * nnz));
     TRY_GPU(sc.alloc((void **)&ci, sizeof(int32_t) * nnz));
     TRY_GPU(sc.alloc((void **)&order, sizeof(int32_t) * nnz));
     if (m.longest <= kLongestSorted) {
         const PermutedRows a = {m.colidx, d_perm, from, rp, ci, order, flag};
         const unsigned waves = (unsigned)((n + kThreads / 64 - 1) / (kThreads / 64));
-        hipLaunchKernelGGL(permute_short_kernel, dim3(waves < 2048 ? waves : 2048), dim3(kThreads), 0, 0, n, a);
+        hipLaunchKernelGGL(permute_short_kernel, dim3(waves < 2048 ? waves : 2048), dim3(kThreads), 0, setup_stream(), n, a);
         TRY_GPU(hipGetLastError());
         if (m.longest > 64) {
-            hipLaunchKernelGGL((permute_long_kernel<256, kMediumRow>), dim3(2048), dim3(256), 0, 0, m.r.medium, m.r.counts, a);
+            hipLaunchKernelGGL((permute_long_kernel<256, kMediumRow>), dim3(2048), dim3(256), 0, setup_stream(), m.r.medium, m.r.counts, a);
             TRY_GPU(hipGetLastError());
         }
         if (m.longest > kMediumRow) {
-            hipLaunchKernelGGL((permute_long_kernel<1024, kLongestSorted>), dim3(512), dim3(1024), 0, 0, m.r.large,
+            hipLaunchKernelGGL((permute_long_kernel<1024, kLongestSorted>), dim3(512), dim3(1024), 0, setup_stream(), m.r.large,
                                m.r.counts + 1, a);
             TRY_GPU(hipGetLastError());
         }
@@ -712,20 +712,20 @@ int permute_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, const f
         unsigned long long *key = nullptr, *sorted = nullptr;
         int32_t *ids = nullptr;
         TRY_GPU(sc.alloc((void **)&ids, sizeof(int32_t) * nnz));
-        hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, 0, nnz, ids, (int32_t *)nullptr);
+        hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, setup_stream(), nnz, ids, (int32_t *)nullptr);
         TRY_GPU(hipGetLastError());
         TRY_GPU(sc.alloc((void **)&key, sizeof(long long) * nnz));
         TRY_GPU(sc.alloc((void **)&sorted, sizeof(long long) * nnz));
         const int bits = key_bits(n);
-        hipLaunchKernelGGL(permuted_key_kernel, dim3((unsigned)((nnz + kSlice - 1) / kSlice)), dim3(kThreads), 0, 0, n, nnz,
+        hipLaunchKernelGGL(permuted_key_kernel, dim3((unsigned)((nnz + kSlice - 1) / kSlice)), dim3(kThreads), 0, setup_stream(), n, nnz,
                            m.rowptr, m.colidx, d_perm, bits, key);
         TRY_GPU(hipGetLastError());
         TRY_GPU(sort_pairs(key, sorted, reinterpret_cast<const uint32_t *>(ids), reinterpret_cast<uint32_t *>(order), nnz,
                            2 * bits, false, sc));
-        hipLaunchKernelGGL(permuted_cols_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, 0, nnz, sorted, bits, ci, flag);
+        hipLaunchKernelGGL(permuted_cols_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, setup_stream(), nnz, sorted, bits, ci, flag);
         TRY_GPU(hipGetLastError());
     }
-    TRY_GPU(hipMemcpy(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost));
+    TRY_GPU(setup_copy(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost));
     if (bad) return kUseHost; // a column twice in a row: their order is the host sort's business
     // (an output in the place of the values is not written before they are read)
     auto in_values = [&](const int32_t *out, int64_t count) {
@@ -736,7 +736,7 @@ int permute_gpu(int64_t n, const int32_t *rowptr, const int32_t *colidx, const f
     TRY_GPU(copy_to_host(out_rowptr, rp, sizeof(int32_t) * (n + 1)));
     TRY_GPU(copy_to_host(out_colidx, ci, sizeof(int32_t) * nnz));
     TRY_GPU(values.wait());
-    hipLaunchKernelGGL(permuted_vals_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, 0, nnz, order, va, va_out);
+    hipLaunchKernelGGL(permuted_vals_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, setup_stream(), nnz, order, va, va_out);
     TRY_GPU(hipGetLastError());
     TRY_GPU(copy_to_host(out_vals, va_out, sizeof(float) * nnz));
     return PCSR_OK;

@@ -160,9 +160,9 @@ hipError_t sort_pairs_u32(const uint32_t *kin, uint32_t *kout, const uint32_t *v
     if (n < kSortLeast || n > kSortMost) {
         size_t bytes = 0;
         void *tmp = nullptr;
-        hipError_t e = hipcub::DeviceRadixSort::SortPairs(nullptr, bytes, kin, kout, vin, vout, (int)n, 0, bits);
+        hipError_t e = hipcub::DeviceRadixSort::SortPairs(nullptr, bytes, kin, kout, vin, vout, (int)n, 0, bits, setup_stream());
         if (e == hipSuccess) e = sc.alloc(&tmp, bytes);
-        return e == hipSuccess ? hipcub::DeviceRadixSort::SortPairs(tmp, bytes, kin, kout, vin, vout, (int)n, 0, bits) : e;
+        return e == hipSuccess ? hipcub::DeviceRadixSort::SortPairs(tmp, bytes, kin, kout, vin, vout, (int)n, 0, bits, setup_stream()) : e;
     }
     SortPass p;
     p.n = n;
@@ -185,10 +185,10 @@ hipError_t sort_pairs_u32(const uint32_t *kin, uint32_t *kout, const uint32_t *v
         const bool last = (passes - 1 - i) % 2 == 0; // passes end in kout / vout
         p.kout = last ? kout : ktmp;
         p.vout = last ? vout : vtmp;
-        hipLaunchKernelGGL(sort_count_kernel, dim3(p.tiles), dim3(kThreads), 0, 0, p);
+        hipLaunchKernelGGL(sort_count_kernel, dim3(p.tiles), dim3(kThreads), 0, setup_stream(), p);
         hipLaunchKernelGGL(sort_tiles_kernel, dim3(((1 << p.bits) + kThreads / 64 - 1) / (kThreads / 64)), dim3(kThreads), 0,
-                           0, 1 << p.bits, p.tiles, p.counts, p.totals);
-        hipLaunchKernelGGL(sort_scatter_kernel, dim3(p.tiles), dim3(kThreads), 0, 0, p);
+                           setup_stream(), 1 << p.bits, p.tiles, p.counts, p.totals);
+        hipLaunchKernelGGL(sort_scatter_kernel, dim3(p.tiles), dim3(kThreads), 0, setup_stream(), p);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -261,7 +261,10 @@ __global__ void __launch_bounds__(kTurnThreads) __attribute__((amdgpu_waves_per_
     if constexpr (!SECOND) {
 #pragma unroll
         for (int k = 0; k < kTurnItems; ++k) // (only now: the registers)
-            if (mine + k * 64 < n) val[k] = a.vals[tile.begin + mine + k * 64];
+            if (mine + k * 64 < n) {
+                const int64_t t = tile.begin + mine + k * 64;
+                val[k] = a.vals ? a.vals[t] : __int_as_float((int)t);
+            }
         in_order([&](int k) { return row[k]; }, [&](int k, unsigned x) { a.mid_key[at[k]] = high[k] | x; });
     }
     in_order([&](int k) { return __float_as_uint(val[k]); },
@@ -277,7 +280,29 @@ __global__ void __launch_bounds__(kThreads) turn_rowptr_kernel(int64_t n_cols, i
     rowptr[c] = c == n_cols ? (int32_t)nnz : offsets[(c >> low_bits) * tiles + first[c & ((1 << low_bits) - 1)]];
 }
 
+// t_vals[i] = vals[place i]; its first content are the places.  12 M nonzeros of 500-node communities: 50 us.
+__global__ void __launch_bounds__(kThreads) turned_values_kernel(int64_t nnz, const float *vals, float *t_vals)
+{
+    const int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+    if (i + 4 <= nnz) {
+        int4u at = *reinterpret_cast<const int4u *>(t_vals + i);
+        float4u v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = vals[at[k]];
+        *reinterpret_cast<float4u *>(t_vals + i) = v;
+    } else {
+        for (int64_t k = i; k < nnz; ++k) t_vals[k] = vals[__float_as_int(t_vals[k])];
+    }
+}
+
 } // namespace
+
+hipError_t turned_values(int64_t nnz, const float *d_vals, float *t_vals)
+{
+    if (nnz <= 0) return hipSuccess;
+    hipLaunchKernelGGL(turned_values_kernel, dim3(blocks_for((nnz + 3) / 4)), dim3(kThreads), 0, setup_stream(), nnz, d_vals, t_vals);
+    return hipGetLastError();
+}
 
 bool transpose_in_two_passes(int64_t n_rows, int64_t n_cols, int64_t nnz)
 {
@@ -315,10 +340,10 @@ int transpose_two_passes(int64_t n_rows, int64_t n_cols, int64_t nnz, const int3
     HIP_TRY(sc.alloc((void **)&sums2, sizeof(int32_t) * n2));
     HIP_TRY(sc.alloc((void **)&first, sizeof(int32_t) << kTurnDigit));
     HIP_TRY(sc.alloc((void **)&table, sizeof(int2) * tiles2));
-    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes1, counts1, sums1, (int)n1));
-    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes2, counts2, sums2, (int)n2));
+    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes1, counts1, sums1, (int)n1, setup_stream()));
+    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes2, counts2, sums2, (int)n2, setup_stream()));
     HIP_TRY(sc.alloc(&tmp, bytes1 > bytes2 ? bytes1 : bytes2));
-    HIP_TRY(hipMemsetAsync(table, 0, sizeof(int2) * tiles2, nullptr)); // tiles past the last are empty
+    HIP_TRY(hipMemsetAsync(table, 0, sizeof(int2) * tiles2, setup_stream())); // tiles past the last are empty
     const size_t lds1 = sizeof(int32_t) * std::max(kTurnTile, kTurnWaves << a.low_bits);
     const size_t lds2 = sizeof(int32_t) * std::max(kTurnTile, kTurnWaves << a.high_bits);
     // more than 64 KB of LDS in all has to be allowed
@@ -328,27 +353,27 @@ int transpose_two_passes(int64_t n_rows, int64_t n_cols, int64_t nnz, const int3
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
     a.tiles = tiles1;
     a.counts = counts1;
-    hipLaunchKernelGGL(turn_count_kernel<false>, dim3(tiles1), dim3(kTurnThreads), 0, 0, a);
+    hipLaunchKernelGGL(turn_count_kernel<false>, dim3(tiles1), dim3(kTurnThreads), 0, setup_stream(), a);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tmp, bytes1, counts1, sums1, (int)n1));
+    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tmp, bytes1, counts1, sums1, (int)n1, setup_stream()));
     a.counts = sums1;
-    hipLaunchKernelGGL(turn_scatter_kernel<false>, dim3(tiles1), dim3(kTurnThreads), lds1, 0, a);
+    hipLaunchKernelGGL(turn_scatter_kernel<false>, dim3(tiles1), dim3(kTurnThreads), lds1, setup_stream(), a);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(turn_tiles_kernel, dim3(1), dim3(1 << kTurnDigit), 0, 0, a, sums1, tiles1, table, first);
+    hipLaunchKernelGGL(turn_tiles_kernel, dim3(1), dim3(1 << kTurnDigit), 0, setup_stream(), a, sums1, tiles1, table, first);
     HIP_TRY(hipGetLastError());
     a.tiles = tiles2;
     a.table = table;
     a.counts = counts2;
-    hipLaunchKernelGGL(turn_count_kernel<true>, dim3(tiles2), dim3(kTurnThreads), 0, 0, a);
+    hipLaunchKernelGGL(turn_count_kernel<true>, dim3(tiles2), dim3(kTurnThreads), 0, setup_stream(), a);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tmp, bytes2, counts2, sums2, (int)n2));
+    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tmp, bytes2, counts2, sums2, (int)n2, setup_stream()));
     a.counts = sums2;
-    hipLaunchKernelGGL(turn_scatter_kernel<true>, dim3(tiles2), dim3(kTurnThreads), lds2, 0, a);
+    hipLaunchKernelGGL(turn_scatter_kernel<true>, dim3(tiles2), dim3(kTurnThreads), lds2, setup_stream(), a);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(turn_rowptr_kernel, dim3(blocks_for(n_cols + 1)), dim3(kThreads), 0, 0, n_cols, nnz, a.low_bits, tiles2,
+    hipLaunchKernelGGL(turn_rowptr_kernel, dim3(blocks_for(n_cols + 1)), dim3(kThreads), 0, setup_stream(), n_cols, nnz, a.low_bits, tiles2,
                        sums2, first, t_rowptr);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(nullptr));
+    HIP_TRY(setup_wait());
     return PCSR_OK;
 }
 

@@ -442,32 +442,32 @@ int windows_device(int64_t M, int64_t n_cols, int32_t win, const int32_t *d_rowp
     HIP_TRY(sc.alloc((void **)&a.start, sizeof(int32_t) * n_seg * kSegBlocks));
     HIP_TRY(sc.alloc((void **)&a.count, sizeof(int32_t) * (n_seg + 1)));
     HIP_TRY(sc.alloc((void **)&d_tot, sizeof(Totals)));
-    HIP_TRY(hipMemsetAsync(d_tot, 0, sizeof(Totals), nullptr));
-    HIP_TRY(hipMemsetAsync(a.count, 0, sizeof(int32_t) * (n_seg + 1), nullptr));
+    HIP_TRY(hipMemsetAsync(d_tot, 0, sizeof(Totals), setup_stream()));
+    HIP_TRY(hipMemsetAsync(a.count, 0, sizeof(int32_t) * (n_seg + 1), setup_stream()));
     a.hits = &d_tot->hits;
     a.gave_up = &d_tot->gave_up;
-    hipLaunchKernelGGL(window_cut_kernel, dim3((unsigned)n_seg), dim3(kCutThreads), 0, 0, a);
+    hipLaunchKernelGGL(window_cut_kernel, dim3((unsigned)n_seg), dim3(kCutThreads), 0, setup_stream(), a);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(window_own_kernel, dim3((unsigned)n_seg, kOwnGroups), dim3(kCutThreads), 0, 0, a);
+    hipLaunchKernelGGL(window_own_kernel, dim3((unsigned)n_seg, kOwnGroups), dim3(kCutThreads), 0, setup_stream(), a);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(window_scan_kernel, dim3(1), dim3(1024), 0, 0, (int)n_seg, a.count);
+    hipLaunchKernelGGL(window_scan_kernel, dim3(1), dim3(1024), 0, setup_stream(), (int)n_seg, a.count);
     HIP_TRY(hipGetLastError());
     int32_t nb = 0;
-    HIP_TRY(hipMemcpyAsync(&nb, a.count + n_seg, sizeof(nb), hipMemcpyDeviceToHost, nullptr));
-    HIP_TRY(hipMemcpy(&tot, d_tot, sizeof(tot), hipMemcpyDeviceToHost));
+    HIP_TRY(setup_copy(&nb, a.count + n_seg, sizeof(nb), hipMemcpyDeviceToHost));
+    HIP_TRY(setup_copy(&tot, d_tot, sizeof(tot), hipMemcpyDeviceToHost));
     if (tot.gave_up) return PCSR_E_UNSUPPORTED;
     int32_t *win_ptr = nullptr, *win_start = nullptr, *lo = nullptr, *hi = nullptr;
     HIP_TRY(sc.alloc((void **)&win_ptr, sizeof(int32_t) * (nb + 1)));
     HIP_TRY(sc.alloc((void **)&win_start, sizeof(int32_t) * (nb + 1)));
     HIP_TRY(sc.alloc((void **)&lo, sizeof(int32_t) * (M + 1)));
     HIP_TRY(sc.alloc((void **)&hi, sizeof(int32_t) * (M + 1)));
-    hipLaunchKernelGGL(window_compact_kernel, dim3((unsigned)n_seg), dim3(kThreads), 0, 0, a.ptr_end, a.start, a.count,
+    hipLaunchKernelGGL(window_compact_kernel, dim3((unsigned)n_seg), dim3(kThreads), 0, setup_stream(), a.ptr_end, a.start, a.count,
                        win_ptr, win_start);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(window_runs_kernel, dim3((unsigned)nb), dim3(kThreads), 0, 0, win_ptr, win_start, win, d_rowptr,
+    hipLaunchKernelGGL(window_runs_kernel, dim3((unsigned)nb), dim3(kThreads), 0, setup_stream(), win_ptr, win_start, win, d_rowptr,
                        d_colidx, lo, hi);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(nullptr));
+    HIP_TRY(setup_wait());
     out->ptr = win_ptr;
     out->start = win_start;
     out->lo = lo;

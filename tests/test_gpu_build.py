@@ -151,3 +151,51 @@ def test_one_wrong_column_is_found_wherever_it_is(where):
     assert _device_build_fails(n, m, pointer, ci)
     pointer[row] = -3
     assert _device_build_fails(n, m, pointer, ci)
+
+
+def _same_handle(a, b):
+    assert pc.pcsr_format(a) == pc.pcsr_format(b)
+    x, y = pc.pcsr_export(a), pc.pcsr_export(b)
+    assert x.keys() == y.keys()
+    for k in x:
+        assert np.array_equal(np.asarray(x[k]).view(np.uint32) if k == "val" else x[k],
+                              np.asarray(y[k]).view(np.uint32) if k == "val" else y[k]), k
+
+
+# both directions at once: values on a thread of their own from 4 MB on (1,048,576 nonzeros), the transpose in two passes from 262,144 on
+# and up to 2^20 columns, on the host below 10,000; from device memory too, and from four threads
+@pytest.mark.parametrize("rows,cols,nnz", [(301, 257, 9000), (3001, 9001, 12000), (20001, 15013, 300000), (20001, 15013, 1048575),
+                                           (40001, 30011, 1048577), (30011, (1 << 20) + 5, 1200000), (70001, 513, 2000003)])
+@pytest.mark.parametrize("params", [None, dict(V=1), dict(V=2), dict(V=1, S=1, SG=8, flags=pc.PCSR_FLAG_COLUMN_ORDER)])
+@pytest.mark.parametrize("threads", [1, 4])
+def test_both_directions_at_once(rows, cols, nnz, params, threads):
+    from concurrent.futures import ThreadPoolExecutor
+
+    from paper_2605_15695_amd import binding
+
+    rng = np.random.default_rng(nnz + rows)
+    key = np.unique(rng.integers(0, rows * cols, int(nnz * (1.02 + 0.6 * nnz / (rows * cols)))))
+    key = key[np.sort(rng.permutation(key.shape[0])[:nnz])]
+    rp = np.searchsorted(key, np.arange(rows + 1) * cols).astype(np.int32)
+    ci, va = (key % cols).astype(np.int32), rng.standard_normal(key.shape[0]).astype(np.float32)
+    forward, backward = (rows, cols, rp, ci, va), (cols, rows, *pc.pcsr_transpose_csr(rows, cols, rp, ci, va))
+
+    def alone(m):
+        p = pc.make_params(**params) if params is not None else pc.pcsr_select(pc.pcsr_features(*m[:4]), 24)
+        if params is None:
+            p.lanes_per_row = p.vec = p.rep = 0
+        p.flags |= pc.PCSR_FLAG_GPU_BUILD
+        return pc.pcsr_build(*m, p)
+
+    want = alone(forward), alone(backward)
+
+    def one(on_device):
+        arrays = [torch.from_numpy(x).cuda() for x in (rp, ci, va)] if on_device else (rp, ci, va)
+        torch.cuda.synchronize()
+        return binding.pcsr_operator_build(rows, cols, *arrays, pc.make_params(**params) if params is not None else None, 24, True)
+
+    with ThreadPoolExecutor(threads) as pool:
+        for made in pool.map(one, [False, True] * threads):
+            for h, w in zip(made, want):
+                _same_handle(h, w)
+                h.close()
