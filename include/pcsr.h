@@ -70,6 +70,11 @@ enum {
                                   of the search does not fit the flag does nothing               */
     PCSR_FLAG_FAR_OFFSETS = 512, /* rows of B are addressed in 64 bits whatever its size, as those of a B of more than
                                   0xe0000000 bytes always are.  C is the same bits either way: for tests and timing    */
+    PCSR_FLAG_COLUMN_BANDS = 1024, /* V = 1, S = 0, built on the GPU, no col_window: products may walk the rows in up to 12 bands of
+                                  columns, one after the other, where that is faster (a band of B that L2 holds); the
+                                  handle keeps 44 bytes a row for it, nothing if that does not fit.  The sums of a row's
+                                  bands are added in ascending order, the same bits on every run.  The host builder
+                                  ignores it, and with CLUSTER_IF_USEFUL it does nothing where communities are found */
     PCSR_FLAG_CLUSTER_WINDOWS = 1 << 28, /* with CLUSTER_IF_USEFUL, and set by pcsr_select where one
                                   product pays for it: a second copy of the nonzeros (8 bytes each,
                                   for as long as the handle lives) by which products of 64 columns

@@ -24,6 +24,7 @@ PCSR_FLAG_COLUMN_ORDER = 64
 PCSR_FLAG_WINDOW_IF_USEFUL = 128
 PCSR_FLAG_CLUSTER_IF_USEFUL = 256
 PCSR_FLAG_FAR_OFFSETS = 512
+PCSR_FLAG_COLUMN_BANDS = 1024
 PCSR_FLAG_CLUSTER_WINDOWS = 1 << 28
 PCSR_N_FEATURES = 17
 FEATURE_NAMES = ("n", "n_hat", "nnz", "delta", "d", "d_hat", "d_max", "CV", "CV_hat",

@@ -96,6 +96,7 @@ struct pcsr_handle_s {
     int32_t *d_item_slot = nullptr;   // per item: workspace slot, -1 for a sole item (S only)
     int32_t *d_sched = nullptr;       // column-ordered schedule: 4 int32 per launch position
     int32_t *d_split_slot = nullptr;  // their first workspace slots (n_split + 1 entries)
+    int32_t *d_bands = nullptr;       // PCSR_FLAG_COLUMN_BANDS: where the rows' columns pass into each band but the first
     int32_t *d_long = nullptr;        // positions in d_split of panels with more than kLongPanelSlots items
     int64_t n_long = 0;
     int32_t *d_win = nullptr;     // window start per item block
@@ -121,7 +122,7 @@ void release_device(pcsr_handle_t h)
 {
     void *const all[] = {h->d_rowptr, h->d_colidx,     h->d_val,  h->d_trow, h->d_split,   h->d_item_slot, h->d_sched,
                          h->d_split_slot, h->d_long, h->d_win,  h->d_win_ptr, h->d_win_lo, h->d_win_hi, h->d_ws,
-                         h->win.rowptr, h->win.colidx, h->win.val, h->win.rows, h->win.ptr, h->win.hi};
+                         h->win.rowptr, h->win.colidx, h->win.val, h->win.rows, h->win.ptr, h->win.hi, h->d_bands};
     // the blocks are handed out again at once, so nothing may still be using them
     const bool idle = h->device >= 0 && pcsr::pool_quiesce(h->device);
     for (void *p : all) idle ? pcsr::pool_free(p) : pcsr::pool_release(p);
@@ -129,6 +130,7 @@ void release_device(pcsr_handle_t h)
     h->d_item_slot = h->d_sched = h->d_split_slot = h->d_long = h->d_win_ptr = nullptr;
     h->d_win_lo = h->d_win_hi = nullptr;
     h->d_val = h->d_ws = nullptr;
+    h->d_bands = nullptr;
     h->ws_bytes = 0;
     h->win = {};
 }
@@ -426,7 +428,8 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     int rc = pcsr::build_device(n_rows, n_cols, nnz, rowptr, colidx, vals, prm.V, prm.S, prm.SG, prm.omega,
                                 !(prm.flags & PCSR_FLAG_NO_VALIDATE), column_order,
                                 (prm.flags & PCSR_FLAG_CLUSTER_IF_USEFUL) && !prm.col_window,
-                                (prm.flags & PCSR_FLAG_CLUSTER_WINDOWS) != 0, known, late, &db, &herr);
+                                (prm.flags & PCSR_FLAG_CLUSTER_WINDOWS) != 0,
+                                (prm.flags & PCSR_FLAG_COLUMN_BANDS) && !prm.col_window, known, late, &db, &herr);
     h->host.n_rows = n_rows;
     h->host.n_cols = n_cols;
     h->host.nnz = nnz;
@@ -447,6 +450,7 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     h->d_sched = db.sched;
     h->d_split_slot = db.split_slot;
     h->d_long = db.long_list;
+    h->d_bands = db.bands;
     h->n_split = db.n_split;
     h->n_split_items = db.n_split_items;
     h->n_long = db.n_long;
@@ -871,6 +875,53 @@ static int spmm_check(pcsr_handle_t h, const float *B, float *C, int32_t K, pcsr
     return PCSR_OK;
 }
 
+// How many bands of columns a product of scattered rows is best walked in (a divisor of kColumnBands), and the us that they save.  A
+// band of B that an XCD's L2 holds is gathered from there; each band of several costs a launch, a look at every row and a pass over
+// C.  The rates are those that fit 1,200 measured times best (uniform columns, 14 to 300 a row, 40,000 to 1,000,000 rows, 6 to 256
+// columns, 1 to 12 bands): the number picked is 0.9 % off the best of them on average and 14 % at most, and never over 1.3 % off one
+// band.  Us in one band and in those picked: rows of 134, 300,000 of them, K = 16 667 and 366 (6 bands), K = 32 706 and 527 (6), K = 64 1459 and
+// 1197 (6); of 60, 150,000, K = 16 118 and 76 (3), K = 48 291 and 211 (6); of 60, 400,000, K = 10 462 and 235 (4), K = 64 908 in one; of 30,
+// 400,000, K = 9 202 and 145 (3), K = 16 193 in one; of 300, 100,000, K = 32 385 and 224 (4).
+static int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, int32_t tile, double *saved)
+{
+    const double slices = (K + tile - 1) / tile, row = 4.0 * K / slices;
+    const double grain = (double)std::min(128, (4 * K) & -(4 * K)); // rows of B begin at multiples of it
+    const double miss = std::ceil((row + 128.0 - grain) / 32.0) / 4.0 / 39e3, hit = std::max(1.0 / 140e3, row / 31e6);
+    auto us = [&](int m) {
+        const double near = std::cbrt(std::min(1.0, 3.5e6 * m / std::max(n_cols * row, 1.0)));
+        const double passes = m * (1.7 + n_rows * 1e-3 * (slices * (0.006 + 0.00106 * lanes) + 0.00133 * K));
+        return slices * nnz * (near * hit + (1.0 - near) * miss) + (m > 1 ? passes : 0.0);
+    };
+    int best = 1;
+    // Rows of less than 256 are better added up in fewer than 12 parts, and in tiles of whole rows by whole and half wavefronts, whose
+    // sums were of 8 before, in parts of 20 and more.
+    const double least = K > 64 && K % 32 != 0 ? 20.0 : 0.0;
+    for (const int m : {2, 3, 4, 6, 12})
+        if (nnz >= std::max(m < 12 ? 0.0 : 256.0, least * m) * n_rows && us(m) < (best > 1 ? 0.98 : 1.0) * us(best)) best = m;
+    *saved = us(1) - us(best);
+    return *saved > 0.03 * us(1) ? best : 1;
+}
+
+// Bands leave their sums in C, where the tail of one pass has its rows read before they are written.
+static bool tail_reads_c(const pcsr::Epilogue &e, const float *C, int64_t n_rows, int32_t K)
+{
+    auto meets = [&](const float *p, int64_t count) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p), c = reinterpret_cast<uintptr_t>(C);
+        return p && a < c + 4u * (uintptr_t)n_rows * (uintptr_t)K && c < a + 4u * (uintptr_t)count;
+    };
+    return e.on && (meets(e.self, n_rows * K) || meets(e.mask, n_rows * K) || meets(e.bias, K) || meets(e.self_eps, 1));
+}
+
+// 0: the kernel for bands does not have the shape.  (A product in one band is that kernel's, too: it adds up long rows more exactly.)
+static int band_passes(pcsr_handle_t h, int32_t K, const pcsr::LaunchShape &ls, const pcsr::Epilogue &epi, const float *C)
+{
+    double saved;
+    if (ls.window || ls.ipg > 1 || !pcsr::band_kernel_exists(ls.k_lpr, ls.k_vec, ls.k_rep, epi.on)) return 0;
+    if (tail_reads_c(epi, C, h->host.n_rows, K)) return 1;
+    return band_count((double)h->host.n_rows, (double)h->host.n_cols, (double)h->host.nnz, K, ls.k_lpr, ls.k_lpr * ls.k_vec * ls.k_rep,
+                      &saved);
+}
+
 // Enqueues the kernels of one SpMM.  ws: workspace of at least workspace_need(h, K) bytes
 // (ignored when that is 0).
 static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, const pcsr::LaunchShape &ls,
@@ -927,6 +978,21 @@ static int spmm_enqueue(pcsr_handle_t h, const float *B, float *C, int32_t K, co
         a.rows = h->win.rows;
     }
     a.epi = epi;
+    a.band = 0;
+    const int passes = h->d_bands ? band_passes(h, K, ls, epi, C) : 0;
+    if (passes > 0) {
+        const int step = pcsr::kColumnBands / passes;
+        const int64_t n = h->host.n_rows;
+        for (int p = 0; p < passes; ++p) {
+            const bool first = p == 0, last = p == passes - 1;
+            a.band = pcsr::kBandOn | (first ? pcsr::kBandFirst : 0) | (last ? pcsr::kBandLast : 0) | (passes > 3 ? pcsr::kBandSums64 : 0);
+            a.rowptr = first ? h->d_rowptr : h->d_bands + (p * step - 1) * n;
+            a.trow = last ? h->d_rowptr + 1 : h->d_bands + ((p + 1) * step - 1) * n;
+            a.epi = last ? epi : pcsr::Epilogue();
+            if (!hip_ok(pcsr::launch_spmm(h->host.V, h->host.S, ls, a, s))) return PCSR_E_HIP;
+        }
+        return PCSR_OK;
+    }
     if (!hip_ok(pcsr::launch_spmm(h->host.V, h->host.S, ls, a, s))) return PCSR_E_HIP;
     if (two_pass) {
         if (!hip_ok(pcsr::launch_reduce_split(h->d_split, h->d_split_slot, h->n_split, h->d_long, h->n_long, h->host.V, ws, C,
@@ -1215,20 +1281,38 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // K = 64 the same column-ordered schedule, with items of 32, turns the split into a
     // column partition of A, each XCD gathering from its own range of B rows (uniform
     // random columns, 96 per row, K = 128: 1.5x; 48 per row, K = 256: 1.13x; at 32 per
-    // row the second items are too short and it loses 15 %).  Narrower B rows are cached
-    // well enough as they are; there pairing rows (V = 2) wins, by doubling the gathers a
-    // lane group has in flight.  Rows with local columns lose up to half their speed under
-    // the column order (it gives up the reuse between neighbouring rows).
+    // row the second items are too short and it loses 15 %).  Narrower rows of B
+    // are walked in bands of columns, or paired (below).  Rows with local columns lose up to half
+    // their speed under the column order (it gives up the reuse between neighbouring rows).
     const bool scattered = f[16] < 4.0 * 1025.0 / (n > 1.0 ? n : 1.0);
+    // Such rows walked in bands of columns: where one product saves what the handle's table of them costs its build (300,000 rows of
+    // 134: 183 -> 263 us, 60,000 of 140: 78 -> 99, 1,000,000 of 44: 187 -> 336), or where the other choice is the far dearer build of pairs.
+    const int band_lanes = K <= 16 || (K > 32 && K <= 64) || (K > 64 && K % 32 == 0) ? 16 : K <= 128 ? 32 : 64;
+    const int band_tile = K <= 32 ? band_lanes : 4 * band_lanes;
+    double saved = 0.0;
+    const bool fills_paired = n * (double)(K < 32 ? 4 : 8) / 128.0 >= 3500.0;
+    const bool paired_else =
+        d_hat >= 40.0 && fills_paired && K > 16 && K < 64 && (K > 32 || n * (double)K * 4.0 <= 16.0 * 1048576.0);
+    const bool banded = !skewed && !windowed && scattered && d_hat >= 12.0 && K > 8 &&
+                        band_count(n, n, f[2], K, band_lanes, band_tile, &saved) > 1 &&
+                        (paired_else || saved > 12.0 + 1e-6 * f[2] + 1e-4 * n);
     // K of 17..32 with scattered columns and a B beyond 16 MB (rows gathered from the
-    // memory side, not from L2): one dword per lane again, a row per half wavefront
+    // memory side, not from L2), or in bands: one dword per lane again, a row per half wavefront
     // (uniform random columns, 16 to 64 per row, 150,000 rows or more: 7-24 % faster than
-    // the best 16-byte shape; slower when B is small or the columns are local).
+    // the best 16-byte shape; slower when B is small or the columns are local.  In bands: 300,000 rows of 134, K = 32: 527 us, 8 lanes
+    // of 16 bytes 580).
     const bool wide_scatter = !skewed && scattered && d_hat >= 12.0 && K > 16 && K <= 32 &&
-                              n * (double)K * 4.0 > 16.0 * 1048576.0;
+                              (banded || n * (double)K * 4.0 > 16.0 * 1048576.0);
     if (wide_scatter) vec = 1;
     const bool long_uniform = !skewed && !windowed && !wide_scatter && d_hat >= 40.0 && scattered;
-    const bool long_uniform_wide = long_uniform && K >= 64;
+    // But not where a slice of B is over 20 MB, 2.5 times what the L2s hold together: the order then saves less than
+    // the parts' sums cost, and unsplit rows, in bands or not, take 0.77-0.95 of the time (rows of 44 to 300, 100,000 to 1,000,000 of them, K = 64
+    // to 256; rows of 90, 100,000 of them, K = 128: 485 -> 350 us, of 44, 1,000,000: 3937 -> 3087; slices of 15 MB 0.92-1.10, of 10 MB
+    // 0.95-1.15).  Rows over kClusterItem stay split, as communities among them would have to be, and so do widths over 256 that
+    // are no multiple of 32, whose tile no band kernel has.
+    const bool split_pays =
+        n * 4.0 * std::min(K, band_tile) <= 20e6 || d_max > pcsr::kClusterItem || (K > 256 && K % 32 != 0);
+    const bool long_uniform_wide = long_uniform && K >= 64 && split_pays;
     p.S = (skewed || long_uniform_wide) ? 1 : 0;
     // Items of 32 vectors where uniform rows are split (of 64: 2-31 % slower on rows of 70 and more,
     // 9-12 % faster on uniform rows of 48).  Of 64 for power-law
@@ -1247,10 +1331,12 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // puts the break-even near 30 % padding; on MI355X clique-like inputs win at 11 %
     // padding (1.23x at K=128) and lose at 27 %, because adjacent rows of one wavefront
     // already share their B lines in L1.  Power-law inputs: V = 2 ties or loses in the sweeps.
-    // Long scattered rows at K below 64 (above): paired as well, unless the matrix is so small
-    // that halving the number of work items leaves wavefront slots empty (30,000 rows of
-    // 160, K = 32: V = 2 runs at 0.55 of V = 1).
-    const bool pair_long = long_uniform && n * (double)(K < 32 ? 4 : 8) / 128.0 >= 3500.0;
+    // Long scattered rows of a B that needs no bands: paired as well below K = 64, which doubles the gathers a lane group has in
+    // flight, unless the matrix is so small that halving the number of work items leaves wavefront slots empty (30,000 rows of
+    // 160, K = 32: V = 2 runs at 0.55 of V = 1), and not at K = 9 to 16 or with a B beyond 16 MB: there V = 2 takes 0.98-1.08 of the time
+    // and 5 to 9 times the build (1,000,000 rows of 44, K = 48: 1649 us for 1534, 1646 to build for 187).
+    const bool pairs = long_uniform && K < 64 && fills_paired;
+    const bool pair_long = pairs && !banded && (K <= 8 || (K > 16 && n * (double)K * 4.0 <= 16.0 * 1048576.0));
     // Rows of C of 48 or 64 bytes are written one by one by a pair's lanes, part lines each, where single rows' lane groups
     // fill lines together: V = 1 takes 0.59-0.99 of V = 2 (with a self term 0.50-1.03, and a mask 0.58-0.99) on road-like graphs of 2 to 7
     // a row and uniform ones of 3 to 6, 300,000 and 2,000,000 rows.  C below 8 MB (120,000 rows) 0.85-1.01, products of under 10 us.
@@ -1297,9 +1383,13 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // Scattered columns, rows of 8 to 40, K from 64: a 64-column slice per half wavefront
     // with dwordx2 loads (uniform random columns, 8 to 32 per row, K = 64 and 128: 3-7 %
     // over the best 16-byte shape; local columns keep the 16-byte shapes).
-    if (!skewed && !windowed && !long_uniform && scattered && d_hat >= 8.0 && K >= 64 && K % 2 == 0) {
+    if (!skewed && !windowed && !p.S && !banded && scattered && d_hat >= 8.0 && K >= 64 && K % 2 == 0) {
         lpr = 32;
         vec = 2;
+        rep = 1;
+    }
+    if (banded && K >= 64) { // (300,000 rows of 134 in bands, K = 128: 2212 us, that shape 2342)
+        lpr = 16;
         rep = 1;
     }
     // K of 17..32, rows of 32 and more that are neither split nor paired: 16 lanes of one
@@ -1322,7 +1412,7 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     if (K > 64 && K % 32 != 0 && (p.S || scattered || K % 4 != 0)) {
         // one tile for the whole row instead of slices of 64: 1.06-1.36x (0.96x on rows of 96, K = 300)
         wide_shape(K, 64, &wide, &wide_rep);
-    } else if (K > 32 && K <= 64 && K % 32 != 0 && !p.S && scattered && d_hat >= 8.0 && b_bytes > 24.0 * 1048576.0) {
+    } else if (K > 32 && K <= 64 && K % 32 != 0 && !p.S && !banded && scattered && d_hat >= 8.0 && b_bytes > 24.0 * 1048576.0) {
         // half a wavefront per scattered row: 0-6 % where B is gathered from the memory side, 20-30 %
         // slower where L2 holds it (uniform columns, 9 to 200 per row; on a par at 20-25 MB)
         wide = 32;
@@ -1342,6 +1432,8 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     p.waves_per_wg = p.S ? 4 : (d_hat >= 16.0 && !pair_long ? 4 : 2);
     p.items_per_group = 1;
     p.col_window = 0;
+    // (Also where long rows are neither split nor paired but in one band: for its sums.)
+    if ((banded || (pairs && !pair_long) || (long_uniform && K >= 64)) && p.V == 1 && !p.S) p.flags |= PCSR_FLAG_COLUMN_BANDS;
     // Column-window blocking: rows that gather from a neighbourhood of their own index (most
     // nonzeros within 512 columns of the diagonal) and are long enough that every staged row
     // of B is used dozens of times.  A 500-node community graph of degree 48 runs 1.1x

@@ -21,6 +21,7 @@ struct DeviceBuild {
     int64_t P = 0, M = 0, nnz_v = 0, n_split = 0, n_split_items = 0, n_long = 0, max_item_len = 0;
     int32_t S = 0, SG = 0;
     bool vals_due = false;  // val is still to be filled, once `late` is there
+    int32_t *bands = nullptr; // band_ends of the rows (or null), kColumnBands - 1 of them one after the other
     bool clustered = false; // the schedule runs the rows community by community
     struct {                // the arrays of a product with windows of communities (blocks 0: none)
         int32_t *rowptr = nullptr, *colidx = nullptr, *rows = nullptr, *ptr = nullptr, *hi = nullptr;
@@ -37,13 +38,15 @@ struct DeviceBuild {
 // known: what the check counts, of arrays that have been checked (null: they are checked if `validate`, and counted).
 // clusters: where the rows turn out to form communities, S = 1 with items of kClusterItem and the schedule by community;
 // windows: and, where they fit in LDS, out->win beside it.
+// bands: S = 0 and V = 1, where it stays so: out->bands, if there is memory for it.
+constexpr int kColumnBands = 12;
 constexpr int32_t kClusterItem = 1024;
 struct RowStats {
     int64_t longest, nonempty;
 };
 int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_rowptr,
                  const int32_t *d_colidx, const float *d_vals, int32_t V, int32_t S, int32_t SG,
-                 int32_t omega, bool validate, bool column_order, bool clusters, bool windows, const RowStats *known, Late *late,
+                 int32_t omega, bool validate, bool column_order, bool clusters, bool windows, bool bands, const RowStats *known, Late *late,
                  DeviceBuild *out, int *hip_err);
 
 // Whether rows share more columns than chance has them: enqueues the count of a sample on the null stream (d_out: two

@@ -17,11 +17,14 @@ struct Epilogue {
     const float *mask = nullptr;     // n_rows x K
 };
 
+// the first band, the last one, and: its vectors are added up in sums of 64, not 32
+constexpr int32_t kBandOn = 1, kBandFirst = 2, kBandLast = 4, kBandSums64 = 8;
+
 struct SpmmArgs {
     const int32_t *rowptr; // M+1, device
     const int32_t *colidx; // nnz_v, device
     const float *val;      // nnz_v * V, device
-    const int32_t *trow;   // M (S only), device
+    const int32_t *trow;   // M, device: S: the items' panels; in bands: where the rows' vectors of this band end
     const float *B;
     float *C;
     int32_t M;      // work items
@@ -43,6 +46,9 @@ struct SpmmArgs {
     int32_t outer; // long items: sums of 32 vectors are added up apart (plain walk with S), or as the window kernel says
     int32_t mean_item; // vectors of a work item on average
     int32_t far; // 1: no 32-bit offsets into B
+    // One band of columns (0: all of them): row i's vectors in it are [rowptr[i], trow[i]), and their sum is added to what the bands
+    // before left in C.
+    int32_t band; // kBand* bits
     // column-window blocking (window kernel only)
     const int32_t *win_ptr;   // item range [win_ptr[b], win_ptr[b+1]) of block b (= workgroup b)
     const int32_t *win_start; // per item block: first column of the staged window or -1
@@ -75,6 +81,8 @@ struct LaunchShape {
 bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg);
 // with an epilogue (plain walk; the batched and window kernels take one at any shape)
 bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep);
+// for a band of columns
+bool band_kernel_exists(int lpr, int vec, int rep, bool epilogue);
 bool window_kernel_exists(int V, int lpr, int vec, int rep);
 // The one shape of the kernel for windows of communities; what its first launch on a device needs done outside a capture.
 constexpr int kRowsLanes = 16, kRowsVec = 4, kRowsMost = 512;

@@ -316,6 +316,13 @@ template <int VEC> __device__ __forceinline__ void load_near4(__amdgpu_buffer_rs
 constexpr int kAsIs = 0;
 constexpr int kLongItems = 1; // balanced handles with long items (SpmmArgs::outer): sums of 32 vectors are added up apart
 constexpr int kEarlyTail = 2; // unsplit products whose tail reads the row: the self and mask rows are requested before the traversal
+// Single unsplit rows, a band of columns at a time (SpmmArgs::band), one launch each.  Scattered rows of B come from memory, at 57 G
+// lines of 128 bytes a second, unless an XCD's L2 holds them, which gives 190 G rows: the band of B that a launch reads is
+// as small as that, and the price is C read and written once more by each (uniform columns, 300,000 rows of 134, K = 16: 667 us in one, 542,
+// 437, 372, 366 and 446 in 2, 3, 4, 6 and 12).  Sums of 8 vectors are added up to 32 in up to
+// three bands, to 64 in more, before they go to the row's, which costs nothing: the rms difference from 64 bits of rows of 44, 60, 90, 134 and
+// 300 ones between 0 and 1 is 4.3 to 4.8e-8 of their sum (300: 4.8 to 5.8), 4.7 to 5.1 (5.8) by items of 32 and 5.0 to 7.1 in one sum.
+constexpr int kBands = 3;
 
 // EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
 // branch alone cost the instance <2, false, 64, 1, 2> 4 %.
@@ -383,7 +390,7 @@ spmm_kernel(SpmmArgs a)
         }
     } else {
         head = a.rowptr[item_l];
-        tail = a.rowptr[item_l + 1];
+        tail = FORM == kBands ? a.trow[item_l] : a.rowptr[item_l + 1];
     }
     if constexpr (LPR == 64) {
         head = __builtin_amdgcn_readfirstlane(head);
@@ -447,6 +454,17 @@ spmm_kernel(SpmmArgs a)
         }
     }
 
+    // What the bands before have left, requested beside the first entries; sums of 32 or 64 vectors are added to it, as OUTER below has it.
+    float before[FORM == kBands ? REP : 1][VEC];
+    if constexpr (FORM == kBands) {
+#pragma unroll
+        for (int r = 0; r < REP; ++r) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) before[r][e] = 0.0f;
+            if (!(a.band & kBandFirst) && kv[r]) load_vec<VEC>(a.C + (long)panel * K + kc[r], before[r]);
+        }
+    }
+
     // one lane's entries of the chunk that starts at `base` (zeros past the end of the range)
     auto load_entry = [&](int base, int (&c)[NH], float (&av)[NH][V]) {
 #pragma unroll
@@ -506,7 +524,8 @@ spmm_kernel(SpmmArgs a)
     float av_next[NH][V];
     load_entry(head, c_next, av_next);
     constexpr int PERIOD = CH < 32 ? 32 / CH : 1;
-    int until = PERIOD; // chunks until the next sum is put apart (the same in every lane group)
+    const int band_period = FORM == kBands && (a.band & kBandSums64) ? 64 / CH : PERIOD;
+    int until = FORM == kBands ? band_period : PERIOD; // chunks until the next sum is put apart (the same in every lane group)
     for (int base = head; base < tail; base += CH) {
         long off[NH]; // DPP: in bytes, computed once by the lane that holds the entry
         unsigned near_off[NH]; // NEAR: the same
@@ -539,7 +558,7 @@ spmm_kernel(SpmmArgs a)
         // apart, whatever the chunk.  Rows of 48 against 64 bits, rms of their sum of magnitudes: 1.67e-8, where sums
         // of a chunk of 32 and 64 lanes made it 2.23 and 2.79e-8 (items of 32 in chunks of 16: 1.82e-8).  These kernels wait on
         // memory: the additions cost nothing (250,000 rows, K = 128 262 us, K = 256 577, both as before).
-        constexpr bool FOLD = S && LPR >= 32;
+        constexpr bool FOLD = (S && LPR >= 32) || FORM == kBands;
         auto fold = [&] {
 #pragma unroll
             for (int v = 0; v < V; ++v)
@@ -641,6 +660,18 @@ spmm_kernel(SpmmArgs a)
             for (int r = 0; r < REP; ++r)
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) acc[v][r][e] += part[v][r][e];
+        if constexpr (FORM == kBands) {
+            if (--until == 0) {
+                until = band_period;
+#pragma unroll
+                for (int r = 0; r < REP; ++r)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) {
+                        before[r][e] += acc[0][r][e];
+                        acc[0][r][e] = 0.0f;
+                    }
+            }
+        }
         if constexpr (OUTER) {
             if (--until == 0) {
                 until = PERIOD;
@@ -655,6 +686,24 @@ spmm_kernel(SpmmArgs a)
     // of its panel.  An item of a panel that was split (TRow names the panel) either
     // leaves its partial rows in the workspace slot that belongs to it, for the second
     // pass to add in item order, or, without a workspace, accumulates with atomics.
+    if constexpr (FORM == kBands) {
+        static_assert(V == 1 && !S);
+        if (tail == head && !(a.band & kBandFirst) && !(EPI && (a.band & kBandLast))) return; // C is as it was
+#pragma unroll
+        for (int r = 0; r < REP; ++r) {
+            if (!kv[r]) continue;
+            float *const at = a.C + (long)panel * K + kc[r];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc[0][r][e] = before[r][e] + acc[0][r][e];
+            if (a.band & kBandLast) {
+                if constexpr (EPI) finish<VEC>(a.epi, (long)panel, a.K, kc[r], acc[0][r]);
+                store_vec<VEC>(at, acc[0][r]);
+            } else {
+                store_vec_cached<VEC>(at, acc[0][r]);
+            }
+        }
+        return;
+    }
     const bool sole = slot < 0;
     float *wrow = nullptr;
     if constexpr (S) {
@@ -1345,6 +1394,8 @@ template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn
         return nullptr;
     else if constexpr (FORM == kEarlyTail && (S || V * REP * VEC > 8))
         return nullptr;
+    else if constexpr (FORM == kBands && (S || V != 1 || REP != 1 || LPR < 8 || (VEC == 1 && LPR > 32) || (VEC == 2 && LPR != 32)))
+        return nullptr;
     else {
         // A whole wavefront to a row has its addresses in scalar registers; more repeats than these are taken only where asked for.
         if constexpr (LPR < 64 && REP <= 2)
@@ -1541,6 +1592,11 @@ bool kernel_exists(int V, int S, int lpr, int vec, int rep, int ipg)
     return pick_any(V, S, lpr, vec, rep, ipg) != nullptr;
 }
 
+bool band_kernel_exists(int lpr, int vec, int rep, bool epilogue)
+{
+    return (epilogue ? pick<true, kBands>(1, 0, lpr, vec, rep) : pick<false, kBands>(1, 0, lpr, vec, rep)) != nullptr;
+}
+
 bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep)
 {
     return pick<true>(V, S, lpr, vec, rep) != nullptr;
@@ -1578,7 +1634,10 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
     const bool near = near_enough(args) && !short_items;
     KernelFn fn;
     size_t lds = 0;
-    if (args.outer) {
+    if (args.band) {
+        fn = epi ? pick<true, kBands>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near_enough(args))
+                 : pick<false, kBands>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near_enough(args));
+    } else if (args.outer) {
         fn = epi ? pick<true, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near)
                  : pick<false, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near);
         lds = sizeof(float) * 64 * ls.waves * V * ls.k_rep * ls.k_vec; // 64 KB at most

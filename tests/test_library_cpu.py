@@ -412,6 +412,30 @@ def test_selector_proposes_the_window_only_where_the_build_keeps_it():
     h.close()
 
 
+def test_selector_walks_scattered_rows_in_bands():
+    """Where a B of scattered rows outgrows L2 and the product saves what the table costs; never for rows that are split or local."""
+    g = synth.workload("sbm_shuffled", "small")
+    f = np.array(pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx), dtype=np.float64)
+
+    def pick(n, deg, K, near=0.0, cv=0.1, d_max=None):
+        x = f.copy()
+        x[0] = x[1] = n
+        x[2], x[4], x[5], x[6], x[7], x[8], x[15], x[16] = n * deg, deg / n, deg, d_max or 2 * deg, cv, cv, 0.5, near
+        return pc.pcsr_select(x, K)
+
+    for n, deg, K, bands, shape in ((300_000, 134, 16, True, (16, 1, 1)), (300_000, 134, 32, True, (32, 1, 1)), (300_000, 134, 48, True, (16, 4, 1)),
+                                    (100_000, 90, 128, True, (16, 4, 1)), (60_000, 90, 16, False, (16, 1, 1)), (400_000, 9, 16, False, (16, 1, 1)),
+                                    (1_000_000, 30, 64, False, (32, 2, 1)), (1_000_000, 44, 128, True, (32, 2, 1))):
+        p = pick(n, deg, K)
+        assert (p.V, p.S, p.lanes_per_row, p.vec, p.rep) == (1, 0, *shape), (n, deg, K)
+        assert bool(p.flags & pc.PCSR_FLAG_COLUMN_BANDS) == bands, (n, deg, K)
+    for p in (pick(300_000, 134, 16, near=0.9), pick(300_000, 134, 16, cv=4.0, d_max=20_000), pick(40_000, 134, 64),
+              pick(300_000, 134, 128, d_max=2000), pick(300_000, 134, 300)):
+        assert not p.flags & pc.PCSR_FLAG_COLUMN_BANDS
+    # none of them asks for more alignment or a workspace where it did not, and none splits rows that were not
+    assert pick(300_000, 134, 62).vec == 2 and pick(300_000, 134, 63).vec == 1
+
+
 def test_query_kernel_reports_what_is_launched():
     """The shape that stands in where the one asked for reads rows badly; elsewhere the two queries agree."""
     shape = lambda q: (q["lanes_per_row"], q["vec"], q["rep"])  # noqa: E731

@@ -222,3 +222,28 @@ h.close()
 pc.pcsr_release_cached()
 assert fake.fake_hip_live() == 0
 """)
+
+
+def test_without_memory_for_the_bands_products_go_without(fake):
+    _run(fake, """
+checked = np.zeros(10, np.int32)                           # bad, first, last, longest, nonempty
+checked[[2, 3, 4]] = n * deg, deg, n
+flags = pc.PCSR_FLAG_GPU_BUILD | pc.PCSR_FLAG_COLUMN_BANDS
+
+
+def built():
+    fake.fake_hip_fail(0, 0)
+    fake.fake_hip_answer(0, ctypes.c_size_t(checked.nbytes), checked.ctypes.data_as(ctypes.c_void_p))
+    h = pc.pcsr_build(n, n, rowptr, colidx, vals, pc.make_params(V=1, flags=flags))
+    left = fake.fake_hip_live()
+    h.close()
+    pc.pcsr_release_cached()
+    assert fake.fake_hip_live() == 0
+    return left, fake.fake_hip_allocations()
+
+
+whole = built()
+fake.fake_hip_refuse(2 << 20, 2 << 20)                     # the table of the bands, in whole MiB
+less = built()
+assert less[0] < whole[0] and less[1] >= whole[1]
+""")
