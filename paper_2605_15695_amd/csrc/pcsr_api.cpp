@@ -50,6 +50,13 @@ int32_t checked_flags(const pcsr_params_t &p)
     return p.flags & ~kWideBits;
 }
 
+// Lanes of one dword for a row of up to 8 columns: more than it has, as a group of 16 runs to the end of its own row, not of four,
+// and broadcasts by DPP where 4 lanes shuffle.  Time of 8 and 16 lanes over 4 of the widest loads: rows of 16 to 134 that are not
+// split, K = 2, 4 and 8 0.65-0.97 and 0.48-0.94 (300,000 rows of 134, K = 4 553 us, 387 and 333; 250,000 of 48 in communities, K = 8
+// 84, 57 and 52), pairs 0.72-1.00 and 0.62-0.92; items of balanced handles 0.72-0.85 and 0.72-0.90, which take 8 (R-MAT 2^22, K = 8: 1731
+// us, 1280 and 1308).  Rows of 6 to 14 with local columns 0.96-1.7.
+int narrow_lanes(int S) { return S ? 8 : 16; }
+
 // The narrowest tile of 16-byte loads that covers a row of K columns.
 void wide_shape(int32_t K, int cap, int *lanes, int *rep)
 {
@@ -256,8 +263,13 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     if (!h_vec && !h_lpr && K > 8 && K <= 16 && h->host.win_cols == 0 &&
         h->host.nnz_v >= 8 * std::max<int64_t>(h->host.P, 1))
         vec = 1;
+    // and K of up to 8, rows of 32 and more (single rows of 18 and 27 that share their neighbours' columns 0.86-1.58 of 4 lanes' time)
+    const bool narrow = !h_vec && !h_lpr && !h_rep && K <= 8 && h->host.win_cols == 0 && h->ipg <= 1 &&
+                        h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
+    if (narrow) vec = 1;
     if (K % vec != 0) return PCSR_E_UNSUPPORTED;
     int lpr = h_lpr;
+    if (narrow) lpr = narrow_lanes(h->host.S);
     if (!lpr) {
         int need = (K + vec - 1) / vec;
         if (h->host.win_cols > 0) {
@@ -1265,13 +1277,19 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // many rows per wavefront).
     int vec = K % 4 == 0 ? 4 : (K % 2 == 0 ? 2 : 1);
     if (K > 8 && K <= 16 && d_hat >= 8.0) vec = 1;
+    const double n = f[0];
+    const bool scattered = f[16] < 4.0 * 1025.0 / (n > 1.0 ? n : 1.0); // (see below)
+    // Up to 8 the same (narrow_lanes); of scattered rows from 8 on, which wait on memory (1,000,000 rows of 9, K = 8: 160 -> 150 us).
+    // Odd widths had one dword a lane before: local rows of 15 0.95-1.05, one column of 9 to 21 a row 1.16-1.30.
+    const double least_narrow = K == 1 ? 32.0 : scattered && !skewed ? 8.0 : K % 2 ? 20.0 : 16.0;
+    const bool narrow = K <= 8 && d_hat >= least_narrow && !(skewed && K % 2);
+    if (narrow) vec = 1;
     // Rows that gather from a neighbourhood of their own index are served from LDS instead
     // (see the column window below), from K = 64 (at 32 it ties with the plain kernel) and if
     // the product is large enough to give every compute unit a few window blocks: a block
     // occupies a whole compute unit, and with too few rounds of blocks the last one leaves
     // most of the chip idle (90,000 rows in communities of 300: 0.55x of the plain kernel
     // at K = 32, 0.81x at K = 128; 200,000 rows at K = 64: 1.1x).
-    const double n = f[0];
     // Rows that share most columns with their neighbour (padding below 30 %) do better
     // paired, V = 2, than from LDS (cliques of 48, K = 128: 0.98 against 0.82 of the best).
     const bool windowed = !skewed && f[16] >= 0.6 && d_hat >= 40.0 && vec == 4 && pr2 >= 0.3 && K >= 64 &&
@@ -1284,7 +1302,6 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // row the second items are too short and it loses 15 %).  Narrower rows of B
     // are walked in bands of columns, or paired (below).  Rows with local columns lose up to half
     // their speed under the column order (it gives up the reuse between neighbouring rows).
-    const bool scattered = f[16] < 4.0 * 1025.0 / (n > 1.0 ? n : 1.0);
     // Such rows walked in bands of columns: where one product saves what the handle's table of them costs its build (300,000 rows of
     // 134: 183 -> 263 us, 60,000 of 140: 78 -> 99, 1,000,000 of 44: 187 -> 336), or where the other choice is the far dearer build of pairs.
     const int band_lanes = K <= 16 || (K > 32 && K <= 64) || (K > 64 && K % 32 == 0) ? 16 : K <= 128 ? 32 : 64;
@@ -1293,7 +1310,7 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     const bool fills_paired = n * (double)(K < 32 ? 4 : 8) / 128.0 >= 3500.0;
     const bool paired_else =
         d_hat >= 40.0 && fills_paired && K > 16 && K < 64 && (K > 32 || n * (double)K * 4.0 <= 16.0 * 1048576.0);
-    const bool banded = !skewed && !windowed && scattered && d_hat >= 12.0 && K > 8 &&
+    const bool banded = !skewed && !windowed && scattered && d_hat >= 12.0 && K > 2 &&
                         band_count(n, n, f[2], K, band_lanes, band_tile, &saved) > 1 &&
                         (paired_else || saved > 12.0 + 1e-6 * f[2] + 1e-4 * n);
     // K of 17..32 with scattered columns and a B beyond 16 MB (rows gathered from the
@@ -1333,10 +1350,10 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // already share their B lines in L1.  Power-law inputs: V = 2 ties or loses in the sweeps.
     // Long scattered rows of a B that needs no bands: paired as well below K = 64, which doubles the gathers a lane group has in
     // flight, unless the matrix is so small that halving the number of work items leaves wavefront slots empty (30,000 rows of
-    // 160, K = 32: V = 2 runs at 0.55 of V = 1), and not at K = 9 to 16 or with a B beyond 16 MB: there V = 2 takes 0.98-1.08 of the time
+    // 160, K = 32: V = 2 runs at 0.55 of V = 1), and not up to K = 16 or with a B beyond 16 MB: there V = 2 takes 0.98-1.18 of the time
     // and 5 to 9 times the build (1,000,000 rows of 44, K = 48: 1649 us for 1534, 1646 to build for 187).
     const bool pairs = long_uniform && K < 64 && fills_paired;
-    const bool pair_long = pairs && !banded && (K <= 8 || (K > 16 && n * (double)K * 4.0 <= 16.0 * 1048576.0));
+    const bool pair_long = pairs && !banded && K > 16 && n * (double)K * 4.0 <= 16.0 * 1048576.0;
     // Rows of C of 48 or 64 bytes are written one by one by a pair's lanes, part lines each, where single rows' lane groups
     // fill lines together: V = 1 takes 0.59-0.99 of V = 2 (with a self term 0.50-1.03, and a mask 0.58-0.99) on road-like graphs of 2 to 7
     // a row and uniform ones of 3 to 6, 300,000 and 2,000,000 rows.  C below 8 MB (120,000 rows) 0.85-1.01, products of under 10 us.
@@ -1386,6 +1403,10 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     if (!skewed && !windowed && !p.S && !banded && scattered && d_hat >= 8.0 && K >= 64 && K % 2 == 0) {
         lpr = 32;
         vec = 2;
+        rep = 1;
+    }
+    if (narrow) {
+        lpr = narrow_lanes(p.S);
         rep = 1;
     }
     if (banded && K >= 64) { // (300,000 rows of 134 in bands, K = 128: 2212 us, that shape 2342)

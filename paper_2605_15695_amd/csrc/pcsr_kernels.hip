@@ -323,6 +323,10 @@ constexpr int kEarlyTail = 2; // unsplit products whose tail reads the row: the 
 // three bands, to 64 in more, before they go to the row's, which costs nothing: the rms difference from 64 bits of rows of 44, 60, 90, 134 and
 // 300 ones between 0 and 1 is 4.3 to 4.8e-8 of their sum (300: 4.8 to 5.8), 4.7 to 5.1 (5.8) by items of 32 and 5.0 to 7.1 in one sum.
 constexpr int kBands = 3;
+// Up to 8 columns of unsplit rows by 16 lanes (narrow_lanes says why), whose sums are of 4 vectors as those of 4 lanes with wider
+// loads are, or of 8 where items are of 22 and more on average: rms difference from 64 bits of rows of 13, 18, 25 and 32 numbers between
+// 0 and 1 4.36, 4.53, 4.65 and 4.72e-8 of their sum, by 4 lanes 4.36, 4.53, 4.90 and 5.23, in sums of 16 5.76, 5.73, 5.46 and 5.44.
+constexpr int kNarrow = 4;
 
 // EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
 // branch alone cost the instance <2, false, 64, 1, 2> 4 %.
@@ -558,7 +562,8 @@ spmm_kernel(SpmmArgs a)
         // apart, whatever the chunk.  Rows of 48 against 64 bits, rms of their sum of magnitudes: 1.67e-8, where sums
         // of a chunk of 32 and 64 lanes made it 2.23 and 2.79e-8 (items of 32 in chunks of 16: 1.82e-8).  These kernels wait on
         // memory: the additions cost nothing (250,000 rows, K = 128 262 us, K = 256 577, both as before).
-        constexpr bool FOLD = (S && LPR >= 32) || FORM == kBands;
+        constexpr bool FOLD = (S && LPR >= 32) || FORM == kBands || FORM == kNarrow;
+        const bool fours = FORM == kNarrow && a.mean_item < 22;
         auto fold = [&] {
 #pragma unroll
             for (int v = 0; v < V; ++v)
@@ -634,6 +639,7 @@ spmm_kernel(SpmmArgs a)
                         for (int e = 0; e < VEC; ++e) part[v][r][e] = fmaf(aj, b[u][r][e], part[v][r][e]);
                 }
                 if (FOLD && (j + u) % 8 == 7) fold();
+                if (FORM == kNarrow && (j + u) % 8 == 3 && fours) fold();
             }
         };
         if constexpr (DPP) {
@@ -1396,6 +1402,8 @@ template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn
         return nullptr;
     else if constexpr (FORM == kBands && (S || V != 1 || REP != 1 || LPR < 8 || (VEC == 1 && LPR > 32) || (VEC == 2 && LPR != 32)))
         return nullptr;
+    else if constexpr (FORM == kNarrow && (S || LPR != 16 || VEC != 1 || REP != 1))
+        return nullptr;
     else {
         // A whole wavefront to a row has its addresses in scalar registers; more repeats than these are taken only where asked for.
         if constexpr (LPR < 64 && REP <= 2)
@@ -1637,6 +1645,8 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
     if (args.band) {
         fn = epi ? pick<true, kBands>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near_enough(args))
                  : pick<false, kBands>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near_enough(args));
+    } else if (args.K <= 8 && !S && ls.k_lpr == 16 && ls.k_vec == 1 && ls.k_rep == 1 && ls.ipg <= 1) {
+        fn = epi ? pick<true, kNarrow>(V, S, 16, 1, 1, near) : pick<false, kNarrow>(V, S, 16, 1, 1, near);
     } else if (args.outer) {
         fn = epi ? pick<true, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near)
                  : pick<false, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near);

@@ -1,0 +1,41 @@
+"""Products of up to 8 columns: 16 lanes of one dword for rows that are not split, 8 for items of balanced handles."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_15695_amd as pc
+from tests.test_gpu_near_operand import _rows, _tail
+
+pytestmark = pytest.mark.gpu
+
+
+# rows around the lanes' 16 entries, with empty ones; of less than 22 on average, of more, and of over 32, which auto shapes take as well
+@pytest.mark.parametrize("lengths", [(0, 33), (15, 50), (30, 90)])
+@pytest.mark.parametrize("V,S", [(1, 0), (2, 0), (1, 1), (2, 1)])
+def test_every_width(V, S, lengths):
+    rng = np.random.default_rng(lengths[1] + V)
+    n, n_cols = 1500, 1700
+    rowptr, colidx, vals = _rows(rng, np.where(np.arange(n) % 50 == 7, 0, rng.integers(*lengths, n)), n_cols)
+    lanes = 8 if S else 16
+    kw = dict(V=V, S=S, SG=32 * S, waves_per_wg=4)
+    for K in range(1, 9):
+        B = rng.standard_normal((n_cols, K)).astype(np.float32)
+        b = torch.from_numpy(B).cuda()
+        ref, bound = oracle.spmm(rowptr, colidx, vals, B)
+        same = []
+        for shape in (dict(lanes_per_row=lanes, vec=1, rep=1), dict(), dict(lanes_per_row=lanes, vec=1, rep=1, flags=pc.PCSR_FLAG_FAR_OFFSETS)):
+            h = pc.pcsr_build(n, n_cols, rowptr, colidx, vals, pc.make_params(**kw, **shape))
+            if lengths[0] == 30 and V == 1 and not S:
+                q = pc.pcsr_query_launch(h, K)
+                assert (q["lanes_per_row"], q["vec"], q["rep"]) == (16, 1, 1)
+            C = torch.full((n, K), float("nan"), device="cuda")
+            pc.pcsr_spmm(h, b, C, K)
+            ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, bound)
+            assert ok, (K, shape, worst)
+            same.append(C)
+            T, expect = _tail(h, b, K, rng)
+            ok, worst = oracle.within_tolerance(T.cpu().numpy(), *expect(ref, bound))
+            assert ok, (K, shape, "tail", worst)
+            h.close()
+        assert torch.equal(same[0], same[2])

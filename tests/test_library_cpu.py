@@ -436,6 +436,27 @@ def test_selector_walks_scattered_rows_in_bands():
     assert pick(300_000, 134, 62).vec == 2 and pick(300_000, 134, 63).vec == 1
 
 
+def test_selector_gives_narrow_rows_more_lanes_than_columns():
+    """Up to 8 columns: 16 lanes of one dword for long rows, 8 for items of split ones; short local rows and odd widths keep their shape."""
+    g = synth.workload("sbm", "small")
+    f = np.array(pc.pcsr_features(g.n_rows, g.n_cols, g.rowptr, g.colidx), dtype=np.float64)
+
+    def pick(deg, K, near=0.9, cv=0.1, d_max=100):
+        x = f.copy()
+        x[0] = x[1] = 200_000
+        x[2], x[4], x[5], x[6], x[7], x[8], x[15], x[16] = x[0] * deg, deg / x[0], deg, d_max, cv, cv, 0.5, near
+        p = pc.pcsr_select(x, K)
+        return p.S, p.lanes_per_row, p.vec, p.rep
+
+    for K in (2, 4, 6, 8):
+        assert pick(16, K) == (0, 16, 1, 1) and pick(9, K, near=0.0) == (0, 16, 1, 1)
+        assert pick(40, K, cv=4.0, d_max=20_000) == (1, 8, 1, 1)
+        assert pick(15, K)[1:] == (4, 4 if K % 4 == 0 else 2, 1) and pick(7, K, near=0.0)[2] > 1
+    for K, lanes in ((1, 4), (3, 4), (5, 8), (7, 8)):
+        assert pick(19, K) == (0, lanes, 1, 1) and pick(40, K) == (0, 16, 1, 1)
+        assert pick(40, K, cv=4.0, d_max=20_000) == (1, lanes, 1, 1)
+
+
 def test_query_kernel_reports_what_is_launched():
     """The shape that stands in where the one asked for reads rows badly; elsewhere the two queries agree."""
     shape = lambda q: (q["lanes_per_row"], q["vec"], q["rep"])  # noqa: E731
