@@ -266,10 +266,17 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     // and K of up to 8, rows of 32 and more (single rows of 18 and 27 that share their neighbours' columns 0.86-1.58 of 4 lanes' time)
     const bool narrow = !h_vec && !h_lpr && !h_rep && K <= 8 && h->host.win_cols == 0 && h->ipg <= 1 &&
                         h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
-    if (narrow) vec = 1;
+    // and K of 17 to 32, single rows of 32 and more, for which pcsr_select has these shapes, too: half as many rows a wavefront as with 8
+    // lanes of 16 bytes take 0.62-0.92 of the time in half wavefronts, scattered and in bands, 0.84-0.92 otherwise, tails 0.63-0.94 (150,000
+    // scattered rows of 60, K = 24 209 us and 126; 250,000 of 48 in shuffled communities, K = 32 236 and 198; 100,000 of 85 in cliques 64 and
+    // 57; of less than 32 1.00).
+    const bool dwords = !h_vec && !h_lpr && !h_rep && K > 16 && K <= 32 && h->host.win_cols == 0 && h->ipg <= 1 && h->host.V == 1 &&
+                        !h->host.S && h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
+    if (narrow || dwords) vec = 1;
     if (K % vec != 0) return PCSR_E_UNSUPPORTED;
     int lpr = h_lpr;
     if (narrow) lpr = narrow_lanes(h->host.S);
+    if (dwords) lpr = h->d_bands ? 32 : 16;
     if (!lpr) {
         int need = (K + vec - 1) / vec;
         if (h->host.win_cols > 0) {
@@ -346,7 +353,7 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
             if (h->flags & kWideShape) wide = 4 << ((h->flags & kWideShape) >> kWideShift) >> 1;
             if (h->flags & kWidePair) wide_vec = 2;
             if (h->flags & kWideTwice) wide_rep = 2;
-        } else if (K % 4 != 0 || (h->host.S && K > 64 && K % 32 != 0)) {
+        } else if (!dwords && (K % 4 != 0 || (h->host.S && K > 64 && K % 32 != 0))) {
             wide_shape(K, h->host.S && K <= 64 ? 16 : 64, &wide, &wide_rep);
         }
         const int64_t wt = (int64_t)wide * wide_vec * wide_rep;
@@ -1313,13 +1320,14 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     const bool banded = !skewed && !windowed && scattered && d_hat >= 12.0 && K > 2 &&
                         band_count(n, n, f[2], K, band_lanes, band_tile, &saved) > 1 &&
                         (paired_else || saved > 12.0 + 1e-6 * f[2] + 1e-4 * n);
-    // K of 17..32 with scattered columns and a B beyond 16 MB (rows gathered from the
-    // memory side, not from L2), or in bands: one dword per lane again, a row per half wavefront
+    // K of 17..32 with scattered columns: one dword per lane again, a row per half wavefront
     // (uniform random columns, 16 to 64 per row, 150,000 rows or more: 7-24 % faster than
-    // the best 16-byte shape; slower when B is small or the columns are local.  In bands: 300,000 rows of 134, K = 32: 527 us, 8 lanes
-    // of 16 bytes 580).
+    // the best 16-byte shape; slower when the columns are local.  In bands: 300,000 rows of 134, K = 32: 527 us, 8 lanes
+    // of 16 bytes 580.  A B of less than 16 MB: over 8 lanes of 16 bytes and 16 of two dwords 0.73-0.98, rows of 14 to 140, 4,000 to 200,000
+    // of them, but 1.03 with 13 a row and K = 17).  Rows that are paired otherwise stay so.
     const bool wide_scatter = !skewed && scattered && d_hat >= 12.0 && K > 16 && K <= 32 &&
-                              (banded || n * (double)K * 4.0 > 16.0 * 1048576.0);
+                              (banded || n * (double)K * 4.0 > 16.0 * 1048576.0 ||
+                               ((d_hat < 40.0 || !fills_paired) && (d_hat >= 16.0 || K % 4 == 0)));
     if (wide_scatter) vec = 1;
     const bool long_uniform = !skewed && !windowed && !wide_scatter && d_hat >= 40.0 && scattered;
     // But not where a slice of B is over 20 MB, 2.5 times what the L2s hold together: the order then saves less than

@@ -323,9 +323,10 @@ constexpr int kEarlyTail = 2; // unsplit products whose tail reads the row: the 
 // three bands, to 64 in more, before they go to the row's, which costs nothing: the rms difference from 64 bits of rows of 44, 60, 90, 134 and
 // 300 ones between 0 and 1 is 4.3 to 4.8e-8 of their sum (300: 4.8 to 5.8), 4.7 to 5.1 (5.8) by items of 32 and 5.0 to 7.1 in one sum.
 constexpr int kBands = 3;
-// Up to 8 columns of unsplit rows by 16 lanes (narrow_lanes says why), whose sums are of 4 vectors as those of 4 lanes with wider
+// One dword a lane, its sums put together more often than the lanes' entries are.  Up to 8 columns of unsplit rows by 16 lanes (narrow_lanes says why), whose sums are of 4 vectors as those of 4 lanes with wider
 // loads are, or of 8 where items are of 22 and more on average: rms difference from 64 bits of rows of 13, 18, 25 and 32 numbers between
-// 0 and 1 4.36, 4.53, 4.65 and 4.72e-8 of their sum, by 4 lanes 4.36, 4.53, 4.90 and 5.23, in sums of 16 5.76, 5.73, 5.46 and 5.44.
+// 0 and 1 4.36, 4.53, 4.65 and 4.72e-8 of their sum, by 4 lanes 4.36, 4.53, 4.90 and 5.23, in sums of 16 5.76, 5.73, 5.46 and 5.44.  And 17 to 32 columns of single rows by 32 lanes, or 16 with two
+// columns each, in place of 8 with four, in sums of 8 as those have (of 16 and 32: rows of 30 5.4 and 8.1e-8, of 8 4.7).
 constexpr int kNarrow = 4;
 
 // EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
@@ -563,7 +564,7 @@ spmm_kernel(SpmmArgs a)
         // of a chunk of 32 and 64 lanes made it 2.23 and 2.79e-8 (items of 32 in chunks of 16: 1.82e-8).  These kernels wait on
         // memory: the additions cost nothing (250,000 rows, K = 128 262 us, K = 256 577, both as before).
         constexpr bool FOLD = (S && LPR >= 32) || FORM == kBands || FORM == kNarrow;
-        const bool fours = FORM == kNarrow && a.mean_item < 22;
+        const bool fours = FORM == kNarrow && REP == 1 && a.mean_item < 22;
         auto fold = [&] {
 #pragma unroll
             for (int v = 0; v < V; ++v)
@@ -1402,7 +1403,7 @@ template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn
         return nullptr;
     else if constexpr (FORM == kBands && (S || V != 1 || REP != 1 || LPR < 8 || (VEC == 1 && LPR > 32) || (VEC == 2 && LPR != 32)))
         return nullptr;
-    else if constexpr (FORM == kNarrow && (S || LPR != 16 || VEC != 1 || REP != 1))
+    else if constexpr (FORM == kNarrow && (S || VEC != 1 || !((LPR == 16 && REP == 1) || (V == 1 && LPR * REP == 32 && LPR >= 16))))
         return nullptr;
     else {
         // A whole wavefront to a row has its addresses in scalar registers; more repeats than these are taken only where asked for.
@@ -1421,6 +1422,8 @@ template <int V, bool S, int LPR, int VEC, bool EPI, int FORM> KernelFn pick_rep
         }
     } else { // the shapes resolve_launch arrives at when everything is left to it
         if (rep == 1) return instance<V, S, LPR, VEC, 1, EPI, FORM>(near);
+        if constexpr (FORM == kNarrow)
+            if (rep == 2) return instance<V, S, LPR, VEC, 2, EPI, FORM>(near);
         if constexpr (LPR == 64) {
             if (rep == 2) return instance<V, S, LPR, VEC, 2, EPI, FORM>(near);
             if constexpr (!S)
@@ -1607,7 +1610,7 @@ bool band_kernel_exists(int lpr, int vec, int rep, bool epilogue)
 
 bool epilogue_kernel_exists(int V, int S, int lpr, int vec, int rep)
 {
-    return pick<true>(V, S, lpr, vec, rep) != nullptr;
+    return pick<true>(V, S, lpr, vec, rep) != nullptr || pick<true, kNarrow>(V, S, lpr, vec, rep) != nullptr;
 }
 
 static bool near_enough(const SpmmArgs &a)
@@ -1640,13 +1643,16 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
     const bool past_l2 = (double)args.n_cols * args.K * 4.0 > 32.0 * 1048576.0;
     const bool short_items = !S && args.mean_item < 16 && (ls.k_lpr < 16 || (V == 2 && ls.k_vec == 1 && !epi && past_l2));
     const bool near = near_enough(args) && !short_items;
+    const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 &&
+                        (args.K <= 8 ? ls.k_lpr == 16 && ls.k_rep == 1
+                                     : V == 1 && args.K > 16 && args.K <= 32 && ls.k_lpr >= 16 && ls.k_lpr * ls.k_rep == 32);
     KernelFn fn;
     size_t lds = 0;
     if (args.band) {
         fn = epi ? pick<true, kBands>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near_enough(args))
                  : pick<false, kBands>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near_enough(args));
-    } else if (args.K <= 8 && !S && ls.k_lpr == 16 && ls.k_vec == 1 && ls.k_rep == 1 && ls.ipg <= 1) {
-        fn = epi ? pick<true, kNarrow>(V, S, 16, 1, 1, near) : pick<false, kNarrow>(V, S, 16, 1, 1, near);
+    } else if (narrow) {
+        fn = epi ? pick<true, kNarrow>(V, S, ls.k_lpr, 1, ls.k_rep, near) : pick<false, kNarrow>(V, S, ls.k_lpr, 1, ls.k_rep, near);
     } else if (args.outer) {
         fn = epi ? pick<true, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near)
                  : pick<false, kLongItems>(V, S, ls.k_lpr, ls.k_vec, ls.k_rep, near);

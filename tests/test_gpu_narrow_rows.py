@@ -1,4 +1,4 @@
-"""Products of up to 8 columns: 16 lanes of one dword for rows that are not split, 8 for items of balanced handles."""
+"""One dword a lane: up to 8 columns with 16 lanes for rows that are not split, 8 for items of balanced handles; 17 to 32 of single rows."""
 import numpy as np
 import pytest
 import torch
@@ -39,3 +39,28 @@ def test_every_width(V, S, lengths):
             assert ok, (K, shape, "tail", worst)
             h.close()
         assert torch.equal(same[0], same[2])
+
+
+@pytest.mark.parametrize("lengths", [(0, 40), (30, 90)])
+@pytest.mark.parametrize("K", [17, 24, 31, 32])
+def test_single_rows_of_17_to_32_columns(K, lengths):
+    rng = np.random.default_rng(K + lengths[1])
+    n, n_cols = 1500, 1700
+    rowptr, colidx, vals = _rows(rng, np.where(np.arange(n) % 50 == 7, 0, rng.integers(*lengths, n)), n_cols)
+    B = rng.standard_normal((n_cols, K)).astype(np.float32)
+    b = torch.from_numpy(B).cuda()
+    ref, bound = oracle.spmm(rowptr, colidx, vals, B)
+    shapes = [dict(lanes_per_row=16, vec=1, rep=2), dict(lanes_per_row=32, vec=1, rep=1)]
+    for kw in (*shapes, *(dict(flags=pc.PCSR_FLAG_FAR_OFFSETS, **s) for s in shapes), dict(), dict(flags=pc.PCSR_FLAG_COLUMN_BANDS | pc.PCSR_FLAG_GPU_BUILD)):
+        h = pc.pcsr_build(n, n_cols, rowptr, colidx, vals, pc.make_params(**kw))
+        if lengths[0] == 30 and "vec" not in kw:
+            q = pc.pcsr_query_kernel(h, K)
+            assert (q["lanes_per_row"], q["vec"], q["rep"]) == ((32, 1, 1) if kw else (16, 1, 2))
+        C = torch.full((n, K), float("nan"), device="cuda")
+        pc.pcsr_spmm(h, b, C, K)
+        ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, bound)
+        assert ok, (kw, worst)
+        T, expect = _tail(h, b, K, rng)
+        ok, worst = oracle.within_tolerance(T.cpu().numpy(), *expect(ref, bound))
+        assert ok, (kw, "tail", worst)
+        h.close()
