@@ -109,8 +109,8 @@ enum {
  *     vec            fp32 values per lane per B load: 1, 2 or 4; must divide K; 0 = auto
  *                    (the widest that divides K; 1 for K of 9..16 when lanes_per_row is
  *                    auto too and rows average 8 vectors or more, and for K up to 8, with
- *                    8 or 16 lanes, and of 17..32 with V = 1, S = 0, when rep
- *                    is too and they average 32).
+ *                    8 or 16 lanes, and of 17..32 (and multiples of 4 up to 64)
+ *                    with V = 1, S = 0, when rep is too and they average 32).
  *     rep            column tiles per lane (the coarsening factor F): 1, 2 or 4; 0 = auto.
  *                    One work item covers lanes_per_row*vec*rep columns of C per grid.y
  *                    slice; wider K is covered by more grid.y slices.

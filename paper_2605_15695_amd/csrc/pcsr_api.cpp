@@ -270,13 +270,16 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     // lanes of 16 bytes take 0.62-0.92 of the time in half wavefronts, scattered and in bands, 0.84-0.92 otherwise, tails 0.63-0.94 (150,000
     // scattered rows of 60, K = 24 209 us and 126; 250,000 of 48 in shuffled communities, K = 32 236 and 198; 100,000 of 85 in cliques 64 and
     // 57; of less than 32 1.00).
-    const bool dwords = !h_vec && !h_lpr && !h_rep && K > 16 && K <= 32 && h->host.win_cols == 0 && h->ipg <= 1 && h->host.V == 1 &&
-                        !h->host.S && h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
+    // Up to 64 columns likewise, two to a lane of a half wavefront, in place of 16 lanes of 16 bytes: 0.90-0.97 (100,000 rows of 85 in
+    // cliques, K = 64 110 us and 99), but not in bands (100,000 of 48, K = 48 107 us and 137).
+    const bool dwords = !h_vec && !h_lpr && !h_rep && K > 16 && (K <= 32 || (K <= 64 && K % 4 == 0 && !h->d_bands)) &&
+                        h->host.win_cols == 0 && h->ipg <= 1 && h->host.V == 1 && !h->host.S &&
+                        h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
     if (narrow || dwords) vec = 1;
     if (K % vec != 0) return PCSR_E_UNSUPPORTED;
     int lpr = h_lpr;
     if (narrow) lpr = narrow_lanes(h->host.S);
-    if (dwords) lpr = h->d_bands ? 32 : 16;
+    if (dwords) lpr = h->d_bands || K > 32 ? 32 : 16;
     if (!lpr) {
         int need = (K + vec - 1) / vec;
         if (h->host.win_cols > 0) {
@@ -1408,10 +1411,21 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // Scattered columns, rows of 8 to 40, K from 64: a 64-column slice per half wavefront
     // with dwordx2 loads (uniform random columns, 8 to 32 per row, K = 64 and 128: 3-7 %
     // over the best 16-byte shape; local columns keep the 16-byte shapes).
+    // But 16 bytes a lane where B is so small that L2 holds it: K = 128 and 192, 2 to 16 MB 0.79-0.98 (8,000 rows of 22, K = 128 9.9 us
+    // and 7.8; 25 MB and more 0.99-1.08).
     if (!skewed && !windowed && !p.S && !banded && scattered && d_hat >= 8.0 && K >= 64 && K % 2 == 0) {
-        lpr = 32;
-        vec = 2;
+        const bool in_l2 = b_bytes > 2e6 && b_bytes < 16e6 && K >= 96 && K % 32 == 0;
+        lpr = in_l2 ? 16 : 32;
+        vec = in_l2 ? 4 : 2;
         rep = 1;
+    }
+    // Single long rows of 33 to 64 columns: a dword a lane and two columns of it, as resolve_launch has it for auto shapes; and scattered ones
+    // of 12 and more, K = 64, that L2 holds: 0.77-0.95 of 32 lanes of two floats (20,000 rows of 34 15.7 us and 12.4; at 13 MB 0.98-1.00).
+    if (!p.S && p.V == 1 && !windowed && !banded && K > 32 && K <= 64 && K % 4 == 0 &&
+        (scattered ? K == 64 && d_hat >= 12.0 && b_bytes < 10e6 : d_hat >= 32.0)) {
+        lpr = 32;
+        vec = 1;
+        rep = 2;
     }
     if (narrow) {
         lpr = narrow_lanes(p.S);

@@ -326,7 +326,7 @@ constexpr int kBands = 3;
 // One dword a lane, its sums put together more often than the lanes' entries are.  Up to 8 columns of unsplit rows by 16 lanes (narrow_lanes says why), whose sums are of 4 vectors as those of 4 lanes with wider
 // loads are, or of 8 where items are of 22 and more on average: rms difference from 64 bits of rows of 13, 18, 25 and 32 numbers between
 // 0 and 1 4.36, 4.53, 4.65 and 4.72e-8 of their sum, by 4 lanes 4.36, 4.53, 4.90 and 5.23, in sums of 16 5.76, 5.73, 5.46 and 5.44.  And 17 to 32 columns of single rows by 32 lanes, or 16 with two
-// columns each, in place of 8 with four, in sums of 8 as those have (of 16 and 32: rows of 30 5.4 and 8.1e-8, of 8 4.7).
+// columns each, in place of 8 with four, in sums of 8 as those have (of 16 and 32: rows of 30 5.4 and 8.1e-8, of 8 4.7); up to 64 by 32 with two.
 constexpr int kNarrow = 4;
 
 // EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
@@ -1403,7 +1403,7 @@ template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn
         return nullptr;
     else if constexpr (FORM == kBands && (S || V != 1 || REP != 1 || LPR < 8 || (VEC == 1 && LPR > 32) || (VEC == 2 && LPR != 32)))
         return nullptr;
-    else if constexpr (FORM == kNarrow && (S || VEC != 1 || !((LPR == 16 && REP == 1) || (V == 1 && LPR * REP == 32 && LPR >= 16))))
+    else if constexpr (FORM == kNarrow && (S || VEC != 1 || !((LPR == 16 && REP == 1) || (V == 1 && LPR >= 16 && LPR <= 32 && LPR * REP >= 32 && REP <= 2))))
         return nullptr;
     else {
         // A whole wavefront to a row has its addresses in scalar registers; more repeats than these are taken only where asked for.
@@ -1645,7 +1645,8 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
     const bool near = near_enough(args) && !short_items;
     const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 &&
                         (args.K <= 8 ? ls.k_lpr == 16 && ls.k_rep == 1
-                                     : V == 1 && args.K > 16 && args.K <= 32 && ls.k_lpr >= 16 && ls.k_lpr * ls.k_rep == 32);
+                                     : V == 1 && args.K > 16 && args.K <= 64 && ls.k_lpr >= 16 && ls.k_lpr <= 32 && ls.k_rep <= 2 &&
+                                           ls.k_lpr * ls.k_rep == (args.K <= 32 ? 32 : 64));
     KernelFn fn;
     size_t lds = 0;
     if (args.band) {

@@ -1,4 +1,4 @@
-"""One dword a lane: up to 8 columns with 16 lanes for rows that are not split, 8 for items of balanced handles; 17 to 32 of single rows."""
+"""One dword a lane: up to 8 columns with 16 lanes for rows that are not split, 8 for items of balanced handles; 17 to 64 of single rows."""
 import numpy as np
 import pytest
 import torch
@@ -42,20 +42,20 @@ def test_every_width(V, S, lengths):
 
 
 @pytest.mark.parametrize("lengths", [(0, 40), (30, 90)])
-@pytest.mark.parametrize("K", [17, 24, 31, 32])
-def test_single_rows_of_17_to_32_columns(K, lengths):
+@pytest.mark.parametrize("K", [17, 24, 31, 32, 36, 60, 64])
+def test_single_rows_of_17_to_64_columns(K, lengths):
     rng = np.random.default_rng(K + lengths[1])
     n, n_cols = 1500, 1700
     rowptr, colidx, vals = _rows(rng, np.where(np.arange(n) % 50 == 7, 0, rng.integers(*lengths, n)), n_cols)
     B = rng.standard_normal((n_cols, K)).astype(np.float32)
     b = torch.from_numpy(B).cuda()
     ref, bound = oracle.spmm(rowptr, colidx, vals, B)
-    shapes = [dict(lanes_per_row=16, vec=1, rep=2), dict(lanes_per_row=32, vec=1, rep=1)]
+    shapes = [dict(lanes_per_row=16, vec=1, rep=2), dict(lanes_per_row=32, vec=1, rep=1)] if K <= 32 else [dict(lanes_per_row=32, vec=1, rep=2)]
     for kw in (*shapes, *(dict(flags=pc.PCSR_FLAG_FAR_OFFSETS, **s) for s in shapes), dict(), dict(flags=pc.PCSR_FLAG_COLUMN_BANDS | pc.PCSR_FLAG_GPU_BUILD)):
         h = pc.pcsr_build(n, n_cols, rowptr, colidx, vals, pc.make_params(**kw))
         if lengths[0] == 30 and "vec" not in kw:
             q = pc.pcsr_query_kernel(h, K)
-            assert (q["lanes_per_row"], q["vec"], q["rep"]) == ((32, 1, 1) if kw else (16, 1, 2))
+            assert (q["lanes_per_row"], q["vec"], q["rep"]) == (((32, 1, 1) if kw else (16, 1, 2)) if K <= 32 else (16, 4, 1) if kw else (32, 1, 2))
         C = torch.full((n, K), float("nan"), device="cuda")
         pc.pcsr_spmm(h, b, C, K)
         ok, worst = oracle.within_tolerance(C.cpu().numpy(), ref, bound)
