@@ -356,6 +356,12 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
             if (h->flags & kWideShape) wide = 4 << ((h->flags & kWideShape) >> kWideShift) >> 1;
             if (h->flags & kWidePair) wide_vec = 2;
             if (h->flags & kWideTwice) wide_rep = 2;
+            // In bands, slices that share columns take one (band_passes): at other widths than the one that the shape came with a
+            // row in one tile instead (300,000 rows of 134, selected at K = 50, us at K = 66 2777 and 1597; 100,000 of 90 509 and 248).
+            if (wide && h->d_bands && K % wide_vec != 0 && wide * wide_vec * wide_rep < K) {
+                wide_vec = 4;
+                wide_shape(K, 64, &wide, &wide_rep);
+            }
         } else if (!dwords && (K % 4 != 0 || (h->host.S && K > 64 && K % 32 != 0))) {
             wide_shape(K, h->host.S && K <= 64 ? 16 : 64, &wide, &wide_rep);
         }
@@ -924,6 +930,11 @@ static int band_count(double n_rows, double n_cols, double nnz, int32_t K, int l
     return *saved > 0.03 * us(1) ? best : 1;
 }
 
+// Bands add to what is in C.  Where a shape's loads do not divide K, the last lane of a row also computes columns of the lane before it:
+// harmless in one wavefront, which reads all of them before it writes any, and while all write the same bits; but the lane before the
+// last slice's is in another workgroup, whose sum of this band may be there already.  (The first band reads nothing.)
+static bool slices_share_columns(int32_t K, const pcsr::LaunchShape &ls) { return K % ls.k_vec != 0 && ls.k_grid_y > 1; }
+
 // Bands leave their sums in C, where the tail of one pass has its rows read before they are written.
 static bool tail_reads_c(const pcsr::Epilogue &e, const float *C, int64_t n_rows, int32_t K)
 {
@@ -939,7 +950,7 @@ static int band_passes(pcsr_handle_t h, int32_t K, const pcsr::LaunchShape &ls, 
 {
     double saved;
     if (ls.window || ls.ipg > 1 || !pcsr::band_kernel_exists(ls.k_lpr, ls.k_vec, ls.k_rep, epi.on)) return 0;
-    if (tail_reads_c(epi, C, h->host.n_rows, K)) return 1;
+    if (slices_share_columns(K, ls) || tail_reads_c(epi, C, h->host.n_rows, K)) return 1;
     return band_count((double)h->host.n_rows, (double)h->host.n_cols, (double)h->host.nnz, K, ls.k_lpr, ls.k_lpr * ls.k_vec * ls.k_rep,
                       &saved);
 }

@@ -412,7 +412,7 @@ spmm_kernel(SpmmArgs a)
     }
     // K no multiple of VEC: the last vector of a row is moved back to end with it.  The columns it
     // shares with its neighbour are computed and stored twice, the same bits; the atomic
-    // write-back skips them.
+    // write-back skips them, and bands after the first are launched only where the neighbour is in the same wavefront.
 #pragma unroll
     for (int r = 0; r < REP; ++r)
         if (kv[r]) kc[r] = min(kc[r], a.K - VEC);

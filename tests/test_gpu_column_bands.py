@@ -61,6 +61,30 @@ def test_bands_against_the_oracle(graph, shape, K):
         assert np.array_equal(x, got[0])
 
 
+# a handle selected for one width at another, which its stand-in shape would cover in slices that share columns
+@pytest.mark.parametrize("hint,K", [(33, 65), (50, 66), (62, 126), (66, 130), (75, 131), (126, 134), (66, 258), (50, 514)])
+def test_slices_that_share_columns(graph, hint, K):
+    rowptr, colidx, vals = graph
+    f = np.array(pc.pcsr_features(N, N_COLS, rowptr, colidx), dtype=np.float64)
+    f[:2], f[2], f[4:7], f[16] = 300_000, 300_000 * 134, 134, 0.0
+    p = pc.pcsr_select(f, hint)
+    p.flags &= ~(pc.PCSR_FLAG_CLUSTER_IF_USEFUL | pc.PCSR_FLAG_CLUSTER_WINDOWS)
+    assert (p.V, p.S) == (1, 0) and p.flags & BANDS
+    h = pc.pcsr_build(N, N_COLS, *_dev(rowptr, colidx, vals), p)
+    q = pc.pcsr_query_kernel(h, K)
+    assert K % q["vec"] and (q["grid_y"] > 1) == (K > 512)
+    B = np.random.default_rng(K).standard_normal((N_COLS, K)).astype(np.float32)
+    b, got = _dev(B)[0], []
+    for _ in range(3):
+        C = torch.full((N, K), float("nan"), device="cuda")
+        pc.pcsr_spmm(h, b, C, K)
+        got.append(C.cpu().numpy())
+    ok, worst = oracle.within_tolerance(got[0], *oracle.spmm(rowptr, colidx, vals, B))
+    assert ok, worst
+    assert all(np.array_equal(x, got[0]) for x in got)
+    h.close()
+
+
 def _launches(f):
     from torch.profiler import ProfilerActivity, profile
 
