@@ -235,6 +235,33 @@ void window_tail(pcsr_handle_t h, pcsr::LaunchShape *ls)
     ls->k_grid_y = 1;
 }
 
+// How many bands of columns a product of scattered rows is best walked in (a divisor of kColumnBands), and the us that they save.  A
+// band of B that an XCD's L2 holds is gathered from there; each band of several costs a launch, a look at every row and a pass over
+// C.  The rates are those that fit 1,200 measured times best (uniform columns, 14 to 300 a row, 40,000 to 1,000,000 rows, 6 to 256
+// columns, 1 to 12 bands): the number picked is 0.9 % off the best of them on average and 14 % at most, and never over 1.3 % off one
+// band.  Us in one band and in those picked: rows of 134, 300,000 of them, K = 16 667 and 366 (6 bands), K = 32 706 and 527 (6), K = 64 1459 and
+// 1197 (6); of 60, 150,000, K = 16 118 and 76 (3), K = 48 291 and 211 (6); of 60, 400,000, K = 10 462 and 235 (4), K = 64 908 in one; of 30,
+// 400,000, K = 9 202 and 145 (3), K = 16 193 in one; of 300, 100,000, K = 32 385 and 224 (4).
+int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, int32_t tile, double *saved)
+{
+    const double slices = (K + tile - 1) / tile, row = 4.0 * K / slices;
+    const double grain = (double)std::min(128, (4 * K) & -(4 * K)); // rows of B begin at multiples of it
+    const double miss = std::ceil((row + 128.0 - grain) / 32.0) / 4.0 / 39e3, hit = std::max(1.0 / 140e3, row / 31e6);
+    auto us = [&](int m) {
+        const double near = std::cbrt(std::min(1.0, 3.5e6 * m / std::max(n_cols * row, 1.0)));
+        const double passes = m * (1.7 + n_rows * 1e-3 * (slices * (0.006 + 0.00106 * lanes) + 0.00133 * K));
+        return slices * nnz * (near * hit + (1.0 - near) * miss) + (m > 1 ? passes : 0.0);
+    };
+    int best = 1;
+    // Rows of less than 256 are better added up in fewer than 12 parts, and in tiles of whole rows by whole and half wavefronts, whose
+    // sums were of 8 before, in parts of 20 and more.
+    const double least = K > 64 && K % 32 != 0 ? 20.0 : 0.0;
+    for (const int m : {2, 3, 4, 6, 12})
+        if (nnz >= std::max(m < 12 ? 0.0 : 256.0, least * m) * n_rows && us(m) < (best > 1 ? 0.98 : 1.0) * us(best)) best = m;
+    *saved = us(1) - us(best);
+    return *saved > 0.03 * us(1) ? best : 1;
+}
+
 // Launch shape for width K under the handle's kernel parameters ("0 = auto" resolved).
 // epilogue: for pcsr_spmm_epilogue, whose kernels exist for the auto shapes only; a handle with
 // another shape of its own uses those.
@@ -275,11 +302,21 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     const bool dwords = !h_vec && !h_lpr && !h_rep && K > 16 && (K <= 32 || (K <= 64 && K % 4 == 0 && !h->d_bands)) &&
                         h->host.win_cols == 0 && h->ipg <= 1 && h->host.V == 1 && !h->host.S &&
                         h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
+    // Rows of 64 columns and more of a handle with bands go in slices, as pcsr_select has them: of 64 columns in 16 lanes where there are
+    // several bands, else half a wavefront to 64 columns.  Us of such slices, of a tile of the whole row and of items of 32 in column order: rows
+    // of 90, 100,000 of them, K = 128 346, 469 and 446, K = 256 675, 1182 and 889, K = 512 1411, 2469 and 1779; of 134, 300,000, K = 256 4755,
+    // 5756 and 5096; of 44, 500,000 (one band), K = 256 2983, 3077 and 3637.  Rows that are no multiple of 128 bytes long have lines
+    // that two slices would read: K = 200 993, 951 and 1018, K = 300 1739, 1531 and 1605.
+    double saved;
+    const bool sliced = !h_vec && !h_lpr && !h_rep && h->d_bands && h->ipg <= 1 && K >= 64 && K % 32 == 0;
+    const bool in_bands = sliced && band_count((double)h->host.n_rows, (double)h->host.n_cols, (double)h->host.nnz, K, 16, 64, &saved) > 1;
     if (narrow || dwords) vec = 1;
+    if (sliced) vec = in_bands ? 4 : 2;
     if (K % vec != 0) return PCSR_E_UNSUPPORTED;
     int lpr = h_lpr;
     if (narrow) lpr = narrow_lanes(h->host.S);
     if (dwords) lpr = h->d_bands || K > 32 ? 32 : 16;
+    if (sliced) lpr = in_bands ? 16 : 32;
     if (!lpr) {
         int need = (K + vec - 1) / vec;
         if (h->host.win_cols > 0) {
@@ -298,7 +335,7 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     if (!rep) {
         int need = (K + lpr * vec - 1) / (lpr * vec);
         rep = 1;
-        const int most = !h->host.S ? 4 : (h->clustered ? 2 : 1);
+        const int most = sliced ? 1 : h->d_bands ? 2 : !h->host.S ? 4 : (h->clustered ? 2 : 1); // (the band kernel's)
         if (h->host.win_cols == 0)
             while (rep < need && rep < most) rep <<= 1;
     }
@@ -901,33 +938,6 @@ static int spmm_check(pcsr_handle_t h, const float *B, float *C, int32_t K, pcsr
     if (!hip_ok(hipGetDevice(&dev))) return PCSR_E_HIP;
     if (dev != h->device) return PCSR_E_INVALID_ARG;
     return PCSR_OK;
-}
-
-// How many bands of columns a product of scattered rows is best walked in (a divisor of kColumnBands), and the us that they save.  A
-// band of B that an XCD's L2 holds is gathered from there; each band of several costs a launch, a look at every row and a pass over
-// C.  The rates are those that fit 1,200 measured times best (uniform columns, 14 to 300 a row, 40,000 to 1,000,000 rows, 6 to 256
-// columns, 1 to 12 bands): the number picked is 0.9 % off the best of them on average and 14 % at most, and never over 1.3 % off one
-// band.  Us in one band and in those picked: rows of 134, 300,000 of them, K = 16 667 and 366 (6 bands), K = 32 706 and 527 (6), K = 64 1459 and
-// 1197 (6); of 60, 150,000, K = 16 118 and 76 (3), K = 48 291 and 211 (6); of 60, 400,000, K = 10 462 and 235 (4), K = 64 908 in one; of 30,
-// 400,000, K = 9 202 and 145 (3), K = 16 193 in one; of 300, 100,000, K = 32 385 and 224 (4).
-static int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, int32_t tile, double *saved)
-{
-    const double slices = (K + tile - 1) / tile, row = 4.0 * K / slices;
-    const double grain = (double)std::min(128, (4 * K) & -(4 * K)); // rows of B begin at multiples of it
-    const double miss = std::ceil((row + 128.0 - grain) / 32.0) / 4.0 / 39e3, hit = std::max(1.0 / 140e3, row / 31e6);
-    auto us = [&](int m) {
-        const double near = std::cbrt(std::min(1.0, 3.5e6 * m / std::max(n_cols * row, 1.0)));
-        const double passes = m * (1.7 + n_rows * 1e-3 * (slices * (0.006 + 0.00106 * lanes) + 0.00133 * K));
-        return slices * nnz * (near * hit + (1.0 - near) * miss) + (m > 1 ? passes : 0.0);
-    };
-    int best = 1;
-    // Rows of less than 256 are better added up in fewer than 12 parts, and in tiles of whole rows by whole and half wavefronts, whose
-    // sums were of 8 before, in parts of 20 and more.
-    const double least = K > 64 && K % 32 != 0 ? 20.0 : 0.0;
-    for (const int m : {2, 3, 4, 6, 12})
-        if (nnz >= std::max(m < 12 ? 0.0 : 256.0, least * m) * n_rows && us(m) < (best > 1 ? 0.98 : 1.0) * us(best)) best = m;
-    *saved = us(1) - us(best);
-    return *saved > 0.03 * us(1) ? best : 1;
 }
 
 // Bands add to what is in C.  Where a shape's loads do not divide K, the last lane of a row also computes columns of the lane before it:

@@ -322,6 +322,9 @@ constexpr int kEarlyTail = 2; // unsplit products whose tail reads the row: the 
 // 437, 372, 366 and 446 in 2, 3, 4, 6 and 12).  Sums of 8 vectors are added up to 32 in up to
 // three bands, to 64 in more, before they go to the row's, which costs nothing: the rms difference from 64 bits of rows of 44, 60, 90, 134 and
 // 300 ones between 0 and 1 is 4.3 to 4.8e-8 of their sum (300: 4.8 to 5.8), 4.7 to 5.1 (5.8) by items of 32 and 5.0 to 7.1 in one sum.
+// A whole wavefront's chunk is 64 vectors: half of it at a time where sums are of 32 (rows of 60, K = 260 4.97 -> 4.19e-8, items of 32
+// 4.18; the time is the same).  Over 256 columns it has two tiles of them, in place of the plain kernel, whose sums
+// are of 64 there (rows of 60 11.0e-8, of 90 8.8, here 4.45; 1362 us and 1355, 1265 and 1325).
 constexpr int kBands = 3;
 // One dword a lane, its sums put together more often than the lanes' entries are.  Up to 8 columns of unsplit rows by 16 lanes (narrow_lanes says why), whose sums are of 4 vectors as those of 4 lanes with wider
 // loads are, or of 8 where items are of 22 and more on average: rms difference from 64 bits of rows of 13, 18, 25 and 32 numbers between
@@ -523,6 +526,18 @@ spmm_kernel(SpmmArgs a)
     };
     if constexpr (OUTER) outer([](float (&x)[VEC], float *at) { store_lds<VEC>(at, x); });
 
+    auto band_apart = [&] {
+        if constexpr (FORM == kBands) {
+#pragma unroll
+            for (int r = 0; r < REP; ++r)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    before[r][e] += acc[0][r][e];
+                    acc[0][r][e] = 0.0f;
+                }
+        }
+    };
+
     // The next chunk's colIdx/val are requested before the current chunk's gathers, so
     // that a chunk costs one memory round trip, not two.
     int c_next[NH];
@@ -641,6 +656,7 @@ spmm_kernel(SpmmArgs a)
                 }
                 if (FOLD && (j + u) % 8 == 7) fold();
                 if (FORM == kNarrow && (j + u) % 8 == 3 && fours) fold();
+                if (FORM == kBands && CH == 64 && (j + u) % 32 == 31 && !(a.band & kBandSums64)) band_apart(); // half a chunk
             }
         };
         if constexpr (DPP) {
@@ -670,13 +686,7 @@ spmm_kernel(SpmmArgs a)
         if constexpr (FORM == kBands) {
             if (--until == 0) {
                 until = band_period;
-#pragma unroll
-                for (int r = 0; r < REP; ++r)
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        before[r][e] += acc[0][r][e];
-                        acc[0][r][e] = 0.0f;
-                    }
+                band_apart();
             }
         }
         if constexpr (OUTER) {
@@ -1401,7 +1411,7 @@ template <int V, bool S, int LPR, int VEC, int REP, bool EPI, int FORM> KernelFn
         return nullptr;
     else if constexpr (FORM == kEarlyTail && (S || V * REP * VEC > 8))
         return nullptr;
-    else if constexpr (FORM == kBands && (S || V != 1 || REP != 1 || LPR < 8 || (VEC == 1 && LPR > 32) || (VEC == 2 && LPR != 32)))
+    else if constexpr (FORM == kBands && (S || V != 1 || LPR < 8 || (VEC == 1 && LPR > 32) || (VEC == 2 && LPR != 32) || (REP != 1 && !(REP == 2 && VEC == 4 && LPR == 64))))
         return nullptr;
     else if constexpr (FORM == kNarrow && (S || VEC != 1 || !((LPR == 16 && REP == 1) || (V == 1 && LPR >= 16 && LPR <= 32 && LPR * REP >= 32 && REP <= 2))))
         return nullptr;

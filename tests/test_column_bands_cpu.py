@@ -57,3 +57,17 @@ assert {K} % q["vec"] and q["grid_y"] > 1
 assert launches(h, {K}) == 1
 h.close()
 """)
+
+
+def test_auto_shapes_are_those_of_the_band_kernel(fake):  # noqa: F811
+    """Wide rows left to the library, as an operator's are: slices of 64 columns, or a tile of up to 512."""
+    _run(fake, HANDLE + """
+h = handle(flags=pc.PCSR_FLAG_GPU_BUILD | pc.PCSR_FLAG_COLUMN_BANDS)
+shape = lambda K: (lambda q: (q["lanes_per_row"], q["vec"], q["rep"], q["grid_y"]))(pc.pcsr_query_kernel(h, K))  # noqa: E731
+for K in (64, 96, 128, 256, 512, 1024):
+    assert shape(K) == (16, 4, 1, (K + 63) // 64) and launches(h, K) > 1, K
+    assert pc.pcsr_query_launch(h, K) == pc.pcsr_query_kernel(h, K)
+for K, s in ((72, (32, 4, 1, 1)), (200, (64, 4, 1, 1)), (260, (64, 4, 2, 1)), (515, (64, 4, 2, 2)), (1000, (64, 4, 2, 2))):
+    assert shape(K) == s, K
+h.close()
+""")

@@ -85,6 +85,31 @@ def test_slices_that_share_columns(graph, hint, K):
     h.close()
 
 
+# auto shapes, as operators have them: tiles of the whole row, slices of 64 and 512 columns, and more than one tile holds
+@pytest.mark.parametrize("K", [64, 100, 128, 200, 260, 300, 512, 515, 640, 1000])
+def test_wide_rows_are_as_exact_as_items_of_32(graph, K):
+    """Rows of 60 to 240 numbers between 0 and 1, rms difference from 64 bits beside that of the same rows split into items of 32 in
+    column order: sums of 8, in sums of 32 or 64, in that of the row, are about as many roundings."""
+    rowptr, colidx, vals = graph
+    dev = _dev(rowptr, colidx, np.abs(vals))
+    B = torch.rand(N_COLS, K, device="cuda", generator=torch.Generator("cuda").manual_seed(K))
+    rows = np.arange(2, N - 1, 97)
+    at = np.concatenate([np.arange(rowptr[r], rowptr[r + 1]) for r in rows])
+    part = dev[2][torch.from_numpy(at).cuda()].double()[:, None] * B[dev[1][torch.from_numpy(at).cuda()].long()].double()
+    ref = torch.zeros(rows.size, K, dtype=torch.float64, device="cuda").index_add_(
+        0, torch.from_numpy(np.repeat(np.arange(rows.size), np.diff(rowptr)[rows])).cuda(), part)
+    full = (ref > 0).all(1)
+    rms = []
+    for kw in (dict(flags=BANDS), dict(S=1, SG=32, flags=pc.PCSR_FLAG_COLUMN_ORDER)):
+        h = pc.pcsr_build(N, N_COLS, *dev, pc.make_params(**kw))
+        C = torch.empty(N, K, device="cuda")
+        pc.pcsr_spmm(h, B, C, K)
+        off = ((C[torch.from_numpy(rows).cuda()].double() - ref)[full] / ref[full])
+        rms.append(float(off.square().mean().sqrt()))
+        h.close()
+    assert rms[0] < 1.15 * rms[1], rms
+
+
 def _launches(f):
     from torch.profiler import ProfilerActivity, profile
 
