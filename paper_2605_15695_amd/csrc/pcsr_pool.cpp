@@ -338,60 +338,72 @@ Sides &sides()
 
 namespace {
 // Pinned memory that a kernel leaves results in for the host: of one thread at a time, kept for the next one when that ends.
+// Coherent: the host looks at it while the kernel is still there.
 constexpr size_t kMailBytes = 256;
 struct Mail {
     unsigned char data[kMailBytes];
-    unsigned seq; // of the last results in it
+    unsigned seq; // of the results in it
 };
-struct MailList {
+struct Box {
+    Mail *mail = nullptr;
+    unsigned last = 0; // number of the last hand-over, whether it arrived or not
+};
+struct BoxList {
     std::mutex mu;
-    std::vector<Mail *> idle;
+    std::vector<Box> idle;
 };
-MailList &mail_list()
+BoxList &box_list()
 {
-    static MailList *l = new MailList;
+    static BoxList *l = new BoxList;
     return *l;
 }
-struct OwnMail {
-    Mail *mail = nullptr;
+struct OwnBox {
+    Box box;
     bool tried = false;
-    Mail *get() noexcept
+    Box *get() noexcept
     try {
-        if (mail || tried) return mail;
+        if (box.mail) return &box;
+        if (tried) return nullptr;
         tried = true;
-        MailList &l = mail_list();
+        BoxList &l = box_list();
         {
             std::lock_guard<std::mutex> lock(l.mu);
             l.idle.reserve(l.idle.size() + 1);
             if (!l.idle.empty()) {
-                mail = l.idle.back();
+                box = l.idle.back();
                 l.idle.pop_back();
-                return mail;
+                return &box;
             }
         }
         void *p = nullptr;
-        if (hipHostMalloc(&p, sizeof(Mail), hipHostMallocPortable) != hipSuccess) {
+        if (hipHostMalloc(&p, sizeof(Mail), hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
-        mail = static_cast<Mail *>(p);
-        mail->seq = 0;
-        return mail;
+        box.mail = static_cast<Mail *>(p);
+        box.mail->seq = box.last;
+        return &box;
     } catch (...) {
         return nullptr;
     }
-    ~OwnMail()
+    // What was to arrive may do so at any time: never used again, nor given back.
+    void retire() noexcept
     {
-        if (!mail) return;
+        box = Box();
+        tried = false;
+    }
+    ~OwnBox()
+    {
+        if (!box.mail) return;
         try {
-            MailList &l = mail_list();
+            BoxList &l = box_list();
             std::lock_guard<std::mutex> lock(l.mu);
-            l.idle.push_back(mail);
+            l.idle.push_back(box);
         } catch (...) {
         }
     }
 };
-thread_local OwnMail t_mail;
+thread_local OwnBox t_box;
 thread_local bool t_enqueued = true; // on t_setup_stream, since it was last known to be idle
 constexpr int kSpins = 200000;       // some milliseconds; then the runtime's own wait, which also reports errors
 } // namespace
@@ -413,19 +425,26 @@ hipError_t setup_wait() noexcept
 hipError_t setup_copy(void *dst, const void *src, size_t bytes, hipMemcpyKind kind) noexcept
 {
     const hipStream_t s = t_setup_stream;
-    Mail *const mail = kind == hipMemcpyDeviceToHost && bytes <= kMailBytes && bytes % 4 == 0 ? t_mail.get() : nullptr;
-    if (mail) {
-        const unsigned seq = mail->seq + 1;
+    Box *const box = kind == hipMemcpyDeviceToHost && bytes <= kMailBytes && bytes % 4 == 0 ? t_box.get() : nullptr;
+    if (box) {
+        Mail *const mail = box->mail;
+        const unsigned seq = ++box->last;
         hipError_t e = deliver(mail->data, src, (int)(bytes / 4), &mail->seq, seq, s);
-        if (e != hipSuccess) return e;
-        const volatile unsigned *const arrived = &mail->seq;
-        for (int i = 0; i < kSpins && *arrived != seq; ++i) __builtin_ia32_pause();
-        if (*arrived != seq) {
-            e = hipStreamSynchronize(s);
-            if (e != hipSuccess) return e;
-            if (*arrived != seq) return hipErrorUnknown;
+        if (e != hipSuccess) {
+            t_box.retire();
+            return e;
         }
-        std::atomic_thread_fence(std::memory_order_acquire);
+        auto arrived = [&] { return __atomic_load_n(&mail->seq, __ATOMIC_ACQUIRE) == seq; };
+        for (int i = 0; e == hipSuccess && i < kSpins && !arrived(); ++i) __builtin_ia32_pause();
+        if (!arrived()) {
+            const hipError_t w = hipStreamSynchronize(s);
+            if (e == hipSuccess) e = w;
+            if (!arrived()) {
+                t_box.retire();
+                if (e == hipSuccess) e = hipErrorUnknown;
+            }
+        }
+        if (e != hipSuccess) return e;
         std::memcpy(dst, mail->data, bytes);
         t_enqueued = false;
         return hipSuccess;

@@ -1,7 +1,7 @@
 // A device of host memory for the CPU tests of the library's host code: the HIP calls it makes, with
 // allocations that can be made to fail, on the device and (operator new) on the host.  Kernels do not run
-// (hipLaunchKernel does nothing), so only what happens before the first result of one is read can be
-// tested, and what follows a result that a test supplies (fake_hip_answer).
+// (but for the one that brings results to the host), so only what happens before the first result of one is
+// read can be tested, and what follows a result that a test supplies (fake_hip_answer).
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -22,7 +22,7 @@ void operator delete(void *p) noexcept { std::free(p); }
 void operator delete(void *p, std::size_t) noexcept { std::free(p); }
 
 extern "C" {
-enum { kOk = 0, kOutOfMemory = 2 };
+enum { kOk = 0, kOutOfMemory = 2, kLaunchFailure = 719, kCaptureImplicit = 906 };
 static int calls, first_bad, last_bad; // allocations [first_bad, last_bad] fail, counted from 1
 static std::size_t refuse_from, refuse_to; // and those of refuse_from to refuse_to bytes
 static long live;
@@ -60,7 +60,6 @@ int hipGetDevice(int *d) { *d = 0; return kOk; }
 int hipSetDevice(int d) { (void)d; return kOk; }
 int hipGetLastError(void) { return kOk; }
 int hipDeviceSynchronize(void) { return kOk; }
-int hipStreamSynchronize(void *s) { (void)s; return kOk; }
 int hipMalloc(void **p, std::size_t bytes)
 {
     ++calls;
@@ -77,20 +76,36 @@ int hipFree(void *p)
     std::free(p);
     return kOk;
 }
-int hipHostMalloc(void **p, std::size_t bytes, unsigned flags) { (void)p; (void)bytes; (void)flags; return kOutOfMemory; }
+// Pinned memory: none unless asked for.
+static int pinned;
+static unsigned pinned_flags = ~0u; // those that all of it was asked for with
+void fake_hip_pinned(int on) { pinned = on; }
+unsigned fake_hip_pinned_flags(void) { return pinned_flags; }
+int hipHostMalloc(void **p, std::size_t bytes, unsigned flags)
+{
+    if (!pinned) return kOutOfMemory;
+    pinned_flags &= flags;
+    *p = std::calloc(1, bytes);
+    return *p ? kOk : kOutOfMemory;
+}
 // A copy of `bytes` bytes to the host brings these in place of what is there (bytes 0: none does).
 static std::size_t answer_bytes[4];
-static unsigned char answers[4][64];
+static unsigned char answers[4][128];
 void fake_hip_answer(int slot, std::size_t bytes, const void *what)
 {
     answer_bytes[slot] = bytes;
     std::memcpy(answers[slot], what, bytes);
 }
-int hipMemcpy(void *dst, const void *src, std::size_t bytes, int kind)
+static void to_host(void *dst, const void *src, std::size_t bytes)
 {
     std::memcpy(dst, src, bytes);
     for (int i = 0; i < 4; ++i)
-        if (kind == 2 && bytes && bytes == answer_bytes[i]) std::memcpy(dst, answers[i], bytes);
+        if (bytes && bytes == answer_bytes[i]) std::memcpy(dst, answers[i], bytes);
+}
+int hipMemcpy(void *dst, const void *src, std::size_t bytes, int kind)
+{
+    if (capturing) return kCaptureImplicit;
+    kind == 2 ? to_host(dst, src, bytes) : (void)std::memcpy(dst, src, bytes);
     return kOk;
 }
 int hipMemcpyAsync(void *dst, const void *src, std::size_t bytes, int kind, void *s)
@@ -118,10 +133,48 @@ int __hipPopCallConfiguration(Dim3 *grid, Dim3 *block, std::size_t *lds, void **
     *stream = pushed.stream;
     return kOk;
 }
+// The one kernel that is run: deliver_kernel, which leaves results in pinned memory.  Its next run can be kept back: the wait for it
+// fails, and it runs when the next one would, which then does so when it is waited for.
+static const void *deliver_kernel;
+void __hipRegisterFunction(void *, const void *fn, char *, const char *name, unsigned, void *, void *, void *, void *, int *)
+{
+    if (std::strstr(name, "deliver_kernel")) deliver_kernel = fn;
+}
+struct Delivery {
+    void *to;
+    unsigned char what[256];
+    std::size_t bytes;
+    unsigned *flag, seq;
+};
+static Delivery kept;
+static enum { kRuns, kNextKept, kKept, kLate } delivery = kRuns;
+void fake_hip_keep_back(void) { delivery = kNextKept; }
+static void arrive(const Delivery &d)
+{
+    std::memcpy(d.to, d.what, d.bytes);
+    __atomic_store_n(d.flag, d.seq, __ATOMIC_RELEASE);
+}
+static void deliver(void **args)
+{
+    Delivery d = {*(void **)args[0], {}, 4u * (std::size_t)*(int *)args[2], *(unsigned **)args[3], *(unsigned *)args[4]};
+    to_host(d.what, *(const void **)args[1], d.bytes);
+    if (delivery == kRuns) return arrive(d);
+    if (delivery == kKept) arrive(kept);
+    kept = d;
+    delivery = delivery == kKept ? kLate : kKept;
+}
+int hipStreamSynchronize(void *s)
+{
+    (void)s;
+    if (delivery == kKept) return kLaunchFailure;
+    if (delivery == kLate) arrive(kept), delivery = kRuns;
+    return kOk;
+}
 int hipLaunchKernel(const void *fn, Dim3 grid, Dim3 block, void **args, std::size_t lds, void *stream)
 {
-    (void)fn, (void)grid, (void)block, (void)args, (void)lds, (void)stream;
+    (void)grid, (void)block, (void)lds, (void)stream;
     ++launches;
+    if (fn == deliver_kernel) deliver(args);
     return kOk;
 }
 }
