@@ -34,3 +34,14 @@ assert features(111)[0] == binding.PCSR_E_HIP              # the wait for them f
 assert features(222) == (0, 222.0)                         # and they arrive while the next call waits for its own
 assert features(333) == (0, 333.0)
 """)
+
+
+def test_refused_while_a_stream_is_captured(fake):  # noqa: F811
+    """As a copy on the null stream is, however the results come: what the capture is yet to make would be counted."""
+    _run(fake, FEATURES + """
+assert features(77) == (0, 77.0)
+fake.fake_hip_capture(1)
+assert features(78)[0] == binding.PCSR_E_HIP
+fake.fake_hip_capture(0)
+assert features(79) == (0, 79.0)
+""")
