@@ -103,6 +103,7 @@ struct pcsr_handle_s {
     int32_t *d_item_slot = nullptr;   // per item: workspace slot, -1 for a sole item (S only)
     int32_t *d_sched = nullptr;       // column-ordered schedule: 4 int32 per launch position
     int32_t *d_split_slot = nullptr;  // their first workspace slots (n_split + 1 entries)
+    bool dropped = false;             // built without an array that did not fit (DeviceBuild::dropped)
     int32_t *d_bands = nullptr;       // PCSR_FLAG_COLUMN_BANDS: where the rows' columns pass into each band but the first
     int32_t *d_long = nullptr;        // positions in d_split of panels with more than kLongPanelSlots items
     int64_t n_long = 0;
@@ -516,6 +517,7 @@ int handle_from_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_
     h->d_split_slot = db.split_slot;
     h->d_long = db.long_list;
     h->d_bands = db.bands;
+    h->dropped = db.dropped;
     h->n_split = db.n_split;
     h->n_split_items = db.n_split_items;
     h->n_long = db.n_long;
@@ -853,7 +855,10 @@ static int operator_on_gpu(int64_t n_rows, int64_t n_cols, int64_t nnz, const in
                     rc = PCSR_E_OOM;
                 }
                 beside.join();
-                return rc != PCSR_OK ? rc : failed(rc2, hip2);
+                if (rc == PCSR_OK) rc = failed(rc2, hip2);
+                // What the one had no room for beside the other's scratch may fit when it is alone: the same memory, the same handles.
+                if (rc == PCSR_OK && (made[0]->dropped || made[1]->dropped)) rc = PCSR_E_OOM;
+                return rc;
             }
         }
     }

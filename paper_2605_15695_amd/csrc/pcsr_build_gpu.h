@@ -23,6 +23,7 @@ struct DeviceBuild {
     bool vals_due = false;  // val is still to be filled, once `late` is there
     int32_t *bands = nullptr; // band_ends of the rows (or null), kColumnBands - 1 of them one after the other
     bool clustered = false; // the schedule runs the rows community by community
+    bool dropped = false;   // something that the product can do without did not fit in memory
     struct {                // the arrays of a product with windows of communities (blocks 0: none)
         int32_t *rowptr = nullptr, *colidx = nullptr, *rows = nullptr, *ptr = nullptr, *hi = nullptr;
         float *val = nullptr;

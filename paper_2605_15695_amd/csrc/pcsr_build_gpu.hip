@@ -891,6 +891,7 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
     if (clusters && cluster_probe_says(check.common, n_rows)) {
         rc = cluster_rows(n_rows, d_rowptr, d_colidx, &labels.p, &label_size, hip_err);
         if (rc != PCSR_OK && rc != PCSR_E_OOM) return rc; // without the memory for it: the order asked for otherwise
+        out->dropped |= rc == PCSR_E_OOM;
         if (labels.p) {
             S = 1;
             SG = kClusterItem;
@@ -904,6 +905,7 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
         if (late) HIP_TRY(late->wait());
         rc = cluster_windows(n_rows, nnz, d_rowptr, d_colidx, d_vals, labels.p, out, hip_err);
         if (rc != PCSR_OK && rc != PCSR_E_OOM) return rc; // without the memory for them: the order alone
+        out->dropped |= rc == PCSR_E_OOM;
     }
     if (V == 1) {
         if (!S) {
@@ -1081,6 +1083,7 @@ int build_device(int64_t n_rows, int64_t n_cols, int64_t nnz, const int32_t *d_r
             sc.release(b);
         } else {
             (void)hipGetLastError(); // products without them
+            out->dropped = true;
         }
     }
     out->vals_due = late && V == 1;

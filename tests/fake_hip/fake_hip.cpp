@@ -24,7 +24,8 @@ void operator delete(void *p, std::size_t) noexcept { std::free(p); }
 extern "C" {
 enum { kOk = 0, kOutOfMemory = 2, kLaunchFailure = 719, kCaptureImplicit = 906 };
 static int calls, first_bad, last_bad; // allocations [first_bad, last_bad] fail, counted from 1
-static std::size_t refuse_from, refuse_to; // and those of refuse_from to refuse_to bytes
+static std::size_t refuse_from, refuse_to; // and those of refuse_from to refuse_to bytes, so often
+static int refuse_left;
 static long live;
 
 void fake_hip_fail(int first, int last)
@@ -37,7 +38,9 @@ void fake_hip_refuse(std::size_t from, std::size_t to)
 {
     refuse_from = from;
     refuse_to = to;
+    refuse_left = 1 << 30;
 }
+void fake_hip_refuse_times(int times) { refuse_left = times; }
 void fake_new_fail(int at)
 {
     new_calls = 0;
@@ -64,7 +67,10 @@ int hipMalloc(void **p, std::size_t bytes)
 {
     ++calls;
     if (calls >= first_bad && calls <= last_bad) return kOutOfMemory;
-    if (refuse_to && bytes >= refuse_from && bytes <= refuse_to) return kOutOfMemory;
+    if (refuse_to && bytes >= refuse_from && bytes <= refuse_to && refuse_left > 0) {
+        --refuse_left;
+        return kOutOfMemory;
+    }
     *p = std::calloc(1, bytes ? bytes : 1);
     if (!*p) return kOutOfMemory;
     ++live;
@@ -74,6 +80,29 @@ int hipFree(void *p)
 {
     if (p) --live;
     std::free(p);
+    return kOk;
+}
+// Streams: none unless asked for, and then all the same.
+static int streams, streams_made;
+void fake_hip_streams(int on) { streams = on; }
+int fake_hip_streams_made(void) { return streams_made; }
+int hipStreamCreateWithFlags(void **s, unsigned flags)
+{
+    (void)flags;
+    static int made;
+    if (!streams) return kOutOfMemory;
+    ++streams_made;
+    *s = &made;
+    return kOk;
+}
+int hipStreamDestroy(void *s) { (void)s; return kOk; }
+int hipGetStreamDeviceId(void *s) { (void)s; return 0; }
+int hipFuncSetAttribute(const void *fn, int attribute, int value) { (void)fn, (void)attribute, (void)value; return kOk; }
+int hipDeviceGetAttribute(int *value, int attribute, int device) { (void)attribute, (void)device; *value = 256; return kOk; }
+int hipGetDevicePropertiesR0600(void *properties, int device)
+{
+    (void)device;
+    std::memset(properties, 0, 1472); // hipDeviceProp_t
     return kOk;
 }
 // Pinned memory: none unless asked for.
@@ -110,9 +139,8 @@ int hipMemcpy(void *dst, const void *src, std::size_t bytes, int kind)
 }
 int hipMemcpyAsync(void *dst, const void *src, std::size_t bytes, int kind, void *s)
 {
-    (void)kind;
     (void)s;
-    std::memcpy(dst, src, bytes);
+    kind == 2 ? to_host(dst, src, bytes) : (void)std::memcpy(dst, src, bytes);
     return kOk;
 }
 int hipMemsetAsync(void *dst, int v, std::size_t bytes, void *s) { (void)s; std::memset(dst, v, bytes); return kOk; }

@@ -247,3 +247,36 @@ fake.fake_hip_refuse(2 << 20, 2 << 20)                     # the table of the ba
 less = built()
 assert less[0] < whole[0] and less[1] >= whole[1]
 """)
+
+
+# how often the bands of a direction do not fit: beside the other direction's scratch, or whenever they are asked for
+@pytest.mark.parametrize("times", [0, 1, 2, 1 << 30])
+def test_operators_are_built_again_where_the_other_direction_took_the_room(fake, times):
+    """What a handle goes without does not depend on what the other direction, built at the same time, had allocated just then."""
+    _run(fake, f"""
+rowptr, colidx = np.arange(0, n * 100 + 1, 100, dtype=np.int32), np.tile(np.arange(100, dtype=np.int32) * 300, n)
+checked, xcds = np.zeros(10, np.int32), np.arange(9, dtype=np.int32) * (n // 8)
+checked[[2, 3, 4]] = n * 100, 100, n                       # bad, first, last, longest, nonempty
+for slot, a in enumerate((checked, xcds)):
+    fake.fake_hip_answer(slot, ctypes.c_size_t(a.nbytes), a.ctypes.data_as(ctypes.c_void_p))
+fake.fake_hip_streams(1)
+vals = np.ones(n * 100, np.float32)
+args = n, n, rowptr, colidx, vals, pc.make_params(V=1, flags=pc.PCSR_FLAG_COLUMN_BANDS), 256, True
+
+
+def bands(h):                                              # several launches, if the handle has them
+    before = fake.fake_hip_launches()
+    assert binding._lib().pcsr_spmm(h.raw, ctypes.c_void_p(1 << 33), ctypes.c_void_p(1 << 40), 256, None) == 0
+    return fake.fake_hip_launches() - before > 1
+
+
+fake.fake_hip_refuse(2 << 20, 2 << 20)                     # the table of the bands, in whole MiB
+fake.fake_hip_refuse_times({times})
+a, b = binding.pcsr_operator_build(*args)
+assert fake.fake_hip_streams_made() > 0                    # both directions at once, the first time
+assert bands(a) == bands(b) == ({times} < 1 << 30), (bands(a), bands(b))
+a.close()
+b.close()
+pc.pcsr_release_cached()
+assert fake.fake_hip_live() == 0
+""")
