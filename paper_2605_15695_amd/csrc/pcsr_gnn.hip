@@ -22,14 +22,16 @@ __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_a
 // 128 of them, where the fp32 instructions are off by 1.44 / 2.03e-7.  One accumulator for all six is off by 0.93 / 1.53, but to one side: these
 // instructions cut off what does not reach the last bit of a sum, and sums of 200,000 such results were off 5 to 10 times as much as before.
 // They do 2420 TFLOP/s here for 150: 2.7 times the rate with six of them.
-// Rows with numbers of 2^60 and more, infinities among them, and all rows where a weight or a bias reaches 2^20 and 2^60, are left to the
-// fp32 instructions, in a loop of their own: an infinity has no pieces, and below that neither the products of two layers nor their pieces'
-// overflow.  Below 2^-110 the last piece runs out of exponent: off by 2^-134 at most.
+// Rows and weights are taken 2^16 times as large, and the sums 2^-32 times: bf16 reaches as low as 2^-133, floats to 2^-149, so that the last
+// piece of the smallest number is whole, and no bit of a sum changes (rows of 2^-115 were off by 1.1e-6, of 2^-124 by 5.6e-4 without).
+// Rows with numbers of 2^50 and more, infinities among them, and all rows where a weight or a bias reaches 2^16 and 2^50, are left to the
+// fp32 instructions, in a loop of their own that takes 6 times as long: an infinity has no pieces, and below that neither the
+// products of two layers nor their pieces' overflow: 64 (64 * 2^50 * 2^16) * 2^16 * 2^32 = 2^126.
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 struct Pieces {
     u4 p[3]; // of eight floats
 };
-constexpr float kRowsBelow = 0x1p60f, kWeightsBelow = 0x1p20f;
+constexpr float kRowsBelow = 0x1p50f, kWeightsBelow = 0x1p16f, kLarger = 0x1p16f, kLargerSum = kLarger * kLarger;
 
 __device__ __forceinline__ unsigned bf16_pair(float a, float b)
 {
@@ -43,6 +45,8 @@ __device__ __forceinline__ float bf16_high(unsigned p) { return __builtin_bit_ca
 __device__ __forceinline__ Pieces split(float (&x)[8])
 {
     Pieces s;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] *= kLarger;
 #pragma unroll
     for (int p = 0; p < 3; ++p)
 #pragma unroll
@@ -234,7 +238,10 @@ template <int KT, int NT, bool SPLIT> struct Product {
             for (int nt = 0; nt < NS; nt += S) {
                 f4 low[S];
 #pragma unroll
-                for (int i = 0; i < S; ++i) low[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int i = 0; i < S; ++i) {
+                    low[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                    acc[nt + i] *= kLargerSum;
+                }
 #pragma unroll
                 for (int k = 0; k < kSteps; ++k) {
                     Pieces w[S];
@@ -246,7 +253,7 @@ template <int KT, int NT, bool SPLIT> struct Product {
                     mfma_pieces<S>(w, xs[k], acc + nt, low);
                 }
 #pragma unroll
-                for (int i = 0; i < S; ++i) acc[nt + i] += low[i];
+                for (int i = 0; i < S; ++i) acc[nt + i] = (acc[nt + i] + low[i]) * (1.0f / kLargerSum);
             }
         } else {
 #pragma unroll 1
@@ -282,15 +289,16 @@ template <int T> __device__ __forceinline__ bool small_rows(const f4 (&x)[T])
     }
     return __builtin_amdgcn_ballot_w64(!(most < kRowsBelow)) == 0;
 }
-// the same of the weights and a bias (null: none) for the workgroup; a barrier
-template <int N, bool SPLIT> __device__ __forceinline__ bool small_weights(float most, const f4 *bias)
+// the same of the weights and of biases (null: none) as stage_bias has left them, for the workgroup; a barrier
+template <int N, bool SPLIT> __device__ __forceinline__ bool small_weights(float most, const f4 *bias = nullptr, const f4 *other = nullptr)
 {
     if (!SPLIT) {
         __syncthreads();
         return true;
     }
     float b = 0.0f;
-    for (int o = threadIdx.x; bias && o < N; o += blockDim.x) b = fmaxf(b, fabsf(reinterpret_cast<const float *>(bias)[o]));
+    for (const f4 *one : {bias, other})
+        for (int o = threadIdx.x; one && o < N; o += blockDim.x) b = fmaxf(b, fabsf(reinterpret_cast<const float *>(one)[o]));
     return !__syncthreads_or(!(most < kWeightsBelow) || !(b < kRowsBelow));
 }
 
@@ -595,7 +603,7 @@ __global__ void __launch_bounds__(64 * piece_waves(KT, NT), RED || piece_waves(K
     stage_bias<NT>(bias, p.bias, 16 * NT);
     float most = 0.0f;
     const auto W = Weights::stage(wfrag, p.W, p.w_transposed, most);
-    bool in_pieces = small_weights<0, Weights::kSplit>(most, nullptr);
+    bool in_pieces = small_weights<16 * NT, Weights::kSplit>(most, bias);
 
     f4 csum[RED ? NT : 1], csums[RED ? NT : 1]; // sums of kSumRun groups are put apart
     float dot = 0.0f, dots = 0.0f;
@@ -733,7 +741,7 @@ template <int KT, int MT> __global__ void __launch_bounds__(64 * kWaves, mlp_blo
     const auto W1 = Product<KT, MT, split_mlp(MT)>::stage(w1, p.W1, 0, most);
     const auto W2 = Product<MT, MT, split_mlp(MT)>::stage(w2, p.W2, 0, most);
     constexpr bool kSplit = split_mlp(MT);
-    bool in_pieces = small_weights<16 * MT, kSplit>(most, bias1);
+    bool in_pieces = small_weights<16 * MT, kSplit>(most, bias1, bias2);
     const long full = p.n >> 4, stride = (long)gridDim.x * kWaves;
     long g = (long)blockIdx.x * kWaves + wave;
     f4 xn[KT];
@@ -883,7 +891,7 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
         if constexpr (TWO) return Product<MT, AT, kSplit>::stage(w1, p.W1, 1, most);
         else return 0;
     }();
-    bool in_pieces = small_weights<0, kSplit>(most, nullptr);
+    bool in_pieces = small_weights<0, kSplit>(most);
 
     const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     f4 acc2[BT][MT], acc1[TWO ? MT : 1][TWO ? AT : 1], csum[MT];

@@ -202,14 +202,16 @@ def _matches(got, ref, size, terms):
     assert bool(((got - ref).abs() <= terms * 2.0 ** -24 * size + 1e-30)[finite].all())
 
 
-# products in pieces: rows, weights and biases that have no pieces (from 2^60 and 2^20 on, and infinities), in the first rows, among those of
+# products in pieces: rows, weights and biases that have no pieces (from 2^50 and 2^16 on, and infinities), in the first rows, among those of
 # a loop that has begun, in a group that is not whole.  One number of a product may be all of its size, so that every sum after it is
 # rounded at that size: the bound is that of the whole chain, of as many terms as the product has and, for sums over rows, as a wavefront has
 # rows (40009 / 2048 groups of 16, or steps of 16 rows in four parts) and a column has partial sums (512, 16 of them in a chain).
 @pytest.mark.parametrize("a,b", [(16, 64), (32, 64), (64, 64), (48, 64), (64, 96), (96, 96), (64, 128), (128, 128)])
 @pytest.mark.parametrize("n,row", [(5, 0), (40009, 39000), (40009, 40008)])
 @pytest.mark.parametrize("value,where", [(float("inf"), "row"), (-3e30, "row"), (2.0 ** 60, "row"), (float("inf"), "weight"),
-                                         (2.0 ** 20, "weight"), (1e30, "weight"), (float("inf"), "bias"), (1e30, "bias")])
+                                         (2.0 ** 20, "weight"), (1e30, "weight"), (float("inf"), "bias"), (1e30, "bias"),
+                                         (2.0 ** 50, "row"), (1.1e15, "row"), (2.0 ** 16, "weight"), (65535.0, "weight"), (1.1e15, "bias"),
+                                         (2.0 ** 50, "bias")])
 def test_numbers_without_pieces(a, b, n, row, value, where):
     g = torch.Generator(device="cuda").manual_seed(a * 100 + b)
     X, H = (torch.randn(n, a, generator=g, device="cuda") for _ in range(2))
@@ -246,6 +248,93 @@ def test_numbers_without_pieces(a, b, n, row, value, where):
     _matches(dW1, G1.t() @ Xd, size2.t() @ Xd.abs(), b + 400)
     _matches(dW2, Gd.t() @ Z.double(), Gd.abs().t() @ Z.double(), 400)
     _matches(db1, G1.sum(0), size2.sum(0), b + 400)
+
+
+def _in_pieces(a, b, seed, scale_rows=1.0, scale_weights=1.0, n=20011):
+    """(name, got, 64 bits, magnitudes) of the layers' products of normal numbers, whatever form the widths take them in"""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    X, H = (torch.randn(n, a, generator=g, device="cuda") * scale_rows for _ in range(2))
+    G = torch.randn(n, b, generator=g, device="cuda") * scale_rows
+    W1 = torch.randn(b, a, generator=g, device="cuda") * scale_weights
+    W2 = torch.randn(b, b, generator=g, device="cuda")
+    zero = torch.zeros(b, device="cuda")
+    d = _dense(a, b)
+    d.ws_floats = max(d.ws_floats, d.lib.pcsr_gnn_workspace_floats(b, b))
+    Xd, Gd, W1d, W2d = (t.double() for t in (X, G, W1, W2))
+    fwd, back = (Xd @ W1d.t(), Xd.abs() @ W1d.abs().t()), (Gd @ W1d, Gd.abs() @ W1d.abs())
+    yield "linear", d.linear(X, W1), *fwd
+    yield "turned", d.linear(G, W1, transposed=True), *back
+    Z, Y = d.mlp(X, W1, zero, W2, zero, False)
+    yield "first", Z, torch.relu(fwd[0]), fwd[1]
+    yield "second", Y, Z.double() @ W2d.t(), Z.double().abs() @ W2d.abs().t()
+    yield "back", d.linear_backward(G, X, W1)[0], *back
+    Z = torch.relu(torch.randn(n, b, generator=g, device="cuda"))
+    on = (Z > 0).double()
+    dA = d.mlp_backward(G, Z, X, H, W1, W2, True)[0]
+    yield "both", dA, (Gd @ W2d * on) @ W1d, (Gd.abs() @ W2d.abs() * on) @ W1d.abs()
+
+
+# Against 64 bits: the fp32 instructions are off by 1.45e-7 over 64 terms and 2.03e-7 over 128 (2-norm), pieces by 0.50 and 0.65e-7; with
+# all six products in one accumulator it is 0.93 and 1.53e-7, to one side, and without the two smallest 34e-7.  The mean difference is
+# 0.4e-10 of the magnitudes at most, where that of one accumulator is ten times as much.
+@pytest.mark.parametrize("a,b,pieces", [(64, 64, ("first", "second", "back")), (32, 64, ("first", "second", "both")), (64, 96, ("linear", "turned")),
+                                        (64, 128, ("linear", "turned")), (96, 96, ("linear", "turned")), (96, 128, ("linear", "turned")),
+                                        (128, 128, ("linear", "turned"))])
+def test_products_in_pieces_are_more_exact_than_fp32_ones(a, b, pieces):
+    most = {32: 0.65e-7, 64: 0.75e-7, 96: 0.85e-7, 128: 0.95e-7}
+    seen = []
+    for name, got, ref, size in _in_pieces(a, b, a * 100 + b):
+        off = got.double() - ref
+        seen.append((name, float(off.norm() / ref.norm()), float((off / size.clamp_min(1e-30)).mean())))
+    for name, norm, mean in seen:
+        if name in pieces:
+            terms = a if name in ("linear", "first") else b
+            assert norm < (1.1e-7 if name == "both" else most[terms]), seen
+            assert abs(mean) < 1.5e-10, seen
+
+
+# Numbers near the least that a float can be: bf16 does not reach as low, so the pieces are of numbers 2^16 times as large.  The
+# bound is that of a chain of fp32 sums, each off by half of the last bit or of the least number.
+@pytest.mark.parametrize("a,b", [(32, 64), (64, 64), (64, 96), (96, 96), (64, 128), (128, 128)])
+@pytest.mark.parametrize("rows,weights", [(-105, 0), (-115, 0), (-124, 0), (-130, 0), (-146, 0), (0, -115), (0, -130), (0, -146), (-60, -60),
+                                          (40, -130), (-130, 12)])
+def test_small_numbers_have_pieces(a, b, rows, weights):
+    for name, got, ref, size in _in_pieces(a, b, a * 100 + b, 2.0 ** rows, 2.0 ** weights, n=4099):
+        terms = 2 * b + 4 if name == "both" else b + 2 if name in ("turned", "back", "second") else a + 2
+        off = (got.double() - ref).abs()
+        # (the products of two layers round twice: the second takes the least number of the first by its weights)
+        least = terms * 2.0 ** -150 * (1.0 + 4.0 * b * max(2.0 ** weights, 1.0) * (name == "both"))
+        assert bool((off <= terms * 2.0 ** -24 * size + least).all()), (name, float((off / (size + 1e-300)).max()))
+        if rows + weights >= -120:  # no sum is near the least number: the fp32 instructions' 2-norm over 128 terms, and over two layers
+            assert float(off.norm() / ref.norm()) < 2.5e-7, name
+
+
+# one large number whose weight is zero beside small ones: these are the result
+def test_small_numbers_beside_large_ones():
+    n, a, b = 1000, 96, 128
+    g = torch.Generator(device="cuda").manual_seed(1)
+    X, W = torch.randn(n, a, generator=g, device="cuda") * 2.0 ** -118, torch.randn(b, a, generator=g, device="cuda")
+    X[:, 5], W[:, 5] = 3.0, 0.0
+    ref, size = X.double() @ W.double().t(), X.double().abs() @ W.double().abs().t()
+    _matches(_dense(a, b).linear(X, W) * 2.0 ** 100, ref * 2.0 ** 100, size * 2.0 ** 100, a + 2)
+
+
+@pytest.mark.parametrize("a,b", [(64, 64), (64, 96), (64, 128), (128, 128)])
+@pytest.mark.parametrize("n,row", [(5, 0), (4099, 3000), (4099, 4098)])
+@pytest.mark.parametrize("where", ["row", "weight"])
+def test_no_number_shows_where_it_belongs(a, b, n, row, where):
+    g = torch.Generator(device="cuda").manual_seed(a * 100 + b)
+    X, G = torch.randn(n, a, generator=g, device="cuda"), torch.randn(n, b, generator=g, device="cuda")
+    W = torch.randn(b, a, generator=g, device="cuda")
+    if where == "row":
+        X[row, 7] = G[row, 9] = float("nan")
+    else:
+        W[5, 3] = float("nan")
+    d = _dense(a, b)
+    Xd, Gd, Wd = X.double(), G.double(), W.double()
+    _matches(d.linear(X, W), Xd @ Wd.t(), Xd.abs() @ Wd.abs().t(), a + 2)
+    for got in (d.linear(G, W, transposed=True), d.linear_backward(G, X, W)[0]):
+        _matches(got, Gd @ Wd, Gd.abs() @ Wd.abs(), b + 2)
 
 
 @pytest.mark.parametrize("name,kw", [("rmat20", dict(V=1, S=1, SG=4)), ("rmat20", dict(V=2, S=0)),
