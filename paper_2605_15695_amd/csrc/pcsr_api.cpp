@@ -1438,12 +1438,15 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // with dwordx2 loads (uniform random columns, 8 to 32 per row, K = 64 and 128: 3-7 %
     // over the best 16-byte shape; local columns keep the 16-byte shapes).
     // But 16 bytes a lane where B is so small that L2 holds it: K = 128 and 192, 2 to 16 MB 0.79-0.98 (8,000 rows of 22, K = 128 9.9 us
-    // and 7.8; 25 MB and more 0.99-1.08).
-    if (!skewed && !windowed && !p.S && !banded && scattered && d_hat >= 8.0 && K >= 64 && K % 2 == 0) {
-        const bool in_l2 = b_bytes > 2e6 && b_bytes < 16e6 && K >= 96 && K % 32 == 0;
-        lpr = in_l2 ? 16 : 32;
-        vec = in_l2 ? 4 : 2;
+    // and 7.8; 25 MB and more 0.99-1.08), and in bands.  That shape only stands in (below): the handle takes every even width and
+    // operands at 8-byte addresses.
+    bool quads = false;
+    if (!skewed && !windowed && !p.S && (!banded || d_hat < 40.0) && scattered && d_hat >= 8.0 && K >= 64 && K % 2 == 0) {
+        const bool in_l2 = b_bytes > 2e6 && b_bytes < 16e6 && K >= 96;
+        lpr = 32;
+        vec = 2;
         rep = 1;
+        quads = (in_l2 || banded) && K % 32 == 0;
     }
     // Single long rows of 33 to 64 columns: a dword a lane and two columns of it, as resolve_launch has it for auto shapes; and scattered ones
     // of 12 and more, K = 64, that L2 holds: 0.77-0.95 of 32 lanes of two floats (20,000 rows of 34 15.7 us and 12.4; at 13 MB 0.98-1.00).
@@ -1457,7 +1460,7 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
         lpr = narrow_lanes(p.S);
         rep = 1;
     }
-    if (banded && K >= 64) { // (300,000 rows of 134 in bands, K = 128: 2212 us, that shape 2342)
+    if (banded && K >= 64 && (d_hat >= 40.0 || K % 2)) { // (300,000 rows of 134 in bands, K = 128: 2212 us, halves of two floats 2342)
         lpr = 16;
         rep = 1;
     }
@@ -1490,6 +1493,8 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
         pair = K <= 32 && !p.S && d_hat >= 8.0;
         wide_shape(K, lpr_cap, &wide, &wide_rep);
         if (pair) wide = 16;
+    } else if (quads) {
+        wide = 16;
     }
     if (wide) {
         int code = 1;

@@ -544,3 +544,34 @@ def test_no_search_for_communities_where_it_would_split_a_row_that_is_whole():
         assert picked(20.0, d_max).S == 0 and picked(20.0, d_max).flags & flag
     assert picked(20.0, 1025).S == 0 and not picked(20.0, 1025).flags & flag
     assert picked(48.0, 1025).S == 1 and picked(48.0, 1025).flags & flag   # split as it is
+
+
+def _uniform(n, deg, **fields):
+    """Features of rows of about deg scattered columns."""
+    return _features("poisson", **{**dict(n=n, n_hat=n, nnz=n * deg, d=deg / n, d_hat=deg, d_max=2 * deg, CV=0.2, CV_hat=0.2, PR_2=0.5,
+                                         near_512=1000 / n), **fields})
+
+
+def _chosen_for(f, K):
+    """pcsr_select's parameters and a (small) handle that has them."""
+    p = pc.pcsr_select(f, K)
+    p.flags |= HOST
+    g = synth.workload("poisson", "small")
+    return p, pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, p)
+
+
+def _kernel(h, K):
+    q = pc.pcsr_query_kernel(h, K)
+    return q["lanes_per_row"], q["vec"], q["rep"]
+
+
+# a B that L2 holds; one that is walked in bands; one of neither
+@pytest.mark.parametrize("n,deg,hint,launched", [(8_000, 22, 128, (16, 4, 1)), (20_000, 12, 192, (16, 4, 1)), (60_000, 36, 256, (16, 4, 1)),
+                                                 (400_000, 20, 128, (32, 2, 1))])
+def test_a_handle_takes_every_even_width_whatever_its_shape_gains(n, deg, hint, launched):
+    """Rows of 8 to 40 scattered columns, from K = 64 on: two floats a lane are what widths and operands are held against."""
+    p, h = _chosen_for(_uniform(n, deg), hint)
+    assert (p.S, p.lanes_per_row, p.vec, p.rep) == (0, 32, 2, 1) and _kernel(h, hint) == launched
+    for K in (2, 6, 16, 62, 66, 70, 130, 194, 258):
+        assert pc.pcsr_query_launch(h, K)["vec"] == 2 and (K > 16 or _kernel(h, K) == (32, 2, 1))
+    h.close()
