@@ -25,14 +25,16 @@ constexpr uint32_t kMagic = 0x50435352u; // "PCSR"
 // Bits of pcsr_params_t.flags in which pcsr_select passes a shape to launch in place of the one in
 // lanes_per_row, vec and rep (see resolve_launch): 4 (kWidePair: 2) floats per load, one (kWideTwice:
 // two) loads per lane, lanes per row 4 << (code - 1) for codes 1 to 5; above them the shape that it
-// stands in for (stands_for), without which the bits say nothing.  Cleared by pcsr_set_kernel_params.
+// stands in for (stands_for), without which the bits say nothing; kWideBeyond: only for rows wider than
+// that one's tile.  Cleared by pcsr_set_kernel_params.
 constexpr int kWideShift = 16;
 constexpr int32_t kWideShape = 7 << kWideShift;
 constexpr int32_t kWidePair = 8 << kWideShift;
 constexpr int32_t kWideTwice = 16 << kWideShift;
 constexpr int kWideForShift = 21;
 constexpr int32_t kWideFor = 127 << kWideForShift;
-constexpr int32_t kWideBits = kWideShape | kWidePair | kWideTwice | kWideFor;
+constexpr int32_t kWideBeyond = 1 << 29;
+constexpr int32_t kWideBits = kWideShape | kWidePair | kWideTwice | kWideFor | kWideBeyond;
 
 int32_t stands_for(int lanes, int vec, int rep)
 {
@@ -388,7 +390,8 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     // auto shape; never where the caller asked for lanes or vectors): widths that are no
     // multiple of 4, and 64-column slices of rows that are no multiple of 128 bytes long, of which
     // every slice touches a line more than it needs.
-    if (!ls->window && ipg == 1 && K > 16) {
+    const bool beyond = (h_lpr || h_vec || h_rep) && (h->flags & kWideBeyond);
+    if (!ls->window && ipg == 1 && K > (beyond ? tile : 16)) {
         int wide = 0, wide_vec = 4, wide_rep = 1;
         if (h_lpr || h_vec || h_rep) {
             if (h->flags & kWideShape) wide = 4 << ((h->flags & kWideShape) >> kWideShift) >> 1;
@@ -1479,7 +1482,7 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // Shape to launch in its place (see resolve_launch).  All figures: uniform columns, 12 to 136
     // per row, R-MAT scale 20, a shuffled community graph.
     int wide = 0, wide_rep = 1;
-    bool pair = false;
+    bool pair = false, beyond = false;
     const bool dword = wide_scatter || (lpr == 16 && vec == 1 && rep == 2 && K <= 32);
     if (K > 64 && K % 32 != 0 && (p.S || scattered || K % 4 != 0)) {
         // one tile for the whole row instead of slices of 64: 1.06-1.36x (0.96x on rows of 96, K = 300)
@@ -1495,11 +1498,21 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
         if (pair) wide = 16;
     } else if (quads) {
         wide = 16;
+    } else if (narrow && p.S && K % 4 == 0) {
+        // Items of 8 lanes of a dword are for up to 8 columns: others as 4 lanes of 16 bytes (R-MAT 2^20, a handle for K = 8: K = 16 337 us
+        // and 238, K = 64 1423 and 960, K = 256 6153 and 3834).
+        wide = 4;
+        beyond = true;
+    } else if (wide_scatter && !banded && d_hat < 32.0 && b_bytes <= 16.0 * 1048576.0) {
+        // and a dword a lane of rows in L2 for up to 32 (20,000 rows of 22, a handle for K = 24: K = 192 29.0 us and 27.1, K = 256 36.3 and 33.4)
+        wide = K % 4 == 0 ? 8 : 16;
+        pair = K % 4 != 0;
+        beyond = true;
     }
     if (wide) {
         int code = 1;
         while (4 << code >> 1 < wide) ++code;
-        p.flags |= code << kWideShift | (pair ? kWidePair : 0) | (wide_rep == 2 ? kWideTwice : 0) | stands_for(lpr, vec, rep);
+        p.flags |= code << kWideShift | (pair ? kWidePair : 0) | (wide_rep == 2 ? kWideTwice : 0) | (beyond ? kWideBeyond : 0) | stands_for(lpr, vec, rep);
     }
     // Workgroup size: four wavefronts, two for short rows and for paired long rows (eight
     // were 4-7 % slower than four on every unsplit input of the later validation sets).

@@ -94,7 +94,7 @@ def _baseline_lib():
     return lib
 
 
-STAND_IN = 0xfff << 16  # flag bits in which pcsr_select passes a shape that stands in for its own
+STAND_IN = 0xfff << 16 | 1 << 29  # flag bits in which pcsr_select passes a shape that stands in for its own
 
 
 def rule_alternatives(p, K: int):

@@ -552,12 +552,16 @@ def _uniform(n, deg, **fields):
                                          near_512=1000 / n), **fields})
 
 
+def _small():
+    g = synth.workload("poisson", "small")
+    return g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals
+
+
 def _chosen_for(f, K):
     """pcsr_select's parameters and a (small) handle that has them."""
     p = pc.pcsr_select(f, K)
     p.flags |= HOST
-    g = synth.workload("poisson", "small")
-    return p, pc.pcsr_build(g.n_rows, g.n_cols, g.rowptr, g.colidx, g.vals, p)
+    return p, pc.pcsr_build(*_small(), p)
 
 
 def _kernel(h, K):
@@ -575,3 +579,22 @@ def test_a_handle_takes_every_even_width_whatever_its_shape_gains(n, deg, hint, 
     for K in (2, 6, 16, 62, 66, 70, 130, 194, 258):
         assert pc.pcsr_query_launch(h, K)["vec"] == 2 and (K > 16 or _kernel(h, K) == (32, 2, 1))
     h.close()
+
+
+def test_shapes_of_narrow_rows_are_for_narrow_rows():
+    """A dword a lane gains at the widths it was chosen for; at others the handle runs the wide loads that it had."""
+    skewed = _uniform(1 << 20, 16, d_hat=25.0, CV=8.0, CV_hat=8.0, d_max=30_000)
+    for hint in (4, 8):
+        p, h = _chosen_for(skewed, hint)
+        assert (p.S, p.lanes_per_row, p.vec, p.rep) == (1, 8, 1, 1)
+        assert [_kernel(h, K) for K in (4, 8, 12, 16, 64, 75, 256)] == [(8, 1, 1)] * 2 + [(4, 4, 1)] * 5
+        q = pc.pcsr_query_kernel(h, 75)
+        assert q["grid_y"] == 5 and q["grid_x"] < pc.pcsr_query_launch(h, 75)["grid_x"]
+        h.close()
+        p.rep = 2                                            # the caller's shape is the caller's at every width
+        assert _kernel(pc.pcsr_build(*_small(), p), 64) == (8, 1, 2)
+    for hint, beyond in ((24, (8, 4, 1)), (30, (16, 2, 1))):
+        p, h = _chosen_for(_uniform(20_000, 22), hint)
+        assert (p.S, p.lanes_per_row, p.vec, p.rep) == (0, 32, 1, 1)
+        assert [_kernel(h, K) for K in (8, 17, hint, 32, 33, 128, 256)] == [(32, 1, 1)] * 4 + [beyond] * 3
+        h.close()
