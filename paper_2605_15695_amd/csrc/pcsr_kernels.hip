@@ -1653,10 +1653,13 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
     const bool past_l2 = (double)args.n_cols * args.K * 4.0 > 32.0 * 1048576.0;
     const bool short_items = !S && args.mean_item < 16 && (ls.k_lpr < 16 || (V == 2 && ls.k_vec == 1 && !epi && past_l2));
     const bool near = near_enough(args) && !short_items;
-    const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 &&
-                        (args.K <= 8 ? ls.k_lpr == 16 && ls.k_rep == 1
-                                     : V == 1 && args.K > 16 && args.K <= 64 && ls.k_lpr >= 16 && ls.k_lpr <= 32 && ls.k_rep <= 2 &&
-                                           ls.k_lpr * ls.k_rep == (args.K <= 32 ? 32 : 64));
+    // Plain products in these shapes at any width: pcsr_select gives them to handles that had sums of 4 to 8 vectors in wide loads
+    // (20,000 rows of 22, a handle for K = 8 at K = 64: rms 4.7e-8 of the sum, 5.6 in sums of 16, 4.7 now), and the additions show
+    // nowhere (K = 9 to 16, rows of 9 to 80: 0.99-1.02 of the time).  Tails come in auto shapes: of 9 to 16 columns they have sums of 16,
+    // and ask for their rows early.
+    const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 && (!epi || args.K <= 8 || args.K > 16) &&
+                        ((ls.k_lpr == 16 && ls.k_rep == 1) ||
+                         (V == 1 && ls.k_lpr >= 16 && ls.k_lpr <= 32 && ls.k_rep <= 2 && ls.k_lpr * ls.k_rep >= 32));
     KernelFn fn;
     size_t lds = 0;
     if (args.band) {
