@@ -579,7 +579,7 @@ spmm_kernel(SpmmArgs a)
         // of a chunk of 32 and 64 lanes made it 2.23 and 2.79e-8 (items of 32 in chunks of 16: 1.82e-8).  These kernels wait on
         // memory: the additions cost nothing (250,000 rows, K = 128 262 us, K = 256 577, both as before).
         constexpr bool FOLD = (S && LPR >= 32) || FORM == kBands || FORM == kNarrow;
-        const bool fours = FORM == kNarrow && REP == 1 && a.mean_item < 22;
+        const bool fours = FORM == kNarrow && LPR == 16 && REP == 1 && a.mean_item < 22; // (wider groups: of 8, as 8 lanes' chunks)
         auto fold = [&] {
 #pragma unroll
             for (int v = 0; v < V; ++v)
