@@ -26,7 +26,8 @@ constexpr uint32_t kMagic = 0x50435352u; // "PCSR"
 // lanes_per_row, vec and rep (see resolve_launch): 4 (kWidePair: 2) floats per load, one (kWideTwice:
 // two) loads per lane, lanes per row 4 << (code - 1) for codes 1 to 5; above them the shape that it
 // stands in for (stands_for), without which the bits say nothing; kWideBeyond: only for rows wider than
-// that one's tile.  Cleared by pcsr_set_kernel_params.
+// that one's tile; kAutoNarrow: up to kAutoNarrowMost columns the auto shapes instead, of a handle whose own
+// has that stands_for.  Cleared by pcsr_set_kernel_params.
 constexpr int kWideShift = 16;
 constexpr int32_t kWideShape = 7 << kWideShift;
 constexpr int32_t kWidePair = 8 << kWideShift;
@@ -34,7 +35,9 @@ constexpr int32_t kWideTwice = 16 << kWideShift;
 constexpr int kWideForShift = 21;
 constexpr int32_t kWideFor = 127 << kWideForShift;
 constexpr int32_t kWideBeyond = 1 << 29;
-constexpr int32_t kWideBits = kWideShape | kWidePair | kWideTwice | kWideFor | kWideBeyond;
+constexpr int32_t kAutoNarrow = 1 << 30;
+constexpr int32_t kAutoNarrowMost = 32;
+constexpr int32_t kWideBits = kWideShape | kWidePair | kWideTwice | kWideFor | kWideBeyond | kAutoNarrow;
 
 int32_t stands_for(int lanes, int vec, int rep)
 {
@@ -48,7 +51,7 @@ int32_t checked_flags(const pcsr_params_t &p)
 {
     const int code = (p.flags & kWideShape) >> kWideShift;
     const bool own = p.lanes_per_row && p.vec && p.rep;
-    if (own && code >= 1 && code <= 5 && (p.flags & kWideFor) == stands_for(p.lanes_per_row, p.vec, p.rep)) return p.flags;
+    if (own && (code >= 1 || (p.flags & kAutoNarrow)) && code <= 5 && (p.flags & kWideFor) == stands_for(p.lanes_per_row, p.vec, p.rep)) return p.flags;
     return p.flags & ~kWideBits;
 }
 
@@ -286,7 +289,7 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
         return PCSR_OK;
     }
     const bool plain = h->host.win_cols == 0 && h->ipg <= 1;
-    const bool own = !(epilogue && plain && (h->lpr || h->vec || h->rep));
+    const bool own = !(epilogue && plain && (h->lpr || h->vec || h->rep)) && !((h->flags & kAutoNarrow) && K <= kAutoNarrowMost);
     const int h_lpr = own ? h->lpr : 0, h_vec = own ? h->vec : 0, h_rep = own ? h->rep : 0;
     int vec = h_vec ? h_vec : (K % 4 == 0 ? 4 : (K % 2 == 0 ? 2 : 1));
     // as pcsr_select: K of 9..16 is served by 16 lanes of one dword unless rows are very short
@@ -1509,6 +1512,10 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
         pair = K % 4 != 0;
         beyond = true;
     }
+    // Rows that are not split for K = 64 and more: few columns of them are best left to the library (150,000 rows of 60, a handle for K = 64:
+    // K = 4, 8, 16 and 24 146, 144, 170 and 187 us in its shape, 91, 91, 99 and 168 when its rows were split, 50, 60, 77 and 127 in auto shapes).
+    const bool auto_narrow = long_uniform && K >= 64 && !p.S && p.V == 1;
+    if (auto_narrow) p.flags |= kAutoNarrow | stands_for(lpr, vec, rep);
     if (wide) {
         int code = 1;
         while (4 << code >> 1 < wide) ++code;

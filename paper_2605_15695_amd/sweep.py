@@ -94,7 +94,8 @@ def _baseline_lib():
     return lib
 
 
-STAND_IN = 0xfff << 16 | 1 << 29  # flag bits in which pcsr_select passes a shape that stands in for its own
+STAND_IN = 0xfff << 16 | 3 << 29  # flag bits in which pcsr_select passes a shape that stands in for its own
+STAND_IN_CODE = 7 << 16  # of them, which shape (0: none)
 
 
 def rule_alternatives(p, K: int):
@@ -107,7 +108,7 @@ def rule_alternatives(p, K: int):
         return q
 
     out = [("pick", p, None)]
-    if p.flags & STAND_IN:
+    if p.flags & STAND_IN_CODE:
         out.append(("own shape", changed(flags=p.flags & ~STAND_IN), None))
     if K % 4 == 0 and K > 32 and not p.col_window:
         lanes = 4

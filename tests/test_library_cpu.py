@@ -598,3 +598,29 @@ def test_shapes_of_narrow_rows_are_for_narrow_rows():
         assert (p.S, p.lanes_per_row, p.vec, p.rep) == (0, 32, 1, 1)
         assert [_kernel(h, K) for K in (8, 17, hint, 32, 33, 128, 256)] == [(32, 1, 1)] * 4 + [beyond] * 3
         h.close()
+
+
+def test_few_columns_of_rows_that_are_not_split_for_many():
+    """Handles for 64 and more columns of long scattered rows: up to 32 they run what is left to the library, unless the caller sets a shape."""
+    auto = pc.pcsr_build(*_small(), pc.make_params(flags=HOST))
+    for hint in (64, 75, 100, 128, 130, 256):
+        f = _uniform(150_000, 60)
+        p, h = _chosen_for(f, hint)
+        own = p.lanes_per_row, p.vec, p.rep
+        assert (p.S, p.V) == (0, 1) and p.flags & pc.PCSR_FLAG_COLUMN_BANDS
+        assert [_kernel(h, K) for K in (1, 4, 7, 16, 17, 24, 32)] == [_kernel(auto, K) for K in (1, 4, 7, 16, 17, 24, 32)]
+        assert (_kernel(h, 64) == own or hint % 32) and pc.pcsr_query_launch(h, 64)["vec"] == own[1]
+        h.close()
+        for field, value in (("lanes_per_row", 8), ("vec", 1 if p.vec > 1 else 2), ("rep", 4)):
+            changed = type(p).from_buffer_copy(p)
+            setattr(changed, field, value)
+            h = pc.pcsr_build(*_small(), changed)
+            assert _kernel(h, 16) == (changed.lanes_per_row, changed.vec, changed.rep)
+            h.close()
+        h = pc.pcsr_build(*_small(), p)
+        pc.pcsr_set_kernel_params(h, *own, p.waves_per_wg)
+        assert _kernel(h, 16) == own
+        h.close()
+    p, _ = _chosen_for(_uniform(60_000, 60), 64)             # split as before
+    assert p.S == 1 and not p.flags >> 29
+    auto.close()
