@@ -261,7 +261,7 @@ int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, i
     int best = 1;
     // Rows of less than 256 are better added up in fewer than 12 parts, and in tiles of whole rows by whole and half wavefronts, whose
     // sums were of 8 before, in parts of 20 and more.
-    const double least = K > 64 && K % 32 != 0 ? 20.0 : 0.0;
+    const double least = tile >= 128 || (K > 64 && K % 32 != 0) ? 20.0 : 0.0;
     for (const int m : {2, 3, 4, 6, 12})
         if (nnz >= std::max(m < 12 ? 0.0 : 256.0, least * m) * n_rows && us(m) < (best > 1 ? 0.98 : 1.0) * us(best)) best = m;
     *saved = us(1) - us(best);

@@ -71,3 +71,15 @@ for K, s in ((72, (32, 4, 1, 1)), (200, (64, 4, 1, 1)), (260, (64, 4, 2, 1)), (5
     assert shape(K) == s, K
 h.close()
 """)
+
+
+def test_wide_tiles_keep_parts_of_20_at_every_width(fake):  # noqa: F811
+    """A handle whose tile is a whole row of 75 to 256 columns, at other widths: its sums were of 8, and shorter parts are less exact."""
+    _run(fake, HANDLE.replace("m, deg, n_cols = 20000, 134, 300_000", "m, deg, n_cols = 100_000, 90, 100_000") + """
+parts = {}
+for lanes in (16, 32, 64):
+    h = handle(flags=pc.PCSR_FLAG_GPU_BUILD | pc.PCSR_FLAG_COLUMN_BANDS, lanes_per_row=lanes, vec=4, rep=1)
+    parts[lanes] = [launches(h, K) for K in (48, 64, 96, 128)]
+    h.close()
+assert max(parts[16]) == 6 and max(parts[32] + parts[64]) == 90 // 20, parts
+""")
