@@ -326,10 +326,13 @@ constexpr int kEarlyTail = 2; // unsplit products whose tail reads the row: the 
 // 4.18; the time is the same).  Over 256 columns it has two tiles of them, in place of the plain kernel, whose sums
 // are of 64 there (rows of 60 11.0e-8, of 90 8.8, here 4.45; 1362 us and 1355, 1265 and 1325).
 constexpr int kBands = 3;
-// One dword a lane, its sums put together more often than the lanes' entries are.  Up to 8 columns of unsplit rows by 16 lanes (narrow_lanes says why), whose sums are of 4 vectors as those of 4 lanes with wider
+// One dword a lane, its sums put together more often than the lanes' entries are, and those of 32 added up apart.  Up to 8 columns of
+// unsplit rows by 16 lanes (narrow_lanes says why), whose sums are of 4 vectors as those of 4 lanes with wider
 // loads are, or of 8 where items are of 22 and more on average: rms difference from 64 bits of rows of 13, 18, 25 and 32 numbers between
-// 0 and 1 4.36, 4.53, 4.65 and 4.72e-8 of their sum, by 4 lanes 4.36, 4.53, 4.90 and 5.23, in sums of 16 5.76, 5.73, 5.46 and 5.44.  And 17 to 32 columns of single rows by 32 lanes, or 16 with two
-// columns each, in place of 8 with four, in sums of 8 as those have (of 16 and 32: rows of 30 5.4 and 8.1e-8, of 8 4.7); up to 64 by 32 with two.
+// 0 and 1 4.36, 4.53, 4.65 and 4.72e-8 of their sum, by 4 lanes 4.36, 4.53, 4.90 and 5.23, in sums of 16 5.76, 5.73, 5.46 and 5.44.  And
+// 17 to 32 columns of single rows by 32 lanes, or 16 with two columns each, in place of 8 with four, in sums of 8 as those have (of 16
+// and 32: rows of 30 5.4 and 8.1e-8, of 8 4.7); up to 64 by 32 with two.  Rows of 90, 134 and 300: 4.5, 4.8 and 5.8, in one sum of
+// them without those of 32 5.85, 6.6 and 9.6, in sums of 16 5.2, 5.5 and 7.2.
 constexpr int kNarrow = 4;
 
 // EPI: with an elementwise tail.  Instances of their own, for the auto launch shapes only: the
@@ -462,15 +465,23 @@ spmm_kernel(SpmmArgs a)
         }
     }
 
-    // What the bands before have left, requested beside the first entries; sums of 32 or 64 vectors are added to it, as OUTER below has it.
-    float before[FORM == kBands ? REP : 1][VEC];
-    if constexpr (FORM == kBands) {
+    // Sums of 32 or 64 vectors are added up here, as OUTER below has it; to what the bands before have left, requested beside the first
+    // entries.
+    // (Pairs are local more often than not, and bound by their instructions: none of it there.  20,000 rows of 70 in cliques, K = 16 9.3 and
+    // 9.8 us.)  Items of 8 lanes of a dword, up to 8 columns of balanced handles, have sums of 4, as the 4 lanes of wide loads had (R-MAT 2^16,
+    // K = 4: 3.55e-8 of the sum, of 8 3.74).
+    constexpr bool FOURS = S && LPR == 8 && VEC == 1 && REP == 1;
+    constexpr bool APART = FORM == kBands || (FORM == kNarrow && V == 1) || (FOURS && !OUTER);
+    float apart[APART ? V : 1][APART ? REP : 1][VEC];
+    if constexpr (APART) {
 #pragma unroll
-        for (int r = 0; r < REP; ++r) {
+        for (int v = 0; v < V; ++v)
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) before[r][e] = 0.0f;
-            if (!(a.band & kBandFirst) && kv[r]) load_vec<VEC>(a.C + (long)panel * K + kc[r], before[r]);
-        }
+            for (int r = 0; r < REP; ++r) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) apart[v][r][e] = 0.0f;
+                if (FORM == kBands && !(a.band & kBandFirst) && kv[r]) load_vec<VEC>(a.C + (long)panel * K + kc[r], apart[v][r]);
+            }
     }
 
     // one lane's entries of the chunk that starts at `base` (zeros past the end of the range)
@@ -526,15 +537,17 @@ spmm_kernel(SpmmArgs a)
     };
     if constexpr (OUTER) outer([](float (&x)[VEC], float *at) { store_lds<VEC>(at, x); });
 
-    auto band_apart = [&] {
-        if constexpr (FORM == kBands) {
+    auto put_apart = [&] {
+        if constexpr (APART) {
 #pragma unroll
-            for (int r = 0; r < REP; ++r)
+            for (int v = 0; v < V; ++v)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    before[r][e] += acc[0][r][e];
-                    acc[0][r][e] = 0.0f;
-                }
+                for (int r = 0; r < REP; ++r)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) {
+                        apart[v][r][e] += acc[v][r][e];
+                        acc[v][r][e] = 0.0f;
+                    }
         }
     };
 
@@ -545,7 +558,7 @@ spmm_kernel(SpmmArgs a)
     load_entry(head, c_next, av_next);
     constexpr int PERIOD = CH < 32 ? 32 / CH : 1;
     const int band_period = FORM == kBands && (a.band & kBandSums64) ? 64 / CH : PERIOD;
-    int until = FORM == kBands ? band_period : PERIOD; // chunks until the next sum is put apart (the same in every lane group)
+    int until = band_period; // chunks until the next sum is put apart (the same in every lane group)
     for (int base = head; base < tail; base += CH) {
         long off[NH]; // DPP: in bytes, computed once by the lane that holds the entry
         unsigned near_off[NH]; // NEAR: the same
@@ -579,6 +592,7 @@ spmm_kernel(SpmmArgs a)
         // of a chunk of 32 and 64 lanes made it 2.23 and 2.79e-8 (items of 32 in chunks of 16: 1.82e-8).  These kernels wait on
         // memory: the additions cost nothing (250,000 rows, K = 128 262 us, K = 256 577, both as before).
         constexpr bool FOLD = (S && LPR >= 32) || FORM == kBands || FORM == kNarrow;
+        static_assert(!FOURS || U % 4 == 0);
         const bool fours = FORM == kNarrow && LPR == 16 && REP == 1 && a.mean_item < 22; // (wider groups: of 8, as 8 lanes' chunks)
         auto fold = [&] {
 #pragma unroll
@@ -655,8 +669,9 @@ spmm_kernel(SpmmArgs a)
                         for (int e = 0; e < VEC; ++e) part[v][r][e] = fmaf(aj, b[u][r][e], part[v][r][e]);
                 }
                 if (FOLD && (j + u) % 8 == 7) fold();
+                if (FOURS && u % 4 == 3) fold();
                 if (FORM == kNarrow && (j + u) % 8 == 3 && fours) fold();
-                if (FORM == kBands && CH == 64 && (j + u) % 32 == 31 && !(a.band & kBandSums64)) band_apart(); // half a chunk
+                if (FORM == kBands && CH == 64 && (j + u) % 32 == 31 && !(a.band & kBandSums64)) put_apart(); // half a chunk
             }
         };
         if constexpr (DPP) {
@@ -677,16 +692,17 @@ spmm_kernel(SpmmArgs a)
                     step(j, std::false_type{});
             }
         }
+        if constexpr (!(FOLD && U % 8 == 0) && !FOURS) // (every step ends with a fold)
 #pragma unroll
-        for (int v = 0; v < V; ++v)
+            for (int v = 0; v < V; ++v)
 #pragma unroll
-            for (int r = 0; r < REP; ++r)
+                for (int r = 0; r < REP; ++r)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[v][r][e] += part[v][r][e];
-        if constexpr (FORM == kBands) {
+                    for (int e = 0; e < VEC; ++e) acc[v][r][e] += part[v][r][e];
+        if constexpr (APART) {
             if (--until == 0) {
                 until = band_period;
-                band_apart();
+                put_apart();
             }
         }
         if constexpr (OUTER) {
@@ -698,6 +714,14 @@ spmm_kernel(SpmmArgs a)
         }
     }
     if constexpr (OUTER) outer(add_outer);
+    if constexpr (APART && FORM != kBands) {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int r = 0; r < REP; ++r)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[v][r][e] = apart[v][r][e] + acc[v][r][e];
+    }
 
     // write-back (Algorithm 2, last block): plain store for an item that is the only one
     // of its panel.  An item of a panel that was split (TRow names the panel) either
@@ -711,7 +735,7 @@ spmm_kernel(SpmmArgs a)
             if (!kv[r]) continue;
             float *const at = a.C + (long)panel * K + kc[r];
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) acc[0][r][e] = before[r][e] + acc[0][r][e];
+            for (int e = 0; e < VEC; ++e) acc[0][r][e] = apart[0][r][e] + acc[0][r][e];
             if (a.band & kBandLast) {
                 if constexpr (EPI) finish<VEC>(a.epi, (long)panel, a.K, kc[r], acc[0][r]);
                 store_vec<VEC>(at, acc[0][r]);
@@ -1655,9 +1679,9 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
     const bool near = near_enough(args) && !short_items;
     // Plain products in these shapes at any width: pcsr_select gives them to handles that had sums of 4 to 8 vectors in wide loads
     // (20,000 rows of 22, a handle for K = 8 at K = 64: rms 4.7e-8 of the sum, 5.6 in sums of 16, 4.7 now), and the additions show
-    // nowhere (K = 9 to 16, rows of 9 to 80: 0.99-1.02 of the time).  Tails come in auto shapes: of 9 to 16 columns they have sums of 16,
-    // and ask for their rows early.
-    const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 && (!epi || args.K <= 8 || args.K > 16) &&
+    // nowhere (K = 9 to 16, rows of 9 to 80: 0.99-1.02 of the time).  But pairs of 9 to 16 columns have sums of 16, as they had, and so have
+    // tails, which come in auto shapes and ask for their rows early.
+    const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 && ((!epi && V == 1) || args.K <= 8 || args.K > 16) &&
                         ((ls.k_lpr == 16 && ls.k_rep == 1) ||
                          (V == 1 && ls.k_lpr >= 16 && ls.k_lpr <= 32 && ls.k_rep <= 2 && ls.k_lpr * ls.k_rep >= 32));
     KernelFn fn;

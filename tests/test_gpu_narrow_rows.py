@@ -94,3 +94,45 @@ def test_other_widths_are_as_exact_as_wide_loads(V, shape, wide, lengths):
             h.close()
         # 24,000 to 780,000 numbers: the rms of them is known to 1 % and less, and one of sums of 16 is 15 % and more off
         assert len(rms) == 1 or rms[0] < 1.05 * rms[1], (K, rms)
+
+
+def _rms(rowptr, colidx, vals, n_cols, K, kws, seed):
+    """rms difference from 64 bits, of rows' sums of numbers between 0 and 1, by each of the handles"""
+    B = np.random.default_rng(seed).random((n_cols, K), dtype=np.float32)
+    b, out = torch.from_numpy(B).cuda(), []
+    ref, bound = oracle.spmm(rowptr, colidx, vals, B)
+    full = ref > 0
+    for kw in kws:
+        h = pc.pcsr_build(rowptr.size - 1, n_cols, rowptr, colidx, vals, pc.make_params(waves_per_wg=4, **kw))
+        C = torch.full((rowptr.size - 1, K), float("nan"), device="cuda")
+        pc.pcsr_spmm(h, b, C, K)
+        got = C.cpu().numpy()
+        ok, worst = oracle.within_tolerance(got, ref, bound)
+        assert ok, (K, kw, worst)
+        out.append(np.sqrt(np.mean(((got.astype(np.float64) - ref)[full] / ref[full]) ** 2)))
+        h.close()
+    return out
+
+
+# sums of 8 (or 4), in sums of 32, in that of the row: as many roundings as items of 32 in chunks of 16 have
+@pytest.mark.parametrize("K", [4, 8, 12, 16, 17, 24, 32, 48, 64, 100])
+@pytest.mark.parametrize("shape", [(16, 1, 1), (32, 1, 1), (16, 1, 2), (32, 1, 2)])
+def test_long_rows_are_as_exact_as_items_of_32(shape, K):
+    rng = np.random.default_rng(K)
+    n, n_cols = 3000, 5000
+    rowptr, colidx, vals = _rows(rng, np.where(np.arange(n) % 50 == 7, 0, rng.integers(150, 300, n)), n_cols)
+    own, items = _rms(rowptr, colidx, np.abs(vals), n_cols, K, [dict(zip(("lanes_per_row", "vec", "rep"), shape)),
+                                                                dict(lanes_per_row=16, vec=1, rep=1, S=1, SG=32)], K)
+    assert own < 1.1 * items, (own, items)
+
+
+@pytest.mark.parametrize("V", [1, 2])
+@pytest.mark.parametrize("lengths", [(7, 10), (14, 40)])
+def test_narrow_items_are_as_exact_as_wide_loads(V, lengths):
+    rng = np.random.default_rng(lengths[0])
+    n, n_cols = 20000, 30000
+    rowptr, colidx, vals = _rows(rng, rng.integers(*lengths, n), n_cols)
+    kw = dict(V=V, S=1, SG=32)
+    for K in (4, 8):
+        own, wide = _rms(rowptr, colidx, np.abs(vals), n_cols, K, [dict(kw, lanes_per_row=8, vec=1, rep=1), dict(kw, lanes_per_row=4, vec=4, rep=1)], K)
+        assert own < 1.03 * wide, (K, own, wide)
