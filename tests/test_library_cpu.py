@@ -624,3 +624,15 @@ def test_few_columns_of_rows_that_are_not_split_for_many():
     p, _ = _chosen_for(_uniform(60_000, 60), 64)             # split as before
     assert p.S == 1 and not p.flags >> 29
     auto.close()
+
+
+def test_few_columns_of_short_scattered_rows():
+    """16 lanes where B is beyond what L2 holds or rows are of 12 and more; between them the shapes that they had."""
+    shape = lambda n, deg, K: (lambda p: (p.lanes_per_row, p.vec, p.rep))(pc.pcsr_select(_uniform(n, deg), K))  # noqa: E731
+    for n, deg in ((300_000, 9), (300_000, 8.5), (400_000, 8.5), (300_000, 11)):
+        assert shape(n, deg, 2) == (4, 2, 1) and shape(n, deg, 3) == (4, 1, 1)
+        assert shape(n, deg, 6) == shape(n, deg, 8) == (16, 1, 1)
+        assert shape(n, deg, 4) == ((16, 1, 1) if deg >= 9 or n > 312_500 else (4, 4, 1))
+        assert shape(n, deg, 5) == ((16, 1, 1) if n > 325_000 else (8, 1, 1))
+    for n, deg in ((1_000_000, 9), (300_000, 12), (60_000, 9)):
+        assert shape(n, deg, 2) == shape(n, deg, 3) == shape(n, deg, 4) == shape(n, deg, 5) == (16, 1, 1)
