@@ -469,7 +469,7 @@ spmm_kernel(SpmmArgs a)
     // entries.
     // (Pairs are local more often than not, and bound by their instructions: none of it there.  20,000 rows of 70 in cliques, K = 16 9.3 and
     // 9.8 us.)  Items of 8 lanes of a dword, up to 8 columns of balanced handles, have sums of 4, as the 4 lanes of wide loads had (R-MAT 2^16,
-    // K = 4: 3.55e-8 of the sum, of 8 3.74).
+    // K = 4: 3.55e-8 of the sum, of 8 3.74); odd widths never had those, and keep sums of 8 (30,000 rows of 45, K = 7: 4.45, of 4 4.70).
     constexpr bool FOURS = S && LPR == 8 && VEC == 1 && REP == 1;
     constexpr bool APART = FORM == kBands || (FORM == kNarrow && V == 1) || (FOURS && !OUTER);
     float apart[APART ? V : 1][APART ? REP : 1][VEC];
@@ -592,7 +592,8 @@ spmm_kernel(SpmmArgs a)
         // of a chunk of 32 and 64 lanes made it 2.23 and 2.79e-8 (items of 32 in chunks of 16: 1.82e-8).  These kernels wait on
         // memory: the additions cost nothing (250,000 rows, K = 128 262 us, K = 256 577, both as before).
         constexpr bool FOLD = (S && LPR >= 32) || FORM == kBands || FORM == kNarrow;
-        static_assert(!FOURS || U % 4 == 0);
+        static_assert(!FOURS || U == 8);
+        const bool even = FOURS && a.K % 2 == 0;
         const bool fours = FORM == kNarrow && LPR == 16 && REP == 1 && a.mean_item < 22; // (wider groups: of 8, as 8 lanes' chunks)
         auto fold = [&] {
 #pragma unroll
@@ -669,7 +670,7 @@ spmm_kernel(SpmmArgs a)
                         for (int e = 0; e < VEC; ++e) part[v][r][e] = fmaf(aj, b[u][r][e], part[v][r][e]);
                 }
                 if (FOLD && (j + u) % 8 == 7) fold();
-                if (FOURS && u % 4 == 3) fold();
+                if (FOURS && (u % 8 == 7 || (u % 4 == 3 && even))) fold();
                 if (FORM == kNarrow && (j + u) % 8 == 3 && fours) fold();
                 if (FORM == kBands && CH == 64 && (j + u) % 32 == 31 && !(a.band & kBandSums64)) put_apart(); // half a chunk
             }

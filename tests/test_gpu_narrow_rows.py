@@ -136,3 +136,7 @@ def test_narrow_items_are_as_exact_as_wide_loads(V, lengths):
     for K in (4, 8):
         own, wide = _rms(rowptr, colidx, np.abs(vals), n_cols, K, [dict(kw, lanes_per_row=8, vec=1, rep=1), dict(kw, lanes_per_row=4, vec=4, rep=1)], K)
         assert own < 1.03 * wide, (K, own, wide)
+    eights = _rms(rowptr, colidx, np.abs(vals), n_cols, 8, [dict(kw, lanes_per_row=8, vec=4, rep=1)], 8)[0]
+    for K in (5, 7):                                         # odd widths had 8 lanes before, and sums of 8
+        own = _rms(rowptr, colidx, np.abs(vals), n_cols, K, [dict(kw, lanes_per_row=8, vec=1, rep=1)], K)[0]
+        assert own < 1.03 * eights, (K, own, eights)
