@@ -83,3 +83,17 @@ for lanes in (16, 32, 64):
     h.close()
 assert max(parts[16]) == 6 and max(parts[32] + parts[64]) == 90 // 20, parts
 """)
+
+
+def test_tiles_of_512_columns_are_walked_in_bands_where_much_is_saved(fake):  # noqa: F811
+    _run(fake, HANDLE.replace("m, deg, n_cols = 20000, 134, 300_000", "m, deg, n_cols = 100_000, 90, 200_000") + """
+h = handle(flags=pc.PCSR_FLAG_GPU_BUILD | pc.PCSR_FLAG_COLUMN_BANDS)
+for K, several in ((130, True), (256, True), (260, False), (300, False), (340, False)):
+    assert (launches(h, K) > 1) == several, K
+h.close()
+""")
+    _run(fake, HANDLE.replace("n_cols = 20000, 134, 300_000", "n_cols = 20000, 134, 100_000") + """
+h = handle(flags=pc.PCSR_FLAG_GPU_BUILD | pc.PCSR_FLAG_COLUMN_BANDS)
+assert launches(h, 260) > 1 and launches(h, 300) > 1
+h.close()
+""")
