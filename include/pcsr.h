@@ -120,9 +120,10 @@ enum {
  *                    0 = auto.  Values above 1 need S = 0, items_per_group <
  *                    lanes_per_row, no work item longer than 1024 vectors and
  *                    V*vec*rep*items_per_group <= 32.
- *   flags   PCSR_FLAG_* bits.  Bits 16-27 are pcsr_select's: a launch shape with loads wider
- *           than vec (K need not be a multiple of them; C is the same) for exactly the
- *           lanes_per_row, vec and rep it returned with them; ignored with any other.
+ *   flags   PCSR_FLAG_* bits.  Bits 16-27, 29 and 30 are pcsr_select's: launch shapes in place of its own
+ *           for some widths, mostly with loads wider than vec (K need not be a multiple of them), for exactly
+ *           the lanes_per_row, vec and rep it returned with them; ignored with any other.  Bit 15 is
+ *           pcsr_operator_build's.
  */
 typedef struct {
     int32_t V;

@@ -39,6 +39,12 @@ constexpr int32_t kAutoNarrow = 1 << 30;
 constexpr int32_t kAutoNarrowMost = 32;
 constexpr int32_t kWideBits = kWideShape | kWidePair | kWideTwice | kWideFor | kWideBeyond | kAutoNarrow;
 
+// Set by pcsr_operator_build, whose handles run auto shapes, where it picked the parameters: the columns are scattered.
+constexpr int32_t kScattered = 1 << 15;
+
+// No more nonzeros near the diagonal than four times what uniform columns would put there.
+bool scattered_columns(const double *f) { return f[16] < 4.0 * 1025.0 / (f[0] > 1.0 ? f[0] : 1.0); }
+
 int32_t stands_for(int lanes, int vec, int rep)
 {
     auto bits = [](int x) { return x > 0 ? 31 - __builtin_clz((unsigned)x) : 0; };
@@ -306,8 +312,15 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     // scattered rows of 60, K = 24 209 us and 126; 250,000 of 48 in shuffled communities, K = 32 236 and 198; 100,000 of 85 in cliques 64 and
     // 57; of less than 32 1.00).
     // Up to 64 columns likewise, two to a lane of a half wavefront, in place of 16 lanes of 16 bytes: 0.90-0.97 (100,000 rows of 85 in
-    // cliques, K = 64 110 us and 99), but not in bands (100,000 of 48, K = 48 107 us and 137).
-    const bool dwords = !h_vec && !h_lpr && !h_rep && K > 16 && (K <= 32 || (K <= 64 && K % 4 == 0 && !h->d_bands)) &&
+    // cliques, K = 64 110 us and 99), but not in bands (100,000 of 48, K = 48 107 us and 137), nor long rows of scattered columns where an
+    // XCD's L2 holds some of B and the memory-side cache the rest: operators of 16,000 to 80,000 rows of 60 and more, K = 52 to 64 1.01-1.18
+    // (30,000 of 134 64 us and 73, of 300 125 and 148; 0.91-1.00 below, 0.97-1.00 above; with a tail, whose rows that form asks for late,
+    // 1.01-1.19 from 2.5 MB on), K = 36 to 48 0.96-1.06, of 134 1.02-1.06 from 7 MB on.  (Rows of 36 0.95-1.06, and more exact.)
+    const double b_bytes = 4.0 * (double)h->host.n_cols * K;
+    const int64_t panels = std::max<int64_t>(h->host.P, 1);
+    const bool between = (h->flags & kScattered) && b_bytes < 18e6 && h->host.nnz_v >= 56 * panels &&
+                         (K > 48 ? b_bytes > (epilogue ? 2.5e6 : 3.8e6) : b_bytes > 7e6 && h->host.nnz_v >= 100 * panels);
+    const bool dwords = !h_vec && !h_lpr && !h_rep && K > 16 && (K <= 32 || (K <= 64 && K % 4 == 0 && !h->d_bands && !between)) &&
                         h->host.win_cols == 0 && h->ipg <= 1 && h->host.V == 1 && !h->host.S &&
                         h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
     // Rows of over 64 columns of a handle with bands go in slices, as pcsr_select has them: of 64 columns in 16 lanes where there are
@@ -737,6 +750,7 @@ static int operator_params(const pcsr_params_t *p, bool pick, const double *f, i
     }
     const int rc = pcsr_select(f, K, prm);
     if (rc == PCSR_OK) prm->lanes_per_row = prm->vec = prm->rep = 0;
+    if (rc == PCSR_OK && scattered_columns(f)) prm->flags |= kScattered;
     return rc;
 }
 
@@ -1322,7 +1336,7 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     int vec = K % 4 == 0 ? 4 : (K % 2 == 0 ? 2 : 1);
     if (K > 8 && K <= 16 && d_hat >= 8.0) vec = 1;
     const double n = f[0];
-    const bool scattered = f[16] < 4.0 * 1025.0 / (n > 1.0 ? n : 1.0); // (see below)
+    const bool scattered = scattered_columns(f); // (see below)
     // Up to 8 the same (narrow_lanes); of scattered rows from 8 on, which wait on memory (1,000,000 rows of 9, K = 8: 160 -> 150 us).
     // Odd widths had one dword a lane before: local rows of 15 0.95-1.05, one column of 9 to 21 a row 1.16-1.30.
     // Up to five columns of under 12 that L2 holds but L1 does not: their wide loads are faster (300,000 rows of 8.5, K = 2 17.5 us and

@@ -140,3 +140,26 @@ def test_narrow_items_are_as_exact_as_wide_loads(V, lengths):
     for K in (5, 7):                                         # odd widths had 8 lanes before, and sums of 8
         own = _rms(rowptr, colidx, np.abs(vals), n_cols, K, [dict(kw, lanes_per_row=8, vec=1, rep=1)], K)[0]
         assert own < 1.03 * eights, (K, own, eights)
+
+
+def test_operators_run_scattered_rows_of_a_middling_b_in_wide_loads():
+    """33 to 64 columns of long single rows: a dword a lane, but not where the columns are scattered and L2 holds some of B."""
+    from paper_2605_15695_amd.gnn import PcsrOperator
+
+    rng = np.random.default_rng(3)
+    n = 30_000
+    kernel = lambda op, K: (lambda q: (q["lanes_per_row"], q["vec"], q["rep"]))(pc.pcsr_query_kernel(op.fwd, K))  # noqa: E731
+    rowptr, colidx, vals = _rows(rng, rng.integers(60, 80, n), n)
+    op = PcsrOperator(n, n, rowptr, colidx, vals, symmetric=True, K_hint=16)
+    assert kernel(op, 64) == kernel(op, 60) == (16, 4, 1) and kernel(op, 40) == (32, 1, 2) and kernel(op, 24) == (16, 1, 2)
+    for K in (40, 64):
+        B = rng.standard_normal((n, K)).astype(np.float32)
+        ok, worst = oracle.within_tolerance(op(torch.from_numpy(B).cuda()).cpu().numpy(), *oracle.spmm(rowptr, colidx, vals, B))
+        assert ok, (K, worst)
+        T, expect = _tail(op.fwd, torch.from_numpy(B).cuda(), K, rng)
+        ok, worst = oracle.within_tolerance(T.cpu().numpy(), *expect(*oracle.spmm(rowptr, colidx, vals, B)))
+        assert ok, (K, "tail", worst)
+    near = np.stack([np.sort(rng.choice(600, 50, replace=False)) for _ in range(n)]) + np.clip(np.arange(n) - 300, 0, n - 600)[:, None]
+    op = PcsrOperator(n, n, np.arange(0, 50 * n + 1, 50, dtype=np.int32), near.ravel().astype(np.int32),
+                      rng.standard_normal(50 * n).astype(np.float32), symmetric=True, K_hint=64)
+    assert kernel(op, 64) == kernel(op, 40) == (32, 1, 2)    # local columns
