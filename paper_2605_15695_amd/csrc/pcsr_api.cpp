@@ -250,10 +250,10 @@ void window_tail(pcsr_handle_t h, pcsr::LaunchShape *ls)
 // How many bands of columns a product of scattered rows is best walked in (a divisor of kColumnBands), and the us that they save.  A
 // band of B that an XCD's L2 holds is gathered from there; each band of several costs a launch, a look at every row and a pass over
 // C.  The rates are those that fit 1,200 measured times best (uniform columns, 14 to 300 a row, 40,000 to 1,000,000 rows, 6 to 256
-// columns, 1 to 12 bands): the number picked is 0.9 % off the best of them on average and 14 % at most, and never over 1.3 % off one
-// band.  Us in one band and in those picked: rows of 134, 300,000 of them, K = 16 667 and 366 (6 bands), K = 32 706 and 527 (6), K = 64 1459 and
-// 1197 (6); of 60, 150,000, K = 16 118 and 76 (3), K = 48 291 and 211 (6); of 60, 400,000, K = 10 462 and 235 (4), K = 64 908 in one; of 30,
-// 400,000, K = 9 202 and 145 (3), K = 16 193 in one; of 300, 100,000, K = 32 385 and 224 (4).
+// columns, 1 to 12 bands): the number picked is 0.9 % off the best of them on average and 14 % at most, and never over 1.3 % off
+// one band.  Us in one band and in those picked: rows of 134, 300,000 of them, K = 16 667 and 366 (6 bands), K = 32 706 and 527 (6),
+// K = 64 1459 and 1197 (6); of 60, 150,000, K = 16 118 and 76 (3), K = 48 291 and 211 (6); of 60, 400,000, K = 10 462 and 235 (4),
+// K = 64 908 in one; of 30, 400,000, K = 9 202 and 145 (3), K = 16 193 in one; of 300, 100,000, K = 32 385 and 224 (4).
 int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, int32_t tile, double *saved)
 {
     const double slices = (K + tile - 1) / tile, row = 4.0 * K / slices;
@@ -271,8 +271,8 @@ int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, i
     for (const int m : {2, 3, 4, 6, 12})
         if (nnz >= std::max(m < 12 ? 0.0 : 256.0, least * m) * n_rows && us(m) < (best > 1 ? 0.98 : 1.0) * us(best)) best = m;
     *saved = us(1) - us(best);
-    // (Tiles of 512 columns, which those times do not have, save 0.05 to 0.15 less than that: K = 260 to 500, 100,000 rows of 134 0.88-0.99 of
-    // the time in 6 where 0.81-0.87 was expected, 200,000 of 100 1.02-1.06 for 0.95, 300,000 of 90 1.05 for 0.96.)
+    // (Tiles of 512 columns, which those times do not have, save 0.05 to 0.15 less than that: K = 260 to 500, 100,000 rows of 134
+    // 0.88-0.99 of the time in 6 where 0.81-0.87 was expected, 200,000 of 100 1.02-1.06 for 0.95, 300,000 of 90 1.05 for 0.96.)
     return *saved > (tile > 256 ? 0.1 : 0.03) * us(1) ? best : 1;
 }
 
@@ -307,15 +307,15 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     // and K of up to 8, rows of 32 and more (single rows of 18 and 27 that share their neighbours' columns 0.86-1.58 of 4 lanes' time)
     const bool narrow = !h_vec && !h_lpr && !h_rep && K <= 8 && h->host.win_cols == 0 && h->ipg <= 1 &&
                         h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
-    // and K of 17 to 32, single rows of 32 and more, for which pcsr_select has these shapes, too: half as many rows a wavefront as with 8
-    // lanes of 16 bytes take 0.62-0.92 of the time in half wavefronts, scattered and in bands, 0.84-0.92 otherwise, tails 0.63-0.94 (150,000
-    // scattered rows of 60, K = 24 209 us and 126; 250,000 of 48 in shuffled communities, K = 32 236 and 198; 100,000 of 85 in cliques 64 and
-    // 57; of less than 32 1.00).
-    // Up to 64 columns likewise, two to a lane of a half wavefront, in place of 16 lanes of 16 bytes: 0.90-0.97 (100,000 rows of 85 in
-    // cliques, K = 64 110 us and 99), but not in bands (100,000 of 48, K = 48 107 us and 137), nor long rows of scattered columns where an
-    // XCD's L2 holds some of B and the memory-side cache the rest: operators of 16,000 to 80,000 rows of 60 and more, K = 52 to 64 1.01-1.18
-    // (30,000 of 134 64 us and 73, of 300 125 and 148; 0.91-1.00 below, 0.97-1.00 above; with a tail, whose rows that form asks for late,
-    // 1.01-1.19 from 2.5 MB on), K = 36 to 48 0.96-1.06, of 134 1.02-1.06 from 7 MB on.  (Rows of 36 0.95-1.06, and more exact.)
+    // and K of 17 to 32, single rows of 32 and more, for which pcsr_select has these shapes, too: half as many rows a wavefront as
+    // with 8 lanes of 16 bytes take 0.62-0.92 of the time in half wavefronts, scattered and in bands, 0.84-0.92 otherwise, tails
+    // 0.63-0.94 (150,000 scattered rows of 60, K = 24 209 us and 126; 250,000 of 48 in shuffled communities, K = 32 236 and 198;
+    // 100,000 of 85 in cliques 64 and 57; of less than 32 1.00).  Up to 64 columns likewise, two to a lane of a half wavefront, in
+    // place of 16 lanes of 16 bytes: 0.90-0.97 (100,000 rows of 85 in cliques, K = 64 110 us and 99), but not in bands (100,000 of
+    // 48, K = 48 107 us and 137), nor long rows of scattered columns where an XCD's L2 holds some of B and the memory-side cache
+    // the rest: operators of 16,000 to 80,000 rows of 60 and more, K = 52 to 64 1.01-1.18 (30,000 of 134 64 us and 73, of 300 125
+    // and 148; 0.91-1.00 below, 0.97-1.00 above; with a tail, whose rows that form asks for late, 1.01-1.19 from 2.5 MB on), K = 36
+    // to 48 0.96-1.06, of 134 1.02-1.06 from 7 MB on.  (Rows of 36 0.95-1.06, and more exact.)
     const double b_bytes = 4.0 * (double)h->host.n_cols * K;
     const int64_t panels = std::max<int64_t>(h->host.P, 1);
     const bool between = (h->flags & kScattered) && b_bytes < 18e6 && h->host.nnz_v >= 56 * panels &&
@@ -323,11 +323,11 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     const bool dwords = !h_vec && !h_lpr && !h_rep && K > 16 && (K <= 32 || (K <= 64 && K % 4 == 0 && !h->d_bands && !between)) &&
                         h->host.win_cols == 0 && h->ipg <= 1 && h->host.V == 1 && !h->host.S &&
                         h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
-    // Rows of over 64 columns of a handle with bands go in slices, as pcsr_select has them: of 64 columns in 16 lanes where there are
-    // several bands, else half a wavefront to 64 columns.  Us of such slices, of a tile of the whole row and of items of 32 in column order: rows
-    // of 90, 100,000 of them, K = 128 346, 469 and 446, K = 256 675, 1182 and 889, K = 512 1411, 2469 and 1779; of 134, 300,000, K = 256 4755,
-    // 5756 and 5096; of 44, 500,000 (one band), K = 256 2983, 3077 and 3637.  Rows that are no multiple of 128 bytes long have lines
-    // that two slices would read: K = 200 993, 951 and 1018, K = 300 1739, 1531 and 1605.
+    // Rows of over 64 columns of a handle with bands go in slices, as pcsr_select has them: of 64 columns in 16 lanes where there
+    // are several bands, else half a wavefront to 64 columns.  Us of such slices, of a tile of the whole row and of items of 32 in
+    // column order: rows of 90, 100,000 of them, K = 128 346, 469 and 446, K = 256 675, 1182 and 889, K = 512 1411, 2469 and 1779;
+    // of 134, 300,000, K = 256 4755, 5756 and 5096; of 44, 500,000 (one band), K = 256 2983, 3077 and 3637.  Rows that are no
+    // multiple of 128 bytes long have lines that two slices would read: K = 200 993, 951 and 1018, K = 300 1739, 1531 and 1605.
     double saved;
     const bool sliced = !h_vec && !h_lpr && !h_rep && h->d_bands && h->ipg <= 1 && K > 64 && K % 32 == 0;
     const bool in_bands = sliced && band_count((double)h->host.n_rows, (double)h->host.n_cols, (double)h->host.nnz, K, 16, 64, &saved) > 1;
@@ -1337,11 +1337,11 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     if (K > 8 && K <= 16 && d_hat >= 8.0) vec = 1;
     const double n = f[0];
     const bool scattered = scattered_columns(f); // (see below)
-    // Up to 8 the same (narrow_lanes); of scattered rows from 8 on, which wait on memory (1,000,000 rows of 9, K = 8: 160 -> 150 us).
-    // Odd widths had one dword a lane before: local rows of 15 0.95-1.05, one column of 9 to 21 a row 1.16-1.30.
-    // Up to five columns of under 12 that L2 holds but L1 does not: their wide loads are faster (300,000 rows of 8.5, K = 2 17.5 us and
-    // 20.9, K = 3 20.7 and 22.6, K = 5 25.8 and 26.7; 1.02-1.20 from 1.7 MB, 1.1 of three columns, up to 5, 6.5 of five, 0.94-1.01 from there
-    // on; rows of 10 0.97-1.09, of 12 0.84-1.02; four columns 1.03-1.04, but 0.99 with 9 a row).
+    // Up to 8 the same (narrow_lanes); of scattered rows from 8 on, which wait on memory (1,000,000 rows of 9, K = 8: 160 -> 150
+    // us).  Odd widths had one dword a lane before: local rows of 15 0.95-1.05, one column of 9 to 21 a row 1.16-1.30.  Up to five
+    // columns of under 12 that L2 holds but L1 does not: their wide loads are faster (300,000 rows of 8.5, K = 2 17.5 us and 20.9,
+    // K = 3 20.7 and 22.6, K = 5 25.8 and 26.7; 1.02-1.20 from 1.7 MB, 1.1 of three columns, up to 5, 6.5 of five, 0.94-1.01 from
+    // there on; rows of 10 0.97-1.09, of 12 0.84-1.02; four columns 1.03-1.04, but 0.99 with 9 a row).
     const double b_few = n * (double)K * 4.0;
     const bool few = K >= 2 && K <= 5 && b_few > (K == 3 ? 1.1e6 : 1.7e6) && b_few < (K == 5 ? 6.5e6 : 5e6);
     const double least_few = !few ? 8.0 : K == 4 ? 8.8 : 11.5;
@@ -1358,16 +1358,14 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // paired, V = 2, than from LDS (cliques of 48, K = 128: 0.98 against 0.82 of the best).
     const bool windowed = !skewed && f[16] >= 0.6 && d_hat >= 40.0 && vec == 4 && pr2 >= 0.3 && K >= 64 &&
                           n * (double)((K + 63) / 64) >= 200000.0;
-    // Uniformly long rows with scattered columns (mean length 40 or more, no more nonzeros
-    // near the diagonal than four times what uniform columns would put there).  From
-    // K = 64 the same column-ordered schedule, with items of 32, turns the split into a
-    // column partition of A, each XCD gathering from its own range of B rows (uniform
-    // random columns, 96 per row, K = 128: 1.5x; 48 per row, K = 256: 1.13x; at 32 per
-    // row the second items are too short and it loses 15 %).  Narrower rows of B
-    // are walked in bands of columns, or paired (below).  Rows with local columns lose up to half
-    // their speed under the column order (it gives up the reuse between neighbouring rows).
-    // Such rows walked in bands of columns: where one product saves what the handle's table of them costs its build (300,000 rows of
-    // 134: 183 -> 263 us, 60,000 of 140: 78 -> 99, 1,000,000 of 44: 187 -> 336), or where the other choice is the far dearer build of pairs.
+    // Uniformly long rows with scattered columns (mean length 40 or more, no more nonzeros near the diagonal than four times what
+    // uniform columns would put there).  From K = 64 the same column-ordered schedule, with items of 32, turns the split into a
+    // column partition of A, each XCD gathering from its own range of B rows (uniform random columns, 96 per row, K = 128: 1.5x; 48
+    // per row, K = 256: 1.13x; at 32 per row the second items are too short and it loses 15 %).  Narrower rows of B are walked in
+    // bands of columns, or paired (below).  Rows with local columns lose up to half their speed under the column order (it gives up
+    // the reuse between neighbouring rows).  Such rows walked in bands of columns: where one product saves what the handle's table
+    // of them costs its build (300,000 rows of 134: 183 -> 263 us, 60,000 of 140: 78 -> 99, 1,000,000 of 44: 187 -> 336), or where
+    // the other choice is the far dearer build of pairs.
     const int band_lanes = K <= 16 || (K > 32 && K <= 64) || (K > 64 && K % 32 == 0) ? 16 : K <= 128 ? 32 : 64;
     const int band_tile = K <= 32 ? band_lanes : 4 * band_lanes;
     double saved = 0.0;
@@ -1377,21 +1375,21 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     const bool banded = !skewed && !windowed && scattered && d_hat >= 12.0 && K > 2 &&
                         band_count(n, n, f[2], K, band_lanes, band_tile, &saved) > 1 &&
                         (paired_else || saved > 12.0 + 1e-6 * f[2] + 1e-4 * n);
-    // K of 17..32 with scattered columns: one dword per lane again, a row per half wavefront
-    // (uniform random columns, 16 to 64 per row, 150,000 rows or more: 7-24 % faster than
-    // the best 16-byte shape; slower when the columns are local.  In bands: 300,000 rows of 134, K = 32: 527 us, 8 lanes
-    // of 16 bytes 580.  A B of less than 16 MB: over 8 lanes of 16 bytes and 16 of two dwords 0.73-0.98, rows of 14 to 140, 4,000 to 200,000
-    // of them, but 1.03 with 13 a row and K = 17).  Rows that are paired otherwise stay so.
+    // K of 17..32 with scattered columns: one dword per lane again, a row per half wavefront (uniform random columns, 16 to 64 per
+    // row, 150,000 rows or more: 7-24 % faster than the best 16-byte shape; slower when the columns are local.  In bands: 300,000
+    // rows of 134, K = 32: 527 us, 8 lanes of 16 bytes 580.  A B of less than 16 MB: over 8 lanes of 16 bytes and 16 of two dwords
+    // 0.73-0.98, rows of 14 to 140, 4,000 to 200,000 of them, but 1.03 with 13 a row and K = 17).  Rows that are paired otherwise
+    // stay so.
     const bool wide_scatter = !skewed && scattered && d_hat >= 12.0 && K > 16 && K <= 32 &&
                               (banded || n * (double)K * 4.0 > 16.0 * 1048576.0 ||
                                ((d_hat < 40.0 || !fills_paired) && (d_hat >= 16.0 || K % 4 == 0)));
     if (wide_scatter) vec = 1;
     const bool long_uniform = !skewed && !windowed && !wide_scatter && d_hat >= 40.0 && scattered;
-    // But not where a slice of B is over 20 MB, 2.5 times what the L2s hold together: the order then saves less than
-    // the parts' sums cost, and unsplit rows, in bands or not, take 0.77-0.95 of the time (rows of 44 to 300, 100,000 to 1,000,000 of them, K = 64
-    // to 256; rows of 90, 100,000 of them, K = 128: 485 -> 350 us, of 44, 1,000,000: 3937 -> 3087; slices of 15 MB 0.92-1.10, of 10 MB
-    // 0.95-1.15).  Rows over kClusterItem stay split, as communities among them would have to be, and so do widths over 256 that
-    // are no multiple of 32, whose tile no band kernel has.
+    // But not where a slice of B is over 20 MB, 2.5 times what the L2s hold together: the order then saves less than the parts'
+    // sums cost, and unsplit rows, in bands or not, take 0.77-0.95 of the time (rows of 44 to 300, 100,000 to 1,000,000 of them, K
+    // = 64 to 256; rows of 90, 100,000 of them, K = 128: 485 -> 350 us, of 44, 1,000,000: 3937 -> 3087; slices of 15 MB 0.92-1.10,
+    // of 10 MB 0.95-1.15).  Rows over kClusterItem stay split, as communities among them would have to be, and so do widths over 256
+    // that are no multiple of 32, whose tile no band kernel has.
     const bool split_pays =
         n * 4.0 * std::min(K, band_tile) <= 20e6 || d_max > pcsr::kClusterItem || (K > 256 && K % 32 != 0);
     const bool long_uniform_wide = long_uniform && K >= 64 && split_pays;
@@ -1476,8 +1474,9 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
         rep = 1;
         quads = (in_l2 || banded) && K % 32 == 0;
     }
-    // Single long rows of 33 to 64 columns: a dword a lane and two columns of it, as resolve_launch has it for auto shapes; and scattered ones
-    // of 12 and more, K = 64, that L2 holds: 0.77-0.95 of 32 lanes of two floats (20,000 rows of 34 15.7 us and 12.4; at 13 MB 0.98-1.00).
+    // Single long rows of 33 to 64 columns: a dword a lane and two columns of it, as resolve_launch has it for auto shapes; and
+    // scattered ones of 12 and more, K = 64, that L2 holds: 0.77-0.95 of 32 lanes of two floats (20,000 rows of 34 15.7 us and
+    // 12.4; at 13 MB 0.98-1.00).
     if (!p.S && p.V == 1 && !windowed && !banded && K > 32 && K <= 64 && K % 4 == 0 &&
         (scattered ? K == 64 && d_hat >= 12.0 && b_bytes < 10e6 : d_hat >= 32.0)) {
         lpr = 32;
@@ -1529,13 +1528,15 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
         wide = 4;
         beyond = true;
     } else if (wide_scatter && !banded && d_hat < 32.0 && b_bytes <= 16.0 * 1048576.0) {
-        // and a dword a lane of rows in L2 for up to 32 (20,000 rows of 22, a handle for K = 24: K = 192 29.0 us and 27.1, K = 256 36.3 and 33.4)
+        // and a dword a lane of rows in L2 for up to 32 (20,000 rows of 22, a handle for K = 24: K = 192 29.0 us and 27.1, K = 256
+        // 36.3 and 33.4)
         wide = K % 4 == 0 ? 8 : 16;
         pair = K % 4 != 0;
         beyond = true;
     }
-    // Rows that are not split for K = 64 and more: few columns of them are best left to the library (150,000 rows of 60, a handle for K = 64:
-    // K = 4, 8, 16 and 24 146, 144, 170 and 187 us in its shape, 91, 91, 99 and 168 when its rows were split, 50, 60, 77 and 127 in auto shapes).
+    // Rows that are not split for K = 64 and more: few columns of them are best left to the library (150,000 rows of 60, a handle
+    // for K = 64: K = 4, 8, 16 and 24 146, 144, 170 and 187 us in its shape, 91, 91, 99 and 168 when its rows were split, 50, 60,
+    // 77 and 127 in auto shapes).
     const bool auto_narrow = long_uniform && K >= 64 && !p.S && p.V == 1;
     if (auto_narrow) p.flags |= kAutoNarrow | stands_for(lpr, vec, rep);
     if (wide) {

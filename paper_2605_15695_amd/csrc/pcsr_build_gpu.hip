@@ -742,9 +742,9 @@ __global__ void __launch_bounds__(kThreads) features_final_kernel(int64_t nnz, c
         *out = {r.n_hat, nnz - r.shared, r.nonempty2, d.M1, d.M2, r.near, r.bw_sum, r.bw_max, d.ss, d.ss_hat, r.d_max, 0};
 }
 
-// Where the rows' columns pass into each band but the first: how many lie below the start of each of kColumnBands equal parts of the
-// columns.  Counted, 16 lanes a row, as that reads the columns once and in order (300,000 rows of 134: 80 us, most of it the table; a search for each
-// start takes 290); and the ends ascend and cover the row whatever order its columns have.
+// Where the rows' columns pass into each band but the first: how many lie below the start of each of kColumnBands equal parts of
+// the columns.  Counted, 16 lanes a row, as that reads the columns once and in order (300,000 rows of 134: 80 us, most of it the
+// table; a search for each start takes 290); and the ends ascend and cover the row whatever order its columns have.
 __global__ void __launch_bounds__(kThreads) bands_kernel(int64_t n_rows, int64_t n_cols, const int32_t *rowptr, const int32_t *colidx,
                                                          int32_t *bands)
 {

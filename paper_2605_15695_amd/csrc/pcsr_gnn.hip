@@ -15,18 +15,20 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-// fp32 products on the bf16 matrix instructions, which do 16 times the work.  A float is the sum of three bf16 numbers, to the last
-// bit (8 of its 24 bits each), and a product of two floats that of the six products of their pieces that reach 2^-24 of it.
-// v_mfma_f32_16x16x32_bf16: lane l holds A[i = l%16][k = 8*(l/16) and on] and B likewise, eight numbers each; results as above.
-// The five smaller products are added up apart from the largest.  Against 64 bits, 2-norm of normal numbers: 0.50 / 0.65e-7 over 64 /
-// 128 of them, where the fp32 instructions are off by 1.44 / 2.03e-7.  One accumulator for all six is off by 0.93 / 1.53, but to one side: these
-// instructions cut off what does not reach the last bit of a sum, and sums of 200,000 such results were off 5 to 10 times as much as before.
-// They do 2420 TFLOP/s here for 150: 2.7 times the rate with six of them.
-// Rows and weights are taken 2^16 times as large, and the sums 2^-32 times: bf16 reaches as low as 2^-133, floats to 2^-149, so that the last
-// piece of the smallest number is whole, and no bit of a sum changes (rows of 2^-115 were off by 1.1e-6, of 2^-124 by 5.6e-4 without).
-// Rows with numbers of 2^50 and more, infinities among them, and all rows where a weight or a bias reaches 2^16 and 2^50, are left to the
-// fp32 instructions, in a loop of their own that takes 6 times as long: an infinity has no pieces, and below that neither the
-// products of two layers nor their pieces' overflow: 64 (64 * 2^50 * 2^16) * 2^16 * 2^32 = 2^126.
+// fp32 products on the bf16 matrix instructions, which do 16 times the work (Henry, Tang, Heinecke: Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations, ARITH 2019, have the method).  A float is the sum of three
+// bf16 numbers, to the last bit (8 of its 24 bits each), and a product of two floats that of the six products of their pieces that
+// reach 2^-24 of it.  v_mfma_f32_16x16x32_bf16: lane l holds A[i = l%16][k = 8*(l/16) and on] and B likewise, eight numbers each;
+// results as above.  The five smaller products are added up apart from the largest.  Against 64 bits, 2-norm of normal numbers: 0.50
+// / 0.65e-7 over 64 / 128 of them, where the fp32 instructions are off by 1.44 / 2.03e-7.  One accumulator for all six is off by
+// 0.93 / 1.53, but to one side: these instructions cut off what does not reach the last bit of a sum, and sums of 200,000 such
+// results were off 5 to 10 times as much as before.  They do 2420 TFLOP/s here for 150: 2.7 times the rate with six of them.  Rows
+// and weights are taken 2^16 times as large, and the sums 2^-32 times: bf16 reaches as low as 2^-133, floats to 2^-149, so that the
+// last piece of the smallest number is whole, and no bit of a sum changes (rows of 2^-115 were off by 1.1e-6, of 2^-124 by 5.6e-4
+// without).  It costs 0 to 2.7 % (2,000,000 rows: 128 -> 128 437 and 448 us, 96 -> 96 332 and 339, two layers of 64 293 and 301,
+// backward the same).  Rows with numbers of 2^50 and more, infinities among them, and all rows where a weight or a bias reaches 2^16
+// and 2^50, are left to the fp32 instructions, in a loop of their own that takes 6 times as long: an infinity has no pieces, and
+// below that neither the products of two layers nor their pieces' overflow: 64 (64 * 2^50 * 2^16) * 2^16 * 2^32 = 2^126.
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 struct Pieces {
     u4 p[3]; // of eight floats
@@ -119,12 +121,13 @@ struct LinearArgs {
 constexpr int blocks_per_cu(int kt, int nt) { return kt + nt <= 8 ? 3 : 2; } // registers and LDS allow no more
 // piece_kernel: eight wavefronts to one copy of the weights where two copies do not fit
 constexpr int piece_waves(int kt, int nt) { return kt + nt > 12 ? 8 : 4; }
-// Without conditions in its loop a wavefront keeps more loads and stores on their way, and fewer of them do: at 2,000,000 / 300,000 /
-// 65,536 rows one workgroup to a compute unit in place of two or three takes 0.88 / 0.80 / 0.73 of the time of 64 -> 64 before (two: 0.95, 0.86,
-// 0.89), 48 -> 48 0.92 / 0.91 / 0.82, 128 -> 16 0.96 / 0.94 / 0.88, with a mask and column sums 0.99 / 0.97 / 0.95.  Narrower ones want two (16 -> 64
-// 1.17 with one, 0.97 with two, 1.05 with three).  So do 64 columns of 96 and of 128 (one takes 1.04-1.20 of two at 300,000 rows, 0.96-1.07 at
-// 2,000,000; with a mask and no sums 128 -> 64 had lost: 63 us for 56, now 53), 48 of 128 with a mask or sums (1.07-1.08; 0.91-0.96), and 16 -> 96
-// without, written by more than it is read (158 and 154 us in a training step of 2,000,000 rows; with a mask 305 and 323).
+// Without conditions in its loop a wavefront keeps more loads and stores on their way, and fewer of them do: at 2,000,000 / 300,000
+// / 65,536 rows one workgroup to a compute unit in place of two or three takes 0.88 / 0.80 / 0.73 of the time of 64 -> 64 before
+// (two: 0.95, 0.86, 0.89), 48 -> 48 0.92 / 0.91 / 0.82, 128 -> 16 0.96 / 0.94 / 0.88, with a mask and column sums 0.99 / 0.97 /
+// 0.95.  Narrower ones want two (16 -> 64 1.17 with one, 0.97 with two, 1.05 with three).  So do 64 columns of 96 and of 128 (one
+// takes 1.04-1.20 of two at 300,000 rows, 0.96-1.07 at 2,000,000; with a mask and no sums 128 -> 64 had lost: 63 us for 56, now
+// 53), 48 of 128 with a mask or sums (1.07-1.08; 0.91-0.96), and 16 -> 96 without, written by more than it is read (158 and 154 us
+// in a training step of 2,000,000 rows; with a mask 305 and 323).
 constexpr int piece_blocks_per_cu(int kt, int nt, bool red, bool mask)
 {
     return kt + nt <= 5 || (kt >= 6 && nt == 4) || (kt == 8 && nt == 3 && (red || mask)) || (kt == 1 && nt == 6 && !red && !mask) ? 2 : 1;
@@ -164,16 +167,18 @@ __device__ __forceinline__ void multiply(const f4 *wfrag, int lane, const f4 (&x
     }
 }
 
-// Where pieces are taken: where the matrix rate bounds a pass as much as memory does.  Elsewhere the work of splitting shows (us at 2,000,000
-// rows, fp32 products / pieces): 32 -> 32 92 / 113, 48 -> 64 157 / 174, 96 -> 16 162 / 178, 64 -> 64 alone 186 / 193; but 64 -> 128 333 / 315, 128 -> 64
-// 315 / 302, 96 -> 96 359 / 336, 96 -> 128 451 / 361, 128 -> 128 558 / 434 (200,000 rows 77 / 53); two layers 16 -> 64 -> 64 237 / 225, 64 -> 64 -> 64
-// 323 / 284 (200,000 rows 41 / 31) but 48 -> 48 -> 48 230 / 230; one layer backward 64 -> 64 327 / 300, 48 -> 48 226 / 226, 32 -> 32 151 / 156; two
-// layers backward 64 from 32 450 / 410, 48 from 48 387 / 389.  64 from 48 and 64 backward have no registers for it (spilled, 587 -> 616).
+// Where pieces are taken: where the matrix rate bounds a pass as much as memory does.  Elsewhere the work of splitting shows (us at
+// 2,000,000 rows, fp32 products / pieces): 32 -> 32 92 / 113, 48 -> 64 157 / 174, 96 -> 16 162 / 178, 64 -> 64 alone 186 / 193; but
+// 64 -> 128 333 / 315, 128 -> 64 315 / 302, 96 -> 96 359 / 336, 96 -> 128 451 / 361, 128 -> 128 558 / 434 (200,000 rows 77 / 53);
+// two layers 16 -> 64 -> 64 237 / 225, 64 -> 64 -> 64 323 / 284 (200,000 rows 41 / 31) but 48 -> 48 -> 48 230 / 230; one layer
+// backward 64 -> 64 327 / 300, 48 -> 48 226 / 226, 32 -> 32 151 / 156; two layers backward 64 from 32 450 / 410, 48 from 48 387 /
+// 389.  64 from 48 and 64 backward have no registers for it (spilled, 587 -> 616).
 constexpr bool split_piece(int kt, int nt) { return kt >= 4 && nt >= 4 && kt * nt > 16; }
 constexpr bool split_mlp(int mt) { return mt == 4; }
 constexpr bool split_back(int bt, int mt, int at, bool two) { return two ? mt == 4 && at <= 2 : bt * mt >= 12; }
 
-// acc += op(W) x for 16 rows, with W in LDS as `words` of 16 bytes.  SPLIT: in pieces, but for sixteen inputs, where six products take as long.
+// acc += op(W) x for 16 rows, with W in LDS as `words` of 16 bytes.  SPLIT: in pieces, but for sixteen inputs, where six products
+// take as long.
 constexpr std::true_type kInPieces{};
 constexpr std::false_type kAsTheyAre{};
 template <int KT, int NT, bool SPLIT> struct Product {
@@ -1010,10 +1015,10 @@ __global__ void __launch_bounds__(64 * kWaves, 2) back_kernel(BackArgs p)
 }
 
 // Bound by memory whatever the layout.  Arrays larger than the memory-side cache leave it as they are read (2,000,000 rows, 16 x 64
-// 114 -> 104 us, 128 x 16 194 -> 170, 32 x 32 91 -> 82; 300,000 rows, which fit, are 3-4 % slower so at 128 x 16, and left there for the next
-// kernel).  Only a side that one square reads: the others' reads come from L2 (128 x 32 215 -> 190 us, with both sides 222), and so
-// does the rest of a line of 128 bytes that two squares of 48 columns share (in a training step of 2,000,000 rows 96 x 16 192 us so, 172
-// kept).  Wider shapes lose (96 x 96 398 -> 483).
+// 114 -> 104 us, 128 x 16 194 -> 170, 32 x 32 91 -> 82; 300,000 rows, which fit, are 3-4 % slower so at 128 x 16, and left there
+// for the next kernel).  Only a side that one square reads: the others' reads come from L2 (128 x 32 215 -> 190 us, with both sides
+// 222), and so does the rest of a line of 128 bytes that two squares of 48 columns share (in a training step of 2,000,000 rows 96 x
+// 16 192 us so, 172 kept).  Wider shapes lose (96 x 96 398 -> 483).
 constexpr bool wgrad_light(int tg, int tx) { return tg * tx <= 8; }
 constexpr long kMemorySideCache = 256l << 20;
 
@@ -1029,21 +1034,19 @@ struct WgradArgs {
     long unchecked;     // rows before which a lane may read past the end of its row
 };
 
-// dW = G^T X: the rows are the k of the matrix instruction, four per instruction.  A lane reads T consecutive
-// columns of a row (T*(l%16) and on), which feed T tiles: tile t holds the columns T*i + t.  A wavefront
-// keeps up to 64 x 64 of dW in its accumulators and walks 16 rows a step; the rows of the next two steps are on their way
-// (requested right after the products that free their registers: no copies between two sets).
-// Weights wider than 64 are cut into two or four squares.  Long inputs: workgroups of eight wavefronts take all squares over the
-// same rows.  Short ones are in the caches, and what a workgroup leaves costs more than the second read of them: four
-// wavefronts to a square, fewer partial dW of fewer rows each.
-// Rows are dealt to 512 to 2048 wavefronts.  Those of a workgroup and square are added through LDS, and each workgroup leaves one
-// partial of its squares, summed by sum_partials_kernel in a fixed order.
-// Whole steps read without conditions.  Where a width is rounded up, lanes past the end of a row read the next
-// one's columns, whose sums nobody stores; the last rows, where that would pass the end of the array, and
-// steps of fewer rows take loads that check both.  Four-byte addresses do for loads of any width.
-// 2,000,000 rows, with the sums, beside conditions on every load and squares of 64 as workgroups of their own: 128 x 128 676 -> 581 us
-// (matrix cores 78 % busy at 2.0 GHz), 96 x 96 692 -> 389, 64 x 64 203 -> 182, 48 x 48 187 -> 139, 128 x 16 187 -> 170, 16 x 64 108 -> 104;
-// 32,768 rows: 128 x 128 23.9 -> 23.1, 64 x 128 18.0 -> 15.9, 96 x 96 22.7 -> 16.4.  torch's product of the transposed G takes 2900 at 64 x 64.
+// dW = G^T X: the rows are the k of the matrix instruction, four per instruction.  A lane reads T consecutive columns of a row
+// (T*(l%16) and on), which feed T tiles: tile t holds the columns T*i + t.  A wavefront keeps up to 64 x 64 of dW in its
+// accumulators and walks 16 rows a step; the rows of the next two steps are on their way (requested right after the products that
+// free their registers: no copies between two sets).  Weights wider than 64 are cut into two or four squares.  Long inputs:
+// workgroups of eight wavefronts take all squares over the same rows.  Short ones are in the caches, and what a workgroup leaves
+// costs more than the second read of them: four wavefronts to a square, fewer partial dW of fewer rows each.  Rows are dealt to 512
+// to 2048 wavefronts.  Those of a workgroup and square are added through LDS, and each workgroup leaves one partial of its squares,
+// summed by sum_partials_kernel in a fixed order.  Whole steps read without conditions.  Where a width is rounded up, lanes past the
+// end of a row read the next one's columns, whose sums nobody stores; the last rows, where that would pass the end of the array,
+// and steps of fewer rows take loads that check both.  Four-byte addresses do for loads of any width.  2,000,000 rows, with the sums,
+// beside conditions on every load and squares of 64 as workgroups of their own: 128 x 128 676 -> 581 us (matrix cores 78 % busy at
+// 2.0 GHz), 96 x 96 692 -> 389, 64 x 64 203 -> 182, 48 x 48 187 -> 139, 128 x 16 187 -> 170, 16 x 64 108 -> 104; 32,768 rows: 128 x
+// 128 23.9 -> 23.1, 64 x 128 18.0 -> 15.9, 96 x 96 22.7 -> 16.4.  torch's product of the transposed G takes 2900 at 64 x 64.
 template <int TG, int TX>
 __global__ void __launch_bounds__(2 * 64 * kWaves, 2) wgrad_kernel(WgradArgs p)
 {
@@ -1534,8 +1537,9 @@ int pcsr_gnn_wgrad(int64_t n, int32_t a, int32_t b, const float *G, const float 
     const int tg = wgrad_tiles(b), tx = wgrad_tiles(a);
     WgradArgs p;
     const int squares_g = wgrad_squares(b), squares_x = wgrad_squares(a), all = squares_g * squares_x;
-    // Squares as workgroups of their own, where dW is cut, up to 131,072 rows (us beside all squares in one: 128 x 128 32,768 rows 23.1 / 27.3,
-    // 65,536 31.8 / 35.4, 131,072 49.1 / 52.3; 64 x 128 15.9 / 20.1, 23.8 / 23.5 and 32.5 / 32.2; 300,000 rows, the old form, 112 / 101 and 62 / 55).
+    // Squares as workgroups of their own, where dW is cut, up to 131,072 rows (us beside all squares in one: 128 x 128 32,768 rows
+    // 23.1 / 27.3, 65,536 31.8 / 35.4, 131,072 49.1 / 52.3; 64 x 128 15.9 / 20.1, 23.8 / 23.5 and 32.5 / 32.2; 300,000 rows, the
+    // old form, 112 / 101 and 62 / 55).
     const bool apart = all == 1 || n <= (1 << 17);
     const int waves = apart ? kWaves : 2 * kWaves;
     const long most = kWgradBlocks / (apart ? all : 2);

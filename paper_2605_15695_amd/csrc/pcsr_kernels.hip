@@ -317,14 +317,14 @@ constexpr int kAsIs = 0;
 constexpr int kLongItems = 1; // balanced handles with long items (SpmmArgs::outer): sums of 32 vectors are added up apart
 constexpr int kEarlyTail = 2; // unsplit products whose tail reads the row: the self and mask rows are requested before the traversal
 // Single unsplit rows, a band of columns at a time (SpmmArgs::band), one launch each.  Scattered rows of B come from memory, at 57 G
-// lines of 128 bytes a second, unless an XCD's L2 holds them, which gives 190 G rows: the band of B that a launch reads is
-// as small as that, and the price is C read and written once more by each (uniform columns, 300,000 rows of 134, K = 16: 667 us in one, 542,
-// 437, 372, 366 and 446 in 2, 3, 4, 6 and 12).  Sums of 8 vectors are added up to 32 in up to
-// three bands, to 64 in more, before they go to the row's, which costs nothing: the rms difference from 64 bits of rows of 44, 60, 90, 134 and
-// 300 ones between 0 and 1 is 4.3 to 4.8e-8 of their sum (300: 4.8 to 5.8), 4.7 to 5.1 (5.8) by items of 32 and 5.0 to 7.1 in one sum.
-// A whole wavefront's chunk is 64 vectors: half of it at a time where sums are of 32 (rows of 60, K = 260 4.97 -> 4.19e-8, items of 32
-// 4.18; the time is the same).  Over 256 columns it has two tiles of them, in place of the plain kernel, whose sums
-// are of 64 there (rows of 60 11.0e-8, of 90 8.8, here 4.45; 1362 us and 1355, 1265 and 1325).
+// lines of 128 bytes a second, unless an XCD's L2 holds them, which gives 190 G rows: the band of B that a launch reads is as small
+// as that, and the price is C read and written once more by each (uniform columns, 300,000 rows of 134, K = 16: 667 us in one, 542,
+// 437, 372, 366 and 446 in 2, 3, 4, 6 and 12).  Sums of 8 vectors are added up to 32 in up to three bands, to 64 in more, before
+// they go to the row's, which costs nothing: the rms difference from 64 bits of rows of 44, 60, 90, 134 and 300 ones between 0 and
+// 1 is 4.3 to 4.8e-8 of their sum (300: 4.8 to 5.8), 4.7 to 5.1 (5.8) by items of 32 and 5.0 to 7.1 in one sum.  A whole wavefront's
+// chunk is 64 vectors: half of it at a time where sums are of 32 (rows of 60, K = 260 4.97 -> 4.19e-8, items of 32 4.18; the time
+// is the same).  Over 256 columns it has two tiles of them, in place of the plain kernel, whose sums are of 64 there (rows of 60
+// 11.0e-8, of 90 8.8, here 4.45; 1362 us and 1355, 1265 and 1325).
 constexpr int kBands = 3;
 // One dword a lane, its sums put together more often than the lanes' entries are, and those of 32 added up apart.  Up to 8 columns of
 // unsplit rows by 16 lanes (narrow_lanes says why), whose sums are of 4 vectors as those of 4 lanes with wider
@@ -465,11 +465,11 @@ spmm_kernel(SpmmArgs a)
         }
     }
 
-    // Sums of 32 or 64 vectors are added up here, as OUTER below has it; to what the bands before have left, requested beside the first
-    // entries.
-    // (Pairs are local more often than not, and bound by their instructions: none of it there.  20,000 rows of 70 in cliques, K = 16 9.3 and
-    // 9.8 us.)  Items of 8 lanes of a dword, up to 8 columns of balanced handles, have sums of 4, as the 4 lanes of wide loads had (R-MAT 2^16,
-    // K = 4: 3.55e-8 of the sum, of 8 3.74); odd widths never had those, and keep sums of 8 (30,000 rows of 45, K = 7: 4.45, of 4 4.70).
+    // Sums of 32 or 64 vectors are added up here, as OUTER below has it; to what the bands before have left, requested beside the
+    // first entries.  (Pairs are local more often than not, and bound by their instructions: none of it there.  20,000 rows of 70 in
+    // cliques, K = 16 9.3 and 9.8 us.)  Items of 8 lanes of a dword, up to 8 columns of balanced handles, have sums of 4, as the 4
+    // lanes of wide loads had (R-MAT 2^16, K = 4: 3.55e-8 of the sum, of 8 3.74); odd widths never had those, and keep sums of 8
+    // (30,000 rows of 45, K = 7: 4.45, of 4 4.70).
     constexpr bool FOURS = S && LPR == 8 && VEC == 1 && REP == 1;
     constexpr bool APART = FORM == kBands || (FORM == kNarrow && V == 1) || (FOURS && !OUTER);
     float apart[APART ? V : 1][APART ? REP : 1][VEC];
@@ -506,13 +506,13 @@ spmm_kernel(SpmmArgs a)
         }
     };
 
-    // OUTER, as the second pass adds the sums of items of 32 (64 where a whole wavefront takes an item, whose own sums are of 8).
-    // One running sum over a whole row loses more the longer the row.  Rms of the difference from 64 bits, relative to the sum
+    // OUTER, as the second pass adds the sums of items of 32 (64 where a whole wavefront takes an item, whose own sums are of
+    // 8).  One running sum over a whole row loses more the longer the row.  Rms of the difference from 64 bits, relative to the sum
     // of magnitudes, at K = 8, 32, 64, 256: rows of 300 6.1, 5.9, 6.7 and 6.0e-9 (11.0, 8.1, 7.5 and 8.5e-9 with one running sum,
-    // 6.1, 5.9, 6.7 and 6.7e-9 by items of 32), of 1000 4.4, 4.4, 4.7 and 3.9e-9 (9.8, 7.2, 5.8 and 7.4e-9; 4.5, 4.5, 4.8 and 4.8e-9).
-    // The time is the same within 1 % (250,000 rows of 48, K = 16 80 -> 82 us, 128 263, 512 1285).  In LDS, four floats or so per thread, which only that
-    // thread uses: four more registers would cost an instance a wavefront per SIMD, and so the slot's address is made anew
-    // each time, and the slot holds zeros at first.
+    // 6.1, 5.9, 6.7 and 6.7e-9 by items of 32), of 1000 4.4, 4.4, 4.7 and 3.9e-9 (9.8, 7.2, 5.8 and 7.4e-9; 4.5, 4.5, 4.8 and
+    // 4.8e-9).  The time is the same within 1 % (250,000 rows of 48, K = 16 80 -> 82 us, 128 263, 512 1285).  In LDS, four floats or
+    // so per thread, which only that thread uses: four more registers would cost an instance a wavefront per SIMD, and so the
+    // slot's address is made anew each time, and the slot holds zeros at first.
     extern __shared__ __align__(16) float lds[];
     const int wave_at = __builtin_amdgcn_readfirstlane(wave) * 64;
     auto outer = [&](auto use) {
@@ -1671,17 +1671,17 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
     const bool epi = args.epi.on && ls.ipg <= 1;
     // Unsplit items of less than a chunk.  4 and 8 lanes: 32-bit offsets save little beside the slots and lanes that have nothing to
     // load and now read all the same (time with them over without, rows of 3 to 14, the shapes that are taken unasked: 300,000 rows
-    // 0.97-1.05, 1,500,000 0.96-1.10 but for one 0.82; items of 16 to 24 0.96-1.05).  Paired items of one dword a lane, plain: B of 72 and 96 MB
-    // 1.00-1.11 with 10 and 14 vectors, 0.96-1.05 with 17 and 20; of 14 and 19 MB, which L2 holds, 0.93-0.96 at any length.  Single ones gain
-    // (8 to 18 vectors 0.84-1.00, uniform columns 0.98-1.00), and so do tails (pairs 0.87-1.03, mostly below 0.95) and wide loads of 16
-    // lanes and more (0.93-1.02).
+    // 0.97-1.05, 1,500,000 0.96-1.10 but for one 0.82; items of 16 to 24 0.96-1.05).  Paired items of one dword a lane, plain: B of
+    // 72 and 96 MB 1.00-1.11 with 10 and 14 vectors, 0.96-1.05 with 17 and 20; of 14 and 19 MB, which L2 holds, 0.93-0.96 at any
+    // length.  Single ones gain (8 to 18 vectors 0.84-1.00, uniform columns 0.98-1.00), and so do tails (pairs 0.87-1.03, mostly
+    // below 0.95) and wide loads of 16 lanes and more (0.93-1.02).
     const bool past_l2 = (double)args.n_cols * args.K * 4.0 > 32.0 * 1048576.0;
     const bool short_items = !S && args.mean_item < 16 && (ls.k_lpr < 16 || (V == 2 && ls.k_vec == 1 && !epi && past_l2));
     const bool near = near_enough(args) && !short_items;
     // Plain products in these shapes at any width: pcsr_select gives them to handles that had sums of 4 to 8 vectors in wide loads
     // (20,000 rows of 22, a handle for K = 8 at K = 64: rms 4.7e-8 of the sum, 5.6 in sums of 16, 4.7 now), and the additions show
-    // nowhere (K = 9 to 16, rows of 9 to 80: 0.99-1.02 of the time).  But pairs of 9 to 16 columns have sums of 16, as they had, and so have
-    // tails, which come in auto shapes and ask for their rows early.
+    // nowhere (K = 9 to 16, rows of 9 to 80: 0.99-1.02 of the time).  But pairs of 9 to 16 columns have sums of 16, as they had, and
+    // so have tails, which come in auto shapes and ask for their rows early.
     const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 && ((!epi && V == 1) || args.K <= 8 || args.K > 16) &&
                         ((ls.k_lpr == 16 && ls.k_rep == 1) ||
                          (V == 1 && ls.k_lpr >= 16 && ls.k_lpr <= 32 && ls.k_rep <= 2 && ls.k_lpr * ls.k_rep >= 32));
