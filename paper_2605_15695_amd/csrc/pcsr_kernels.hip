@@ -467,9 +467,9 @@ spmm_kernel(SpmmArgs a)
 
     // Sums of 32 or 64 vectors are added up here, as OUTER below has it; to what the bands before have left, requested beside the
     // first entries.  (Pairs are local more often than not, and bound by their instructions: none of it there.  20,000 rows of 70 in
-    // cliques, K = 16 9.3 and 9.8 us.)  Items of 8 lanes of a dword, up to 8 columns of balanced handles, have sums of 4, as the 4
-    // lanes of wide loads had (R-MAT 2^16, K = 4: 3.55e-8 of the sum, of 8 3.74); odd widths never had those, and keep sums of 8
-    // (30,000 rows of 45, K = 7: 4.45, of 4 4.70).
+    // cliques, K = 16 9.3 and 9.8 us.)  Items of 8 lanes of a dword, up to 8 columns of balanced handles, have sums of 4 where items
+    // are short, as the 4 lanes of wide loads had (R-MAT 2^16, K = 4: 3.55e-8 of the sum, of 8 3.74), of 8 where they are of 22 and more
+    // on average (30,000 rows of 45 in items of 32: 4.35, of 4 4.65) and at odd widths, which never had 4.
     constexpr bool FOURS = S && LPR == 8 && VEC == 1 && REP == 1;
     constexpr bool APART = FORM == kBands || (FORM == kNarrow && V == 1) || (FOURS && !OUTER);
     float apart[APART ? V : 1][APART ? REP : 1][VEC];
@@ -593,8 +593,9 @@ spmm_kernel(SpmmArgs a)
         // memory: the additions cost nothing (250,000 rows, K = 128 262 us, K = 256 577, both as before).
         constexpr bool FOLD = (S && LPR >= 32) || FORM == kBands || FORM == kNarrow;
         static_assert(!FOURS || U == 8);
-        const bool even = FOURS && a.K % 2 == 0;
-        const bool fours = FORM == kNarrow && LPR == 16 && REP == 1 && a.mean_item < 22; // (wider groups: of 8, as 8 lanes' chunks)
+        const bool even = FOURS && a.K % 2 == 0 && a.mean_item < 22;
+        // (Wider groups past the widths they are for: of 8, as 8 lanes' chunks.)
+        const bool fours = FORM == kNarrow && REP == 1 && a.mean_item < 22 && (LPR == 16 || (a.K > 16 && a.K <= 32));
         auto fold = [&] {
 #pragma unroll
             for (int v = 0; v < V; ++v)
@@ -1680,9 +1681,11 @@ hipError_t launch_spmm(int V, int S, const LaunchShape &ls, const SpmmArgs &args
     const bool near = near_enough(args) && !short_items;
     // Plain products in these shapes at any width: pcsr_select gives them to handles that had sums of 4 to 8 vectors in wide loads
     // (20,000 rows of 22, a handle for K = 8 at K = 64: rms 4.7e-8 of the sum, 5.6 in sums of 16, 4.7 now), and the additions show
-    // nowhere (K = 9 to 16, rows of 9 to 80: 0.99-1.02 of the time).  But pairs of 9 to 16 columns have sums of 16, as they had, and
-    // so have tails, which come in auto shapes and ask for their rows early.
-    const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 && ((!epi && V == 1) || args.K <= 8 || args.K > 16) &&
+    // nowhere (K = 9 to 16, rows of 9 to 80: 0.99-1.02 of the time).  But pairs of over 8 columns have sums of 16 as before, where they are
+    // of 22 and more on average (100,000 rows of 80 in cliques 5.4, of 8 6.3) or of 9 to 16 columns, and so have tails of 9 to 16, which come
+    // in auto shapes and ask for their rows early.
+    const bool at_width = V == 1 ? !epi || args.K <= 8 || args.K > 16 : args.K <= 8 || (args.K > 16 && args.mean_item < 22);
+    const bool narrow = !S && ls.k_vec == 1 && ls.ipg <= 1 && at_width &&
                         ((ls.k_lpr == 16 && ls.k_rep == 1) ||
                          (V == 1 && ls.k_lpr >= 16 && ls.k_lpr <= 32 && ls.k_rep <= 2 && ls.k_lpr * ls.k_rep >= 32));
     KernelFn fn;

@@ -163,3 +163,19 @@ def test_operators_run_scattered_rows_of_a_middling_b_in_wide_loads():
     op = PcsrOperator(n, n, np.arange(0, 50 * n + 1, 50, dtype=np.int32), near.ravel().astype(np.int32),
                       rng.standard_normal(50 * n).astype(np.float32), symmetric=True, K_hint=64)
     assert kernel(op, 64) == kernel(op, 40) == (32, 1, 2)    # local columns
+
+
+# Rows of 9 to 17, which have sums of 4 at the widths that the shapes are for; items of 32 of long ones, which have sums of 8; pairs of long rows at
+# widths that their shape is not for, which have sums of 16 vectors
+@pytest.mark.parametrize("lengths,own,like,widths", [
+    ((9, 18), dict(lanes_per_row=32, vec=1, rep=1), dict(lanes_per_row=4, vec=4, rep=1), (20, 24, 32)),
+    ((44, 65), dict(S=1, SG=32, lanes_per_row=8, vec=1, rep=1), dict(S=1, SG=32, lanes_per_row=8, vec=4, rep=1), (4, 8)),
+    ((60, 100), dict(V=2, lanes_per_row=16, vec=1, rep=1), dict(V=2, lanes_per_row=16, vec=4, rep=1), (12, 24, 64)),
+])
+def test_sums_are_as_long_as_rows_want_them(lengths, own, like, widths):
+    rng = np.random.default_rng(lengths[0])
+    n, n_cols = 16000, 20000
+    rowptr, colidx, vals = _rows(rng, rng.integers(*lengths, n), n_cols)
+    for K in widths:
+        a, b = _rms(rowptr, colidx, np.abs(vals), n_cols, K, [own, like], K)
+        assert a < 1.03 * b, (K, a, b)
