@@ -1338,12 +1338,13 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     const double n = f[0];
     const bool scattered = scattered_columns(f); // (see below)
     // Up to 8 the same (narrow_lanes); of scattered rows from 8 on, which wait on memory (1,000,000 rows of 9, K = 8: 160 -> 150
-    // us).  Odd widths had one dword a lane before: local rows of 15 0.95-1.05, one column of 9 to 21 a row 1.16-1.30.  Up to five
-    // columns of under 12 that L2 holds but L1 does not: their wide loads are faster (300,000 rows of 8.5, K = 2 17.5 us and 20.9,
-    // K = 3 20.7 and 22.6, K = 5 25.8 and 26.7; 1.02-1.20 from 1.7 MB, 1.1 of three columns, up to 5, 6.5 of five, 0.94-1.01 from
-    // there on; rows of 10 0.97-1.09, of 12 0.84-1.02; four columns 1.03-1.04, but 0.99 with 9 a row).
+    // us).  Odd widths had one dword a lane before: local rows of 15 0.95-1.05, one column of 9 to 21 a row 1.16-1.30.
+    // Two to four columns of under 12 that L2 holds but L1 does not: their wide loads are faster (300,000 rows of 8.5, K = 2 17.5 us
+    // and 20.9, K = 3 20.7 and 22.6; 1.02-1.20 from 1.7 MB, 1.1 of three columns, up to 5, 0.94-1.01 from there on; rows of 10
+    // 0.97-1.09, of 12 0.84-1.02; four columns 1.03-1.04, but 0.99 with 9 a row).  Five 1.02-1.10, but a dword in 8 lanes has sums of
+    // 8 there: rms 4.44e-8 of the sum for 4.04.
     const double b_few = n * (double)K * 4.0;
-    const bool few = K >= 2 && K <= 5 && b_few > (K == 3 ? 1.1e6 : 1.7e6) && b_few < (K == 5 ? 6.5e6 : 5e6);
+    const bool few = K >= 2 && K <= 4 && b_few > (K == 3 ? 1.1e6 : 1.7e6) && b_few < 5e6;
     const double least_few = !few ? 8.0 : K == 4 ? 8.8 : 11.5;
     const double least_narrow = K == 1 ? 32.0 : scattered && !skewed ? least_few : K % 2 ? 20.0 : 16.0;
     const bool narrow = K <= 8 && d_hat >= least_narrow && !(skewed && K % 2);

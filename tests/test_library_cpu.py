@@ -633,6 +633,6 @@ def test_few_columns_of_short_scattered_rows():
         assert shape(n, deg, 2) == (4, 2, 1) and shape(n, deg, 3) == (4, 1, 1)
         assert shape(n, deg, 6) == shape(n, deg, 8) == (16, 1, 1)
         assert shape(n, deg, 4) == ((16, 1, 1) if deg >= 9 or n > 312_500 else (4, 4, 1))
-        assert shape(n, deg, 5) == ((16, 1, 1) if n > 325_000 else (8, 1, 1))
+        assert shape(n, deg, 5) == (16, 1, 1)
     for n, deg in ((1_000_000, 9), (300_000, 12), (60_000, 9)):
         assert shape(n, deg, 2) == shape(n, deg, 3) == shape(n, deg, 4) == shape(n, deg, 5) == (16, 1, 1)
