@@ -934,10 +934,12 @@ static int64_t workspace_need(pcsr_handle_t h, int32_t K)
 }
 
 // Bytes that the operands have to be aligned to: those of the load width that the parameters mean, not of what is launched
-// (whose loads are at 4-byte addresses anyway).  An order that the build found does not ask for more.
+// (whose loads are at 4-byte addresses anyway).  An order that the build found does not ask for more, nor do auto shapes in place of
+// the handle's own.
 static uintptr_t operand_align(pcsr_handle_t h, const pcsr::LaunchShape &ls)
 {
-    return 4u * (unsigned)(h->asked_vec ? std::min(h->asked_vec, ls.vec) : ls.vec);
+    const int asked = h->asked_vec ? h->asked_vec : h->flags & kAutoNarrow ? h->vec : 0;
+    return 4u * (unsigned)(asked ? std::min(asked, ls.vec) : ls.vec);
 }
 
 // Checks shared by the SpMM entry points; resolves the launch shape.
@@ -1538,7 +1540,9 @@ int pcsr_select(const double *f, int32_t K, pcsr_params_t *out)
     // Rows that are not split for K = 64 and more: few columns of them are best left to the library (150,000 rows of 60, a handle
     // for K = 64: K = 4, 8, 16 and 24 146, 144, 170 and 187 us in its shape, 91, 91, 99 and 168 when its rows were split, 50, 60,
     // 77 and 127 in auto shapes).
-    const bool auto_narrow = long_uniform && K >= 64 && !p.S && p.V == 1;
+    // So are those of rows of 8 to 40 whose shape only stands in (20,000 rows of 22, a handle for K = 128, K = 16 11.0 us in halves of
+    // two floats, 7.6 in 16 lanes of 16 bytes, 6.6 in auto shapes).
+    const bool auto_narrow = quads || (long_uniform && K >= 64 && !p.S && p.V == 1);
     if (auto_narrow) p.flags |= kAutoNarrow | stands_for(lpr, vec, rep);
     if (wide) {
         int code = 1;
