@@ -247,6 +247,10 @@ void window_tail(pcsr_handle_t h, pcsr::LaunchShape *ls)
     ls->k_grid_y = 1;
 }
 
+// Auto shapes' slices of rows of over 64 columns are in parts of 20 and more, as the tiles of whole rows were that they have taken the
+// place of (100,000 rows of 60, K = 128: rms 4.66e-8 of the sum in 6 bands, 4.38 in 3; 296 us and 315, 373 in those tiles).
+constexpr double kSlicedPart = 20.0;
+
 // How many bands of columns a product of scattered rows is best walked in (a divisor of kColumnBands), and the us that they save.  A
 // band of B that an XCD's L2 holds is gathered from there; each band of several costs a launch, a look at every row and a pass over
 // C.  The rates are those that fit 1,200 measured times best (uniform columns, 14 to 300 a row, 40,000 to 1,000,000 rows, 6 to 256
@@ -254,7 +258,8 @@ void window_tail(pcsr_handle_t h, pcsr::LaunchShape *ls)
 // one band.  Us in one band and in those picked: rows of 134, 300,000 of them, K = 16 667 and 366 (6 bands), K = 32 706 and 527 (6),
 // K = 64 1459 and 1197 (6); of 60, 150,000, K = 16 118 and 76 (3), K = 48 291 and 211 (6); of 60, 400,000, K = 10 462 and 235 (4),
 // K = 64 908 in one; of 30, 400,000, K = 9 202 and 145 (3), K = 16 193 in one; of 300, 100,000, K = 32 385 and 224 (4).
-int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, int32_t tile, double *saved)
+// least_part: vectors of a row in a band, at least.
+int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, int32_t tile, double *saved, double least_part = 0.0)
 {
     const double slices = (K + tile - 1) / tile, row = 4.0 * K / slices;
     const double grain = (double)std::min(128, (4 * K) & -(4 * K)); // rows of B begin at multiples of it
@@ -267,7 +272,7 @@ int band_count(double n_rows, double n_cols, double nnz, int32_t K, int lanes, i
     int best = 1;
     // Rows of less than 256 are better added up in fewer than 12 parts, and in tiles of whole rows by whole and half wavefronts, whose
     // sums were of 8 before, in parts of 20 and more.
-    const double least = tile >= 128 || (K > 64 && K % 32 != 0) ? 20.0 : 0.0;
+    const double least = tile >= 128 || (K > 64 && K % 32 != 0) ? 20.0 : least_part;
     for (const int m : {2, 3, 4, 6, 12})
         if (nnz >= std::max(m < 12 ? 0.0 : 256.0, least * m) * n_rows && us(m) < (best > 1 ? 0.98 : 1.0) * us(best)) best = m;
     *saved = us(1) - us(best);
@@ -330,7 +335,8 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     // multiple of 128 bytes long have lines that two slices would read: K = 200 993, 951 and 1018, K = 300 1739, 1531 and 1605.
     double saved;
     const bool sliced = !h_vec && !h_lpr && !h_rep && h->d_bands && h->ipg <= 1 && K > 64 && K % 32 == 0;
-    const bool in_bands = sliced && band_count((double)h->host.n_rows, (double)h->host.n_cols, (double)h->host.nnz, K, 16, 64, &saved) > 1;
+    const bool in_bands =
+        sliced && band_count((double)h->host.n_rows, (double)h->host.n_cols, (double)h->host.nnz, K, 16, 64, &saved, kSlicedPart) > 1;
     if (narrow || dwords) vec = 1;
     if (sliced) vec = in_bands ? 4 : 2;
     if (K % vec != 0) return PCSR_E_UNSUPPORTED;
@@ -991,7 +997,7 @@ static int band_passes(pcsr_handle_t h, int32_t K, const pcsr::LaunchShape &ls, 
     if (ls.window || ls.ipg > 1 || !pcsr::band_kernel_exists(ls.k_lpr, ls.k_vec, ls.k_rep, epi.on)) return 0;
     if (slices_share_columns(K, ls) || tail_reads_c(epi, C, h->host.n_rows, K)) return 1;
     return band_count((double)h->host.n_rows, (double)h->host.n_cols, (double)h->host.nnz, K, ls.k_lpr, ls.k_lpr * ls.k_vec * ls.k_rep,
-                      &saved);
+                      &saved, !(h->lpr || h->vec || h->rep) && K > 64 ? kSlicedPart : 0.0);
 }
 
 // Enqueues the kernels of one SpMM.  ws: workspace of at least workspace_need(h, K) bytes
