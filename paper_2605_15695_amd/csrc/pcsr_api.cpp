@@ -250,6 +250,7 @@ void window_tail(pcsr_handle_t h, pcsr::LaunchShape *ls)
 // Auto shapes' slices of rows of over 64 columns are in parts of 20 and more, as the tiles of whole rows were that they have taken the
 // place of (100,000 rows of 60, K = 128: rms 4.66e-8 of the sum in 6 bands, 4.38 in 3; 296 us and 315, 373 in those tiles).
 constexpr double kSlicedPart = 20.0;
+constexpr int32_t kSlicedMost = 1 << 20; // (more slices than a grid has otherwise)
 
 // How many bands of columns a product of scattered rows is best walked in (a divisor of kColumnBands), and the us that they save.  A
 // band of B that an XCD's L2 holds is gathered from there; each band of several costs a launch, a look at every row and a pass over
@@ -334,7 +335,7 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
     // of 134, 300,000, K = 256 4755, 5756 and 5096; of 44, 500,000 (one band), K = 256 2983, 3077 and 3637.  Rows that are no
     // multiple of 128 bytes long have lines that two slices would read: K = 200 993, 951 and 1018, K = 300 1739, 1531 and 1605.
     double saved;
-    const bool sliced = !h_vec && !h_lpr && !h_rep && h->d_bands && h->ipg <= 1 && K > 64 && K % 32 == 0;
+    const bool sliced = !h_vec && !h_lpr && !h_rep && h->d_bands && h->ipg <= 1 && K > 64 && K % 32 == 0 && K <= kSlicedMost;
     const bool in_bands =
         sliced && band_count((double)h->host.n_rows, (double)h->host.n_cols, (double)h->host.nnz, K, 16, 64, &saved, kSlicedPart) > 1;
     if (narrow || dwords) vec = 1;

@@ -69,6 +69,7 @@ for K in (64, 96, 128, 256, 512, 1024):
     assert pc.pcsr_query_launch(h, K) == pc.pcsr_query_kernel(h, K)
 for K, s in ((72, (32, 4, 1, 1)), (200, (64, 4, 1, 1)), (260, (64, 4, 2, 1)), (515, (64, 4, 2, 2)), (1000, (64, 4, 2, 2))):
     assert shape(K) == s, K
+assert shape(1 << 20)[2:] == (1, 1 << 14) and shape(8_000_000) == (64, 4, 2, 15625)  # as wide as a grid takes
 h.close()
 """)
 
