@@ -331,9 +331,10 @@ int resolve_launch(pcsr_handle_t h, int32_t K, pcsr::LaunchShape *ls, bool epilo
                         h->host.nnz_v >= 32 * std::max<int64_t>(h->host.P, 1);
     // Rows of over 64 columns of a handle with bands go in slices, as pcsr_select has them: of 64 columns in 16 lanes where there
     // are several bands, else half a wavefront to 64 columns.  Us of such slices, of a tile of the whole row and of items of 32 in
-    // column order: rows of 90, 100,000 of them, K = 128 346, 469 and 446, K = 256 675, 1182 and 889, K = 512 1411, 2469 and 1779;
-    // of 134, 300,000, K = 256 4755, 5756 and 5096; of 44, 500,000 (one band), K = 256 2983, 3077 and 3637.  Rows that are no
-    // multiple of 128 bytes long have lines that two slices would read: K = 200 993, 951 and 1018, K = 300 1739, 1531 and 1605.
+    // column order: rows of 90, 100,000 of them, K = 128 392, 471 and 483, K = 256 775, 1182 and 965, K = 512 1549, 2512 and 1941;
+    // of 134, 300,000, K = 256 4781, 5774 and 5356; of 44, 500,000 (one band), K = 256 3028, 3113 and 3796.  Rows that are no
+    // multiple of 128 bytes long have lines that two slices would read: in such a tile K = 200 959, and 1065 in items, K = 300 1544 and
+    // 1667 (in slices, of another session, 1.04 and 1.14 of the tile).
     double saved;
     const bool sliced = !h_vec && !h_lpr && !h_rep && h->d_bands && h->ipg <= 1 && K > 64 && K % 32 == 0 && K <= kSlicedMost;
     const bool in_bands =
